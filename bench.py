@@ -30,26 +30,9 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 
-# HBM bytes per launch in the cold steps of workloads 4 and 5, from rocprofv3 --pmc FETCH_SIZE and
-# WRITE_SIZE (profiles/bench_config4_hbm_traffic.txt, profiles/bench_config5_hbm_traffic.txt; fetch
-# scaled x2.000, write x1.000 by the counters of a 512 MiB device copy).  They describe the kernels
-# whose source hashes to TRAFFIC_SOURCE_SHA256; with any other kernel source, or any other workload,
-# the field is reported as null.
-TRAFFIC_BYTES = {
-    4: {"lookup": 0.17e6, "class_scan": 6.29e6, "key_build": 15.64e6, "gather": 0.04e6, "apply": 57.06e6, "advance": 0.21e6},
-    5: {"lookup": 0.44e6, "class_scan": 26.85e6, "key_build": 34.19e6, "gather": 14.15e6, "apply": 314.61e6, "advance": 0.75e6},
-}
-TRAFFIC_SOURCE_SHA256 = "c1d8daad70d0835bc464156a5d396d9bf041c0cb349521bf7c01c30c35672916"
 WINDOW_START = 64              # first timed step of the trajectory (the warm-up steps come right before it)
 N_PASSES = 5                   # timed passes per figure; the median is reported
 RAMP_SECONDS = 0.08            # GPU work done before timing, for the clocks to settle
-
-
-def kernel_source_sha256():
-    import hashlib
-    path = os.path.join(ROOT, "paper_2507_16768_amd", "csrc", "wg_kernels.hip")
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
 
 
 def _oracle_steps(w, lo, hi, n_steps):
@@ -336,7 +319,7 @@ def main():
         p = h.profile_read()
         h.profile_enable(False)
         return {k[:-3] + "_us": 1e3 * p[k] / K
-                for k in ("lookup_ms", "scan_ms", "build_ms", "gather_ms", "advance_ms", "apply_ms")}
+                for k in ("lookup_ms", "build_ms", "advance_ms", "apply_ms")}
 
     # ---- the whole step in one call: advance + fill + apply ----
     def single_step(cold, k):
@@ -357,7 +340,7 @@ def main():
         return passes(lambda: single_rewind(cold), lambda k: single_step(cold, k))
 
     def decode_kernel_times(cold):
-        """Per-kernel durations of wg_decode_step: its first kernel counts as lookup, its last as gather."""
+        """Per-kernel durations of wg_decode_step: its first kernel counts as lookup, its second as build."""
         ramp(lambda: single_rewind(cold), lambda k: single_step(cold, k))
         single_rewind(cold)
         torch.cuda.synchronize()
@@ -368,8 +351,7 @@ def main():
         torch.cuda.synchronize()
         p = h.profile_read()
         h.profile_enable(False)
-        return {"advance_lookup_us": 1e3 * p["lookup_ms"] / K, "scan_us": 1e3 * p["scan_ms"] / K,
-                "build_us": 1e3 * p["build_ms"] / K, "gather_apply_us": 1e3 * p["gather_ms"] / K}
+        return {"advance_lookup_us": 1e3 * p["lookup_ms"] / K, "rows_apply_us": 1e3 * p["build_ms"] / K}
 
     # ---- spread of the step time: one event per step boundary (their cost is inside the figures) ----
     def step_spread(cold):
@@ -591,35 +573,29 @@ def main():
     # dense work it avoids ----
     sum_len = int(w.vocab.offsets[-1])
     row_bytes = V / 8.0
-    n_class_rows = 3.0                                        # stay, end and their union
-    scan_bytes_per_class = sum_len + V + n_class_rows * row_bytes      # token bytes + a length byte per token + the rows written
-    key_bytes_per_key = 3 * row_bytes                           # one class row in, the row out twice (cache and bitmask)
     entry_bytes = 8.0
-    gather_rows = B - builds_per_step                           # rows the gather copies (a claimer's row is written by key_build)
-    gather_bytes_cold = gather_rows * 2 * row_bytes
-    gather_bytes_warm = B * 2 * row_bytes
+    # a row that is made goes out twice (cache and bitmask), any other is read and written once; a class
+    # table taken up reads at least the row of its tokens with bytes and keeps two rows
+    rows_bytes_cold = B * 2 * row_bytes + entries_per_step * entry_bytes + scans_per_step * 3 * row_bytes
+    rows_bytes_warm = B * 2 * row_bytes
     apply_dense_bytes = B * (row_bytes + 2 * esz * V)
     apply_min_bytes = B * row_bytes + esz * disallowed_per_step      # mask in, -inf out, nothing else
     state_bytes = B * (8 + 4 + 8)                               # state in and out, token in
     alg = {
         "lookup": (B * 16.0, kt_cold["lookup_us"]),
-        "class_scan": (scans_per_step * scan_bytes_per_class, kt_cold["scan_us"]),
-        "key_build": (builds_per_step * key_bytes_per_key + entries_per_step * entry_bytes, kt_cold["build_us"]),
-        "gather": (gather_bytes_cold, kt_cold["gather_us"]),
+        "rows": (rows_bytes_cold, kt_cold["build_us"]),
         "apply": (apply_min_bytes, kt_cold["apply_us"]),
         "advance": (state_bytes + B * (sum_len / float(V)), kt_cold["advance_us"]),
     }
-    traffic_ok = kernel_source_sha256() == TRAFFIC_SOURCE_SHA256
     kernels = []
     for name, (nbytes, us) in alg.items():
         gbs = nbytes / (us * 1e-6) / 1e9 if us > 0 else 0.0
         kernels.append({"kernel": name, "algorithmic_bytes_per_launch": nbytes, "us_per_launch": us,
                         "achieved_GBs": gbs, "frac": gbs / HBM_PEAK_GBS,
-                        "traffic": TRAFFIC_BYTES.get(w.index, {}).get(name) if traffic_ok else None,
-                        "bound": "hbm" if name in ("class_scan", "key_build", "gather", "apply") else "latency"})
+                        "bound": "hbm" if name in ("rows", "apply") else "latency"})
     dominant = max((k for k in kernels if k["bound"] == "hbm"), key=lambda k: k["us_per_launch"])
     method_bytes_cold = sum(v[0] for v in alg.values())
-    method_bytes_warm = alg["lookup"][0] + gather_bytes_warm + apply_min_bytes + alg["advance"][0]
+    method_bytes_warm = alg["lookup"][0] + rows_bytes_warm + apply_min_bytes + alg["advance"][0]
     # the same step in the accounting the throughput target is stated in: one streamed pass over the
     # vocabulary per built key, the gather, and a dense read-modify-write of the logits.  The kernels
     # move none of these bytes; the figure says what a scan-per-key design would have to sustain.
@@ -643,7 +619,6 @@ def main():
                    "logits_dtype": w.dtype},
         "roofline": {"kernel": dominant["kernel"], "bound": "hbm", "achieved": dominant["achieved_GBs"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dominant["frac"],
-                     "traffic": dominant["traffic"],
                      "algorithmic_bytes_per_launch": dominant["algorithmic_bytes_per_launch"],
                      "us_per_launch": dominant["us_per_launch"],
                      "kernels": kernels,
@@ -651,11 +626,6 @@ def main():
         "cold": {"ms_per_step_passes": [s * 1e3 for s in cold_passes],
                  "keys_built_per_step": builds_per_step, "class_scans_per_step": scans_per_step,
                  "exit_entries_per_step": entries_per_step,
-                 # token bytes taken through a checkpoint's byte table per second: by the class scan
-                 # (every token once per scanned table, over the scan's own time), and what a walk of
-                 # the whole vocabulary per built key would have to sustain at this step time
-                 "byte_steps_per_s": {"class_scan": scans_per_step * sum_len / (kt_cold["scan_us"] * 1e-6) if kt_cold["scan_us"] > 0 else None,
-                                      "scan_per_key_dense_equivalent": builds_per_step * sum_len / sec_cold},
                  "method_bytes_per_step": method_bytes_cold,
                  "step_frac_method_bytes": method_bytes_cold / sec_cold / 1e9 / HBM_PEAK_GBS,
                  "dense_equivalent_GBs": dense_cold / sec_cold / 1e9,
@@ -668,7 +638,7 @@ def main():
                  "dense_equivalent_GBs": dense_warm / sec_warm / 1e9,
                  "frac_of_hbm_peak_dense_equivalent": dense_warm / sec_warm / 1e9 / HBM_PEAK_GBS},
         "kernels_us_per_step": {"cold": kt_cold, "warm": kt_warm},
-        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, four launches)",
+        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, two launches)",
                              "cold_ms_per_step": sec_single_cold * 1e3, "warm_ms_per_step": sec_single_warm * 1e3,
                              "cold_request_steps_per_s": B / sec_single_cold,
                              "warm_request_steps_per_s": B / sec_single_warm,

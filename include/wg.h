@@ -102,12 +102,12 @@ typedef struct {
     uint64_t hits;          /* ... whose mask was already cached */
     uint64_t builds;        /* mask rows built (one per distinct missing key) */
     uint64_t uncached_builds;/* ... of which could not be kept because every cache row was taken */
-    uint64_t class_scans;   /* vocabulary scans (one per distinct missing allow/wait class table) */
-    uint64_t entries_walked;/* candidate tokens examined by the row builds (index ranges and class lists) */
+    uint64_t class_scans;   /* allow / wait class tables taken up (one per distinct table and cache generation) */
+    uint64_t entries_walked;/* candidate tokens examined by the row builds (ranges of the vocabulary's indexes) */
     uint64_t keys;          /* distinct masks the compiled instances can ask for (instances of one shape share theirs) */
     uint64_t cache_rows;    /* rows the cache can hold (wg_cache_resize) */
     uint64_t rows_in_use;   /* rows holding a mask since the last clear */
-    uint64_t arena_bytes;   /* device bytes reserved for cached rows and class indexes */
+    uint64_t arena_bytes;   /* device bytes reserved for cached rows and the class tables' rows */
 } wg_cache_stats_t;
 
 /* State kinds reported by wg_table_state. */
@@ -221,12 +221,8 @@ int wg_cache_resize(wg_handle_t h, uint32_t rows);
 int wg_reserve_batch(wg_handle_t h, uint32_t max_batch);
 uint32_t wg_max_batch(wg_handle_t h);       /* the current reservation */
 
-/* wg_set_scan_batch: how many of the class tables a call has to index (the context-free part of
- * the masks, "Mask Generation and Global Caching": a mask depends on the allow / wait sets only)
- * one workgroup takes through its share of the vocabulary together: 1 .. 8, or 0 (what wg_compile
- * sets) to let each call choose -- one table while the call brings few, more as it brings many,
- * and always one for a handle with few class tables.  A tuning knob: every setting gives the same
- * masks.  Takes effect with the next call; a HIP graph recorded before keeps the old setting. */
+/* wg_set_scan_batch: 0 .. 8, anything else gives WG_ERR_INVALID.  Has no effect: masks are made from the
+ * vocabulary's static indexes without a scan of class tables, so there is nothing to batch. */
 int wg_set_scan_batch(wg_handle_t h, uint32_t tables);
 
 uint32_t wg_num_states(wg_handle_t h);
@@ -326,10 +322,9 @@ int wg_advance_fill_masks(wg_handle_t h, wg_state_t *d_states, const int32_t *d_
  * advanced by the tokens sampled in the step before (d_tokens == NULL skips this: first step),
  * the masks of the new states are produced into d_bitmask as by wg_fill_masks and applied to
  * d_logits ([B][V] with V of the handle's vocabulary, layout as in wg_apply_mask) as by
- * wg_apply_mask.  Same results as wg_advance + wg_fill_masks + wg_apply_mask in four kernel
- * launches instead of six: the advance rides in the lookup kernel and the masking in the gather
- * kernel (rows whose address or stride rules out 16-byte stores are masked by the separate
- * apply kernels instead).  In wg_profile_read the combined kernels count as lookup and gather. */
+ * wg_apply_mask.  Same results as wg_advance + wg_fill_masks + wg_apply_mask in two kernel
+ * launches instead of four: the advance rides in the lookup kernel and the masking in the kernel
+ * that makes the rows.  In wg_profile_read the combined kernels count as lookup and build. */
 int wg_decode_step(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t B,
                    uint32_t *d_bitmask, void *d_logits, wg_dtype_t dtype, int64_t row_stride_elems,
                    void *stream);
@@ -354,7 +349,8 @@ const char *wg_last_error(void);
  * synchronises, adds up the elapsed times since the last read and resets the record. */
 typedef struct {
     uint64_t fill_calls, advance_calls;
-    double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations */
+    double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations (a fill has a
+                                                                     lookup and a build kernel; scan and gather stay 0) */
     uint64_t apply_calls;
     double apply_ms;
 } wg_profile_t;

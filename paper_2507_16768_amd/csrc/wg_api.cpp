@@ -25,18 +25,16 @@ struct wg_table_s {
 
 struct wg_vocab_s {
     DeviceVocab dv{};
-    uint8_t *d_bytes = nullptr, *d_len8 = nullptr;
-    uint32_t *d_offsets = nullptr, *d_lit_start = nullptr, *d_len_rows = nullptr;
-    uint64_t *d_chunks = nullptr, *d_sig = nullptr;
-    uint8_t *d_first8 = nullptr;
-    ExitEntry *d_lit_entries = nullptr, *d_sorted = nullptr, *d_bigram = nullptr;
-    uint32_t *d_dir0 = nullptr, *d_dirN = nullptr, *d_byte_rows = nullptr;
+    uint8_t *d_len8 = nullptr;
+    uint32_t *d_lit_start = nullptr, *d_place_start = nullptr, *d_len_rows = nullptr;
+    uint64_t *d_chunks = nullptr;
+    ExitEntry *d_index = nullptr;
+    uint32_t *d_dir0 = nullptr, *d_dirN = nullptr, *d_rows = nullptr;
     int device = 0;
     void release() {
-        (void)hipFree(d_bytes); (void)hipFree(d_len8); (void)hipFree(d_offsets);
-        (void)hipFree(d_lit_start); (void)hipFree(d_len_rows); (void)hipFree(d_chunks);
-        (void)hipFree(d_lit_entries); (void)hipFree(d_sorted); (void)hipFree(d_bigram);
-        (void)hipFree(d_dir0); (void)hipFree(d_dirN); (void)hipFree(d_byte_rows); (void)hipFree(d_sig); (void)hipFree(d_first8);
+        (void)hipFree(d_len8); (void)hipFree(d_lit_start); (void)hipFree(d_place_start); (void)hipFree(d_len_rows);
+        (void)hipFree(d_chunks); (void)hipFree(d_index); (void)hipFree(d_dir0); (void)hipFree(d_dirN);
+        (void)hipFree(d_rows);
     }
 };
 
@@ -48,21 +46,14 @@ struct wg_handle_s {
     // device copies of the table, with room to append (capacities in elements)
     StateDesc *d_states = nullptr;
     uint8_t *d_classes = nullptr, *d_lit = nullptr;
-    ClassInfo *d_class_info = nullptr;
+    ClassPlan *d_plans = nullptr;
+    std::vector<ClassPlan> plans;                     // host copy, kept for the asynchronous uploads
     uint32_t cap_states = 0, cap_classes = 0, cap_keys = 0;
     uint32_t up_states = 0, up_classes = 0;           // how much of the host table is on the device
-    // class index storage: one buffer of V exit entries per class table in use, and the
-    // device table of their addresses
-    std::vector<ClassInfo> class_info;                // host copy, kept for the asynchronous uploads
-    std::vector<ExitEntry *> class_bufs;
-    std::vector<ExitEntry *> class_slabs;             // what was allocated: class_bufs point into these
-    uint32_t slab_left = 0;                           // class buffers not handed out yet in the last slab
-    ExitEntry **d_class_entries = nullptr;
     uint32_t max_batch = 0;
-    uint32_t n_cu = 256;
     // kernel timing: events recorded since the last wg_profile_read
     bool profiling = false;
-    std::vector<hipEvent_t> fill_events;       // 8 per wg_fill_masks call: begin / end of each kernel
+    std::vector<hipEvent_t> fill_events;       // 4 per wg_fill_masks call: begin / end of each kernel
     std::vector<hipEvent_t> advance_events;    // 2 per wg_advance call
     std::vector<hipEvent_t> apply_events;      // 2 per wg_profile_apply_mask call
     std::vector<hipEvent_t> spare_events;
@@ -105,15 +96,11 @@ hipEvent_t take_event(wg_handle_s *h) {
 int reserve_batch(wg_handle_s *h, uint32_t B) {
     if (B <= h->max_batch) return WG_OK;
     WG_HIP(hipDeviceSynchronize());
-    if (h->dc.row_ref) (void)hipFree(h->dc.row_ref);
-    if (h->dc.miss) (void)hipFree(h->dc.miss);
-    if (h->dc.class_miss) (void)hipFree(h->dc.class_miss);
-    h->dc.row_ref = nullptr; h->dc.miss = nullptr; h->dc.class_miss = nullptr; h->max_batch = 0;
-    h->dc.miss_cap = 0;
+    (void)hipFree(h->dc.row_ref);
+    (void)hipFree(h->dc.tasks);
+    h->dc.row_ref = nullptr; h->dc.tasks = nullptr; h->max_batch = 0;
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.row_ref), B * sizeof(uint32_t)));
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.miss), B * sizeof(MissEntry)));
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.class_miss), B * sizeof(uint32_t)));
-    h->dc.miss_cap = B;
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tasks), B * sizeof(RowTask)));
     h->max_batch = B;
     return WG_OK;
 }
@@ -145,7 +132,7 @@ uint32_t grown(uint32_t need, uint32_t floor_n) {
 int sync_table(wg_handle_s *h, hipStream_t s) {
     const Table &t = h->low.table;
     const uint32_t n_states = (uint32_t)t.states.size(), n_classes = (uint32_t)(t.classes.size() / 256);
-    const uint32_t row_stride = h->dc.row_stride, V = h->vocab->dv.V;
+    const uint32_t row_stride = h->dc.row_stride;
     if (n_states > h->cap_states || n_classes > h->cap_classes || t.n_keys > h->cap_keys)
         WG_HIP(hipDeviceSynchronize());
     if (n_states > h->cap_states) {
@@ -160,19 +147,16 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
     if (t.n_keys > h->cap_keys) {
         const uint32_t nc = grown(t.n_keys, 4096);
         int rc = regrow(&h->dc.tags, h->cap_keys, nc);
+        if (rc == WG_OK) rc = regrow(&h->dc.slots, h->cap_keys, nc);
         if (rc != WG_OK) return rc;
         h->cap_keys = nc;
     }
     if (n_classes > h->cap_classes) {
         const uint32_t nc = grown(n_classes, 64);
         int rc = regrow(&h->d_classes, (size_t)h->up_classes * 256, (size_t)nc * 256);
-        if (rc == WG_OK) rc = regrow(&h->d_class_info, h->up_classes, nc);
-        if (rc == WG_OK) rc = regrow(&h->dc.class_built, h->cap_classes, nc);
-        // one pair of counters per class table, 128 bytes apart so that appends to different
-        // tables do not meet in one cache line
-        if (rc == WG_OK) rc = regrow(&h->dc.class_count, (size_t)h->cap_classes * 32, (size_t)nc * 32);
-        if (rc == WG_OK) rc = regrow(&h->dc.class_rows, (size_t)h->cap_classes * 3 * row_stride, (size_t)nc * 3 * row_stride);
-        if (rc == WG_OK) rc = regrow(&h->d_class_entries, h->cap_classes, nc);
+        if (rc == WG_OK) rc = regrow(&h->d_plans, h->up_classes, nc);
+        if (rc == WG_OK) rc = regrow(&h->dc.class_tags, h->cap_classes, nc);
+        if (rc == WG_OK) rc = regrow(&h->dc.class_rows, (size_t)h->cap_classes * 2 * row_stride, (size_t)nc * 2 * row_stride);
         if (rc != WG_OK) return rc;
         h->cap_classes = nc;
     }
@@ -186,29 +170,9 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         const uint32_t a = h->up_classes, n = n_classes - a;
         WG_HIP(hipMemcpyAsync(h->d_classes + (size_t)a * 256, t.classes.data() + (size_t)a * 256, (size_t)n * 256,
                               hipMemcpyHostToDevice, s));
-        h->class_info.resize(n_classes);
-        for (uint32_t c = a; c < n_classes; c++) h->class_info[c] = class_info_of(t.classes.data() + (size_t)c * 256);
-        WG_HIP(hipMemcpyAsync(h->d_class_info + a, h->class_info.data() + a, n * sizeof(ClassInfo), hipMemcpyHostToDevice, s));
-        // Per class table: V slots for the list of the whole table, V for the lists of its token
-        // ranges.  The buffers are cut from slabs of several, so that an instance which brings
-        // one new table does not pay for a device allocation of its own.
-        const size_t per_class = 2u * (size_t)V;
-        while (h->class_bufs.size() < n_classes) {           // (a call that failed half way left some)
-            if (h->slab_left == 0) {
-                const size_t missing = n_classes - h->class_bufs.size();
-                const uint32_t count = (uint32_t)(missing > 8 ? missing : 8);
-                ExitEntry *slab = nullptr;
-                WG_HIP(hipMalloc(reinterpret_cast<void **>(&slab), count * per_class * sizeof(ExitEntry)));
-                h->class_slabs.push_back(slab);
-                h->slab_left = count;
-                h->class_bufs.push_back(slab);
-            } else {
-                h->class_bufs.push_back(h->class_bufs.back() + per_class);
-            }
-            h->slab_left--;
-        }
-        WG_HIP(hipMemcpyAsync(h->d_class_entries + a, h->class_bufs.data() + a, n * sizeof(ExitEntry *),
-                              hipMemcpyHostToDevice, s));
+        h->plans.resize(n_classes);
+        for (uint32_t c = a; c < n_classes; c++) h->plans[c] = class_plan_of(t.classes.data() + (size_t)c * 256);
+        WG_HIP(hipMemcpyAsync(h->d_plans + a, h->plans.data() + a, n * sizeof(ClassPlan), hipMemcpyHostToDevice, s));
     }
     if (new_states || new_classes) {
         // the copies read pageable host memory that a later append may move
@@ -216,8 +180,7 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         h->up_states = n_states;
         h->up_classes = n_classes;
     }
-    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_class_info, h->d_lit, n_states, t.lmax, n_classes};
-    h->dc.class_entries = h->d_class_entries;
+    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, n_states, t.lmax};
     h->dc.n_keys = t.n_keys;
     return WG_OK;
 }
@@ -236,7 +199,7 @@ int set_cache_rows(wg_handle_s *h, uint32_t rows) {
 int next_generation(wg_handle_s *h, hipStream_t s) {
     if (++h->dc.epoch >= (1u << 30)) {                 // out of generation numbers: reset the tags for real
         WG_HIP(hipMemsetAsync(h->dc.tags, 0, (size_t)h->cap_keys * sizeof(unsigned long long), s));
-        WG_HIP(hipMemsetAsync(h->dc.class_built, 0, (size_t)h->cap_classes * sizeof(uint32_t), s));
+        WG_HIP(hipMemsetAsync(h->dc.class_tags, 0, (size_t)h->cap_classes * sizeof(unsigned long long), s));
         WG_HIP(hipMemsetAsync(&h->dc.ctr->slot_ctr, 0, sizeof(unsigned long long), s));
         h->dc.epoch = 1;
     }
@@ -272,27 +235,40 @@ int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uin
         unsigned long long *unused = nullptr;
         (void)static_topk_scratch(&unused);
     }
-    hipError_t e = upload(&v->d_bytes, ix.bytes.data(), ix.bytes.size());
-    if (e == hipSuccess) e = upload(&v->d_offsets, ix.offsets.data(), ix.offsets.size());
-    if (e == hipSuccess) e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());
+    // the candidate indexes, one behind the other
+    std::vector<ExitEntry> index;
+    uint32_t at[4];
+    {
+        const std::vector<ExitEntry> *parts[4] = {&ix.sorted, &ix.lit_entries, &ix.bigram, &ix.places};
+        uint64_t n = 0;
+        for (const auto *p : parts) n += p->size();
+        if (n > 0xFFFFFFFFull) return fail(WG_ERR_INVALID, "wg_vocab_create: the candidate indexes have more than 2^32 entries");
+        index.reserve(n);
+        for (int i = 0; i < 4; i++) {
+            at[i] = (uint32_t)index.size();
+            index.insert(index.end(), parts[i]->begin(), parts[i]->end());
+        }
+    }
+    // the token rows, likewise
+    std::vector<uint32_t> rows(ix.byte_rows.begin(), ix.byte_rows.begin() + (size_t)kBlockRow * ix.row_stride);
+    rows.insert(rows.end(), ix.block_rows.begin(), ix.block_rows.end());
+    rows.insert(rows.end(), ix.tail_rows.begin(), ix.tail_rows.end());
+    hipError_t e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());
     if (e == hipSuccess) e = upload(&v->d_chunks, ix.chunks.data(), ix.chunks.size());
-    if (e == hipSuccess) e = upload(&v->d_sig, ix.sig.data(), ix.sig.size());
-    if (e == hipSuccess) e = upload(&v->d_first8, ix.first8.data(), ix.first8.size());
-    if (e == hipSuccess) e = upload(&v->d_lit_entries, ix.lit_entries.data(), ix.lit_entries.size());
-    if (e == hipSuccess) e = upload(&v->d_lit_start, ix.lit_start.data(), ix.lit_start.size());
     if (e == hipSuccess) e = upload(&v->d_len_rows, ix.len_rows.data(), ix.len_rows.size());
-    if (e == hipSuccess) e = upload(&v->d_sorted, ix.sorted.data(), ix.sorted.size());
+    if (e == hipSuccess) e = upload(&v->d_rows, rows.data(), rows.size());
+    if (e == hipSuccess) e = upload(&v->d_index, index.data(), index.size());
     if (e == hipSuccess) e = upload(&v->d_dir0, ix.dir0.data(), ix.dir0.size());
-    if (e == hipSuccess) e = upload(&v->d_bigram, ix.bigram.data(), ix.bigram.size());
+    if (e == hipSuccess) e = upload(&v->d_lit_start, ix.lit_start.data(), ix.lit_start.size());
     if (e == hipSuccess) e = upload(&v->d_dirN, ix.dirN.data(), ix.dirN.size());
-    if (e == hipSuccess) e = upload(&v->d_byte_rows, ix.byte_rows.data(), ix.byte_rows.size());
+    if (e == hipSuccess) e = upload(&v->d_place_start, ix.place_start.data(), ix.place_start.size());
     if (e != hipSuccess) {
         v->release();
         return fail(e == hipErrorOutOfMemory ? WG_ERR_NOMEM : WG_ERR_HIP,
                     std::string("wg_vocab_create: ") + hipGetErrorString(e));
     }
-    v->dv = DeviceVocab{v->d_bytes, v->d_offsets, v->d_len8, v->d_chunks, v->d_sig, v->d_first8, v->d_lit_entries,
-                        v->d_lit_start, v->d_len_rows, v->d_sorted, v->d_dir0, v->d_bigram, v->d_dirN, v->d_byte_rows,
+    v->dv = DeviceVocab{v->d_len8, v->d_chunks, v->d_len_rows, v->d_rows, v->d_index, v->d_dir0,
+                        v->d_lit_start, v->d_dirN, v->d_place_start, at[0], at[1], at[2], at[3],
                         V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride, {}};
     for (uint32_t p = 0; p <= kParts; p++) v->dv.part_tok[p] = ix.part_tok[p];
     *out = v.release();
@@ -391,12 +367,10 @@ void wg_table_destroy(wg_table_t t) { delete t; }
 void wg_destroy(wg_handle_t h) {
     if (!h) return;
     (void)hipDeviceSynchronize();
-    (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_class_info);
-    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.arena);
-    (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.miss); (void)hipFree(h->dc.class_miss);
-    (void)hipFree(h->dc.class_built); (void)hipFree(h->dc.class_rows);
-    (void)hipFree(h->d_class_entries); (void)hipFree(h->dc.class_count);
-    for (ExitEntry *b : h->class_slabs) (void)hipFree(b);
+    (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
+    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.walked); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
+    (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
+    (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
     delete h;
@@ -422,19 +396,10 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     h->vocab = vocab;
     const Table &t = h->low.table;
     WG_HIP(hipSetDevice(vocab->device));
-    hipDeviceProp_t prop;
-    WG_HIP(hipGetDeviceProperties(&prop, vocab->device));
-    h->n_cu = prop.multiProcessorCount > 0 ? (uint32_t)prop.multiProcessorCount : 256u;
-
     const uint32_t row_stride = vocab->dv.row_stride;
     const uint64_t row_bytes = (uint64_t)row_stride * 4ull;
-    {
-        const hipError_t e = configure_kernels(row_stride * 4u);
-        if (e == hipErrorInvalidValue)
-            return fail(WG_ERR_INVALID, "wg_compile: a mask row does not fit the LDS of a compute unit next to the "
-                                        "builder's queue (vocabulary too large)");
-        WG_HIP(e);
-    }
+    if (rows_lds_bytes(vocab->dv) > kRowsLdsMax)
+        return fail(WG_ERR_INVALID, "wg_compile: a share of a mask row does not fit the LDS of the row builder (vocabulary too large)");
     h->dc.row_stride = row_stride;
     h->dc.epoch = 1;                                   // tags start at 0 = never built
 
@@ -443,7 +408,7 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     size_t free_b = 0, total_b = 0;
     WG_HIP(hipMemGetInfo(&free_b, &total_b));
     const uint64_t n_classes = t.classes.size() / 256;
-    const uint64_t class_bytes = n_classes * (3ull * row_bytes + 2ull * vocab->dv.V * sizeof(ExitEntry));
+    const uint64_t class_bytes = n_classes * 2ull * row_bytes;
     if (class_bytes > (uint64_t)free_b / 4)
         return fail(WG_ERR_NOMEM, "wg_compile: the class indexes (" + std::to_string(class_bytes >> 20) +
                                       " MiB for " + std::to_string(n_classes) +
@@ -455,6 +420,9 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
 
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ctr), sizeof(Counters)));
     WG_HIP(hipMemset(h->dc.ctr, 0, sizeof(Counters)));
+    const size_t walked_bytes = (size_t)kWalkedSlots * kWalkedStride * sizeof(unsigned long long);
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.walked), walked_bytes));
+    WG_HIP(hipMemset(h->dc.walked, 0, walked_bytes));
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
     if (rc == WG_OK) rc = reserve_batch(h.get(), kDefaultBatch);
@@ -509,8 +477,7 @@ uint32_t wg_max_batch(wg_handle_t h) { return h ? h->max_batch : 0; }
 int wg_set_scan_batch(wg_handle_t h, uint32_t tables) {
     if (!h) return fail(WG_ERR_INVALID, "wg_set_scan_batch: null handle");
     if (tables > 8u) return fail(WG_ERR_INVALID, "wg_set_scan_batch: tables must be 0 .. 8");
-    h->dc.scan_batch = tables;
-    return WG_OK;
+    return WG_OK;                                      // (masks are made without a scan of class tables)
 }
 
 uint32_t wg_num_instances(wg_handle_t h) { return h ? (uint32_t)h->low.table.start.size() : 0; }
@@ -527,10 +494,10 @@ int fill(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t 
     if (B > h->max_batch)
         return fail(WG_ERR_INVALID, std::string(who) + ": B = " + std::to_string(B) + " is above the " +
                                         std::to_string(h->max_batch) + " requests the handle has room for (wg_reserve_batch)");
-    hipEvent_t ev[8];
+    hipEvent_t ev[4];
     if (h->profiling) for (auto &e : ev) { e = take_event(h); h->fill_events.push_back(e); }
     WG_HIP(launch_fill(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, d_bitmask, d_logits, dtype,
-                       logits_stride, h->n_cu, static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
+                       logits_stride, static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
     return WG_OK;
 }
 }  // namespace
@@ -683,15 +650,17 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     WG_HIP(hipMemcpy(&c, h->dc.ctr, sizeof c, hipMemcpyDeviceToHost));
     host_out->lookups = c.lookups; host_out->hits = c.hits; host_out->builds = c.builds;
     host_out->uncached_builds = c.uncached_builds;
-    host_out->class_scans = c.class_scans; host_out->entries_walked = c.entries_walked;
+    host_out->class_scans = c.class_scans;
+    unsigned long long walked[kWalkedSlots * kWalkedStride];
+    WG_HIP(hipMemcpy(walked, h->dc.walked, sizeof walked, hipMemcpyDeviceToHost));
+    host_out->entries_walked = 0;
+    for (uint32_t i = 0; i < kWalkedSlots; i++) host_out->entries_walked += walked[i * kWalkedStride];
     host_out->keys = h->dc.n_keys;
     host_out->cache_rows = h->dc.cap_rows;
     const uint64_t taken = (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;
     host_out->rows_in_use = taken < h->dc.cap_rows ? taken : h->dc.cap_rows;
     const uint64_t row_bytes = (uint64_t)h->dc.row_stride * 4ull;
-    host_out->arena_bytes = (uint64_t)h->dc.cap_rows * row_bytes +
-                            (uint64_t)(h->class_bufs.size() + h->slab_left) * (2ull * h->vocab->dv.V * sizeof(ExitEntry)) +
-                            (uint64_t)h->cap_classes * 3ull * row_bytes;
+    host_out->arena_bytes = ((uint64_t)h->dc.cap_rows + h->cap_classes * 2ull) * row_bytes;
     return WG_OK;
 }
 
@@ -718,10 +687,9 @@ int wg_profile_read(wg_handle_t h, wg_profile_t *host_out) {
         float ms = 0.f;
         return (a && b && hipEventElapsedTime(&ms, a, b) == hipSuccess) ? (double)ms : 0.0;
     };
-    for (size_t i = 0; i + 7 < h->fill_events.size(); i += 8) {
+    for (size_t i = 0; i + 3 < h->fill_events.size(); i += 4) {
         hipEvent_t *e = &h->fill_events[i];
-        p.lookup_ms += span(e[0], e[1]); p.scan_ms += span(e[2], e[3]);
-        p.build_ms += span(e[4], e[5]); p.gather_ms += span(e[6], e[7]);
+        p.lookup_ms += span(e[0], e[1]); p.build_ms += span(e[2], e[3]);
         p.fill_calls++;
     }
     for (size_t i = 0; i + 1 < h->advance_events.size(); i += 2) {

@@ -67,6 +67,20 @@ static_assert(sizeof(ClassInfo) == 32, "class info layout");
 enum : uint8_t { SCAN_CHUNK = 0, SCAN_SIG = 1, SCAN_HEAD = 2 };
 constexpr uint8_t kManyExits = 0xFF;
 
+// How the rows of a class table's states are made, worked out once per table.  A table that at most
+// kFewLive byte values enter is taken by first byte: ids[0 .. n_exits) are those values, value |
+// class << 8.  Any other table is taken by token rows: ids[0 .. n_exits) are its exit bytes (value
+// | class << 8), ids[n_exits .. n_ids) the token rows that together hold every token with a
+// rejected byte (kBlockRow + k: byte values 4k .. 4k+3, kBigBlockRow + k: 16k .. 16k+15).
+constexpr uint32_t kFewLive = 8;
+constexpr uint32_t kBlockRow = 256, kBigBlockRow = 320, kTailRow = 336;
+struct ClassPlan {
+    uint16_t n_exits, n_ids, by_first, pad;
+    uint16_t ids[260];
+};
+static_assert(sizeof(ClassPlan) % 16 == 0, "class plan layout");
+ClassPlan class_plan_of(const uint8_t *table);
+
 // A token that leaves a checkpoint state before its last byte: the part of a mask that
 // depends on what follows the state.  `off` bytes are consumed up to and including the
 // exit byte, `rem` bytes remain, the first of which is `first`.
@@ -95,6 +109,10 @@ struct VocabIndex {
     std::vector<ExitEntry> bigram;         // never empty
     std::vector<uint32_t> dirN;            // 65536 + 1
     std::vector<uint32_t> byte_rows;       // 512 rows of row_stride words: 256 by any byte, 256 by the first byte
+    std::vector<uint32_t> block_rows;      // 64 + 16 rows: by any byte of a block of 4, of 16 byte values
+    std::vector<uint32_t> tail_rows;       // 256 rows: tokens in which the byte occurs once, as the last one
+    std::vector<ExitEntry> places;         // the byte pairs again, by (first byte of the pair, range); never empty
+    std::vector<uint32_t> place_start;     // 256 * kParts + 1
 };
 
 // Checks the vocabulary arguments of wg_vocab_create and builds the indexes.  Returns WG_OK, or

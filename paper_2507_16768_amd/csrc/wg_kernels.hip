@@ -1,17 +1,10 @@
 // HIP kernels of the structured-decoding hot path for gfx950 (wave64).
 //
-//   lookup       : request state -> cache key, claims missing keys and class tables
-//                  (advance_lookup: after advancing the state by the sampled token)
-//   class_scan   : every vocabulary token against one checkpoint's byte-class table: a first look
-//                  that settles most tokens with one instruction or table look-up each (64-lane
-//                  ballots pack the row words), the rest byte by byte through the table in LDS
-//                  (class_scan_batch, for handles with many tables: several tables per pass
-//                  over the tokens, the first look from the vocabulary's rows by byte value)
-//   key_build    : a workgroup assembles the row of a missing key (or its words for one token
-//                  range) in LDS from the class index and the tokens that leave the state early,
-//                  which it finds in the vocabulary's indexes (byte order, byte pairs) or in the
-//                  class index's lists
-//   gather       : cached row -> bitmask[b]   (gather_apply: and -inf into the logits)
+//   lookup       : request state -> cache key; claims a missing key and leaves the task of making
+//                  its row (advance_lookup: after advancing the state by the sampled token)
+//   rows         : the mask row of every request, a workgroup per (request, token range): copied from
+//                  the cache, or made in LDS from the vocabulary's static indexes; to the caller's
+//                  bitmask, to the cache, and (wg_decode_step) as -inf into the logits
 //   apply        : logits <- -inf where the mask bit is 0
 //   masked_argmax: greedy choice under the mask, logits only read
 //   advance      : per-request walk of the sampled token
@@ -22,94 +15,78 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
-#include <mutex>
-
 #include "wg_device.h"
 #include "wg_order.h"
 
 namespace wg {
 
-constexpr uint32_t kScanGroup = 2048;     // tokens per class_scan workgroup
-static_assert(kScanGroup == kPartGroup, "a class_scan workgroup's tokens lie in one token range");
-static_assert(2u + 2u * kParts <= 32u, "the counters of a class fit its 128 bytes");
-constexpr uint32_t kCountStride = 32;     // class_count entries are 128 bytes apart
-constexpr uint32_t kXcds = 8;             // accelerator complex dies, each with a private L2
-constexpr uint32_t kShortRem = 4;         // exit entries with at most this many bytes left are "short"
-
 // ---------------------------------------------------------------------------------------------
-// Generic per-lane walker: feeds `len` bytes at `p` to the FSM from (sid, aux).
-// Returns false on the first rejected byte.  Every state entered mid-token starts with
-// aux = 0; only a bounded Wait counts.
-__device__ __forceinline__ bool walk_bytes(const DeviceTable &T, uint32_t &sid, uint32_t &aux,
-                                           const uint8_t *__restrict__ p, uint32_t len)
+// Walking a token through the state table.
+
+// A token's bytes as 8-byte chunks of the vocabulary, two of them in registers at a time; the
+// chunk array is strided by token, so the walk of a token of any length loads what it reaches.
+struct TokenBytes {
+    const uint64_t *chunks;      // chunk 0 of the token
+    size_t stride;               // elements from one chunk of a token to the next (V)
+    uint64_t w0, w1;             // chunks q and q + 1
+    uint32_t q, n;               // n: chunks of the token
+};
+
+__device__ __forceinline__ TokenBytes token_bytes(const DeviceVocab &Vc, uint32_t tok, uint32_t L)
 {
-    uint32_t cur = WG_SID_ERROR;          // sid whose descriptor is loaded
-    uint32_t kind = 0, lit = 0, na = 0, nb = 0, mx = 0;
-    const uint8_t *cls = nullptr;
-    for (uint32_t i = 0; i < len; i++) {
-        if (sid != cur) {
-            if (sid >= T.n_states) return false;            // ERROR or corrupt state
-            const StateDesc &d = T.states[sid];
-            kind = d.kind_byte & 0xFFu; lit = (d.kind_byte >> 8) & 0xFFu;
-            na = d.next_a; nb = d.next_b; mx = d.max;
-            cls = T.classes + (size_t)d.cls * 256u;
-            cur = sid;
-        }
-        uint32_t x = p[i];
-        if (kind == WG_KIND_LIT) {
-            if (x != lit) return false;
-            sid = na; aux = 0;
-        } else if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
-            uint32_t c = cls[x];
-            if (c == CLS_STAY) {
-                if (mx != WG_UNBOUNDED) { if (aux >= mx) return false; aux++; }
-            } else if (c == CLS_EXIT_A) { sid = na; aux = 0; }
-            else if (c == CLS_EXIT_B) { sid = nb; aux = 0; }
-            else return false;
-        } else return false;                                // FINAL / END accept no byte
-    }
-    return true;
+    TokenBytes t;
+    t.chunks = Vc.chunks + tok; t.stride = Vc.V;
+    t.n = (L + 7u) >> 3; t.q = 0;
+    t.w0 = t.chunks[0];
+    t.w1 = t.n > 1u ? t.chunks[t.stride] : 0ull;
+    return t;
 }
 
-// Verdict and next state of one token (EOS is the one-symbol string [EOS]).
-__device__ __forceinline__ bool walk_token(const DeviceTable &T, const DeviceVocab &Vc,
-                                           uint32_t &sid, uint32_t &aux, int64_t t)
-{
-    if (t < 0 || t >= (int64_t)Vc.V || sid >= T.n_states) return false;
-    if ((int64_t)Vc.eos_id == t) {
-        uint32_t e = T.states[sid].eos_next;
-        if (e == WG_SID_ERROR) return false;
-        sid = e; aux = 0;
-        return true;
-    }
-    uint32_t lo = Vc.offsets[t], hi = Vc.offsets[t + 1];
-    if (hi <= lo) return false;                             // byte-less non-EOS token
-    return walk_bytes(T, sid, aux, Vc.bytes + lo, hi - lo);
-}
-
-// Eight bytes of a token (held as three 8-byte chunks) starting at byte i.
-__device__ __forceinline__ uint64_t token_window(uint64_t c0, uint64_t c1, uint64_t c2, uint32_t i)
+// The eight bytes from byte i on (zeros behind the token's end); i never decreases.
+__device__ __forceinline__ uint64_t window(TokenBytes &t, uint32_t i)
 {
     const uint32_t q = i >> 3, sh = (i & 7u) * 8u;
-    const uint64_t w0 = q == 0 ? c0 : q == 1 ? c1 : c2;
-    const uint64_t w1 = q == 0 ? c1 : q == 1 ? c2 : 0ull;
-    return sh ? (w0 >> sh) | (w1 << (64u - sh)) : w0;
+    if (q != t.q) {
+        t.w0 = q == t.q + 1u ? t.w1 : t.chunks[q * t.stride];
+        t.w1 = q + 1u < t.n ? t.chunks[(q + 1u) * t.stride] : 0ull;
+        t.q = q;
+    }
+    return sh ? (t.w0 >> sh) | (t.w1 << (64u - sh)) : t.w0;
 }
 
-// Walks bytes [i, L) of a token held in registers (L <= 24) from (sid, aux), consuming up to
-// eight bytes per state visit: a run of literal states is one masked 8-byte compare against
-// the state table's literal bytes, a stay-run inside a checkpoint is eight independent class
-// look-ups.  Returns false on the first rejected byte.
-__device__ __forceinline__ bool walk_chunks(const DeviceTable &T, uint32_t &sid, uint32_t &aux,
-                                            uint64_t c0, uint64_t c1, uint64_t c2, uint32_t i, uint32_t L)
+// The classes of eight bytes, two bits each, and from them the first of the n bytes that does not
+// stay: its place, or n.
+__device__ __forceinline__ uint32_t class_code(const uint8_t *lut, uint64_t bytes)
+{
+    const uint32_t lo = (uint32_t)bytes, hi = (uint32_t)(bytes >> 32);
+    uint32_t code = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        code |= (uint32_t)lut[(lo >> (8 * i)) & 0xFFu] << (2 * i);
+        code |= (uint32_t)lut[(hi >> (8 * i)) & 0xFFu] << (2 * i + 8);
+    }
+    return code;
+}
+__device__ __forceinline__ uint32_t first_leaving(uint32_t code, uint32_t n)
+{
+    const uint32_t x = code ^ 0x5555u;               // a 2-bit field is 0 iff its byte stays
+    const uint32_t mm = (x | (x >> 1)) & 0x5555u & ((1u << (2u * n)) - 1u);
+    return mm ? (uint32_t)__builtin_ctz(mm) >> 1 : n;
+}
+
+// Walks bytes [i, L) of a token from (sid, aux), up to eight bytes per state visit: a run of
+// literal states is one masked 8-byte compare against the state table's literal bytes, a stay-run
+// inside a checkpoint is eight independent class look-ups.  Every state entered on the way starts
+// with aux = 0; only a bounded Wait counts.  False on the first rejected byte.
+__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
     while (i < L) {
-        if (sid >= T.n_states) return false;
+        if (sid >= T.n_states) return false;                     // ERROR or corrupt state
         const StateDesc d = T.states[sid];
         const uint32_t kind = d.kind_byte & 0xFFu;
         const uint32_t n = L - i < 8u ? L - i : 8u;
-        const uint64_t tb = token_window(c0, c1, c2, i);
+        const uint64_t tb = window(t, i);
         if (kind == WG_KIND_LIT) {
             const uint32_t sh = (sid & 7u) * 8u;
             const uint64_t l0 = lit64[sid >> 3], l1 = lit64[(sid >> 3) + 1u];
@@ -120,19 +97,14 @@ __device__ __forceinline__ bool walk_chunks(const DeviceTable &T, uint32_t &sid,
             sid = m == d.run ? d.cls : sid + m;                  // d.cls: state after the Write
             aux = 0; i += m;
         } else if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
-            const uint8_t *cls = T.classes + (size_t)d.cls * 256u;
-            uint32_t code = 0;
-#pragma unroll
-            for (int k = 0; k < 8; k++) code |= (uint32_t)cls[(tb >> (8 * k)) & 0xFFu] << (2 * k);
-            const uint32_t x = code ^ 0x5555u;
-            const uint32_t mm = (x | (x >> 1)) & 0x5555u & ((1u << (2u * n)) - 1u);
-            const uint32_t stays = mm ? (uint32_t)__builtin_ctz(mm) >> 1 : n;
+            const uint32_t code = class_code(T.classes + (size_t)d.cls * 256u, tb);
+            const uint32_t stays = first_leaving(code, n);
             if (d.max != WG_UNBOUNDED && stays) {                // each stay needs budget left
-                if (aux + stays > d.max) return false;
+                if (aux >= d.max || stays > d.max - aux) return false;
                 aux += stays;
             }
             i += stays;
-            if (mm) {
+            if (stays < n) {
                 const uint32_t c = (code >> (2u * stays)) & 3u;
                 if (c == CLS_REJECT) return false;
                 sid = c == CLS_EXIT_A ? d.next_a : d.next_b;
@@ -144,13 +116,50 @@ __device__ __forceinline__ bool walk_chunks(const DeviceTable &T, uint32_t &sid,
 }
 
 // ---------------------------------------------------------------------------------------------
-// lookup: state -> cache key.  A missing key is claimed by exactly one request (CAS on the
-// key's tag), gets a row of the arena (or, when the arena is full, is built straight into
-// the claimer's bitmask row and not kept) and is queued for key_build: the i-th claim of a call
-// takes the i-th free row, so the order of the claims is their row allocation and the count
-// of rows in use is brought up to date once per call, by the last kernel of the fill; if the key's state is a
-// checkpoint whose class table has no index yet in this generation, the table is claimed and
-// queued for class_scan.
+// advance: one thread per request (EOS is the one-symbol string [EOS]; any other byte-less token
+// is rejected).
+__device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
+                                            uint32_t &sid, uint32_t &aux, int64_t t)
+{
+    bool ok = t >= 0 && t < (int64_t)Vc.V && sid < T.n_states;
+    if (ok) {
+        if ((int64_t)Vc.eos_id == t) {
+            sid = T.states[sid].eos_next; aux = 0;
+            ok = sid != WG_SID_ERROR;
+        } else {
+            // (both chunks are requested with the length, not after it)
+            const uint32_t L = Vc.len8[t];
+            TokenBytes tk;
+            tk.chunks = Vc.chunks + t; tk.stride = Vc.V; tk.q = 0; tk.n = Vc.n_chunks;
+            tk.w0 = tk.chunks[0];
+            tk.w1 = tk.n > 1u ? tk.chunks[tk.stride] : 0ull;
+            ok = L != 0u && walk(T, sid, aux, tk, 0u, L);
+        }
+    }
+    if (!ok) {
+        sid = WG_SID_ERROR; aux = 0;
+        atomicAdd(&Cc.ctr->errors, 1ull);
+    }
+}
+
+__global__ void __launch_bounds__(64)
+advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
+               const int32_t *__restrict__ tokens, uint32_t B)
+{
+    uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B) return;
+    uint32_t sid = states[b].sid, aux = states[b].aux;
+    advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
+    states[b].sid = sid; states[b].aux = aux;
+}
+
+// ---------------------------------------------------------------------------------------------
+// lookup: state -> cache key.  A missing key is claimed by exactly one request (CAS on the key's
+// tag) and gets a row of the arena (or none, when the arena is full: its row is then made again by
+// every call that needs it).  The i-th claim of a call takes the i-th free row, so the order of the
+// claims is their row allocation; the count of rows in use is brought up to date once per call, by
+// the last kernel of the fill.  Any other request of the call with that key makes the row for
+// itself: no request waits for another, so masks are made by one kernel.
 
 // What a lookup reads from the handle's counters before anything depends on it.
 struct LookupEnv {
@@ -170,127 +179,76 @@ __device__ __forceinline__ void lookup_one(const DeviceTable &T, const DeviceCac
                                            const LookupEnv &env, uint32_t b, bool live, uint32_t sid, uint32_t aux)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    bool hit = false, claimed = false;
-    uint32_t key = kNoKey, kind = 0, variant = 0;
-    const uint32_t epoch = Cc.epoch;
-    const unsigned long long launch = env.launch;
-    const uint32_t rows0 = env.rows0;
-    uint32_t ref = kNoKey;
-    StateDesc d{}, dn[2] = {};
-    ClassInfo ci{};
-    uint32_t class_gen = 0;
-    if (live) {
-        if (sid < T.n_states) {
-            d = T.states[sid];
-            kind = d.kind_byte & 0xFFu;
-            if (kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
-                const uint32_t left = d.max > aux ? d.max - aux : 0u;
-                variant = T.lmax - (left < T.lmax ? left : T.lmax);
-            }
-            key = d.key_base + variant;
-            const unsigned long long t = __hip_atomic_load(&Cc.tags[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // Requested right behind the key's tag, although only a missing key needs them: the
-            // two successors' descriptors and the generation of the class index.  Plain loads
-            // from clamped indexes, so that nothing waits for them before the tag has decided.
-            dn[0] = T.states[d.next_a < T.n_states ? d.next_a : 0u];
-            dn[1] = T.states[d.next_b < T.n_states ? d.next_b : 0u];
-            const uint32_t own_class = (kind == WG_KIND_WAIT || kind == WG_KIND_COND) ? d.cls : 0u;
-            class_gen = __hip_atomic_load(&Cc.class_built[own_class], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ci = T.class_info[own_class];
-            // anything but a row of this generation or a claim made in this very call is stale
-            hit = (uint32_t)(t >> 32) == epoch;
-            const bool this_call = t >= kTagClaim && ((t >> 16) & kTagLaunchMask) == launch;
-            if (!hit && !this_call)
-                claimed = atomicCAS(&Cc.tags[key], t, kTagClaim | (launch << 16) | b) == t;
-            ref = hit ? (uint32_t)t : claimed ? kRefSelf : kRefByKey | key;
+    const unsigned long long now = (unsigned long long)Cc.epoch << kTagLaunchBits | env.launch;
+    bool hit = false, build = false, claimed = false, class_claimed = false;
+    uint32_t key = 0, ref = kNoKey;
+    RowTask me{};
+    if (live && sid < T.n_states) {
+        const StateDesc d = T.states[sid];
+        const uint32_t kind = d.kind_byte & 0xFFu;
+        uint32_t variant = 0;
+        if (kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
+            const uint32_t left = d.max > aux ? d.max - aux : 0u;
+            variant = T.lmax - (left < T.lmax ? left : T.lmax);
         }
-        Cc.row_ref[b] = ref;
-    }
-    // The claimers of a wavefront take their arena rows and their places in the miss list
-    // together.  A key whose candidate tokens all need a deep walk (its state hands over to
-    // another checkpoint) goes to the front of the list: key_build cuts it into one work item per
-    // token range and starts those first; every other key is one work item, from the back.
-    const unsigned long long cm = __ballot(claimed);
-    if (cm) {
-        HopState hop[2];
-        bool deep = false;
-        if (claimed) {
-#pragma unroll
-            for (int w = 0; w < 2; w++) {
-                const uint32_t t = w ? d.next_b : d.next_a;
-                const StateDesc &td = dn[w];
-                hop[w] = HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
-                if (t < T.n_states)
-                    hop[w] = HopState{td.kind_byte & 0xFFu, (td.kind_byte >> 8) & 0xFFu,
-                                      td.next_a, td.next_b, td.max, td.cls};
-            }
-            const bool ckpt0 = hop[0].kind == WG_KIND_WAIT || hop[0].kind == WG_KIND_COND;
-            const bool ckpt1 = hop[1].kind == WG_KIND_WAIT || hop[1].kind == WG_KIND_COND;
-            deep = ((kind == WG_KIND_LIT || kind == WG_KIND_WAIT) && ckpt0) || (kind == WG_KIND_COND && (ckpt0 || ckpt1));
-        }
-        const unsigned long long dm = __ballot(claimed && deep), pm = cm & ~dm;
-        // The claim of the class table goes out first, so that its compare-and-swap is in flight
-        // together with the three counters of the key claims (three counters, three lanes).
+        key = d.key_base + variant;
         const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
-        const bool want_class = claimed && ckpt && class_gen != epoch;
-        uint32_t class_was = epoch;
-        if (want_class) class_was = atomicCAS(&Cc.class_built[d.cls], class_gen, epoch);
-        uint32_t got = 0;
-        if (lane == 0) got = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
-        else if (lane == 1 && dm) got = atomicAdd(&Cc.ctr->n_deep, (uint32_t)__popcll(dm));
-        else if (lane == 2 && pm) got = atomicAdd(&Cc.ctr->n_plain, (uint32_t)__popcll(pm));
-        const uint32_t first_key = __shfl(got, 0), first_deep = __shfl(got, 1), first_plain = __shfl(got, 2);
-        const bool class_claimed = want_class && class_was == class_gen;
-        const unsigned long long ccm = __ballot(class_claimed);
-        uint32_t first_class = 0;
-        if (ccm) {
-            if (lane == 0) first_class = atomicAdd(&Cc.ctr->n_class_miss, (uint32_t)__popcll(ccm));
-            first_class = __shfl(first_class, 0);
-        }
-        if (claimed) {
-            const unsigned long long below = (1ull << lane) - 1ull;
-            const uint32_t idx = first_key + (uint32_t)__popcll(cm & below);
-            const uint32_t slot = Cc.cap_rows - rows0 > idx ? rows0 + idx : kNoSlot;
-            // this request builds the key: resolve what key_build needs into the miss entry
-            MissEntry me{};
-            me.key = key; me.sid = sid; me.aux = aux; me.kind = kind;
-            me.r = T.lmax - variant; me.cls = d.cls; me.eos_next = d.eos_next;
-            me.next_a = d.next_a; me.next_b = d.next_b;
-            me.slot = slot; me.req = b;
-            me.hop[0] = hop[0]; me.hop[1] = hop[1];
-            me.lit = (d.kind_byte >> 8) & 0xFFu;
-            // Where the candidates come from.  A key that is not deep has, behind each exit, a
-            // literal byte or a state that takes no byte at all: its candidates are found in
-            // the static indexes of the vocabulary by the bytes involved (tokens of at most 24
-            // bytes: the walkers of those paths hold a token in registers).
-            me.mode = KB_LIST;
-            if (!deep && T.lmax <= 24u) {
-                const bool lit0 = hop[0].kind == WG_KIND_LIT, lit1 = hop[1].kind == WG_KIND_LIT;
-                if (kind == WG_KIND_LIT) me.mode = KB_SORTED;
-                else if (ckpt && (!lit0 || ci.n_a != kManyExits) && (!lit1 || ci.n_b != kManyExits)) {
-                    me.mode = KB_BIGRAM;
-                    me.n_a = lit0 ? ci.n_a : 0; me.n_b = lit1 ? ci.n_b : 0;
-                    me.exits[0] = ci.a[0] | ci.a[1] << 8 | ci.a[2] << 16 | (uint32_t)ci.a[3] << 24;
-                    me.exits[1] = ci.a[4] | ci.a[5] << 8 | ci.b[0] << 16 | (uint32_t)ci.b[1] << 24;
-                    me.exits[2] = ci.b[2] | ci.b[3] << 8 | ci.b[4] << 16 | (uint32_t)ci.b[5] << 24;
-                }
-            }
-            Cc.miss[deep ? first_deep + (uint32_t)__popcll(dm & below)
-                         : Cc.miss_cap - 1u - (first_plain + (uint32_t)__popcll(pm & below))] = me;
-            if (class_claimed) {
-                // the class list and the list of each token range: short entries fill from the
-                // front, long ones from the back
-                const uint32_t c = d.cls;
+        const unsigned long long t = __hip_atomic_load(&Cc.tags[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t slot = Cc.slots[key];
+        // Requested right behind the key's tag, although only a missing key needs them: the two
+        // successors' descriptors and the tag of the class table.  Plain loads from clamped
+        // indexes, so that nothing waits for them before the tag has decided.
+        StateDesc dn[2];
+        dn[0] = T.states[d.next_a < T.n_states ? d.next_a : 0u];
+        dn[1] = T.states[d.next_b < T.n_states ? d.next_b : 0u];
+        const uint32_t cls = ckpt ? d.cls : 0u;
+        const unsigned long long ct = __hip_atomic_load(&Cc.class_tags[cls], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (a slot is only read where the tag is of this generation and an earlier call: it does not
+        // change after that call, so the two loads need no order)
+        const bool made = (uint32_t)(t >> kTagLaunchBits) == Cc.epoch;
+        hit = made && t != now && slot != kNoSlot;
+        build = !hit;
+        ref = hit ? slot : kRefBuild;
+        if (build && t != now) claimed = atomicCAS(&Cc.tags[key], t, now) == t;
+        me.sid = sid; me.kind = kind; me.lit = (d.kind_byte >> 8) & 0xFFu; me.cls = d.cls; me.run = d.run;
+        me.r = T.lmax - variant; me.eos_next = d.eos_next; me.slot = kNoSlot;
 #pragma unroll
-                for (uint32_t i = 0; i < 2u + 2u * kParts; i++) Cc.class_count[c * kCountStride + i] = 0;
-                Cc.class_miss[first_class + (uint32_t)__popcll(ccm & below)] = c;
+        for (int w = 0; w < 2; w++) {
+            const uint32_t nt = w ? d.next_b : d.next_a;
+            me.hop[w] = HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
+            if (nt < T.n_states) {
+                const bool lit = (dn[w].kind_byte & 0xFFu) == WG_KIND_LIT;
+                me.hop[w] = HopState{dn[w].kind_byte & 0xFFu, (dn[w].kind_byte >> 8) & 0xFFu,
+                                     lit ? nt : dn[w].next_a, dn[w].next_b, lit ? dn[w].run : dn[w].max, dn[w].cls};
             }
         }
+        me.class_state = ct != now && (uint32_t)(ct >> kTagLaunchBits) == Cc.epoch ? CLASS_READY : CLASS_SELF;
+        if (claimed && ckpt && me.class_state != CLASS_READY && ct != now) {
+            class_claimed = atomicCAS(&Cc.class_tags[cls], ct, now) == ct;
+            if (class_claimed) me.class_state = CLASS_OWN;
+        }
+    }
+    // the claimers of a wavefront take their arena rows together
+    const unsigned long long cm = __ballot(claimed), km = __ballot(class_claimed);
+    if (cm) {
+        uint32_t first = 0;
+        if (lane == 0) first = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
+        if (lane == 1 && km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
+        first = __shfl(first, 0);
+        if (claimed) {
+            const uint32_t idx = first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
+            me.slot = Cc.cap_rows - env.rows0 > idx ? env.rows0 + idx : kNoSlot;
+            Cc.slots[key] = me.slot;
+        }
+    }
+    if (live) {
+        Cc.row_ref[b] = ref;
+        if (build) Cc.tasks[b] = me;
     }
     const unsigned long long hv = __ballot(hit), lv = __ballot(live);
     if (lane == 0) {
         atomicAdd(&Cc.ctr->lookups, (unsigned long long)__popcll(lv));
-        atomicAdd(&Cc.ctr->hits, (unsigned long long)__popcll(hv));
+        if (hv) atomicAdd(&Cc.ctr->hits, (unsigned long long)__popcll(hv));
     }
 }
 
@@ -305,963 +263,454 @@ lookup_kernel(DeviceTable T, DeviceCache Cc, const wg_state_t *__restrict__ stat
     lookup_one(T, Cc, env, b, live, sid, aux);
 }
 
-// ---------------------------------------------------------------------------------------------
-// class_scan: runs every vocabulary token through one checkpoint's class table (the part of
-// a mask that depends only on the operator's allow / wait sets, hence shared by every state
-// and request using the same sets).  Per token: the first byte that does not stay and its
-// class.  Results: row [stay] = tokens whose bytes all stay, row [end] = tokens that exit on
-// their last byte, and one ExitEntry per token that exits earlier.
-//
-// A workgroup handles one (class table, 2048-token group): the 256-byte table sits in LDS and
-// every lane owns 8 tokens (one in each of its wavefront's 8 slices of 64).  A first look
-// settles most tokens with one instruction or one table look-up each (which one depends on the
-// table: all bytes stay by the token's byte signature, rejected by the first byte, or the first
-// 8 bytes through the table); the rest are queued in LDS and finished byte by byte on full
-// wavefronts.  Rows and exit entries are assembled in LDS and leave in whole runs; the places of
-// the entries in the global lists are taken with four atomics per workgroup.
-
-// Classifies up to 8 bytes of one chunk.  Returns true once the token is decided.
-__device__ __forceinline__ bool scan_chunk(const uint8_t *lut, uint64_t cb, uint32_t L, uint32_t k,
-                                           uint32_t &res, uint32_t &j)
+// advance followed by the lookup of the next step's fill: the new state goes straight from the
+// walker into the cache lookup.
+__global__ void __launch_bounds__(64)
+advance_lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
+                      const int32_t *__restrict__ tokens, uint32_t B)
 {
-    const uint32_t lo = (uint32_t)cb, hi = (uint32_t)(cb >> 32);
-    uint32_t code = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        code |= (uint32_t)lut[(lo >> (8 * i)) & 0xFFu] << (2 * i);
-        code |= (uint32_t)lut[(hi >> (8 * i)) & 0xFFu] << (2 * i + 8);
+    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool live = b < B;
+    const LookupEnv env = lookup_env(Cc);
+    uint32_t sid = 0, aux = 0;
+    if (live) {
+        sid = states[b].sid; aux = states[b].aux;
+        advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
+        states[b].sid = sid; states[b].aux = aux;
     }
-    const uint32_t nvalid = L - 8u * k < 8u ? L - 8u * k : 8u;
-    const uint32_t x = code ^ 0x5555u;               // a 2-bit field is 0 iff its byte stays
-    const uint32_t mm = (x | (x >> 1)) & 0x5555u & ((1u << (2u * nvalid)) - 1u);
-    if (mm) {
-        const uint32_t jj = (uint32_t)__builtin_ctz(mm) >> 1;
-        j = 8u * k + jj;
-        res = (code >> (2u * jj)) & 3u;              // 0 reject, 2 / 3 exit
-        return true;
-    }
-    if (L <= 8u * k + 8u) { res = 1u; return true; } // every byte stays
-    return false;
-}
-
-// Appends the early exits of a wavefront's tokens to the workgroup's staging list in LDS: those
-// with a short remainder from the front, the others from the back (a token leaves at most one
-// entry, so the two ends cannot meet); one LDS atomic per wavefront and end.
-__device__ __forceinline__ void stage_entry(uint2 *ent, uint32_t *n_ent, bool early, uint32_t tok, uint32_t nx,
-                                            uint32_t res, uint32_t first, uint32_t rem)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    const bool is_long = rem > kShortRem;
-    const unsigned long long bx = __ballot(early && !is_long), by = __ballot(early && is_long);
-    if (!(bx | by)) return;
-    uint32_t b0 = 0, b1 = 0;
-    if (lane == 0) {
-        if (bx) b0 = atomicAdd(&n_ent[0], (uint32_t)__popcll(bx));
-        if (by) b1 = atomicAdd(&n_ent[1], (uint32_t)__popcll(by));
-    }
-    b0 = __shfl(b0, 0); b1 = __shfl(b1, 0);
-    if (early) {
-        const uint32_t rank = (uint32_t)__popcll((is_long ? by : bx) & ((1ull << lane) - 1ull));
-        ent[is_long ? kScanGroup - 1u - (b1 + rank) : b0 + rank] = uint2{tok, nx | res << 8 | first << 16 | rem << 24};
-    }
-}
-
-constexpr uint32_t kScanThreads = 256;
-constexpr uint32_t kScanWgs = 5;          // workgroups of class_scan a compute unit holds (its registers)
-constexpr uint32_t kScanPer = kScanGroup / kScanThreads;     // tokens per lane of class_scan
-static_assert(kScanPer * kScanThreads == kScanGroup, "a lane owns a whole number of tokens");
-
-__global__ void __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(5, 8)))
-class_scan_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc)
-{
-    __shared__ __attribute__((aligned(16))) uint8_t lut[256];
-    __shared__ uint32_t row_s[kScanGroup / 32u], row_e[kScanGroup / 32u];   // the group's words of the two rows
-    __shared__ uint2 ent[kScanGroup];                // early exits of the group, from both ends
-    __shared__ uint16_t que[kScanGroup];             // tokens (by their place in the group) the first look did not decide
-    __shared__ uint32_t n_ent[2], n_que;
-    __shared__ uint32_t list_base[2][2];             // where this workgroup's entries start in the two lists
-    const uint32_t n = Cc.ctr->n_class_miss;
-    const uint32_t groups = (Vc.V + kScanGroup - 1u) / kScanGroup;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, tid = threadIdx.x;
-    const uint32_t V = Vc.V;
-    // Workgroups are handed to the 8 XCDs round-robin and each XCD has its own L2.  XCD x takes
-    // the token groups g with g % 8 == x for every class table, so a group's bytes are fetched
-    // into one L2 once and then shared by all tables, instead of once per XCD.
-    const uint32_t nx = gridDim.x < kXcds ? gridDim.x : kXcds;           // a tiny grid uses fewer
-    const uint32_t xcd = blockIdx.x % nx, local = blockIdx.x / nx;
-    const uint32_t local_wgs = (gridDim.x - xcd + nx - 1u) / nx;         // workgroups on this XCD
-    const uint32_t my_groups = groups > xcd ? (groups - xcd + nx - 1u) / nx : 0u;
-    // Work item = (class table ci of the call's list, token group) with the table index in the
-    // upper part, so that which list entry a workgroup reads first depends on its place in the
-    // grid only: it is requested together with the length of the list, not after it.
-    const uint64_t total = (uint64_t)n * my_groups;
-    const uint32_t ci_first = my_groups ? local / my_groups : 0u;
-    const uint32_t c_first = Cc.class_miss[ci_first < Cc.miss_cap ? ci_first : 0u];   // the list has miss_cap places
-    for (uint64_t item = local; item < total; item += local_wgs) {
-        const uint32_t ci = (uint32_t)(item / my_groups);
-        const uint32_t g = (uint32_t)(item % my_groups) * nx + xcd;
-        // What the first look needs of a token does not depend on the table: the signatures and
-        // first bytes of the lane's tokens are requested before the table is known.  A lane owns
-        // kScanPer tokens, one in each of its wavefront's slices of 64, so that a ballot over a
-        // slice is two words of a row.
-        unsigned long long sg[kScanPer];
-        uint32_t fb[kScanPer];
-#pragma unroll
-        for (uint32_t s = 0; s < kScanPer; s++) {
-            const uint32_t tk = g * kScanGroup + (wave * kScanPer + s) * 64u + lane;
-            sg[s] = tk < V ? Vc.sig[tk] : 0ull;
-            fb[s] = tk < V ? Vc.first8[tk] : 0u;
-        }
-        const uint32_t c = item == local ? c_first : Cc.class_miss[ci];
-        uint32_t part = 0;
-#pragma unroll
-        for (uint32_t q = 1; q < kParts; q++) part += g * kScanGroup >= Vc.part_tok[q];
-        __syncthreads();                             // the item before is done with the LDS
-        if (tid < 64u)
-            reinterpret_cast<uint32_t *>(lut)[tid] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)c * 256u)[tid];
-        if (tid < kScanGroup / 32u) row_e[tid] = 0;
-        if (tid == 0) { n_ent[0] = 0; n_ent[1] = 0; n_que = 0; }
-        const uint32_t scan = T.class_info[c].scan;
-        const unsigned long long nonstay = T.class_info[c].nonstay;
-        __syncthreads();
-        // First look, every token.  It settles the tokens whose bytes all stay (a table where
-        // nearly every byte value stays: none of the token's bytes folds onto one that does not),
-        // the tokens rejected by their first byte (a table that rejects most byte values), or what
-        // the first 8 bytes settle without leaving an exit entry; every other token is queued,
-        // so that the byte-by-byte work runs on full wavefronts.
-        unsigned long long qm[kScanPer];             // per slice: the lanes whose token is queued
-        uint32_t n_mine = 0;                         // queued tokens of this wavefront
-#pragma unroll
-        for (uint32_t s = 0; s < kScanPer; s++) {
-            const uint32_t tk = g * kScanGroup + (wave * kScanPer + s) * 64u + lane;
-            const bool valid = tk < V;
-            bool stays = false, ends = false, queued = false;
-            if (scan == SCAN_SIG) {
-                queued = valid && (sg[s] & nonstay) != 0ull;
-                stays = valid && !queued;
-            } else if (scan == SCAN_HEAD) {
-                queued = valid && lut[fb[s]] != CLS_REJECT;
-            } else if (valid) {
-                const uint32_t L = Vc.len8[tk];
-                uint32_t res = 0, j = 0;
-                const bool decided = L == 0u || scan_chunk(lut, Vc.chunks[tk], L, 0, res, j);
-                stays = decided && res == 1u;
-                ends = decided && res >= 2u && j + 1u == L;
-                queued = !decided || (res >= 2u && j + 1u < L);
-            }
-            const unsigned long long bs = __ballot(stays), be = __ballot(ends);
-            if (lane == 0) {
-                row_s[(wave * kScanPer + s) * 2u] = (uint32_t)bs; row_s[(wave * kScanPer + s) * 2u + 1u] = (uint32_t)(bs >> 32);
-                if (be) { row_e[(wave * kScanPer + s) * 2u] = (uint32_t)be; row_e[(wave * kScanPer + s) * 2u + 1u] = (uint32_t)(be >> 32); }
-            }
-            qm[s] = __ballot(queued);
-            n_mine += (uint32_t)__popcll(qm[s]);
-        }
-        {
-            // the wavefront's queued tokens take their places together: one LDS atomic, then a
-            // token's place is the wavefront's first place, plus the queued tokens of the slices
-            // before, plus the queued lanes below in its own slice
-            uint32_t qb = 0;
-            if (lane == 0 && n_mine) qb = atomicAdd(&n_que, n_mine);
-            qb = __shfl(qb, 0);
-#pragma unroll
-            for (uint32_t s = 0; s < kScanPer; s++) {
-                if ((qm[s] >> lane) & 1ull)
-                    que[qb + (uint32_t)__popcll(qm[s] & ((1ull << lane) - 1ull))] = (uint16_t)((wave * kScanPer + s) * 64u + lane);
-                qb += (uint32_t)__popcll(qm[s]);
-            }
-        }
-        __syncthreads();
-        // Second look: the queued tokens byte by byte, one per thread and round.
-        const uint32_t nq = n_que;
-        for (uint32_t i0 = 0; i0 < nq; i0 += kScanThreads) {
-            const bool act = i0 + tid < nq;
-            const uint32_t idx = que[act ? i0 + tid : 0u];
-            const uint32_t tok = g * kScanGroup + idx;           // below V
-            const uint32_t Lq = act ? Vc.len8[tok] : 0u;
-            // (all three chunks are requested at once, whatever the length: no load waits for another)
-            const uint64_t d0 = Vc.chunks[tok];
-            const uint64_t d1 = Vc.chunks[(Vc.n_chunks > 1u ? (size_t)V : 0u) + tok];
-            const uint64_t d2 = Vc.chunks[(Vc.n_chunks > 2u ? 2ull * V : 0ull) + tok];
-            uint32_t res = 0, j = 0;
-            if (Lq) {
-                bool decided = scan_chunk(lut, d0, Lq, 0, res, j);
-                if (!decided) decided = scan_chunk(lut, d1, Lq, 1, res, j);
-                if (!decided) decided = scan_chunk(lut, d2, Lq, 2, res, j);
-                for (uint32_t k = 3; k < Vc.n_chunks && !decided; k++)
-                    decided = scan_chunk(lut, Vc.chunks[(size_t)k * V + tok], Lq, k, res, j);
-            }
-            const bool exits = res >= 2u;
-            if (res == 1u) atomicOr(&row_s[idx >> 5], 1u << (idx & 31u));
-            if (exits && j + 1u == Lq) atomicOr(&row_e[idx >> 5], 1u << (idx & 31u));
-            const uint32_t nxt = j + 1u;
-            const bool early = exits && nxt < Lq;
-            uint32_t first = 0;
-            if (early) {
-                if (nxt < 24u) {
-                    const uint64_t cw = nxt < 8u ? d0 : nxt < 16u ? d1 : d2;
-                    first = (uint32_t)(cw >> (8u * (nxt & 7u))) & 0xFFu;
-                } else first = Vc.bytes[Vc.offsets[tok] + nxt];
-            }
-            stage_entry(ent, n_ent, early, tok, nxt, res, first, Lq - nxt);
-        }
-        __syncthreads();
-        // Out: the workgroup's entries go to two lists, the one of the whole class table (first V
-        // slots of the class's buffer), read by keys that are built by one workgroup, and the one
-        // of its token range (second V slots, range p owning [V + part_tok[p], V + part_tok[p+1])),
-        // read by the work items of keys that are cut by range; short remainders fill a list from
-        // the front, long ones from the back, so that a wavefront of key_build walks remainders of
-        // similar length.  The four places are taken with four atomics that are in flight together.
-        const uint32_t n_short = n_ent[0], n_long = n_ent[1];
-        if (tid < 4u) {
-            const uint32_t side = tid & 1u, which = tid >> 1;              // which: 0 class, 1 range
-            const uint32_t cnt = side ? n_long : n_short;
-            const uint32_t ctr = which ? 2u + 2u * part + side : side;
-            list_base[which][side] = cnt ? atomicAdd(&Cc.class_count[c * kCountStride + ctr], cnt) : 0u;
-        }
-        __syncthreads();
-        uint2 *out = reinterpret_cast<uint2 *>(Cc.class_entries[c]);
-        const uint32_t out_lo = V + Vc.part_tok[part], out_hi = V + Vc.part_tok[part + 1u];
-        for (uint32_t i = tid; i < n_short; i += kScanThreads) {
-            const uint2 e = ent[i];
-            out[list_base[0][0] + i] = e;
-            out[out_lo + list_base[1][0] + i] = e;
-        }
-        for (uint32_t i = tid; i < n_long; i += kScanThreads) {
-            const uint2 e = ent[kScanGroup - 1u - i];
-            out[V - 1u - (list_base[0][1] + i)] = e;
-            out[out_hi - 1u - (list_base[1][1] + i)] = e;
-        }
-        // the three rows of the class index: all bytes stay, exit on the last byte, and their union
-        if (tid < kScanGroup / 32u) {
-            const uint32_t w = g * (kScanGroup / 32u) + tid;
-            if (w < Vc.W) {
-                uint32_t *rows = Cc.class_rows + (size_t)(3u * c) * Cc.row_stride;
-                const uint32_t a = row_s[tid], b = row_e[tid];
-                rows[w] = a; rows[Cc.row_stride + w] = b; rows[2u * Cc.row_stride + w] = a | b;
-            }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && n) atomicAdd(&Cc.ctr->class_scans, (unsigned long long)n);
+    lookup_one(T, Cc, env, b, live, sid, aux);
 }
 
 // ---------------------------------------------------------------------------------------------
-// class_scan for a call that brings many class tables: a workgroup takes a 2048-token group
-// through up to kScanBatch tables together.  What a table-by-table pass pays once per table --
-// the chain first look -> queue -> byte-by-byte look -> list places -> stores, each link a trip
-// to memory -- is paid once per batch, and the byte-by-byte look runs on the queued tokens of
-// all the batch's tables, so on full wavefronts.
+// Masking a stretch of one row's logits: -inf over the tokens [lo, hi) whose bit is 0.  `row` is in
+// LDS, its bit 0 is token `base`; the whole workgroup calls it.
 //
-// The first look takes 32 tokens at a time, from the vocabulary's rows by byte value: the tokens
-// that contain a byte which does not stay are the OR of the rows of those bytes, and every other
-// token with bytes is all-stay; of the former, the tokens whose first byte is not rejected (an OR
-// of first-byte rows, of the rejected bytes and complemented when those are fewer) are queued,
-// the others are rejected by their first byte.  A side with more than kScanRowsMax rows lets
-// every token through instead, which costs work, not correctness: the queue may hold any token,
-// the byte-by-byte look decides.  That look has two stages: the first 8 bytes of every queued
-// token, then the longer tokens those 8 bytes did not decide, queued again so that they too fill
-// their wavefronts.
-// Results are the ones class_scan_kernel leaves (rows, lists, counters); the order of entries
-// inside a list differs, which no reader depends on.
-constexpr uint32_t kScanBatch = 8;        // class tables of one work item
-constexpr uint32_t kScanQueue = 4096;     // places of the queue for the byte-by-byte look
-constexpr uint32_t kScanLong = 1024;      // places of the queue for its second stage
-constexpr uint32_t kScanStage = 768;      // exit entries held in LDS before they leave
-constexpr uint32_t kScanRowsMax = 64;     // most rows ORed for one side of a table's first look
-constexpr uint32_t kScanRowsUnroll = 8;   // rows a wavefront requests together
-constexpr uint32_t kScanFixed = 3;        // what a work item costs before its first table, in tables
-constexpr uint32_t kScanBatchWgs = 5;     // workgroups of this kernel a compute unit holds (its LDS and registers)
-constexpr uint32_t kScanBatchFrom = 4096; // (class tables of a handle) x (token groups) above which it takes this kernel
-static_assert(kScanBatch <= 8u && kScanGroup <= 2048u, "a queue place holds table and token in 14 bits");
-static_assert(kScanStage <= 4096u && kScanThreads <= kScanStage, "the rank of a staged entry has 12 bits; a round's entries fit");
-static_assert(kScanThreads <= kScanLong && kScanGroup <= kScanQueue, "a round fits the second queue, a table's tokens the first");
-
-__global__ void __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(5, 8)))
-class_scan_batch_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc)
+// Nothing is read from the logits where it can be helped: a 16-byte piece with no allowed token is
+// overwritten, an untouched one is skipped, a mixed one gets one store per disallowed token
+// (found by count-trailing-zeros: a piece of a free-text row has one or two).  Such a store covers
+// part of a 64-byte block, which the last-level cache (256 MB) merges as long as the logits fit it;
+// beyond that the memory reads and writes the block.  kLine is for that case: every 128-byte line
+// with a disallowed token is read where it has to be and written whole, 8 lanes x 16 bytes.
+// Rows may start at any element: the pieces are cut where the addresses allow 16-byte stores, the
+// tokens before and behind them are stored one by one.
+template <typename Elem, bool kLine>
+__device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi, uint32_t base, const uint32_t *row)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lut[kScanBatch][256];
-    __shared__ uint32_t row_s[kScanBatch][kScanGroup / 32u], row_e[kScanBatch][kScanGroup / 32u];
-    __shared__ uint2 ent[kScanStage];                // early exits of the batch's tables, in the order found
-    __shared__ uint16_t meta[kScanStage];            // of a staged entry: table | long << 3 | rank in (table, side) << 4
-    __shared__ uint16_t que[kScanQueue];             // table << 11 | the token's place in the group
-    __shared__ uint16_t que_long[kScanLong];         // the same, tokens the first 8 bytes did not decide
-    __shared__ uint32_t acc[kScanBatch][2][kScanGroup / 32u];   // the ORs of the first look: [0] has a byte that does not stay, [1] by first byte
-    __shared__ uint16_t row_list[kScanBatch * 2u * kScanRowsMax];   // the rows to OR: table << 9 | row of byte_rows
-    __shared__ uint8_t first_inv[kScanBatch];        // the first-byte OR is of the rejected bytes
-    __shared__ uint32_t cls_s[kScanBatch];
-    __shared__ uint32_t n_ent[kScanBatch][2], list_base[kScanBatch][2][2];
-    __shared__ uint32_t n_rows, n_que, n_long, n_stage;
-    const uint32_t n = Cc.ctr->n_class_miss;
-    if (n == 0) return;
-    const uint32_t groups = (Vc.V + kScanGroup - 1u) / kScanGroup;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, tid = threadIdx.x;
-    const uint32_t V = Vc.V;
-    // how many of the lanes before this one are set in a ballot
+    constexpr uint32_t kPer = 16u / sizeof(Elem);                  // tokens of a piece
+    constexpr uint32_t kAlign = kLine ? 128u : 16u;
+    constexpr uint32_t kBatch = 4u;                                // pieces of a thread in flight together
+    constexpr uint32_t kAll = (1u << kPer) - 1u;
+    constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
+    constexpr uint32_t kFill = sizeof(Elem) == 4 ? 0xFF800000u : 0xFF80FF80u;
+    const uint32_t tid = threadIdx.x, nt = blockDim.x;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(logits + lo);
+    uint32_t head = at % sizeof(Elem) ? hi - lo : (uint32_t)((kAlign - at % kAlign) % kAlign / sizeof(Elem));
+    if (head > hi - lo) head = hi - lo;
+    const uint32_t t0 = lo + head, pieces = (hi - t0) / kPer, t1 = t0 + pieces * kPer;
+    auto disallowed = [&](uint32_t t) { return !((row[(t - base) >> 5] >> ((t - base) & 31u)) & 1u); };
+    for (uint32_t i = tid; i < head; i += nt) if (disallowed(lo + i)) logits[lo + i] = kNinf;
+    for (uint32_t t = t1 + tid; t < hi; t += nt) if (disallowed(t)) logits[t] = kNinf;
+    const uint32_t off = t0 - base;
+    for (uint32_t p0 = 0; p0 < pieces; p0 += nt * kBatch) {
+        uint32_t z[kBatch];                                        // disallowed tokens of the pieces
+#pragma unroll
+        for (uint32_t i = 0; i < kBatch; i++) {
+            const uint32_t p = p0 + i * nt + tid, bit = off + p * kPer;
+            // (the word behind the row's last one is there to be read)
+            z[i] = p < pieces ? ~__builtin_amdgcn_alignbit(row[(bit >> 5) + 1u], row[bit >> 5], bit & 31u) & kAll : 0u;
+        }
+        if (kLine) {
+            uint4 v[kBatch];
+            bool put[kBatch];
+            const unsigned long long line = 0xFFull << (tid & 56u);
+#pragma unroll
+            for (uint32_t i = 0; i < kBatch; i++) {
+                const uint32_t p = p0 + i * nt + tid;
+                put[i] = p < pieces && (__ballot(z[i] != 0u) & line);
+                v[i] = uint4{0u, 0u, 0u, 0u};
+                if (put[i] && z[i] != kAll) v[i] = *reinterpret_cast<const uint4 *>(logits + t0 + (size_t)p * kPer);
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < kBatch; i++) {
+                if (!put[i]) continue;
+                uint32_t d[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                for (uint32_t k = 0; k < 4u; k++) {
+                    uint32_t m;
+                    if (sizeof(Elem) == 4) m = (uint32_t)__builtin_amdgcn_sbfe(z[i], k, 1);
+                    else m = ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k, 1) & 0xFFFFu) | ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k + 1, 1) << 16);
+                    d[k] = (d[k] & ~m) | (kFill & m);
+                }
+                *reinterpret_cast<uint4 *>(logits + t0 + (size_t)(p0 + i * nt + tid) * kPer) = uint4{d[0], d[1], d[2], d[3]};
+            }
+        } else {
+#pragma unroll
+            for (uint32_t i = 0; i < kBatch; i++) {
+                Elem *p = logits + t0 + (size_t)(p0 + i * nt + tid) * kPer;
+                if (z[i] == kAll) *reinterpret_cast<uint4 *>(p) = uint4{kFill, kFill, kFill, kFill};
+                else while (z[i]) { p[__builtin_ctz(z[i])] = kNinf; z[i] &= z[i] - 1u; }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// rows: a workgroup per (request, share of the token ranges).  A row made in an earlier call is
+// copied; a missing one is made in LDS from the request's task and the vocabulary's static
+// indexes, each workgroup making the words of its own tokens:
+//   a literal state admits the tokens that begin with its byte and go on with what follows it:
+//     candidates by the first two bytes (or by the first byte, where a checkpoint follows);
+//   a checkpoint admits tokens whose bytes all stay, tokens that leave it with their last byte
+//     (these two depend on its class table only, and are kept per table), and tokens that leave it
+//     earlier and go on in the successor.  A table that few byte values enter (kFewLive) takes every
+//     token that begins with one of them as a candidate and decides it from its bytes.  Any other
+//     table gets its all-stay tokens 32 at a time, as the complement of the OR of the rows of the
+//     byte values that do not stay; the tokens that leave with their last byte are found by that
+//     byte, those that leave earlier by the exit byte and the literal byte behind it (or, where a
+//     checkpoint follows, by the exit byte).
+// Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
+// that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
+// stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
+// what is left in LDS and decides them 64 at a time, so that the walks run on full wavefronts.
+constexpr uint32_t kRowThreads = 256;
+constexpr uint32_t kRowWaves = kRowThreads / 64u;
+constexpr uint32_t kRowBatch = 4;          // index entries of a lane in flight together
+constexpr uint32_t kRanges = 256;          // index ranges of a key: at most one per byte value
+constexpr uint32_t kAlone = 128;           // candidates that one wavefront sees to, while the others do the rows
+constexpr uint32_t kOrBatch = 4;           // token rows in flight together,
+constexpr uint32_t kOrWords = 4;           // for this many words of a thread
+
+enum : uint32_t {
+    FROM_PREFIX = 1,    // sorted, by two bytes
+    FROM_STAY = 2,      // by first byte, which stays
+    FROM_A = 3,         // by first byte, which leaves through A (or is the literal state's own)
+    FROM_B = 4,
+    FROM_PAIR = 5,      // by exit byte and the literal byte behind it
+    FROM_DEEP_A = 6,    // by exit byte (and range), a checkpoint behind it
+    FROM_DEEP_B = 7,
+};
+
+typedef __attribute__((address_space(1))) uint2 global_u2;   // a load known to go to device memory
+
+struct RowShared {
+    uint8_t own[256], hop[2][256];             // class tables of the state and of its successors
+    uint32_t start[kRanges], upto[kRanges];    // first entry of a range, candidates up to its end
+    uint16_t code[kRanges];                    // byte value | FROM_* << 8
+    uint32_t queue[kRowWaves][64u * (kRowBatch + 1u)];   // tokens to decide: id | length << 24
+    uint32_t n_ranges, total;
+};
+
+// Inclusive prefix sum over the wavefront, in registers (every lane calls it).
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);    // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);    // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);    // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);    // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // last lane of row 0 / 2 into row 1 / 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // lane 31 into the upper half
+    return x;
+}
+
+__device__ __forceinline__ bool is_checkpoint(uint32_t kind) { return kind == WG_KIND_WAIT || kind == WG_KIND_COND; }
+
+// The first 24 bytes of the literal run a state lies in, held by every lane.
+struct RunBytes { uint64_t w[3]; };
+__device__ __forceinline__ RunBytes run_bytes(const DeviceTable &T, uint32_t sid)
+{
+    // (16 zero bytes lie behind the last state's literal byte; a run ends before them)
+    const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
+    const uint32_t q = sid >> 3, sh = (sid & 7u) * 8u, last = (T.n_states >> 3) + 1u;
+    uint64_t x[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; k++) x[k] = lit64[q + k < last ? q + k : last];
+    RunBytes r;
+#pragma unroll
+    for (uint32_t k = 0; k < 3u; k++) r.w[k] = sh ? (x[k] >> sh) | (x[k + 1u] << (64u - sh)) : x[k];
+    return r;
+}
+
+// Walks bytes [i, L), i < L, of a token from a literal state with `run` bytes to go, its first 24 in
+// `lit`, then the state table from the state `after` them.
+__device__ __forceinline__ bool walk_run(const DeviceTable &T, const RunBytes &lit, uint32_t sid, uint32_t run, uint32_t after,
+                                         TokenBytes &t, uint32_t i, uint32_t L)
+{
+    const uint32_t n = L - i < run ? L - i : run;
+#pragma unroll
+    for (uint32_t k = 0; k < 3u; k++) {
+        if (8u * k >= n) break;
+        const uint32_t m = n - 8u * k;
+        const uint64_t mask = m >= 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
+        if ((window(t, i + 8u * k) ^ lit.w[k]) & mask) return false;
+    }
+    uint32_t aux = 0;
+    if (n <= 24u) { sid = n == run ? after : sid + n; i += n; }
+    else { sid += 24u; i += 24u; }
+    return walk(T, sid, aux, t, i, L);
+}
+
+// Walks bytes [i, L), i < L, of a token from the staged successor; goes on through the state table
+// when the token moves on to a third state.
+__device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h, const uint8_t *lut, const RunBytes &lit,
+                                         TokenBytes &t, uint32_t i, uint32_t L)
+{
+    uint32_t sid = WG_SID_ERROR, aux = 0;
+    if (h.kind == WG_KIND_LIT) return walk_run(T, lit, h.next_a, h.max, h.cls, t, i, L);
+    if (is_checkpoint(h.kind)) {
+        for (;;) {
+            const uint32_t n = L - i < 8u ? L - i : 8u;
+            const uint32_t code = class_code(lut, window(t, i)), stays = first_leaving(code, n);
+            if (h.max != WG_UNBOUNDED) { if (stays > h.max - aux) return false; aux += stays; }
+            i += stays;
+            if (stays < n) {
+                const uint32_t c = (code >> (2u * stays)) & 3u;
+                if (c == CLS_REJECT) return false;
+                sid = c == CLS_EXIT_A ? h.next_a : h.next_b;
+                i++;
+                break;
+            }
+            if (i >= L) return true;
+        }
+    } else return false;
+    aux = 0;
+    return walk(T, sid, aux, t, i, L);
+}
+
+// First token of range p (as part_tok says; computed, because an array in a kernel argument is not
+// indexed in registers).
+__device__ __forceinline__ uint32_t range_token(const DeviceVocab &Vc, uint32_t p)
+{
+    const uint32_t groups = (Vc.V + kPartGroup - 1u) / kPartGroup, t = p * groups / kParts * kPartGroup;
+    return p >= kParts || t > Vc.V ? Vc.V : t;
+}
+
+// The words [w_lo, w_hi) of a missing row are row[] | early[] (LDS, word 0 = w_lo): early holds what
+// the candidates add, row the rest, so that the two are made side by side.
+__device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, RowShared &sh,
+                                         const RowTask &me, const HopState &ha, const HopState &hb, uint32_t p0, uint32_t span,
+                                         uint32_t w_lo, uint32_t w_hi, uint32_t *row, uint32_t *early, uint32_t b)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t n_words = w_hi - w_lo, rs = Cc.row_stride;
+    const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
+    const bool literal = me.kind == WG_KIND_LIT, ckpt = is_checkpoint(me.kind);
+    const bool ckpt_a = is_checkpoint(ha.kind), ckpt_b = is_checkpoint(hb.kind);
+    // the literal byte behind an exit, or a value no byte has
+    const uint32_t lit_a = ha.kind == WG_KIND_LIT ? ha.lit : 0x100u, lit_b = hb.kind == WG_KIND_LIT ? hb.lit : 0x100u;
     auto before = [](unsigned long long bal) {
         return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
     };
-    // (the same hand-out of token groups to XCDs as in class_scan_kernel)
-    const uint32_t nx = gridDim.x < kXcds ? gridDim.x : kXcds;
-    const uint32_t xcd = blockIdx.x % nx, local = blockIdx.x / nx;
-    const uint32_t local_wgs = (gridDim.x - xcd + nx - 1u) / nx;
-    const uint32_t my_groups = groups > xcd ? (groups - xcd + nx - 1u) / nx : 0u;
-    // Tables per work item.  The launch is one workgroup per place the chip has for this kernel,
-    // and a workgroup takes every local_wgs-th item of its XCD; an item costs a fixed part (the
-    // trips to memory of its chain) and a part per table.  The number of tables is the one under
-    // which the busiest XCD is done soonest by that count.
-    uint32_t per = Cc.scan_batch;
-    if (!per) {
-        const uint32_t most_groups = (groups + nx - 1u) / nx, fewest_wgs = gridDim.x / nx ? gridDim.x / nx : 1u;
-        uint32_t best = 0xFFFFFFFFu;
-        for (uint32_t p = 1; p <= kScanBatch; p++) {
-            const uint64_t wide = (uint64_t)((n + p - 1u) / p) * most_groups;
-            const uint32_t items = wide > 0x7FFFFFFFull ? 0x7FFFFFFFu : (uint32_t)wide;
-            const uint32_t cost = ((items + fewest_wgs - 1u) / fewest_wgs) * (kScanFixed + p);
-            if (cost < best) { best = cost; per = p; }
-        }
-    }
-    per = per < 1u ? 1u : per > kScanBatch ? kScanBatch : per;
-    const uint32_t batches = (n + per - 1u) / per;
-    const uint64_t total = (uint64_t)batches * my_groups;
-    for (uint64_t item = local; item < total; item += local_wgs) {
-        const uint32_t t0 = (uint32_t)(item / my_groups) * per;
-        const uint32_t nt = n - t0 < per ? n - t0 : per;
-        const uint32_t g = (uint32_t)(item % my_groups) * nx + xcd;
-        // the tokens of this thread's word of the group that have bytes (none beyond V)
-        const uint32_t word_hb = g * (kScanGroup / 32u) + (tid >> 2);
-        const uint32_t has_bytes = word_hb < Vc.row_stride ? Vc.len_rows[(size_t)(Vc.lmax + 1u) * Vc.row_stride + word_hb] : 0u;
-        uint32_t part = 0;
-#pragma unroll
-        for (uint32_t q = 1; q < kParts; q++) part += g * kScanGroup >= Vc.part_tok[q];
-        const uint32_t out_lo = V + Vc.part_tok[part], out_hi = V + Vc.part_tok[part + 1u];
-        if (tid == 0) { n_rows = 0; n_que = 0; n_long = 0; n_stage = 0; }   // (the item before is past their last use)
-        __syncthreads();                             // the item before is done with the LDS
-        // The tables come in, a wavefront one table at a time, a lane 4 of its byte values; what
-        // the lanes see of the table says which rows its first look ORs.
-        for (uint32_t i = tid; i < nt * 64u; i += kScanThreads) {
-            const uint32_t t = i >> 6;               // (the same for the whole wavefront)
-            const uint32_t c = Cc.class_miss[t0 + t];
-            const uint32_t cw = reinterpret_cast<const uint32_t *>(T.classes + (size_t)c * 256u)[lane];
-            reinterpret_cast<uint32_t *>(lut[t])[lane] = cw;
-            unsigned long long moves[4], lives[4];   // per byte value 4 * lane + k: does not stay / is not rejected
-            uint32_t n_moves = 0, n_lives = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < 4u; k++) {
-                const uint32_t cl = (cw >> (8u * k)) & 0xFFu;
-                moves[k] = __ballot(cl != CLS_STAY);
-                lives[k] = __ballot(cl != CLS_REJECT);
-                n_moves += (uint32_t)__popcll(moves[k]);
-                n_lives += (uint32_t)__popcll(lives[k]);
-            }
-            const bool all_a = n_moves > kScanRowsMax;
-            const bool inv = n_lives > kScanRowsMax, all_b = inv && 256u - n_lives > kScanRowsMax;
-            const uint32_t cnt_a = all_a ? 0u : n_moves, cnt_b = all_b ? 0u : inv ? 256u - n_lives : n_lives;
-            row_e[t][lane] = 0;
-            acc[t][0][lane] = all_a ? 0xFFFFFFFFu : 0u;
-            acc[t][1][lane] = all_b ? 0xFFFFFFFFu : 0u;
-            uint32_t at = 0;
-            if (lane == 0) {
-                cls_s[t] = c; n_ent[t][0] = 0; n_ent[t][1] = 0; first_inv[t] = inv && !all_b;
-                if (cnt_a + cnt_b) at = atomicAdd(&n_rows, cnt_a + cnt_b);
-            }
-            at = __shfl(at, 0);
-#pragma unroll
-            for (uint32_t k = 0; k < 4u; k++) {
-                if (!all_a) {
-                    if ((moves[k] >> lane) & 1ull)
-                        row_list[at + before(moves[k])] = (uint16_t)(t << 9 | (4u * lane + k));
-                    at += (uint32_t)__popcll(moves[k]);
-                }
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 4u; k++) {
-                if (!all_b) {
-                    const unsigned long long pick = inv ? ~lives[k] : lives[k];
-                    if ((pick >> lane) & 1ull)
-                        row_list[at + before(pick)] = (uint16_t)(t << 9 | 256u | (4u * lane + k));
-                    at += (uint32_t)__popcll(pick);
-                }
-            }
-        }
-        __syncthreads();
-
-        uint32_t stage_bound = 0, que_bound = 0, long_bound = 0;   // no fewer than n_stage / n_que / n_long, known without a look
-        // The staged entries leave: per table and side, a run in the list of the whole table and a
-        // run in the list of the token range, their places taken with one atomic each.
-        // (Called by the whole workgroup, after a barrier that follows the last staged entry.)
-        auto flush = [&]() {
-            const uint32_t ns = n_stage;
-            if (tid < nt * 4u) {
-                const uint32_t t = tid >> 2, side = tid & 1u, which = (tid >> 1) & 1u;
-                const uint32_t cnt = n_ent[t][side];
-                const uint32_t ctr = which ? 2u + 2u * part + side : side;
-                list_base[t][which][side] = cnt ? atomicAdd(&Cc.class_count[cls_s[t] * kCountStride + ctr], cnt) : 0u;
-            }
-            __syncthreads();
-            for (uint32_t i = tid; i < ns; i += kScanThreads) {
-                const uint2 e = ent[i];
-                const uint32_t m = meta[i], t = m & 7u, r = m >> 4;
-                uint2 *out = reinterpret_cast<uint2 *>(Cc.class_entries[cls_s[t]]);
-                if (!(m & 8u)) {
-                    out[list_base[t][0][0] + r] = e;
-                    out[out_lo + list_base[t][1][0] + r] = e;
-                } else {
-                    out[V - 1u - (list_base[t][0][1] + r)] = e;
-                    out[out_hi - 1u - (list_base[t][1][1] + r)] = e;
-                }
-            }
-            __syncthreads();
-            if (tid < nt * 2u) n_ent[tid >> 1][tid & 1u] = 0;
-            if (tid == 0) n_stage = 0;
-            stage_bound = 0;
-            __syncthreads();
-        };
-        // Room in the staging list for the entries of one more round (every thread takes the same way).
-        auto stage_room = [&]() {
-            if (stage_bound + kScanThreads > kScanStage) {
-                // count exactly, between two barriers so that every thread reads the same number
-                __syncthreads();
-                const uint32_t staged = n_stage;
-                __syncthreads();
-                if (staged + kScanThreads > kScanStage) flush();
-                else stage_bound = staged;
-            }
-            stage_bound += kScanThreads;
-        };
-        // What the byte-by-byte look found for a token goes to the rows and the staging list: the
-        // first byte that does not stay is byte j with class res (1: none, all bytes stay).
-        auto settle = [&](uint32_t t, uint32_t idx, uint32_t tok, uint32_t Lq, uint32_t res, uint32_t j, uint32_t first) {
-            const bool exits = res >= 2u;
-            if (res == 1u) atomicOr(&row_s[t][idx >> 5], 1u << (idx & 31u));
-            if (exits && j + 1u == Lq) atomicOr(&row_e[t][idx >> 5], 1u << (idx & 31u));
-            const uint32_t nxt = j + 1u;
-            const bool early = exits && nxt < Lq;
-            const unsigned long long be = __ballot(early);
-            if (!be) return;
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&n_stage, (uint32_t)__popcll(be));
-            base = __shfl(base, 0);
-            if (early) {
-                const uint32_t rem = Lq - nxt, side = rem > kShortRem;
-                const uint32_t r = atomicAdd(&n_ent[t][side], 1u);
-                const uint32_t at = base + before(be);
-                ent[at] = uint2{tok, nxt | res << 8 | first << 16 | rem << 24};
-                meta[at] = (uint16_t)(t | side << 3 | r << 4);
-            }
-        };
-        // Second stage: the tokens longer than 8 bytes whose first 8 all stay, from byte 8 on.
-        // (Called by the whole workgroup, after a barrier that follows the last write to its queue.)
-        auto drain_long = [&]() {
-            const uint32_t nl = n_long;
-            __syncthreads();                         // every thread has read the length
-            for (uint32_t i0 = 0; i0 < nl; i0 += kScanThreads) {
-                stage_room();
-                if (i0 + wave * 64u >= nl) continue;                    // nothing for this wavefront in the last round
-                const bool act = i0 + tid < nl;
-                const uint32_t q = que_long[act ? i0 + tid : 0u];
-                const uint32_t t = q >> 11, idx = q & (kScanGroup - 1u);
-                const uint32_t tok = g * kScanGroup + idx;               // below V
-                const uint32_t Lq = act ? Vc.len8[tok] : 0u;             // above 8
-                const uint64_t d1 = Vc.chunks[(Vc.n_chunks > 1u ? (size_t)V : 0u) + tok];
-                const uint64_t d2 = Vc.chunks[(Vc.n_chunks > 2u ? 2ull * V : 0ull) + tok];
-                uint32_t res = 0, j = 0;
-                if (Lq) {
-                    bool decided = scan_chunk(lut[t], d1, Lq, 1, res, j);
-                    if (!decided) decided = scan_chunk(lut[t], d2, Lq, 2, res, j);
-                    for (uint32_t k = 3; k < Vc.n_chunks && !decided; k++)
-                        decided = scan_chunk(lut[t], Vc.chunks[(size_t)k * V + tok], Lq, k, res, j);
-                }
-                uint32_t first = 0;
-                if (res >= 2u && j + 1u < Lq) {
-                    const uint32_t nxt = j + 1u;
-                    if (nxt < 24u) first = (uint32_t)((nxt < 16u ? d1 : d2) >> (8u * (nxt & 7u))) & 0xFFu;
-                    else first = Vc.bytes[Vc.offsets[tok] + nxt];
-                }
-                settle(t, idx, tok, Lq, res, j, first);
-            }
-            __syncthreads();                         // the rounds are over
-            if (tid == 0) n_long = 0;
-            long_bound = 0;
-            __syncthreads();
-        };
-        // First stage: the first 8 bytes of every queued token, one token per thread and round.
-        // (Called by the whole workgroup, after a barrier that follows the last write to the queue.)
-        auto drain = [&]() {
-            const uint32_t nq = n_que;
-            __syncthreads();                         // every thread has read the length
-            // what a round needs of its tokens is requested a round ahead, so that the trip to
-            // memory of one round runs under the work of the round before
-            uint32_t q_next = 0, L_next = 0;
-            uint64_t d_next = 0;
-            auto request = [&](uint32_t i0) {
-                const bool act = i0 + tid < nq;
-                q_next = que[act ? i0 + tid : 0u];
-                const uint32_t tok = g * kScanGroup + (q_next & (kScanGroup - 1u));   // below V
-                L_next = act ? Vc.len8[tok] : 0u;
-                d_next = Vc.chunks[tok];
-            };
-            if (nq) request(0u);
-            for (uint32_t i0 = 0; i0 < nq; i0 += kScanThreads) {
-                if (long_bound + kScanThreads > kScanLong) {
-                    // the second queue may be short of room for a round: count exactly, empty it if need be
-                    __syncthreads();
-                    const uint32_t waiting = n_long;
-                    __syncthreads();
-                    if (waiting + kScanThreads > kScanLong) drain_long();
-                    else long_bound = waiting;
-                }
-                long_bound += kScanThreads;
-                stage_room();                        // (after the second stage may have run: it stages entries too)
-                const uint32_t q = q_next, Lq = L_next;
-                const uint64_t d0 = d_next;
-                if (i0 + kScanThreads < nq) request(i0 + kScanThreads);
-                if (i0 + wave * 64u >= nq) continue;                    // nothing for this wavefront in the last round
-                const uint32_t t = q >> 11, idx = q & (kScanGroup - 1u);
-                const uint32_t tok = g * kScanGroup + idx;
-                uint32_t res = 0, j = 0;
-                const bool decided = Lq == 0u || scan_chunk(lut[t], d0, Lq, 0, res, j);
-                // undecided: to the second queue
-                const unsigned long long bu = __ballot(!decided);
-                if (bu) {
-                    uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&n_long, (uint32_t)__popcll(bu));
-                    base = __shfl(base, 0);
-                    if (!decided) que_long[base + before(bu)] = (uint16_t)q;
-                }
-                uint32_t first = 0;
-                if (decided && res >= 2u && j + 1u < Lq) {
-                    const uint32_t nxt = j + 1u;     // at most 8
-                    first = nxt < 8u ? (uint32_t)(d0 >> (8u * nxt)) & 0xFFu : (uint32_t)Vc.chunks[(size_t)V + tok] & 0xFFu;
-                }
-                settle(t, idx, tok, decided ? Lq : 0u, decided ? res : 0u, j, first);
-            }
-            __syncthreads();                         // the rounds are over: the second queue is written
-            if (tid == 0) n_que = 0;
-            que_bound = 0;
-            __syncthreads();
-        };
-
-        // First look, the ORs: a lane takes one word (32 tokens) of the group, a wavefront every
-        // fourth stretch of kScanRowsUnroll rows of the list, requested together; the ORs meet in LDS.
-        {
-            const uint32_t gw = g * (kScanGroup / 32u) + lane;
-            const bool in_row = gw < Vc.row_stride;
-            const uint32_t nr = n_rows;
-            for (uint32_t base = wave * kScanRowsUnroll; base < nr; base += 4u * kScanRowsUnroll) {
-                uint32_t code[kScanRowsUnroll], x[kScanRowsUnroll];
-#pragma unroll
-                for (uint32_t u = 0; u < kScanRowsUnroll; u++) {
-                    code[u] = row_list[base + u < nr ? base + u : base];
-                    x[u] = in_row ? Vc.byte_rows[(size_t)(code[u] & 511u) * Vc.row_stride + gw] : 0u;
-                }
-#pragma unroll
-                for (uint32_t u = 0; u < kScanRowsUnroll; u++)
-                    if (base + u < nr && x[u]) atomicOr(&acc[code[u] >> 9][(code[u] >> 8) & 1u][lane], x[u]);
-            }
-        }
-        __syncthreads();
-        // First look, the tokens: a thread takes a byte of a word (8 tokens): all-stay tokens go to
-        // the row, queued ones take their places in the queue.
-        for (uint32_t t = 0; t < nt; t++) {
-            if (que_bound + kScanGroup > kScanQueue) {
-                // the queue may be short of room for a whole group: count exactly, empty it if need be
-                __syncthreads();
-                const uint32_t waiting = n_que;
-                __syncthreads();
-                if (waiting + kScanGroup > kScanQueue) drain();
-                else que_bound = waiting;
-            }
-            que_bound += kScanGroup;
-            const uint32_t wd = tid >> 2, bi = tid & 3u;
-            const uint32_t a = acc[t][0][wd];
-            const uint32_t b = first_inv[t] ? ~acc[t][1][wd] : acc[t][1][wd];
-            if (bi == 0) row_s[t][wd] = ~a & has_bytes;
-            const uint32_t mine = ((a & b & has_bytes) >> (8u * bi)) & 0xFFu;
-            // places in the queue: one LDS atomic per wavefront; a token's place follows from the
-            // ballots of the 8 token positions of a thread
-            unsigned long long bal[8];
-            uint32_t n_mine = 0;
-#pragma unroll
-            for (uint32_t j = 0; j < 8u; j++) {
-                bal[j] = __ballot((mine >> j) & 1u);
-                n_mine += (uint32_t)__popcll(bal[j]);
-            }
-            uint32_t at = 0;
-            if (lane == 0 && n_mine) at = atomicAdd(&n_que, n_mine);
-            at = __shfl(at, 0);
-#pragma unroll
-            for (uint32_t j = 0; j < 8u; j++) {
-                if ((mine >> j) & 1u)
-                    que[at + before(bal[j])] = (uint16_t)(t << 11 | (wd * 32u + bi * 8u + j));
-                at += (uint32_t)__popcll(bal[j]);
-            }
-        }
-        __syncthreads();
-        drain();
-        drain_long();
-        if (n_stage) flush();                        // (read behind the barrier that ends drain_long, the same for every thread)
-        for (uint32_t i = tid; i < nt * (kScanGroup / 32u); i += kScanThreads) {
-            const uint32_t t = i / (kScanGroup / 32u), wd = i % (kScanGroup / 32u);
-            const uint32_t w = g * (kScanGroup / 32u) + wd;
-            if (w < Vc.W) {
-                uint32_t *rows = Cc.class_rows + (size_t)(3u * cls_s[t]) * Cc.row_stride;
-                const uint32_t a = row_s[t][wd], b = row_e[t][wd];
-                rows[w] = a; rows[Cc.row_stride + w] = b; rows[2u * Cc.row_stride + w] = a | b;
-            }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&Cc.ctr->class_scans, (unsigned long long)n);
-}
-
-// ---------------------------------------------------------------------------------------------
-// key_build: a workgroup assembles the mask row of a missing state key in LDS -- or, for a key
-// whose candidates all need a deep walk, its words for one of the kParts token ranges, so that
-// such a key is shared among kParts workgroups instead of holding up the whole launch:
-//   (a) the context-free part from the class index (budget-limited through the per-length
-//       rows of the vocabulary), zeros for a literal / END / FINAL state;
-//   (b) the tokens that leave the state early (exit list of the class table, or the
-//       first-byte buckets of a literal state): first all of them are filtered, then the rest
-//       of each survivor is walked from the successor state, and an accepted token sets its bit
-//       with an LDS atomic.  The two possible successors are workgroup-uniform, so their
-//       descriptors and class tables are staged in LDS and the first hop of every walk runs out
-//       of LDS and registers; only a token that leaves the successor as well continues through
-//       the table in HBM;
-//   (c) the EOS bit, then the words go to the cache arena.
-__device__ __forceinline__ uint32_t token_byte(uint64_t c0, uint64_t c1, uint64_t c2, uint32_t i)
-{
-    const uint64_t cw = i < 8u ? c0 : i < 16u ? c1 : c2;
-    return (uint32_t)(cw >> (8u * (i & 7u))) & 0xFFu;
-}
-
-// Walks bytes [i, L) of a token held in registers (L <= 24) from the staged successor; hands
-// over to walk_chunks when the token moves on to a third state.
-__device__ __forceinline__ bool walk_first_hop(const DeviceTable &T, const HopState &h,
-                                               const uint8_t *lut, uint64_t c0, uint64_t c1, uint64_t c2, uint32_t i, uint32_t L)
-{
-    uint32_t sid, aux = 0;
-    if (h.kind == WG_KIND_LIT) {
-        if (token_byte(c0, c1, c2, i) != h.lit) return false;
-        sid = h.next_a; i++;
-    } else if (h.kind == WG_KIND_WAIT || h.kind == WG_KIND_COND) {
-        for (;;) {
-            if (i >= L) return true;
-            const uint32_t c = lut[token_byte(c0, c1, c2, i)];
-            i++;
-            if (c == CLS_STAY) {
-                if (h.max != WG_UNBOUNDED) { if (aux >= h.max) return false; aux++; }
-                continue;
-            }
-            if (c == CLS_EXIT_A) { sid = h.next_a; break; }
-            if (c == CLS_EXIT_B) { sid = h.next_b; break; }
-            return false;
-        }
-        aux = 0;
-    } else return false;
-    return walk_chunks(T, sid, aux, c0, c1, c2, i, L);
-}
-
-// True iff the first n bytes of a token held in registers (n <= 24) all stay in the checkpoint
-// whose class table is `lut`.
-__device__ __forceinline__ bool stays_prefix(const uint8_t *lut, uint64_t c0, uint64_t c1, uint64_t c2, uint32_t n)
-{
-    for (uint32_t i = 0; i < n; i++)
-        if (lut[token_byte(c0, c1, c2, i)] != CLS_STAY) return false;
-    return true;
-}
-
-constexpr uint32_t kKbThreads = 512;       // two workgroups per compute unit
-constexpr uint32_t kKbSegs = 2u * kMaxExitBytes;   // index ranges a key of the direct paths reads (2 for KB_SORTED)
-constexpr uint32_t kKbPer = 8;             // candidates a thread filters per pass
-static_assert(kKbPer % 2u == 0u, "deep items take their candidates two at a time");
-constexpr uint32_t kKbQueue = kKbThreads * kKbPer;   // candidates waiting for their walk: a whole pass fits (48 KB of LDS)
-typedef __attribute__((address_space(1))) uint2 global_u2;   // a load known to go to device memory
-
-// Walks what is left of a candidate token from the state its exit leads to.
-__device__ __forceinline__ bool walk_candidate(const DeviceTable &T, const DeviceVocab &Vc, const MissEntry &me,
-                                               const uint8_t (*hop_lut)[256], const ExitEntry &x, bool regs_ok,
-                                               uint64_t c0)
-{
-    const int w = x.cls == CLS_EXIT_B;
-    if (regs_ok) {
-        const uint32_t L = (uint32_t)x.off + x.rem;
-        const uint64_t c1 = L > 8u ? Vc.chunks[(size_t)Vc.V + x.tok] : 0ull;
-        const uint64_t c2 = L > 16u ? Vc.chunks[2ull * Vc.V + x.tok] : 0ull;
-        return walk_first_hop(T, me.hop[w], hop_lut[w], c0, c1, c2, x.off, L);
-    }
-    uint32_t sid = w ? me.next_b : me.next_a, aux = 0;
-    return walk_bytes(T, sid, aux, Vc.bytes + Vc.offsets[x.tok] + x.off, x.rem);
-}
-
-__global__ void __launch_bounds__(kKbThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
-key_build_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict__ bitmask)
-{
-    extern __shared__ __attribute__((aligned(16))) uint32_t row[];
-    __shared__ __attribute__((aligned(16))) uint8_t hop_lut[2][256];
-    __shared__ __attribute__((aligned(16))) uint8_t own_lut[256];
-    __shared__ uint2 queue[kKbQueue];
-    __shared__ uint32_t queued[2];                   // candidates queued in the passes of even / odd number
-    __shared__ uint32_t seg_at[kKbSegs], seg_len[kKbSegs];   // direct paths: the index ranges of the key
-    // One sequence of work items for the whole grid: first the range items of the deep keys (front
-    // of the miss list, kParts items per key), which take longest, then the plain keys (back of the
-    // list), handed out round-robin.  Which miss entry a workgroup's first item reads is only
-    // known once the counts have arrived; it is requested beforehand as if the item were a deep
-    // one, and requested again if it turns out to be a plain one.
-    const uint32_t n_deep = Cc.ctr->n_deep, n_plain = Cc.ctr->n_plain, n_claims = Cc.ctr->n_claims;
-    const uint32_t rs = Cc.row_stride, tid = threadIdx.x, lane = tid & 63u;
-    const bool regs_ok = Vc.lmax <= 24u;             // a whole token fits three 8-byte chunks
-    const uint32_t n_deep_items = n_deep * kParts, n_items = n_deep_items + n_plain;
-    auto entry_of = [&](uint32_t list, uint32_t item) {
-        const uint32_t at = list == 0u ? item / kParts : Cc.miss_cap - 1u - item;
-        return at < Cc.miss_cap ? at : 0u;
-    };
-    MissEntry me = Cc.miss[entry_of(0u, blockIdx.x)];
+    // the class tables, a wavefront each
     {
-    for (uint32_t unit = blockIdx.x; unit < n_items; unit += gridDim.x) {
-        const uint32_t list = unit < n_deep_items ? 0u : 1u;
-        const uint32_t item = list == 0u ? unit : unit - n_deep_items;
-        if (unit != blockIdx.x || list == 1u) me = Cc.miss[entry_of(list, item)];
-        const uint32_t kind = me.kind, r = me.r;
-        const uint32_t p0 = list == 0u ? item % kParts : 0u, span = list == 0u ? 1u : kParts;
-        // this item's words of the row, in 16-byte units
-        const uint32_t q_lo = Vc.part_tok[p0] >> 7;
-        const uint32_t q_hi = p0 + span == kParts ? rs / 4u : Vc.part_tok[p0 + span] >> 7;
-        // Its candidate tokens, ents[i < n_front ? at_front + i : at_back + i - n_front]: the
-        // first-byte buckets of a literal state (contiguous over these ranges), or the two-ended
-        // list of a checkpoint's class table: the whole one, or the one of range p0.
-        const ExitEntry *ents = nullptr;
-        uint32_t cnt = 0, n_front = 0, at_front = 0, at_back = 0;
-        const uint4 *stay = nullptr, *end = nullptr;
-        const uint32_t mode = me.mode;
-        const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
-        if (kind == WG_KIND_LIT && mode == KB_LIST) {
-            ents = Vc.lit_entries;
-            at_front = Vc.lit_start[me.lit * kParts + p0];
-            cnt = n_front = Vc.lit_start[me.lit * kParts + p0 + span] - at_front;
-        } else if (ckpt) {
-            if (mode == KB_LIST) {
-                ents = Cc.class_entries[me.cls];
-                const uint32_t *cc = Cc.class_count + me.cls * kCountStride + (span == kParts ? 0u : 2u + 2u * p0);
-                n_front = cc[0];
-                const uint32_t n_back = cc[1];
-                cnt = n_front + n_back;
-                at_front = span == kParts ? 0u : Vc.V + Vc.part_tok[p0];
-                at_back = (span == kParts ? Vc.V : Vc.V + Vc.part_tok[p0 + 1u]) - n_back;
+        uint8_t *to = wave == 0u ? sh.own : wave == 1u ? sh.hop[0] : sh.hop[1];
+        const bool want = wave == 0u ? ckpt : wave == 1u ? ckpt_a : wave == 2u ? ckpt_b : false;
+        const uint32_t c = wave == 0u ? me.cls : wave == 1u ? ha.cls : hb.cls;
+        if (want) reinterpret_cast<uint32_t *>(to)[lane] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)c * 256u)[lane];
+    }
+    for (uint32_t w = tid; w < n_words; w += kRowThreads) early[w] = 0u;
+    // the literal bytes of the state's own run, or behind its exits
+    const RunBytes run_a = run_bytes(T, literal ? me.sid : ha.kind == WG_KIND_LIT ? ha.next_a : 0u);
+    const RunBytes run_b = run_bytes(T, hb.kind == WG_KIND_LIT ? hb.next_a : 0u);
+    const bool few_budget = ckpt && me.r < Vc.lmax;            // the byte budget binds inside a token
+    const uint32_t *len_stay = Vc.len_rows + (size_t)me.r * rs + w_lo, *len_end = len_stay + rs;
+    // the plan of the state's class table: a lane holds one of its first 64 ids
+    const ClassPlan &plan = T.plans[ckpt ? me.cls : 0u];
+    const uint32_t n_exits = plan.n_exits, n_ids = plan.n_ids;
+    const bool by_first = ckpt && plan.by_first;
+    uint32_t ids = plan.ids[lane];
+    __syncthreads();
+    uint32_t total = 0;
+    if (wave == 0u) {
+        // the index ranges with the key's candidates
+        uint32_t n = 0, sure = 0;
+        if (literal) {
+            // (the one-byte tokens are taken as rows below: examined, but not one by one)
+            if (lane == 0) {
+                if (!ckpt_a) sure = Vc.dir0[me.lit * 257u + 1u] - Vc.dir0[me.lit * 257u];
             }
-            stay = reinterpret_cast<const uint4 *>(Cc.class_rows + (size_t)(3u * me.cls) * rs);
-            end = stay + rs / 4u;
+            n = ckpt_a || lit_a < 0x100u ? 1u : 0u;
+        } else if (ckpt) n = n_exits;
+        for (uint32_t r0 = 0; r0 < n; r0 += 64u) {
+            const uint32_t i = r0 + lane;
+            uint32_t lo = 0, len = 0;
+            if (i < n) {
+                const uint32_t id = literal ? me.lit : r0 ? plan.ids[i] : ids, x = id & 0xFFu, c = id >> 8;
+                const bool side = c == CLS_EXIT_B;
+                const uint32_t lit = side ? lit_b : lit_a;
+                uint32_t from = literal ? (ckpt_a ? FROM_A : FROM_PREFIX)
+                                        : by_first ? (c == CLS_STAY ? FROM_STAY : side ? FROM_B : FROM_A)
+                                                   : lit < 0x100u ? FROM_PAIR : (side ? ckpt_b : ckpt_a) ? (side ? FROM_DEEP_B : FROM_DEEP_A) : 0u;
+                const uint32_t *dir = Vc.place_start;
+                uint32_t a = x * kParts + p0, z = a + span, at = Vc.at_places;
+                if (from == FROM_PREFIX) { dir = Vc.dir0; a = x * 257u + 1u + lit; z = a + 1u; at = Vc.at_sorted; }
+                else if (from == FROM_PAIR) { dir = Vc.dirN; a = x << 8 | lit; z = a + 1u; at = Vc.at_pairs; }
+                else if (from && from <= FROM_B) { dir = Vc.lit_start; at = Vc.at_first; }
+                else if (!from) z = a;                         // nothing goes on behind this exit
+                lo = dir[a];
+                len = dir[z] - lo;
+                lo += at;
+                sh.code[i] = (uint16_t)(x | from << 8);
+            }
+            const uint32_t inc = wave_prefix_sum(len);
+            if (i < n) { sh.start[i] = lo; sh.upto[i] = total + inc; }
+            total += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         }
-        // the two possible successors: class tables staged in LDS for the first hop
-#pragma unroll
-        for (int w = 0; w < 2; w++)
-            if ((me.hop[w].kind == WG_KIND_WAIT || me.hop[w].kind == WG_KIND_COND) && tid < 64u)
-                reinterpret_cast<uint32_t *>(hop_lut[w])[tid] =
-                    reinterpret_cast<const uint32_t *>(T.classes + (size_t)me.hop[w].cls * 256u)[tid];
-        if (mode == KB_BIGRAM && tid >= 64u && tid < 128u)
-            reinterpret_cast<uint32_t *>(own_lut)[tid - 64u] =
-                reinterpret_cast<const uint32_t *>(T.classes + (size_t)me.cls * 256u)[tid - 64u];
-        // Direct paths: the few index ranges that hold the key's candidates.  A literal state:
-        // the token that is its byte alone, and the tokens that go on with the literal byte
-        // after it (none when no byte can follow).  A checkpoint: for each exit byte e of a side
-        // whose exit leads to a literal byte y, the places in the vocabulary where y follows e.
-        uint32_t n_seg = 0;
-        if (mode == KB_SORTED) n_seg = me.hop[0].kind == WG_KIND_LIT ? 2u : 1u;
-        else if (mode == KB_BIGRAM) n_seg = (uint32_t)me.n_a + me.n_b;
-        if (tid < n_seg) {
-            const uint32_t *dir;
-            uint32_t at;
-            if (mode == KB_SORTED) { dir = Vc.dir0; at = me.lit * 257u + (tid ? 1u + me.hop[0].lit : 0u); }
-            else {
-                const uint32_t w = tid >= me.n_a, k = w ? kMaxExitBytes + tid - me.n_a : tid;
-                const uint32_t word = k < 4u ? me.exits[0] : k < 8u ? me.exits[1] : me.exits[2];
-                const uint32_t e = (word >> (8u * (k & 3u))) & 0xFFu;
-                dir = Vc.dirN; at = (e << 8) | (w ? me.hop[1].lit : me.hop[0].lit);
+        if (lane == 0) {
+            sh.n_ranges = n; sh.total = total;
+            if (p0 == 0u && sure + total) atomicAdd(&Cc.walked[(b % kWalkedSlots) * kWalkedStride], (unsigned long long)(sure + total));
+            if (Vc.eos_id >= 0 && me.eos_next != WG_SID_ERROR) {
+                const uint32_t ew = (uint32_t)Vc.eos_id >> 5;
+                if (ew >= w_lo && ew < w_hi) early[ew - w_lo] |= 1u << ((uint32_t)Vc.eos_id & 31u);
             }
-            const uint32_t lo = dir[at], hi = dir[at + 1u];
-            seg_at[tid] = lo; seg_len[tid] = hi - lo;
         }
-        if (tid == 0) { queued[0] = 0; queued[1] = 0; }
-        // The first pass of candidates is requested before the row is set up, so that the loads
-        // are under way while (a) runs: kKbPer per thread, plain 8-byte loads from clamped
-        // indexes (a load inside a lane-dependent branch would be waited for on the spot).
-        const global_u2 *ents2 = (const global_u2 *)(ents ? ents : Vc.lit_entries);
-        // (an empty list still issues one load: from the first bucket entry, which always exists)
-        if (cnt == 0u) { ents2 = (const global_u2 *)Vc.lit_entries; at_back = 0u; }
-        uint2 x[kKbPer];
-        auto request = [&](uint32_t i0) {
-#pragma unroll
-            for (uint32_t j = 0; j < kKbPer; j++) {
-                uint32_t i = i0 + j * kKbThreads + tid;
-                i = i < cnt ? i : (cnt ? cnt - 1u : 0u);
-                const global_u2 *src = ents2 + (i < n_front ? at_front + i : at_back + (i - n_front));
-                x[j] = uint2{src->x, src->y};
-            }
-        };
-        request(0);
-        // (a)
-        uint4 *row4 = reinterpret_cast<uint4 *>(row);
-        if (!stay) {
-            for (uint32_t q = q_lo + tid; q < q_hi; q += kKbThreads) row4[q] = uint4{0u, 0u, 0u, 0u};
-        } else if (r >= Vc.lmax) {
-            const uint4 *both = end + rs / 4u;
-            for (uint32_t q = q_lo + tid; q < q_hi; q += kKbThreads) row4[q] = both[q];
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        // meanwhile the other wavefronts fill in what does not depend on a token's neighbours
+        const uint32_t t3 = tid - 64u, n3 = kRowThreads - 64u;
+        uint32_t *keep = Cc.class_rows + (size_t)(2u * me.cls) * rs + w_lo;
+        if (literal) {
+            const uint32_t *has = Vc.rows + (size_t)me.lit * rs + w_lo, *one = Vc.len_rows + rs + w_lo;
+            for (uint32_t w = t3; w < n_words; w += n3) row[w] = ckpt_a ? 0u : has[w] & one[w];
+        } else if (!ckpt || by_first) {
+            for (uint32_t w = t3; w < n_words; w += n3) row[w] = 0u;
+        } else if (me.class_state == CLASS_READY) {
+            for (uint32_t w = t3; w < n_words; w += n3)
+                row[w] = few_budget ? (keep[w] & len_stay[w]) | (keep[rs + w] & len_end[w]) : keep[w] | keep[rs + w];
         } else {
-            // r allow-bytes may still be consumed: all-stay tokens need length <= r, tokens
-            // that exit on their last byte have length - 1 stay bytes
-            const uint4 *l0 = reinterpret_cast<const uint4 *>(Vc.len_rows + (size_t)r * rs);
-            const uint4 *l1 = l0 + rs / 4u;
-            for (uint32_t q = q_lo + tid; q < q_hi; q += kKbThreads) {
-                const uint4 a = stay[q], b = end[q], x = l0[q], y = l1[q];
-                row4[q] = uint4{(a.x & x.x) | (b.x & y.x), (a.y & x.y) | (b.y & y.y),
-                                (a.z & x.z) | (b.z & y.z), (a.w & x.w) | (b.w & y.w)};
-            }
-        }
-        __syncthreads();
-        // (b) The candidates, kKbThreads * kKbPer per pass.  (b1) filter: every candidate is
-        // looked at once.  One that ends with its exit byte is accepted at once, one whose next
-        // byte cannot start the literal that follows is dropped, the others wait in LDS for (b2)
-        // their walk -- so that the walks, each a chain of dependent loads, run densely packed
-        // instead of a few lanes of every wavefront holding the others up.
-        uint32_t examined = 0;
-        if (mode != KB_LIST) {
-            // Every candidate of a direct path is walked: a token in byte order from the key's own
-            // literal state, a byte pair from the first byte of its token -- the bytes before the
-            // pair have to stay in the checkpoint (within its byte budget), the first of the pair
-            // leaves it, and what follows is walked from the successor.
-            const global_u2 *src = (const global_u2 *)(mode == KB_SORTED ? Vc.sorted : Vc.bigram);
-            uint32_t total = 0;
-            for (uint32_t sgi = 0; sgi < n_seg; sgi++) total += seg_len[sgi];
-            for (uint32_t i = tid; i < total; i += kKbThreads) {
-                uint32_t sgi = 0, at = i;
-                while (at >= seg_len[sgi]) { at -= seg_len[sgi]; sgi++; }
-                const global_u2 *pe = src + seg_at[sgi] + at;
-                const uint32_t tok = pe->x, y = pe->y;
-                const uint32_t off = y & 0xFFu, L = off + (y >> 24);
-                const uint64_t c0 = Vc.chunks[tok];
-                const uint64_t c1 = L > 8u ? Vc.chunks[(size_t)Vc.V + tok] : 0ull;
-                const uint64_t c2 = L > 16u ? Vc.chunks[2ull * Vc.V + tok] : 0ull;
-                bool ok;
-                if (mode == KB_SORTED) {
-                    uint32_t sid = me.sid, aux = 0;
-                    ok = walk_chunks(T, sid, aux, c0, c1, c2, 0u, L);
-                } else {
-                    ok = off - 1u <= r && stays_prefix(own_lut, c0, c1, c2, off - 1u);
-                    if (ok) {
-                        const uint32_t cls = own_lut[token_byte(c0, c1, c2, off - 1u)];
-                        ok = cls >= CLS_EXIT_A &&
-                             (cls == CLS_EXIT_B ? walk_first_hop(T, me.hop[1], hop_lut[1], c0, c1, c2, off, L)
-                                                : walk_first_hop(T, me.hop[0], hop_lut[0], c0, c1, c2, off, L));
-                    }
+            const uint32_t *has = Vc.len_rows + (size_t)(Vc.lmax + 1u) * rs + w_lo, *rows = Vc.rows + w_lo;
+            auto id_of = [&](uint32_t i) {                     // i is the same for the whole wavefront
+                return i < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)ids, (int)i) : (uint32_t)plan.ids[i];
+            };
+            for (uint32_t w0 = t3; w0 < n_words; w0 += n3 * kOrWords) {
+                // one: tokens with a byte value that does not stay, two: with several; tail: tokens with
+                // an exit byte once, at their end.  A token leaves with its last byte iff it is in tail and
+                // not in two, its bytes all stay iff it is not in one.
+                uint32_t at[kOrWords], one[kOrWords], two[kOrWords], tail[kOrWords], hb[kOrWords], ls[kOrWords], le[kOrWords];
+#pragma unroll
+                for (uint32_t v = 0; v < kOrWords; v++) {
+                    at[v] = w0 + v * n3 < n_words ? w0 + v * n3 : w0;
+                    one[v] = 0u; two[v] = 0u; tail[v] = 0u; hb[v] = has[at[v]];
+                    ls[v] = le[v] = 0xFFFFFFFFu;
+                    if (few_budget) { ls[v] = len_stay[at[v]]; le[v] = len_end[at[v]]; }
                 }
-                if (ok) atomicOr(&row[tok >> 5], 1u << (tok & 31u));
-            }
-            examined = total;
-            __syncthreads();
-        }
-        if (mode == KB_LIST && list == 0u) {
-            // A range item of a deep key: every entry of its list that is within the byte budget
-            // has to be walked (the successor is a checkpoint, so no first byte rules an entry
-            // out), which leaves nothing to filter: each thread walks the entries it requested.
-            for (uint32_t i0 = 0; i0 < cnt; i0 += kKbThreads * kKbPer) {
-                if (i0) request(i0);
-                // two candidates at a time, their first chunks requested together (most tokens
-                // are no longer than that), so that the two walks do not queue up behind one
-                // another's first load
+                for (uint32_t i = 0; i < n_exits; i++) {
+                    const uint32_t id = id_of(i) & 0xFFu;
+                    const uint32_t *src = rows + (size_t)id * rs, *last = rows + (size_t)(kTailRow + id) * rs;
+                    uint32_t x[kOrWords], y[kOrWords];
 #pragma unroll
-                for (uint32_t j = 0; j < kKbPer; j += 2u) {
-                    if (i0 + j * kKbThreads >= cnt) break;    // no candidate left for any thread
-                    uint64_t first_chunk[2];
+                    for (uint32_t v = 0; v < kOrWords; v++) { x[v] = src[at[v]]; y[v] = last[at[v]]; }
 #pragma unroll
-                    for (uint32_t u = 0; u < 2u; u++) first_chunk[u] = Vc.chunks[x[j + u].x < Vc.V ? x[j + u].x : 0u];
+                    for (uint32_t v = 0; v < kOrWords; v++) { two[v] |= one[v] & x[v]; one[v] |= x[v]; tail[v] |= y[v]; }
+                }
+                for (uint32_t i = n_exits; i < n_ids; i += kOrBatch) {
+                    uint32_t x[kOrBatch][kOrWords];
 #pragma unroll
-                    for (uint32_t u = 0; u < 2u; u++) {
-                        ExitEntry e;
-                        e.tok = x[j + u].x; e.off = (uint8_t)x[j + u].y; e.cls = (uint8_t)(x[j + u].y >> 8);
-                        e.first = (uint8_t)(x[j + u].y >> 16); e.rem = (uint8_t)(x[j + u].y >> 24);
-                        if (i0 + (j + u) * kKbThreads + tid < cnt && (uint32_t)e.off - 1u <= r &&
-                            (e.rem == 0 || walk_candidate(T, Vc, me, hop_lut, e, regs_ok, first_chunk[u])))
-                            atomicOr(&row[e.tok >> 5], 1u << (e.tok & 31u));
+                    for (uint32_t u = 0; u < kOrBatch; u++) {
+                        const uint32_t *src = rows + (size_t)id_of(i + u < n_ids ? i + u : i) * rs;
+#pragma unroll
+                        for (uint32_t v = 0; v < kOrWords; v++) x[u][v] = src[at[v]];
                     }
+#pragma unroll
+                    for (uint32_t u = 0; u < kOrBatch; u++)
+#pragma unroll
+                        for (uint32_t v = 0; v < kOrWords; v++) if (i + u < n_ids) { two[v] |= one[v] & x[u][v]; one[v] |= x[u][v]; }
+                }
+#pragma unroll
+                for (uint32_t v = 0; v < kOrWords; v++) {
+                    const uint32_t s = ~one[v] & hb[v], x = tail[v] & ~two[v];
+                    row[at[v]] = (s & ls[v]) | (x & le[v]);
+                    if (me.class_state == CLASS_OWN) { keep[at[v]] = s; keep[rs + at[v]] = x; }
                 }
             }
-            examined = cnt;
-            cnt = 0;                                     // nothing left for the filter below
-            __syncthreads();
         }
-        constexpr uint32_t kAnyByte = 0x100u;        // no literal follows this exit
-        const uint32_t next_lit[2] = {me.hop[0].kind == WG_KIND_LIT ? me.hop[0].lit : kAnyByte,
-                                      me.hop[1].kind == WG_KIND_LIT ? me.hop[1].lit : kAnyByte};
-        uint32_t pass = 0;
-        for (uint32_t i0 = 0; i0 < cnt; i0 += kKbThreads * kKbPer, pass ^= 1u) {
-            if (i0) request(i0);
-            uint32_t slot[kKbPer], in_wave = 0;               // place among the wavefront's candidates to walk
-            uint32_t need = 0;                                   // bit j: x[j] has to be walked
-#pragma unroll
-            for (uint32_t j = 0; j < kKbPer; j++) {
-                if (i0 + j * kKbThreads >= cnt) break;        // no candidate left for any thread
-                const uint32_t off = x[j].y & 0xFFu, cls = (x[j].y >> 8) & 0xFFu, first = (x[j].y >> 16) & 0xFFu, rem = x[j].y >> 24;
-                const bool live = i0 + j * kKbThreads + tid < cnt && off - 1u <= r;
-                const uint32_t lit = cls == CLS_EXIT_B ? next_lit[1] : next_lit[0];
-                const bool walk = live && rem != 0 && (lit == kAnyByte || first == lit);
-                if (live && rem == 0) atomicOr(&row[x[j].x >> 5], 1u << (x[j].x & 31u));
-                const unsigned long long wm = __ballot(walk);
-                slot[j] = in_wave + (uint32_t)__popcll(wm & ((1ull << lane) - 1ull));
-                in_wave += (uint32_t)__popcll(wm);
-                need |= (uint32_t)walk << j;
-            }
-            if (in_wave) {                                       // one LDS atomic per wavefront and pass
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&queued[pass], in_wave);
-                base = __shfl(base, 0);
-#pragma unroll
-                for (uint32_t j = 0; j < kKbPer; j++)
-                    if ((need >> j) & 1u) queue[base + slot[j]] = x[j];
-            }
-            __syncthreads();
-            // (b2) walk the queued candidates, one per thread and round
-            // The other counter is cleared for the next pass here, between the two barriers of
-            // this pass: its last readers passed the barrier that ended the pass before, and its
-            // next writers wait behind the barrier that ends this one.
-            const uint32_t n_queued = queued[pass];
-            if (tid == 0) queued[pass ^ 1u] = 0;
-            for (uint32_t i = tid; i < n_queued; i += kKbThreads) {
-                const uint2 q = queue[i];
-                ExitEntry e;
-                e.tok = q.x; e.off = (uint8_t)q.y; e.cls = (uint8_t)(q.y >> 8); e.first = (uint8_t)(q.y >> 16); e.rem = (uint8_t)(q.y >> 24);
-                if (walk_candidate(T, Vc, me, hop_lut, e, regs_ok, Vc.chunks[e.tok])) atomicOr(&row[e.tok >> 5], 1u << (e.tok & 31u));
-            }
-            __syncthreads();
+    }
+    // The candidates: a few are the first wavefront's, right away; many are everybody's, once all
+    // know the ranges.
+    auto set_bit = [&](uint32_t tok) { atomicOr(&early[(tok >> 5) - w_lo], 1u << (tok & 31u)); };
+    auto decide = [&](uint32_t e) {
+        const uint32_t tok = e & 0xFFFFFFu, L = e >> 24;
+        TokenBytes t = token_bytes(Vc, tok, L);
+        if (!ckpt) {
+            if (walk_run(T, run_a, me.sid, me.run, me.cls, t, 0u, L)) set_bit(tok);
+            return;
         }
-        if (tid == 0) atomicAdd(&Cc.ctr->entries_walked, (unsigned long long)cnt + examined);
-        if (tid == 0 && Vc.eos_id >= 0 && me.eos_next != WG_SID_ERROR) {
-            const uint32_t ew = (uint32_t)Vc.eos_id >> 5;
-            if (ew >= 4u * q_lo && ew < 4u * q_hi) row[ew] |= 1u << ((uint32_t)Vc.eos_id & 31u);
+        uint32_t j = 0, c = CLS_STAY;
+        while (j < L) {
+            const uint32_t n = L - j < 8u ? L - j : 8u;
+            const uint32_t code = class_code(sh.own, window(t, j)), s = first_leaving(code, n);
+            j += s;
+            if (s < n) { c = (code >> (2u * s)) & 3u; break; }
+        }
+        if (c == CLS_REJECT || j > me.r) return;               // j bytes that stay
+        bool ok = c == CLS_STAY || j + 1u == L;
+        if (!ok) {
+            const bool side_b = c == CLS_EXIT_B;
+            const HopState h{side_b ? hb.kind : ha.kind, 0u, side_b ? hb.next_a : ha.next_a, side_b ? hb.next_b : ha.next_b,
+                             side_b ? hb.max : ha.max, side_b ? hb.cls : ha.cls};
+            const RunBytes lit{{side_b ? run_b.w[0] : run_a.w[0], side_b ? run_b.w[1] : run_a.w[1], side_b ? run_b.w[2] : run_a.w[2]}};
+            ok = walk_hop(T, h, sh.hop[side_b], lit, t, j + 1u, L);
+        }
+        if (ok) set_bit(tok);
+    };
+    const global_u2 *index = (const global_u2 *)Vc.index;
+#pragma nounroll
+    for (uint32_t pass = 0; pass < 2u; pass++) {
+        if (pass) total = sh.total;
+        if (pass ? total > kAlone : wave == 0u && total <= kAlone) {
+            const uint32_t first_at = pass ? wave * 64u : 0u, step = pass ? kRowThreads : 64u;
+            const uint32_t n_ranges = sh.n_ranges;
+            uint32_t n_q = 0, widest = 1u;                             // first step of the search for a candidate's range
+            while (widest * 2u < n_ranges) widest *= 2u;
+            for (uint32_t base = first_at;; base += step * kRowBatch) {
+                const bool more = base < total;
+                if (more) {
+                    uint2 e[kRowBatch];
+                    uint32_t from[kRowBatch];
+#pragma unroll
+                    for (uint32_t u = 0; u < kRowBatch; u++) {
+                        const uint32_t i = base + u * step + lane, ii = i < total ? i : total - 1u;
+                        uint32_t k = 0;                                // the range that holds candidate ii
+                        if (n_ranges > 1u)
+                            for (uint32_t s = widest; s; s >>= 1)
+                                if (k + s < n_ranges && sh.upto[k + s - 1u] <= ii) k += s;
+                        const global_u2 *src = index + sh.start[k] + (ii - (k ? sh.upto[k - 1u] : 0u));
+                        e[u] = uint2{src->x, src->y};
+                        from[u] = i < total ? sh.code[k] >> 8 : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < kRowBatch; u++) {
+                        const uint32_t tok = e[u].x, first = (e[u].y >> 16) & 0xFFu, L = (e[u].y & 0xFFu) + (e[u].y >> 24);
+                        const uint32_t f = from[u];
+                        bool decide_it = false;
+                        if (f != 0u && tok >= tok_lo && tok < tok_hi) {
+                            const bool side_b = f == FROM_B || f == FROM_DEEP_B;
+                            if (f == FROM_PREFIX || f == FROM_PAIR) decide_it = true;
+                            // a one-byte token is settled by the byte's class
+                            else if (L == 1u) { if (f != FROM_STAY || me.r != 0u) set_bit(tok); }
+                            else if (f == FROM_STAY) decide_it = sh.own[first] != CLS_REJECT;
+                            else if (side_b ? ckpt_b : ckpt_a) decide_it = sh.hop[side_b][first] != CLS_REJECT;
+                            else decide_it = (side_b ? lit_b : lit_a) == first;
+                        }
+                        const unsigned long long m = __ballot(decide_it);
+                        if (decide_it) sh.queue[wave][n_q + before(m)] = tok | L << 24;
+                        n_q += (uint32_t)__popcll(m);
+                    }
+                }
+                while (n_q >= 64u || (!more && n_q)) {
+                    const uint32_t take = n_q < 64u ? n_q : 64u;
+                    n_q -= take;
+                    if (lane < take) decide(sh.queue[wave][n_q + lane]);
+                }
+                if (!more) break;
+            }
         }
         __syncthreads();
-        // (c) to its arena row (unless the arena had no row left) and to the bitmask row of the
-        // request that claimed the key, which the gather then leaves alone
-        if (me.slot != kNoSlot) {
-            uint4 *dst = reinterpret_cast<uint4 *>(Cc.arena + (size_t)me.slot * rs);
-            for (uint32_t q = q_lo + tid; q < q_hi; q += kKbThreads) dst[q] = row4[q];
-            if (tid == 0 && p0 == 0) Cc.tags[me.key] = ((unsigned long long)Cc.epoch << 32) | me.slot;
-        }
-        {
-            uint32_t *dst = bitmask + (size_t)me.req * Vc.W;
-            if (Vc.W % 4u == 0u && reinterpret_cast<uintptr_t>(bitmask) % 16u == 0u) {
-                uint4 *dst4 = reinterpret_cast<uint4 *>(dst);
-                for (uint32_t q = q_lo + tid; q < q_hi; q += kKbThreads) dst4[q] = row4[q];
-            } else {
-                const uint32_t w_hi = 4u * q_hi < Vc.W ? 4u * q_hi : Vc.W;
-                for (uint32_t w = 4u * q_lo + tid; w < w_hi; w += kKbThreads) dst[w] = row[w];
-            }
-        }
-        __syncthreads();
+        if (sh.total <= kAlone) break;
     }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && n_claims) atomicAdd(&Cc.ctr->builds, (unsigned long long)n_claims);
 }
 
-// The miss lists have been consumed by the kernels that ran before the last kernel of a fill:
-// one thread of it counts their rows as used and empties them for the next call.
+// The call is over for the cache once its lookups are: one thread of the kernel after them counts
+// the claimed rows as used and opens the next call.
 __device__ __forceinline__ void close_fill(const DeviceCache &Cc)
 {
     const unsigned long long sc = Cc.ctr->slot_ctr;
@@ -1269,134 +718,75 @@ __device__ __forceinline__ void close_fill(const DeviceCache &Cc)
     const uint32_t room = Cc.cap_rows - used, n = Cc.ctr->n_claims;
     if (n > room) Cc.ctr->uncached_builds += n - room;
     Cc.ctr->slot_ctr = ((unsigned long long)Cc.epoch << 32) | (used + (n < room ? n : room));
-    Cc.ctr->n_deep = 0; Cc.ctr->n_plain = 0; Cc.ctr->n_claims = 0; Cc.ctr->n_class_miss = 0;
+    Cc.ctr->builds += n;
+    Cc.ctr->class_scans += Cc.ctr->n_class_claims;
+    Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
     Cc.ctr->launch++;
 }
 
-// Where the mask of request b is: a row of the arena, its own bitmask row already (`in_place`:
-// b claimed the key and key_build wrote the row there), the bitmask row of the request that
-// built it uncached, or nowhere (nullptr: a row of zeros).
-__device__ __forceinline__ const uint32_t *mask_source(const DeviceCache &Cc, uint32_t b, uint32_t B, uint32_t W,
-                                                       const uint32_t *bitmask, bool &in_place)
+// kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_span).
+template <typename Elem, int kMode>
+__global__ void __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(8)))
+rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict__ bitmask, Elem *__restrict__ logits,
+            int64_t logits_stride)
 {
-    in_place = false;
-    const uint32_t ref = Cc.row_ref[b];
-    if (ref < kRefByKey) return ref < Cc.cap_rows ? Cc.arena + (size_t)ref * Cc.row_stride : nullptr;   // cached before this call
-    if (ref == kRefSelf) { in_place = true; return bitmask + (size_t)b * W; }    // written by key_build
-    if (ref == kNoKey) return nullptr;
-    const unsigned long long t = Cc.tags[ref & ~kRefByKey];
-    if ((uint32_t)(t >> 32) == Cc.epoch) return Cc.arena + (size_t)(uint32_t)t * Cc.row_stride;
-    const uint32_t req = (uint32_t)(t & 0xFFFFu);
-    return req < B ? bitmask + (size_t)req * W : nullptr;                        // built uncached for another request of this call
-}
-
-template <bool kVec>
-__global__ void __launch_bounds__(256)
-gather_kernel(DeviceCache Cc, uint32_t W, uint32_t *__restrict__ bitmask)
-{
-    const uint32_t b = blockIdx.y;
-    if (blockIdx.x == 0 && b == 0 && threadIdx.x == 0) close_fill(Cc);
-    bool in_place;
-    const uint32_t *src = mask_source(Cc, b, gridDim.y, W, bitmask, in_place);
-    if (in_place) return;
-    uint32_t *dst = bitmask + (size_t)b * W;
-    if (kVec) {
-        const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
-        uint4 *d4 = reinterpret_cast<uint4 *>(dst);
-        for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < W / 4u; q += gridDim.x * blockDim.x)
-            d4[q] = src ? s4[q] : uint4{0u, 0u, 0u, 0u};
+    extern __shared__ __attribute__((aligned(16))) uint32_t row[];
+    __shared__ __attribute__((aligned(16))) RowShared sh;
+    const uint32_t b = blockIdx.y, tid = threadIdx.x, span = kParts / gridDim.x, p0 = blockIdx.x * span;
+    const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
+    const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
+    if (tok_lo >= tok_hi) return;                    // (never the last workgroup of a row)
+    const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
+    const RowTask in = Cc.tasks[b];                   // (requested with the reference; only used where that asks for it)
+    const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)Cc.row_ref[b]);
+    uint4 *row4 = reinterpret_cast<uint4 *>(row);
+    uint32_t slot = kNoSlot;
+    if (ref == kRefBuild) {
+        // (the same for every lane: to scalar registers)
+        auto one = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+        auto hop = [&](const HopState &h) { return HopState{one(h.kind), one(h.lit), one(h.next_a), one(h.next_b), one(h.max), one(h.cls)}; };
+        const HopState ha = hop(in.hop[0]), hb = hop(in.hop[1]);
+        const RowTask me{one(in.sid), one(in.kind), one(in.lit), one(in.cls), one(in.run), one(in.r), one(in.class_state), one(in.eos_next), one(in.slot), {}};
+        slot = me.slot;
+        uint32_t *early = row + 4u * n4 + 4u;
+        make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, early, b);
+        for (uint32_t w = tid; w < 4u * n4; w += kRowThreads) row[w] = w < n_words ? row[w] | early[w] : 0u;
     } else {
-        for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < W; w += gridDim.x * blockDim.x)
-            dst[w] = src ? src[w] : 0u;
+        const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
+        for (uint32_t q = tid; q < n4; q += kRowThreads) row4[q] = ref < Cc.cap_rows ? src[q] : uint4{0u, 0u, 0u, 0u};
     }
+    __syncthreads();
+    if (slot != kNoSlot) {
+        uint4 *dst = reinterpret_cast<uint4 *>(Cc.arena + (size_t)slot * rs + w_lo);
+        for (uint32_t q = tid; q < n4; q += kRowThreads) dst[q] = row4[q];
+    }
+    {
+        uint32_t *dst = bitmask + (size_t)b * Vc.W + w_lo;
+        if (reinterpret_cast<uintptr_t>(dst) % 16u == 0u) {
+            const uint32_t whole = n_words / 4u;
+            for (uint32_t q = tid; q < whole; q += kRowThreads) reinterpret_cast<uint4 *>(dst)[q] = row4[q];
+            if (tid < n_words - 4u * whole) dst[4u * whole + tid] = row[4u * whole + tid];
+        } else {
+            for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
+        }
+    }
+    if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
+    if (blockIdx.x == gridDim.x - 1u && b == 0 && tid == 0) close_fill(Cc);
 }
 
-// ---------------------------------------------------------------------------------------------
-// apply: a thread takes mask bytes (8 consecutive tokens each) 256 apart, all loaded before any
-// is used.  Nothing is read from the logits:
-// a fully allowed group is skipped, a group with no allowed token is overwritten with one
-// 16-byte store per 8 bf16 (two for fp32), and a mixed group stores -inf element by element,
-// one store per disallowed token (found by count-trailing-zeros, so a group inside a
-// free-text Wait, which has one or two such tokens, issues one or two stores).
-constexpr uint32_t kApplyGroups = 2;       // mask bytes per thread, 256 apart
-template <typename Vec, int kVecs, typename Elem>
+// apply: a workgroup takes kApplyTokens tokens of a row.
+constexpr uint32_t kApplyTokens = 8192;
+template <typename Elem, bool kLine>
 __global__ void __launch_bounds__(256)
-apply_vec_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
-                 const uint32_t *__restrict__ bitmask, Elem ninf)
+apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
-    const uint32_t b = blockIdx.y;
-    const uint32_t g0 = blockIdx.x * (256u * kApplyGroups) + threadIdx.x;   // group of 8 tokens
-    const uint8_t *row = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * W);
-    uint32_t m[kApplyGroups];
-#pragma unroll
-    for (uint32_t i = 0; i < kApplyGroups; i++) {
-        const uint32_t g = g0 + i * 256u;
-        m[i] = g * 8u < V ? row[g] : 0xFFu;
-    }
-#pragma unroll
-    for (uint32_t i = 0; i < kApplyGroups; i++) {
-        if (m[i] == 0xFFu) continue;
-        Elem *p = logits + (int64_t)b * row_stride + (int64_t)(g0 + i * 256u) * 8;
-        uint32_t z = ~m[i] & 0xFFu;                                 // disallowed positions
-        if (z == 0xFFu) {
-            union { Vec v[kVecs]; Elem e[8]; } u;
-#pragma unroll
-            for (int k = 0; k < 8; k++) u.e[k] = ninf;
-            Vec *pv = reinterpret_cast<Vec *>(p);
-#pragma unroll
-            for (int k = 0; k < kVecs; k++) pv[k] = u.v[k];
-        } else {
-            while (z) { p[__builtin_ctz(z)] = ninf; z &= z - 1u; }
-        }
-    }
-}
-
-// gather and apply in one pass, the last kernel of a whole decode step: a thread takes four
-// mask bytes (8 tokens each) 256 apart, loaded together so that finding where the request's
-// mask lives is paid once; each byte goes to the caller's bitmask row and its disallowed tokens
-// are stored as -inf.
-constexpr uint32_t kGaGroups = 4;          // mask bytes per thread of gather_apply, 256 apart
-template <typename Vec, int kVecs, typename Elem>
-__global__ void __launch_bounds__(256)
-gather_apply_kernel(DeviceCache Cc, Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
-                    uint32_t *__restrict__ bitmask, Elem ninf)
-{
-    const uint32_t b = blockIdx.y;
-    bool in_place;
-    const uint32_t *src = mask_source(Cc, b, gridDim.y, W, bitmask, in_place);
-    const uint32_t g0 = blockIdx.x * (256u * kGaGroups) + threadIdx.x;      // group of 8 tokens
-    uint32_t m[kGaGroups];
-#pragma unroll
-    for (uint32_t i = 0; i < kGaGroups; i++) {
-        const uint32_t g = g0 + i * 256u;
-        m[i] = (src && g < 4u * W) ? reinterpret_cast<const uint8_t *>(src)[g] : 0u;
-    }
-    if (!in_place) {
-        uint8_t *dst = reinterpret_cast<uint8_t *>(bitmask + (size_t)b * W);
-#pragma unroll
-        for (uint32_t i = 0; i < kGaGroups; i++) {
-            const uint32_t g = g0 + i * 256u;
-            if (g < 4u * W) dst[g] = (uint8_t)m[i];
-        }
-    }
-#pragma unroll
-    for (uint32_t i = 0; i < kGaGroups; i++) {
-        const uint32_t g = g0 + i * 256u;
-        if (g * 8u >= V || m[i] == 0xFFu) continue;
-        Elem *p = logits + (int64_t)b * row_stride + (int64_t)g * 8;
-        uint32_t z = ~m[i] & 0xFFu;                                 // disallowed positions
-        if (z == 0xFFu) {
-            union { Vec v[kVecs]; Elem e[8]; } u;
-#pragma unroll
-            for (int k = 0; k < 8; k++) u.e[k] = ninf;
-            Vec *pv = reinterpret_cast<Vec *>(p);
-#pragma unroll
-            for (int k = 0; k < kVecs; k++) pv[k] = u.v[k];
-        } else {
-            while (z) { p[__builtin_ctz(z)] = ninf; z &= z - 1u; }
-        }
-    }
-    if (blockIdx.x == 0 && b == 0 && threadIdx.x == 0) close_fill(Cc);
+    __shared__ uint32_t row[kApplyTokens / 32u + 1u];
+    const uint32_t b = blockIdx.y, lo = blockIdx.x * kApplyTokens, hi = lo + kApplyTokens < V ? lo + kApplyTokens : V;
+    static_assert(kApplyTokens == 32u * 256u, "a mask word per thread");
+    const uint32_t w = (lo >> 5) + threadIdx.x;
+    row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
+    __syncthreads();
+    mask_span<Elem, kLine>(logits + (int64_t)b * row_stride, lo, hi, lo, row);
 }
 
 // masked argmax: a row is split over several workgroups; a thread takes 32-token groups (one mask word and up
@@ -1524,71 +914,6 @@ masked_argmax_finish_kernel(int32_t *__restrict__ tokens, uint32_t B)
     tokens[b] = best ? (int32_t)(0xFFFFFFFFu - (uint32_t)best) : -1;
     g_argmax_key[b] = 0ull;
 }
-
-template <typename Elem>
-__global__ void __launch_bounds__(256)
-apply_scalar_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
-                    const uint32_t *__restrict__ bitmask, Elem ninf)
-{
-    uint32_t b = blockIdx.y;
-    uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= V) return;
-    uint32_t word = bitmask[(size_t)b * W + (t >> 5)];
-    if (!((word >> (t & 31u)) & 1u)) logits[(int64_t)b * row_stride + t] = ninf;
-}
-
-// ---------------------------------------------------------------------------------------------
-// advance: one thread per request.  The token's bytes are fetched as 8-byte chunks (three
-// independent loads) and walked with walk_chunks; tokens longer than 24 bytes take the
-// generic byte-at-a-time walker.
-__device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                                            uint32_t &sid, uint32_t &aux, int64_t t)
-{
-    bool ok;
-    if (Vc.lmax > 24u || t < 0 || t >= (int64_t)Vc.V || (int64_t)Vc.eos_id == t) {
-        ok = walk_token(T, Vc, sid, aux, t);
-    } else {
-        const uint32_t L = Vc.len8[t];
-        const uint64_t c0 = Vc.chunks[t];
-        const uint64_t c1 = Vc.n_chunks > 1u ? Vc.chunks[(size_t)Vc.V + t] : 0ull;
-        const uint64_t c2 = Vc.n_chunks > 2u ? Vc.chunks[2ull * Vc.V + t] : 0ull;
-        ok = L != 0u && sid < T.n_states && walk_chunks(T, sid, aux, c0, c1, c2, 0u, L);
-    }
-    if (!ok) {
-        sid = WG_SID_ERROR; aux = 0;
-        atomicAdd(&Cc.ctr->errors, 1ull);
-    }
-}
-
-__global__ void __launch_bounds__(64)
-advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
-               const int32_t *__restrict__ tokens, uint32_t B)
-{
-    uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    uint32_t sid = states[b].sid, aux = states[b].aux;
-    advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
-    states[b].sid = sid; states[b].aux = aux;
-}
-
-// advance followed by the lookup of the next step's fill, one thread per request: the new
-// state goes straight from the walker into the cache lookup.
-__global__ void __launch_bounds__(64)
-advance_lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
-                      const int32_t *__restrict__ tokens, uint32_t B)
-{
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = b < B;
-    const LookupEnv env = lookup_env(Cc);
-    uint32_t sid = 0, aux = 0;
-    if (live) {
-        sid = states[b].sid; aux = states[b].aux;
-        advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
-        states[b].sid = sid; states[b].aux = aux;
-    }
-    lookup_one(T, Cc, env, b, live, sid, aux);
-}
-
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
 // Write and of the Writes that follow it directly, up to the next state that is not a literal
 // byte.  One thread per request; a run of literal states is copied from the state table's
@@ -1647,36 +972,10 @@ select_kernel(const uint32_t *__restrict__ bitmask, uint32_t W, const uint64_t *
         }
     }
 }
-
 // ---------------------------------------------------------------------------------------------
 // launchers (host)
 
 static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
-
-// key_build keeps a whole mask row (dynamic LDS) next to its candidate queue and tables (static
-// LDS); together they may pass the 64 KB a kernel gets without asking.  The limit is a property
-// of the kernel on a device, shared by every handle of the process, so it is only ever raised: a
-// handle with short rows compiled later leaves the room a handle with long rows needs.  Returns
-// hipErrorInvalidValue when a row does not fit the 160 KB of a compute unit at all.
-hipError_t configure_kernels(uint32_t row_bytes)
-{
-    static std::mutex mu;
-    static uint32_t granted[64];                     // per device: dynamic LDS key_build may ask for
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    hipFuncAttributes attr;
-    e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(key_build_kernel));
-    if (e != hipSuccess) return e;
-    if (attr.sharedSizeBytes + (size_t)row_bytes > 160u * 1024u) return hipErrorInvalidValue;
-    std::lock_guard<std::mutex> lock(mu);
-    const uint32_t slot = (uint32_t)dev < 64u ? (uint32_t)dev : 63u;
-    if ((uint32_t)dev < 64u && row_bytes <= granted[slot]) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(key_build_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_bytes);
-    if (e == hipSuccess && (uint32_t)dev < 64u) granted[slot] = row_bytes;
-    return e;
-}
 
 // Launches on stream s; with a pair of events the kernel's own begin / end timestamps are
 // recorded into them (hipExtLaunchKernelGGL), which times the kernel without the queue gaps
@@ -1689,75 +988,71 @@ static inline void launch(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStre
     else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 
-static bool apply_vec_ok(const void *logits, int dtype, uint32_t V, int64_t row_stride)
+// Logits larger than this are masked by whole lines (see mask_span): 128 bytes are read where a
+// line is mixed, but no store leaves the memory to read and write the block around it.
+constexpr uint64_t kLineBytes = 192ull << 20;
+
+static bool by_lines(int dtype, uint32_t B, uint32_t V)
 {
-    const size_t esz = dtype == WG_F32 ? 4 : 2;
-    return reinterpret_cast<uintptr_t>(logits) % 16 == 0 && (row_stride * (int64_t)esz) % 16 == 0 && V % 8u == 0;
+    return (uint64_t)B * V * (dtype == WG_F32 ? 4u : 2u) > kLineBytes;
+}
+
+// Workgroups per row: the row is cut at its token ranges, into as many pieces as there are groups
+// of kPartGroup tokens, at most kParts.
+static uint32_t row_parts(uint32_t V)
+{
+    uint32_t parts = kParts;
+    while (parts > 1u && (uint64_t)parts * kPartGroup > V) parts >>= 1;
+    return parts;
+}
+
+uint32_t rows_lds_bytes(const DeviceVocab &Vc)
+{
+    const uint32_t parts = row_parts(Vc.V), span = kParts / parts;
+    uint32_t most = 0;
+    for (uint32_t p = 0; p < kParts; p += span) {
+        const uint32_t n = ((Vc.part_tok[p + span] + 31u) >> 5) - (Vc.part_tok[p] >> 5);
+        most = n > most ? n : most;
+    }
+    return 2u * (((most + 3u) & ~3u) + 4u) * 4u;
 }
 
 hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
-                       void *logits, int dtype, int64_t logits_stride,
-                       uint32_t n_cu, hipStream_t s, hipEvent_t *ev)
+                       void *logits, int dtype, int64_t logits_stride, hipStream_t s, hipEvent_t *ev)
 {
     if (tokens) launch(advance_lookup_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, ev, T, Vc, Cc, states, tokens, B);
     else launch(lookup_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, ev, T, Cc, static_cast<const wg_state_t *>(states), B);
-    // the number of misses is only known on the device: both build kernels stride a fixed
-    // grid over whatever the lookup queued and fall through when nothing is queued
-    // (a call scans at most one class table per request, and no more than the handle has; the
-    // kernels hold 5 workgroups per compute unit, and a launch of more costs a warm step time)
-    uint32_t groups = cdiv(Vc.V, kScanGroup);
-    uint64_t scan_items = (uint64_t)(B < T.n_classes ? B : T.n_classes) * groups;
-    uint32_t cap = n_cu * kScanWgs;
-    // a handle with few class tables scans them one per work item; with many, a call may bring so
-    // many that they are taken several at a time
-    if (Cc.scan_batch ? Cc.scan_batch > 1u : (uint64_t)T.n_classes * groups > kScanBatchFrom)
-        launch(class_scan_batch_kernel, dim3(scan_items < n_cu * kScanBatchWgs ? (uint32_t)scan_items : n_cu * kScanBatchWgs),
-               dim3(kScanThreads), 0, s, ev ? ev + 2 : nullptr, T, Vc, Cc);
-    else
-        launch(class_scan_kernel, dim3(scan_items < cap ? (uint32_t)scan_items : cap), dim3(kScanThreads), 0, s,
-               ev ? ev + 2 : nullptr, T, Vc, Cc);
-    // up to kParts work items per key; two 512-thread workgroups fit a compute unit
-    const uint32_t kb = n_cu * 2u;
-    const uint64_t kb_items = (uint64_t)B * kParts;
-    launch(key_build_kernel, dim3(kb_items < kb ? (uint32_t)kb_items : kb), dim3(kKbThreads), Cc.row_stride * 4u, s,
-           ev ? ev + 4 : nullptr, T, Vc, Cc, bitmask);
-    hipEvent_t *ge = ev ? ev + 6 : nullptr;
-    if (logits && apply_vec_ok(logits, dtype, Vc.V, logits_stride)) {
-        const dim3 g(cdiv(4u * Vc.W, 256 * kGaGroups), B);
-        if (dtype == WG_F32)
-            launch(gather_apply_kernel<uint4, 2, uint32_t>, g, dim3(256), 0, s, ge, Cc, (uint32_t *)logits,
-                   logits_stride, Vc.V, Vc.W, bitmask, 0xFF800000u);
-        else
-            launch(gather_apply_kernel<uint4, 1, uint16_t>, g, dim3(256), 0, s, ge, Cc, (uint16_t *)logits,
-                   logits_stride, Vc.V, Vc.W, bitmask, (uint16_t)0xFF80u);
-        return hipGetLastError();
+    const dim3 g(row_parts(Vc.V), B);
+    const uint32_t lds = rows_lds_bytes(Vc);
+    hipEvent_t *re = ev ? ev + 2 : nullptr;
+    if (!logits) {
+        launch(rows_kernel<uint16_t, 0>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, (uint16_t *)nullptr, (int64_t)0);
+    } else if (dtype == WG_F32) {
+        uint32_t *x = static_cast<uint32_t *>(logits);
+        if (by_lines(dtype, B, Vc.V)) launch(rows_kernel<uint32_t, 2>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
+        else launch(rows_kernel<uint32_t, 1>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
+    } else {
+        uint16_t *x = static_cast<uint16_t *>(logits);
+        if (by_lines(dtype, B, Vc.V)) launch(rows_kernel<uint16_t, 2>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
+        else launch(rows_kernel<uint16_t, 1>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
     }
-    const bool vec = Vc.W % 4u == 0 && reinterpret_cast<uintptr_t>(bitmask) % 16 == 0;
-    if (vec) launch(gather_kernel<true>, dim3(cdiv(Vc.W / 4u, 256), B), dim3(256), 0, s, ge, Cc, Vc.W, bitmask);
-    else launch(gather_kernel<false>, dim3(cdiv(Vc.W, 256 * 4), B), dim3(256), 0, s, ge, Cc, Vc.W, bitmask);
-    // logits that do not allow 16-byte stores take the separate apply kernels
-    if (logits) return launch_apply(logits, dtype, B, Vc.V, logits_stride, bitmask, s, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
                         const uint32_t *bitmask, hipStream_t s, hipEvent_t *ev)
 {
-    uint32_t W = (V + 31u) / 32u;
-    const bool vec_ok = apply_vec_ok(logits, dtype, V, row_stride);
-    if (vec_ok) {
-        dim3 g(cdiv(V / 8u, 256 * kApplyGroups), B);
-        if (dtype == WG_F32)
-            launch(apply_vec_kernel<uint4, 2, uint32_t>, g, dim3(256), 0, s, ev, (uint32_t *)logits, row_stride, V, W, bitmask, 0xFF800000u);
-        else
-            launch(apply_vec_kernel<uint4, 1, uint16_t>, g, dim3(256), 0, s, ev, (uint16_t *)logits, row_stride, V, W, bitmask, (uint16_t)0xFF80u);
+    const uint32_t W = (V + 31u) / 32u;
+    const dim3 g(cdiv(V, kApplyTokens), B);
+    if (dtype == WG_F32) {
+        uint32_t *x = static_cast<uint32_t *>(logits);
+        if (by_lines(dtype, B, V)) launch(apply_kernel<uint32_t, true>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
+        else launch(apply_kernel<uint32_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
     } else {
-        dim3 g(cdiv(V, 256), B);
-        if (dtype == WG_F32)
-            launch(apply_scalar_kernel<uint32_t>, g, dim3(256), 0, s, ev, (uint32_t *)logits, row_stride, V, W, bitmask, 0xFF800000u);
-        else
-            launch(apply_scalar_kernel<uint16_t>, g, dim3(256), 0, s, ev, (uint16_t *)logits, row_stride, V, W, bitmask, (uint16_t)0xFF80u);
+        uint16_t *x = static_cast<uint16_t *>(logits);
+        if (by_lines(dtype, B, V)) launch(apply_kernel<uint16_t, true>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
+        else launch(apply_kernel<uint16_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
     }
     return hipGetLastError();
 }

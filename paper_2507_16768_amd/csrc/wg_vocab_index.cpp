@@ -27,6 +27,30 @@ ClassInfo class_info_of(const uint8_t *table) {
     return ci;
 }
 
+ClassPlan class_plan_of(const uint8_t *table) {
+    ClassPlan p{};
+    uint32_t live = 0, n = 0;
+    for (uint32_t x = 0; x < 256; x++) live += table[x] != CLS_REJECT;
+    p.by_first = live <= kFewLive;
+    auto rejects = [&](uint32_t from, uint32_t count) {
+        for (uint32_t x = from; x < from + count; x++) if (table[x] != CLS_REJECT) return false;
+        return true;
+    };
+    for (uint32_t x = 0; x < 256; x++)
+        if (p.by_first ? table[x] != CLS_REJECT : table[x] >= CLS_EXIT_A) p.ids[n++] = (uint16_t)(x | table[x] << 8);
+    p.n_exits = (uint16_t)n;
+    if (!p.by_first)
+        for (uint32_t k = 0; k < 16; k++) {
+            if (rejects(16u * k, 16u)) { p.ids[n++] = (uint16_t)(kBigBlockRow + k); continue; }
+            for (uint32_t q = 4u * k; q < 4u * k + 4u; q++) {
+                if (rejects(4u * q, 4u)) { p.ids[n++] = (uint16_t)(kBlockRow + q); continue; }
+                for (uint32_t x = 4u * q; x < 4u * q + 4u; x++) if (table[x] == CLS_REJECT) p.ids[n++] = (uint16_t)x;
+            }
+        }
+    p.n_ids = (uint16_t)n;                                 // at most 256: a row stands for at least one value
+    return p;
+}
+
 namespace {
 
 int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, int32_t eos_id,
@@ -158,6 +182,41 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
         for (uint32_t i = 0; i < len8[t]; i++) byte_rows[(size_t)bytes[off[t] + i] * rs + (t >> 5)] |= 1u << (t & 31u);
         if (len8[t]) byte_rows[(size_t)(256u + first8[t]) * rs + (t >> 5)] |= 1u << (t & 31u);
     }
+    // Blocks of 4 and of 16 byte values: a set of byte values is the OR of the blocks it holds whole
+    // and of the single rows of the rest, so that an allow list's complement is a few dozen rows.
+    std::vector<uint32_t> block_rows((size_t)80 * rs, 0);
+    for (uint32_t x = 0; x < 256; x++)
+        for (uint32_t w = 0; w < rs; w++) {
+            block_rows[(size_t)(x / 4u) * rs + w] |= byte_rows[(size_t)x * rs + w];
+            block_rows[(size_t)(64u + x / 16u) * rs + w] |= byte_rows[(size_t)x * rs + w];
+        }
+    // The tokens in which a byte value occurs once, as the last byte: the ones that leave a checkpoint
+    // with their last byte, when it is an exit byte and none of the others fails to stay.
+    std::vector<uint32_t> tail_rows((size_t)256 * rs, 0);
+    for (uint32_t t = 0; t < V; t++) {
+        const uint32_t L = len8[t];
+        if (!L) continue;
+        const uint8_t last = bytes[off[t] + L - 1u];
+        if (!std::memchr(bytes.data() + off[t], last, L - 1u)) tail_rows[(size_t)last * rs + (t >> 5)] |= 1u << (t & 31u);
+    }
+    // The pairs again by their first byte and token range: what a checkpoint whose exit byte leads
+    // to another checkpoint has to look at, each range's share apart.
+    std::vector<uint32_t> place_start(256 * kParts + 1, 0);
+    for (uint32_t t = 0; t < V; t++)
+        for (uint32_t i = 1; i < len8[t]; i++) place_start[(uint32_t)bytes[off[t] + i - 1] * kParts + part_of(t) + 1u]++;
+    for (uint32_t y = 0; y < 256 * kParts; y++) place_start[y + 1] += place_start[y];
+    std::vector<ExitEntry> places(bigram.size());
+    {
+        std::vector<uint32_t> at(place_start.begin(), place_start.end() - 1);
+        for (uint32_t t = 0; t < V; t++) {
+            const uint32_t p = part_of(t);
+            for (uint32_t i = 1; i < len8[t]; i++) {
+                ExitEntry e;
+                e.tok = t; e.off = (uint8_t)i; e.cls = 0; e.first = bytes[off[t] + i]; e.rem = (uint8_t)(len8[t] - i);
+                places[at[(uint32_t)bytes[off[t] + i - 1] * kParts + p]++] = e;
+            }
+        }
+    }
     VocabIndex &ix = *out;
     ix.V = V; ix.W = W; ix.row_stride = rs; ix.lmax = lmax; ix.n_chunks = n_chunks;
     for (uint32_t p = 0; p <= kParts; p++) ix.part_tok[p] = part_tok[p];
@@ -165,6 +224,8 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
     ix.chunks.swap(chunks); ix.sig.swap(sig); ix.lit_entries.swap(lit_entries); ix.lit_start.swap(lit_start);
     ix.len_rows.swap(len_rows); ix.sorted.swap(sorted); ix.dir0.swap(dir0); ix.bigram.swap(bigram);
     ix.dirN.swap(dirN); ix.byte_rows.swap(byte_rows);
+    ix.block_rows.swap(block_rows); ix.tail_rows.swap(tail_rows); ix.places.swap(places); ix.place_start.swap(place_start);
+
     return WG_OK;
 }
 

@@ -1,0 +1,156 @@
+"""GPU parity of the row builder and of the masking at the sizes where they can go wrong: vocabularies
+at the edges of token ranges and mask words, class tables at the edges of the two ways to take one,
+logits at every alignment, and logits above the size from which whole lines are written."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import wg_synth as ws
+from oracle import oracle as O
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2507_16768_amd as wg
+    wg.load_library()
+    return torch
+
+
+def _set(chars):
+    return "{" + ", ".join("\\x%02X" % c for c in chars) + "}"
+
+
+# byte values that enter the table: 1, 2, 8 and 9 of them, a block of 16 that stays between blocks that
+# do not, exits that share a block with rejected values, no value that stays, all of them
+_TABLES = [((), b"a"), (b"b", b"a"), (b"bcdefgh", b"a"), (b"bcdefghi", b"a"), (bytes(range(0x60, 0x70)), b"pq"),
+           (bytes(range(0x20, 0x30)) + b"abc", b"x/"), ((), bytes(range(0x30, 0x3A))), (bytes(range(256)), b"<"),
+           (bytes(c for c in range(0x20, 0x7F) if c % 3), b"!$'")]
+
+
+def _texts():
+    out = []
+    for i, (allow, leave) in enumerate(_TABLES):
+        stay = _set([c for c in allow if c not in leave])
+        for bound in ("", ", max=3"):
+            w = "Wait(allow=%s, wait=%s%s)" % (stay, _set(leave), bound)
+            out.append('Sequence(%s, Write("ab"))' % w)
+            out.append("Sequence(Write(\"z\"), %s, Wait(denies={}, wait={>}, max=2))" % w)      # a checkpoint behind it
+        out.append('IfElse(condition=Wait(allow=%s, true_waits=%s, false_waits={\\x7E}), if_body=Write("a b c d e f g h i j k l m"), '
+                   'else_body=Wait(allow={a, b}, wait={c}))' % (_set([c for c in allow if c not in leave and c != 0x7E]), _set(leave)))
+    return out
+
+
+@pytest.mark.parametrize("V,longest", [(257, 8), (2047, 24), (2049, 24), (4096, 9), (16384, 24), (16385, 33), (18432, 24)])
+def test_rows_of_every_kind_of_table(torch_cuda, V, longest):
+    torch = torch_cuda
+    texts = _texts()
+    base = ws.make_workload(2, V=V, B=1, steps=1)
+    w = dataclasses.replace(base, vocab=ws.make_vocab(V, ("geometric", 4, longest), seed=V, utf8_tenths=1), texts=texts,
+                            args=[{}] * len(texts), B=len(texts), request_template=np.arange(len(texts), dtype=np.int64))
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    st = []
+    for sid in range(1, o.num_states):
+        d = o.describe(sid)
+        st += [[sid, a] for a in range(d["max"] + 1)] if d["kind"] == "WAIT" and d["max"] >= 0 else [[sid, 0]]
+    st = np.array(st + st[::7], dtype=np.uint32)                    # some states twice in a call
+    want = o.fill_masks(st)
+    d_mask = torch.empty((len(st), h.W), dtype=torch.int32, device="cuda")
+    for rep in ("cold", "warm", "cleared"):
+        if rep == "cleared":
+            h.cache_clear()
+        d_mask.fill_(0x35353535)
+        h.fill_masks(H.dev_states(st), d_mask)
+        assert (H.host_mask(d_mask) == want).all(), (rep, np.flatnonzero((H.host_mask(d_mask) != want).any(1))[:8])
+
+
+def _unpack(torch, mask, V):
+    shifts = torch.arange(32, dtype=torch.int32, device="cuda")
+    return ((mask[:, :, None] >> shifts) & 1).bool().reshape(mask.shape[0], -1)[:, :V]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [33, 1000, 8191, 8193, 20001])
+def test_masking_at_every_alignment(torch_cuda, V, dtype):
+    """apply_mask on rows that start 0 .. 17 elements into a buffer, odd and even strides."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(V)
+    B = 5
+    mask = torch.randint(-2 ** 31, 2 ** 31, (B, (V + 31) // 32), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    mask[1], mask[2], mask[3, ::2] = 0, -1, 0
+    if V % 32:
+        mask[:, -1] &= (1 << (V % 32)) - 1
+    for off in (0, 1, 3, 8, 17):
+        for pad in (0, 1, 8, 63):
+            buf = torch.randn((B * (V + pad) + 32,), generator=g, device="cuda").to(dt)
+            x = buf[off:off + B * (V + pad)].view(B, V + pad)[:, :V]
+            want = buf.clone()
+            y = want[off:off + B * (V + pad)].view(B, V + pad)[:, :V]
+            y.masked_fill_(~_unpack(torch, mask, V), float("-inf"))
+            wg.apply_mask(x, mask)
+            bits = torch.int32 if dtype == "f32" else torch.int16
+            assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
+
+
+@pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("f32", 400, 128256, 0)])
+def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, pad):
+    """More than 192 MiB of logits: lines are read where they are mixed and written whole."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(B)
+    buf = torch.randn((B, V + pad), generator=g, device="cuda").to(dt)
+    mask = torch.randint(-2 ** 31, 2 ** 31, (B, (V + 31) // 32), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    mask[::3] = 0
+    mask[1::3] |= torch.randint(-2 ** 31, 2 ** 31, mask[1::3].shape, generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    mask[1::6, : mask.shape[1] // 2] = -1
+    if V % 32:
+        mask[:, -1] &= (1 << (V % 32)) - 1
+    want = buf.clone()
+    for lo in range(0, B, 64):
+        want[lo:lo + 64, :V].masked_fill_(~_unpack(torch, mask[lo:lo + 64], V), float("-inf"))
+    wg.apply_mask(buf[:, :V], mask)
+    bits = torch.int32 if dtype == "f32" else torch.int16
+    assert torch.equal(buf.view(bits), want.view(bits))
+
+
+@pytest.mark.parametrize("dtype,stride_pad", [("bf16", 0), ("f32", 5)])
+def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
+    """wg_decode_step with logits beyond the last-level cache against the separate calls (which the
+    other tests compare with the oracle): masks, states and masked logits, cold and warm."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    w = ws.make_workload(5, V=151936 if dtype == "bf16" else 60001, B=720 if dtype == "bf16" else 900, steps=3)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    st = H.dev_states(H.start_states(o, w))
+    ref = st.clone()
+    mask, ref_mask = (torch.empty((w.B, h.W), dtype=torch.int32, device="cuda") for _ in range(2))
+    draws = torch.from_numpy(w.token_draws(3).view(np.int64)).cuda()
+    tok = torch.empty(w.B, dtype=torch.int32, device="cuda")
+    for k in range(3):
+        x = torch.randn((w.B, w.vocab.V + stride_pad), device="cuda").to(dt)
+        y = x.clone()
+        if k != 1:
+            h.cache_clear()
+        h.decode_step(st, tok if k else None, mask, x[:, :w.vocab.V])
+        if k:
+            h.advance(ref, tok)
+        h.cache_clear()
+        h.fill_masks(ref, ref_mask)
+        wg.apply_mask(y[:, :w.vocab.V], ref_mask)
+        assert torch.equal(mask, ref_mask) and torch.equal(st, ref), k
+        bits = torch.int32 if dtype == "f32" else torch.int16
+        assert torch.equal(x.view(bits), y.view(bits)), k
+        assert (H.host_mask(mask)[::90] == o.fill_masks(H.host_states(st)[::90])).all()
+        wg.select_tokens(mask, w.vocab.V, draws[k], tok)
+    assert h.error_count() == 0
