@@ -1,4 +1,7 @@
-"""ctypes binding of libwgrammar.so: same names as the C ABI, argument marshalling only.
+"""Binding of libwgrammar.so: same names as the C ABI, argument marshalling only.
+
+The calls of a decode loop go through the native module `_native` (csrc/wg_python.cpp), which checks
+the tensors and calls the C ABI without Python code in between; set-up and inspection use ctypes.
 
 Device buffers are torch tensors (torch is used for device memory and streams, nothing
 else).  There is no fallback: if the shared library is missing, loading fails.
@@ -20,6 +23,7 @@ SHARE_STATES = 2          # or-ed to either: states with equal futures share the
 SID_FINAL, SID_ERROR = 0, 0xFFFFFFFF
 
 _lib = None
+_native = None
 
 
 class WgError(RuntimeError):
@@ -69,7 +73,7 @@ def library_path():
 
 def load_library():
     """Loads the in-tree shared library; raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     path = library_path()
@@ -130,8 +134,16 @@ def load_library():
     L.wg_profile_enable.argtypes = [vp, C.c_int]
     L.wg_profile_read.argtypes = [vp, C.POINTER(_Profile)]
     L.wg_profile_apply_mask.argtypes = [vp, vp, C.c_int, u32, u32, i64, vp, vp]
+    from . import _native as native       # fails loudly when it has not been built
+    native.set_error(WgError)
+    _native = native
     _lib = L
     return L
+
+
+def _load_native():
+    load_library()
+    return _native
 
 
 def _check(rc):
@@ -271,73 +283,36 @@ class Handle:
         self.start_states = starts[:n]
         self.num_states = L.wg_num_states(self._h)
         self.W = L.wg_mask_words(self._h)
+        self.V = vocab.V
+        self._p = self._h.value                  # the handle as the native module takes it
 
     def fill_masks(self, states, bitmask, stream=None):
-        import torch
-        B = states.shape[0]
-        if tuple(states.shape) != (B, 2) or tuple(bitmask.shape) != (B, self.W):
-            raise ValueError("states must be [B, 2] and bitmask [B, W]")
-        _check(load_library().wg_fill_masks(self._h, _dev(states, torch.int32, "states"), B,
-                                            _dev(bitmask, torch.int32, "bitmask"), _stream_ptr(stream)))
+        _native.fill_masks(self._p, self.W, states, bitmask, stream)
 
     def advance(self, states, tokens, stream=None):
-        import torch
-        B = states.shape[0]
-        if tuple(states.shape) != (B, 2) or tuple(tokens.shape) != (B,):
-            raise ValueError("states must be [B, 2] and tokens [B]")
-        _check(load_library().wg_advance(self._h, _dev(states, torch.int32, "states"),
-                                         _dev(tokens, torch.int32, "tokens"), B, _stream_ptr(stream)))
+        _native.advance(self._p, states, tokens, stream)
 
     def advance_fill_masks(self, states, tokens, bitmask, stream=None):
-        import torch
-        B = states.shape[0]
-        if tuple(states.shape) != (B, 2) or tuple(tokens.shape) != (B,) or tuple(bitmask.shape) != (B, self.W):
-            raise ValueError("states must be [B, 2], tokens [B] and bitmask [B, W]")
-        _check(load_library().wg_advance_fill_masks(
-            self._h, _dev(states, torch.int32, "states"), _dev(tokens, torch.int32, "tokens"), B,
-            _dev(bitmask, torch.int32, "bitmask"), _stream_ptr(stream)))
+        _native.advance_fill_masks(self._p, self.W, states, tokens, bitmask, stream)
 
     def decode_step(self, states, tokens, bitmask, logits, stream=None):
         """wg_decode_step; tokens may be None (first step)."""
-        import torch
-        B = states.shape[0]
-        if tuple(states.shape) != (B, 2) or tuple(bitmask.shape) != (B, self.W):
-            raise ValueError("states must be [B, 2] and bitmask [B, W]")
-        if tokens is not None and tuple(tokens.shape) != (B,):
-            raise ValueError("tokens must be [B]")
-        if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1 or logits.shape[0] != B:
-            raise ValueError("logits must be a [B, V] device tensor with unit inner stride")
-        if logits.shape[1] != self.vocab.V:
-            raise ValueError("logits must have the vocabulary's width")
-        dt = {torch.float32: F32, torch.bfloat16: BF16}.get(logits.dtype)
-        if dt is None:
-            raise ValueError("logits must be float32 or bfloat16")
-        _check(load_library().wg_decode_step(
-            self._h, _dev(states, torch.int32, "states"),
-            None if tokens is None else _dev(tokens, torch.int32, "tokens"), B,
-            _dev(bitmask, torch.int32, "bitmask"), C.c_void_p(logits.data_ptr()), dt, logits.stride(0),
-            _stream_ptr(stream)))
+        _native.decode_step(self._p, self.W, self.V, states, tokens, bitmask, logits, stream)
 
     def forced_bytes(self, states, out_bytes, out_lens, end_states=None, stream=None):
         """wg_forced_bytes: out_bytes uint8 [B, cap], out_lens int32 [B], end_states int32 [B, 2] or None."""
-        import torch
-        B = states.shape[0]
-        if tuple(states.shape) != (B, 2) or out_bytes.dim() != 2 or out_bytes.shape[0] != B or tuple(out_lens.shape) != (B,):
-            raise ValueError("states must be [B, 2], out_bytes [B, cap] and out_lens [B]")
-        if end_states is not None and tuple(end_states.shape) != (B, 2):
-            raise ValueError("end_states must be [B, 2]")
-        _check(load_library().wg_forced_bytes(
-            self._h, _dev(states, torch.int32, "states"), B, out_bytes.shape[1],
-            _dev(out_bytes, torch.uint8, "out_bytes"), _dev(out_lens, torch.int32, "out_lens"),
-            None if end_states is None else _dev(end_states, torch.int32, "end_states"), _stream_ptr(stream)))
+        _native.forced_bytes(self._p, states, out_bytes, out_lens, end_states, stream)
 
     def add_instances(self, texts, args, stream=None, marshalled=None):
         """wg_add_instances: returns the start states [n, 2] of the new instances.  `marshalled`
         takes what marshal_templates(texts, args) made beforehand instead of texts and args."""
         L = load_library()
-        c_texts, c_args, n, _keep = marshalled if marshalled is not None else _marshal_templates(texts, args)
+        n = marshalled[2] if marshalled is not None else len(texts)
         starts = np.zeros((max(n, 1), 2), dtype=np.uint32)
-        _check(L.wg_add_instances(self._h, c_texts, c_args, n, starts.ctypes.data, _stream_ptr(stream)))
+        if marshalled is not None:
+            _check(L.wg_add_instances(self._h, marshalled[0], marshalled[1], n, starts.ctypes.data, _stream_ptr(stream)))
+        else:
+            _native.add_instances(self._p, texts, args, starts.ctypes.data, stream)
         self.start_states = np.concatenate([self.start_states, starts[:n]])
         self.num_states = L.wg_num_states(self._h)
         return starts[:n]
@@ -358,7 +333,7 @@ class Handle:
         _check(load_library().wg_cache_resize(self._h, int(rows)))
 
     def cache_clear(self, stream=None):
-        _check(load_library().wg_cache_clear(self._h, _stream_ptr(stream)))
+        _native.cache_clear(self._p, stream)
 
     def cache_stats(self):
         s = _Stats()
@@ -398,36 +373,12 @@ class Handle:
 
 def apply_mask(logits, bitmask, stream=None):
     """wg_apply_mask on a [B, V] float32 or bfloat16 device tensor (rows may be strided)."""
-    import torch
-    if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1:
-        raise ValueError("logits must be a 2-d device tensor with unit inner stride")
-    if logits.dtype == torch.float32:
-        dt = F32
-    elif logits.dtype == torch.bfloat16:
-        dt = BF16
-    else:
-        raise ValueError("logits must be float32 or bfloat16")
-    B, V = logits.shape
-    if tuple(bitmask.shape) != (B, (V + 31) // 32):
-        raise ValueError("bitmask must be [B, ceil(V/32)]")
-    _check(load_library().wg_apply_mask(C.c_void_p(logits.data_ptr()), dt, B, V, logits.stride(0),
-                                        _dev(bitmask, torch.int32, "bitmask"), _stream_ptr(stream)))
+    (_native or _load_native()).apply_mask(logits, bitmask, stream)
 
 
 def masked_argmax(logits, bitmask, tokens, stream=None):
     """wg_masked_argmax on a [B, V] float32 or bfloat16 device tensor; tokens is int32 [B]."""
-    import torch
-    if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1:
-        raise ValueError("logits must be a 2-d device tensor with unit inner stride")
-    dt = {torch.float32: F32, torch.bfloat16: BF16}.get(logits.dtype)
-    if dt is None:
-        raise ValueError("logits must be float32 or bfloat16")
-    B, V = logits.shape
-    if tuple(bitmask.shape) != (B, (V + 31) // 32) or tuple(tokens.shape) != (B,):
-        raise ValueError("bitmask must be [B, ceil(V/32)] and tokens [B]")
-    _check(load_library().wg_masked_argmax(C.c_void_p(logits.data_ptr()), dt, B, V, logits.stride(0),
-                                           _dev(bitmask, torch.int32, "bitmask"),
-                                           _dev(tokens, torch.int32, "tokens"), _stream_ptr(stream)))
+    (_native or _load_native()).masked_argmax(logits, bitmask, tokens, stream)
 
 
 def masked_topk_workspace(B, V, k):
@@ -438,22 +389,9 @@ def masked_topk_workspace(B, V, k):
 def masked_topk(logits, bitmask, ids, values, workspace, stream=None):
     """wg_masked_topk on a [B, V] float32 or bfloat16 device tensor: ids is int32 [B, k], values
     [B, k] of the logits' dtype, workspace a device tensor of at least masked_topk_workspace bytes."""
-    import torch
-    if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1:
-        raise ValueError("logits must be a 2-d device tensor with unit inner stride")
-    dt = {torch.float32: F32, torch.bfloat16: BF16}.get(logits.dtype)
-    if dt is None:
-        raise ValueError("logits must be float32 or bfloat16")
-    B, V = logits.shape
-    if ids.dim() != 2 or ids.shape[0] != B or tuple(values.shape) != tuple(ids.shape):
-        raise ValueError("ids and values must be [B, k]")
-    if tuple(bitmask.shape) != (B, (V + 31) // 32):
-        raise ValueError("bitmask must be [B, ceil(V/32)]")
-    _check(load_library().wg_masked_topk(C.c_void_p(logits.data_ptr()), dt, B, V, logits.stride(0),
-                                         _dev(bitmask, torch.int32, "bitmask"), ids.shape[1],
-                                         _dev(ids, torch.int32, "ids"), _dev(values, logits.dtype, "values"),
-                                         _dev(workspace, None, "workspace"),
-                                         workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
+    if workspace is None:
+        raise ValueError("workspace must be a contiguous device tensor")
+    (_native or _load_native()).masked_topk(logits, bitmask, ids, values, workspace, stream)
 
 
 def masked_topk_static_capacity():
@@ -463,27 +401,9 @@ def masked_topk_static_capacity():
 
 def masked_topk_static(logits, bitmask, ids, values, stream=None):
     """wg_masked_topk_static: wg_masked_topk with the library's own workspace (nothing allocated)."""
-    import torch
-    if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1:
-        raise ValueError("logits must be a 2-d device tensor with unit inner stride")
-    dt = {torch.float32: F32, torch.bfloat16: BF16}.get(logits.dtype)
-    if dt is None:
-        raise ValueError("logits must be float32 or bfloat16")
-    B, V = logits.shape
-    if ids.dim() != 2 or ids.shape[0] != B or tuple(values.shape) != tuple(ids.shape):
-        raise ValueError("ids and values must be [B, k]")
-    if tuple(bitmask.shape) != (B, (V + 31) // 32):
-        raise ValueError("bitmask must be [B, ceil(V/32)]")
-    _check(load_library().wg_masked_topk_static(C.c_void_p(logits.data_ptr()), dt, B, V, logits.stride(0),
-                                                _dev(bitmask, torch.int32, "bitmask"), ids.shape[1],
-                                                _dev(ids, torch.int32, "ids"), _dev(values, logits.dtype, "values"),
-                                                _stream_ptr(stream)))
+    (_native or _load_native()).masked_topk(logits, bitmask, ids, values, None, stream)
 
 
 def select_tokens(bitmask, V, draws, tokens, stream=None):
     """wg_select_tokens: harness sampler stand-in."""
-    import torch
-    B = bitmask.shape[0]
-    _check(load_library().wg_select_tokens(_dev(bitmask, torch.int32, "bitmask"), B, V,
-                                           _dev(draws, torch.int64, "draws"),
-                                           _dev(tokens, torch.int32, "tokens"), _stream_ptr(stream)))
+    (_native or _load_native()).select_tokens(bitmask, V, draws, tokens, stream)

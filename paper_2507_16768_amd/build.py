@@ -12,11 +12,41 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wal
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+NATIVE = os.path.join(HERE, "_native.so")      # the Python module behind binding.py, on top of LIB
+NATIVE_SOURCE = "wg_python.cpp"
+
+
 def is_stale():
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS + [NATIVE_SOURCE])
+
+
+def _torch_dir():
+    import importlib.util
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def build_native(verbose=False):
+    """The Python module: host code only, against torch's headers and LIB."""
+    import sysconfig
+    torch = _torch_dir()
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = NATIVE + ".%d.tmp" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-isystem", os.path.join(torch, "include"), "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-o", tmp, os.path.join(CSRC, NATIVE_SOURCE), LIB, "-L" + os.path.join(torch, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(torch, "lib")]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + r.stdout + r.stderr)
+    os.replace(tmp, NATIVE)
+    return NATIVE
 
 
 def build(verbose=False):
@@ -29,6 +59,7 @@ def build(verbose=False):
     if r.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + r.stdout + r.stderr)
     os.replace(tmp, LIB)
+    build_native(verbose)
     return LIB
 
 
