@@ -249,7 +249,7 @@ int wg_apply_mask(void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t V,
  * logits are only read (nothing is set to -inf), so this call replaces wg_apply_mask + argmax.
  * A NaN ranks below every number (also below -inf), equal values (-0.0 equals +0.0) keep the
  * lowest token id, a row that allows nothing gives -1.  Layout of logits and mask as in
- * wg_apply_mask.  The workgroups of a row merge through a per-GPU scratch array inside the
+ * wg_apply_mask.  The workgroups of a row of a small batch merge through a per-GPU scratch array inside the
  * library, so two wg_masked_argmax calls must not overlap on one GPU (order them on one stream). */
 int wg_masked_argmax(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t V,
                      int64_t row_stride_elems, const uint32_t *d_bitmask, int32_t *d_tokens,
@@ -264,10 +264,10 @@ int wg_masked_argmax(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_
  * allows fewer than k tokens ends with ids of -1 and values of -inf.  1 <= k <= 64;
  * B <= 65535; ceil(V / 8192) * k <= 4096.  d_ids is int32 [B][k], d_values [B][k] of `dtype`.
  * d_workspace: device memory of at least wg_masked_topk_workspace(B, V, k) bytes, 8-byte
- * aligned, owned by the caller, overwritten by the call (it holds the best k of every 8,192
- * tokens of a row between the call's two kernels); calls that share a workspace must not
+ * aligned, owned by the caller, overwritten by the call (for a small batch it holds the best k of
+ * every 8,192 tokens of a row between the call's two kernels); calls that share a workspace must not
  * overlap.  Mask bits at and above V must be zero, as wg_fill_masks leaves them.  Enqueues
- * two kernels on `stream`; nothing is allocated.  Arguments outside the limits above, a null
+ * one or two kernels on `stream`; nothing is allocated.  Arguments outside the limits above, a null
  * pointer or a workspace that is too small or misaligned give WG_ERR_INVALID and launch nothing. */
 uint64_t wg_masked_topk_workspace(uint32_t B, uint32_t V, uint32_t k);
 int wg_masked_topk(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t V,
@@ -282,7 +282,7 @@ int wg_masked_topk(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t 
  * process ends; wg_masked_topk_static_capacity() returns its size in bytes), so a call needs
  * B * ceil(V / 8192) * k * 8 <= 4,194,304 (B = 256, V = 151,936, k = 64 takes 2.5 MB); anything
  * larger gives WG_ERR_INVALID and launches nothing.  The call allocates and frees nothing and
- * enqueues two kernels on `stream`; the array's address on the current device is asked of the
+ * enqueues one or two kernels on `stream`; the array's address on the current device is asked of the
  * HIP runtime once (by wg_vocab_create on that device, else by the first call).  Every call on a
  * GPU uses that GPU's one array: calls that overlap on one GPU (two streams, two threads) race;
  * order them on one stream.  Nothing has to be cleared between calls: the first kernel writes

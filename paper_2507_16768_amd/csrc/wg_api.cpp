@@ -578,8 +578,6 @@ int wg_masked_topk(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t 
     if (B > kMaxBatch) return fail(WG_ERR_INVALID, "wg_masked_topk: B above 65535");
     if (k == 0 || k > kTopkMax) return fail(WG_ERR_INVALID, "wg_masked_topk: k must be 1 .. 64");
     const uint64_t n_slices = ((uint64_t)V + kTopkSlice - 1u) / kTopkSlice;
-    // the lists of a row's slices are merged in LDS, next to the merge's own 18 KB, within the
-    // 64 KB a kernel gets without asking
     if (n_slices * k > kTopkMergeKeys)
         return fail(WG_ERR_INVALID, "wg_masked_topk: ceil(V / 8192) * k above 4096 (the lists of a row do not fit the merge)");
     if (workspace_bytes < wg_masked_topk_workspace(B, V, k))

@@ -1,0 +1,678 @@
+// Sampling under the mask for gfx950 (wave64): the greedy choice and the k best allowed tokens of every
+// row, logits read once and never written.
+//
+// A workgroup of 1,024 threads takes a row.  The row's mask goes to LDS; every thread then keeps the
+// largest allowed logit of its 16-byte pieces and where it was.  From 256 rows on that is HBM bound,
+// and nothing has to be merged.  One compute unit streams only about 30 GB/s however much it has in
+// flight (a 304 KB row takes 10 us), so smaller batches cut their rows: the greedy choice into as
+// many workgroups as there are compute units, merged by the last of them to finish; the k best of
+// long rows into slices of 8,192 tokens, merged by a second kernel.
+//
+// Times for V = 151,936, bf16, the greedy choice and k = 50, before -> now (before: a workgroup per slice
+// and a second kernel always): B = 1 12.5 -> 5.9 and 13.7 -> 12.1 us, B = 64 12.2 -> 8.3 and 18.9 -> 17.9,
+// B = 256 19.5 -> 17.1 and 38.6 -> 21.8, B = 1,024 56 -> 52 and 117 -> 67.
+//
+// The k best need no sorting of the row: in each of n wavefronts the ceil(k / n)-th largest of the 64
+// thread maxima is found by bisection on ballots, and the least of these is a lower bound for the k-th
+// best token.  Two to three times k tokens reach it; they are ranked by counting.
+//
+// Rows may start at any element: pieces are aligned 16-byte blocks, the first of them may begin
+// before the row and the last may end behind it, and the staged mask has those tokens as disallowed.
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+
+#include "wg_device.h"
+#include "wg_order.h"
+
+namespace wg {
+
+constexpr uint32_t kThreads = 1024;
+constexpr uint32_t kWaves = kThreads / 64u;
+constexpr uint32_t kSegWords = 8192;                 // mask words staged at a time (32 KB: 262,144 tokens)
+constexpr uint32_t kCand = 1024;                     // candidates ranked in LDS
+constexpr uint32_t kNoPiece = 0xFFFFFFFFu;
+
+// One row of logits as aligned 16-byte pieces.
+template <typename Elem>
+struct Row {
+    static constexpr uint32_t kPer = 16u / sizeof(Elem);          // tokens of a piece: 8 bf16, 4 fp32
+    static constexpr uint32_t kAll = (1u << kPer) - 1u;
+    const Elem *tokens;
+    const uint4 *blocks;                             // piece p holds the tokens p * kPer - skew ...
+    uint32_t skew, pieces, V;
+    bool whole;                                      // elements lie at multiples of their size: pieces can be loaded as such
+
+    __device__ __forceinline__ Row(const Elem *row, uint32_t V_) : tokens(row), V(V_)
+    {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(row);
+        whole = at % sizeof(Elem) == 0u;
+        skew = whole ? (uint32_t)(at % 16u / sizeof(Elem)) : 0u;
+        blocks = reinterpret_cast<const uint4 *>(at - (at % 16u));
+        pieces = (V + skew + kPer - 1u) / kPer;
+    }
+    // A piece with allowed tokens m.  An aligned 16-byte block that holds a token of the row lies in
+    // the row's own memory page, also where it begins before the row or ends behind it.
+    __device__ __forceinline__ uint4 load(uint32_t p, uint32_t m) const
+    {
+        if (whole) return blocks[p];
+        union { uint4 v; Elem e[kPer]; } u;
+        u.v = uint4{0u, 0u, 0u, 0u};
+        for (uint32_t i = 0; i < kPer; i++)
+            if ((m >> i) & 1u) u.e[i] = tokens[(size_t)p * kPer + i];
+        return u.v;
+    }
+    __device__ __forceinline__ uint32_t token(uint32_t p, uint32_t i) const { return p * kPer + i - skew; }
+};
+
+// Word i of the row's mask moved up by the skew: bit s of the result is the token s - skew.
+__device__ __forceinline__ uint32_t mask_word(const uint32_t *mask, uint32_t W, uint32_t V, uint32_t skew, uint32_t i)
+{
+    auto word = [&](uint32_t w) {
+        uint32_t x = w < W ? mask[w] : 0u;
+        if (w == W - 1u && (V & 31u)) x &= (1u << (V & 31u)) - 1u;
+        return x;
+    };
+    const uint32_t hi = word(i);
+    return skew ? (hi << skew) | ((i ? word(i - 1u) : 0u) >> (32u - skew)) : hi;
+}
+
+// The allowed tokens of piece p, from the mask as it lies in memory.
+template <typename Elem>
+__device__ __forceinline__ uint32_t piece_mask(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t p)
+{
+    const uint32_t bit = p * Row<Elem>::kPer;
+    return (mask_word(mask, W, r.V, r.skew, bit >> 5) >> (bit & 31u)) & Row<Elem>::kAll;
+}
+
+// The largest allowed number of a piece (NaN when there is none): a disallowed token's bits are
+// forced to all ones, which is a NaN in both formats, and the hardware maximum ignores NaNs, so
+// NaN logits drop out the same way.
+__device__ __forceinline__ float piece_max(const uint4 &v, uint32_t m, uint16_t)
+{
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t nm = ~m;
+    float a = __builtin_nanf(""), b = a;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {                     // dword k holds tokens 2k (low half) and 2k+1
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe(nm, 2 * k, 1), hi = (uint32_t)__builtin_amdgcn_sbfe(nm, 2 * k + 1, 1);
+        const uint32_t x = d[k] | (lo & 0xFFFFu) | (hi << 16);
+        a = __builtin_fmaxf(a, __uint_as_float(x << 16));
+        b = __builtin_fmaxf(b, __uint_as_float(x & 0xFFFF0000u));
+    }
+    return __builtin_fmaxf(a, b);
+}
+__device__ __forceinline__ float piece_max(const uint4 &v, uint32_t m, uint32_t)
+{
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t nm = ~m;
+    float a = __builtin_nanf("");
+#pragma unroll
+    for (int k = 0; k < 4; k++) a = __builtin_fmaxf(a, __uint_as_float(d[k] | (uint32_t)__builtin_amdgcn_sbfe(nm, k, 1)));
+    return a;
+}
+
+// Streams the pieces [lo, hi) of the row, lo a multiple of 32: what(p, piece, allowed tokens) for every
+// piece of the thread that has an allowed token, in ascending order.  `words` is kSegWords words of
+// LDS.  The whole workgroup calls it.
+template <typename Elem, typename F>
+__device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t *words,
+                                           uint32_t lo, uint32_t hi, F what)
+{
+    constexpr uint32_t kPer = Row<Elem>::kPer, kSegPieces = kSegWords * 32u / kPer;
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t s0 = lo; s0 < hi; s0 += kSegPieces) {
+        const uint32_t n = hi - s0 < kSegPieces ? hi - s0 : kSegPieces;
+        const uint32_t w0 = s0 / (32u / kPer), nw = (n * kPer + 31u) / 32u;
+        if (s0 != lo) __syncthreads();                     // the segment before is done with the LDS
+        for (uint32_t i = tid; i < nw; i += kThreads) words[i] = mask_word(mask, W, r.V, r.skew, w0 + i);
+        __syncthreads();
+        // two batches of three pieces, one in flight while the other is looked at (B = 256, V = 151,936,
+        // bf16: 17.1 us; one batch of eight 17.9, two of four 18.9; within the 64 registers of two workgroups
+        // on a compute unit)
+        constexpr uint32_t kHalf = 3u;
+        uint32_t m[2][kHalf];
+        uint4 v[2][kHalf];
+        auto request = [&](uint32_t (&mm)[kHalf], uint4 (&vv)[kHalf], uint32_t q0) {
+#pragma unroll
+            for (uint32_t j = 0; j < kHalf; j++) {
+                const uint32_t q = q0 + j * kThreads, bit = q * kPer;
+                mm[j] = q < n ? (words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : 0u;
+                vv[j] = uint4{0u, 0u, 0u, 0u};
+                if (mm[j]) vv[j] = r.load(s0 + q, mm[j]);
+            }
+        };
+        auto look = [&](const uint32_t (&mm)[kHalf], const uint4 (&vv)[kHalf], uint32_t q0) {
+#pragma unroll
+            for (uint32_t j = 0; j < kHalf; j++)
+                if (mm[j]) what(s0 + q0 + j * kThreads, vv[j], mm[j]);
+        };
+        request(m[0], v[0], tid);
+        for (uint32_t q0 = tid; q0 < n; q0 += kThreads * kHalf * 2u) {
+            request(m[1], v[1], q0 + kThreads * kHalf);
+            look(m[0], v[0], q0);
+            request(m[0], v[0], q0 + kThreads * kHalf * 2u);
+            look(m[1], v[1], q0 + kThreads * kHalf);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// masked argmax.  A row cut into several workgroups is merged through the two arrays: each workgroup
+// raises the row's key (the order key of its logit << 32 | ~id; 0: nothing allowed) and then takes
+// a ticket; the one that takes the last ticket finds the row's key complete, and leaves both zero
+// for the next call.  One copy per GPU: calls that cut their rows must not overlap on one GPU.
+constexpr uint32_t kCutRows = 256;
+__device__ unsigned long long g_argmax_key[kCutRows];
+__device__ uint32_t g_argmax_ticket[kCutRows];
+
+template <typename Elem>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
+                     const uint32_t *__restrict__ bitmask, int32_t *__restrict__ tokens)
+{
+    __shared__ uint32_t words[kSegWords];
+    __shared__ float part[kWaves];
+    __shared__ uint32_t best_token;
+    const uint32_t b = blockIdx.y, tid = threadIdx.x;
+    const uint32_t *mask = bitmask + (size_t)b * W;
+    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    const uint32_t share = ((r.pieces + gridDim.x - 1u) / gridDim.x + 31u) & ~31u;
+    const uint32_t lo = blockIdx.x * share < r.pieces ? blockIdx.x * share : r.pieces;
+    const uint32_t hi = r.pieces - lo < share ? r.pieces : lo + share;
+    float best = __builtin_nanf("");
+    uint32_t where = kNoPiece;                        // the thread's first piece with `best`
+    stream_row(r, mask, W, words, lo, hi, [&](uint32_t p, const uint4 &v, uint32_t m) {
+        const float x = piece_max(v, m, Elem(0));
+        if (x > best || (where == kNoPiece && x == x)) { best = x; where = p; }
+    });
+    float top = best;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = __builtin_fmaxf(top, __shfl_xor(top, o));
+    if ((tid & 63u) == 0u) part[tid >> 6] = top;
+    if (tid == 0) best_token = 0xFFFFFFFFu;
+    __syncthreads();
+    top = part[0];
+#pragma unroll
+    for (uint32_t w = 1; w < kWaves; w++) top = __builtin_fmaxf(top, part[w]);
+    const bool number = top == top;
+    if (number) {
+        // The lowest token whose logit equals the maximum (as numbers, so -0.0 and +0.0 tie), from
+        // the threads that hold it: their first such piece once more.
+        if (where != kNoPiece && best == top) {
+            const uint32_t m = piece_mask(r, mask, W, where);
+            union { uint4 v; Elem e[Row<Elem>::kPer]; } u;
+            u.v = r.load(where, m);
+            uint32_t eq = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < Row<Elem>::kPer; i++) eq |= (uint32_t)(elem_float(u.e[i]) == top) << i;
+            atomicMin(&best_token, r.token(where, (uint32_t)__builtin_ctz(eq & m)));
+        }
+    } else {
+        // no number among the allowed tokens: the lowest of them (all NaN), if there is one
+        for (uint32_t p = lo + tid; p < hi; p += kThreads) {
+            const uint32_t m = piece_mask(r, mask, W, p);
+            if (m) { atomicMin(&best_token, r.token(p, (uint32_t)__builtin_ctz(m))); break; }
+        }
+    }
+    __syncthreads();
+    if (tid) return;
+    uint32_t token = best_token;                      // all ones is -1: nothing allowed
+    if (gridDim.x > 1u) {
+        const unsigned long long key = token == 0xFFFFFFFFu ? 0ull :
+            (unsigned long long)(number ? order_key(__float_as_uint(top)) : 0u) << 32 | (0xFFFFFFFFu - token);
+        const unsigned long long was = atomicMax(&g_argmax_key[b], key);
+        asm volatile("" : : "v"(was) : "memory");     // the key is raised before the ticket is taken
+        if (atomicAdd(&g_argmax_ticket[b], 1u) != gridDim.x - 1u) return;
+        const unsigned long long row = atomicExch(&g_argmax_key[b], 0ull);
+        g_argmax_ticket[b] = 0u;
+        token = row ? 0xFFFFFFFFu - (uint32_t)row : 0xFFFFFFFFu;
+    }
+    tokens[b] = (int32_t)token;
+}
+
+// ---------------------------------------------------------------------------------------------
+// masked top-k.  The rank of a token is its order key plus one (0: not allowed, 1: a NaN), then the
+// lower id.
+template <typename Elem>
+__device__ __forceinline__ uint32_t rank_of(Elem e) { return order_key(__float_as_uint(elem_float(e))) + 1u; }
+
+// The n-th largest of the wavefront's 64 values with its low 12 bits cleared (0 when fewer than n are
+// above 0), by bisection: a ballot and a count per bit.
+__device__ __forceinline__ uint32_t nth_of_wave(uint32_t v, uint32_t n)
+{
+    uint32_t bound = 0;
+#pragma unroll
+    for (uint32_t bit = 31u; bit >= 12u; bit--) {
+        const uint32_t test = bound | 1u << bit;
+        if ((uint32_t)__popcll(__ballot(v >= test)) >= n) bound = test;
+    }
+    return bound;
+}
+
+// A value that at least k of the workgroup's values reach (0 when there are none such): the least of
+// the wavefronts' ceil(k / n)-th largest.  `least` is a word of LDS per wavefront.
+template <uint32_t kN>
+__device__ __forceinline__ uint32_t bound_of(uint32_t own, uint32_t k, uint32_t *least)
+{
+    const uint32_t mine = nth_of_wave(own, (k + kN - 1u) / kN);
+    if ((threadIdx.x & 63u) == 0u) least[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    uint32_t bound = least[0];
+#pragma unroll
+    for (uint32_t w = 1; w < kN; w++) bound = least[w] < bound ? least[w] : bound;
+    return bound;
+}
+
+// The number from which on tokens reach a bound above 0 (ranks are order keys plus one).
+__device__ __forceinline__ float bound_value(uint32_t bound)
+{
+    const uint32_t key = bound - 1u;
+    uint32_t u = (key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key;
+    if ((u & 0x7FFFFFFFu) > 0x7F800000u) u = 0xFF800000u;       // below every number: from -inf on
+    return __uint_as_float(u);
+}
+// Which of the allowed tokens of a piece reach the bound (all of them a bound of 0, NaNs too).
+__device__ __forceinline__ uint32_t reaching(const uint4 &v, uint32_t m, uint32_t bound, float value, uint16_t)
+{
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    uint32_t take = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        take |= (uint32_t)(__uint_as_float(d[k] << 16) >= value) << (2 * k);
+        take |= (uint32_t)(__uint_as_float(d[k] & 0xFFFF0000u) >= value) << (2 * k + 1);
+    }
+    return bound ? take & m : m;
+}
+__device__ __forceinline__ uint32_t reaching(const uint4 &v, uint32_t m, uint32_t bound, float value, uint32_t)
+{
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    uint32_t take = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) take |= (uint32_t)(__uint_as_float(d[k]) >= value) << k;
+    return bound ? take & m : m;
+}
+
+// The keys of n candidate tokens, from their logits read again (which register of which thread holds a
+// candidate's is not known at compile time; they are in the L2).
+template <uint32_t kT, typename Elem>
+__device__ __forceinline__ void make_keys(unsigned long long *cand, const uint32_t *ids, uint32_t n, const Row<Elem> &r)
+{
+    for (uint32_t i = threadIdx.x; i < n; i += kT) {
+        const uint32_t id = ids[i];
+        cand[i] = (unsigned long long)rank_of(r.tokens[id]) << 32 | (0xFFFFFFFFu - id);
+    }
+}
+
+// Ranks n keys by counting, eight lanes to a key; calls emit(rank, key) for the best k.
+template <uint32_t kT, typename F>
+__device__ __forceinline__ void rank_keys(const unsigned long long *cand, uint32_t n, uint32_t k, F emit)
+{
+    const uint32_t sub = threadIdx.x & 7u;
+    for (uint32_t i = threadIdx.x >> 3; i < n; i += kT / 8u) {
+        const unsigned long long x = cand[i];
+        uint32_t better = 0;
+#pragma unroll 4
+        for (uint32_t q = sub; q < n; q += 8u) better += cand[q] > x;
+        better += __shfl_xor(better, 1); better += __shfl_xor(better, 2); better += __shfl_xor(better, 4);
+        if (sub == 0u && better < k) emit(better, x);
+    }
+}
+
+// The logit behind a key: its bits follow from the rank, except that a zero's sign and a NaN's payload
+// are lost in it, so those are read again.
+template <typename Elem>
+__device__ __forceinline__ Elem logit_of(unsigned long long key, const Elem *row)
+{
+    const uint32_t order = (uint32_t)(key >> 32) - 1u;
+    const uint32_t u = (order & 0x80000000u) ? order & 0x7FFFFFFFu : ~order;
+    if (u == 0u || order == 0u) return row[0xFFFFFFFFu - (uint32_t)key];
+    return (Elem)(sizeof(Elem) == 4 ? u : u >> 16);
+}
+
+struct TopkShared {
+    uint32_t words[kSegWords];                       // the staged mask
+    union {
+        unsigned long long cand[kCand];              // the candidates: rank << 32 | ~id
+        uint32_t bins[256];
+    };
+    uint32_t threads[kThreads];                      // threads that hold candidates
+    uint32_t id[kCand];                              // the candidates' tokens, before their keys are made
+    uint32_t count[kWaves];
+    uint32_t n, n_threads, digit, above;
+};
+
+template <typename Elem>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
+                   const uint32_t *__restrict__ bitmask, uint32_t k, int32_t *__restrict__ ids,
+                   Elem *__restrict__ values, Elem ninf)
+{
+    constexpr uint32_t kPer = Row<Elem>::kPer;
+    __shared__ TopkShared sh;
+    const uint32_t b = blockIdx.x, tid = threadIdx.x;
+    const uint32_t *mask = bitmask + (size_t)b * W;
+    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    int32_t *id_out = ids + (size_t)b * k;
+    Elem *value_out = values + (size_t)b * k;
+    float best = __builtin_nanf("");
+    uint32_t any = 0;                                 // the thread has an allowed token
+    stream_row(r, mask, W, sh.words, 0u, r.pieces, [&](uint32_t, const uint4 &v, uint32_t m) {
+        best = __builtin_fmaxf(best, piece_max(v, m, Elem(0)));
+        any = 1u;
+    });
+    const uint32_t own = best == best ? order_key(__float_as_uint(best)) + 1u : any;
+    if (tid == 0) { sh.n = 0u; sh.n_threads = 0u; }
+    const uint32_t bound = bound_of<kWaves>(own, k, sh.count);
+    // Candidates: the allowed tokens at or above the bound, in the pieces of the threads whose maximum
+    // is.  Those pieces are looked at again, by all threads; they fit their list unless hundreds of
+    // tokens tie at the bound or are NaN.
+    if (any && own >= bound) sh.threads[atomicAdd(&sh.n_threads, 1u)] = tid;
+    __syncthreads();
+    const uint32_t per = (r.pieces + kThreads - 1u) / kThreads, items = sh.n_threads * per;
+    const bool staged = r.pieces * kPer <= kSegWords * 32u;        // the row's mask is in LDS as a whole
+    const float value = bound_value(bound);
+    constexpr uint32_t kItems = sizeof(Elem) == 4u ? 1u : 2u;      // in flight together, within 64 registers
+    for (uint32_t i0 = tid; i0 < items; i0 += kThreads * kItems) {
+        uint4 v[kItems];
+        uint32_t m[kItems], p[kItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kItems; j++) {
+            const uint32_t i = i0 + j * kThreads, of = i / per;
+            m[j] = 0u; p[j] = 0u;
+            v[j] = uint4{0u, 0u, 0u, 0u};
+            if (i < items) p[j] = sh.threads[of] + (i - of * per) * kThreads;
+            if (i < items && p[j] < r.pieces) {
+                const uint32_t bit = p[j] * kPer;
+                m[j] = staged ? (sh.words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : piece_mask(r, mask, W, p[j]);
+                if (m[j]) v[j] = r.load(p[j], m[j]);
+            }
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kItems; j++) {
+            uint32_t take = reaching(v[j], m[j], bound, value, Elem(0));
+            while (take) {
+                const uint32_t i = (uint32_t)__builtin_ctz(take);
+                take &= take - 1u;
+                const uint32_t at = atomicAdd(&sh.n, 1u);
+                if (at < kCand) sh.id[at] = r.token(p[j], i);
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t n = sh.n;
+    if (n <= kCand) make_keys<kThreads>(sh.cand, sh.id, n, r);
+    __syncthreads();                                  // every thread has read the count
+    if (n > kCand) {
+        // Too many tie.  The rank of the k-th best exactly, a byte at a time from the counts of the
+        // tokens that agree in the bytes before; then the tokens above it, and of those at it the
+        // lowest ids.
+        uint32_t rank = 0, above = 0;                 // tokens above the bytes fixed so far
+#pragma nounroll
+        for (uint32_t shift = 32u; shift;) {
+            shift -= 8u;
+            for (uint32_t i = tid; i < 256u; i += kThreads) sh.bins[i] = 0u;
+            __syncthreads();
+            for (uint32_t t = tid; t < V; t += kThreads)
+                if ((mask[t >> 5] >> (t & 31u)) & 1u) {
+                    const uint32_t x = rank_of(r.tokens[t]);
+                    if (shift == 24u || (x >> (shift + 8u)) == (rank >> (shift + 8u))) atomicAdd(&sh.bins[(x >> shift) & 255u], 1u);
+                }
+            __syncthreads();
+            if (tid == 0) {
+                uint32_t d = 255u, c = above;
+                while (d && c + sh.bins[d] < k) c += sh.bins[d--];
+                sh.digit = d; sh.above = c;
+            }
+            __syncthreads();
+            rank |= sh.digit << shift; above = sh.above;
+            __syncthreads();
+        }
+        // the tokens above it leave their keys at the list's front, the ties behind them in order of id
+        if (tid == 0) { sh.n = 0u; sh.digit = above; }
+        __syncthreads();
+        for (uint32_t t0 = 0; t0 < V; t0 += kThreads) {
+            const uint32_t t = t0 + tid;
+            const bool in = t < V && ((mask[t >> 5] >> (t & 31u)) & 1u);
+            const uint32_t x = in ? rank_of(r.tokens[t]) : 0u;
+            if (x > rank) sh.cand[atomicAdd(&sh.n, 1u)] = (unsigned long long)x << 32 | (0xFFFFFFFFu - t);
+            const unsigned long long tie = __ballot(in && x == rank);
+            if ((tid & 63u) == 0u) sh.count[tid >> 6] = (uint32_t)__popcll(tie);
+            __syncthreads();
+            uint32_t at = sh.digit, all = 0;
+#pragma nounroll
+            for (uint32_t w = 0; w < kWaves; w++) { if (w < (tid >> 6)) at += sh.count[w]; all += sh.count[w]; }
+            at += (uint32_t)__popcll(tie & ((1ull << (tid & 63u)) - 1ull));
+            if (in && x == rank && at < k) sh.cand[at] = (unsigned long long)x << 32 | (0xFFFFFFFFu - t);
+            __syncthreads();
+            if (tid == 0) sh.digit += all;
+            __syncthreads();
+        }
+        n = k;                                        // (more than kCand tokens are allowed)
+    }
+    // ranked by counting, the best k leave
+    rank_keys<kThreads>(sh.cand, n, k, [&](uint32_t at, unsigned long long key) {
+        const uint32_t id = 0xFFFFFFFFu - (uint32_t)key;
+        id_out[at] = (int32_t)id;
+        value_out[at] = logit_of(key, r.tokens);
+    });
+    // fewer than k allowed tokens in the row: the rest says so
+    for (uint32_t i = n + tid; i < k; i += kThreads) { id_out[i] = -1; value_out[i] = ninf; }
+}
+
+// Small batches: a slice of kTopkSlice tokens of a row per workgroup of 256 threads, a thread's 32
+// tokens in registers.  The best k of the slice leave for the workspace, best first.
+constexpr uint32_t kSliceThreads = 256;
+constexpr uint32_t kSliceWaves = kSliceThreads / 64u;
+constexpr uint32_t kSlicePer = kTopkSlice / kSliceThreads;       // tokens of a thread
+constexpr uint32_t kSliceCand = kTopkMax * kSlicePer;            // k threads reach the exact bound, with 32 tokens each
+static_assert(kSlicePer == 32u, "a bit per token of a thread");
+
+struct SliceShared {
+    unsigned long long cand[kSliceCand];
+    uint32_t id[kSliceCand];
+    uint32_t count[kSliceWaves];
+    uint32_t n;
+};
+
+template <typename Elem>
+__global__ void __launch_bounds__(kSliceThreads) __attribute__((amdgpu_waves_per_eu(5)))
+topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
+                  const uint32_t *__restrict__ bitmask, uint32_t k, unsigned long long *__restrict__ lists)
+{
+    constexpr uint32_t kPer = Row<Elem>::kPer, kPieces = kSlicePer / kPer;
+    __shared__ SliceShared sh;
+    const uint32_t b = blockIdx.y, tid = threadIdx.x;
+    const uint32_t *mask = bitmask + (size_t)b * W;
+    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    const uint32_t base = blockIdx.x * (kTopkSlice / kPer);       // first piece of the slice
+    unsigned long long *out = lists + ((size_t)b * gridDim.x + blockIdx.x) * k;
+    // (the last slice also takes the piece that a skewed row has behind a whole number of slices)
+    const uint32_t hi = blockIdx.x == gridDim.x - 1u ? r.pieces : base + kTopkSlice / kPer;
+    uint32_t m[kPieces];
+    union { uint4 v; Elem e[kPer]; } u[kPieces];
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; j++) {
+        const uint32_t p = base + j * kSliceThreads + tid;
+        m[j] = p < hi ? piece_mask(r, mask, W, p) : 0u;
+    }
+    const uint32_t extra = base + kTopkSlice / kPer + tid;        // at most one such piece
+    const uint32_t m_extra = extra < hi ? piece_mask(r, mask, W, extra) : 0u;
+    float best = __builtin_nanf("");
+    uint32_t any = m_extra;
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; j++) {
+        u[j].v = uint4{0u, 0u, 0u, 0u};
+        if (m[j]) u[j].v = r.load(base + j * kSliceThreads + tid, m[j]);
+        any |= m[j];
+    }
+    uint4 v_extra = uint4{0u, 0u, 0u, 0u};
+    if (m_extra) v_extra = r.load(extra, m_extra);
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], Elem(0)));
+    if (m_extra) best = __builtin_fmaxf(best, piece_max(v_extra, m_extra, Elem(0)));
+    if (tid == 0) sh.n = 0u;
+    const uint32_t own = best == best ? order_key(__float_as_uint(best)) + 1u : any ? 1u : 0u;
+    const uint32_t bound = bound_of<kSliceWaves>(own, k, sh.count);
+    const float value = bound_value(bound);
+    auto put = [&](uint32_t p, uint32_t take) {
+        while (take) {
+            const uint32_t i = (uint32_t)__builtin_ctz(take);
+            take &= take - 1u;
+            const uint32_t at = atomicAdd(&sh.n, 1u);
+            if (at < kSliceCand) sh.id[at] = r.token(p, i);
+        }
+    };
+    if (own >= bound) {
+#pragma unroll
+        for (uint32_t j = 0; j < kPieces; j++) put(base + j * kSliceThreads + tid, reaching(u[j].v, m[j], bound, value, Elem(0)));
+        put(extra, reaching(v_extra, m_extra, bound, value, Elem(0)));
+    }
+    __syncthreads();
+    uint32_t n = sh.n;
+    if (n > kSliceCand) {
+        // Thousands tie at the bound or are NaN.  k rounds, the best key below the last one each time.
+        unsigned long long last = ~0ull;
+        for (uint32_t q = 0; q < k; q++) {
+            unsigned long long top = 0ull;
+            auto see = [&](uint32_t p, const Elem *e, uint32_t allowed) {
+#pragma unroll
+                for (uint32_t i = 0; i < kPer; i++) {
+                    const unsigned long long key = (allowed >> i) & 1u ? (unsigned long long)rank_of(e[i]) << 32 | (0xFFFFFFFFu - r.token(p, i)) : 0ull;
+                    if (key < last && key > top) top = key;
+                }
+            };
+#pragma unroll
+            for (uint32_t j = 0; j < kPieces; j++) see(base + j * kSliceThreads + tid, u[j].e, m[j]);
+            union { uint4 v; Elem e[kPer]; } ux;
+            ux.v = v_extra;
+            see(extra, ux.e, m_extra);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) { const unsigned long long other = __shfl_xor(top, o); top = other > top ? other : top; }
+            __syncthreads();
+            if ((tid & 63u) == 0u) sh.cand[tid >> 6] = top;
+            __syncthreads();
+            last = sh.cand[0];
+            for (uint32_t w = 1; w < kSliceWaves; w++) last = sh.cand[w] > last ? sh.cand[w] : last;
+            if (tid == 0) out[q] = last;
+        }
+        return;
+    }
+    make_keys<kSliceThreads>(sh.cand, sh.id, n, r);
+    __syncthreads();
+    rank_keys<kSliceThreads>(sh.cand, n, k, [&](uint32_t at, unsigned long long x) { out[at] = x; });
+    for (uint32_t i = n + tid; i < k; i += kSliceThreads) out[i] = 0ull;
+}
+
+// A row's slices merged: the same bound and count on the keys that they left.
+template <typename Elem>
+__global__ void __launch_bounds__(kSliceThreads)
+topk_merge_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t n_slices, uint32_t k,
+                  const unsigned long long *__restrict__ lists, int32_t *__restrict__ ids, Elem *__restrict__ values, Elem ninf)
+{
+    constexpr uint32_t kHeld = kTopkMergeKeys / kSliceThreads;    // most keys of a thread
+    __shared__ unsigned long long cand[kTopkMergeKeys];
+    __shared__ uint32_t count[kSliceWaves], n_cand;
+    const uint32_t b = blockIdx.x, tid = threadIdx.x, n = n_slices * k;
+    unsigned long long x[kHeld];
+    uint32_t own = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kHeld; j++) {
+        const uint32_t i = tid + j * kSliceThreads;
+        x[j] = 0ull;
+        if (j * kSliceThreads >= n) continue;
+        if (i < n) x[j] = lists[(size_t)b * n + i];
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kHeld; j++) { const uint32_t h = (uint32_t)(x[j] >> 32); own = h > own ? h : own; }
+    if (tid == 0) n_cand = 0u;
+    const uint32_t bound = bound_of<kSliceWaves>(own, k, count);
+#pragma unroll
+    for (uint32_t j = 0; j < kHeld; j++) {
+        if (j * kSliceThreads >= n) break;
+        if (x[j] && (uint32_t)(x[j] >> 32) >= bound) cand[atomicAdd(&n_cand, 1u)] = x[j];
+    }
+    __syncthreads();
+    const uint32_t c = n_cand;
+    rank_keys<kSliceThreads>(cand, c, k, [&](uint32_t at, unsigned long long key) {
+        const uint32_t id = 0xFFFFFFFFu - (uint32_t)key;
+        ids[(size_t)b * k + at] = (int32_t)id;
+        values[(size_t)b * k + at] = logit_of(key, logits + (int64_t)b * row_stride);
+    });
+    for (uint32_t i = c + tid; i < k; i += kSliceThreads) { ids[(size_t)b * k + i] = -1; values[(size_t)b * k + i] = ninf; }
+}
+
+// The lists of wg_masked_topk_static: what wg_masked_topk takes from its caller, one copy per GPU for
+// the life of the process.  topk_slice writes every key that topk_merge reads.
+static __device__ __align__(256) unsigned long long scratch[kTopkStaticKeys];
+
+hipError_t static_topk_scratch(unsigned long long **out)
+{
+    constexpr int kDevices = 64;
+    static std::mutex mu;
+    static unsigned long long *ptr[kDevices];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!ptr[dev]) {
+        void *p = nullptr;
+        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        if (e != hipSuccess) return e;
+        if (!p) return hipErrorInvalidSymbol;
+        ptr[dev] = static_cast<unsigned long long *>(p);
+    }
+    *out = ptr[dev];
+    return hipSuccess;
+}
+
+// Workgroups of the greedy choice per row: as many as the compute units hold one of each, at least
+// 16,384 tokens in each.
+static uint32_t argmax_parts(uint32_t B, uint32_t V)
+{
+    uint32_t parts = 1u;
+    while (parts < 16u && parts * 2u * B <= kCutRows && parts * 2u * 16384u <= V) parts *= 2u;
+    return parts;
+}
+
+// The k best are taken by a workgroup per row where a row streams in about the time of the second
+// kernel, or where there are rows enough to keep the chip busy (V = 128,256 fp32, 513 KB: slices 18.1
+// against 22.3 us at B = 64, 28.5 against 26.1 at B = 128; up to 304 KB the row is never slower).
+static bool topk_by_row(uint32_t B, uint64_t row_bytes) { return row_bytes <= (320u << 10) || B >= 96u; }
+
+hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
+                                const uint32_t *bitmask, int32_t *tokens, hipStream_t s)
+{
+    const uint32_t W = (V + 31u) / 32u;
+    const dim3 g(argmax_parts(B, V), B);
+    if (dtype == WG_F32) masked_argmax_kernel<uint32_t><<<g, kThreads, 0, s>>>(static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask, tokens);
+    else masked_argmax_kernel<uint16_t><<<g, kThreads, 0, s>>>(static_cast<const uint16_t *>(logits), row_stride, V, W, bitmask, tokens);
+    return hipGetLastError();
+}
+
+template <typename Elem>
+static void topk(const Elem *logits, uint32_t B, uint32_t V, int64_t row_stride, const uint32_t *bitmask, uint32_t k,
+                 int32_t *ids, Elem *values, Elem ninf, unsigned long long *lists, hipStream_t s)
+{
+    const uint32_t W = (V + 31u) / 32u;
+    if (topk_by_row(B, (uint64_t)V * sizeof(Elem))) {
+        masked_topk_kernel<Elem><<<B, kThreads, 0, s>>>(logits, row_stride, V, W, bitmask, k, ids, values, ninf);
+        return;
+    }
+    const uint32_t n_slices = (V + kTopkSlice - 1u) / kTopkSlice;
+    topk_slice_kernel<Elem><<<dim3(n_slices, B), kSliceThreads, 0, s>>>(logits, row_stride, V, W, bitmask, k, lists);
+    topk_merge_kernel<Elem><<<B, kSliceThreads, 0, s>>>(logits, row_stride, n_slices, k, lists, ids, values, ninf);
+}
+
+hipError_t launch_masked_topk(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
+                              const uint32_t *bitmask, uint32_t k, int32_t *ids, void *values, unsigned long long *lists, hipStream_t s)
+{
+    if (dtype == WG_F32)
+        topk<uint32_t>(static_cast<const uint32_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint32_t *>(values), 0xFF800000u, lists, s);
+    else
+        topk<uint16_t>(static_cast<const uint16_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint16_t *>(values), (uint16_t)0xFF80u, lists, s);
+    return hipGetLastError();
+}
+
+}  // namespace wg

@@ -154,3 +154,46 @@ def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
         assert (H.host_mask(mask)[::90] == o.fill_masks(H.host_states(st)[::90])).all()
         wg.select_tokens(mask, w.vocab.V, draws[k], tok)
     assert h.error_count() == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,V,off", [(1, 33, 0), (3, 8193, 1), (130, 5000, 3), (2, 90001, 0), (97, 90001, 5), (40, 151936, 0), (3, 300007, 1)])
+def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
+    """masked_argmax and masked_topk where rows are cut and where they are not, at any alignment, with
+    ties (as many as tie-breaking by token id decides), NaNs, both zeros, -inf and rows that allow
+    little or nothing; each call twice, so that nothing is left behind in the merge arrays."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    rng = np.random.default_rng(V + B)
+    x = rng.standard_normal((B, V)).astype(np.float32)
+    x[:, rng.integers(0, V, V // 20)] = np.nan
+    x[0] = np.round(x[0])                                           # thousands tie, zeros of both signs
+    if B > 2:
+        x[1], x[2] = -np.inf, np.nan
+        x[2, V // 2] = -0.0
+    host = x if dtype == "f32" else ws.to_bf16_bits(x)
+    bits = rng.integers(0, 1 << 32, (B, (V + 31) // 32), dtype=np.uint32)
+    if B > 3:
+        bits[3], bits[4 % B] = 0, 0
+        bits[4 % B, -1] = 1
+    if V % 32:
+        bits[:, -1] &= np.uint32((1 << (V % 32)) - 1)
+    d = H.dev_logits(host)
+    buf = torch.zeros((B * (V + off) + 64,), dtype=d.dtype, device="cuda")
+    view = buf[off:off + B * (V + off)].view(B, V + off)[:, :V]
+    view.copy_(d)
+    mask = torch.from_numpy(bits.view(np.int32)).cuda()
+    tok = torch.empty(B, dtype=torch.int32, device="cuda")
+    want = O.masked_argmax(host, bits)
+    for _ in range(2):
+        tok.fill_(-7)
+        wg.masked_argmax(view, mask, tok)
+        assert (tok.cpu().numpy() == want).all()
+    for k in (1, 7, 64):
+        ids = torch.empty((B, k), dtype=torch.int32, device="cuda")
+        vals = torch.empty((B, k), dtype=d.dtype, device="cuda")
+        work = torch.empty(wg.masked_topk_workspace(B, V, k), dtype=torch.uint8, device="cuda")
+        wg.masked_topk(view, mask, ids, vals, work)
+        want_ids, want_vals = O.masked_topk(host, bits, k)
+        assert (ids.cpu().numpy() == want_ids).all(), k
+        assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
