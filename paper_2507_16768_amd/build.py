@@ -9,7 +9,9 @@ SOURCES = ["wg_api.cpp", "wg_lower.cpp", "wg_regex.cpp", "wg_vocab_index.cpp", "
 HEADERS = ["wg_internal.h", "wg_device.h", "wg_order.h", os.path.join("..", "..", "include", "wg.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          # packed-fp32 instruction selection is switched off for every kernel in this library
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # found by its name next to the Python module, wherever the tree lies
+         "-Wl,-soname,libwgrammar.so"]
 
 
 NATIVE = os.path.join(HERE, "_native.so")      # the Python module behind binding.py, on top of LIB
@@ -37,7 +39,7 @@ def build_native(verbose=False):
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-isystem", os.path.join(torch, "include"), "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"),
            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
-           "-o", tmp, os.path.join(CSRC, NATIVE_SOURCE), LIB, "-L" + os.path.join(torch, "lib"),
+           "-o", tmp, os.path.join(CSRC, NATIVE_SOURCE), "-L" + HERE, "-l:libwgrammar.so", "-L" + os.path.join(torch, "lib"),
            "-lc10", "-lc10_hip", "-ltorch", "-ltorch_cpu", "-ltorch_python",
            "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(torch, "lib")]
     if verbose:

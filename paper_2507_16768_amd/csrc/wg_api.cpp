@@ -368,7 +368,7 @@ void wg_destroy(wg_handle_t h) {
     if (!h) return;
     (void)hipDeviceSynchronize();
     (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
-    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.walked); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
+    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
@@ -420,9 +420,9 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
 
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ctr), sizeof(Counters)));
     WG_HIP(hipMemset(h->dc.ctr, 0, sizeof(Counters)));
-    const size_t walked_bytes = (size_t)kWalkedSlots * kWalkedStride * sizeof(unsigned long long);
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.walked), walked_bytes));
-    WG_HIP(hipMemset(h->dc.walked, 0, walked_bytes));
+    const size_t spread_bytes = (size_t)kSpread * kSpreadStride * sizeof(unsigned long long);
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.spread), spread_bytes));
+    WG_HIP(hipMemset(h->dc.spread, 0, spread_bytes));
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
     if (rc == WG_OK) rc = reserve_batch(h.get(), kDefaultBatch);
@@ -646,13 +646,16 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     Counters c;
     WG_HIP(hipDeviceSynchronize());
     WG_HIP(hipMemcpy(&c, h->dc.ctr, sizeof c, hipMemcpyDeviceToHost));
-    host_out->lookups = c.lookups; host_out->hits = c.hits; host_out->builds = c.builds;
+    host_out->lookups = c.lookups; host_out->builds = c.builds;
     host_out->uncached_builds = c.uncached_builds;
     host_out->class_scans = c.class_scans;
-    unsigned long long walked[kWalkedSlots * kWalkedStride];
-    WG_HIP(hipMemcpy(walked, h->dc.walked, sizeof walked, hipMemcpyDeviceToHost));
-    host_out->entries_walked = 0;
-    for (uint32_t i = 0; i < kWalkedSlots; i++) host_out->entries_walked += walked[i * kWalkedStride];
+    unsigned long long spread[kSpread * kSpreadStride];
+    WG_HIP(hipMemcpy(spread, h->dc.spread, sizeof spread, hipMemcpyDeviceToHost));
+    host_out->entries_walked = host_out->hits = 0;
+    for (uint32_t i = 0; i < kSpread; i++) {
+        host_out->entries_walked += spread[i * kSpreadStride + kSpreadWalked];
+        host_out->hits += spread[i * kSpreadStride + kSpreadHits];
+    }
     host_out->keys = h->dc.n_keys;
     host_out->cache_rows = h->dc.cap_rows;
     const uint64_t taken = (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;

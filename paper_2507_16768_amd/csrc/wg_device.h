@@ -75,7 +75,7 @@ struct Counters {
     uint32_t n_class_claims;     // class tables claimed in the call in flight
     unsigned long long slot_ctr; // generation << 32 | arena rows in use in that generation (<= cap_rows)
     unsigned long long launch;   // number of the fill call in flight (its last kernel counts it up)
-    unsigned long long lookups, hits, builds, uncached_builds, class_scans, errors;
+    unsigned long long lookups, builds, uncached_builds, class_scans, errors;
 };
 
 // The tag of a key or of a class table: the cache generation (30 bits) in which, and the fill call
@@ -91,11 +91,12 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 constexpr uint32_t kRefBuild = 0xFFFFFFFEu;
 constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
-constexpr uint32_t kWalkedSlots = 64, kWalkedStride = 16;   // the counter of examined candidates is spread over 64 lines
+// Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
+constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1;
 
 struct DeviceCache {
     Counters *ctr;
-    unsigned long long *walked;  // kWalkedSlots counters, kWalkedStride apart
+    unsigned long long *spread;  // kSpread groups of counters, kSpreadStride apart
     // per state key
     unsigned long long *tags;
     uint32_t *slots;             // arena row of a claimed key, or kNoSlot: the arena was full (and stays so)

@@ -230,8 +230,10 @@ __device__ __forceinline__ void lookup_one(const DeviceTable &T, const DeviceCac
     const unsigned long long cm = __ballot(claimed), km = __ballot(class_claimed);
     if (cm) {
         uint32_t first = 0;
-        if (lane == 0) first = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
-        if (lane == 1 && km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
+        if (lane == 0) {
+            first = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
+            if (km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
+        }
         first = __shfl(first, 0);
         if (claimed) {
             const uint32_t idx = first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
@@ -243,11 +245,9 @@ __device__ __forceinline__ void lookup_one(const DeviceTable &T, const DeviceCac
         Cc.row_ref[b] = ref;
         if (build) Cc.tasks[b] = me;
     }
-    const unsigned long long hv = __ballot(hit), lv = __ballot(live);
-    if (lane == 0) {
-        atomicAdd(&Cc.ctr->lookups, (unsigned long long)__popcll(lv));
-        if (hv) atomicAdd(&Cc.ctr->hits, (unsigned long long)__popcll(hv));
-    }
+    // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread)
+    const unsigned long long hv = __ballot(hit);
+    if (lane == 0 && hv) atomicAdd(&Cc.spread[(blockIdx.x % kSpread) * kSpreadStride + kSpreadHits], (unsigned long long)__popcll(hv));
 }
 
 __global__ void __launch_bounds__(64)
@@ -555,7 +555,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         }
         if (lane == 0) {
             sh.n_ranges = n; sh.total = total;
-            if (p0 == 0u && sure + total) atomicAdd(&Cc.walked[(b % kWalkedSlots) * kWalkedStride], (unsigned long long)(sure + total));
+            if (p0 == 0u && sure + total) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)(sure + total));
             if (Vc.eos_id >= 0 && me.eos_next != WG_SID_ERROR) {
                 const uint32_t ew = (uint32_t)Vc.eos_id >> 5;
                 if (ew >= w_lo && ew < w_hi) early[ew - w_lo] |= 1u << ((uint32_t)Vc.eos_id & 31u);
@@ -709,8 +709,9 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
 
 // The call is over for the cache once its lookups are: one thread of the kernel after them counts
 // the claimed rows as used and opens the next call.
-__device__ __forceinline__ void close_fill(const DeviceCache &Cc)
+__device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B)
 {
+    Cc.ctr->lookups += B;
     const unsigned long long sc = Cc.ctr->slot_ctr;
     const uint32_t used = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;
     const uint32_t room = Cc.cap_rows - used, n = Cc.ctr->n_claims;
@@ -769,7 +770,7 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
         }
     }
     if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
-    if (blockIdx.x == gridDim.x - 1u && b == 0 && tid == 0) close_fill(Cc);
+    if (blockIdx.x == gridDim.x - 1u && b == 0 && tid == 0) close_fill(Cc, gridDim.y);
 }
 
 // apply: a workgroup takes kApplyTokens tokens of a row.
