@@ -51,6 +51,8 @@ struct wg_handle_s {
     uint32_t cap_states = 0, cap_classes = 0, cap_keys = 0;
     uint32_t up_states = 0, up_classes = 0;           // how much of the host table is on the device
     uint32_t max_batch = 0;
+    uint32_t n_cu = 256;
+    uint32_t *d_free_rows = nullptr;
     // kernel timing: events recorded since the last wg_profile_read
     bool profiling = false;
     std::vector<hipEvent_t> fill_events;       // 4 per wg_fill_masks call: begin / end of each kernel
@@ -98,9 +100,12 @@ int reserve_batch(wg_handle_s *h, uint32_t B) {
     WG_HIP(hipDeviceSynchronize());
     (void)hipFree(h->dc.row_ref);
     (void)hipFree(h->dc.tasks);
-    h->dc.row_ref = nullptr; h->dc.tasks = nullptr; h->max_batch = 0;
+    (void)hipFree(h->dc.tickets);
+    h->dc.row_ref = nullptr; h->dc.tasks = nullptr; h->dc.tickets = nullptr; h->max_batch = 0;
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.row_ref), B * sizeof(uint32_t)));
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tasks), B * sizeof(RowTask)));
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tickets), B * sizeof(uint32_t)));
+    WG_HIP(hipMemset(h->dc.tickets, 0, B * sizeof(uint32_t)));
     h->max_batch = B;
     return WG_OK;
 }
@@ -181,6 +186,14 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         h->up_classes = n_classes;
     }
     h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, n_states, t.lmax};
+    if (h->dc.direct && t.n_keys > h->dc.cap_rows) {
+        // more keys than rows from now on: the rows in use stay where they are, the others are handed out
+        // in order of first use
+        if (!h->d_free_rows) WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->d_free_rows), (size_t)h->dc.cap_rows * sizeof(uint32_t)));
+        WG_HIP(launch_free_rows(h->dc, h->dc.n_keys, h->d_free_rows, s));
+        h->dc.direct = 0;
+        h->dc.free_rows = h->d_free_rows;
+    }
     h->dc.n_keys = t.n_keys;
     return WG_OK;
 }
@@ -192,11 +205,16 @@ int set_cache_rows(wg_handle_s *h, uint32_t rows) {
     (void)hipFree(h->dc.arena);
     h->dc.arena = arena;
     h->dc.cap_rows = rows;
+    (void)hipFree(h->d_free_rows);                     // (it has a place for every row)
+    h->d_free_rows = nullptr;
+    h->dc.free_rows = nullptr;
     return WG_OK;
 }
 
 // A new cache generation: every row and class index made so far is stale from the next call on.
 int next_generation(wg_handle_s *h, hipStream_t s) {
+    h->dc.direct = h->dc.n_keys <= h->dc.cap_rows;
+    h->dc.free_rows = nullptr;
     if (++h->dc.epoch >= (1u << 30)) {                 // out of generation numbers: reset the tags for real
         WG_HIP(hipMemsetAsync(h->dc.tags, 0, (size_t)h->cap_keys * sizeof(unsigned long long), s));
         WG_HIP(hipMemsetAsync(h->dc.class_tags, 0, (size_t)h->cap_classes * sizeof(unsigned long long), s));
@@ -370,6 +388,7 @@ void wg_destroy(wg_handle_t h) {
     (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
     (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
+    (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_groups); (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
@@ -423,8 +442,15 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     const size_t spread_bytes = (size_t)kSpread * kSpreadStride * sizeof(unsigned long long);
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.spread), spread_bytes));
     WG_HIP(hipMemset(h->dc.spread, 0, spread_bytes));
+    const size_t group_bytes = (size_t)(kTicketGroups + 1) * kSpreadStride * sizeof(unsigned long long);
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ticket_groups), group_bytes));
+    WG_HIP(hipMemset(h->dc.ticket_groups, 0, group_bytes));
+    int cus = 0;
+    WG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, vocab->device));
+    if (cus > 0) h->n_cu = (uint32_t)cus;
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
+    h->dc.direct = t.n_keys <= h->dc.cap_rows;
     if (rc == WG_OK) rc = reserve_batch(h.get(), kDefaultBatch);
     if (rc != WG_OK) return rc;
     WG_HIP(hipDeviceSynchronize());
@@ -497,7 +523,7 @@ int fill(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t 
     hipEvent_t ev[4];
     if (h->profiling) for (auto &e : ev) { e = take_event(h); h->fill_events.push_back(e); }
     WG_HIP(launch_fill(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, d_bitmask, d_logits, dtype,
-                       logits_stride, static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
+                       logits_stride, h->n_cu, static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
     return WG_OK;
 }
 }  // namespace

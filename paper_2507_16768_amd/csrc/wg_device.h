@@ -78,13 +78,15 @@ struct Counters {
     unsigned long long lookups, builds, uncached_builds, class_scans, errors;
 };
 
-// The tag of a key or of a class table: the cache generation (30 bits) in which, and the fill call
-// (its number's low 34 bits) by which it was claimed; 0 means never.  A key's row, or a table's two
-// rows, are in place once that call is over: for every later call of the generation the tag says
-// "made", for the claiming call itself "being made" -- a request of the same call that needs the
-// same key makes its own copy of the row and waits for nobody.
-constexpr uint32_t kTagLaunchBits = 34;
-constexpr unsigned long long kTagLaunchMask = (1ull << kTagLaunchBits) - 1ull;
+// The tag of a key or of a class table: the cache generation (30 bits) in which, the fill call (its
+// number's low 18 bits) by which and the request for which it was claimed; 0 means never.  A key's
+// row, or a table's two rows, are in place once that call is over: for every later call of the
+// generation the tag says "made", for the claiming call itself "being made" -- a request of the same
+// call that needs the same key makes its own copy of the row and waits for nobody.  (A call whose
+// number agrees with an old claim's in all 18 bits takes that row for one being made and makes a
+// copy too: the same row, one hit fewer.)
+constexpr uint32_t kTagRequestBits = 16, kTagEpochShift = 34;
+constexpr unsigned long long kTagLaunchMask = (1ull << (kTagEpochShift - kTagRequestBits)) - 1ull;
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 // What the lookup leaves per request: the arena row of a mask made before the call, kRefBuild (its
 // task says how to make it), or kNoKey (no such state: a row of zeros).  Rows stay below 2^30.
@@ -93,21 +95,26 @@ constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
 constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1;
+constexpr uint32_t kTicketGroups = 16;
 
 struct DeviceCache {
     Counters *ctr;
     unsigned long long *spread;  // kSpread groups of counters, kSpreadStride apart
     // per state key
     unsigned long long *tags;
-    uint32_t *slots;             // arena row of a claimed key, or kNoSlot: the arena was full (and stays so)
-    uint32_t *arena;             // cap_rows rows of row_stride words, handed out in order of first use
+    uint32_t *slots;             // not direct: arena row of a claimed key, or kNoSlot: the arena was full (and stays so)
+    uint32_t *arena;             // cap_rows rows of row_stride words
     uint32_t cap_rows;
+    uint32_t direct;             // the arena has a row for every key: key k keeps row k; else rows are handed out in order of first use,
+    const uint32_t *free_rows;   // in this order (null: by number)
     // per class table (the context-free part of every mask of a state using that table)
     unsigned long long *class_tags;
     uint32_t *class_rows;        // 2 rows per class: [stay] all bytes stay, [end] exits on its last byte
     // per call
     uint32_t *row_ref;           // [B] arena row, kRefBuild or kNoKey
     RowTask *tasks;              // [B]
+    uint32_t *tickets;           // [B] workgroups of a row that have done their lookup, what they claimed above
+    unsigned long long *ticket_groups;   // kTicketGroups + 1 counters, kSpreadStride apart
     uint32_t row_stride;         // words, multiple of 4
     uint32_t n_keys;
     uint32_t epoch;              // cache generation of this call
@@ -119,7 +126,8 @@ struct DeviceCache {
 hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
                        void *logits, int dtype, int64_t logits_stride,
-                       hipStream_t s, hipEvent_t *ev);
+                       uint32_t n_cu, hipStream_t s, hipEvent_t *ev);
+hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s);
 // Dynamic LDS of the rows kernel for this vocabulary; with its static part it stays within the 64 KB
 // a kernel gets without asking.
 uint32_t rows_lds_bytes(const DeviceVocab &Vc);

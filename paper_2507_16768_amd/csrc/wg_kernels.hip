@@ -1,10 +1,12 @@
 // HIP kernels of the structured-decoding hot path for gfx950 (wave64).
 //
-//   lookup       : request state -> cache key; claims a missing key and leaves the task of making
-//                  its row (advance_lookup: after advancing the state by the sampled token)
 //   rows         : the mask row of every request, a workgroup per (request, token range): copied from
 //                  the cache, or made in LDS from the vocabulary's static indexes; to the caller's
-//                  bitmask, to the cache, and (wg_decode_step) as -inf into the logits
+//                  bitmask, to the cache, and (wg_decode_step) as -inf into the logits.  In front of
+//                  it, where the batch is small enough in the same kernel, the state is advanced by the
+//                  sampled token (wg_advance_fill_masks, wg_decode_step) and looked up
+//   lookup       : the same by itself: request state -> cache key; claims a missing key and leaves the
+//                  task of making its row
 //   apply        : logits <- -inf where the mask bit is 0
 //   advance      : per-request walk of the sampled token
 //   forced_bytes : per request, the rest of the Write run its state lies in
@@ -75,19 +77,25 @@ __device__ __forceinline__ uint32_t first_leaving(uint32_t code, uint32_t n)
 // Walks bytes [i, L) of a token from (sid, aux), up to eight bytes per state visit: a run of
 // literal states is one masked 8-byte compare against the state table's literal bytes, a stay-run
 // inside a checkpoint is eight independent class look-ups.  Every state entered on the way starts
-// with aux = 0; only a bounded Wait counts.  False on the first rejected byte.
-__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, TokenBytes &t, uint32_t i, uint32_t L)
+// with aux = 0; only a bounded Wait counts.  False on the first rejected byte.  kAhead: d holds the
+// descriptor of sid, at the call and after it, and the literal bytes are requested with it, for a
+// caller that goes on from the state it ends in (a step of the lookup kernel's walk is one trip to
+// memory instead of two: 6.2 -> 5.6 us at B = 256); elsewhere the extra loads only cost.
+template <bool kAhead>
+__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, StateDesc &d, TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
     while (i < L) {
         if (sid >= T.n_states) return false;                     // ERROR or corrupt state
-        const StateDesc d = T.states[sid];
+        uint64_t l0 = 0, l1 = 0;
+        if (kAhead) { l0 = lit64[sid >> 3]; l1 = lit64[(sid >> 3) + 1u]; }
+        else d = T.states[sid];
         const uint32_t kind = d.kind_byte & 0xFFu;
         const uint32_t n = L - i < 8u ? L - i : 8u;
         const uint64_t tb = window(t, i);
         if (kind == WG_KIND_LIT) {
+            if (!kAhead) { l0 = lit64[sid >> 3]; l1 = lit64[(sid >> 3) + 1u]; }
             const uint32_t sh = (sid & 7u) * 8u;
-            const uint64_t l0 = lit64[sid >> 3], l1 = lit64[(sid >> 3) + 1u];
             const uint64_t lv = sh ? (l0 >> sh) | (l1 << (64u - sh)) : l0;
             const uint32_t m = n < d.run ? n : d.run;            // literal bytes compared now
             const uint64_t mask = m == 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
@@ -102,44 +110,57 @@ __device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32
                 aux += stays;
             }
             i += stays;
-            if (stays < n) {
-                const uint32_t c = (code >> (2u * stays)) & 3u;
-                if (c == CLS_REJECT) return false;
-                sid = c == CLS_EXIT_A ? d.next_a : d.next_b;
-                aux = 0; i += 1u;
-            }
+            if (stays == n) continue;
+            const uint32_t c = (code >> (2u * stays)) & 3u;
+            if (c == CLS_REJECT) return false;
+            sid = c == CLS_EXIT_A ? d.next_a : d.next_b;
+            aux = 0; i += 1u;
         } else return false;                                     // FINAL / END accept no byte
+        if (kAhead && sid < T.n_states) d = T.states[sid];
     }
     return true;
+}
+__device__ __forceinline__ bool walk_from(const DeviceTable &T, uint32_t sid, TokenBytes &t, uint32_t i, uint32_t L)
+{
+    uint32_t aux = 0;
+    StateDesc d;
+    return walk<false>(T, sid, aux, d, t, i, L);
 }
 
 // ---------------------------------------------------------------------------------------------
 // advance: one thread per request (EOS is the one-symbol string [EOS]; any other byte-less token
 // is rejected).
+// d: the descriptor of sid (when there is such a state) at the call and, with kAhead, after it.
+template <bool kAhead>
 __device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                                            uint32_t &sid, uint32_t &aux, int64_t t)
+                                            uint32_t &sid, uint32_t &aux, StateDesc &d, int64_t t, bool count_error)
 {
     bool ok = t >= 0 && t < (int64_t)Vc.V && sid < T.n_states;
     if (ok) {
+        // (both chunks are requested with the length, not after it)
+        const uint32_t L = Vc.len8[t];
+        TokenBytes tk;
+        tk.chunks = Vc.chunks + t; tk.stride = Vc.V; tk.q = 0; tk.n = Vc.n_chunks;
+        tk.w0 = tk.chunks[0];
+        tk.w1 = tk.n > 1u ? tk.chunks[tk.stride] : 0ull;
         if ((int64_t)Vc.eos_id == t) {
-            sid = T.states[sid].eos_next; aux = 0;
+            sid = d.eos_next; aux = 0;
             ok = sid != WG_SID_ERROR;
-        } else {
-            // (both chunks are requested with the length, not after it)
-            const uint32_t L = Vc.len8[t];
-            TokenBytes tk;
-            tk.chunks = Vc.chunks + t; tk.stride = Vc.V; tk.q = 0; tk.n = Vc.n_chunks;
-            tk.w0 = tk.chunks[0];
-            tk.w1 = tk.n > 1u ? tk.chunks[tk.stride] : 0ull;
-            ok = L != 0u && walk(T, sid, aux, tk, 0u, L);
-        }
+            if (kAhead && sid < T.n_states) d = T.states[sid];
+        } else ok = L != 0u && walk<kAhead>(T, sid, aux, d, tk, 0u, L);
     }
     if (!ok) {
         sid = WG_SID_ERROR; aux = 0;
-        atomicAdd(&Cc.ctr->errors, 1ull);
+        if (count_error) atomicAdd(&Cc.ctr->errors, 1ull);
     }
 }
 
+__device__ __forceinline__ StateDesc descriptor(const DeviceTable &T, uint32_t sid) { return T.states[sid < T.n_states ? sid : 0u]; }
+
+// One thread per request, 4 requests to a wavefront: the paths of the requests of a wavefront are
+// walked one after the other, each step a trip to memory (the lookup with an advance before it, B = 256:
+// 7.5 us with 64, 6.2 with 4; the advance alone 5.2 and 4.8).
+constexpr uint32_t kLookupThreads = 4;
 __global__ void __launch_bounds__(64)
 advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
                const int32_t *__restrict__ tokens, uint32_t B)
@@ -147,87 +168,110 @@ advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__rest
     uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
     uint32_t sid = states[b].sid, aux = states[b].aux;
-    advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
+    const int32_t t = tokens[b];
+    StateDesc d = descriptor(T, sid);
+    advance_one<false>(T, Vc, Cc, sid, aux, d, (int64_t)t, true);
     states[b].sid = sid; states[b].aux = aux;
 }
 
 // ---------------------------------------------------------------------------------------------
 // lookup: state -> cache key.  A missing key is claimed by exactly one request (CAS on the key's
-// tag) and gets a row of the arena (or none, when the arena is full: its row is then made again by
-// every call that needs it).  The i-th claim of a call takes the i-th free row, so the order of the
-// claims is their row allocation; the count of rows in use is brought up to date once per call, by
-// the last kernel of the fill.  Any other request of the call with that key makes the row for
-// itself: no request waits for another, so masks are made by one kernel.
-
-// What a lookup reads from the handle's counters before anything depends on it.
-struct LookupEnv {
-    unsigned long long launch;   // number of this fill call
-    uint32_t rows0;              // arena rows in use before this call
+// tag), which keeps the row it makes: in the arena row of the key's own number (Cc.direct: the arena
+// has a row for every key), or else the i-th claim of a call takes the i-th free row, and a claim
+// that finds none left keeps nothing: its row is made again by every call that needs it.  The count
+// of rows in use is brought up to date once per call, when all its lookups are done.  Any other
+// request of the call with that key makes the row for itself: no request waits for another.
+struct Found {
+    uint32_t key, ref;           // ref: as left in row_ref
+    bool hit, claimed, class_claimed, keep;   // keep: this request claimed the key (here or in another workgroup of its row)
+    RowTask me;                  // when ref is kRefBuild
 };
 
-__device__ __forceinline__ LookupEnv lookup_env(const DeviceCache &Cc)
+// What a call writes into the tags it claims, but for the request; `launch` is ctr->launch.
+__device__ __forceinline__ unsigned long long tag_now(const DeviceCache &Cc, unsigned long long launch)
 {
-    const unsigned long long sc = Cc.ctr->slot_ctr;
-    return LookupEnv{Cc.ctr->launch & kTagLaunchMask, (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u};
+    return (unsigned long long)Cc.epoch << kTagEpochShift | (launch & kTagLaunchMask) << kTagRequestBits;
 }
 
-// The lookup of request b in state (sid, aux); every lane of the wavefront calls it, `live`
-// says whether the lane has a request.
-__device__ __forceinline__ void lookup_one(const DeviceTable &T, const DeviceCache &Cc,
-                                           const LookupEnv &env, uint32_t b, bool live, uint32_t sid, uint32_t aux)
+// The lookup of request b in state (sid, aux), d its descriptor.
+__device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache &Cc, unsigned long long now, uint32_t b,
+                                         uint32_t sid, uint32_t aux, const StateDesc &d)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    const unsigned long long now = (unsigned long long)Cc.epoch << kTagLaunchBits | env.launch;
-    bool hit = false, build = false, claimed = false, class_claimed = false;
-    uint32_t key = 0, ref = kNoKey;
-    RowTask me{};
-    if (live && sid < T.n_states) {
-        const StateDesc d = T.states[sid];
-        const uint32_t kind = d.kind_byte & 0xFFu;
-        uint32_t variant = 0;
-        if (kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
-            const uint32_t left = d.max > aux ? d.max - aux : 0u;
-            variant = T.lmax - (left < T.lmax ? left : T.lmax);
+    Found f{};
+    f.ref = kNoKey;
+    if (sid >= T.n_states) return f;
+    const unsigned long long mine = now | b;
+    const uint32_t kind = d.kind_byte & 0xFFu;
+    uint32_t variant = 0;
+    if (kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
+        const uint32_t left = d.max > aux ? d.max - aux : 0u;
+        variant = T.lmax - (left < T.lmax ? left : T.lmax);
+    }
+    f.key = d.key_base + variant;
+    const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
+    const unsigned long long t = __hip_atomic_load(&Cc.tags[f.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t slot = Cc.direct ? f.key : Cc.slots[f.key];
+    // Requested right behind the key's tag, although only a missing key needs them: the two
+    // successors' descriptors and the tag of the class table.  Plain loads from clamped indexes, so
+    // that nothing waits for them before the tag has decided.
+    const StateDesc da = descriptor(T, d.next_a), db = descriptor(T, d.next_b);
+    const uint32_t cls = ckpt ? d.cls : 0u;
+    const unsigned long long ct = __hip_atomic_load(&Cc.class_tags[cls], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (a slot is only read where the tag is of this generation and an earlier call: it does not
+    // change after that call, so the two loads need no order)
+    const bool made = (uint32_t)(t >> kTagEpochShift) == Cc.epoch;
+    const bool this_call = (t >> kTagRequestBits) == (now >> kTagRequestBits);
+    f.hit = made && !this_call && slot != kNoSlot;
+    f.ref = f.hit ? slot : kRefBuild;
+    if (f.hit) return f;
+    unsigned long long is = t;
+    if (!this_call) {
+        is = atomicCAS(&Cc.tags[f.key], t, mine);
+        f.claimed = is == t;
+    }
+    f.keep = f.claimed || is == mine;
+    const bool class_this_call = (ct >> kTagRequestBits) == (now >> kTagRequestBits);
+    uint32_t class_state = (uint32_t)(ct >> kTagEpochShift) == Cc.epoch && !class_this_call ? CLASS_READY : CLASS_SELF;
+    if (f.keep && ckpt && class_state != CLASS_READY) {
+        unsigned long long cis = ct;
+        if (!class_this_call) {
+            cis = atomicCAS(&Cc.class_tags[cls], ct, mine);
+            f.class_claimed = cis == ct;
         }
-        key = d.key_base + variant;
-        const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
-        const unsigned long long t = __hip_atomic_load(&Cc.tags[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t slot = Cc.slots[key];
-        // Requested right behind the key's tag, although only a missing key needs them: the two
-        // successors' descriptors and the tag of the class table.  Plain loads from clamped
-        // indexes, so that nothing waits for them before the tag has decided.
-        StateDesc dn[2];
-        dn[0] = T.states[d.next_a < T.n_states ? d.next_a : 0u];
-        dn[1] = T.states[d.next_b < T.n_states ? d.next_b : 0u];
-        const uint32_t cls = ckpt ? d.cls : 0u;
-        const unsigned long long ct = __hip_atomic_load(&Cc.class_tags[cls], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // (a slot is only read where the tag is of this generation and an earlier call: it does not
-        // change after that call, so the two loads need no order)
-        const bool made = (uint32_t)(t >> kTagLaunchBits) == Cc.epoch;
-        hit = made && t != now && slot != kNoSlot;
-        build = !hit;
-        ref = hit ? slot : kRefBuild;
-        if (build && t != now) claimed = atomicCAS(&Cc.tags[key], t, now) == t;
-        me.sid = sid; me.kind = kind; me.lit = (d.kind_byte >> 8) & 0xFFu; me.cls = d.cls; me.run = d.run;
-        me.r = T.lmax - variant; me.eos_next = d.eos_next; me.slot = kNoSlot;
-#pragma unroll
-        for (int w = 0; w < 2; w++) {
-            const uint32_t nt = w ? d.next_b : d.next_a;
-            me.hop[w] = HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
-            if (nt < T.n_states) {
-                const bool lit = (dn[w].kind_byte & 0xFFu) == WG_KIND_LIT;
-                me.hop[w] = HopState{dn[w].kind_byte & 0xFFu, (dn[w].kind_byte >> 8) & 0xFFu,
-                                     lit ? nt : dn[w].next_a, dn[w].next_b, lit ? dn[w].run : dn[w].max, dn[w].cls};
-            }
+        if (f.class_claimed || cis == mine) class_state = CLASS_OWN;
+    }
+    auto hop = [&](uint32_t nt, const StateDesc &n) {
+        if (nt >= T.n_states) return HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
+        const bool lit = (n.kind_byte & 0xFFu) == WG_KIND_LIT;
+        return HopState{n.kind_byte & 0xFFu, (n.kind_byte >> 8) & 0xFFu, lit ? nt : n.next_a, n.next_b, lit ? n.run : n.max, n.cls};
+    };
+    f.me = RowTask{sid, kind, (d.kind_byte >> 8) & 0xFFu, d.cls, d.run, T.lmax - variant, class_state, d.eos_next,
+                   f.keep && Cc.direct ? f.key : kNoSlot, {hop(d.next_a, da), hop(d.next_b, db)}};
+    return f;
+}
+
+// One thread per request.  With tokens the states are advanced first.
+__global__ void __launch_bounds__(64)
+lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
+              const int32_t *__restrict__ tokens, uint32_t B)
+{
+    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63u;
+    const unsigned long long sc = Cc.ctr->slot_ctr, launch = Cc.ctr->launch;
+    const uint32_t rows0 = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;      // rows in use before this call
+    Found f{};
+    f.ref = kNoKey;
+    if (b < B) {
+        uint32_t sid = states[b].sid, aux = states[b].aux;
+        const int32_t t = tokens ? tokens[b] : 0;
+        StateDesc d = descriptor(T, sid);
+        if (tokens) {
+            advance_one<true>(T, Vc, Cc, sid, aux, d, (int64_t)t, true);
+            states[b].sid = sid; states[b].aux = aux;
         }
-        me.class_state = ct != now && (uint32_t)(ct >> kTagLaunchBits) == Cc.epoch ? CLASS_READY : CLASS_SELF;
-        if (claimed && ckpt && me.class_state != CLASS_READY && ct != now) {
-            class_claimed = atomicCAS(&Cc.class_tags[cls], ct, now) == ct;
-            if (class_claimed) me.class_state = CLASS_OWN;
-        }
+        f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, d);
     }
     // the claimers of a wavefront take their arena rows together
-    const unsigned long long cm = __ballot(claimed), km = __ballot(class_claimed);
+    const unsigned long long cm = __ballot(f.claimed), km = __ballot(f.class_claimed);
     if (cm) {
         uint32_t first = 0;
         if (lane == 0) {
@@ -235,48 +279,19 @@ __device__ __forceinline__ void lookup_one(const DeviceTable &T, const DeviceCac
             if (km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
         }
         first = __shfl(first, 0);
-        if (claimed) {
-            const uint32_t idx = first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
-            me.slot = Cc.cap_rows - env.rows0 > idx ? env.rows0 + idx : kNoSlot;
-            Cc.slots[key] = me.slot;
+        if (f.claimed && !Cc.direct) {
+            const uint32_t idx = rows0 + first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
+            f.me.slot = idx < Cc.cap_rows ? (Cc.free_rows ? Cc.free_rows[idx] : idx) : kNoSlot;
+            Cc.slots[f.key] = f.me.slot;
         }
     }
-    if (live) {
-        Cc.row_ref[b] = ref;
-        if (build) Cc.tasks[b] = me;
+    if (b < B) {
+        Cc.row_ref[b] = f.ref;
+        if (f.ref == kRefBuild) Cc.tasks[b] = f.me;
     }
     // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread)
-    const unsigned long long hv = __ballot(hit);
+    const unsigned long long hv = __ballot(f.hit);
     if (lane == 0 && hv) atomicAdd(&Cc.spread[(blockIdx.x % kSpread) * kSpreadStride + kSpreadHits], (unsigned long long)__popcll(hv));
-}
-
-__global__ void __launch_bounds__(64)
-lookup_kernel(DeviceTable T, DeviceCache Cc, const wg_state_t *__restrict__ states, uint32_t B)
-{
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = b < B;
-    const LookupEnv env = lookup_env(Cc);
-    uint32_t sid = 0, aux = 0;
-    if (live) { sid = states[b].sid; aux = states[b].aux; }
-    lookup_one(T, Cc, env, b, live, sid, aux);
-}
-
-// advance followed by the lookup of the next step's fill: the new state goes straight from the
-// walker into the cache lookup.
-__global__ void __launch_bounds__(64)
-advance_lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
-                      const int32_t *__restrict__ tokens, uint32_t B)
-{
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = b < B;
-    const LookupEnv env = lookup_env(Cc);
-    uint32_t sid = 0, aux = 0;
-    if (live) {
-        sid = states[b].sid; aux = states[b].aux;
-        advance_one(T, Vc, Cc, sid, aux, (int64_t)tokens[b]);
-        states[b].sid = sid; states[b].aux = aux;
-    }
-    lookup_one(T, Cc, env, b, live, sid, aux);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -396,6 +411,8 @@ struct RowShared {
     uint16_t code[kRanges];                    // byte value | FROM_* << 8
     uint32_t queue[kRowWaves][64u * (kRowBatch + 1u)];   // tokens to decide: id | length << 24
     uint32_t n_ranges, total;
+    RowTask task;                              // what the row's lookup left (one-kernel fill)
+    uint32_t ref;
 };
 
 // Inclusive prefix sum over the wavefront, in registers (every lane calls it).
@@ -441,10 +458,9 @@ __device__ __forceinline__ bool walk_run(const DeviceTable &T, const RunBytes &l
         const uint64_t mask = m >= 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
         if ((window(t, i + 8u * k) ^ lit.w[k]) & mask) return false;
     }
-    uint32_t aux = 0;
     if (n <= 24u) { sid = n == run ? after : sid + n; i += n; }
     else { sid += 24u; i += 24u; }
-    return walk(T, sid, aux, t, i, L);
+    return walk_from(T, sid, t, i, L);
 }
 
 // Walks bytes [i, L), i < L, of a token from the staged successor; goes on through the state table
@@ -470,8 +486,7 @@ __device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h
             if (i >= L) return true;
         }
     } else return false;
-    aux = 0;
-    return walk(T, sid, aux, t, i, L);
+    return walk_from(T, sid, t, i, L);
 }
 
 // First token of range p (as part_tok says; computed, because an array in a kernel argument is not
@@ -707,37 +722,86 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
     }
 }
 
-// The call is over for the cache once its lookups are: one thread of the kernel after them counts
-// the claimed rows as used and opens the next call.
-__device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B)
+// The call is over for the cache once its lookups are: one thread then counts the claimed rows as used
+// and opens the next call.
+__device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, uint32_t n, uint32_t n_classes)
 {
-    Cc.ctr->lookups += B;
     const unsigned long long sc = Cc.ctr->slot_ctr;
     const uint32_t used = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;
-    const uint32_t room = Cc.cap_rows - used, n = Cc.ctr->n_claims;
+    const uint32_t room = Cc.cap_rows - used;
     if (n > room) Cc.ctr->uncached_builds += n - room;
     Cc.ctr->slot_ctr = ((unsigned long long)Cc.epoch << 32) | (used + (n < room ? n : room));
+    Cc.ctr->lookups += B;
     Cc.ctr->builds += n;
-    Cc.ctr->class_scans += Cc.ctr->n_class_claims;
-    Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
+    Cc.ctr->class_scans += n_classes;
     Cc.ctr->launch++;
 }
 
+// A workgroup of a one-kernel fill has done its lookup: `claims` says what it claimed (1: a key,
+// +0x100: a class table as well).  Returns what is left to do at the kernel's end.
+__device__ __forceinline__ uint32_t take_ticket(const DeviceCache &Cc, uint32_t b, uint32_t claims)
+{
+    return atomicAdd(&Cc.tickets[b], 1u | claims << 8);
+}
+// The last workgroup of a row writes the row's state, the last row of a group adds up the group, the
+// last group closes the call: no counter is added to by more than a few dozen workgroups.  Every
+// counter is left at zero.
+__device__ __forceinline__ void close_row(const DeviceCache &Cc, uint32_t b, uint32_t B, uint32_t parts, uint32_t ticket, uint32_t claims,
+                                          wg_state_t *states, uint32_t sid, uint32_t aux)
+{
+    if ((ticket & 0xFFu) != parts - 1u) return;
+    Cc.tickets[b] = 0u;
+    if (states) states[b] = wg_state_t{sid, aux};
+    const uint32_t g = b % kTicketGroups, n_groups = B < kTicketGroups ? B : kTicketGroups;
+    const unsigned long long got = (ticket >> 8) + claims;
+    unsigned long long add = 1ull | (got & 0xFFu) << 20 | (got >> 8) << 40;
+    unsigned long long *group = Cc.ticket_groups + g * kSpreadStride, *top = Cc.ticket_groups + kTicketGroups * kSpreadStride;
+    unsigned long long was = atomicAdd(group, add);
+    if ((was & 0xFFFFFull) != (B - g + kTicketGroups - 1u) / kTicketGroups - 1u) return;
+    *group = 0ull;
+    add = (was + add) & ~0xFFFFFull | 1ull;
+    was = atomicAdd(top, add);
+    if ((was & 0xFFFFFull) != n_groups - 1u) return;
+    *top = 0ull;
+    was += add;
+    close_fill(Cc, B, (uint32_t)(was >> 20) & 0xFFFFFu, (uint32_t)(was >> 40) & 0xFFFFFu);
+}
+
 // kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_span).
-template <typename Elem, int kMode>
-__global__ void __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(8)))
+// kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
+// before it (tokens may be null), and takes a ticket; the state is written when all of them have read
+// it.  One launch instead of two, and a row waits for its own lookup only, not for the longest walk
+// of the batch.
+template <typename Elem, int kMode, bool kWhole>
+__global__ void __launch_bounds__(kRowThreads, kWhole ? 4 : 8)
 rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict__ bitmask, Elem *__restrict__ logits,
-            int64_t logits_stride)
+            int64_t logits_stride, wg_state_t *__restrict__ states, const int32_t *__restrict__ tokens)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t row[];
     __shared__ __attribute__((aligned(16))) RowShared sh;
     const uint32_t b = blockIdx.y, tid = threadIdx.x, span = kParts / gridDim.x, p0 = blockIdx.x * span;
     const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
-    if (tok_lo >= tok_hi) return;                    // (never the last workgroup of a row)
     const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
-    const RowTask in = Cc.tasks[b];                   // (requested with the reference; only used where that asks for it)
-    const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)Cc.row_ref[b]);
+    uint32_t ticket = 0, claims = 0, sid = 0, aux = 0;
+    if (kWhole) {
+        if (tid == 0) {
+            const unsigned long long launch = Cc.ctr->launch;
+            sid = states[b].sid; aux = states[b].aux;
+            const int32_t t = tokens ? tokens[b] : 0;
+            StateDesc d = descriptor(T, sid);
+            if (tokens) advance_one<true>(T, Vc, Cc, sid, aux, d, (int64_t)t, p0 == 0u);
+            const Found f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, d);
+            sh.ref = f.ref;
+            if (f.ref == kRefBuild) sh.task = f.me;
+            claims = (f.claimed ? 1u : 0u) | (f.class_claimed ? 0x100u : 0u);
+            ticket = take_ticket(Cc, b, claims);
+            if (f.hit && p0 == 0u) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadHits], 1ull);
+        }
+        __syncthreads();
+    }
+    const RowTask in = kWhole ? sh.task : Cc.tasks[b];   // (requested with the reference; only used where that asks for it)
+    const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kWhole ? sh.ref : Cc.row_ref[b]));
     uint4 *row4 = reinterpret_cast<uint4 *>(row);
     uint32_t slot = kNoSlot;
     if (ref == kRefBuild) {
@@ -770,7 +834,38 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
         }
     }
     if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
-    if (blockIdx.x == gridDim.x - 1u && b == 0 && tid == 0) close_fill(Cc, gridDim.y);
+    if (kWhole) {
+        if (tid == 0) close_row(Cc, b, gridDim.y, gridDim.x, ticket, claims, tokens ? states : nullptr, sid, aux);
+    } else if (blockIdx.x == 0 && b == 0 && tid == 0) {
+        close_fill(Cc, gridDim.y, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
+        Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
+    }
+}
+
+// The arena stops being addressed by key (more keys than rows): the rows that no key of this
+// generation holds, behind as many places as rows are in use; the held keys get their slots.
+__global__ void __launch_bounds__(1024)
+free_rows_kernel(DeviceCache Cc, uint32_t n_keys, uint32_t *__restrict__ free_rows)
+{
+    __shared__ uint32_t wave_n[16], base;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const unsigned long long sc = Cc.ctr->slot_ctr;
+    if (tid == 0) base = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;
+    for (uint32_t i = tid; i < n_keys; i += 1024u) Cc.slots[i] = i;
+    for (uint32_t r0 = 0; r0 < Cc.cap_rows; r0 += 1024u) {
+        const uint32_t r = r0 + tid;
+        const bool is_free = r < Cc.cap_rows && !(r < n_keys && (uint32_t)(Cc.tags[r] >> kTagEpochShift) == Cc.epoch);
+        const unsigned long long m = __ballot(is_free);
+        __syncthreads();
+        if (lane == 0) wave_n[wave] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t at = base, all = 0;
+        for (uint32_t w = 0; w < 16u; w++) { if (w < wave) at += wave_n[w]; all += wave_n[w]; }
+        at += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (is_free && at < Cc.cap_rows) free_rows[at] = r;
+        __syncthreads();
+        if (tid == 0) base += all;
+    }
 }
 
 // apply: a workgroup takes kApplyTokens tokens of a row.
@@ -893,24 +988,38 @@ uint32_t rows_lds_bytes(const DeviceVocab &Vc)
 
 hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
-                       void *logits, int dtype, int64_t logits_stride, hipStream_t s, hipEvent_t *ev)
+                       void *logits, int dtype, int64_t logits_stride, uint32_t n_cu, hipStream_t s, hipEvent_t *ev)
 {
-    if (tokens) launch(advance_lookup_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, ev, T, Vc, Cc, states, tokens, B);
-    else launch(lookup_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, ev, T, Cc, static_cast<const wg_state_t *>(states), B);
     const dim3 g(row_parts(Vc.V), B);
     const uint32_t lds = rows_lds_bytes(Vc);
+    // One kernel up to a workgroup per compute unit: there the launch it saves (10 to 13 us of 70 to 85 a
+    // pass of 8 cached steps, B <= 8, 151936 tokens) outweighs the lookup that every workgroup of a row
+    // repeats; with four per unit it is 199 us instead of 190 where the rows are made, and with eight 278
+    // instead of 232.
+    const bool whole = Cc.direct && (uint64_t)B * g.x <= n_cu && !by_lines(dtype, B, Vc.V);
+    if (!whole) launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
     hipEvent_t *re = ev ? ev + 2 : nullptr;
+    auto rows = [&](auto kernel, auto *x) { launch(kernel, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
     if (!logits) {
-        launch(rows_kernel<uint16_t, 0>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, (uint16_t *)nullptr, (int64_t)0);
+        if (whole) rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr);
+        else rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);
     } else if (dtype == WG_F32) {
         uint32_t *x = static_cast<uint32_t *>(logits);
-        if (by_lines(dtype, B, Vc.V)) launch(rows_kernel<uint32_t, 2>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
-        else launch(rows_kernel<uint32_t, 1>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
+        if (whole) rows(rows_kernel<uint32_t, 1, true>, x);
+        else if (by_lines(dtype, B, Vc.V)) rows(rows_kernel<uint32_t, 2, false>, x);
+        else rows(rows_kernel<uint32_t, 1, false>, x);
     } else {
         uint16_t *x = static_cast<uint16_t *>(logits);
-        if (by_lines(dtype, B, Vc.V)) launch(rows_kernel<uint16_t, 2>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
-        else launch(rows_kernel<uint16_t, 1>, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride);
+        if (whole) rows(rows_kernel<uint16_t, 1, true>, x);
+        else if (by_lines(dtype, B, Vc.V)) rows(rows_kernel<uint16_t, 2, false>, x);
+        else rows(rows_kernel<uint16_t, 1, false>, x);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s)
+{
+    free_rows_kernel<<<1, 1024, 0, s>>>(Cc, n_keys, free_rows);
     return hipGetLastError();
 }
 
@@ -935,7 +1044,7 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
                           wg_state_t *states, const int32_t *tokens, uint32_t B, hipStream_t s,
                           hipEvent_t *ev)
 {
-    launch(advance_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, ev, T, Vc, Cc, states, tokens, B);
+    launch(advance_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
     return hipGetLastError();
 }
 
