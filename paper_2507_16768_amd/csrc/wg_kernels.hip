@@ -957,13 +957,21 @@ static inline void launch(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStre
     else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 
-// Logits larger than this are masked by whole lines (see mask_span): 128 bytes are read where a
-// line is mixed, but no store leaves the memory to read and write the block around it.
-constexpr uint64_t kLineBytes = 192ull << 20;
+// Logits of more bytes than these are masked by whole lines (see mask_span): 128 bytes are read where a
+// line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
+// depends on how many tokens of a line are disallowed, which the host does not know; the lines lie where
+// masks of 16 to 63 % disallowed tokens lose as much as they gain.  By elements / by lines, us, the kernel
+// of a cached step on 151936 tokens, 20 operator html templates and random trees:
+//   bf16, 194 MB 49 / 65 and 89 / 71, 243 MB 87 / 89 and 115 / 91, 311 MB 116 / 106 and 143 / 112
+//   fp32, 200 MB 28 / 58 and 75 / 72, 311 MB 65 / 83 and 131 / 111, 389 MB 109 / 112 and 168 / 141
+// (a block holds twice as many bf16 tokens, so fewer of them stay untouched.)  Deciding by the density
+// of each row or line was slower than the better of the two for all.
+constexpr uint64_t kLineBytes16 = 192ull << 20, kLineBytes32 = 320ull << 20;
 
 static bool by_lines(int dtype, uint32_t B, uint32_t V)
 {
-    return (uint64_t)B * V * (dtype == WG_F32 ? 4u : 2u) > kLineBytes;
+    const uint64_t n = (uint64_t)B * V;
+    return dtype == WG_F32 ? n * 4u > kLineBytes32 : n * 2u > kLineBytes16;
 }
 
 // Workgroups per row: the row is cut at its token ranges, into as many pieces as there are groups

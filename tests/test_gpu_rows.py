@@ -100,9 +100,10 @@ def test_masking_at_every_alignment(torch_cuda, V, dtype):
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
 
 
-@pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("f32", 400, 128256, 0)])
+@pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("f32", 400, 128256, 0), ("f32", 700, 128256, 0)])
 def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, pad):
-    """More than 192 MiB of logits: lines are read where they are mixed and written whole."""
+    """More than 192 MiB of bf16 or 320 MiB of fp32 logits: lines are read where they are mixed and
+    written whole."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -128,7 +129,7 @@ def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
     other tests compare with the oracle): masks, states and masked logits, cold and warm."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
-    w = ws.make_workload(5, V=151936 if dtype == "bf16" else 60001, B=720 if dtype == "bf16" else 900, steps=3)
+    w = ws.make_workload(5, V=151936 if dtype == "bf16" else 90001, B=720 if dtype == "bf16" else 1000, steps=3)
     o = H.make_oracle(w)
     v, h = H.make_gpu(w)
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
