@@ -388,7 +388,7 @@ void wg_destroy(wg_handle_t h) {
     (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
     (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
-    (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_groups); (void)hipFree(h->d_free_rows);
+    (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_all); (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
@@ -442,9 +442,8 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     const size_t spread_bytes = (size_t)kSpread * kSpreadStride * sizeof(unsigned long long);
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.spread), spread_bytes));
     WG_HIP(hipMemset(h->dc.spread, 0, spread_bytes));
-    const size_t group_bytes = (size_t)(kTicketGroups + 1) * kSpreadStride * sizeof(unsigned long long);
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ticket_groups), group_bytes));
-    WG_HIP(hipMemset(h->dc.ticket_groups, 0, group_bytes));
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ticket_all), sizeof(unsigned long long)));
+    WG_HIP(hipMemset(h->dc.ticket_all, 0, sizeof(unsigned long long)));
     int cus = 0;
     WG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, vocab->device));
     if (cus > 0) h->n_cu = (uint32_t)cus;

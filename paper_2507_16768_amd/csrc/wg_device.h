@@ -95,7 +95,6 @@ constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
 constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1;
-constexpr uint32_t kTicketGroups = 16;
 
 struct DeviceCache {
     Counters *ctr;
@@ -113,8 +112,8 @@ struct DeviceCache {
     // per call
     uint32_t *row_ref;           // [B] arena row, kRefBuild or kNoKey
     RowTask *tasks;              // [B]
-    uint32_t *tickets;           // [B] workgroups of a row that have done their lookup, what they claimed above
-    unsigned long long *ticket_groups;   // kTicketGroups + 1 counters, kSpreadStride apart
+    uint32_t *tickets;           // [B] workgroups of a row that have done their lookup (zero between calls),
+    unsigned long long *ticket_all;      // workgroups of the call, and what they claimed above
     uint32_t row_stride;         // words, multiple of 4
     uint32_t n_keys;
     uint32_t epoch;              // cache generation of this call

@@ -74,66 +74,114 @@ __device__ __forceinline__ uint32_t first_leaving(uint32_t code, uint32_t n)
     return mm ? (uint32_t)__builtin_ctz(mm) >> 1 : n;
 }
 
+// One visit of a literal state by a walk whose next eight bytes are tb, n of them the token's; l0, l1:
+// the literal bytes around the state's.  False: a byte differs.
+__device__ __forceinline__ bool literal_step(const StateDesc &d, uint64_t l0, uint64_t l1, uint64_t tb, uint32_t n,
+                                             uint32_t &sid, uint32_t &aux, uint32_t &i)
+{
+    const uint32_t sh = (sid & 7u) * 8u;
+    const uint64_t lv = sh ? (l0 >> sh) | (l1 << (64u - sh)) : l0;
+    const uint32_t m = n < d.run ? n : d.run;                // literal bytes compared now
+    const uint64_t mask = m == 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
+    if ((tb ^ lv) & mask) return false;
+    sid = m == d.run ? d.cls : sid + m;                      // d.cls: state after the Write
+    aux = 0; i += m;
+    return true;
+}
+// The same of a checkpoint, code: the classes of the eight bytes.  left: the exit that was taken, or
+// CLS_STAY.
+__device__ __forceinline__ bool class_step(const StateDesc &d, uint32_t code, uint32_t n, uint32_t &aux, uint32_t &i, uint32_t &left)
+{
+    const uint32_t stays = first_leaving(code, n);
+    if (d.max != WG_UNBOUNDED && stays) {                    // each stay needs budget left
+        if (aux >= d.max || stays > d.max - aux) return false;
+        aux += stays;
+    }
+    i += stays;
+    left = CLS_STAY;
+    if (stays == n) return true;
+    left = (code >> (2u * stays)) & 3u;
+    aux = 0; i += 1u;
+    return left != CLS_REJECT;
+}
+
 // Walks bytes [i, L) of a token from (sid, aux), up to eight bytes per state visit: a run of
 // literal states is one masked 8-byte compare against the state table's literal bytes, a stay-run
 // inside a checkpoint is eight independent class look-ups.  Every state entered on the way starts
-// with aux = 0; only a bounded Wait counts.  False on the first rejected byte.  kAhead: d holds the
-// descriptor of sid, at the call and after it, and the literal bytes are requested with it, for a
-// caller that goes on from the state it ends in (a step of the lookup kernel's walk is one trip to
-// memory instead of two: 6.2 -> 5.6 us at B = 256); elsewhere the extra loads only cost.
-template <bool kAhead>
-__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, StateDesc &d, TokenBytes &t, uint32_t i, uint32_t L)
+// with aux = 0; only a bounded Wait counts.  False on the first rejected byte.
+__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
     while (i < L) {
-        if (sid >= T.n_states) return false;                     // ERROR or corrupt state
-        uint64_t l0 = 0, l1 = 0;
-        if (kAhead) { l0 = lit64[sid >> 3]; l1 = lit64[(sid >> 3) + 1u]; }
-        else d = T.states[sid];
+        if (sid >= T.n_states) return false;                 // ERROR or corrupt state
+        const StateDesc d = T.states[sid];
         const uint32_t kind = d.kind_byte & 0xFFu;
         const uint32_t n = L - i < 8u ? L - i : 8u;
         const uint64_t tb = window(t, i);
         if (kind == WG_KIND_LIT) {
-            if (!kAhead) { l0 = lit64[sid >> 3]; l1 = lit64[(sid >> 3) + 1u]; }
-            const uint32_t sh = (sid & 7u) * 8u;
-            const uint64_t lv = sh ? (l0 >> sh) | (l1 << (64u - sh)) : l0;
-            const uint32_t m = n < d.run ? n : d.run;            // literal bytes compared now
-            const uint64_t mask = m == 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
-            if ((tb ^ lv) & mask) return false;
-            sid = m == d.run ? d.cls : sid + m;                  // d.cls: state after the Write
-            aux = 0; i += m;
+            if (!literal_step(d, lit64[sid >> 3], lit64[(sid >> 3) + 1u], tb, n, sid, aux, i)) return false;
         } else if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
-            const uint32_t code = class_code(T.classes + (size_t)d.cls * 256u, tb);
-            const uint32_t stays = first_leaving(code, n);
-            if (d.max != WG_UNBOUNDED && stays) {                // each stay needs budget left
-                if (aux >= d.max || stays > d.max - aux) return false;
-                aux += stays;
-            }
-            i += stays;
-            if (stays == n) continue;
-            const uint32_t c = (code >> (2u * stays)) & 3u;
-            if (c == CLS_REJECT) return false;
-            sid = c == CLS_EXIT_A ? d.next_a : d.next_b;
-            aux = 0; i += 1u;
-        } else return false;                                     // FINAL / END accept no byte
-        if (kAhead && sid < T.n_states) d = T.states[sid];
+            uint32_t left;
+            if (!class_step(d, class_code(T.classes + (size_t)d.cls * 256u, tb), n, aux, i, left)) return false;
+            if (left != CLS_STAY) sid = left == CLS_EXIT_A ? d.next_a : d.next_b;
+        } else return false;                                 // FINAL / END accept no byte
+    }
+    return true;
+}
+
+// A state and the literal bytes around it, requested together (of state 0 where there is no such state).
+struct Visit { StateDesc d; uint64_t l0, l1; };
+__device__ __forceinline__ Visit visit(const DeviceTable &T, uint32_t sid)
+{
+    const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
+    const uint32_t s = sid < T.n_states ? sid : 0u;
+    return Visit{T.states[s], lit64[s >> 3], lit64[(s >> 3) + 1u]};
+}
+// walk() for one token by itself, where every step is a trip to memory that nothing else hides (a pass of
+// 8 cached steps of one request 53 -> 49 us, of 4 mixed requests 58 -> 54): v is
+// the visit of sid, at the call and after it.  It is requested before it is known to be needed: with the
+// classes of a checkpoint's bytes both of its successors'.
+__device__ __forceinline__ bool walk_ahead(const DeviceTable &T, uint32_t &sid, uint32_t &aux, Visit &v, TokenBytes &t, uint32_t L)
+{
+    uint32_t i = 0;
+    while (i < L) {
+        if (sid >= T.n_states) return false;
+        const StateDesc d = v.d;
+        const uint32_t kind = d.kind_byte & 0xFFu;
+        const uint32_t n = L - i < 8u ? L - i : 8u;
+        const uint64_t tb = window(t, i);
+        if (kind == WG_KIND_LIT) {
+            if (!literal_step(d, v.l0, v.l1, tb, n, sid, aux, i)) return false;
+            v = visit(T, sid);
+        } else if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
+            // (behind the classes, so that a walk that stays does not wait for them)
+            const uint8_t *lut = T.classes + (size_t)d.cls * 256u;
+            uint32_t c[8], code = 0, left;
+#pragma unroll
+            for (int k = 0; k < 8; k++) c[k] = lut[(tb >> (8 * k)) & 0xFFu];
+            asm volatile("" ::: "memory");
+            const Visit va = visit(T, d.next_a), vb = visit(T, d.next_b);
+#pragma unroll
+            for (int k = 0; k < 8; k++) code |= c[k] << (2 * k);
+            if (!class_step(d, code, n, aux, i, left)) return false;
+            if (left == CLS_EXIT_A) { sid = d.next_a; v = va; }
+            else if (left == CLS_EXIT_B) { sid = d.next_b; v = vb; }
+        } else return false;
     }
     return true;
 }
 __device__ __forceinline__ bool walk_from(const DeviceTable &T, uint32_t sid, TokenBytes &t, uint32_t i, uint32_t L)
 {
     uint32_t aux = 0;
-    StateDesc d;
-    return walk<false>(T, sid, aux, d, t, i, L);
+    return walk(T, sid, aux, t, i, L);
 }
 
 // ---------------------------------------------------------------------------------------------
 // advance: one thread per request (EOS is the one-symbol string [EOS]; any other byte-less token
 // is rejected).
-// d: the descriptor of sid (when there is such a state) at the call and, with kAhead, after it.
-template <bool kAhead>
+// v: the visit of sid, at the call and after it.
 __device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                                            uint32_t &sid, uint32_t &aux, StateDesc &d, int64_t t, bool count_error)
+                                            uint32_t &sid, uint32_t &aux, Visit &v, int64_t t, bool count_error)
 {
     bool ok = t >= 0 && t < (int64_t)Vc.V && sid < T.n_states;
     if (ok) {
@@ -144,10 +192,10 @@ __device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVo
         tk.w0 = tk.chunks[0];
         tk.w1 = tk.n > 1u ? tk.chunks[tk.stride] : 0ull;
         if ((int64_t)Vc.eos_id == t) {
-            sid = d.eos_next; aux = 0;
+            sid = v.d.eos_next; aux = 0;
             ok = sid != WG_SID_ERROR;
-            if (kAhead && sid < T.n_states) d = T.states[sid];
-        } else ok = L != 0u && walk<kAhead>(T, sid, aux, d, tk, 0u, L);
+            v = visit(T, sid);
+        } else ok = L != 0u && walk_ahead(T, sid, aux, v, tk, L);
     }
     if (!ok) {
         sid = WG_SID_ERROR; aux = 0;
@@ -169,8 +217,8 @@ advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__rest
     if (b >= B) return;
     uint32_t sid = states[b].sid, aux = states[b].aux;
     const int32_t t = tokens[b];
-    StateDesc d = descriptor(T, sid);
-    advance_one<false>(T, Vc, Cc, sid, aux, d, (int64_t)t, true);
+    Visit v = visit(T, sid);
+    advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, true);
     states[b].sid = sid; states[b].aux = aux;
 }
 
@@ -193,21 +241,28 @@ __device__ __forceinline__ unsigned long long tag_now(const DeviceCache &Cc, uns
     return (unsigned long long)Cc.epoch << kTagEpochShift | (launch & kTagLaunchMask) << kTagRequestBits;
 }
 
+// The key of the state (sid, aux), d its descriptor; kNoKey: no such state.
+__device__ __forceinline__ uint32_t key_of(const DeviceTable &T, uint32_t sid, uint32_t aux, const StateDesc &d, uint32_t &variant)
+{
+    variant = 0;
+    if ((d.kind_byte & 0xFFu) == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
+        const uint32_t left = d.max > aux ? d.max - aux : 0u;
+        variant = T.lmax - (left < T.lmax ? left : T.lmax);
+    }
+    return sid < T.n_states ? d.key_base + variant : kNoKey;
+}
+
 // The lookup of request b in state (sid, aux), d its descriptor.
 __device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache &Cc, unsigned long long now, uint32_t b,
                                          uint32_t sid, uint32_t aux, const StateDesc &d)
 {
     Found f{};
     f.ref = kNoKey;
-    if (sid >= T.n_states) return f;
+    uint32_t variant;
+    f.key = key_of(T, sid, aux, d, variant);
+    if (f.key == kNoKey) return f;
     const unsigned long long mine = now | b;
     const uint32_t kind = d.kind_byte & 0xFFu;
-    uint32_t variant = 0;
-    if (kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
-        const uint32_t left = d.max > aux ? d.max - aux : 0u;
-        variant = T.lmax - (left < T.lmax ? left : T.lmax);
-    }
-    f.key = d.key_base + variant;
     const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
     const unsigned long long t = __hip_atomic_load(&Cc.tags[f.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t slot = Cc.direct ? f.key : Cc.slots[f.key];
@@ -263,12 +318,12 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
     if (b < B) {
         uint32_t sid = states[b].sid, aux = states[b].aux;
         const int32_t t = tokens ? tokens[b] : 0;
-        StateDesc d = descriptor(T, sid);
+        Visit v = visit(T, sid);
         if (tokens) {
-            advance_one<true>(T, Vc, Cc, sid, aux, d, (int64_t)t, true);
+            advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, true);
             states[b].sid = sid; states[b].aux = aux;
         }
-        f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, d);
+        f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, v.d);
     }
     // the claimers of a wavefront take their arena rows together
     const unsigned long long cm = __ballot(f.claimed), km = __ballot(f.class_claimed);
@@ -737,40 +792,11 @@ __device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, ui
     Cc.ctr->launch++;
 }
 
-// A workgroup of a one-kernel fill has done its lookup: `claims` says what it claimed (1: a key,
-// +0x100: a class table as well).  Returns what is left to do at the kernel's end.
-__device__ __forceinline__ uint32_t take_ticket(const DeviceCache &Cc, uint32_t b, uint32_t claims)
-{
-    return atomicAdd(&Cc.tickets[b], 1u | claims << 8);
-}
-// The last workgroup of a row writes the row's state, the last row of a group adds up the group, the
-// last group closes the call: no counter is added to by more than a few dozen workgroups.  Every
-// counter is left at zero.
-__device__ __forceinline__ void close_row(const DeviceCache &Cc, uint32_t b, uint32_t B, uint32_t parts, uint32_t ticket, uint32_t claims,
-                                          wg_state_t *states, uint32_t sid, uint32_t aux)
-{
-    if ((ticket & 0xFFu) != parts - 1u) return;
-    Cc.tickets[b] = 0u;
-    if (states) states[b] = wg_state_t{sid, aux};
-    const uint32_t g = b % kTicketGroups, n_groups = B < kTicketGroups ? B : kTicketGroups;
-    const unsigned long long got = (ticket >> 8) + claims;
-    unsigned long long add = 1ull | (got & 0xFFu) << 20 | (got >> 8) << 40;
-    unsigned long long *group = Cc.ticket_groups + g * kSpreadStride, *top = Cc.ticket_groups + kTicketGroups * kSpreadStride;
-    unsigned long long was = atomicAdd(group, add);
-    if ((was & 0xFFFFFull) != (B - g + kTicketGroups - 1u) / kTicketGroups - 1u) return;
-    *group = 0ull;
-    add = (was + add) & ~0xFFFFFull | 1ull;
-    was = atomicAdd(top, add);
-    if ((was & 0xFFFFFull) != n_groups - 1u) return;
-    *top = 0ull;
-    was += add;
-    close_fill(Cc, B, (uint32_t)(was >> 20) & 0xFFFFFu, (uint32_t)(was >> 40) & 0xFFFFFu);
-}
-
 // kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_span).
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
-// before it (tokens may be null), and takes a ticket; the state is written when all of them have read
-// it.  One launch instead of two, and a row waits for its own lookup only, not for the longest walk
+// before it (tokens may be null), and takes two tickets right after it: the last workgroup of a row to
+// do so writes the row's state (all have read it), the last of all closes the call, each at its end, when
+// the tickets' answers have long been there.  One launch instead of two, and a row waits for its own lookup only, not for the longest walk
 // of the batch.
 template <typename Elem, int kMode, bool kWhole>
 __global__ void __launch_bounds__(kRowThreads, kWhole ? 4 : 8)
@@ -783,19 +809,34 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
     const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
-    uint32_t ticket = 0, claims = 0, sid = 0, aux = 0;
+    uint32_t ticket = 0, sid = 0, aux = 0;
+    unsigned long long all = 0, mine_all = 0;         // workgroups | keys claimed << 20 | class tables claimed << 40
+    uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
     if (kWhole) {
+        StateDesc d{};
+        unsigned long long launch = 0;
         if (tid == 0) {
-            const unsigned long long launch = Cc.ctr->launch;
+            launch = Cc.ctr->launch;
             sid = states[b].sid; aux = states[b].aux;
             const int32_t t = tokens ? tokens[b] : 0;
-            StateDesc d = descriptor(T, sid);
-            if (tokens) advance_one<true>(T, Vc, Cc, sid, aux, d, (int64_t)t, p0 == 0u);
+            Visit v = visit(T, sid);
+            if (tokens) advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, p0 == 0u);
+            d = v.d;
+            uint32_t variant;
+            sh.ref = key_of(T, sid, aux, d, variant);
+        }
+        __syncthreads();
+        // (key k has arena row k: the row is requested while its tag is looked at)
+        const uint32_t key = sh.ref;
+        if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
+        __syncthreads();
+        if (tid == 0) {
             const Found f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, d);
             sh.ref = f.ref;
             if (f.ref == kRefBuild) sh.task = f.me;
-            claims = (f.claimed ? 1u : 0u) | (f.class_claimed ? 0x100u : 0u);
-            ticket = take_ticket(Cc, b, claims);
+            mine_all = 1ull | (f.claimed ? 1ull << 20 : 0ull) | (f.class_claimed ? 1ull << 40 : 0ull);
+            all = atomicAdd(Cc.ticket_all, mine_all);
+            ticket = tokens ? atomicAdd(&Cc.tickets[b], 1u) : 0u;
             if (f.hit && p0 == 0u) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadHits], 1ull);
         }
         __syncthreads();
@@ -816,7 +857,7 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
         for (uint32_t w = tid; w < 4u * n4; w += kRowThreads) row[w] = w < n_words ? row[w] | early[w] : 0u;
     } else {
         const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
-        for (uint32_t q = tid; q < n4; q += kRowThreads) row4[q] = ref < Cc.cap_rows ? src[q] : uint4{0u, 0u, 0u, 0u};
+        for (uint32_t q = tid; q < n4; q += kRowThreads) row4[q] = ref >= Cc.cap_rows ? uint4{0u, 0u, 0u, 0u} : kWhole && q == tid ? ahead : src[q];
     }
     __syncthreads();
     if (slot != kNoSlot) {
@@ -835,7 +876,17 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     }
     if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
     if (kWhole) {
-        if (tid == 0) close_row(Cc, b, gridDim.y, gridDim.x, ticket, claims, tokens ? states : nullptr, sid, aux);
+        if (tid == 0) {
+            if (tokens && ticket == gridDim.x - 1u) {
+                Cc.tickets[b] = 0u;
+                states[b] = wg_state_t{sid, aux};
+            }
+            if ((uint32_t)(all & 0xFFFFFu) == gridDim.x * gridDim.y - 1u) {
+                *Cc.ticket_all = 0ull;
+                all += mine_all;
+                close_fill(Cc, gridDim.y, (uint32_t)(all >> 20) & 0xFFFFFu, (uint32_t)(all >> 40));
+            }
+        }
     } else if (blockIdx.x == 0 && b == 0 && tid == 0) {
         close_fill(Cc, gridDim.y, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
         Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
