@@ -287,8 +287,7 @@ int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uin
     }
     v->dv = DeviceVocab{v->d_len8, v->d_chunks, v->d_len_rows, v->d_rows, v->d_index, v->d_dir0,
                         v->d_lit_start, v->d_dirN, v->d_place_start, at[0], at[1], at[2], at[3],
-                        V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride, {}};
-    for (uint32_t p = 0; p <= kParts; p++) v->dv.part_tok[p] = ix.part_tok[p];
+                        V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride};
     *out = v.release();
     return WG_OK;
 }

@@ -43,7 +43,6 @@ struct DeviceVocab {
     uint32_t lmax;
     uint32_t n_chunks;           // ceil(lmax / 8)
     uint32_t row_stride;         // words per mask row in device arenas (multiple of 4)
-    uint32_t part_tok[kParts + 1];  // first token of each range; part_tok[kParts] == V
 };
 
 // A successor state as the row builder needs it for the first hop of a walk.

@@ -40,11 +40,11 @@ struct Table {
     uint32_t flags = 0;
 };
 
-// The token ids are cut into kParts contiguous ranges (on 2048-token boundaries, so on 256-byte
-// boundaries of a mask row; a class_scan workgroup takes kPartGroup tokens, all in one range).  Every list of candidate tokens is kept per range, so that the
-// row of a state key whose candidates all need a deep walk can be built by several workgroups,
-// each owning the words of its ranges, without any merging.
-constexpr uint32_t kParts = 8;
+// The token ids are cut into kParts contiguous ranges, on boundaries of kPartGroup tokens, so on
+// 256-byte boundaries of a mask row.  Every list of candidate tokens is kept per range, so that a row
+// can be made by several workgroups, each owning the words of some neighbouring ranges, without any
+// merging.
+constexpr uint32_t kParts = 32;
 constexpr uint32_t kPartGroup = 2048;
 
 // What the kernels want to know about a class table without reading its 256 bytes: the bytes

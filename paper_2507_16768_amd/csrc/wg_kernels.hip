@@ -544,9 +544,9 @@ __device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h
     return walk_from(T, sid, t, i, L);
 }
 
-// First token of range p (as part_tok says; computed, because an array in a kernel argument is not
-// indexed in registers).
-__device__ __forceinline__ uint32_t range_token(const DeviceVocab &Vc, uint32_t p)
+// First token of range p (as the vocabulary's index is made; computed, because an array in a kernel
+// argument is not indexed in registers).
+__host__ __device__ __forceinline__ uint32_t range_token(const DeviceVocab &Vc, uint32_t p)
 {
     const uint32_t groups = (Vc.V + kPartGroup - 1u) / kPartGroup, t = p * groups / kParts * kPartGroup;
     return p >= kParts || t > Vc.V ? Vc.V : t;
@@ -1025,21 +1025,36 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
     return dtype == WG_F32 ? n * 4u > kLineBytes32 : n * 2u > kLineBytes16;
 }
 
-// Workgroups per row: the row is cut at its token ranges, into as many pieces as there are groups
-// of kPartGroup tokens, at most kParts.
-static uint32_t row_parts(uint32_t V)
+// Workgroups per row: the row is cut at its token ranges, into `most` pieces where each gets kPartGroup
+// tokens, else into fewer.
+static uint32_t row_parts(uint32_t V, uint32_t most)
 {
-    uint32_t parts = kParts;
+    uint32_t parts = most;
     while (parts > 1u && (uint64_t)parts * kPartGroup > V) parts >>= 1;
     return parts;
+}
+// Most workgroups per row.  8, which is what fills the chip with long rows of 256 requests; more where
+// that leaves compute units idle or with little to do, as long as a workgroup keeps enough tokens to be
+// worth what it starts with (151936 tokens, 70000 tokens, us a pass of 8 cached steps):
+//   up to a workgroup on every second unit, 4096 tokens each: B = 1 69 with 8, 58 with 16, 51 with 32;
+//   B = 4 67, 57, 57; B = 8 72, 66 with 16, 70 with 32 (70000 tokens: 60, 58, 68)
+//   above the one-kernel fill, up to 6 workgroups on a unit, 6144 tokens each: B = 64 118 with 8, 114 with
+//   16; B = 96 137, 130 (with rows to make: 212, 201; 70000 tokens no difference)
+constexpr uint32_t kLeastParts = 8;
+static uint32_t most_parts(uint32_t V, uint32_t B, uint32_t n_cu)
+{
+    uint32_t most = kLeastParts;
+    while (most < kParts && (uint64_t)B * most * 2u <= n_cu / 2u && (uint64_t)most * 2u * 4096u <= V) most *= 2u;
+    if ((uint64_t)B * most > n_cu && (uint64_t)B * 2u * kLeastParts <= n_cu * 6u && 2u * kLeastParts * 6144u <= V) most = 2u * kLeastParts;
+    return most;
 }
 
 uint32_t rows_lds_bytes(const DeviceVocab &Vc)
 {
-    const uint32_t parts = row_parts(Vc.V), span = kParts / parts;
+    const uint32_t parts = row_parts(Vc.V, kLeastParts), span = kParts / parts;
     uint32_t most = 0;
     for (uint32_t p = 0; p < kParts; p += span) {
-        const uint32_t n = ((Vc.part_tok[p + span] + 31u) >> 5) - (Vc.part_tok[p] >> 5);
+        const uint32_t n = ((range_token(Vc, p + span) + 31u) >> 5) - (range_token(Vc, p) >> 5);
         most = n > most ? n : most;
     }
     return 2u * (((most + 3u) & ~3u) + 4u) * 4u;
@@ -1049,7 +1064,7 @@ hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const Device
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
                        void *logits, int dtype, int64_t logits_stride, uint32_t n_cu, hipStream_t s, hipEvent_t *ev)
 {
-    const dim3 g(row_parts(Vc.V), B);
+    const dim3 g(row_parts(Vc.V, most_parts(Vc.V, B, n_cu)), B);
     const uint32_t lds = rows_lds_bytes(Vc);
     // One kernel up to a workgroup per compute unit: there the launch it saves (10 to 13 us of 70 to 85 a
     // pass of 8 cached steps, B <= 8, 151936 tokens) outweighs the lookup that every workgroup of a row

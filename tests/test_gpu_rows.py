@@ -123,6 +123,37 @@ def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, 
     assert torch.equal(buf.view(bits), want.view(bits))
 
 
+@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97),
+                                 (40000, 32), (40000, 33), (8200, 7)])
+def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
+    """Rows cut into 4 to 32 workgroups, looked up in the rows' kernel and before it."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    w = ws.make_workload(5, V=V, B=B, steps=4)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    st = H.dev_states(H.start_states(o, w))
+    ref = st.clone()
+    mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+    draws = torch.from_numpy(w.token_draws(4).view(np.int64)).cuda()
+    tok = torch.empty(B, dtype=torch.int32, device="cuda")
+    for k in range(4):
+        x = torch.randn((B, V), device="cuda").to(torch.bfloat16)
+        y = x.clone()
+        if k == 2:
+            h.cache_clear()
+        h.decode_step(st, tok if k else None, mask, x)
+        if k:
+            h.advance(ref, tok)
+        assert torch.equal(st, ref), k
+        assert (H.host_mask(mask) == o.fill_masks(H.host_states(st))).all(), k
+        y.masked_fill_(~_unpack(torch, mask, V), float("-inf"))
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16)), k
+        wg.select_tokens(mask, V, draws[k], tok)
+    n = h.cache_stats()
+    assert h.error_count() == 0 and n["lookups"] == 4 * B and n["hits"] + n["builds"] <= 4 * B
+
+
 @pytest.mark.parametrize("dtype,stride_pad", [("bf16", 0), ("f32", 5)])
 def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
     """wg_decode_step with logits beyond the last-level cache against the separate calls (which the
