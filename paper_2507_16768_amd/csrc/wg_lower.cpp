@@ -36,6 +36,10 @@ struct Op {
     SetExpr allow, denies, wait, twait, fwait;      // WAIT / COND
     bool bounded = false; uint32_t max = 0;         // WAIT
     std::unique_ptr<Op> body, cond, if_body, else_body;
+    uint32_t number = 0;                            // of this operator in its tree
+    // WAIT / COND without holes: what its sets come to, the same for every instance (see Lowering::add)
+    struct Bound { uint64_t roll_backs = ~0ull; uint32_t cls = 0; bool eos_a = false, eos_b = false; };
+    mutable Bound bound;
     explicit Op(Kind k) : kind(k) {}
 };
 
@@ -50,9 +54,11 @@ class Reader {
         if (look() >= 0) die("trailing text after the operator");
         return op;
     }
+    uint32_t num_ops() const { return n_ops_; }
 
   private:
     const char *s_; size_t n_; size_t i_ = 0;
+    uint32_t n_ops_ = 0;
 
     [[noreturn]] void die(const std::string &m) const {
         throw ParseError("at offset " + std::to_string(i_) + ": " + m);
@@ -159,8 +165,14 @@ class Reader {
         }
     }
 
+    std::unique_ptr<Op> new_op(Op::Kind kind) {
+        auto op = std::make_unique<Op>(kind);
+        op->number = n_ops_++;
+        return op;
+    }
+
     std::unique_ptr<Op> wait_() {
-        auto op = std::make_unique<Op>(Op::WAIT);
+        auto op = new_op(Op::WAIT);
         bool has_body = false;
         keywords([&](const std::string &k) {
             if (k == "allow") op->allow = set();
@@ -197,7 +209,7 @@ class Reader {
         }
         need('(');
         if (name == "Sequence") {
-            auto op = std::make_unique<Op>(Op::SEQ);
+            auto op = new_op(Op::SEQ);
             while (true) {
                 int c = look();
                 if (c == ')') { i_++; return op; }
@@ -206,7 +218,7 @@ class Reader {
             }
         }
         if (name == "Write") {
-            auto op = std::make_unique<Op>(Op::WRITE);
+            auto op = new_op(Op::WRITE);
             if (look() == '$') { i_++; op->hole = word(); } else op->bytes = quoted();
             need(')');
             return op;
@@ -214,7 +226,7 @@ class Reader {
         if (name == "Wait") return wait_();
         if (name == "IfElse" || name == "DoWhile") {
             bool is_if = name == "IfElse";
-            auto op = std::make_unique<Op>(is_if ? Op::IFELSE : Op::DOWHILE);
+            auto op = new_op(is_if ? Op::IFELSE : Op::DOWHILE);
             keywords([&](const std::string &k) {
                 if (k == "condition") op->cond = operator_(false);
                 else if (is_if && k == "if_body") op->if_body = body_or_none();
@@ -234,8 +246,8 @@ class Reader {
 
 class Flattener {
   public:
-    Flattener(Table &t, const wg_args_t *args, uint32_t instance)
-        : t_(t), args_(args), inst_(instance) {}
+    Flattener(Table &t, const wg_args_t *args, uint32_t instance, uint32_t num_ops, uint64_t roll_backs)
+        : t_(t), args_(args), inst_(instance), roll_backs_(roll_backs), size_memo_(num_ops, kUnknown) {}
 
     // Appends the states of one instance (root .. END) and returns its start state.
     uint32_t run(const Op *root) {
@@ -263,7 +275,9 @@ class Flattener {
   private:
     Table &t_; const wg_args_t *args_; uint32_t inst_; uint32_t end_ = 0, n_leaves_ = 0;
     std::vector<uint32_t> eos_exits_;
-    std::unordered_map<const Op *, uint32_t> size_memo_;
+    static constexpr uint32_t kUnknown = 0xFFFFFFFFu;
+    uint64_t roll_backs_;
+    std::vector<uint32_t> size_memo_;                // by operator number
 
     const uint8_t *arg(const std::string &name, uint64_t &len) const {
         if (args_)
@@ -271,10 +285,10 @@ class Flattener {
                 if (name == args_->names[a]) { len = args_->lens[a]; return args_->data[a]; }
         throw ParseError("unbound argument $" + name);
     }
-    std::string literal(const Op *w) const {
-        if (w->hole.empty()) return w->bytes;
-        uint64_t len; const uint8_t *d = arg(w->hole, len);
-        return std::string(reinterpret_cast<const char *>(d), len);
+    const uint8_t *literal(const Op *w, uint64_t &len) const {
+        if (!w->hole.empty()) return arg(w->hole, len);
+        len = w->bytes.size();
+        return reinterpret_cast<const uint8_t *>(w->bytes.data());
     }
     SymbolSet resolve(const SetExpr &e) const {
         SymbolSet s = e.fixed;
@@ -287,18 +301,17 @@ class Flattener {
     // number of leaf states an operator occupies
     uint32_t leaves(const Op *op) {
         if (!op) return 0;
-        auto it = size_memo_.find(op);
-        if (it != size_memo_.end()) return it->second;
+        if (size_memo_[op->number] != kUnknown) return size_memo_[op->number];
         uint32_t n = 0;
         switch (op->kind) {
         case Op::SEQ: for (auto &k : op->kids) n += leaves(k.get()); break;
-        case Op::WRITE: n = static_cast<uint32_t>(literal(op).size()); break;
+        case Op::WRITE: { uint64_t len; literal(op, len); n = static_cast<uint32_t>(len); break; }
         case Op::WAIT: n = 1 + leaves(op->body.get()); break;
         case Op::COND: n = 1; break;
         case Op::IFELSE: n = 1 + leaves(op->if_body.get()) + leaves(op->else_body.get()); break;
         case Op::DOWHILE: n = leaves(op->body.get()) + 1; break;
         }
-        size_memo_[op] = n;
+        size_memo_[op->number] = n;
         return n;
     }
     // Pre-order numbering puts the first executed leaf of a non-empty operator at its
@@ -317,8 +330,7 @@ class Flattener {
         class_ids_[c] = id;
         return id;
     }
-    void checkpoint(uint32_t sid, uint32_t kind, const SetExpr &allow_e, const SetExpr &denies_e,
-                    const SetExpr &a_e, const SetExpr &b_e, uint32_t ta, uint32_t tb, uint32_t max) {
+    Op::Bound bind_sets(const SetExpr &allow_e, const SetExpr &denies_e, const SetExpr &a_e, const SetExpr &b_e) {
         SymbolSet allow{};
         if (denies_e.present) {
             SymbolSet d = resolve(denies_e);
@@ -331,15 +343,25 @@ class Flattener {
             if (a[x] && b[x]) throw ParseError("true_waits and false_waits overlap");
         if (allow[kSymEos] && !a[kSymEos] && !b[kSymEos])
             throw ParseError("<eos> in allow but in no wait set");
+        return Op::Bound{roll_backs_, class_table(allow, a, b), a[kSymEos], b[kSymEos]};
+    }
+    // owner: the WAIT or COND that the sets belong to.
+    void checkpoint(const Op *owner, uint32_t sid, uint32_t kind, const SetExpr &allow_e, const SetExpr &denies_e,
+                    const SetExpr &a_e, const SetExpr &b_e, uint32_t ta, uint32_t tb, uint32_t max) {
+        Op::Bound s = owner->bound;
+        if (s.roll_backs != roll_backs_) {
+            s = bind_sets(allow_e, denies_e, a_e, b_e);
+            if (allow_e.holes.empty() && denies_e.holes.empty() && a_e.holes.empty() && b_e.holes.empty()) owner->bound = s;
+        }
         StateDesc &d = t_.states[sid];
         d = StateDesc{};
         d.kind_byte = kind;
         d.next_a = ta; d.next_b = tb;
         d.max = max;
-        d.cls = class_table(allow, a, b);
+        d.cls = s.cls;
         d.eos_next = WG_SID_ERROR;
-        if (a[kSymEos] || b[kSymEos]) {
-            if ((a[kSymEos] ? ta : tb) != end_)
+        if (s.eos_a || s.eos_b) {
+            if ((s.eos_a ? ta : tb) != end_)
                 throw ParseError("operators follow an exit taken on <eos>");
             eos_exits_.push_back(sid);
         }
@@ -349,21 +371,22 @@ class Flattener {
         static const SetExpr none{};
         switch (op->kind) {
         case Op::WRITE: {
-            std::string b = literal(op);
-            for (size_t k = 0; k < b.size(); k++) {
+            uint64_t n;
+            const uint8_t *b = literal(op, n);
+            for (size_t k = 0; k < n; k++) {
                 StateDesc &d = t_.states[base + k];
                 d = StateDesc{};
-                d.kind_byte = WG_KIND_LIT | (static_cast<uint32_t>(static_cast<uint8_t>(b[k])) << 8);
-                d.next_a = (k + 1 < b.size()) ? base + static_cast<uint32_t>(k) + 1 : cont;
+                d.kind_byte = WG_KIND_LIT | (static_cast<uint32_t>(b[k]) << 8);
+                d.next_a = (k + 1 < n) ? base + static_cast<uint32_t>(k) + 1 : cont;
                 d.next_b = WG_SID_ERROR; d.eos_next = WG_SID_ERROR; d.max = WG_UNBOUNDED;
-                d.run = static_cast<uint32_t>(b.size() - k);
+                d.run = static_cast<uint32_t>(n - k);
                 d.cls = cont;                         // LIT states reuse cls: successor of the whole run
-                t_.lit[base + k] = static_cast<uint8_t>(b[k]);
+                t_.lit[base + k] = b[k];
             }
             break;
         }
         case Op::WAIT:
-            checkpoint(base, WG_KIND_WAIT, op->allow, op->denies, op->wait, none,
+            checkpoint(op, base, WG_KIND_WAIT, op->allow, op->denies, op->wait, none,
                        entry(op->body.get(), base + 1, cont), WG_SID_ERROR,
                        op->bounded ? op->max : WG_UNBOUNDED);
             emit(op->body.get(), base + 1, cont);
@@ -383,7 +406,7 @@ class Flattener {
         }
         case Op::IFELSE: {
             uint32_t ib = base + 1, eb = ib + leaves(op->if_body.get());
-            checkpoint(base, WG_KIND_COND, op->cond->allow, none, op->cond->twait, op->cond->fwait,
+            checkpoint(op->cond.get(), base, WG_KIND_COND, op->cond->allow, none, op->cond->twait, op->cond->fwait,
                        entry(op->if_body.get(), ib, cont), entry(op->else_body.get(), eb, cont),
                        WG_UNBOUNDED);
             emit(op->if_body.get(), ib, cont);
@@ -392,7 +415,7 @@ class Flattener {
         }
         case Op::DOWHILE: {
             uint32_t c = base + leaves(op->body.get());
-            checkpoint(c, WG_KIND_COND, op->cond->allow, none, op->cond->twait, op->cond->fwait,
+            checkpoint(op->cond.get(), c, WG_KIND_COND, op->cond->allow, none, op->cond->twait, op->cond->fwait,
                        entry(op->body.get(), base, c), cont, WG_UNBOUNDED);
             emit(op->body.get(), base, c);
             break;
@@ -407,13 +430,16 @@ class Flattener {
 }  // namespace
 
 struct LoweringState {
-    std::unordered_map<std::string, std::unique_ptr<Op>> parsed;     // static structures, by text
+    struct Tree { std::unique_ptr<Op> root; uint32_t num_ops; };
+    std::unordered_map<std::string, Tree> parsed;                    // static structures, by text
+    uint64_t roll_backs = 0;                          // class ids handed out before the last one may be another set's now
     std::map<std::array<uint8_t, 256>, uint32_t> class_ids;
     // Instances seen so far by the shape of their lowered states (state ids taken relative to the
     // instance's first state): the first state of the first instance of each shape.  A later
     // instance of the same shape -- the same structure instantiated with the same arguments --
     // has, state for state, the same masks, so its states share that instance's cache keys.
-    std::unordered_map<std::string, uint32_t> shapes;
+    // By a hash of the shape; the shape itself is in the table.
+    std::unordered_multimap<uint64_t, uint32_t> shapes;
     // WG_SHARE_STATES: states by what they and the states ahead of them do with bytes.  `own_part`
     // numbers the tuples {kind and literal byte, class table, bound, EOS accepted} in the order
     // they are first seen, `levels` the tuples {level, the state's own part, the numbers of its
@@ -458,20 +484,31 @@ struct LoweringState {
 };
 
 namespace {
-// The states [first, end] of one instance as bytes that do not depend on where the instance lies
-// in the table.
-std::string shape_of(const Table &t, uint32_t first, uint32_t end) {
-    std::string out;
-    out.reserve((size_t)(end - first + 1) * 29);
+// A state of an instance that begins at `first`, as words that do not depend on where that is.
+std::array<uint32_t, 7> relative(const StateDesc &d, uint32_t first) {
     auto rel = [&](uint32_t sid) { return sid == WG_SID_ERROR || sid == WG_SID_FINAL ? sid : sid - first + 1u; };
-    auto put = [&](uint32_t x) { out.append(reinterpret_cast<const char *>(&x), 4); };
+    const bool lit = (d.kind_byte & 0xFFu) == WG_KIND_LIT;
+    return {d.kind_byte, rel(d.next_a), rel(d.next_b), rel(d.eos_next), lit ? rel(d.cls) : d.cls, d.max, d.run};
+}
+uint64_t shape_hash(const Table &t, uint32_t first, uint32_t end) {
+    uint64_t h = end - first;
     for (uint32_t s = first; s <= end; s++) {
-        const StateDesc &d = t.states[s];
-        const bool lit = (d.kind_byte & 0xFFu) == WG_KIND_LIT;
-        put(d.kind_byte); put(rel(d.next_a)); put(rel(d.next_b)); put(rel(d.eos_next));
-        put(lit ? rel(d.cls) : d.cls); put(d.max); put(d.run);
+        const auto x = relative(t.states[s], first);
+        h = (h ^ ((uint64_t)x[0] << 32 | x[1])) * 0x9E3779B97F4A7C15ull;
+        h ^= h >> 32;
+        h = (h ^ ((uint64_t)x[2] << 32 | x[3])) * 0xC2B2AE3D27D4EB4Full;
+        h ^= h >> 32;
+        h = (h ^ ((uint64_t)x[4] << 32 | x[5])) * 0x165667B19E3779F9ull;
+        h ^= h >> 32;
+        h += x[6];
     }
-    return out;
+    return h;
+}
+// (only the last state of an instance is its END, so equal states make equally long instances)
+bool same_shape(const Table &t, uint32_t first, uint32_t end, uint32_t twin) {
+    for (uint32_t s = first; s <= end; s++)
+        if (relative(t.states[s], first) != relative(t.states[twin + (s - first)], twin)) return false;
+    return true;
 }
 }  // namespace
 
@@ -504,6 +541,7 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
         t.states.resize(n_states0); t.tmpl.resize(n_states0); t.lit.resize(n_states0);
         t.key_count.resize(n_states0); t.start.resize(n_start0); t.classes.resize(n_classes0 * 256);
         t.n_keys = n_keys0;
+        st_->roll_backs++;
         for (auto it = st_->class_ids.begin(); it != st_->class_ids.end();)
             it = it->second >= n_classes0 ? st_->class_ids.erase(it) : std::next(it);
     };
@@ -514,12 +552,13 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
             auto it = st_->parsed.find(text);
             if (it == st_->parsed.end()) {
                 Reader r(templates[i]);
-                it = st_->parsed.emplace(text, r.parse_all()).first;
+                auto root = r.parse_all();
+                it = st_->parsed.emplace(text, LoweringState::Tree{std::move(root), r.num_ops()}).first;
             }
-            Flattener f(t, args ? &args[i] : nullptr, static_cast<uint32_t>(t.start.size()));
+            Flattener f(t, args ? &args[i] : nullptr, static_cast<uint32_t>(t.start.size()), it->second.num_ops, st_->roll_backs);
             f.class_ids_.swap(st_->class_ids);
             uint32_t start;
-            try { start = f.run(it->second.get()); }
+            try { start = f.run(it->second.root.get()); }
             catch (...) { f.class_ids_.swap(st_->class_ids); throw; }
             f.class_ids_.swap(st_->class_ids);
             uint32_t after_eos = (t.flags & WG_EOS_RESTART) ? start : WG_SID_FINAL;
@@ -541,8 +580,7 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
     // then serves every request of that shape from one set of rows.
     t.key_count.resize(t.states.size());
     uint32_t k = n_keys0;
-    std::vector<std::string> new_shapes;                              // to take back if memory runs out half way
-    std::vector<uint32_t> new_sigs;
+    std::vector<uint32_t> new_sigs;                                   // to take back if memory runs out half way
     try {
         for (const auto &span : spans) {
             const uint32_t first = span.first, end = span.second;
@@ -551,15 +589,15 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
                 const bool bounded = (d.kind_byte & 0xFF) == WG_KIND_WAIT && d.max != WG_UNBOUNDED;
                 t.key_count[s] = bounded ? t.lmax + 1 : 1;
             }
-            std::string shape = shape_of(t, first, end);
-            const auto seen = st_->shapes.find(shape);
-            if (seen != st_->shapes.end()) {
-                const uint32_t twin = seen->second;
+            const uint64_t shape = shape_hash(t, first, end);
+            auto seen = st_->shapes.equal_range(shape);
+            while (seen.first != seen.second && !same_shape(t, first, end, seen.first->second)) ++seen.first;
+            if (seen.first != seen.second) {
+                const uint32_t twin = seen.first->second;
                 for (uint32_t s = first; s <= end; s++) t.states[s].key_base = t.states[twin + (s - first)].key_base;
                 continue;
             }
-            new_shapes.push_back(shape);
-            st_->shapes.emplace(std::move(shape), first);
+            st_->shapes.emplace(shape, first);
             auto inside = [&](uint32_t sid) { return sid == WG_SID_ERROR || sid == WG_SID_FINAL || (sid >= first && sid <= end); };
             bool closed = true;                      // (every successor lies in the instance itself)
             for (uint32_t s = first; s <= end; s++) closed = closed && inside(t.states[s].next_a) && inside(t.states[s].next_b);
@@ -604,7 +642,8 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
             }
         }
     } catch (...) {
-        for (const std::string &sh : new_shapes) st_->shapes.erase(sh);
+        for (auto it = st_->shapes.begin(); it != st_->shapes.end();)
+            it = it->second >= n_states0 ? st_->shapes.erase(it) : std::next(it);
         for (uint32_t sig : new_sigs) st_->sig_key.erase(sig);
         roll_back();
         throw;
