@@ -52,6 +52,7 @@ struct wg_handle_s {
     uint32_t up_states = 0, up_classes = 0;           // how much of the host table is on the device
     uint32_t max_batch = 0;
     uint32_t n_cu = 256;
+    uint8_t *stage = nullptr;                  // pinned host memory, kStageBytes
     uint32_t *d_free_rows = nullptr;
     // kernel timing: events recorded since the last wg_profile_read
     bool profiling = false;
@@ -66,6 +67,7 @@ namespace {
 
 int fail(int code, const std::string &msg) { set_last_error(msg); return code; }
 
+constexpr size_t kStageBytes = 1u << 20;      // additions up to this size take the pinned memory that the handle keeps
 constexpr uint32_t kDefaultBatch = 1024;   // requests per call a handle has room for after wg_compile
 
 #define WG_HIP(call)                                                                          \
@@ -165,22 +167,35 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         if (rc != WG_OK) return rc;
         h->cap_classes = nc;
     }
-    const bool new_states = n_states > h->up_states, new_classes = n_classes > h->up_classes;
-    if (new_states) {
-        const uint32_t a = h->up_states, n = n_states - a;
-        WG_HIP(hipMemcpyAsync(h->d_states + a, t.states.data() + a, n * sizeof(StateDesc), hipMemcpyHostToDevice, s));
-        WG_HIP(hipMemcpyAsync(h->d_lit + a, t.lit.data() + a, n, hipMemcpyHostToDevice, s));
-    }
-    if (new_classes) {
-        const uint32_t a = h->up_classes, n = n_classes - a;
-        WG_HIP(hipMemcpyAsync(h->d_classes + (size_t)a * 256, t.classes.data() + (size_t)a * 256, (size_t)n * 256,
-                              hipMemcpyHostToDevice, s));
+    if (n_states > h->up_states || n_classes > h->up_classes) {
+        const uint32_t s0 = h->up_states, ns = n_states - s0, c0 = h->up_classes, nc = n_classes - c0;
         h->plans.resize(n_classes);
-        for (uint32_t c = a; c < n_classes; c++) h->plans[c] = class_plan_of(t.classes.data() + (size_t)c * 256);
-        WG_HIP(hipMemcpyAsync(h->d_plans + a, h->plans.data() + a, n * sizeof(ClassPlan), hipMemcpyHostToDevice, s));
-    }
-    if (new_states || new_classes) {
-        // the copies read pageable host memory that a later append may move
+        for (uint32_t c = c0; c < n_classes; c++) h->plans[c] = class_plan_of(t.classes.data() + (size_t)c * 256);
+        struct { void *dst; const void *src; size_t bytes; } part[4] = {
+            {h->d_states + s0, t.states.data() + s0, ns * sizeof(StateDesc)},
+            {h->d_lit + s0, t.lit.data() + s0, ns},
+            {h->d_classes + (size_t)c0 * 256, t.classes.data() + (size_t)c0 * 256, (size_t)nc * 256},
+            {h->d_plans + c0, h->plans.data() + c0, nc * sizeof(ClassPlan)}};
+        size_t all = 0;
+        for (const auto &p : part) all += p.bytes ? p.bytes + 32u : 0u;
+        if (all <= kStageBytes) {
+            AppendSlices slices{};
+            uint32_t n = 0;
+            size_t at = 0;
+            for (const auto &p : part) {
+                if (!p.bytes) continue;
+                at = (at + 15u) & ~(size_t)15u;
+                uint8_t *src = h->stage + at + (reinterpret_cast<uintptr_t>(p.dst) & 15u);
+                std::memcpy(src, p.src, p.bytes);
+                slices.slice[n++] = AppendSlice{static_cast<uint8_t *>(p.dst), src, (uint32_t)p.bytes};
+                at = (size_t)(src - h->stage) + p.bytes;
+            }
+            WG_HIP(launch_append(slices, n, s));
+        } else {
+            for (const auto &p : part)
+                if (p.bytes) WG_HIP(hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyHostToDevice, s));
+        }
+        // (what is copied from may move or be filled again by a later append)
         WG_HIP(hipStreamSynchronize(s));
         h->up_states = n_states;
         h->up_classes = n_classes;
@@ -387,6 +402,7 @@ void wg_destroy(wg_handle_t h) {
     (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
     (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
+    if (h->stage) (void)hipHostFree(h->stage);
     (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_all); (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
@@ -446,6 +462,7 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     int cus = 0;
     WG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, vocab->device));
     if (cus > 0) h->n_cu = (uint32_t)cus;
+    WG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->stage), kStageBytes, hipHostMallocDefault));
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
     h->dc.direct = t.n_keys <= h->dc.cap_rows;

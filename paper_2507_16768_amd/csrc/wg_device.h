@@ -125,6 +125,9 @@ hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const Device
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
                        void *logits, int dtype, int64_t logits_stride,
                        uint32_t n_cu, hipStream_t s, hipEvent_t *ev);
+struct AppendSlice { uint8_t *dst; const uint8_t *src; uint32_t bytes; };
+struct AppendSlices { AppendSlice slice[4]; };
+hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s);
 hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s);
 // Dynamic LDS of the rows kernel for this vocabulary; with its static part it stays within the 64 KB
 // a kernel gets without asking.

@@ -1091,6 +1091,29 @@ hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const Device
     return hipGetLastError();
 }
 
+// New states and classes from pinned host memory to the ends of the device tables, all slices by one
+// launch (the copies of two to four slices from pageable memory took 25 us to enqueue and wait for).  A
+// slice lies in the staging memory as it does in the device's, modulo 16 bytes.
+__global__ void __launch_bounds__(256) append_kernel(AppendSlices a)
+{
+    const AppendSlice s = a.slice[blockIdx.y];
+    const uint32_t skew = (uint32_t)(reinterpret_cast<uintptr_t>(s.dst) & 15u), blocks = (skew + s.bytes + 15u) / 16u;
+    for (uint32_t q = blockIdx.x * 256u + threadIdx.x; q < blocks; q += gridDim.x * 256u) {
+        const uint32_t lo = q ? q * 16u - skew : 0u, hi = q * 16u + 16u - skew < s.bytes ? q * 16u + 16u - skew : s.bytes;
+        if (hi - lo == 16u) *reinterpret_cast<uint4 *>(s.dst + lo) = *reinterpret_cast<const uint4 *>(s.src + lo);
+        else for (uint32_t i = lo; i < hi; i++) s.dst[i] = s.src[i];
+    }
+}
+
+hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s)
+{
+    uint32_t most = 0;
+    for (uint32_t i = 0; i < n; i++) most = a.slice[i].bytes > most ? a.slice[i].bytes : most;
+    const uint32_t blocks = cdiv(most / 16u + 2u, 256u);
+    append_kernel<<<dim3(blocks < 256u ? blocks : 256u, n), 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s)
 {
     free_rows_kernel<<<1, 1024, 0, s>>>(Cc, n_keys, free_rows);

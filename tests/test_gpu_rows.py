@@ -154,6 +154,32 @@ def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
     assert h.error_count() == 0 and n["lookups"] == 4 * B and n["hits"] + n["builds"] <= 4 * B
 
 
+def test_additions_of_every_size(torch_cuda):
+    """Slices of 1 to 40 states at every offset, with and without new class tables, and one above the
+    handle's pinned memory: the states that arrive are those of a compilation at once."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    base = ws.make_workload(2, V=1031, B=1, steps=1)
+    rng = np.random.default_rng(7)
+    text = ["Sequence(Write($x))", 'Sequence(Write($x), Wait(allow=$x, wait={\\x00}))']
+    sizes = list(range(1, 41)) + [60000, 3, 17]
+    texts = [text[n % 2 if n < 100 else 0] for n in sizes]
+    args = [{"x": bytes(rng.integers(1, 256, n, dtype=np.uint8))} for n in sizes]
+    w = dataclasses.replace(base, texts=texts, args=args, B=len(texts), request_template=np.arange(len(texts), dtype=np.int64))
+    o = H.make_oracle(w)
+    h = wg.Handle(texts[:1], args[:1], wg.Vocab(w.vocab.bytes, w.vocab.offsets, w.vocab.eos_id), flags=wg.EOS_RESTART)
+    for i in range(1, len(texts)):
+        first = h.num_states
+        new = h.add_instances(texts[i:i + 1], args[i:i + 1])
+        assert int(new[0, 0]) == o.start_state(i)
+        st = np.arange(first, h.num_states, dtype=np.uint32)[-900:]
+        st = np.stack([st, np.zeros_like(st)], 1)
+        mask = torch.empty((len(st), h.W), dtype=torch.int32, device="cuda")
+        h.fill_masks(H.dev_states(st), mask)
+        assert (H.host_mask(mask) == o.fill_masks(st)).all(), i
+    assert h.num_states == o.num_states
+
+
 @pytest.mark.parametrize("dtype,stride_pad", [("bf16", 0), ("f32", 5)])
 def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
     """wg_decode_step with logits beyond the last-level cache against the separate calls (which the
