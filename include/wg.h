@@ -349,8 +349,10 @@ const char *wg_last_error(void);
  * synchronises, adds up the elapsed times since the last read and resets the record. */
 typedef struct {
     uint64_t fill_calls, advance_calls;
-    double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations (a fill has a
-                                                                     lookup and a build kernel; scan and gather stay 0) */
+    double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations: a fill has a lookup kernel and
+                                                                     one that makes or copies the rows (build_ms); a small
+                                                                     batch has the second alone, which then does the lookups,
+                                                                     and adds nothing to lookup_ms.  scan and gather stay 0 */
     uint64_t apply_calls;
     double apply_ms;
 } wg_profile_t;

@@ -56,9 +56,8 @@ struct wg_handle_s {
     uint32_t *d_free_rows = nullptr;
     // kernel timing: events recorded since the last wg_profile_read
     bool profiling = false;
-    std::vector<hipEvent_t> fill_events;       // 4 per wg_fill_masks call: begin / end of each kernel
-    std::vector<hipEvent_t> advance_events;    // 2 per wg_advance call
-    std::vector<hipEvent_t> apply_events;      // 2 per wg_profile_apply_mask call
+    // (begin / end pairs; a fill that does its lookups in its one kernel has no pair in lookup_events)
+    std::vector<hipEvent_t> lookup_events, rows_events, advance_events, apply_events;
     std::vector<hipEvent_t> spare_events;
     wg_handle_s(uint32_t flags, uint32_t lmax) : low(flags, lmax) {}
 };
@@ -84,16 +83,41 @@ template <class T> hipError_t upload(T **dst, const T *src, size_t n) {
     return n ? hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice) : hipSuccess;
 }
 
-hipEvent_t take_event(wg_handle_s *h) {
-    if (!h->spare_events.empty()) {
-        hipEvent_t e = h->spare_events.back();
-        h->spare_events.pop_back();
+// A kernel's pair of timing events: taken before the launch, entered into the record once the kernel is
+// launched (an event that no launch has recorded has no time to read), given back otherwise.
+class Timing {
+  public:
+    Timing(wg_handle_s *h, bool on, std::vector<hipEvent_t> *record) : h_(h), record_(on && h->profiling ? record : nullptr) {
+        if (!record_) return;
+        try {                                          // room for the pair here and where it is given back, so that nothing throws later
+            for (auto *v : {record_, &h->spare_events})
+                if (v->capacity() < v->size() + 2) v->reserve(2 * v->size() + 64);
+        } catch (const std::bad_alloc &) {
+            record_ = nullptr;                         // not timed
+            return;
+        }
+        for (hipEvent_t &e : ev_) {
+            e = nullptr;
+            if (!h->spare_events.empty()) { e = h->spare_events.back(); h->spare_events.pop_back(); }
+            else (void)hipEventCreate(&e);
+        }
+    }
+    ~Timing() {
+        if (record_) record_->insert(record_->end(), ev_, ev_ + 2);
+    }
+    Timing(const Timing &) = delete;
+    Timing &operator=(const Timing &) = delete;
+    hipEvent_t *events() { return record_ ? ev_ : nullptr; }
+    hipError_t launched(hipError_t e) {
+        if (e != hipSuccess && record_) record_ = &h_->spare_events;
         return e;
     }
-    hipEvent_t e = nullptr;
-    (void)hipEventCreate(&e);
-    return e;
-}
+
+  private:
+    wg_handle_s *h_;
+    std::vector<hipEvent_t> *record_;
+    hipEvent_t ev_[2];
+};
 
 // Room for the per-call lists of a batch of B requests.  Never called from the step path: the
 // device is synchronised and the lists are allocated anew.
@@ -405,7 +429,7 @@ void wg_destroy(wg_handle_t h) {
     if (h->stage) (void)hipHostFree(h->stage);
     (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_all); (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
-    for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events, &h->spare_events})
+    for (auto *v : {&h->lookup_events, &h->rows_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
     delete h;
 }
@@ -535,10 +559,12 @@ int fill(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t 
     if (B > h->max_batch)
         return fail(WG_ERR_INVALID, std::string(who) + ": B = " + std::to_string(B) + " is above the " +
                                         std::to_string(h->max_batch) + " requests the handle has room for (wg_reserve_batch)");
-    hipEvent_t ev[4];
-    if (h->profiling) for (auto &e : ev) { e = take_event(h); h->fill_events.push_back(e); }
-    WG_HIP(launch_fill(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, d_bitmask, d_logits, dtype,
-                       logits_stride, h->n_cu, static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
+    const FillPlan plan = plan_fill(h->vocab->dv, h->dc, B, dtype, h->n_cu);
+    Timing lookup(h, !plan.one_kernel, &h->lookup_events), rows(h, true, &h->rows_events);
+    const hipError_t e = launch_fill(plan, h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, d_bitmask, d_logits, dtype, logits_stride,
+                                     static_cast<hipStream_t>(stream), lookup.events(), rows.events());
+    (void)lookup.launched(e);
+    WG_HIP(rows.launched(e));
     return WG_OK;
 }
 }  // namespace
@@ -585,9 +611,8 @@ int wg_profile_apply_mask(wg_handle_t h, void *d_logits, wg_dtype_t dtype, uint3
     if (B == 0 || V == 0 || B > kMaxBatch) return fail(WG_ERR_INVALID, "wg_profile_apply_mask: bad batch or vocabulary size");
     if (dtype != WG_F32 && dtype != WG_BF16) return fail(WG_ERR_INVALID, "wg_profile_apply_mask: unknown dtype");
     if (row_stride_elems < (int64_t)V) return fail(WG_ERR_INVALID, "wg_profile_apply_mask: row stride smaller than V");
-    hipEvent_t ev[2];
-    for (auto &e : ev) { e = take_event(h); h->apply_events.push_back(e); }
-    WG_HIP(launch_apply(d_logits, dtype, B, V, row_stride_elems, d_bitmask, static_cast<hipStream_t>(stream), ev));
+    Timing apply(h, true, &h->apply_events);
+    WG_HIP(apply.launched(launch_apply(d_logits, dtype, B, V, row_stride_elems, d_bitmask, static_cast<hipStream_t>(stream), apply.events())));
     return WG_OK;
 }
 
@@ -660,10 +685,8 @@ int wg_masked_topk_static(const void *d_logits, wg_dtype_t dtype, uint32_t B, ui
 int wg_advance(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t B, void *stream) {
     if (!h || !d_states || !d_tokens) return fail(WG_ERR_INVALID, "wg_advance: null argument");
     if (B == 0) return fail(WG_ERR_INVALID, "wg_advance: B is 0");
-    hipEvent_t ev[2];
-    if (h->profiling) for (auto &e : ev) { e = take_event(h); h->advance_events.push_back(e); }
-    WG_HIP(launch_advance(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B,
-                          static_cast<hipStream_t>(stream), h->profiling ? ev : nullptr));
+    Timing advance(h, true, &h->advance_events);
+    WG_HIP(advance.launched(launch_advance(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, static_cast<hipStream_t>(stream), advance.events())));
     return WG_OK;
 }
 
@@ -725,27 +748,23 @@ int wg_profile_read(wg_handle_t h, wg_profile_t *host_out) {
     if (!h || !host_out) return fail(WG_ERR_INVALID, "wg_profile_read: null argument");
     WG_HIP(hipDeviceSynchronize());
     wg_profile_t p{};
-    auto span = [](hipEvent_t a, hipEvent_t b) {
-        float ms = 0.f;
-        return (a && b && hipEventElapsedTime(&ms, a, b) == hipSuccess) ? (double)ms : 0.0;
+    // milliseconds of a record's pairs; its events are free for use again
+    auto total = [&](std::vector<hipEvent_t> &v, uint64_t *calls) {
+        double sum = 0.0;
+        for (size_t i = 0; i + 1 < v.size(); i += 2) {
+            float ms = 0.f;
+            if (v[i] && v[i + 1] && hipEventElapsedTime(&ms, v[i], v[i + 1]) == hipSuccess) sum += (double)ms;
+            else (void)hipGetLastError();              // (nobody else's error)
+        }
+        if (calls) *calls = v.size() / 2;
+        h->spare_events.insert(h->spare_events.end(), v.begin(), v.end());
+        v.clear();
+        return sum;
     };
-    for (size_t i = 0; i + 3 < h->fill_events.size(); i += 4) {
-        hipEvent_t *e = &h->fill_events[i];
-        p.lookup_ms += span(e[0], e[1]); p.build_ms += span(e[2], e[3]);
-        p.fill_calls++;
-    }
-    for (size_t i = 0; i + 1 < h->advance_events.size(); i += 2) {
-        p.advance_ms += span(h->advance_events[i], h->advance_events[i + 1]);
-        p.advance_calls++;
-    }
-    for (size_t i = 0; i + 1 < h->apply_events.size(); i += 2) {
-        p.apply_ms += span(h->apply_events[i], h->apply_events[i + 1]);
-        p.apply_calls++;
-    }
-    for (auto *v : {&h->fill_events, &h->advance_events, &h->apply_events}) {
-        h->spare_events.insert(h->spare_events.end(), v->begin(), v->end());
-        v->clear();
-    }
+    p.lookup_ms = total(h->lookup_events, nullptr);
+    p.build_ms = total(h->rows_events, &p.fill_calls);
+    p.advance_ms = total(h->advance_events, &p.advance_calls);
+    p.apply_ms = total(h->apply_events, &p.apply_calls);
     *host_out = p;
     return WG_OK;
 }

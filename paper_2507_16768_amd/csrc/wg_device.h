@@ -118,13 +118,17 @@ struct DeviceCache {
     uint32_t epoch;              // cache generation of this call
 };
 
-// ev, when not null, holds four events: a begin / end pair for each of the two kernels of a fill.
-// With tokens != nullptr the states are first advanced by them (in place, in the lookup kernel);
-// with logits != nullptr the mask is also applied to them (in the rows kernel).
-hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
+// How a fill of B requests is launched: workgroups per row, and whether they do the lookups themselves
+// (one kernel) or find them done by a kernel before theirs.
+struct FillPlan { uint32_t parts; bool one_kernel; };
+FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int dtype, uint32_t n_cu);
+// lookup_ev, rows_ev: a begin / end pair of events for each kernel that the plan has, or null.
+// With tokens != nullptr the states are first advanced by them (in place, with the lookup); with
+// logits != nullptr the mask is also applied to them (in the rows kernel).
+hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
                        void *logits, int dtype, int64_t logits_stride,
-                       uint32_t n_cu, hipStream_t s, hipEvent_t *ev);
+                       hipStream_t s, hipEvent_t *lookup_ev, hipEvent_t *rows_ev);
 struct AppendSlice { uint8_t *dst; const uint8_t *src; uint32_t bytes; };
 struct AppendSlices { AppendSlice slice[4]; };
 hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s);

@@ -1060,20 +1060,28 @@ uint32_t rows_lds_bytes(const DeviceVocab &Vc)
     return 2u * (((most + 3u) & ~3u) + 4u) * 4u;
 }
 
-hipError_t launch_fill(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                       wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
-                       void *logits, int dtype, int64_t logits_stride, uint32_t n_cu, hipStream_t s, hipEvent_t *ev)
+FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int dtype, uint32_t n_cu)
 {
-    const dim3 g(row_parts(Vc.V, most_parts(Vc.V, B, n_cu)), B);
-    const uint32_t lds = rows_lds_bytes(Vc);
+    FillPlan p;
+    p.parts = row_parts(Vc.V, most_parts(Vc.V, B, n_cu));
     // One kernel up to a workgroup per compute unit: there the launch it saves (10 to 13 us of 70 to 85 a
     // pass of 8 cached steps, B <= 8, 151936 tokens) outweighs the lookup that every workgroup of a row
     // repeats; with four per unit it is 199 us instead of 190 where the rows are made, and with eight 278
     // instead of 232.
-    const bool whole = Cc.direct && (uint64_t)B * g.x <= n_cu && !by_lines(dtype, B, Vc.V);
-    if (!whole) launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
-    hipEvent_t *re = ev ? ev + 2 : nullptr;
-    auto rows = [&](auto kernel, auto *x) { launch(kernel, g, dim3(kRowThreads), lds, s, re, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
+    p.one_kernel = Cc.direct && (uint64_t)B * p.parts <= n_cu && !by_lines(dtype, B, Vc.V);
+    return p;
+}
+
+hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
+                       wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
+                       void *logits, int dtype, int64_t logits_stride,
+                       hipStream_t s, hipEvent_t *lookup_ev, hipEvent_t *rows_ev)
+{
+    const dim3 g(plan.parts, B);
+    const uint32_t lds = rows_lds_bytes(Vc);
+    const bool whole = plan.one_kernel;
+    if (!whole) launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, lookup_ev, T, Vc, Cc, states, tokens, B);
+    auto rows = [&](auto kernel, auto *x) { launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
     if (!logits) {
         if (whole) rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr);
         else rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);

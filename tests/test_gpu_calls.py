@@ -1,0 +1,54 @@
+"""GPU tests of what the per-step calls do beside their results: kernel timing and error reports."""
+import numpy as np
+import pytest
+
+import wg_synth as ws
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2507_16768_amd as wg
+    wg.load_library()
+    return torch
+
+
+def _batch(torch, B, V=20000):
+    w = ws.make_workload(4, V=V, B=B, steps=2)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    st = H.dev_states(H.start_states(o, w))
+    return w, o, h, st, torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+
+
+@pytest.mark.parametrize("call", ["fill", "advance_fill", "decode_step"])
+def test_kernel_timing_of_batches_of_one_and_of_two_kernels(torch_cuda, call):
+    """Each kernel that a fill launches is timed, and only those: a small batch (one kernel) after a large
+    one (two), whose events it takes over, adds nothing to the lookup; the calls after a read succeed."""
+    torch = torch_cuda
+    _, _, h, st, mask = _batch(torch, 300)
+    logits = torch.zeros((300, h.V), dtype=torch.bfloat16, device="cuda")
+    tok = torch.full((300,), -1, dtype=torch.int32, device="cuda")
+    h.profile_enable()
+    for B, kernels in ((2, 1), (300, 2), (2, 1), (2, 1)):
+        s, m, x, t = st[:B].clone(), mask[:B], logits[:B], tok[:B]
+        for _ in range(3):
+            if call == "fill":
+                h.fill_masks(s, m)
+            elif call == "advance_fill":
+                h.advance_fill_masks(s, t, m)
+            else:
+                h.decode_step(s, None, m, x)
+        h.advance(s, t)
+        h.profile_apply_mask(x, m)
+        p = h.profile_read()
+        assert (p["fill_calls"], p["advance_calls"], p["apply_calls"]) == (3, 1, 1)
+        assert p["build_ms"] > 0.0 and p["advance_ms"] > 0.0 and p["apply_ms"] > 0.0
+        assert (p["lookup_ms"] > 0.0) == (kernels == 2), (B, p)
+    h.profile_enable(False)
+    h.fill_masks(st, mask)
+    assert h.profile_read()["fill_calls"] == 0
