@@ -14,7 +14,6 @@
 //
 // No MFMA anywhere: the path is byte matching and memory traffic.
 #include <hip/hip_runtime.h>
-#include <hip/hip_ext.h>
 
 #include "wg_device.h"
 
@@ -997,17 +996,6 @@ select_kernel(const uint32_t *__restrict__ bitmask, uint32_t W, const uint64_t *
 
 static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
-// Launches on stream s; with a pair of events the kernel's own begin / end timestamps are
-// recorded into them (hipExtLaunchKernelGGL), which times the kernel without the queue gaps
-// that events recorded between launches would include.
-template <typename K, typename... A>
-static inline void launch(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStream_t s, hipEvent_t *ev,
-                          A... args)
-{
-    if (ev) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, ev[0], ev[1], 0, args...);
-    else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-}
-
 // Logits of more bytes than these are masked by whole lines (see mask_span): 128 bytes are read where a
 // line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
 // depends on how many tokens of a line are disallowed, which the host does not know; the lines lie where
@@ -1080,23 +1068,19 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
     const dim3 g(plan.parts, B);
     const uint32_t lds = rows_lds_bytes(Vc);
     const bool whole = plan.one_kernel;
-    if (!whole) launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, lookup_ev, T, Vc, Cc, states, tokens, B);
-    auto rows = [&](auto kernel, auto *x) { launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
-    if (!logits) {
-        if (whole) rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr);
-        else rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);
-    } else if (dtype == WG_F32) {
-        uint32_t *x = static_cast<uint32_t *>(logits);
-        if (whole) rows(rows_kernel<uint32_t, 1, true>, x);
-        else if (by_lines(dtype, B, Vc.V)) rows(rows_kernel<uint32_t, 2, false>, x);
-        else rows(rows_kernel<uint32_t, 1, false>, x);
-    } else {
-        uint16_t *x = static_cast<uint16_t *>(logits);
-        if (whole) rows(rows_kernel<uint16_t, 1, true>, x);
-        else if (by_lines(dtype, B, Vc.V)) rows(rows_kernel<uint16_t, 2, false>, x);
-        else rows(rows_kernel<uint16_t, 1, false>, x);
+    if (!whole) {
+        const hipError_t e = launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, lookup_ev, T, Vc, Cc, states, tokens, B);
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    auto rows = [&](auto kernel, auto *x) { return launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
+    if (!logits) return whole ? rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr) : rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);
+    const bool lines = by_lines(dtype, B, Vc.V);
+    if (dtype == WG_F32) {
+        uint32_t *x = static_cast<uint32_t *>(logits);
+        return whole ? rows(rows_kernel<uint32_t, 1, true>, x) : lines ? rows(rows_kernel<uint32_t, 2, false>, x) : rows(rows_kernel<uint32_t, 1, false>, x);
+    }
+    uint16_t *x = static_cast<uint16_t *>(logits);
+    return whole ? rows(rows_kernel<uint16_t, 1, true>, x) : lines ? rows(rows_kernel<uint16_t, 2, false>, x) : rows(rows_kernel<uint16_t, 1, false>, x);
 }
 
 // New states and classes from pinned host memory to the ends of the device tables, all slices by one
@@ -1118,14 +1102,12 @@ hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s)
     uint32_t most = 0;
     for (uint32_t i = 0; i < n; i++) most = a.slice[i].bytes > most ? a.slice[i].bytes : most;
     const uint32_t blocks = cdiv(most / 16u + 2u, 256u);
-    append_kernel<<<dim3(blocks < 256u ? blocks : 256u, n), 256, 0, s>>>(a);
-    return hipGetLastError();
+    return launch(append_kernel, dim3(blocks < 256u ? blocks : 256u, n), dim3(256), 0, s, nullptr, a);
 }
 
 hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s)
 {
-    free_rows_kernel<<<1, 1024, 0, s>>>(Cc, n_keys, free_rows);
-    return hipGetLastError();
+    return launch(free_rows_kernel, dim3(1), dim3(1024), 0, s, nullptr, Cc, n_keys, free_rows);
 }
 
 hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
@@ -1135,36 +1117,29 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
     const dim3 g(cdiv(V, kApplyTokens), B);
     if (dtype == WG_F32) {
         uint32_t *x = static_cast<uint32_t *>(logits);
-        if (by_lines(dtype, B, V)) launch(apply_kernel<uint32_t, true>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
-        else launch(apply_kernel<uint32_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
-    } else {
-        uint16_t *x = static_cast<uint16_t *>(logits);
-        if (by_lines(dtype, B, V)) launch(apply_kernel<uint16_t, true>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
-        else launch(apply_kernel<uint16_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
+        return launch(by_lines(dtype, B, V) ? apply_kernel<uint32_t, true> : apply_kernel<uint32_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
     }
-    return hipGetLastError();
+    uint16_t *x = static_cast<uint16_t *>(logits);
+    return launch(by_lines(dtype, B, V) ? apply_kernel<uint16_t, true> : apply_kernel<uint16_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
 }
 
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                           wg_state_t *states, const int32_t *tokens, uint32_t B, hipStream_t s,
                           hipEvent_t *ev)
 {
-    launch(advance_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
-    return hipGetLastError();
+    return launch(advance_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
 }
 
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
                                uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, hipStream_t s)
 {
-    forced_bytes_kernel<<<cdiv(B, 64), 64, 0, s>>>(T, states, B, cap, bytes, lens, end_states);
-    return hipGetLastError();
+    return launch(forced_bytes_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, nullptr, T, states, B, cap, bytes, lens, end_states);
 }
 
 hipError_t launch_select(const uint32_t *bitmask, uint32_t B, uint32_t V, const uint64_t *draws,
                          int32_t *tokens, hipStream_t s)
 {
-    select_kernel<<<B, 256, 0, s>>>(bitmask, (V + 31u) / 32u, draws, tokens);
-    return hipGetLastError();
+    return launch(select_kernel, dim3(B), dim3(256), 0, s, nullptr, bitmask, (V + 31u) / 32u, draws, tokens);
 }
 
 }  // namespace wg

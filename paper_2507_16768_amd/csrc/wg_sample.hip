@@ -646,33 +646,29 @@ hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint3
 {
     const uint32_t W = (V + 31u) / 32u;
     const dim3 g(argmax_parts(B, V), B);
-    if (dtype == WG_F32) masked_argmax_kernel<uint32_t><<<g, kThreads, 0, s>>>(static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask, tokens);
-    else masked_argmax_kernel<uint16_t><<<g, kThreads, 0, s>>>(static_cast<const uint16_t *>(logits), row_stride, V, W, bitmask, tokens);
-    return hipGetLastError();
+    if (dtype == WG_F32) return launch(masked_argmax_kernel<uint32_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask, tokens);
+    return launch(masked_argmax_kernel<uint16_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint16_t *>(logits), row_stride, V, W, bitmask, tokens);
 }
 
 template <typename Elem>
-static void topk(const Elem *logits, uint32_t B, uint32_t V, int64_t row_stride, const uint32_t *bitmask, uint32_t k,
-                 int32_t *ids, Elem *values, Elem ninf, unsigned long long *lists, hipStream_t s)
+static hipError_t topk(const Elem *logits, uint32_t B, uint32_t V, int64_t row_stride, const uint32_t *bitmask, uint32_t k,
+                       int32_t *ids, Elem *values, Elem ninf, unsigned long long *lists, hipStream_t s)
 {
     const uint32_t W = (V + 31u) / 32u;
-    if (topk_by_row(B, (uint64_t)V * sizeof(Elem))) {
-        masked_topk_kernel<Elem><<<B, kThreads, 0, s>>>(logits, row_stride, V, W, bitmask, k, ids, values, ninf);
-        return;
-    }
+    if (topk_by_row(B, (uint64_t)V * sizeof(Elem)))
+        return launch(masked_topk_kernel<Elem>, dim3(B), dim3(kThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, ids, values, ninf);
     const uint32_t n_slices = (V + kTopkSlice - 1u) / kTopkSlice;
-    topk_slice_kernel<Elem><<<dim3(n_slices, B), kSliceThreads, 0, s>>>(logits, row_stride, V, W, bitmask, k, lists);
-    topk_merge_kernel<Elem><<<B, kSliceThreads, 0, s>>>(logits, row_stride, n_slices, k, lists, ids, values, ninf);
+    const hipError_t e = launch(topk_slice_kernel<Elem>, dim3(n_slices, B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, lists);
+    if (e != hipSuccess) return e;
+    return launch(topk_merge_kernel<Elem>, dim3(B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, n_slices, k, lists, ids, values, ninf);
 }
 
 hipError_t launch_masked_topk(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
                               const uint32_t *bitmask, uint32_t k, int32_t *ids, void *values, unsigned long long *lists, hipStream_t s)
 {
     if (dtype == WG_F32)
-        topk<uint32_t>(static_cast<const uint32_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint32_t *>(values), 0xFF800000u, lists, s);
-    else
-        topk<uint16_t>(static_cast<const uint16_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint16_t *>(values), (uint16_t)0xFF80u, lists, s);
-    return hipGetLastError();
+        return topk<uint32_t>(static_cast<const uint32_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint32_t *>(values), 0xFF800000u, lists, s);
+    return topk<uint16_t>(static_cast<const uint16_t *>(logits), B, V, row_stride, bitmask, k, ids, static_cast<uint16_t *>(values), (uint16_t)0xFF80u, lists, s);
 }
 
 }  // namespace wg

@@ -52,3 +52,34 @@ def test_kernel_timing_of_batches_of_one_and_of_two_kernels(torch_cuda, call):
     h.profile_enable(False)
     h.fill_masks(st, mask)
     assert h.profile_read()["fill_calls"] == 0
+
+
+def test_errors_of_other_calls_are_not_reported_as_these(torch_cuda):
+    """A call whose kernels were launched returns WG_OK, also when an earlier HIP call of the thread, made
+    by somebody else, has failed: a caller who takes the step for failed would advance its states twice."""
+    torch = torch_cuda
+    import ctypes
+    import paper_2507_16768_amd as wg
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)                            # the runtime of this process
+    w, o, h, st, mask = _batch(torch, 8)
+    logits = torch.zeros((8, h.V), dtype=torch.float32, device="cuda")
+    tok = torch.empty(8, dtype=torch.int32, device="cuda")
+    ids, vals = torch.empty((8, 4), dtype=torch.int32, device="cuda"), torch.empty((8, 4), device="cuda")
+    lens = torch.empty(8, dtype=torch.int32, device="cuda")
+    out = torch.empty((8, 16), dtype=torch.uint8, device="cuda")
+    draws = torch.zeros(8, dtype=torch.int64, device="cuda")
+    calls = [lambda: h.fill_masks(st, mask), lambda: wg.apply_mask(logits, mask), lambda: wg.masked_argmax(logits, mask, tok),
+             lambda: wg.masked_topk_static(logits, mask, ids, vals), lambda: h.forced_bytes(st, out, lens),
+             lambda: wg.select_tokens(mask, h.V, draws, tok), lambda: h.advance(st, tok), lambda: h.advance_fill_masks(st, tok, mask),
+             lambda: h.decode_step(st, None, mask, logits), lambda: h.add_instances(w.texts[:1], w.args[:1])]
+    for i, call in enumerate(calls):
+        torch.cuda.synchronize()
+        ms = ctypes.c_float()
+        assert hip.hipEventElapsedTime(ctypes.byref(ms), None, None) != 0        # no such events: refused by the runtime
+        try:
+            call()
+        finally:
+            hip.hipGetLastError()
+    torch.cuda.synchronize()
+    assert (H.host_mask(mask) == o.fill_masks(H.host_states(st))).all()
