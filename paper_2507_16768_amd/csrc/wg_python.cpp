@@ -2,10 +2,12 @@
 // tensors, finds the current stream and calls the C ABI from here.  A decode step of a small batch
 // is bound by the host, and the same checks written in Python over ctypes took 8 us of the 13 us a
 // step took (B = 1); here the whole call is about the launches.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 
 #include <cstring>
+#include <exception>
 #include <string>
 #include <vector>
 
@@ -57,17 +59,33 @@ bool handle_of(PyObject *o, wg_handle_t *out) {
     return !PyErr_Occurred();
 }
 
+// The C call f() without the interpreter's lock.  f captures addresses and numbers, no tensors: what asks
+// a tensor may throw (a tensor without storage, as vmap, functorch and fake modes hand them in) and may
+// call back into Python, so it is done before, with the lock held.
 template <typename F> int unlocked(F f) {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
-    return rc;
+    struct Release {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Release() { PyEval_RestoreThread(state); }
+    } released;
+    return f();
+}
+
+// A method of the module: C++ exceptions become Python's, as torch's own calls translate them.
+using Method = PyObject *(PyObject *, PyObject *const *, Py_ssize_t);
+template <Method *f> PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
+    try {
+        return f(self, a, n);
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());
+        return nullptr;
+    }
 }
 
 bool states_ok(const at::Tensor &t) { return t.dim() == 2 && t.size(1) == 2; }
 wg_state_t *states_ptr(const at::Tensor &t) { return static_cast<wg_state_t *>(t.data_ptr()); }
 uint32_t *words(const at::Tensor &t) { return static_cast<uint32_t *>(t.data_ptr()); }
+int32_t *ints(const at::Tensor &t) { return static_cast<int32_t *>(t.data_ptr()); }
+uint32_t rows(const at::Tensor &t) { return (uint32_t)t.size(0); }
 
 // A [B, V] float32 or bfloat16 device tensor with unit inner stride.
 bool logits_ok(const at::Tensor &t, wg_dtype_t *dt, const char *what) {
@@ -85,7 +103,7 @@ PyObject *fill_masks(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const int64_t W = PyLong_AsLongLong(a[1]);
     if (!states_ok(*st) || !shape2(*bm, st->size(0), W)) { bad(PyExc_ValueError, "states must be [B, 2] and bitmask [B, W]"); return nullptr; }
     if (!device(*st, at::kInt, "states") || !device(*bm, at::kInt, "bitmask") || !stream_of(a[4], &s)) return nullptr;
-    return result(unlocked([&] { return wg_fill_masks(h, states_ptr(*st), (uint32_t)st->size(0), words(*bm), s); }));
+    return result(unlocked([=, states = states_ptr(*st), B = rows(*st), mask = words(*bm)] { return wg_fill_masks(h, states, B, mask, s); }));
 }
 
 // advance(handle, states, tokens, stream)
@@ -94,7 +112,7 @@ PyObject *advance(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!count(n, 4) || !handle_of(a[0], &h) || !tensor(a[1], &st, "states") || !tensor(a[2], &tk, "tokens")) return nullptr;
     if (!states_ok(*st) || !shape1(*tk, st->size(0))) { bad(PyExc_ValueError, "states must be [B, 2] and tokens [B]"); return nullptr; }
     if (!device(*st, at::kInt, "states") || !device(*tk, at::kInt, "tokens") || !stream_of(a[3], &s)) return nullptr;
-    return result(unlocked([&] { return wg_advance(h, states_ptr(*st), static_cast<const int32_t *>(tk->data_ptr()), (uint32_t)st->size(0), s); }));
+    return result(unlocked([=, states = states_ptr(*st), tokens = ints(*tk), B = rows(*st)] { return wg_advance(h, states, tokens, B, s); }));
 }
 
 // advance_fill_masks(handle, W, states, tokens, bitmask, stream)
@@ -107,8 +125,8 @@ PyObject *advance_fill_masks(PyObject *, PyObject *const *a, Py_ssize_t n) {
         return nullptr;
     }
     if (!device(*st, at::kInt, "states") || !device(*tk, at::kInt, "tokens") || !device(*bm, at::kInt, "bitmask") || !stream_of(a[5], &s)) return nullptr;
-    return result(unlocked([&] {
-        return wg_advance_fill_masks(h, states_ptr(*st), static_cast<const int32_t *>(tk->data_ptr()), (uint32_t)st->size(0), words(*bm), s);
+    return result(unlocked([=, states = states_ptr(*st), tokens = ints(*tk), B = rows(*st), mask = words(*bm)] {
+        return wg_advance_fill_masks(h, states, tokens, B, mask, s);
     }));
 }
 
@@ -124,10 +142,8 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (lg->size(0) != st->size(0)) { bad(PyExc_ValueError, "logits must be a [B, V] device tensor with unit inner stride"); return nullptr; }
     if (lg->size(1) != V) { bad(PyExc_ValueError, "logits must have the vocabulary's width"); return nullptr; }
     if (!device(*st, at::kInt, "states") || (tk && !device(*tk, at::kInt, "tokens")) || !device(*bm, at::kInt, "bitmask") || !stream_of(a[7], &s)) return nullptr;
-    return result(unlocked([&] {
-        return wg_decode_step(h, states_ptr(*st), tk ? static_cast<const int32_t *>(tk->data_ptr()) : nullptr, (uint32_t)st->size(0),
-                              words(*bm), lg->data_ptr(), dt, lg->stride(0), s);
-    }));
+    return result(unlocked([=, states = states_ptr(*st), tokens = tk ? ints(*tk) : nullptr, B = rows(*st), mask = words(*bm), logits = lg->data_ptr(),
+                            stride = lg->stride(0)] { return wg_decode_step(h, states, tokens, B, mask, logits, dt, stride, s); }));
 }
 
 // forced_bytes(handle, states, out_bytes, out_lens, end_states or None, stream)
@@ -142,10 +158,8 @@ PyObject *forced_bytes(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (es && !shape2(*es, st->size(0), 2)) { bad(PyExc_ValueError, "end_states must be [B, 2]"); return nullptr; }
     if (!device(*st, at::kInt, "states") || !device(*ob, at::kByte, "out_bytes") || !device(*ol, at::kInt, "out_lens") ||
         (es && !device(*es, at::kInt, "end_states")) || !stream_of(a[5], &s)) return nullptr;
-    return result(unlocked([&] {
-        return wg_forced_bytes(h, states_ptr(*st), (uint32_t)st->size(0), (uint32_t)ob->size(1), static_cast<uint8_t *>(ob->data_ptr()),
-                               words(*ol), es ? states_ptr(*es) : nullptr, s);
-    }));
+    return result(unlocked([=, states = states_ptr(*st), B = rows(*st), cap = (uint32_t)ob->size(1), bytes = static_cast<uint8_t *>(ob->data_ptr()),
+                            lens = words(*ol), ends = es ? states_ptr(*es) : nullptr] { return wg_forced_bytes(h, states, B, cap, bytes, lens, ends, s); }));
 }
 
 // cache_clear(handle, stream)
@@ -168,7 +182,9 @@ PyObject *apply_mask(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!count(n, 3) || !masked(a[0], a[1], &lg, &bm, &dt)) return nullptr;
     if (!mask_fits(*lg, *bm)) { bad(PyExc_ValueError, "bitmask must be [B, ceil(V/32)]"); return nullptr; }
     if (!device(*bm, at::kInt, "bitmask") || !stream_of(a[2], &s)) return nullptr;
-    return result(unlocked([&] { return wg_apply_mask(lg->data_ptr(), dt, (uint32_t)lg->size(0), (uint32_t)lg->size(1), lg->stride(0), words(*bm), s); }));
+    return result(unlocked([=, logits = lg->data_ptr(), B = rows(*lg), V = (uint32_t)lg->size(1), stride = lg->stride(0), mask = words(*bm)] {
+        return wg_apply_mask(logits, dt, B, V, stride, mask, s);
+    }));
 }
 
 // masked_argmax(logits, bitmask, tokens, stream)
@@ -177,9 +193,8 @@ PyObject *masked_argmax(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!count(n, 4) || !masked(a[0], a[1], &lg, &bm, &dt) || !tensor(a[2], &tk, "tokens")) return nullptr;
     if (!mask_fits(*lg, *bm) || !shape1(*tk, lg->size(0))) { bad(PyExc_ValueError, "bitmask must be [B, ceil(V/32)] and tokens [B]"); return nullptr; }
     if (!device(*bm, at::kInt, "bitmask") || !device(*tk, at::kInt, "tokens") || !stream_of(a[3], &s)) return nullptr;
-    return result(unlocked([&] {
-        return wg_masked_argmax(lg->data_ptr(), dt, (uint32_t)lg->size(0), (uint32_t)lg->size(1), lg->stride(0), words(*bm),
-                                static_cast<int32_t *>(tk->data_ptr()), s);
+    return result(unlocked([=, logits = lg->data_ptr(), B = rows(*lg), V = (uint32_t)lg->size(1), stride = lg->stride(0), mask = words(*bm), tokens = ints(*tk)] {
+        return wg_masked_argmax(logits, dt, B, V, stride, mask, tokens, s);
     }));
 }
 
@@ -192,12 +207,12 @@ PyObject *masked_topk(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!mask_fits(*lg, *bm)) { bad(PyExc_ValueError, "bitmask must be [B, ceil(V/32)]"); return nullptr; }
     if (!device(*bm, at::kInt, "bitmask") || !device(*id, at::kInt, "ids") || !device(*va, lg->scalar_type(), "values") ||
         (ws && !device(*ws, ws->scalar_type(), "workspace")) || !stream_of(a[5], &s)) return nullptr;
-    const uint32_t B = (uint32_t)lg->size(0), V = (uint32_t)lg->size(1), k = (uint32_t)id->size(1);
-    return result(unlocked([&] {
-        int32_t *ids = static_cast<int32_t *>(id->data_ptr());
-        return ws ? wg_masked_topk(lg->data_ptr(), dt, B, V, lg->stride(0), words(*bm), k, ids, va->data_ptr(), ws->data_ptr(),
-                                   (uint64_t)ws->numel() * ws->element_size(), s)
-                  : wg_masked_topk_static(lg->data_ptr(), dt, B, V, lg->stride(0), words(*bm), k, ids, va->data_ptr(), s);
+    const uint32_t B = rows(*lg), V = (uint32_t)lg->size(1), k = (uint32_t)id->size(1);
+    const bool own = !ws;
+    return result(unlocked([=, logits = lg->data_ptr(), stride = lg->stride(0), mask = words(*bm), ids = ints(*id), values = va->data_ptr(),
+                            work = ws ? ws->data_ptr() : nullptr, bytes = ws ? (uint64_t)ws->numel() * ws->element_size() : 0u] {
+        return own ? wg_masked_topk_static(logits, dt, B, V, stride, mask, k, ids, values, s)
+                   : wg_masked_topk(logits, dt, B, V, stride, mask, k, ids, values, work, bytes, s);
     }));
 }
 
@@ -207,9 +222,8 @@ PyObject *select_tokens(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!count(n, 5) || !tensor(a[0], &bm, "bitmask") || !tensor(a[2], &dr, "draws") || !tensor(a[3], &tk, "tokens")) return nullptr;
     const int64_t V = PyLong_AsLongLong(a[1]);
     if (PyErr_Occurred() || !device(*bm, at::kInt, "bitmask") || !device(*dr, at::kLong, "draws") || !device(*tk, at::kInt, "tokens") || !stream_of(a[4], &s)) return nullptr;
-    const uint32_t B = bm->dim() ? (uint32_t)bm->size(0) : 0u;
-    return result(unlocked([&] {
-        return wg_select_tokens(words(*bm), B, (uint32_t)V, static_cast<const uint64_t *>(dr->data_ptr()), static_cast<int32_t *>(tk->data_ptr()), s);
+    return result(unlocked([=, mask = words(*bm), B = bm->dim() ? rows(*bm) : 0u, draws = static_cast<const uint64_t *>(dr->data_ptr()), tokens = ints(*tk)] {
+        return wg_select_tokens(mask, B, (uint32_t)V, draws, tokens, s);
     }));
 }
 
@@ -279,7 +293,7 @@ PyObject *set_error(PyObject *, PyObject *cls) {
     Py_RETURN_NONE;
 }
 
-#define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
+#define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<name>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(fill_masks), FAST(advance), FAST(advance_fill_masks), FAST(decode_step), FAST(forced_bytes), FAST(cache_clear),
                          FAST(apply_mask), FAST(masked_argmax), FAST(masked_topk), FAST(select_tokens), FAST(add_instances),
                          {"set_error", set_error, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
