@@ -312,7 +312,7 @@ class Handle:
         if marshalled is not None:
             _check(L.wg_add_instances(self._h, marshalled[0], marshalled[1], n, starts.ctypes.data, _stream_ptr(stream)))
         else:
-            _native.add_instances(self._p, texts, args, starts.ctypes.data, stream)
+            _native.add_instances(self._p, texts, args, starts.ctypes.data, n, stream)
         self.start_states = np.concatenate([self.start_states, starts[:n]])
         self.num_states = L.wg_num_states(self._h)
         return starts[:n]

@@ -227,22 +227,30 @@ PyObject *select_tokens(PyObject *, PyObject *const *a, Py_ssize_t n) {
     }));
 }
 
-// add_instances(handle, texts, args or None, starts address, stream): lists of template texts and of
-// argument dictionaries, read in place.
+// add_instances(handle, texts, args or None, starts address, its rows, stream): sequences of template texts and of
+// argument mappings.  The C call reads the strings in place and without the lock, when other threads may
+// change the caller's lists and dictionaries, and a conversion to bytes may run Python code that does:
+// a reference is held to everything that is pointed into, and no container is walked after such code ran.
 PyObject *add_instances(PyObject *, PyObject *const *a, Py_ssize_t n) {
     wg_handle_t h; void *s;
-    if (!count(n, 5) || !handle_of(a[0], &h) || !stream_of(a[4], &s)) return nullptr;
+    if (!count(n, 6) || !handle_of(a[0], &h) || !stream_of(a[5], &s)) return nullptr;
     void *starts = PyLong_AsVoidPtr(a[3]);
+    const Py_ssize_t room = PyLong_AsSsize_t(a[4]);
     if (PyErr_Occurred()) return nullptr;
     struct Refs {                                      // what has to live until the call is over
         std::vector<PyObject *> v;
-        ~Refs() { for (PyObject *o : v) Py_XDECREF(o); }
-        PyObject *keep(PyObject *o) { if (o) v.push_back(o); return o; }
+        ~Refs() { for (PyObject *o : v) Py_DECREF(o); }
+        PyObject *keep(PyObject *o) {                  // takes over a new reference
+            if (o) try { v.push_back(o); } catch (...) { Py_DECREF(o); throw; }
+            return o;
+        }
     } refs;
-    PyObject *texts = refs.keep(PySequence_Fast(a[1], "texts must be a sequence"));
+    PyObject *texts = refs.keep(PySequence_Tuple(a[1]));
     if (!texts) return nullptr;
-    const Py_ssize_t count_ = PySequence_Fast_GET_SIZE(texts);
+    const Py_ssize_t count_ = PyTuple_GET_SIZE(texts);
+    if (count_ > room) { bad(PyExc_ValueError, "more templates than the result has rows"); return nullptr; }
     std::vector<const char *> c_texts((size_t)count_ + 1, nullptr);
+    // o is held by the caller of this; what is made from it here is held by refs
     auto bytes_of = [&](PyObject *o, const char **p, uint64_t *len) {
         if (PyUnicode_Check(o)) { Py_ssize_t k; *p = PyUnicode_AsUTF8AndSize(o, &k); if (len) *len = (uint64_t)k; return *p != nullptr; }
         PyObject *b = o;
@@ -252,26 +260,32 @@ PyObject *add_instances(PyObject *, PyObject *const *a, Py_ssize_t n) {
         return true;
     };
     for (Py_ssize_t i = 0; i < count_; i++)
-        if (!bytes_of(PySequence_Fast_GET_ITEM(texts, i), &c_texts[i], nullptr)) return nullptr;
+        if (!bytes_of(PyTuple_GET_ITEM(texts, i), &c_texts[i], nullptr)) return nullptr;
     std::vector<wg_args_t> c_args;
     std::vector<const char *> names;
     std::vector<const uint8_t *> data;
     std::vector<uint64_t> lens;
     if (a[2] != Py_None) {
-        PyObject *args = refs.keep(PySequence_Fast(a[2], "args must be a sequence"));
+        PyObject *args = refs.keep(PySequence_Tuple(a[2]));
         if (!args) return nullptr;
-        if (PySequence_Fast_GET_SIZE(args) != count_) { bad(PyExc_ValueError, "one argument set per template is required"); return nullptr; }
+        if (PyTuple_GET_SIZE(args) != count_) { bad(PyExc_ValueError, "one argument set per template is required"); return nullptr; }
         std::vector<size_t> first((size_t)count_ + 1, 0);
+        std::vector<PyObject *> items;                 // names and values of one set, in turn
         for (Py_ssize_t i = 0; i < count_; i++) {
-            PyObject *d = PySequence_Fast_GET_ITEM(args, i), *key, *value;
+            PyObject *d = PyTuple_GET_ITEM(args, i), *key, *value;
             if (!PyDict_Check(d) && !(d = refs.keep(PyObject_CallFunctionObjArgs((PyObject *)&PyDict_Type, d, nullptr)))) return nullptr;
+            items.clear();
             Py_ssize_t at = 0;
             while (PyDict_Next(d, &at, &key, &value)) {
-                const char *p; uint64_t len;
                 if (!PyUnicode_Check(key) || PyUnicode_Check(value)) { bad(PyExc_TypeError, "arguments map names to bytes"); return nullptr; }
-                if (!bytes_of(key, &p, nullptr)) return nullptr;
+                Py_INCREF(key); items.push_back(refs.keep(key));
+                Py_INCREF(value); items.push_back(refs.keep(value));
+            }
+            for (size_t k = 0; k < items.size(); k += 2) {
+                const char *p; uint64_t len;
+                if (!bytes_of(items[k], &p, nullptr)) return nullptr;
                 names.push_back(p);
-                if (!bytes_of(value, &p, &len)) return nullptr;
+                if (!bytes_of(items[k + 1], &p, &len)) return nullptr;
                 data.push_back(reinterpret_cast<const uint8_t *>(p)); lens.push_back(len);
             }
             first[i + 1] = names.size();

@@ -59,3 +59,40 @@ def test_tensors_without_storage_raise_instead_of_ending_the_process():
     interpreter's lock held, whichever argument it is."""
     r = subprocess.run([sys.executable, "-c", NO_STORAGE], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.split() == ["done"], (r.returncode, r.stdout, r.stderr[-2000:])
+
+
+def test_arguments_of_add_instances_are_held_through_the_call():
+    """The C call reads texts, names and values where they lie, so each is held whatever happens to the
+    caller's list and dictionaries meanwhile: here a value's own conversion to bytes empties them."""
+    import numpy as np
+    import paper_2507_16768_amd as wg
+    from paper_2507_16768_amd import binding
+    binding.load_library()
+    made = {k: "".join([k, "_of_this_test"]) for k in ("text", "name")}       # strings that nothing else refers to
+    value = bytes(bytearray(b"a literal of its own"))
+    texts, d = [made["text"], "Sequence(Write($x))"], {}
+    args = [d, {"x": b"1"}]
+    held = {}
+
+    class Value:
+        def __bytes__(self):
+            d.clear(); args.clear(); texts.clear()
+            held.update({k: sys.getrefcount(o) - 2 for k, o in made.items()}, value=sys.getrefcount(value) - 2)
+            return b"2"
+
+    d.update({made["name"]: value, "last": Value()})
+    starts = np.zeros((2, 2), dtype=np.uint32)
+    with pytest.raises(wg.WgError, match="null handle"):
+        binding._native.add_instances(0, texts, args, starts.ctypes.data, 2, 0)
+    # (beside the reference that this test itself has to each: `made`, the local `value`)
+    assert held["text"] >= 2 and held["name"] >= 2 and held["value"] >= 1, held
+    assert sys.getrefcount(value) == 2                                        # and let go of afterwards
+
+
+def test_add_instances_takes_no_more_templates_than_it_has_room_for():
+    import numpy as np
+    from paper_2507_16768_amd import binding
+    binding.load_library()
+    starts = np.zeros((2, 2), dtype=np.uint32)
+    with pytest.raises(ValueError, match="rows"):
+        binding._native.add_instances(0, ["Sequence(Write(\"a\"))"] * 2, None, starts.ctypes.data, 1, 0)
