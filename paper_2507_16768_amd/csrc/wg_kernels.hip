@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include "wg_device.h"
+#include "wg_launch.h"
 
 namespace wg {
 

@@ -23,6 +23,7 @@
 #include <mutex>
 
 #include "wg_device.h"
+#include "wg_launch.h"
 #include "wg_order.h"
 
 namespace wg {
