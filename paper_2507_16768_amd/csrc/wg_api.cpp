@@ -157,13 +157,12 @@ uint32_t grown(uint32_t need, uint32_t floor_n) {
     return n > 0xFFFFFFF0ull ? 0xFFFFFFF0u : (uint32_t)n;
 }
 
-// Brings the device copy of the table up to date with the host table after instances were
-// appended.  Within the reserved capacities this only copies the new slices (ordered on `s`
-// with the caller's other work); beyond them the device is synchronised once and the tables move.
-int sync_table(wg_handle_s *h, hipStream_t s) {
+// Room in the device tables for what the host table holds.  Beyond the reserved capacities the device is
+// synchronised once and the tables move.
+int grow_table(wg_handle_s *h, uint32_t n_states, uint32_t n_classes) {
     const Table &t = h->low.table;
-    const uint32_t n_states = (uint32_t)t.states.size(), n_classes = (uint32_t)(t.classes.size() / 256);
     const uint32_t row_stride = h->dc.row_stride;
+    if (t.n_keys > kMaxKeys) return fail(WG_ERR_NOMEM, "more than 2^31 - 2 cache keys");
     if (n_states > h->cap_states || n_classes > h->cap_classes || t.n_keys > h->cap_keys)
         WG_HIP(hipDeviceSynchronize());
     if (n_states > h->cap_states) {
@@ -174,7 +173,6 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         if (rc != WG_OK) return rc;
         h->cap_states = nc;
     }
-    if (t.n_keys > kMaxKeys) return fail(WG_ERR_NOMEM, "more than 2^31 - 2 cache keys");
     if (t.n_keys > h->cap_keys) {
         const uint32_t nc = grown(t.n_keys, 4096);
         int rc = regrow(&h->dc.tags, h->cap_keys, nc);
@@ -191,6 +189,19 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         if (rc != WG_OK) return rc;
         h->cap_classes = nc;
     }
+    return WG_OK;
+}
+
+// Brings the device copy of the table up to date with the host table after instances were
+// appended: the new slices are copied, ordered on `s` with the caller's other work.  Where a step
+// fails, what the kernels are given is as before the call (the tables perhaps at new addresses): the
+// new states become known to them last, when everything they refer to is in place.
+int sync_table(wg_handle_s *h, hipStream_t s) {
+    const Table &t = h->low.table;
+    const uint32_t n_states = (uint32_t)t.states.size(), n_classes = (uint32_t)(t.classes.size() / 256);
+    const int rc = grow_table(h, n_states, n_classes);
+    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, h->dt.n_states, t.lmax};
+    if (rc != WG_OK) return rc;
     if (n_states > h->up_states || n_classes > h->up_classes) {
         const uint32_t s0 = h->up_states, ns = n_states - s0, c0 = h->up_classes, nc = n_classes - c0;
         h->plans.resize(n_classes);
@@ -224,7 +235,6 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         h->up_states = n_states;
         h->up_classes = n_classes;
     }
-    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, n_states, t.lmax};
     if (h->dc.direct && t.n_keys > h->dc.cap_rows) {
         // more keys than rows from now on: the rows in use stay where they are, the others are handed out
         // in order of first use
@@ -234,6 +244,7 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
         h->dc.free_rows = h->d_free_rows;
     }
     h->dc.n_keys = t.n_keys;
+    h->dt.n_states = n_states;
     return WG_OK;
 }
 

@@ -1,0 +1,158 @@
+// Driver for wg_api.cpp on the CPU (test infrastructure): the C ABI's host code under
+// -fsanitize=address,undefined with device memory played by malloc and the kernel launchers by functions
+// that look at every table they are given.  Instances are added to a live handle while one allocation, copy
+// or launch after the other fails: whatever a call that failed left behind, the next fill has to find tables
+// that are there, states within them, and, where the arena is addressed by key, a row for every key.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "../../paper_2507_16768_amd/csrc/wg_device.h"
+
+static long until_failure = -1;          // calls of the runtime that may fail before one does; -1: none does
+static int failures = 0;
+
+#define EXPECT(cond, ...) do { if (!(cond)) { std::printf("FAILED "); std::printf(__VA_ARGS__); std::printf("\n"); failures++; } } while (0)
+
+static bool fails() { return until_failure >= 0 && until_failure-- == 0; }
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n) {
+    if (fails()) return hipErrorOutOfMemory;
+    *p = std::malloc(n ? n : 1);
+    std::memset(*p, 0xA5, n);
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
+hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (fails()) return hipErrorUnknown; std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+hipError_t hipMemset(void *d, int v, size_t n) { if (fails()) return hipErrorUnknown; std::memset(d, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
+hipError_t hipDeviceSynchronize(void) { return fails() ? hipErrorUnknown : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return fails() ? hipErrorUnknown : hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)1 << 30; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *, hipEvent_t, hipEvent_t) { return hipErrorInvalidHandle; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "made up"; }
+}
+
+namespace wg {
+
+// What the kernels take for granted of their tables.
+static void look_at(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc) {
+    uint64_t sum = 0;
+    for (uint32_t sid = 0; sid < T.n_states; sid++) {
+        const StateDesc d = T.states[sid];
+        const uint32_t kind = d.kind_byte & 0xFFu;
+        const uint32_t keys = kind == WG_KIND_WAIT && d.max != WG_UNBOUNDED ? T.lmax + 1u : 1u;
+        EXPECT((uint64_t)d.key_base + keys <= Cc.n_keys, "state %u: keys from %u on, %u of them, %u in the table", sid, d.key_base, keys, Cc.n_keys);
+        if (Cc.direct) EXPECT((uint64_t)d.key_base + keys <= Cc.cap_rows, "state %u: key %u of an arena of %u rows", sid, d.key_base + keys - 1u, Cc.cap_rows);
+        for (uint32_t nt : {d.next_a, d.next_b, d.eos_next}) EXPECT(nt < T.n_states || nt == WG_SID_ERROR, "state %u: successor %u of %u", sid, nt, T.n_states);
+        if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
+            sum += T.classes[(size_t)d.cls * 256u + 255u] + T.plans[d.cls].ids[259] + Cc.class_tags[d.cls];
+            sum += Cc.class_rows[(size_t)(2u * d.cls + 2u) * Vc.row_stride - 1u];
+        }
+        sum += T.lit[sid];
+    }
+    for (uint32_t i = 0; i < 16u; i++) sum += T.lit[T.n_states + i];
+    for (uint32_t k = 0; k < Cc.n_keys; k++) {
+        sum += Cc.tags[k];
+        if (!Cc.direct) sum += Cc.slots[k];
+    }
+    sum += Cc.arena[(size_t)Cc.cap_rows * Vc.row_stride - 1u];
+    if (!Cc.direct && Cc.free_rows) sum += Cc.free_rows[Cc.cap_rows - 1u];
+    if (sum == 1u) std::printf(" ");                 // (the reads are not to be left out)
+}
+
+FillPlan plan_fill(const DeviceVocab &, const DeviceCache &, uint32_t, int, uint32_t) { return FillPlan{8u, false}; }
+hipError_t launch_fill(const FillPlan &, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, wg_state_t *, const int32_t *, uint32_t,
+                       uint32_t *, void *, int, int64_t, hipStream_t, hipEvent_t *, hipEvent_t *) {
+    look_at(T, Vc, Cc);
+    return hipSuccess;
+}
+hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t) {
+    if (fails()) return hipErrorUnknown;
+    for (uint32_t i = 0; i < n; i++) std::memcpy(a.slice[i].dst, a.slice[i].src, a.slice[i].bytes);
+    return hipSuccess;
+}
+hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t) {
+    if (fails()) return hipErrorUnknown;
+    for (uint32_t i = 0; i < n_keys; i++) Cc.slots[i] = i;
+    for (uint32_t i = 0; i < Cc.cap_rows; i++) free_rows[i] = i;
+    return hipSuccess;
+}
+uint32_t rows_lds_bytes(const DeviceVocab &) { return 1024u; }
+hipError_t static_topk_scratch(unsigned long long **out) { *out = nullptr; return hipSuccess; }
+hipError_t launch_apply(void *, int, uint32_t, uint32_t, int64_t, const uint32_t *, hipStream_t, hipEvent_t *) { return hipSuccess; }
+hipError_t launch_masked_argmax(const void *, int, uint32_t, uint32_t, int64_t, const uint32_t *, int32_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_masked_topk(const void *, int, uint32_t, uint32_t, int64_t, const uint32_t *, uint32_t, int32_t *, void *, unsigned long long *,
+                              hipStream_t) { return hipSuccess; }
+hipError_t launch_advance(const DeviceTable &, const DeviceVocab &, const DeviceCache &, wg_state_t *, const int32_t *, uint32_t, hipStream_t,
+                          hipEvent_t *) { return hipSuccess; }
+hipError_t launch_forced_bytes(const DeviceTable &, const wg_state_t *, uint32_t, uint32_t, uint8_t *, uint32_t *, wg_state_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_select(const uint32_t *, uint32_t, uint32_t, const uint64_t *, int32_t *, hipStream_t) { return hipSuccess; }
+
+}  // namespace wg
+
+// One handle; the addition's k-th call of the runtime fails, then the same addition is made again.
+static bool one(wg_vocab_t vocab, long k, uint32_t rows, const std::vector<std::string> &texts, bool clear_between) {
+    const char *base = "Sequence(Write(\"ab\"), Wait(allow={a, b}, wait={c}, max=4))";
+    wg_handle_t h = nullptr;
+    wg_state_t start, more[4], states[2] = {};
+    uint32_t mask[64];
+    EXPECT(wg_compile(&base, nullptr, 1, vocab, WG_EOS_RESTART, &h, &start) == WG_OK, "compile: %s", wg_last_error());
+    if (rows) EXPECT(wg_cache_resize(h, rows) == WG_OK, "resize: %s", wg_last_error());
+    EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill: %s", wg_last_error());
+    std::vector<const char *> c;
+    for (const auto &t : texts) c.push_back(t.c_str());
+    until_failure = k;
+    const int rc = wg_add_instances(h, c.data(), nullptr, (uint32_t)c.size(), more, nullptr);
+    const bool failed = until_failure < 0 && k >= 0;
+    until_failure = -1;
+    EXPECT(failed == (rc != WG_OK), "call %ld: status %d", k, rc);
+    EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill after a failure: %s", wg_last_error());
+    if (clear_between) EXPECT(wg_cache_clear(h, nullptr) == WG_OK, "clear: %s", wg_last_error());
+    const char *last = "Sequence(Write(\"z\"))";
+    EXPECT(wg_add_instances(h, &last, nullptr, 1, more, nullptr) == WG_OK, "addition after a failure: %s", wg_last_error());
+    EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill at the end: %s", wg_last_error());
+    EXPECT(wg_num_states(h) > more[0].sid, "%u states, the last instance starts at %u", wg_num_states(h), more[0].sid);
+    wg_destroy(h);
+    return failed;
+}
+
+int main() {
+    const uint8_t bytes[] = "abcz";
+    const uint64_t offsets[] = {0, 1, 2, 3, 4};
+    wg_vocab_t vocab = nullptr;
+    EXPECT(wg_vocab_create(bytes, offsets, 4, -1, &vocab) == WG_OK, "vocabulary: %s", wg_last_error());
+    // more states and keys than there is room for, as many class tables, and slices too large for the staging memory
+    std::string many = "Sequence(", tables = "Sequence(";
+    for (int i = 0; i < 9000; i++) many += std::string(i ? ", " : "") + "Write(\"" + std::string(1 + i % 3, (char)('a' + i % 23)) + "\")";
+    for (int i = 0; i < 120; i++) {
+        char t[64];
+        std::snprintf(t, sizeof t, "%sWait(allow={\\x%02X}, wait={\\xFF}, max=3)", i ? ", " : "", 0x20 + i);
+        tables += t;
+    }
+    many += ")"; tables += ")";
+    const std::vector<std::vector<std::string>> additions = {{"Sequence(Write(\"c\"))"}, {many}, {tables}, {many, tables, many + " "}};
+    long calls = 0;
+    for (const auto &a : additions)
+        for (uint32_t rows : {0u, 8u, 30000u})
+            for (int clear = 0; clear < 2; clear++)
+                for (long k = 0;; k++) {
+                    calls++;
+                    if (!one(vocab, k, rows, a, clear != 0)) break;
+                }
+    wg_vocab_destroy(vocab);
+    std::printf("%ld additions, failures %d\n", calls, failures);
+    return failures != 0;
+}

@@ -2,7 +2,8 @@
 compiler, regular-expression translator and vocabulary index builder and the C oracle are built with
 -fsanitize=address,undefined into one driver (tests/sanitize/host_check.cpp) and run over
 workload templates with arguments, random operator trees, malformed templates, incremental
-adds with a failing add in between, and regular expressions.  Nothing here touches the GPU."""
+adds with a failing add in between, and regular expressions.  The C ABI's host code is built the same way
+against a runtime played on the CPU (tests/sanitize/api_check.cpp).  Nothing here touches the GPU."""
 import os
 import shutil
 import subprocess
@@ -109,3 +110,24 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     assert "ERROR: AddressSanitizer" not in r.stderr and "runtime error" not in r.stderr and "LeakSanitizer" not in r.stderr, tail
     assert r.stdout.count("index ok ") == 6 and "INDEX" not in r.stdout, tail
     assert r.stdout.count("\nok ") > 100 and r.stdout.count("err") > 15, tail
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_additions_that_fail_half_way_leave_consistent_device_tables(tmp_path):
+    """Every allocation, copy and launch of wg_add_instances fails in turn: the next fill finds its tables in
+    place and no state whose key has no row, and a later addition succeeds."""
+    san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer", "-g", "-O1", "-std=c++17"]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    csrc = os.path.join(ROOT, "paper_2507_16768_amd", "csrc")
+    objs = []
+    for src in [os.path.join(csrc, f) for f in ("wg_api.cpp", "wg_lower.cpp", "wg_regex.cpp", "wg_vocab_index.cpp")] + \
+            [os.path.join(ROOT, "tests", "sanitize", "api_check.cpp")]:
+        obj = str(tmp_path / (os.path.basename(src) + ".o"))
+        subprocess.run(["g++", "-D__HIP_PLATFORM_AMD__=1", "-isystem", os.path.join(rocm, "include")] + san + ["-c", src, "-o", obj], check=True, cwd=ROOT)
+        objs.append(obj)
+    exe = str(tmp_path / "api_check")
+    subprocess.run(["g++"] + san + objs + ["-o", exe], check=True)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0:verify_asan_link_order=0")
+    env.pop("LD_PRELOAD", None)
+    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
+    assert r.returncode == 0 and "failures 0" in r.stdout, (r.stdout[-1500:], r.stderr[-3000:])
