@@ -66,6 +66,17 @@ namespace {
 
 int fail(int code, const std::string &msg) { set_last_error(msg); return code; }
 
+// What a C entry does, f, with the exceptions of the host's allocations turned into its status: they must
+// not leave the library.  who: the entry's name with what went wrong.
+template <typename F> int no_throw(const char *who, F f) {
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+        try { set_last_error(who); } catch (...) {}
+        return WG_ERR_NOMEM;
+    }
+}
+
 constexpr size_t kStageBytes = 1u << 20;      // additions up to this size take the pinned memory that the handle keeps
 constexpr uint32_t kDefaultBatch = 1024;   // requests per call a handle has room for after wg_compile
 
@@ -282,8 +293,8 @@ const char *wg_last_error(void) { return g_last_error.c_str(); }
 
 // ---- vocabulary ------------------------------------------------------------------------------
 
-int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V,
-                    int32_t eos_id, wg_vocab_t *out) {
+static int create_vocab(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V,
+                        int32_t eos_id, wg_vocab_t *out) {
     if (!out) return fail(WG_ERR_INVALID, "wg_vocab_create: out is null");
     *out = nullptr;
     if (!host_offsets || V == 0) return fail(WG_ERR_INVALID, "wg_vocab_create: empty vocabulary");
@@ -294,7 +305,7 @@ int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uin
         const int rc = build_vocab_index(host_bytes, host_offsets, V, eos_id, &ix, &err);
         if (rc != WG_OK) return fail(rc, err);
     }
-    std::unique_ptr<wg_vocab_s> v(new (std::nothrow) wg_vocab_s);
+    std::unique_ptr<wg_vocab_s, void (*)(wg_vocab_t)> v(new (std::nothrow) wg_vocab_s, wg_vocab_destroy);
     if (!v) return fail(WG_ERR_NOMEM, "wg_vocab_create: out of host memory");
     WG_HIP(hipGetDevice(&v->device));
     {
@@ -330,16 +341,19 @@ int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uin
     if (e == hipSuccess) e = upload(&v->d_lit_start, ix.lit_start.data(), ix.lit_start.size());
     if (e == hipSuccess) e = upload(&v->d_dirN, ix.dirN.data(), ix.dirN.size());
     if (e == hipSuccess) e = upload(&v->d_place_start, ix.place_start.data(), ix.place_start.size());
-    if (e != hipSuccess) {
-        v->release();
+    if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? WG_ERR_NOMEM : WG_ERR_HIP,
                     std::string("wg_vocab_create: ") + hipGetErrorString(e));
-    }
     v->dv = DeviceVocab{v->d_len8, v->d_chunks, v->d_len_rows, v->d_rows, v->d_index, v->d_dir0,
                         v->d_lit_start, v->d_dirN, v->d_place_start, at[0], at[1], at[2], at[3],
                         V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride};
     *out = v.release();
     return WG_OK;
+}
+
+int wg_vocab_create(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V,
+                    int32_t eos_id, wg_vocab_t *out) {
+    return no_throw("wg_vocab_create: out of host memory", [&] { return create_vocab(host_bytes, host_offsets, V, eos_id, out); });
 }
 
 void wg_vocab_destroy(wg_vocab_t v) {
@@ -445,8 +459,8 @@ void wg_destroy(wg_handle_t h) {
     delete h;
 }
 
-int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_templates,
-               wg_vocab_t vocab, uint32_t flags, wg_handle_t *out, wg_state_t *start_states_out) {
+static int compile(const char *const *templates, const wg_args_t *args, uint32_t n_templates,
+                   wg_vocab_t vocab, uint32_t flags, wg_handle_t *out, wg_state_t *start_states_out) {
     if (!out) return fail(WG_ERR_INVALID, "wg_compile: out is null");
     *out = nullptr;
     if (!vocab) return fail(WG_ERR_INVALID, "wg_compile: vocab is null");
@@ -458,7 +472,7 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     try {
         h->low.add(templates, args, n_templates);
     } catch (const std::bad_alloc &) {
-        return fail(WG_ERR_NOMEM, "wg_compile: out of host memory");
+        throw;
     } catch (const std::exception &e) {
         return fail(WG_ERR_PARSE, e.what());
     }
@@ -510,15 +524,20 @@ int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_t
     return WG_OK;
 }
 
-int wg_add_instances(wg_handle_t h, const char *const *templates, const wg_args_t *args,
-                     uint32_t n_templates, wg_state_t *start_states_out, void *stream) {
+int wg_compile(const char *const *templates, const wg_args_t *args, uint32_t n_templates,
+               wg_vocab_t vocab, uint32_t flags, wg_handle_t *out, wg_state_t *start_states_out) {
+    return no_throw("wg_compile: out of host memory", [&] { return compile(templates, args, n_templates, vocab, flags, out, start_states_out); });
+}
+
+static int add_instances(wg_handle_t h, const char *const *templates, const wg_args_t *args,
+                         uint32_t n_templates, wg_state_t *start_states_out, void *stream) {
     if (!h) return fail(WG_ERR_INVALID, "wg_add_instances: null handle");
     if (!templates || n_templates == 0) return fail(WG_ERR_INVALID, "wg_add_instances: no templates");
     const size_t first = h->low.table.start.size();
     try {
         h->low.add(templates, args, n_templates);
     } catch (const std::bad_alloc &) {
-        return fail(WG_ERR_NOMEM, "wg_add_instances: out of host memory");
+        throw;
     } catch (const std::exception &e) {
         return fail(WG_ERR_PARSE, e.what());
     }
@@ -529,6 +548,11 @@ int wg_add_instances(wg_handle_t h, const char *const *templates, const wg_args_
         for (uint32_t i = 0; i < n_templates; i++)
             start_states_out[i] = wg_state_t{h->low.table.start[first + i], 0u};
     return WG_OK;
+}
+
+int wg_add_instances(wg_handle_t h, const char *const *templates, const wg_args_t *args,
+                     uint32_t n_templates, wg_state_t *start_states_out, void *stream) {
+    return no_throw("wg_add_instances: out of host memory", [&] { return add_instances(h, templates, args, n_templates, start_states_out, stream); });
 }
 
 int wg_cache_resize(wg_handle_t h, uint32_t rows) {
@@ -755,7 +779,7 @@ int wg_profile_enable(wg_handle_t h, int on) {
     return WG_OK;
 }
 
-int wg_profile_read(wg_handle_t h, wg_profile_t *host_out) {
+static int read_profile(wg_handle_t h, wg_profile_t *host_out) {
     if (!h || !host_out) return fail(WG_ERR_INVALID, "wg_profile_read: null argument");
     WG_HIP(hipDeviceSynchronize());
     wg_profile_t p{};
@@ -778,6 +802,10 @@ int wg_profile_read(wg_handle_t h, wg_profile_t *host_out) {
     p.apply_ms = total(h->apply_events, &p.apply_calls);
     *host_out = p;
     return WG_OK;
+}
+
+int wg_profile_read(wg_handle_t h, wg_profile_t *host_out) {
+    return no_throw("wg_profile_read: out of host memory", [&] { return read_profile(h, host_out); });
 }
 
 int wg_select_tokens(const uint32_t *d_bitmask, uint32_t B, uint32_t V, const uint64_t *d_draws,

@@ -1,6 +1,7 @@
 // Internal layouts shared by the host lowering code and the HIP kernels.
 #pragma once
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -138,7 +139,7 @@ class Lowering {
     Table table;
 
   private:
-    LoweringState *st_;
+    std::unique_ptr<LoweringState> st_;
 };
 
 // Translates a regular expression into template text in the operator syntax; throws

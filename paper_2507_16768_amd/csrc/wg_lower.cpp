@@ -530,7 +530,7 @@ Lowering::Lowering(uint32_t flags, uint32_t lmax) : st_(new LoweringState) {
     st_->class_ids[std::array<uint8_t, 256>{}] = 0;
 }
 
-Lowering::~Lowering() { delete st_; }
+Lowering::~Lowering() = default;
 
 void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t n) {
     Table &t = table;
@@ -578,10 +578,10 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
     // 0..lmax; a larger budget cannot bind inside a single token).  An instance whose lowered
     // states equal those of an earlier instance takes that instance's keys: the global cache
     // then serves every request of that shape from one set of rows.
-    t.key_count.resize(t.states.size());
     uint32_t k = n_keys0;
     std::vector<uint32_t> new_sigs;                                   // to take back if memory runs out half way
     try {
+        t.key_count.resize(t.states.size());
         for (const auto &span : spans) {
             const uint32_t first = span.first, end = span.second;
             for (uint32_t s = first; s <= end; s++) {
@@ -635,8 +635,8 @@ void Lowering::add(const char *const *templates, const wg_args_t *args, uint32_t
             for (uint32_t s = first; s <= end; s++) {
                 const auto known = st_->sig_key.find(cur[s - first]);
                 if (known != st_->sig_key.end()) { t.states[s].key_base = known->second; continue; }
-                st_->sig_key.emplace(cur[s - first], k);
                 new_sigs.push_back(cur[s - first]);
+                st_->sig_key.emplace(cur[s - first], k);
                 t.states[s].key_base = k;
                 k += t.key_count[s];
             }

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -17,6 +18,17 @@ static int failures = 0;
 #define EXPECT(cond, ...) do { if (!(cond)) { std::printf("FAILED "); std::printf(__VA_ARGS__); std::printf("\n"); failures++; } } while (0)
 
 static bool fails() { return until_failure >= 0 && until_failure-- == 0; }
+
+static long until_bad_alloc = -1;        // the same for the host's own allocations
+void *operator new(size_t n) {
+    if (until_bad_alloc >= 0 && until_bad_alloc-- == 0) throw std::bad_alloc();
+    if (void *p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept { return std::malloc(n ? n : 1); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+void operator delete(void *p, const std::nothrow_t &) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n) {
@@ -103,27 +115,31 @@ hipError_t launch_select(const uint32_t *, uint32_t, uint32_t, const uint64_t *,
 
 }  // namespace wg
 
-// One handle; the addition's k-th call of the runtime fails, then the same addition is made again.
-static bool one(wg_vocab_t vocab, long k, uint32_t rows, const std::vector<std::string> &texts, bool clear_between) {
+// One handle; the addition's k-th call of the runtime (or host allocation) fails, and another addition follows.
+static bool one(wg_vocab_t vocab, long k, bool host, uint32_t rows, const std::vector<std::string> &texts, bool clear_between) {
     const char *base = "Sequence(Write(\"ab\"), Wait(allow={a, b}, wait={c}, max=4))";
     wg_handle_t h = nullptr;
     wg_state_t start, more[4], states[2] = {};
     uint32_t mask[64];
-    EXPECT(wg_compile(&base, nullptr, 1, vocab, WG_EOS_RESTART, &h, &start) == WG_OK, "compile: %s", wg_last_error());
+    EXPECT(wg_compile(&base, nullptr, 1, vocab, WG_EOS_RESTART | (host ? WG_SHARE_STATES : 0u), &h, &start) == WG_OK, "compile: %s", wg_last_error());
     if (rows) EXPECT(wg_cache_resize(h, rows) == WG_OK, "resize: %s", wg_last_error());
     EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill: %s", wg_last_error());
     std::vector<const char *> c;
     for (const auto &t : texts) c.push_back(t.c_str());
-    until_failure = k;
+    long &until = host ? until_bad_alloc : until_failure;
+    until = k;
     const int rc = wg_add_instances(h, c.data(), nullptr, (uint32_t)c.size(), more, nullptr);
-    const bool failed = until_failure < 0 && k >= 0;
-    until_failure = -1;
+    const bool failed = until < 0;
+    until = -1;
     EXPECT(failed == (rc != WG_OK), "call %ld: status %d", k, rc);
+    if (failed && host) EXPECT(rc == WG_ERR_NOMEM, "allocation %ld: status %d", k, rc);
+    const uint32_t n_before = wg_num_instances(h);
     EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill after a failure: %s", wg_last_error());
     if (clear_between) EXPECT(wg_cache_clear(h, nullptr) == WG_OK, "clear: %s", wg_last_error());
     const char *last = "Sequence(Write(\"z\"))";
     EXPECT(wg_add_instances(h, &last, nullptr, 1, more, nullptr) == WG_OK, "addition after a failure: %s", wg_last_error());
     EXPECT(wg_fill_masks(h, states, 2, mask, nullptr) == WG_OK, "fill at the end: %s", wg_last_error());
+    EXPECT(wg_num_instances(h) == n_before + 1u, "%u instances after %u", wg_num_instances(h), n_before);
     EXPECT(wg_num_states(h) > more[0].sid, "%u states, the last instance starts at %u", wg_num_states(h), more[0].sid);
     wg_destroy(h);
     return failed;
@@ -150,9 +166,32 @@ int main() {
             for (int clear = 0; clear < 2; clear++)
                 for (long k = 0;; k++) {
                     calls++;
-                    if (!one(vocab, k, rows, a, clear != 0)) break;
+                    if (!one(vocab, k, false, rows, a, clear != 0)) break;
                 }
+    // host memory runs out: nothing is thrown through the C entries
+    for (const auto &a : std::vector<std::vector<std::string>>{additions[0], additions[2]})
+        for (long k = 0;; k++) {
+            calls++;
+            if (!one(vocab, k, true, 0, a, false)) break;
+        }
     wg_vocab_destroy(vocab);
+    for (int what = 0; what < 2; what++)
+        for (long k = 0;; k++) {
+            wg_vocab_t v = nullptr;
+            wg_handle_t h = nullptr;
+            wg_state_t start;
+            const char *text = "Sequence(Write(\"ab\"), Wait(allow={a, b}, wait={c}, max=4))";
+            if (what) EXPECT(wg_vocab_create(bytes, offsets, 4, -1, &v) == WG_OK, "vocabulary: %s", wg_last_error());
+            until_bad_alloc = k;
+            const int rc = what ? wg_compile(&text, nullptr, 1, v, 0, &h, &start) : wg_vocab_create(bytes, offsets, 4, -1, &v);
+            const bool failed = until_bad_alloc < 0;
+            until_bad_alloc = -1;
+            EXPECT(rc == (failed ? WG_ERR_NOMEM : WG_OK), "call %d, allocation %ld: status %d", what, k, rc);
+            wg_destroy(h);
+            wg_vocab_destroy(v);
+            calls++;
+            if (!failed) break;
+        }
     std::printf("%ld additions, failures %d\n", calls, failures);
     return failures != 0;
 }
