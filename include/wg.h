@@ -249,8 +249,9 @@ int wg_apply_mask(void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t V,
  * logits are only read (nothing is set to -inf), so this call replaces wg_apply_mask + argmax.
  * A NaN ranks below every number (also below -inf), equal values (-0.0 equals +0.0) keep the
  * lowest token id, a row that allows nothing gives -1.  Layout of logits and mask as in
- * wg_apply_mask.  The workgroups of a row of a small batch merge through a per-GPU scratch array inside the
- * library, so two wg_masked_argmax calls must not overlap on one GPU (order them on one stream). */
+ * wg_apply_mask.  The workgroups of a row merge through a per-GPU scratch array inside the
+ * library, so two wg_masked_argmax calls must not overlap on one GPU (order them on one stream).  Enqueues one
+ * or two kernels. */
 int wg_masked_argmax(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_t V,
                      int64_t row_stride_elems, const uint32_t *d_bitmask, int32_t *d_tokens,
                      void *stream);

@@ -6,7 +6,9 @@
 // and nothing has to be merged.  One compute unit streams only about 30 GB/s however much it has in
 // flight (a 304 KB row takes 10 us), so smaller batches cut their rows: the greedy choice into as
 // many workgroups as there are compute units, merged by the last of them to finish; the k best of
-// long rows into slices of 8,192 tokens, merged by a second kernel.
+// long rows into slices of 8,192 tokens, merged by a second kernel.  The greedy choice from long fp32 rows is
+// made from such slices too (argmax_slice_kernel): a row of 600 KB per workgroup left compute units
+// idle whenever the rows did not come out even.
 //
 // Times for V = 151,936, bf16, the greedy choice and k = 50, before -> now (before: a workgroup per slice
 // and a second kernel always): B = 1 12.5 -> 5.9 and 13.7 -> 12.1 us, B = 64 12.2 -> 8.3 and 18.9 -> 17.9,
@@ -162,9 +164,10 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
 // masked argmax.  A row cut into several workgroups is merged through the two arrays: each workgroup
 // raises the row's key (the order key of its logit << 32 | ~id; 0: nothing allowed) and then takes
 // a ticket; the one that takes the last ticket finds the row's key complete, and leaves both zero
-// for the next call.  One copy per GPU: calls that cut their rows must not overlap on one GPU.
+// for the next call.  (Rows in slices, below, have no tickets: a second kernel takes the keys.)  One copy
+// per GPU: calls that cut their rows must not overlap on one GPU.
 constexpr uint32_t kCutRows = 256;
-__device__ unsigned long long g_argmax_key[kCutRows];
+__device__ unsigned long long g_argmax_key[kMaxBatch];
 __device__ uint32_t g_argmax_ticket[kCutRows];
 
 template <typename Elem>
@@ -230,6 +233,84 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
         token = row ? 0xFFFFFFFFu - (uint32_t)row : 0xFFFFFFFFu;
     }
     tokens[b] = (int32_t)token;
+}
+
+// fp32 rows of larger batches: a workgroup of 256 threads takes 8,192 tokens, all of its loads in flight
+// together, raises the row's key and is done; a second kernel turns the keys into tokens.  Bound by HBM.
+// Against a workgroup of 1,024 threads per row (two of which fit a compute unit, so that every count of
+// rows but a multiple of 512 leaves units without work) it costs a launch and evens out rows of any number
+// and of any number of allowed tokens.  V = 151,936, everything allowed / nothing in every other row, by row
+// -> in slices, us: B = 48 10.4 -> 10.0 / 10.0 -> 8.5, B = 129 29.8 -> 18.3 / 22.8 -> 12.6, B = 256 33.4 ->
+// 31.0 / 29.8 -> 19.7, B = 300 41.9 -> 35.0 / 36.9 -> 21.9, B = 1,024 111 -> 110 / 79.8 -> 59.9; a ticket
+// in place of the second kernel kept each workgroup for two more trips to memory (B = 1,024: 167).  bf16 rows
+// are not taken so (B = 256 20.1 -> 25.1, B = 1,024 63 -> 74).
+constexpr uint32_t kChoiceThreads = 256, kChoicePieces = 8;
+constexpr uint32_t kChoiceTokens = kChoiceThreads * kChoicePieces * Row<uint32_t>::kPer;
+__global__ void __launch_bounds__(kChoiceThreads)
+argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
+                    const uint32_t *__restrict__ bitmask)
+{
+    constexpr uint32_t kPer = Row<uint32_t>::kPer, kWords = kChoiceTokens / 32u;
+    __shared__ uint32_t words[kWords];
+    __shared__ float part[kChoiceThreads / 64u];
+    __shared__ uint32_t best_token;
+    const uint32_t b = blockIdx.y, tid = threadIdx.x, base = blockIdx.x * (kChoicePieces * kChoiceThreads) + tid;
+    const Row<uint32_t> r(logits + (int64_t)b * row_stride, V);
+    static_assert(kWords == kChoiceThreads, "a mask word per thread");
+    words[tid] = mask_word(bitmask + (size_t)b * W, W, V, r.skew, blockIdx.x * kWords + tid);
+    if (tid == 0) best_token = 0xFFFFFFFFu;
+    __syncthreads();
+    uint32_t m[kChoicePieces];
+    union { uint4 v; uint32_t e[kPer]; } u[kChoicePieces];
+#pragma unroll
+    for (uint32_t j = 0; j < kChoicePieces; j++) {
+        const uint32_t bit = (j * kChoiceThreads + tid) * kPer;
+        m[j] = (words[bit >> 5] >> (bit & 31u)) & Row<uint32_t>::kAll;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kChoicePieces; j++) {
+        u[j].v = uint4{0u, 0u, 0u, 0u};
+        if (m[j]) u[j].v = r.blocks[base + j * kChoiceThreads];  // (elements lie at multiples of their size: launch_masked_argmax)
+    }
+    float best = __builtin_nanf("");
+#pragma unroll
+    for (uint32_t j = 0; j < kChoicePieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], 0u));
+    float top = best;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = __builtin_fmaxf(top, __shfl_xor(top, o));
+    if ((tid & 63u) == 0u) part[tid >> 6] = top;
+    __syncthreads();
+    top = part[0];
+#pragma unroll
+    for (uint32_t w = 1; w < kChoiceThreads / 64u; w++) top = __builtin_fmaxf(top, part[w]);
+    const bool number = top == top;
+    if (!number || best == top) {
+        // the thread's lowest token whose logit equals the maximum (as numbers, so -0.0 and +0.0 tie), or
+        // where no allowed token has a number its lowest allowed one
+        uint32_t token = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = (int)kChoicePieces - 1; j >= 0; j--) {
+            uint32_t eq = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; i++) eq |= (uint32_t)(__uint_as_float(u[j].e[i]) == top) << i;
+            eq = number ? eq & m[j] : m[j];
+            if (eq) token = r.token(base + (uint32_t)j * kChoiceThreads, (uint32_t)__builtin_ctz(eq));
+        }
+        if (token != 0xFFFFFFFFu) atomicMin(&best_token, token);
+    }
+    __syncthreads();
+    if (tid == 0 && best_token != 0xFFFFFFFFu)
+        atomicMax(&g_argmax_key[b], (unsigned long long)(number ? order_key(__float_as_uint(top)) : 0u) << 32 | (0xFFFFFFFFu - best_token));
+}
+// The choices of a batch from its rows' keys, which are left zero for the next call.
+__global__ void __launch_bounds__(64)
+argmax_finish_kernel(int32_t *__restrict__ tokens, uint32_t B)
+{
+    const uint32_t b = blockIdx.x * 64u + threadIdx.x;
+    if (b >= B) return;
+    const unsigned long long row = g_argmax_key[b];
+    tokens[b] = row ? (int32_t)(0xFFFFFFFFu - (uint32_t)row) : -1;
+    g_argmax_key[b] = 0ull;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -637,6 +718,15 @@ static uint32_t argmax_parts(uint32_t B, uint32_t V)
     return parts;
 }
 
+// fp32 rows are taken in slices (argmax_slice_kernel) from 33 rows of five slices on: with four (V = 32,000)
+// B = 256 with nothing allowed in every other row is 8.3 us by row, 9.3 in slices, with five (V = 40,000) 9.1
+// and 8.5; at B = 32, where argmax_parts still cuts rows in eight, V = 151,936 is 8.9 and 9.6, V = 128,256
+// 9.3 and 8.8.
+static bool argmax_in_slices(int dtype, uint32_t B, uint32_t V, const void *logits)
+{
+    return dtype == WG_F32 && B > 32u && V > 4u * kChoiceTokens && reinterpret_cast<uintptr_t>(logits) % 4u == 0u;
+}
+
 // The k best are taken by a workgroup per row where a row streams in about the time of the second
 // kernel, or where there are rows enough to keep the chip busy (V = 128,256 fp32, 513 KB: slices 18.1
 // against 22.3 us at B = 64, 28.5 against 26.1 at B = 128; up to 304 KB the row is never slower).
@@ -646,6 +736,12 @@ hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint3
                                 const uint32_t *bitmask, int32_t *tokens, hipStream_t s)
 {
     const uint32_t W = (V + 31u) / 32u;
+    if (argmax_in_slices(dtype, B, V, logits)) {
+        const uint32_t slices = (V + 3u + kChoiceTokens - 1u) / kChoiceTokens;         // a row may begin 3 tokens into its first piece
+        const hipError_t e = launch(argmax_slice_kernel, dim3(slices, B), dim3(kChoiceThreads), 0, s, nullptr, static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask);
+        if (e != hipSuccess) return e;
+        return launch(argmax_finish_kernel, dim3((B + 63u) / 64u), dim3(64), 0, s, nullptr, tokens, B);
+    }
     const dim3 g(argmax_parts(B, V), B);
     if (dtype == WG_F32) return launch(masked_argmax_kernel<uint32_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask, tokens);
     return launch(masked_argmax_kernel<uint16_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint16_t *>(logits), row_stride, V, W, bitmask, tokens);

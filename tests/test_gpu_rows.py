@@ -255,3 +255,43 @@ def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
         want_ids, want_vals = O.masked_topk(host, bits, k)
         assert (ids.cpu().numpy() == want_ids).all(), k
         assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
+
+
+@pytest.mark.parametrize("B,V,off", [(32, 32769, 0), (33, 32768, 0), (33, 32769, 0), (33, 32769, 3), (40, 40957, 3), (40, 40958, 3), (40, 40961, 2),
+                                     (65, 50021, 1), (129, 131072, 0), (1030, 33000, 0)])
+def test_greedy_choice_of_fp32_rows_in_slices(torch_cuda, B, V, off):
+    """Rows of five and more slices of 8,192 tokens and the sizes just below, rows that begin inside a
+    16-byte block (so that the last tokens make a slice of their own), maxima on either side of a slice's edge,
+    ties, NaNs, both zeros, rows that allow little or nothing; twice, so that no key is left behind."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    rng = np.random.default_rng(V + B + off)
+    x = rng.standard_normal((B, V)).astype(np.float32)
+    x[:, rng.integers(0, V, V // 50)] = np.nan
+    bits = rng.integers(0, 1 << 32, (B, (V + 31) // 32), dtype=np.uint32)
+    x[0] = np.round(x[0])                                           # thousands tie, zeros of both signs
+    x[1], x[2] = -np.inf, np.nan
+    x[2, V // 2] = -0.0
+    x[3] = np.nan
+    bits[4], bits[5], bits[5, -1] = 0, 0, 1
+    for r in range(6, 26):                                          # the same maximum at both sides of an edge, one or both allowed
+        t = 8192 * (1 + r % ((V - 1) // 8192)) - (r % 3)
+        x[r, [t - 1, t]] = 50.0
+        for i, u in enumerate((t - 1, t)):
+            bits[r, u // 32] |= np.uint32(1 << (u % 32))
+            if r % 5 == i:
+                bits[r, u // 32] ^= np.uint32(1 << (u % 32))
+    x[26:29, V - 1] = 60.0
+    bits[26:28, -1] |= np.uint32(1 << ((V - 1) % 32))
+    if V % 32:
+        bits[:, -1] &= np.uint32((1 << (V % 32)) - 1)
+    buf = torch.zeros((B * (V + off) + 64,), dtype=torch.float32, device="cuda")
+    view = buf[off:off + B * (V + off)].view(B, V + off)[:, :V]
+    view.copy_(torch.from_numpy(x))
+    mask = torch.from_numpy(bits.view(np.int32)).cuda()
+    tok = torch.empty(B, dtype=torch.int32, device="cuda")
+    want = O.masked_argmax(x, bits)
+    for _ in range(2):
+        tok.fill_(-7)
+        wg.masked_argmax(view, mask, tok)
+        assert (tok.cpu().numpy() == want).all(), np.flatnonzero(tok.cpu().numpy() != want)[:8]
