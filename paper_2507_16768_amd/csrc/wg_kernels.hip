@@ -999,14 +999,18 @@ static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b -
 
 // Logits of more bytes than these are masked by whole lines (see mask_span): 128 bytes are read where a
 // line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
-// depends on how many tokens of a line are disallowed, which the host does not know; the lines lie where
-// masks of 16 to 63 % disallowed tokens lose as much as they gain.  By elements / by lines, us, the kernel
-// of a cached step on 151936 tokens, 20 operator html templates and random trees:
-//   bf16, 194 MB 49 / 65 and 89 / 71, 243 MB 87 / 89 and 115 / 91, 311 MB 116 / 106 and 143 / 112
-//   fp32, 200 MB 28 / 58 and 75 / 72, 311 MB 65 / 83 and 131 / 111, 389 MB 109 / 112 and 168 / 141
-// (a block holds twice as many bf16 tokens, so fewer of them stay untouched.)  Deciding by the density
-// of each row or line was slower than the better of the two for all.
-constexpr uint64_t kLineBytes16 = 192ull << 20, kLineBytes32 = 320ull << 20;
+// depends on how many tokens of a line are disallowed, which the host does not know; the limits lie where
+// the geometric mean over four kinds of masks is the same for both.  By elements / by lines, us, a cached
+// step on the masks of html outlines, of JSON objects, of both mixed, and of random trees (16, 25, 45 and 63 %
+// of the tokens disallowed):
+//   bf16, V = 151936: 213 MB 55 / 79, 69 / 79, 97 / 84, 113 / 87; 225 MB 67 / 85, 77 / 84, 103 / 90, 110 / 89;
+//   252 MB 100 / 96, 98 / 95, 116 / 101, 129 / 102; 311 MB 127 / 118, 126 / 115, 144 / 121, 148 / 119
+//   fp32, V = 128256: 308 MB 60 / 90, 70 / 93, 113 / 104, 140 / 118; 328 MB 84 / 96, 90 / 98, 120 / 111, 146 / 125;
+//   359 MB 101 / 103, 97 / 102, 131 / 117, 152 / 126; 525 MB 153 / 145, 152 / 144, 189 / 164, 237 / 192
+// (a block holds twice as many bf16 tokens, so fewer of them stay untouched.)  So html outlines lose up to a
+// quarter right above the limit and random trees a quarter right below it.  Deciding by the density of each
+// row or line was slower than the better of the two for all.
+constexpr uint64_t kLineBytes16 = 208ull << 20, kLineBytes32 = 320ull << 20;
 
 static bool by_lines(int dtype, uint32_t B, uint32_t V)
 {
@@ -1024,11 +1028,17 @@ static uint32_t row_parts(uint32_t V, uint32_t most)
 }
 // Most workgroups per row.  8, which is what fills the chip with long rows of 256 requests; more where
 // that leaves compute units idle or with little to do, as long as a workgroup keeps enough tokens to be
-// worth what it starts with (151936 tokens, 70000 tokens, us a pass of 8 cached steps):
-//   up to a workgroup on every second unit, 4096 tokens each: B = 1 69 with 8, 58 with 16, 51 with 32;
-//   B = 4 67, 57, 57; B = 8 72, 66 with 16, 70 with 32 (70000 tokens: 60, 58, 68)
-//   above the one-kernel fill, up to 6 workgroups on a unit, 6144 tokens each: B = 64 118 with 8, 114 with
-//   16; B = 96 137, 130 (with rows to make: 212, 201; 70000 tokens no difference)
+// worth what it starts with:
+//   up to a workgroup on every second unit, 4096 tokens each (us a pass of 8 cached steps, 151936 tokens, 70000
+//   tokens): B = 1 69 with 8, 58 with 16, 51 with 32; B = 4 67, 57, 57; B = 8 72, 66 with 16, 70 with 32
+//   (70000 tokens: 60, 58, 68)
+//   above the one-kernel fill, up to 6 workgroups on a unit, 6144 tokens each.  With 8 / 16, us a step of mixed
+//   requests, rows copied and rows made: V = 151936 B = 48 13.5 / 12.3 and 22.5 / 21.3, B = 96 16.8 / 16.1 and
+//   26.7 / 26.0, B = 128 18.8 / 18.0 and 26.2 / 26.9, B = 160 21.2 / 20.2 and 29.9 / 30.7, B = 256 25.5 / 24.4 and
+//   37.5 / 43.0; V = 98304 B = 48 11.7 / 11.1 and 19.7 / 17.4, B = 96 14.1 / 13.4 and 23.1 / 21.5, B = 160 16.2 /
+//   15.6 and 25.3 / 27.4; html and JSON likewise (B = 128 -4 % and +2 to +5 %).  With fewer tokens the gain ends
+//   sooner: V = 70000 B = 48 10.6 / 10.1 and 18.7 / 17.0, B = 96 12.7 / 12.5 and 21.1 / 21.8 (random trees, fp32:
+//   34.6 / 37.0)
 constexpr uint32_t kLeastParts = 8;
 static uint32_t most_parts(uint32_t V, uint32_t B, uint32_t n_cu)
 {

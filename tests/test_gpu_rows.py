@@ -100,10 +100,10 @@ def test_masking_at_every_alignment(torch_cuda, V, dtype):
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
 
 
-@pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("f32", 400, 128256, 0), ("f32", 700, 128256, 0)])
+@pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("bf16", 740, 151936, 0), ("bf16", 741, 151900, 3), ("f32", 400, 128256, 0), ("f32", 700, 128256, 0)])
 def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, pad):
-    """More than 192 MiB of bf16 or 320 MiB of fp32 logits: lines are read where they are mixed and
-    written whole."""
+    """Either side of 208 MiB of bf16 and 320 MiB of fp32 logits; above them lines are read where they are
+    mixed and written whole."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
