@@ -11,8 +11,8 @@
 // idle whenever the rows did not come out even.
 //
 // Times for V = 151,936, bf16, the greedy choice and k = 50, before -> now (before: a workgroup per slice
-// and a second kernel always): B = 1 12.5 -> 5.9 and 13.7 -> 12.1 us, B = 64 12.2 -> 8.3 and 18.9 -> 17.9,
-// B = 256 19.5 -> 17.1 and 38.6 -> 21.8, B = 1,024 56 -> 52 and 117 -> 67.
+// and a second kernel always): B = 1 12.5 -> 5.9 and 14.6 -> 11.0 us, B = 64 12.2 -> 8.3 and 19.9 -> 18.2,
+// B = 256 19.5 -> 17.1 and 42 -> 28, B = 1,024 56 -> 52 and 117 -> 67.
 //
 // The k best need no sorting of the row: in each of n wavefronts the ceil(k / n)-th largest of the 64
 // thread maxima is found by bisection on ballots, and the least of these is a lower bound for the k-th
@@ -543,7 +543,9 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
 }
 
 // Small batches: a slice of kTopkSlice tokens of a row per workgroup of 256 threads, a thread's 32
-// tokens in registers.  The best k of the slice leave for the workspace, best first.
+// tokens in registers.  The best k of the slice leave for the workspace, best first.  What it takes is the
+// trips to memory one after the other: mask, logits, the candidates' logits again (V = 128,256 fp32, B = 8: 7.3 us
+// with k = 20, 8.2 with k = 50; 7.4 and 8.0 before the row kernel, when candidates were sorted).
 constexpr uint32_t kSliceThreads = 256;
 constexpr uint32_t kSliceWaves = kSliceThreads / 64u;
 constexpr uint32_t kSlicePer = kTopkSlice / kSliceThreads;       // tokens of a thread
@@ -553,6 +555,7 @@ static_assert(kSlicePer == 32u, "a bit per token of a thread");
 struct SliceShared {
     unsigned long long cand[kSliceCand];
     uint32_t id[kSliceCand];
+    uint32_t words[kTopkSlice / 32u + 1u];           // the staged mask
     uint32_t count[kSliceWaves];
     uint32_t n;
 };
@@ -567,33 +570,49 @@ topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t 
     const uint32_t b = blockIdx.y, tid = threadIdx.x;
     const uint32_t *mask = bitmask + (size_t)b * W;
     const Row<Elem> r(logits + (int64_t)b * row_stride, V);
-    const uint32_t base = blockIdx.x * (kTopkSlice / kPer);       // first piece of the slice
     unsigned long long *out = lists + ((size_t)b * gridDim.x + blockIdx.x) * k;
-    // (the last slice also takes the piece that a skewed row has behind a whole number of slices)
-    const uint32_t hi = blockIdx.x == gridDim.x - 1u ? r.pieces : base + kTopkSlice / kPer;
+    // Equal shares of whole mask words: a last slice of a few hundred tokens fills a wavefront or two, the
+    // others then give no bound, and all of its tokens are ranked (V = 115,001: 10 us more).  Where the
+    // row is a whole number of slices the last one also takes the piece that a skewed row has behind them.
+    constexpr uint32_t kStep = 32u / kPer;
+    const uint32_t even = ((r.pieces + gridDim.x - 1u) / gridDim.x + kStep - 1u) / kStep * kStep;
+    const uint32_t share = even < kTopkSlice / kPer ? even : kTopkSlice / kPer;
+    const uint32_t base = blockIdx.x * share < r.pieces ? blockIdx.x * share : r.pieces;      // first piece of the slice
+    const uint32_t own_pieces = blockIdx.x == gridDim.x - 1u || r.pieces - base < share ? r.pieces - base : share;
+    // the slice's mask words, and the one behind them (from memory, piece by piece, they were eight loads one
+    // after the other in front of the logits')
+    constexpr uint32_t kWords = kTopkSlice / 32u;
+    static_assert(kWords == kSliceThreads, "a mask word per thread");
+    const uint32_t first_word = base / kStep;
+    sh.words[tid] = mask_word(mask, W, V, r.skew, first_word + tid);
+    if (tid == 0) { sh.words[kWords] = mask_word(mask, W, V, r.skew, first_word + kWords); sh.n = 0u; }
+    __syncthreads();
     uint32_t m[kPieces];
     union { uint4 v; Elem e[kPer]; } u[kPieces];
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) {
-        const uint32_t p = base + j * kSliceThreads + tid;
-        m[j] = p < hi ? piece_mask(r, mask, W, p) : 0u;
+        const uint32_t q = j * kSliceThreads + tid, bit = q * kPer;
+        m[j] = q < own_pieces ? (sh.words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : 0u;
     }
     const uint32_t extra = base + kTopkSlice / kPer + tid;        // at most one such piece
-    const uint32_t m_extra = extra < hi ? piece_mask(r, mask, W, extra) : 0u;
+    const uint32_t m_extra = kTopkSlice / kPer + tid < own_pieces ? sh.words[kWords] & Row<Elem>::kAll : 0u;
     float best = __builtin_nanf("");
     uint32_t any = m_extra;
 #pragma unroll
-    for (uint32_t j = 0; j < kPieces; j++) {
-        u[j].v = uint4{0u, 0u, 0u, 0u};
-        if (m[j]) u[j].v = r.load(base + j * kSliceThreads + tid, m[j]);
-        any |= m[j];
-    }
+    for (uint32_t j = 0; j < kPieces; j++) { u[j].v = uint4{0u, 0u, 0u, 0u}; any |= m[j]; }
     uint4 v_extra = uint4{0u, 0u, 0u, 0u};
-    if (m_extra) v_extra = r.load(extra, m_extra);
+    if (r.whole) {
+#pragma unroll
+        for (uint32_t j = 0; j < kPieces; j++) if (m[j]) u[j].v = r.blocks[base + j * kSliceThreads + tid];
+        if (m_extra) v_extra = r.blocks[extra];
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < kPieces; j++) if (m[j]) u[j].v = r.load(base + j * kSliceThreads + tid, m[j]);
+        if (m_extra) v_extra = r.load(extra, m_extra);
+    }
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], Elem(0)));
     if (m_extra) best = __builtin_fmaxf(best, piece_max(v_extra, m_extra, Elem(0)));
-    if (tid == 0) sh.n = 0u;
     const uint32_t own = best == best ? order_key(__float_as_uint(best)) + 1u : any ? 1u : 0u;
     const uint32_t bound = bound_of<kSliceWaves>(own, k, sh.count);
     const float value = bound_value(bound);
@@ -646,24 +665,31 @@ topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t 
     for (uint32_t i = n + tid; i < k; i += kSliceThreads) out[i] = 0ull;
 }
 
-// A row's slices merged: the same bound and count on the keys that they left.
-template <typename Elem>
+// A row's slices merged: the same bound and count on the keys that they left, kHeld of a thread at most.  Its
+// time is code fetched and a few trips to LDS and memory: unrolled for 16 keys of a thread always, it was 8.8
+// us for V = 128,256, k = 50 (3.1 to 4 keys of a thread), now 4.4.
+template <typename Elem, uint32_t kHeld>
 __global__ void __launch_bounds__(kSliceThreads)
 topk_merge_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t n_slices, uint32_t k,
                   const unsigned long long *__restrict__ lists, int32_t *__restrict__ ids, Elem *__restrict__ values, Elem ninf)
 {
-    constexpr uint32_t kHeld = kTopkMergeKeys / kSliceThreads;    // most keys of a thread
-    __shared__ unsigned long long cand[kTopkMergeKeys];
+    __shared__ unsigned long long cand[kHeld * kSliceThreads];
     __shared__ uint32_t count[kSliceWaves], n_cand;
     const uint32_t b = blockIdx.x, tid = threadIdx.x, n = n_slices * k;
+    // In order of rank, the slices' best first, and in turn to the wavefronts: then the thread maxima are about
+    // the 256 best, every wavefront has as many good ones as another, and hardly more than k keys reach the
+    // bound.  (In the order of the lists a lane held one rank, where k is 64, and hundreds of keys reached it:
+    // 15.2 us instead of 8.5 for B = 8, V = 151,936 fp32, before the kernel was cut to size.)
     unsigned long long x[kHeld];
     uint32_t own = 0;
+    const uint32_t place = (tid & 63u) * kSliceWaves + (tid >> 6);
 #pragma unroll
     for (uint32_t j = 0; j < kHeld; j++) {
-        const uint32_t i = tid + j * kSliceThreads;
+        const uint32_t i = place + j * kSliceThreads;
         x[j] = 0ull;
         if (j * kSliceThreads >= n) continue;
-        if (i < n) x[j] = lists[(size_t)b * n + i];
+        const uint32_t rank = i / n_slices;
+        if (i < n) x[j] = lists[(size_t)b * n + (i - rank * n_slices) * k + rank];
     }
 #pragma unroll
     for (uint32_t j = 0; j < kHeld; j++) { const uint32_t h = (uint32_t)(x[j] >> 32); own = h > own ? h : own; }
@@ -727,10 +753,21 @@ static bool argmax_in_slices(int dtype, uint32_t B, uint32_t V, const void *logi
     return dtype == WG_F32 && B > 32u && V > 4u * kChoiceTokens && reinterpret_cast<uintptr_t>(logits) % 4u == 0u;
 }
 
-// The k best are taken by a workgroup per row where a row streams in about the time of the second
-// kernel, or where there are rows enough to keep the chip busy (V = 128,256 fp32, 513 KB: slices 18.1
-// against 22.3 us at B = 64, 28.5 against 26.1 at B = 128; up to 304 KB the row is never slower).
-static bool topk_by_row(uint32_t B, uint64_t row_bytes) { return row_bytes <= (320u << 10) || B >= 96u; }
+// The k best are taken by a workgroup per row where the row is short, or where there are rows enough to keep
+// the chip busy: a slice of fp32 is twice the bytes for what it costs besides, so fp32 rows are cut longer; and
+// what it costs grows with k.  Slices / by row, everything allowed, k = 20, 50, 64:
+//   fp32, V = 32000 1.04 to 1.34 for B = 1 to 256; 50021 B = 24 0.84 0.92 1.02, 64 0.88 1.00 1.07, 96 0.92 1.05 1.08;
+//   64000 B = 24 0.75 0.86 0.93, 64 0.84 0.95 1.03, 128 0.94 1.03 1.11; 84000 B = 96 0.81 0.90 1.00, 160 0.85 0.94
+//   1.00, 192 0.90 0.96 1.02; 100003 B = 24 0.62 0.67 0.77, 192 0.84 0.90 0.96, 256 0.91 0.96 1.02; 128256 B = 24 0.55
+//   0.61 0.69, 256 0.90 0.96 1.01 (nothing in every other row: 0.91 1.02 1.08); 151936 B = 24 0.47 0.55 0.63
+//   bf16, V = 64000 0.97 to 1.28; 100003 B = 24 0.85 0.95 1.08, 64 0.95 1.00 1.13; 128256 B = 24 0.76 0.89 0.96, 48 0.78
+//   0.92 1.00, 64 0.85 0.99 1.11; 151936 B = 24 0.69 0.81 0.92, 64 0.83 0.93 1.08, 96 1.03 1.17 1.25
+static bool topk_by_row(uint32_t B, uint32_t V, uint32_t k, uint32_t elem_bytes)
+{
+    if (V < (elem_bytes == 2u ? 14u : 6u) * kTopkSlice) return true;
+    const uint32_t rows = elem_bytes == 2u ? 64u : V < 10u * kTopkSlice ? 96u : V < 14u * kTopkSlice ? 192u : 256u;
+    return B >= (k > 50u ? rows / 2u : rows);
+}
 
 hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,
                                 const uint32_t *bitmask, int32_t *tokens, hipStream_t s)
@@ -752,12 +789,15 @@ static hipError_t topk(const Elem *logits, uint32_t B, uint32_t V, int64_t row_s
                        int32_t *ids, Elem *values, Elem ninf, unsigned long long *lists, hipStream_t s)
 {
     const uint32_t W = (V + 31u) / 32u;
-    if (topk_by_row(B, (uint64_t)V * sizeof(Elem)))
+    if (topk_by_row(B, V, k, sizeof(Elem)))
         return launch(masked_topk_kernel<Elem>, dim3(B), dim3(kThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, ids, values, ninf);
     const uint32_t n_slices = (V + kTopkSlice - 1u) / kTopkSlice;
     const hipError_t e = launch(topk_slice_kernel<Elem>, dim3(n_slices, B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, lists);
     if (e != hipSuccess) return e;
-    return launch(topk_merge_kernel<Elem>, dim3(B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, n_slices, k, lists, ids, values, ninf);
+    constexpr uint32_t kMost = kTopkMergeKeys / kSliceThreads;
+    const uint32_t held = (n_slices * k + kSliceThreads - 1u) / kSliceThreads;
+    return launch(held <= 4u ? topk_merge_kernel<Elem, 4> : held <= 8u ? topk_merge_kernel<Elem, 8> : topk_merge_kernel<Elem, kMost>, dim3(B), dim3(kSliceThreads), 0, s,
+                  nullptr, logits, row_stride, n_slices, k, lists, ids, values, ninf);
 }
 
 hipError_t launch_masked_topk(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,

@@ -215,7 +215,9 @@ def test_decode_step_of_a_large_batch(torch_cuda, dtype, stride_pad):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("B,V,off", [(1, 33, 0), (3, 8193, 1), (130, 5000, 3), (2, 90001, 0), (97, 90001, 5), (40, 151936, 0), (3, 300007, 1)])
+@pytest.mark.parametrize("B,V,off", [(1, 33, 0), (3, 8193, 1), (130, 5000, 3), (2, 90001, 0), (97, 90001, 5), (40, 151936, 0), (3, 300007, 1),
+                                     (5, 90112, 3), (5, 90109, 3), (95, 90110, 2), (8, 49151, 0), (8, 49152, 1), (47, 50021, 0), (95, 50021, 0), (96, 50021, 0),
+                                     (31, 114688, 1), (63, 114689, 0), (64, 114689, 0), (191, 90001, 1), (192, 90001, 1)])
 def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
     """masked_argmax and masked_topk where rows are cut and where they are not, at any alignment, with
     ties (as many as tie-breaking by token id decides), NaNs, both zeros, -inf and rows that allow
