@@ -329,7 +329,9 @@ static int create_vocab(const uint8_t *host_bytes, const uint64_t *host_offsets,
         }
     }
     // the token rows, likewise
-    std::vector<uint32_t> rows(ix.byte_rows.begin(), ix.byte_rows.begin() + (size_t)kBlockRow * ix.row_stride);
+    std::vector<uint32_t> rows;
+    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size());
+    rows.insert(rows.end(), ix.byte_rows.begin(), ix.byte_rows.end());
     rows.insert(rows.end(), ix.block_rows.begin(), ix.block_rows.end());
     rows.insert(rows.end(), ix.tail_rows.begin(), ix.tail_rows.end());
     hipError_t e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());

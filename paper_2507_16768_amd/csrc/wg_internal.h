@@ -48,26 +48,6 @@ struct Table {
 constexpr uint32_t kParts = 32;
 constexpr uint32_t kPartGroup = 2048;
 
-// What the kernels want to know about a class table without reading its 256 bytes: the bytes
-// that leave through exit A / exit B (as long as there are at most kMaxExitBytes of them on a
-// side), which first look the class scan takes, and the folded set of byte values that do not stay.
-constexpr uint32_t kMaxExitBytes = 6;
-struct ClassInfo {
-    uint8_t n_a, n_b;            // bytes of class EXIT_A / EXIT_B, or 0xFF: more than kMaxExitBytes
-    uint8_t scan, pad;           // SCAN_*: how class_scan takes its first look at a token
-    uint8_t a[kMaxExitBytes], b[kMaxExitBytes];
-    unsigned long long nonstay;  // SCAN_SIG: bit (x & 63) for every byte value x that does not stay (never 0)
-    unsigned long long pad2;
-};
-static_assert(sizeof(ClassInfo) == 32, "class info layout");
-// The first look class_scan takes at a token, chosen by what the table does with most bytes:
-//   SCAN_SIG   nearly every byte value stays (a free-text Wait): a token none of whose bytes folds
-//              onto a byte value that does not stay is all-stay, by one AND with its signature;
-//   SCAN_HEAD  most byte values are rejected (an allow list): the first byte decides most tokens;
-//   SCAN_CHUNK anything between: the first 8 bytes through the table.
-enum : uint8_t { SCAN_CHUNK = 0, SCAN_SIG = 1, SCAN_HEAD = 2 };
-constexpr uint8_t kManyExits = 0xFF;
-
 // How the rows of a class table's states are made, worked out once per table.  A table that at most
 // kFewLive byte values enter is taken by first byte: ids[0 .. n_exits) are those values, value |
 // class << 8.  Any other table is taken by token rows: ids[0 .. n_exits) are its exit bytes (value
@@ -97,11 +77,8 @@ static_assert(sizeof(ExitEntry) == 8, "entry layout");
 struct VocabIndex {
     uint32_t V = 0, W = 0, row_stride = 0, lmax = 0, n_chunks = 0;
     uint32_t part_tok[kParts + 1] = {};    // first token of each range; part_tok[kParts] == V
-    std::vector<uint8_t> bytes;            // the token bytes, 8 zero bytes behind them
-    std::vector<uint32_t> offsets;         // V + 1
-    std::vector<uint8_t> len8, first8;     // per token
+    std::vector<uint8_t> len8;             // per token
     std::vector<uint64_t> chunks;          // max(n_chunks, 1) * V
-    std::vector<uint64_t> sig;             // per token
     std::vector<ExitEntry> lit_entries;    // never empty (one unused entry when no token has bytes)
     std::vector<uint32_t> lit_start;       // 256 * kParts + 1
     std::vector<uint32_t> len_rows;        // (lmax + 2) * row_stride
@@ -109,7 +86,7 @@ struct VocabIndex {
     std::vector<uint32_t> dir0;            // 256 * 257 + 1
     std::vector<ExitEntry> bigram;         // never empty
     std::vector<uint32_t> dirN;            // 65536 + 1
-    std::vector<uint32_t> byte_rows;       // 512 rows of row_stride words: 256 by any byte, 256 by the first byte
+    std::vector<uint32_t> byte_rows;       // 256 rows of row_stride words: tokens that contain the byte
     std::vector<uint32_t> block_rows;      // 64 + 16 rows: by any byte of a block of 4, of 16 byte values
     std::vector<uint32_t> tail_rows;       // 256 rows: tokens in which the byte occurs once, as the last one
     std::vector<ExitEntry> places;         // the byte pairs again, by (first byte of the pair, range); never empty
@@ -120,9 +97,6 @@ struct VocabIndex {
 // an error code with the message in *err; `out` is then unspecified.
 int build_vocab_index(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, int32_t eos_id,
                       VocabIndex *out, std::string *err);
-
-// The summary of one 256-byte class table that the kernels read in its place.
-ClassInfo class_info_of(const uint8_t *table);
 
 // The host operator compiler with its memory: parsed template texts (the static structures)
 // and the class tables seen so far, so that instances can be added to a live table.

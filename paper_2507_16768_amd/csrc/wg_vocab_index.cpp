@@ -1,4 +1,4 @@
-// The static indexes of a vocabulary and the summaries of class tables: host code without any
+// The static indexes of a vocabulary and the plans of class tables: host code without any
 // device call, so that it can also be built and checked on its own.
 #include <algorithm>
 #include <cstring>
@@ -7,25 +7,6 @@
 #include "wg_internal.h"
 
 namespace wg {
-
-ClassInfo class_info_of(const uint8_t *table) {
-    ClassInfo ci{};
-    uint32_t n_a = 0, n_b = 0, live = 0;
-    unsigned long long nonstay = 0;
-    for (uint32_t x = 0; x < 256; x++) {
-        const uint8_t c = table[x];
-        live += c != CLS_REJECT;
-        if (c != CLS_STAY) nonstay |= 1ull << (x & 63u);
-        if (c == CLS_EXIT_A) { if (n_a < kMaxExitBytes) ci.a[n_a] = (uint8_t)x; n_a++; }
-        if (c == CLS_EXIT_B) { if (n_b < kMaxExitBytes) ci.b[n_b] = (uint8_t)x; n_b++; }
-    }
-    ci.n_a = n_a > kMaxExitBytes ? kManyExits : (uint8_t)n_a;
-    ci.n_b = n_b > kMaxExitBytes ? kManyExits : (uint8_t)n_b;
-    // (a byte-less token's signature is all ones: any mask but 0 sends it to the second pass)
-    ci.nonstay = nonstay ? nonstay : 1ull << 63;
-    ci.scan = live <= 64 ? SCAN_HEAD : __builtin_popcountll(ci.nonstay) <= 8 ? SCAN_SIG : SCAN_CHUNK;
-    return ci;
-}
 
 ClassPlan class_plan_of(const uint8_t *table) {
     ClassPlan p{};
@@ -73,12 +54,11 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
     const uint32_t W = (V + 31u) / 32u, rs = (W + 3u) & ~3u;
     const uint32_t n_chunks = (lmax + 7u) / 8u;
     // Static indexes of the vocabulary (they depend on the token bytes only):
-    //  - 8 bytes of padding so kernels may over-read a token's tail
-    //  - len8 / chunks: fixed-stride view, 8 bytes per load, for the class scan
+    //  - len8 / chunks: fixed-stride view, 8 bytes per load, for the walks
     //  - first-byte buckets (per token range): the only tokens a literal state can admit
     //  - per-length rows: tokens with 1 <= length <= r, for Waits with a byte budget
-    std::vector<uint8_t> bytes(total + 8, 0), len8(V, 0);
-    if (total) std::memcpy(bytes.data(), host_bytes, total);
+    std::vector<uint8_t> len8(V, 0), part(V, 0);
+    const uint8_t *const bytes = host_bytes;
     std::vector<uint64_t> chunks((size_t)(n_chunks ? n_chunks : 1) * V, 0);
     std::vector<uint32_t> lit_start(256 * kParts + 1, 0), len_rows((size_t)(lmax + 2) * rs, 0);
     // the token ranges that can split the work of one mask row
@@ -88,27 +68,17 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
         const uint64_t t0 = ((uint64_t)p * n_groups / kParts) * kPartGroup;
         part_tok[p] = (p == kParts || t0 > V) ? V : (uint32_t)t0;
     }
-    auto part_of = [&](uint32_t t) {
-        uint32_t p = 0;
+    for (uint32_t t = 0, p = 0; t < V; t++) {
         while (p + 1 < kParts && t >= part_tok[p + 1]) p++;
-        return p;
-    };
-    //  - sig / first8: one AND, or one table look-up, decides most tokens in the class scan
-    std::vector<uint64_t> sig(V, ~0ull);
-    std::vector<uint8_t> first8(V, 0);
+        part[t] = (uint8_t)p;
+    }
     for (uint32_t t = 0; t < V; t++) {
         uint32_t L = ((int64_t)t == eos_id) ? 0u : off[t + 1] - off[t];
         len8[t] = (uint8_t)L;
-        if (L) {
-            uint64_t m = 0;
-            for (uint32_t i = 0; i < L; i++) m |= 1ull << (bytes[off[t] + i] & 63u);
-            sig[t] = m;
-            first8[t] = bytes[off[t]];
-        }
         for (uint32_t i = 0; i < L; i++)
             chunks[(size_t)(i / 8u) * V + t] |= (uint64_t)bytes[off[t] + i] << (8u * (i % 8u));
         if (L) {
-            lit_start[bytes[off[t]] * kParts + part_of(t) + 1u]++;
+            lit_start[bytes[off[t]] * kParts + part[t] + 1u]++;
             for (uint32_t r = L; r <= lmax + 1u; r++) len_rows[(size_t)r * rs + (t >> 5)] |= 1u << (t & 31u);
         }
     }
@@ -117,19 +87,17 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
     // wavefront walk remainders of similar length.
     std::vector<ExitEntry> lit_entries(lit_start[256 * kParts] ? lit_start[256 * kParts] : 1);
     {
-        std::vector<uint32_t> order;
-        order.reserve(V);
-        for (uint32_t t = 0; t < V; t++) if (len8[t]) order.push_back(t);
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
-            const uint32_t fa = bytes[off[a]] * kParts + part_of(a), fb = bytes[off[b]] * kParts + part_of(b);
-            return fa != fb ? fa < fb : len8[a] < len8[b];
-        });
-        for (size_t i = 0; i < order.size(); i++) {
-            const uint32_t t = order[i], L = len8[t];
+        // (counting sorts, by length and then by bucket)
+        std::vector<uint32_t> by_len(lmax + 2u, 0), order(lit_start[256 * kParts]), at(lit_start.begin(), lit_start.end() - 1);
+        for (uint32_t t = 0; t < V; t++) if (len8[t]) by_len[len8[t] + 1u]++;
+        for (uint32_t r = 0; r <= lmax; r++) by_len[r + 1u] += by_len[r];
+        for (uint32_t t = 0; t < V; t++) if (len8[t]) order[by_len[len8[t]]++] = t;
+        for (const uint32_t t : order) {
+            const uint32_t L = len8[t];
             ExitEntry e;
             e.tok = t; e.off = 1; e.cls = CLS_EXIT_A;
             e.first = L > 1 ? bytes[off[t] + 1] : 0; e.rem = (uint8_t)(L - 1);
-            lit_entries[i] = e;
+            lit_entries[at[bytes[off[t]] * kParts + part[t]]++] = e;
         }
     }
     // The vocabulary in byte order (the prefix-indexed view of it): a literal state admits the
@@ -143,7 +111,7 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
         for (uint32_t t = 0; t < V; t++) if (len8[t]) order.push_back(t);
         std::sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
             const uint32_t la = len8[a], lb = len8[b];
-            const int c = std::memcmp(bytes.data() + off[a], bytes.data() + off[b], la < lb ? la : lb);
+            const int c = std::memcmp(bytes + off[a], bytes + off[b], la < lb ? la : lb);
             return c != 0 ? c < 0 : la != lb ? la < lb : a < b;
         });
         sorted.resize(order.size() ? order.size() : 1);
@@ -175,13 +143,11 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
                 bigram[at[(uint32_t)bytes[off[t] + i - 1] << 8 | bytes[off[t] + i]]++] = e;
             }
     }
-    // The vocabulary by byte value, as rows of tokens (which tokens contain the byte x, which start
-    // with it): a class table's first look at 32 tokens is then the OR of a few words.
-    std::vector<uint32_t> byte_rows((size_t)512 * rs, 0);
-    for (uint32_t t = 0; t < V; t++) {
+    // The vocabulary by byte value, as rows of the tokens that contain it: what a class table does with 32
+    // tokens is then the OR of a few words.
+    std::vector<uint32_t> byte_rows((size_t)256 * rs, 0);
+    for (uint32_t t = 0; t < V; t++)
         for (uint32_t i = 0; i < len8[t]; i++) byte_rows[(size_t)bytes[off[t] + i] * rs + (t >> 5)] |= 1u << (t & 31u);
-        if (len8[t]) byte_rows[(size_t)(256u + first8[t]) * rs + (t >> 5)] |= 1u << (t & 31u);
-    }
     // Blocks of 4 and of 16 byte values: a set of byte values is the OR of the blocks it holds whole
     // and of the single rows of the rest, so that an allow list's complement is a few dozen rows.
     std::vector<uint32_t> block_rows((size_t)80 * rs, 0);
@@ -197,19 +163,19 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
         const uint32_t L = len8[t];
         if (!L) continue;
         const uint8_t last = bytes[off[t] + L - 1u];
-        if (!std::memchr(bytes.data() + off[t], last, L - 1u)) tail_rows[(size_t)last * rs + (t >> 5)] |= 1u << (t & 31u);
+        if (!std::memchr(bytes + off[t], last, L - 1u)) tail_rows[(size_t)last * rs + (t >> 5)] |= 1u << (t & 31u);
     }
     // The pairs again by their first byte and token range: what a checkpoint whose exit byte leads
     // to another checkpoint has to look at, each range's share apart.
     std::vector<uint32_t> place_start(256 * kParts + 1, 0);
     for (uint32_t t = 0; t < V; t++)
-        for (uint32_t i = 1; i < len8[t]; i++) place_start[(uint32_t)bytes[off[t] + i - 1] * kParts + part_of(t) + 1u]++;
+        for (uint32_t i = 1; i < len8[t]; i++) place_start[(uint32_t)bytes[off[t] + i - 1] * kParts + part[t] + 1u]++;
     for (uint32_t y = 0; y < 256 * kParts; y++) place_start[y + 1] += place_start[y];
     std::vector<ExitEntry> places(bigram.size());
     {
         std::vector<uint32_t> at(place_start.begin(), place_start.end() - 1);
         for (uint32_t t = 0; t < V; t++) {
-            const uint32_t p = part_of(t);
+            const uint32_t p = part[t];
             for (uint32_t i = 1; i < len8[t]; i++) {
                 ExitEntry e;
                 e.tok = t; e.off = (uint8_t)i; e.cls = 0; e.first = bytes[off[t] + i]; e.rem = (uint8_t)(len8[t] - i);
@@ -220,12 +186,10 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
     VocabIndex &ix = *out;
     ix.V = V; ix.W = W; ix.row_stride = rs; ix.lmax = lmax; ix.n_chunks = n_chunks;
     for (uint32_t p = 0; p <= kParts; p++) ix.part_tok[p] = part_tok[p];
-    ix.bytes.swap(bytes); ix.offsets.swap(off); ix.len8.swap(len8); ix.first8.swap(first8);
-    ix.chunks.swap(chunks); ix.sig.swap(sig); ix.lit_entries.swap(lit_entries); ix.lit_start.swap(lit_start);
+    ix.len8.swap(len8); ix.chunks.swap(chunks); ix.lit_entries.swap(lit_entries); ix.lit_start.swap(lit_start);
     ix.len_rows.swap(len_rows); ix.sorted.swap(sorted); ix.dir0.swap(dir0); ix.bigram.swap(bigram);
     ix.dirN.swap(dirN); ix.byte_rows.swap(byte_rows);
     ix.block_rows.swap(block_rows); ix.tail_rows.swap(tail_rows); ix.places.swap(places); ix.place_start.swap(place_start);
-
     return WG_OK;
 }
 

@@ -1,7 +1,7 @@
 // Sanitizer driver for the host code (test infrastructure): runs the library's operator
 // compiler and regular-expression translator, and the C oracle, over a case file, all built with
 // -fsanitize=address,undefined, and checks that the two compilers agree on the state count.
-// The library's vocabulary indexes and class-table summaries are built under the same sanitizers.
+// The library's vocabulary indexes and class-table plans are built under the same sanitizers.
 // Case file, one record per line, fields separated by a space, byte strings in hex ("-" = empty):
 //   V <bytes> <off0,off1,...> <eos_id>     vocabulary for the oracle's masks
 //   C <flags> <lmax>                       start a case
@@ -11,7 +11,7 @@
 //   R <regex>                              translate, then compile the result in both
 //   I                                      build the static indexes of the last vocabulary and check each
 //                                          against its definition, recounted here token by token
-// After every compile the summary of each new class table is checked against the table itself.
+// After every compile the plan of each new class table is checked against the table itself.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -84,22 +84,16 @@ static void check_index(const uint8_t *vb, const uint64_t *off, uint32_t V, int3
         EXPECT(ix.part_tok[p] <= ix.part_tok[p + 1] && (ix.part_tok[p] % kPartGroup == 0 || ix.part_tok[p] == V), "range %u", p);
     auto part_of = [&](uint32_t t) { uint32_t p = 0; while (!(ix.part_tok[p] <= t && t < ix.part_tok[p + 1])) p++; return p; };
     // per-token views
-    EXPECT(ix.bytes.size() == off[V] + 8 && ix.offsets.size() == V + 1 && ix.len8.size() == V && ix.first8.size() == V &&
-           ix.sig.size() == V && ix.chunks.size() == (size_t)std::max(1u, ix.n_chunks) * V, "array sizes");
-    for (size_t i = 0; i < ix.bytes.size(); i++) EXPECT(ix.bytes[i] == (i < off[V] ? vb[i] : 0), "bytes %zu", i);
+    EXPECT(ix.len8.size() == V && ix.chunks.size() == (size_t)std::max(1u, ix.n_chunks) * V, "array sizes");
     for (uint32_t t = 0; t < V; t++) {
         const uint32_t L = len(t);
-        EXPECT(ix.offsets[t] == off[t] && ix.len8[t] == L && ix.first8[t] == (L ? byte_at(t, 0) : 0), "token %u", t);
-        uint64_t m = 0;
-        for (uint32_t i = 0; i < L; i++) m |= 1ull << (byte_at(t, i) % 64);
-        EXPECT(ix.sig[t] == (L ? m : ~0ull), "sig %u", t);
+        EXPECT(ix.len8[t] == L, "token %u", t);
         for (uint32_t k = 0; k < ix.n_chunks; k++)
             for (uint32_t j = 0; j < 8; j++) {
                 const uint8_t want = 8 * k + j < L ? byte_at(t, 8 * k + j) : 0;
                 EXPECT((uint8_t)(ix.chunks[(size_t)k * V + t] >> (8 * j)) == want, "chunk %u %u %u", t, k, j);
             }
     }
-    EXPECT(ix.offsets[V] == off[V], "last offset");
     // rows of tokens no longer than r
     EXPECT(ix.len_rows.size() == (size_t)(lmax + 2) * ix.row_stride, "len_rows size");
     for (uint32_t r = 0; r <= lmax + 1; r++)
@@ -164,45 +158,71 @@ static void check_index(const uint8_t *vb, const uint64_t *off, uint32_t V, int3
             }
         }
     }
-    // the vocabulary by byte value as token rows: tokens that contain the byte, tokens that start with it
-    EXPECT(ix.byte_rows.size() == (size_t)512 * ix.row_stride, "byte rows size");
+    // the same pairs by their first byte and token range
+    EXPECT(ix.place_start.size() == 256 * kParts + 1 && ix.place_start[0] == 0 && ix.place_start.back() == pairs &&
+           ix.places.size() == std::max<uint64_t>(1, pairs), "place sizes");
     {
-        std::vector<uint32_t> want((size_t)512 * ix.row_stride, 0);
-        for (uint32_t t = 0; t < V; t++)
-            for (uint32_t i = 0; i < len(t); i++) {
-                want[(size_t)byte_at(t, i) * ix.row_stride + t / 32] |= 1u << (t % 32);
-                if (i == 0) want[(size_t)(256 + byte_at(t, 0)) * ix.row_stride + t / 32] |= 1u << (t % 32);
+        std::set<std::pair<uint32_t, uint32_t>> seen;
+        for (uint32_t y = 0; y < 256 * kParts; y++) {
+            EXPECT(ix.place_start[y] <= ix.place_start[y + 1], "place_start %u", y);
+            for (uint32_t i = ix.place_start[y]; i < ix.place_start[y + 1]; i++) {
+                const ExitEntry e = ix.places[i];
+                EXPECT(e.tok < V && e.off >= 1 && e.off < len(e.tok), "place %u", i);
+                EXPECT(seen.insert({e.tok, e.off}).second, "place twice %u", i);
+                EXPECT(byte_at(e.tok, e.off - 1u) == y / kParts && part_of(e.tok) == y % kParts, "place range %u", i);
+                EXPECT(e.cls == 0 && e.first == byte_at(e.tok, e.off) && e.rem == len(e.tok) - e.off, "place fields %u", i);
             }
-        for (size_t i = 0; i < want.size(); i++) EXPECT(ix.byte_rows[i] == want[i], "byte row %zu word %zu", i / ix.row_stride, i % ix.row_stride);
+        }
+    }
+    // token rows: tokens that contain a byte value, one of a block of 4 or of 16, and those in which a byte value
+    // occurs once, as the last byte
+    {
+        const size_t rs = ix.row_stride;
+        EXPECT(ix.byte_rows.size() == 256 * rs && ix.block_rows.size() == 80 * rs && ix.tail_rows.size() == 256 * rs, "token row sizes");
+        std::vector<uint32_t> want(592 * rs, 0);
+        for (uint32_t t = 0; t < V; t++) {
+            uint32_t count[256] = {};
+            for (uint32_t i = 0; i < len(t); i++) count[byte_at(t, i)]++;
+            for (uint32_t x = 0; x < 256; x++)
+                if (count[x])
+                    for (uint32_t row : {x, 256 + x / 4, 320 + x / 16, count[x] == 1 && byte_at(t, len(t) - 1) == x ? 336 + x : x})
+                        want[row * rs + t / 32] |= 1u << (t % 32);
+        }
+        static_assert(kBlockRow == 256 && kBigBlockRow == 320 && kTailRow == 336, "rows in the order they lie in on the device");
+        for (size_t i = 0; i < want.size(); i++) {
+            const size_t r = i / rs;
+            const uint32_t is = r < 256 ? ix.byte_rows[i] : r < 336 ? ix.block_rows[i - 256 * rs] : ix.tail_rows[i - 336 * rs];
+            EXPECT(is == want[i], "token row %zu word %zu", r, i % rs);
+        }
     }
     std::printf("index ok %u %u %llu\n", V, with_bytes, (unsigned long long)pairs);
 }
 
-// The summaries of the class tables from `first` on, each against its 256 bytes.
-static void check_class_info(const wg::Table &t, size_t first) {
+// The plans of the class tables from `first` on, each against its 256 bytes: which byte values it names, and
+// that the rows behind the exits stand for the rejected values, each once, and no others.
+static void check_class_plans(const wg::Table &t, size_t first) {
     using namespace wg;
     for (size_t c = first; c < t.classes.size() / 256; c++) {
         const uint8_t *tab = t.classes.data() + c * 256;
-        const ClassInfo ci = class_info_of(tab);
-        uint32_t cnt[4] = {0, 0, 0, 0};
-        unsigned long long fold = 0;
-        for (uint32_t x = 0; x < 256; x++) {
-            EXPECT(tab[x] < 4, "class byte");
-            cnt[tab[x]]++;
-            if (tab[x] != CLS_STAY) fold |= 1ull << (x % 64);
+        const ClassPlan p = class_plan_of(tab);
+        uint32_t live = 0, named[256] = {};
+        for (uint32_t x = 0; x < 256; x++) { EXPECT(tab[x] < 4, "class byte"); live += tab[x] != CLS_REJECT; }
+        EXPECT(p.by_first == (live <= kFewLive) && p.n_exits <= p.n_ids && p.n_ids <= 256, "plan of %zu", c);
+        EXPECT(!p.by_first || p.n_ids == p.n_exits, "rows of %zu", c);
+        for (uint32_t i = 0; i < p.n_exits; i++) {
+            const uint32_t x = p.ids[i] & 0xFFu;
+            EXPECT(p.ids[i] >> 8 == tab[x] && tab[x] >= (p.by_first ? CLS_STAY : CLS_EXIT_A), "exit %u of %zu", i, c);
+            named[x]++;
         }
-        EXPECT(ci.nonstay != 0 && (fold ? ci.nonstay == fold : true), "nonstay of %zu", c);
-        EXPECT(ci.scan == SCAN_CHUNK || ci.scan == SCAN_SIG || ci.scan == SCAN_HEAD, "scan of %zu", c);
-        const uint8_t n[2] = {ci.n_a, ci.n_b};
-        const uint8_t *lists[2] = {ci.a, ci.b};
-        for (int side = 0; side < 2; side++) {
-            const uint32_t have = cnt[side ? CLS_EXIT_B : CLS_EXIT_A];
-            EXPECT(n[side] == (have > kMaxExitBytes ? kManyExits : have), "exit count of %zu", c);
-            if (n[side] == kManyExits) continue;
-            for (uint32_t i = 0; i < n[side]; i++) {
-                EXPECT(tab[lists[side][i]] == (side ? CLS_EXIT_B : CLS_EXIT_A), "exit byte of %zu", c);
-                EXPECT(i == 0 || lists[side][i - 1] < lists[side][i], "exit order of %zu", c);
-            }
+        for (uint32_t i = p.n_exits; i < p.n_ids; i++) {
+            const uint32_t id = p.ids[i], lo = id < kBlockRow ? id : id < kBigBlockRow ? 4 * (id - kBlockRow) : 16 * (id - kBigBlockRow);
+            const uint32_t n = id < kBlockRow ? 1 : id < kBigBlockRow ? 4 : 16;
+            EXPECT(id < kTailRow, "row id of %zu", c);
+            for (uint32_t x = lo; x < lo + n; x++) { EXPECT(tab[x] == CLS_REJECT, "row %u of %zu", id, c); named[x]++; }
+        }
+        for (uint32_t x = 0; x < 256; x++) {
+            const uint32_t want = p.by_first ? tab[x] != CLS_REJECT : tab[x] != CLS_STAY;
+            EXPECT(named[x] == want, "byte %u of %zu", x, c);
         }
     }
 }
@@ -228,7 +248,7 @@ static void compile_both(wg::Lowering &low, const Pending &p, uint32_t flags, co
     const size_t before = low.table.states.size(), classes_before = low.table.classes.size() / 256;
     bool lib_ok = true;
     try { low.add(texts.data(), a.data(), n); } catch (const std::exception &) { lib_ok = false; }
-    check_class_info(low.table, lib_ok ? classes_before : 0);
+    check_class_plans(low.table, lib_ok ? classes_before : 0);
     char err[256];
     wgo_handle *h = wgo_compile(texts.data(), oa.data(), n, flags & 1u, err, sizeof err);   // (bit 1 is the library's alone: shared keys)
     if (lib_ok != (h != nullptr)) { std::printf("MISMATCH accept %d %d: %s\n", (int)lib_ok, h != nullptr, texts[0]); failures++; }
