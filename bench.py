@@ -1,8 +1,8 @@
 #!/usr/bin/env python3
 """Throughput of the structured-decoding hot path on one MI355X.
 
-A step is one pass of the whole path over one decode batch: mask lookup / build /
-gather (wg_fill_masks), logit masking (wg_apply_mask) and state advance
+A step is one pass of the whole path over one decode batch: mask lookup and mask
+rows (wg_fill_masks), logit masking (wg_apply_mask) and state advance
 (wg_advance).  The workload is the mixed HTML / JSON configuration (B=256 requests,
 V=151,936 tokens, bf16 logits, one template instance per request) on seeded
 synthetic inputs.  "cold" clears the mask cache before every step, so every

@@ -100,7 +100,8 @@ typedef struct {
 typedef struct {
     uint64_t lookups;       /* request-steps served by wg_fill_masks */
     uint64_t hits;          /* ... whose mask was already cached */
-    uint64_t builds;        /* mask rows built (one per distinct missing key) */
+    uint64_t builds;        /* mask rows built and kept (one per distinct missing key; a request whose key another
+                               request of the same call has claimed makes the row for itself and counts nowhere) */
     uint64_t uncached_builds;/* ... of which could not be kept because every cache row was taken */
     uint64_t class_scans;   /* allow / wait class tables taken up (one per distinct table and cache generation) */
     uint64_t entries_walked;/* candidate tokens examined by the row builds (ranges of the vocabulary's indexes) */
@@ -206,15 +207,19 @@ uint32_t wg_num_instances(wg_handle_t h);
 
 /* wg_cache_resize: the cache holds `rows` mask rows from now on (one row is 4*ceil(V/128)*4
  * bytes).  wg_compile sizes it for every key of its instances (at least 4096 rows, at most a
- * quarter of the free device memory).  Rows are handed out in order of first use; once all are
- * taken, further keys are still served correctly but rebuilt on every call that needs them
- * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  Synchronises
- * the device and clears the cache. */
+ * quarter of the free device memory).  While there is a row for every key (wg_cache_stats: keys <=
+ * cache_rows), each key has its own.  With more keys than rows -- after wg_add_instances, or on a
+ * smaller cache -- rows are handed out in order of first use (rows in use stay where they are); once
+ * all are taken, further keys are still served correctly but rebuilt on every call that needs them
+ * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  A fill of a small
+ * batch is one kernel in the first case and two in the second, 0.4 to 2 us more a step at B <= 32;
+ * an engine that expects additions keeps the first by making room for their keys here, at set-up.
+ * Synchronises the device and clears the cache. */
 int wg_cache_resize(wg_handle_t h, uint32_t rows);
 
 /* wg_reserve_batch: room for calls with up to max_batch requests (1 .. 65535) in the handle's
- * per-call lists (which request refers to which cache row, the keys and class tables a call has
- * to build).  wg_compile reserves 1,024.  Only ever grows; when it grows, the device is
+ * per-call lists (which cache row a request refers to, how its row is made, which of its row's
+ * workgroups have done their lookup).  wg_compile reserves 1,024.  Only ever grows; when it grows, the device is
  * synchronised and the lists are allocated anew, so a HIP graph recorded before has to be
  * recorded again.  Call it at set-up, never between the steps of a decode loop: the per-step
  * calls themselves never allocate and refuse a batch above the reservation. */
@@ -222,7 +227,7 @@ int wg_reserve_batch(wg_handle_t h, uint32_t max_batch);
 uint32_t wg_max_batch(wg_handle_t h);       /* the current reservation */
 
 /* wg_set_scan_batch: 0 .. 8, anything else gives WG_ERR_INVALID.  Has no effect: masks are made from the
- * vocabulary's static indexes without a scan of class tables, so there is nothing to batch. */
+ * vocabulary's static indexes without a scan per class table, so there is nothing to batch. */
 int wg_set_scan_batch(wg_handle_t h, uint32_t tables);
 
 uint32_t wg_num_states(wg_handle_t h);
@@ -230,9 +235,10 @@ uint32_t wg_mask_words(wg_handle_t h);      /* W = ceil(V/32) */
 
 /* ---- per-step calls (device pointers, enqueue only) -------------------------------------
  * wg_fill_masks: d_bitmask[b][0..W) <- mask of d_states[b] (mask creation with the global
- * cache of the section "Mask Generation and Global Caching"): cached rows are gathered,
- * missing ones are built once per distinct key and cached.  An ERROR or out-of-range
- * state gets an all-zero row. */
+ * cache of the section "Mask Generation and Global Caching"): cached rows are copied, missing
+ * ones are made, and kept once per distinct key.  An ERROR or out-of-range state gets an all-zero
+ * row.  One kernel for a small batch (up to a workgroup per compute unit, 8 to 32 of them a row),
+ * two for a larger one. */
 int wg_fill_masks(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint32_t *d_bitmask,
                   void *stream);
 
@@ -265,9 +271,9 @@ int wg_masked_argmax(const void *d_logits, wg_dtype_t dtype, uint32_t B, uint32_
  * allows fewer than k tokens ends with ids of -1 and values of -inf.  1 <= k <= 64;
  * B <= 65535; ceil(V / 8192) * k <= 4096.  d_ids is int32 [B][k], d_values [B][k] of `dtype`.
  * d_workspace: device memory of at least wg_masked_topk_workspace(B, V, k) bytes, 8-byte
- * aligned, owned by the caller, overwritten by the call (for a small batch it holds the best k of
- * every 8,192 tokens of a row between the call's two kernels); calls that share a workspace must not
- * overlap.  Mask bits at and above V must be zero, as wg_fill_masks leaves them.  Enqueues
+ * aligned, owned by the caller, overwritten by the call (for a small batch of long rows it holds the
+ * best k of every slice of up to 8,192 tokens between the call's two kernels); calls that share a
+ * workspace must not overlap.  Mask bits at and above V must be zero, as wg_fill_masks leaves them.  Enqueues
  * one or two kernels on `stream`; nothing is allocated.  Arguments outside the limits above, a null
  * pointer or a workspace that is too small or misaligned give WG_ERR_INVALID and launch nothing. */
 uint64_t wg_masked_topk_workspace(uint32_t B, uint32_t V, uint32_t k);
@@ -315,7 +321,8 @@ int wg_forced_bytes(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint3
 /* wg_advance_fill_masks: wg_advance followed by wg_fill_masks on the new states, for the decode
  * loop, where the two always meet (the token sampled under step k's mask is consumed, then step
  * k+1's mask is produced): same results, one kernel launch and one pass over the state
- * descriptors fewer.  In wg_profile_read the combined first kernel is counted as the lookup. */
+ * descriptors fewer: the advance rides in the kernel that does the lookup (one or two kernels, as
+ * wg_fill_masks). */
 int wg_advance_fill_masks(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t B,
                           uint32_t *d_bitmask, void *stream);
 
@@ -323,9 +330,9 @@ int wg_advance_fill_masks(wg_handle_t h, wg_state_t *d_states, const int32_t *d_
  * advanced by the tokens sampled in the step before (d_tokens == NULL skips this: first step),
  * the masks of the new states are produced into d_bitmask as by wg_fill_masks and applied to
  * d_logits ([B][V] with V of the handle's vocabulary, layout as in wg_apply_mask) as by
- * wg_apply_mask.  Same results as wg_advance + wg_fill_masks + wg_apply_mask in two kernel
- * launches instead of four: the advance rides in the lookup kernel and the masking in the kernel
- * that makes the rows.  In wg_profile_read the combined kernels count as lookup and build. */
+ * wg_apply_mask.  Same results as wg_advance + wg_fill_masks + wg_apply_mask in one or two kernel
+ * launches instead of three or four: the advance rides in the kernel that does the lookup and the
+ * masking in the kernel that makes the rows. */
 int wg_decode_step(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t B,
                    uint32_t *d_bitmask, void *d_logits, wg_dtype_t dtype, int64_t row_stride_elems,
                    void *stream);
@@ -344,12 +351,12 @@ int wg_error_count(wg_handle_t h, uint64_t *host_out);
 const char *wg_last_error(void);
 
 /* ---- kernel timing (tracing aid; off by default) ------------------------------------------
- * While enabled, wg_fill_masks and wg_advance launch each of their kernels with a pair of HIP
- * events that take the kernel's own begin and end timestamps (this allocates events on the
- * host as needed).  wg_profile_read
+ * While enabled, the fills (wg_fill_masks, wg_advance_fill_masks, wg_decode_step) and wg_advance
+ * launch each of their kernels with a pair of HIP events that take the kernel's own begin and end
+ * timestamps (this allocates events on the host as needed).  wg_profile_read
  * synchronises, adds up the elapsed times since the last read and resets the record. */
 typedef struct {
-    uint64_t fill_calls, advance_calls;
+    uint64_t fill_calls, advance_calls;   /* (an advance inside a fill counts as part of the fill) */
     double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations: a fill has a lookup kernel and
                                                                      one that makes or copies the rows (build_ms); a small
                                                                      batch has the second alone, which then does the lookups,

@@ -79,7 +79,7 @@ def test_every_literal_state_at_full_size(torch_cuda, idx, n_inst):
 @pytest.mark.parametrize("idx,n_inst", [(2, 1), (3, 1), (4, 6), (5, 16)])
 def test_every_checkpoint_state_at_full_size(torch_cuda, idx, n_inst):
     """Every Wait / condition state (all byte budgets that bind, for a bounded Wait) at the full
-    vocabulary: whether its candidates come from the byte-pair index or from the class lists."""
+    vocabulary: whether its candidates come from the byte-pair index, by the exit byte or by the first byte."""
     torch = torch_cuda
     w = ws.make_workload(idx, steps=1)
     o = H.make_oracle(w)
@@ -192,7 +192,7 @@ def test_instances_of_one_shape_share_their_cache_rows(torch_cuda):
 
 
 def test_two_live_handles_with_long_and_short_rows(torch_cuda):
-    """A handle over the full 151,936-token vocabulary (a 19 KB row next to the builder's queue in
+    """A handle over the full 151,936-token vocabulary (19 KB rows, a share of them in each workgroup's
     LDS) stays usable after a handle over a 4,096-token vocabulary is compiled and used in the
     same process: fills of the two interleaved, every mask against the oracle."""
     torch = torch_cuda
@@ -277,12 +277,12 @@ def test_cold_steps_at_full_size_from_the_middle_of_the_trajectory(torch_cuda):
 
 
 def test_every_kind_of_class_table_and_candidate_source(torch_cuda):
-    """Checkpoints chosen so that every first look of the class scan and every candidate source of
-    the row build is taken: printable text up to '<' (neither nearly-all-stay nor mostly-reject),
-    a free-text Wait, allow lists; exits of one, six, seven and ten byte values in front of a
-    literal (up to six are looked up by byte pair, more take the class list), in front of the end,
-    and in front of another checkpoint; with and without byte budgets.  Every state and budget
-    against the oracle on a 20,011-token vocabulary, cold and again warm."""
+    """Checkpoints chosen so that both ways to take a class table (by first byte, by token rows) and
+    every candidate source of the row build are taken: printable text up to '<', a free-text Wait,
+    allow lists; exits of one, six, seven and ten byte values in front of a literal (byte pairs), in
+    front of the end, and in front of another checkpoint (places behind the exit byte); with and
+    without byte budgets.  Every state and budget against the oracle on a 20,011-token vocabulary,
+    cold and again warm."""
     torch = torch_cuda
     base = ws.make_workload(2, V=20011, B=1, steps=1)
     texts = [
@@ -330,25 +330,22 @@ def test_every_kind_of_class_table_and_candidate_source(torch_cuda):
 
 
 @pytest.mark.parametrize("tables", [0, 1, 2, 3, 8])
-def test_class_tables_scanned_several_at_a_time(torch_cuda, tables):
-    """wg_set_scan_batch: a workgroup of the class scan takes 1, 2, 3 or 8 class tables through its
-    tokens together (0: the call chooses).  Checkpoints chosen so that every path of the batched
-    scan is taken on a 20,011-token vocabulary (10 token groups, the last ragged): tables that
-    queue nearly every token for the byte-by-byte look (the queue is emptied between tables), tables
-    under which nearly every token leaves an exit entry (the staged entries leave more than once per
-    work item), free text, allow lists, a table no byte leaves; 19 templates bring more tables
-    than a batch holds, with a last batch that is not full.  Every state and budget against the
-    oracle, cold, then cold again after a clear, then warm; then the same on a vocabulary of 5,000
-    tokens longer than 8 bytes that all leave their checkpoint after the eighth byte, on a vocabulary
-    with tokens of up to 40 bytes, and on every state of a reduced config 5."""
+def test_many_class_tables_in_one_call(torch_cuda, tables):
+    """Calls that bring 19 templates' class tables at once on a 20,011-token vocabulary (the last token
+    range ragged): tables under which nearly every token leaves early, printable text up to one byte,
+    free text, allow lists, a table no byte leaves.  Every state and budget against the oracle,
+    cold, then cold again after a clear, then warm; then the same on a vocabulary of 5,000 tokens
+    longer than 8 bytes that all leave their checkpoint after the eighth byte, on a vocabulary with
+    tokens of up to 40 bytes, and on every state of a reduced config 5.  wg_set_scan_batch takes 0 to 8
+    and changes nothing."""
     torch = torch_cuda
     base = ws.make_workload(2, V=20011, B=1, steps=1)
     texts = []
-    for i in range(8):        # one allowed letter, every other printable byte leaves: an exit entry per token
+    for i in range(8):        # one allowed letter, every other printable byte leaves: a candidate per place in a token
         a = chr(ord("a") + i)
         texts.append(r'Sequence(Wait(allow={%s}, wait={[\x20-\x60], [\x7b-\x7e], %s}), Write("%s."))'
                      % (a, ", ".join(chr(c) for c in range(ord("a"), ord("z") + 1) if chr(c) != a), a))
-    for i in range(6):        # printable text up to one byte: most tokens need the byte-by-byte look
+    for i in range(6):        # printable text up to one byte
         texts.append(r'Sequence(Wait(allow={[\x20-\x7e]}, wait={%s}, max=%d), Write("ok"))'
                      % (("<", ">", r"\x7b", r"\x7d", r"\x5b", r"\x5d")[i], 3 + i))
     texts += [
@@ -372,9 +369,8 @@ def test_class_tables_scanned_several_at_a_time(torch_cuda, tables):
         return np.array(st, dtype=np.uint32)
 
     # long tokens: 8 to 15 letters a, then b, then a tail; under a table that lets a stay and leaves
-    # at b, the first 8 bytes decide none of them, so all go through the second stage of the
-    # byte-by-byte look and leave their exit entries from there (its queue fills and is emptied
-    # between rounds of the first stage, the staged entries leave between rounds of the second)
+    # at b, the first 8 bytes decide none of them, so every walk goes on into the next chunk and
+    # from there into the successor
     from wg_synth.vocab import from_tokens
     long_tokens = [b""] + [bytes([x]) for x in b"abcdefgh<."]
     for i in range(5000):
@@ -383,12 +379,12 @@ def test_class_tables_scanned_several_at_a_time(torch_cuda, tables):
         if i % 5 == 0:
             long_tokens.append(b"a" * (1 + i % 4) + b"b" + tail)            # short ones between them
     long_texts = [r'Sequence(Wait(allow={a, %s}, wait={b}), Wait(allow={[c-z]}, wait={.}))' % chr(ord("c") + i)
-                  for i in range(9)]                 # every tail is allowed behind the b: a lost exit entry is a lost token
+                  for i in range(9)]                 # every tail is allowed behind the b: a lost candidate is a lost token
     long_w = dataclasses.replace(base, vocab=from_tokens(long_tokens, eos_id=0), texts=long_texts, args=[{}] * len(long_texts),
                                  B=len(long_texts), request_template=np.arange(len(long_texts), dtype=np.int64))
     assert len(set(long_tokens)) == len(long_tokens) and long_w.vocab.lmax <= 24
 
-    # tokens of up to 40 bytes: longer than the three 8-byte chunks the second stage holds
+    # tokens of up to 40 bytes: longer than the 24 bytes of a run that a walk holds
     wide = ws.make_vocab(3001, ("geometric", 10, 40), seed=9, utf8_tenths=1)
     assert wide.lmax == 40
     wide_w = dataclasses.replace(ws.make_workload(5, V=3001, B=16, steps=1), vocab=wide)

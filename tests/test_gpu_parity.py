@@ -168,11 +168,11 @@ def test_fused_advance_and_fill_match_the_separate_calls(torch_cuda, idx, V, B, 
 
 
 @pytest.mark.parametrize("idx,V,B,steps,rows,pad", [
-    (3, 3001, 8, 40, 0, 0),        # V % 8 != 0: the separate apply kernels do the masking
-    (4, 6008, 24, 40, 0, 0),       # bf16, 16-byte stores: masking inside the gather kernel
+    (3, 3001, 8, 40, 0, 0),        # V % 8 != 0: rows that begin at any address
+    (4, 6008, 24, 40, 0, 0),       # bf16, rows at multiples of 16 bytes
     (4, 6008, 24, 24, 0, 8),       # ... with padded logits rows
     (4, 6008, 24, 24, 0, 3),       # ... with a row stride that rules out 16-byte stores
-    (5, 4104, 96, 24, 5, 0),       # five cache rows: most masks are built straight into the bitmask
+    (5, 4104, 96, 24, 5, 0),       # five cache rows: most masks are made and not kept
     (2, 4096, 6, 30, 0, 0),
     (4, None, None, 6, 0, 0),      # full size: B=256, V=151,936, the shape the benchmark times
     (5, None, None, 3, 0, 0),      # full size: B=1,024
@@ -365,7 +365,7 @@ def test_random_trees_every_state_every_token(torch_cuda, restart):
         texts = [ws.to_text(t) for t in trees]
         o = O.Oracle(texts, None, ov, restart=restart)
         h = wg.Handle(texts, None, gv, flags=wg.EOS_RESTART if restart else wg.EOS_STOP)
-        h.set_scan_batch((0, 8, 3)[case % 3])              # the class scan table by table, and several at a time
+        h.set_scan_batch((0, 8, 3)[case % 3])              # (changes nothing)
         st = _all_states(o)
         n_states += len(st)
         h.reserve_batch(len(st))
@@ -494,7 +494,7 @@ def test_cache_cold_warm_and_duplicates(torch_cuda):
     s3 = h.cache_stats()
     assert (H.host_mask(d_mask) == want[None, :]).all()
     assert (s3["builds"], s3["hits"]) == (2, 16)
-    # a Wait state needs its class table scanned once per cache epoch, however many keys use it
+    # a Wait state's class table is taken up once per cache epoch, however many keys use it
     wait_sid = next(s for s in range(h.num_states) if o.describe(s)["kind"] == "WAIT")
     two = H.dev_states(np.array([[wait_sid, 0]] * 16, dtype=np.uint32))
     h.fill_masks(two, d_mask)
