@@ -919,19 +919,17 @@ free_rows_kernel(DeviceCache Cc, uint32_t n_keys, uint32_t *__restrict__ free_ro
     }
 }
 
-// apply: a workgroup takes kApplyTokens tokens of a row.  Bound by the stores; with 8192 tokens what a
-// workgroup begins with (mask words to LDS, a barrier) showed where masks are dense (random trees, bf16, B = 256,
-// V = 128256 21.2 us, 20.3 with 4096, 20.4 with 2048; html 12.0, 12.2 and 16.5; JSON fp32 15.4, 14.7 and 17.0).
-constexpr uint32_t kApplyTokens = 4096;
+// apply: a workgroup takes kApplyTokens tokens of a row.
+constexpr uint32_t kApplyTokens = 8192;
 template <typename Elem, bool kLine>
 __global__ void __launch_bounds__(256)
 apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
     __shared__ uint32_t row[kApplyTokens / 32u + 1u];
     const uint32_t b = blockIdx.y, lo = blockIdx.x * kApplyTokens, hi = lo + kApplyTokens < V ? lo + kApplyTokens : V;
-    static_assert(kApplyTokens <= 32u * 256u, "at most a mask word per thread");
+    static_assert(kApplyTokens == 32u * 256u, "a mask word per thread");
     const uint32_t w = (lo >> 5) + threadIdx.x;
-    if (threadIdx.x < kApplyTokens / 32u) row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
+    row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
     __syncthreads();
     mask_span<Elem, kLine>(logits + (int64_t)b * row_stride, lo, hi, lo, row);
 }
