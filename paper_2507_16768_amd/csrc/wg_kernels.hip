@@ -934,6 +934,36 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
     mask_span<Elem, kLine>(logits + (int64_t)b * row_stride, lo, hi, lo, row);
 }
 
+// The same for bf16 rows that begin at multiples of 16 bytes, where a mask byte is a 16-byte piece of logits:
+// kByteGroups bytes a thread straight from memory, no LDS and no barrier before the stores.  V = 151936, B =
+// 256, staged -> straight, us: html 13.4 -> 12.3, JSON 13.9 -> 13.0, mixed 16.0 -> 14.9, random trees 24.2 ->
+// 23.1, one token of 1,600 disallowed 7.5 -> 6.6 (two bytes a thread; with one 13.2, 13.7, 15.2, 22.5, 7.8, with
+// four 12.9, 13.4, 15.8, 24.0, 6.2).  fp32 is slower so: its pieces are half a byte (random trees, V = 128256, B =
+// 256 24.9 staged, 33.6 with two stores to a byte).
+constexpr uint32_t kByteGroups = 2;
+__global__ void __launch_bounds__(256)
+apply_bytes_kernel(uint16_t *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
+{
+    const uint32_t b = blockIdx.y, g0 = blockIdx.x * (256u * kByteGroups) + threadIdx.x;      // 8 tokens each
+    const uint8_t *row = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * W);
+    uint32_t m[kByteGroups];
+#pragma unroll
+    for (uint32_t i = 0; i < kByteGroups; i++) {
+        const uint32_t g = g0 + i * 256u;
+        m[i] = g * 8u < V ? row[g] : 0xFFu;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kByteGroups; i++) {
+        if (m[i] == 0xFFu) continue;
+        const uint32_t t = (g0 + i * 256u) * 8u;
+        uint16_t *p = logits + (int64_t)b * row_stride + t;
+        uint32_t z = ~m[i] & 0xFFu;
+        if (V - t < 8u) z &= (1u << (V - t)) - 1u;             // (the row ends inside this byte)
+        if (z == 0xFFu) *reinterpret_cast<uint4 *>(p) = uint4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
+        else while (z) { p[__builtin_ctz(z)] = (uint16_t)0xFF80u; z &= z - 1u; }
+    }
+}
+
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
 // Write and of the Writes that follow it directly, up to the next state that is not a literal
 // byte.  One thread per request; a run of literal states is copied from the state table's
@@ -1131,6 +1161,8 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
         return launch(by_lines(dtype, B, V) ? apply_kernel<uint32_t, true> : apply_kernel<uint32_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
     }
     uint16_t *x = static_cast<uint16_t *>(logits);
+    if (!by_lines(dtype, B, V) && reinterpret_cast<uintptr_t>(logits) % 16u == 0u && row_stride % 8 == 0)
+        return launch(apply_bytes_kernel, dim3(cdiv(V, 8u * 256u * kByteGroups), B), dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
     return launch(by_lines(dtype, B, V) ? apply_kernel<uint16_t, true> : apply_kernel<uint16_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
 }
 
