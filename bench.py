@@ -30,9 +30,26 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 
+# HBM bytes per launch in workloads 4 and 5, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
+# (profiles/bench_config4_hbm_traffic.txt, profiles/bench_config5_hbm_traffic.txt; fetch scaled x2.000,
+# write x1.000 by the counters of a 512 MiB device copy): the rows as made in a cold step, lookup as the mean
+# over cold and warm steps, with and without the advance.  They describe the kernels whose source hashes to
+# TRAFFIC_SOURCE_SHA256; with any other kernel source, or any other workload, the field is reported as null.
+TRAFFIC_BYTES = {
+    4: {"lookup": 0.28e6, "rows": 13.84e6, "apply": 57.08e6, "advance": 0.25e6},
+    5: {"lookup": 0.55e6, "rows": 45.64e6, "apply": 535.02e6, "advance": 0.61e6},
+}
+TRAFFIC_SOURCE_SHA256 = "ae59342048bbe9cef48cb80deea5bcf6751713ec8a718396a3624f6d93df8b38"
 WINDOW_START = 64              # first timed step of the trajectory (the warm-up steps come right before it)
 N_PASSES = 5                   # timed passes per figure; the median is reported
 RAMP_SECONDS = 0.08            # GPU work done before timing, for the clocks to settle
+
+
+def kernel_source_sha256():
+    import hashlib
+    path = os.path.join(ROOT, "paper_2507_16768_amd", "csrc", "wg_kernels.hip")
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()
 
 
 def _oracle_steps(w, lo, hi, n_steps):
@@ -587,11 +604,13 @@ def main():
         "apply": (apply_min_bytes, kt_cold["apply_us"]),
         "advance": (state_bytes + B * (sum_len / float(V)), kt_cold["advance_us"]),
     }
+    traffic_ok = kernel_source_sha256() == TRAFFIC_SOURCE_SHA256
     kernels = []
     for name, (nbytes, us) in alg.items():
         gbs = nbytes / (us * 1e-6) / 1e9 if us > 0 else 0.0
         kernels.append({"kernel": name, "algorithmic_bytes_per_launch": nbytes, "us_per_launch": us,
                         "achieved_GBs": gbs, "frac": gbs / HBM_PEAK_GBS,
+                        "traffic": TRAFFIC_BYTES.get(w.index, {}).get(name) if traffic_ok else None,
                         "bound": "hbm" if name in ("rows", "apply") else "latency"})
     dominant = max((k for k in kernels if k["bound"] == "hbm"), key=lambda k: k["us_per_launch"])
     method_bytes_cold = sum(v[0] for v in alg.values())
@@ -619,6 +638,7 @@ def main():
                    "logits_dtype": w.dtype},
         "roofline": {"kernel": dominant["kernel"], "bound": "hbm", "achieved": dominant["achieved_GBs"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dominant["frac"],
+                     "traffic": dominant["traffic"],
                      "algorithmic_bytes_per_launch": dominant["algorithmic_bytes_per_launch"],
                      "us_per_launch": dominant["us_per_launch"],
                      "kernels": kernels,
