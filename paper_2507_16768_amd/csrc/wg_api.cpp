@@ -26,15 +26,12 @@ struct wg_table_s {
 struct wg_vocab_s {
     DeviceVocab dv{};
     uint8_t *d_len8 = nullptr;
-    uint32_t *d_lit_start = nullptr, *d_place_start = nullptr, *d_len_rows = nullptr;
     uint64_t *d_chunks = nullptr;
     ExitEntry *d_index = nullptr;
-    uint32_t *d_dir0 = nullptr, *d_dirN = nullptr, *d_rows = nullptr;
+    uint32_t *d_dirs = nullptr, *d_rows = nullptr;
     int device = 0;
     void release() {
-        (void)hipFree(d_len8); (void)hipFree(d_lit_start); (void)hipFree(d_place_start); (void)hipFree(d_len_rows);
-        (void)hipFree(d_chunks); (void)hipFree(d_index); (void)hipFree(d_dir0); (void)hipFree(d_dirN);
-        (void)hipFree(d_rows);
+        (void)hipFree(d_len8); (void)hipFree(d_chunks); (void)hipFree(d_index); (void)hipFree(d_dirs); (void)hipFree(d_rows);
     }
 };
 
@@ -314,41 +311,36 @@ static int create_vocab(const uint8_t *host_bytes, const uint64_t *host_offsets,
         unsigned long long *unused = nullptr;
         (void)static_topk_scratch(&unused);
     }
-    // the candidate indexes, one behind the other
+    // the candidate indexes, one behind the other, and their directories
     std::vector<ExitEntry> index;
-    uint32_t at[4];
+    std::vector<uint32_t> dirs;
     {
         const std::vector<ExitEntry> *parts[4] = {&ix.sorted, &ix.lit_entries, &ix.bigram, &ix.places};
+        const std::vector<uint32_t> *dir[4] = {&ix.dir0, &ix.lit_start, &ix.dirN, &ix.place_start};
         uint64_t n = 0;
         for (const auto *p : parts) n += p->size();
         if (n > 0xFFFFFFFFull) return fail(WG_ERR_INVALID, "wg_vocab_create: the candidate indexes have more than 2^32 entries");
         index.reserve(n);
+        dirs.reserve(kDirWords);
         for (int i = 0; i < 4; i++) {
-            at[i] = (uint32_t)index.size();
+            const uint32_t at = (uint32_t)index.size();
+            for (uint32_t x : *dir[i]) dirs.push_back(at + x);
             index.insert(index.end(), parts[i]->begin(), parts[i]->end());
         }
     }
     // the token rows, likewise
     std::vector<uint32_t> rows;
-    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size());
-    rows.insert(rows.end(), ix.byte_rows.begin(), ix.byte_rows.end());
-    rows.insert(rows.end(), ix.block_rows.begin(), ix.block_rows.end());
-    rows.insert(rows.end(), ix.tail_rows.begin(), ix.tail_rows.end());
+    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size() + ix.len_rows.size());
+    for (const auto *r : {&ix.byte_rows, &ix.block_rows, &ix.tail_rows, &ix.len_rows}) rows.insert(rows.end(), r->begin(), r->end());
     hipError_t e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());
     if (e == hipSuccess) e = upload(&v->d_chunks, ix.chunks.data(), ix.chunks.size());
-    if (e == hipSuccess) e = upload(&v->d_len_rows, ix.len_rows.data(), ix.len_rows.size());
     if (e == hipSuccess) e = upload(&v->d_rows, rows.data(), rows.size());
     if (e == hipSuccess) e = upload(&v->d_index, index.data(), index.size());
-    if (e == hipSuccess) e = upload(&v->d_dir0, ix.dir0.data(), ix.dir0.size());
-    if (e == hipSuccess) e = upload(&v->d_lit_start, ix.lit_start.data(), ix.lit_start.size());
-    if (e == hipSuccess) e = upload(&v->d_dirN, ix.dirN.data(), ix.dirN.size());
-    if (e == hipSuccess) e = upload(&v->d_place_start, ix.place_start.data(), ix.place_start.size());
+    if (e == hipSuccess) e = upload(&v->d_dirs, dirs.data(), dirs.size());
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? WG_ERR_NOMEM : WG_ERR_HIP,
                     std::string("wg_vocab_create: ") + hipGetErrorString(e));
-    v->dv = DeviceVocab{v->d_len8, v->d_chunks, v->d_len_rows, v->d_rows, v->d_index, v->d_dir0,
-                        v->d_lit_start, v->d_dirN, v->d_place_start, at[0], at[1], at[2], at[3],
-                        V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride};
+    v->dv = DeviceVocab{v->d_len8, v->d_chunks, v->d_rows, v->d_index, v->d_dirs, V, ix.W, eos_id, ix.lmax, ix.n_chunks, ix.row_stride};
     *out = v.release();
     return WG_OK;
 }

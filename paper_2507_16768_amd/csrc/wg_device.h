@@ -7,6 +7,8 @@
 namespace wg {
 
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
+constexpr uint32_t kDirSorted = 0, kDirFirst = kDirSorted + 256 * 257 + 1, kDirPairs = kDirFirst + 256 * kParts + 1,
+                   kDirPlaces = kDirPairs + 65536 + 1, kDirWords = kDirPlaces + 256 * kParts + 1;
 
 struct DeviceTable {
     const StateDesc *states;
@@ -17,27 +19,23 @@ struct DeviceTable {
     uint32_t lmax;
 };
 
-// The candidate indexes of a vocabulary lie in one array of 8-byte entries {tok, off, cls, first,
-// rem}, one behind the other; off + rem is the length of the token in each of them.
+// The arrays of a vocabulary that the row builder reads lie one behind the other, rows with rows and
+// directories with directories: a pointer costs it two of its scalar registers.
 struct DeviceVocab {
     const uint8_t *len8;         // token length in bytes (0 for EOS and byte-less tokens)
     const uint64_t *chunks;      // chunks[k * V + t] = bytes 8k .. 8k+7 of token t, zero padded
-    const uint32_t *len_rows;    // row r (0 .. lmax+1): tokens with 1 <= length <= r
-    // token rows by byte value: row x (0 .. 255) the tokens that contain the byte x; behind them the
-    // blocks, row kBlockRow + k those that contain a byte 4k .. 4k+3, row kBigBlockRow + k a byte
-    // 16k .. 16k+15; row kTailRow + x the tokens in which x occurs once, as the last byte
+    // token rows: row x (0 .. 255) the tokens that contain the byte x, row kBlockRow + k those that
+    // contain a byte 4k .. 4k+3, row kBigBlockRow + k a byte 16k .. 16k+15; row kTailRow + x the tokens in
+    // which x occurs once, as the last byte; row kLenRow + r (r = 0 .. lmax+1) those with 1 <= length <= r
     const uint32_t *rows;
-    const ExitEntry *index;      // the four indexes below
-    // by byte order: range y0 * 257 of dir0 is the token that is the single byte y0, range
-    // y0 * 257 + 1 + y1 the tokens of two or more bytes that start with y0 y1; first = second byte
-    const uint32_t *dir0;        // 256 * 257 + 1 boundaries, from entry at_sorted
-    // by (first byte, token range): off = 1, first = second byte (rem = 0: a one-byte token)
-    const uint32_t *lit_start;   // 256 * kParts + 1 boundaries, from entry at_first
-    // every place where a byte y follows a byte e: range e * 256 + y; off = index of y, first = y
-    const uint32_t *dirN;        // 65536 + 1 boundaries, from entry at_pairs
-    // the same by (e, token range)
-    const uint32_t *place_start; // 256 * kParts + 1 boundaries, from entry at_places
-    uint32_t at_sorted, at_first, at_pairs, at_places;
+    const ExitEntry *index;      // the four candidate indexes, entries {tok, off, cls, first, rem}; off + rem is the token's length
+    // the entry numbers at which the ranges of the indexes begin, four directories:
+    //   kDirSorted: by byte order; range y0 * 257 is the token that is the single byte y0, range
+    //     y0 * 257 + 1 + y1 the tokens of two or more bytes that start with y0 y1; first = second byte
+    //   kDirFirst: by (first byte, token range); off = 1, first = second byte (rem = 0: a one-byte token)
+    //   kDirPairs: every place where a byte y follows a byte e: range e * 256 + y; off = index of y, first = y
+    //   kDirPlaces: the same by (e, token range)
+    const uint32_t *dirs;
     uint32_t V, W;
     int32_t eos_id;
     uint32_t lmax;

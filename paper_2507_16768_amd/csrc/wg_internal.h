@@ -54,7 +54,7 @@ constexpr uint32_t kPartGroup = 2048;
 // | class << 8), ids[n_exits .. n_ids) the token rows that together hold every token with a
 // rejected byte (kBlockRow + k: byte values 4k .. 4k+3, kBigBlockRow + k: 16k .. 16k+15).
 constexpr uint32_t kFewLive = 8;
-constexpr uint32_t kBlockRow = 256, kBigBlockRow = 320, kTailRow = 336;
+constexpr uint32_t kBlockRow = 256, kBigBlockRow = 320, kTailRow = 336, kLenRow = 592;
 struct ClassPlan {
     uint16_t n_exits, n_ids, by_first, pad;
     uint16_t ids[260];

@@ -436,6 +436,10 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 //     byte values that do not stay; the tokens that leave with their last byte are found by that
 //     byte, those that leave earlier by the exit byte and the literal byte behind it (or, where a
 //     checkpoint follows, by the exit byte).
+// The first wavefront sees to the candidates (and to all that it needs for them itself: the successors' class
+// tables and literal bytes come with the directories), the others to the rest.  What the walks need of the
+// successors lies in LDS and not in scalar registers, of which this kernel has too few: with a pointer for each
+// of the vocabulary's arrays and both successors in them 136 values were kept in lanes of vector registers, now 78.
 // Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
 // that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
@@ -450,8 +454,10 @@ constexpr uint32_t kRowWaves = kRowThreads / 64u;
 constexpr uint32_t kRowBatch = 4;          // index entries of a lane in flight together
 constexpr uint32_t kRanges = 256;          // index ranges of a key: at most one per byte value
 constexpr uint32_t kAlone = 128;           // candidates that one wavefront sees to, while the others do the rows
-constexpr uint32_t kOrBatch = 4;           // token rows in flight together,
-constexpr uint32_t kOrWords = 4;           // for this many words of a thread
+// token rows in flight together, 16 bytes of each a thread: a table of thirty rows is four trips to memory (with four
+// rows of four single words, where a share of 500 words also left lanes to load twice, it was eight: a
+// checkpoint of digits, V = 128256, 5.6 us of the row's 15)
+constexpr uint32_t kOrBatch = 8;
 
 enum : uint32_t {
     FROM_PREFIX = 1,    // sorted, by two bytes
@@ -467,11 +473,13 @@ typedef __attribute__((address_space(1))) uint2 global_u2;   // a load known to 
 
 struct RowShared {
     uint8_t own[256], hop[2][256];             // class tables of the state and of its successors
+    uint64_t run[2][3];                        // 24 literal bytes from the state itself, or behind its exits
+    ClassPlan plan;                            // of the state's class table
     uint32_t start[kRanges], upto[kRanges];    // first entry of a range, candidates up to its end
     uint16_t code[kRanges];                    // byte value | FROM_* << 8
     uint32_t queue[kRowWaves][64u * (kRowBatch + 1u)];   // tokens to decide: id | length << 24
     uint32_t n_ranges, total;
-    RowTask task;                              // what the row's lookup left (one-kernel fill)
+    RowTask task;                              // what the row's lookup left; two kernels: its successors only
     uint32_t ref;
 };
 
@@ -489,25 +497,9 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x)
 
 __device__ __forceinline__ bool is_checkpoint(uint32_t kind) { return kind == WG_KIND_WAIT || kind == WG_KIND_COND; }
 
-// The first 24 bytes of the literal run a state lies in, held by every lane.
-struct RunBytes { uint64_t w[3]; };
-__device__ __forceinline__ RunBytes run_bytes(const DeviceTable &T, uint32_t sid)
-{
-    // (16 zero bytes lie behind the last state's literal byte; a run ends before them)
-    const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
-    const uint32_t q = sid >> 3, sh = (sid & 7u) * 8u, last = (T.n_states >> 3) + 1u;
-    uint64_t x[4];
-#pragma unroll
-    for (uint32_t k = 0; k < 4u; k++) x[k] = lit64[q + k < last ? q + k : last];
-    RunBytes r;
-#pragma unroll
-    for (uint32_t k = 0; k < 3u; k++) r.w[k] = sh ? (x[k] >> sh) | (x[k + 1u] << (64u - sh)) : x[k];
-    return r;
-}
-
 // Walks bytes [i, L), i < L, of a token from a literal state with `run` bytes to go, its first 24 in
-// `lit`, then the state table from the state `after` them.
-__device__ __forceinline__ bool walk_run(const DeviceTable &T, const RunBytes &lit, uint32_t sid, uint32_t run, uint32_t after,
+// `lit` (LDS), then the state table from the state `after` them.
+__device__ __forceinline__ bool walk_run(const DeviceTable &T, const uint64_t *lit, uint32_t sid, uint32_t run, uint32_t after,
                                          TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint32_t n = L - i < run ? L - i : run;
@@ -516,7 +508,7 @@ __device__ __forceinline__ bool walk_run(const DeviceTable &T, const RunBytes &l
         if (8u * k >= n) break;
         const uint32_t m = n - 8u * k;
         const uint64_t mask = m >= 8u ? ~0ull : (1ull << (8u * m)) - 1ull;
-        if ((window(t, i + 8u * k) ^ lit.w[k]) & mask) return false;
+        if ((window(t, i + 8u * k) ^ lit[k]) & mask) return false;
     }
     if (n <= 24u) { sid = n == run ? after : sid + n; i += n; }
     else { sid += 24u; i += 24u; }
@@ -525,7 +517,7 @@ __device__ __forceinline__ bool walk_run(const DeviceTable &T, const RunBytes &l
 
 // Walks bytes [i, L), i < L, of a token from the staged successor; goes on through the state table
 // when the token moves on to a third state.
-__device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h, const uint8_t *lut, const RunBytes &lit,
+__device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h, const uint8_t *lut, const uint64_t *lit,
                                          TokenBytes &t, uint32_t i, uint32_t L)
 {
     uint32_t sid = WG_SID_ERROR, aux = 0;
@@ -557,6 +549,21 @@ __host__ __device__ __forceinline__ uint32_t range_token(const DeviceVocab &Vc, 
     return p >= kParts || t > Vc.V ? Vc.V : t;
 }
 
+__device__ __forceinline__ uint4 operator|(const uint4 &a, const uint4 &b) { return uint4{a.x | b.x, a.y | b.y, a.z | b.z, a.w | b.w}; }
+__device__ __forceinline__ uint4 operator&(const uint4 &a, const uint4 &b) { return uint4{a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w}; }
+__device__ __forceinline__ uint4 operator~(const uint4 &a) { return uint4{~a.x, ~a.y, ~a.z, ~a.w}; }
+
+// Brings a class table and its plan to LDS; one wavefront.
+__device__ __forceinline__ void stage_class(const DeviceTable &T, RowShared &sh, uint32_t cls, uint32_t lane)
+{
+    static_assert(sizeof(ClassPlan) % 16 == 0 && sizeof(ClassPlan) / 16 <= 64, "a piece per lane");
+    const uint32_t t = reinterpret_cast<const uint32_t *>(T.classes + (size_t)cls * 256u)[lane];
+    uint4 p{0u, 0u, 0u, 0u};
+    if (lane < sizeof(ClassPlan) / 16u) p = reinterpret_cast<const uint4 *>(T.plans + cls)[lane];
+    reinterpret_cast<uint32_t *>(sh.own)[lane] = t;
+    if (lane < sizeof(ClassPlan) / 16u) reinterpret_cast<uint4 *>(&sh.plan)[lane] = p;
+}
+
 // The words [w_lo, w_hi) of a missing row are row[] | early[] (LDS, word 0 = w_lo): early holds what
 // the candidates add, row the rest, so that the two are made side by side.
 __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, RowShared &sh,
@@ -573,33 +580,24 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
     auto before = [](unsigned long long bal) {
         return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
     };
-    // the class tables, a wavefront each
-    {
-        uint8_t *to = wave == 0u ? sh.own : wave == 1u ? sh.hop[0] : sh.hop[1];
-        const bool want = wave == 0u ? ckpt : wave == 1u ? ckpt_a : wave == 2u ? ckpt_b : false;
-        const uint32_t c = wave == 0u ? me.cls : wave == 1u ? ha.cls : hb.cls;
-        if (want) reinterpret_cast<uint32_t *>(to)[lane] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)c * 256u)[lane];
-    }
-    for (uint32_t w = tid; w < n_words; w += kRowThreads) early[w] = 0u;
-    // the literal bytes of the state's own run, or behind its exits
-    const RunBytes run_a = run_bytes(T, literal ? me.sid : ha.kind == WG_KIND_LIT ? ha.next_a : 0u);
-    const RunBytes run_b = run_bytes(T, hb.kind == WG_KIND_LIT ? hb.next_a : 0u);
     const bool few_budget = ckpt && me.r < Vc.lmax;            // the byte budget binds inside a token
-    const uint32_t *len_stay = Vc.len_rows + (size_t)me.r * rs + w_lo, *len_end = len_stay + rs;
-    // the plan of the state's class table: a lane holds one of its first 64 ids
-    const ClassPlan &plan = T.plans[ckpt ? me.cls : 0u];
-    const uint32_t n_exits = plan.n_exits, n_ids = plan.n_ids;
-    const bool by_first = ckpt && plan.by_first;
-    uint32_t ids = plan.ids[lane];
-    __syncthreads();
+    const uint32_t n_exits = sh.plan.n_exits, n_ids = sh.plan.n_ids;
+    const bool by_first = ckpt && sh.plan.by_first;
     uint32_t total = 0;
     if (wave == 0u) {
         // the index ranges with the key's candidates
         uint32_t n = 0, sure = 0;
+        // with them the class tables of the successors and the literal bytes, for this wavefront's own candidates
+        uint32_t table[2] = {0u, 0u}, byte = 0;
+        if (ckpt_a) table[0] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)ha.cls * 256u)[lane];
+        if (ckpt_b) table[1] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)hb.cls * 256u)[lane];
+        const uint32_t side = lane >= 24u, at = side ? lane - 24u : lane;
+        const uint32_t of = at + (literal ? me.sid : side ? (hb.kind == WG_KIND_LIT ? hb.next_a : 0u) : ha.kind == WG_KIND_LIT ? ha.next_a : 0u);
+        if (lane < 48u && of < T.n_states) byte = T.lit[of];
         if (literal) {
             // (the one-byte tokens are taken as rows below: examined, but not one by one)
             if (lane == 0) {
-                if (!ckpt_a) sure = Vc.dir0[me.lit * 257u + 1u] - Vc.dir0[me.lit * 257u];
+                if (!ckpt_a) sure = Vc.dirs[kDirSorted + me.lit * 257u + 1u] - Vc.dirs[kDirSorted + me.lit * 257u];
             }
             n = ckpt_a || lit_a < 0x100u ? 1u : 0u;
         } else if (ckpt) n = n_exits;
@@ -607,27 +605,29 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
             const uint32_t i = r0 + lane;
             uint32_t lo = 0, len = 0;
             if (i < n) {
-                const uint32_t id = literal ? me.lit : r0 ? plan.ids[i] : ids, x = id & 0xFFu, c = id >> 8;
+                const uint32_t id = literal ? me.lit : sh.plan.ids[i], x = id & 0xFFu, c = id >> 8;
                 const bool side = c == CLS_EXIT_B;
                 const uint32_t lit = side ? lit_b : lit_a;
                 uint32_t from = literal ? (ckpt_a ? FROM_A : FROM_PREFIX)
                                         : by_first ? (c == CLS_STAY ? FROM_STAY : side ? FROM_B : FROM_A)
                                                    : lit < 0x100u ? FROM_PAIR : (side ? ckpt_b : ckpt_a) ? (side ? FROM_DEEP_B : FROM_DEEP_A) : 0u;
-                const uint32_t *dir = Vc.place_start;
-                uint32_t a = x * kParts + p0, z = a + span, at = Vc.at_places;
-                if (from == FROM_PREFIX) { dir = Vc.dir0; a = x * 257u + 1u + lit; z = a + 1u; at = Vc.at_sorted; }
-                else if (from == FROM_PAIR) { dir = Vc.dirN; a = x << 8 | lit; z = a + 1u; at = Vc.at_pairs; }
-                else if (from && from <= FROM_B) { dir = Vc.lit_start; at = Vc.at_first; }
-                else if (!from) z = a;                         // nothing goes on behind this exit
-                lo = dir[a];
-                len = dir[z] - lo;
-                lo += at;
+                uint32_t a = x * kParts + p0, n_at = span;
+                if (from == FROM_PREFIX) { a = kDirSorted + x * 257u + 1u + lit; n_at = 1u; }
+                else if (from == FROM_PAIR) { a = kDirPairs + (x << 8 | lit); n_at = 1u; }
+                else if (from && from <= FROM_B) a += kDirFirst;
+                else a += kDirPlaces;
+                if (!from) n_at = 0u;                          // nothing goes on behind this exit
+                lo = Vc.dirs[a];
+                len = Vc.dirs[a + n_at] - lo;
                 sh.code[i] = (uint16_t)(x | from << 8);
             }
             const uint32_t inc = wave_prefix_sum(len);
             if (i < n) { sh.start[i] = lo; sh.upto[i] = total + inc; }
             total += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         }
+        if (ckpt_a) reinterpret_cast<uint32_t *>(sh.hop[0])[lane] = table[0];
+        if (ckpt_b) reinterpret_cast<uint32_t *>(sh.hop[1])[lane] = table[1];
+        if (lane < 48u) reinterpret_cast<uint8_t *>(sh.run[side])[at] = (uint8_t)byte;
         if (lane == 0) {
             sh.n_ranges = n; sh.total = total;
             if (p0 == 0u && sure + total) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)(sure + total));
@@ -638,61 +638,49 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         }
         __builtin_amdgcn_wave_barrier();
     } else {
-        // meanwhile the other wavefronts fill in what does not depend on a token's neighbours
-        const uint32_t t3 = tid - 64u, n3 = kRowThreads - 64u;
-        uint32_t *keep = Cc.class_rows + (size_t)(2u * me.cls) * rs + w_lo;
-        if (literal) {
-            const uint32_t *has = Vc.rows + (size_t)me.lit * rs + w_lo, *one = Vc.len_rows + rs + w_lo;
-            for (uint32_t w = t3; w < n_words; w += n3) row[w] = ckpt_a ? 0u : has[w] & one[w];
+        // meanwhile the other wavefronts fill in what does not depend on a token's neighbours, four words
+        // of a thread at a time (rows are padded to whole 16 bytes with zeros)
+        const uint32_t n4 = (n_words + 3u) / 4u, n3 = kRowThreads - 64u, q0 = tid - 64u, w4 = w_lo / 4u;
+        const uint4 *rows = reinterpret_cast<const uint4 *>(Vc.rows) + w4;
+        const uint32_t rs4 = rs / 4u;
+        auto token_row = [&](uint32_t id) { return rows + (size_t)id * rs4; };
+        uint4 *row4 = reinterpret_cast<uint4 *>(row), *keep = reinterpret_cast<uint4 *>(Cc.class_rows) + (size_t)(2u * me.cls) * rs4 + w4;
+        if (literal && !ckpt_a) {
+            const uint4 *has = token_row(me.lit), *one = token_row(kLenRow + 1u);
+            for (uint32_t q = q0; q < n4; q += n3) row4[q] = has[q] & one[q];
         } else if (!ckpt || by_first) {
-            for (uint32_t w = t3; w < n_words; w += n3) row[w] = 0u;
-        } else if (me.class_state == CLASS_READY) {
-            for (uint32_t w = t3; w < n_words; w += n3)
-                row[w] = few_budget ? (keep[w] & len_stay[w]) | (keep[rs + w] & len_end[w]) : keep[w] | keep[rs + w];
+            for (uint32_t q = q0; q < n4; q += n3) row4[q] = uint4{0u, 0u, 0u, 0u};
         } else {
-            const uint32_t *has = Vc.len_rows + (size_t)(Vc.lmax + 1u) * rs + w_lo, *rows = Vc.rows + w_lo;
-            auto id_of = [&](uint32_t i) {                     // i is the same for the whole wavefront
-                return i < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)ids, (int)i) : (uint32_t)plan.ids[i];
-            };
-            for (uint32_t w0 = t3; w0 < n_words; w0 += n3 * kOrWords) {
-                // one: tokens with a byte value that does not stay, two: with several; tail: tokens with
-                // an exit byte once, at their end.  A token leaves with its last byte iff it is in tail and
-                // not in two, its bytes all stay iff it is not in one.
-                uint32_t at[kOrWords], one[kOrWords], two[kOrWords], tail[kOrWords], hb[kOrWords], ls[kOrWords], le[kOrWords];
-#pragma unroll
-                for (uint32_t v = 0; v < kOrWords; v++) {
-                    at[v] = w0 + v * n3 < n_words ? w0 + v * n3 : w0;
-                    one[v] = 0u; two[v] = 0u; tail[v] = 0u; hb[v] = has[at[v]];
-                    ls[v] = le[v] = 0xFFFFFFFFu;
-                    if (few_budget) { ls[v] = len_stay[at[v]]; le[v] = len_end[at[v]]; }
+            const uint4 *len_stay = token_row(kLenRow + me.r), *len_end = len_stay + rs4;
+            if (me.class_state == CLASS_READY) {
+                for (uint32_t q = q0; q < n4; q += n3) {
+                    uint4 stay = keep[q], end = keep[rs4 + q];
+                    if (few_budget) { stay = stay & len_stay[q]; end = end & len_end[q]; }
+                    row4[q] = stay | end;
                 }
-                for (uint32_t i = 0; i < n_exits; i++) {
-                    const uint32_t id = id_of(i) & 0xFFu;
-                    const uint32_t *src = rows + (size_t)id * rs, *last = rows + (size_t)(kTailRow + id) * rs;
-                    uint32_t x[kOrWords], y[kOrWords];
-#pragma unroll
-                    for (uint32_t v = 0; v < kOrWords; v++) { x[v] = src[at[v]]; y[v] = last[at[v]]; }
-#pragma unroll
-                    for (uint32_t v = 0; v < kOrWords; v++) { two[v] |= one[v] & x[v]; one[v] |= x[v]; tail[v] |= y[v]; }
-                }
-                for (uint32_t i = n_exits; i < n_ids; i += kOrBatch) {
-                    uint32_t x[kOrBatch][kOrWords];
-#pragma unroll
-                    for (uint32_t u = 0; u < kOrBatch; u++) {
-                        const uint32_t *src = rows + (size_t)id_of(i + u < n_ids ? i + u : i) * rs;
-#pragma unroll
-                        for (uint32_t v = 0; v < kOrWords; v++) x[u][v] = src[at[v]];
+            } else {
+                const uint4 *has = token_row(kLenRow + Vc.lmax + 1u);
+                for (uint32_t q = q0; q < n4; q += n3) {
+                    // one: tokens with a byte value that does not stay, two: with several; tail: tokens with
+                    // an exit byte once, at their end.  A token leaves with its last byte iff it is in tail and
+                    // not in two, its bytes all stay iff it is not in one.
+                    uint4 one{0u, 0u, 0u, 0u}, two = one, tail = one;
+                    for (uint32_t i = 0; i < n_exits; i++) {
+                        const uint32_t id = sh.plan.ids[i] & 0xFFu;
+                        const uint4 x = token_row(id)[q], y = token_row(kTailRow + id)[q];
+                        two = two | (one & x); one = one | x; tail = tail | y;
                     }
+                    for (uint32_t i = n_exits; i < n_ids; i += kOrBatch) {
+                        uint4 x[kOrBatch];
 #pragma unroll
-                    for (uint32_t u = 0; u < kOrBatch; u++)
+                        for (uint32_t u = 0; u < kOrBatch; u++) x[u] = token_row(sh.plan.ids[i + u < n_ids ? i + u : i])[q];
 #pragma unroll
-                        for (uint32_t v = 0; v < kOrWords; v++) if (i + u < n_ids) { two[v] |= one[v] & x[u][v]; one[v] |= x[u][v]; }
-                }
-#pragma unroll
-                for (uint32_t v = 0; v < kOrWords; v++) {
-                    const uint32_t s = ~one[v] & hb[v], x = tail[v] & ~two[v];
-                    row[at[v]] = (s & ls[v]) | (x & le[v]);
-                    if (me.class_state == CLASS_OWN) { keep[at[v]] = s; keep[rs + at[v]] = x; }
+                        for (uint32_t u = 0; u < kOrBatch; u++) if (i + u < n_ids) { two = two | (one & x[u]); one = one | x[u]; }
+                    }
+                    uint4 s = ~one & has[q], x = tail & ~two;
+                    if (me.class_state == CLASS_OWN) { keep[q] = s; keep[rs4 + q] = x; }
+                    if (few_budget) { s = s & len_stay[q]; x = x & len_end[q]; }
+                    row4[q] = s | x;
                 }
             }
         }
@@ -704,7 +692,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         const uint32_t tok = e & 0xFFFFFFu, L = e >> 24;
         TokenBytes t = token_bytes(Vc, tok, L);
         if (!ckpt) {
-            if (walk_run(T, run_a, me.sid, me.run, me.cls, t, 0u, L)) set_bit(tok);
+            if (walk_run(T, sh.run[0], me.sid, me.run, me.cls, t, 0u, L)) set_bit(tok);
             return;
         }
         uint32_t j = 0, c = CLS_STAY;
@@ -718,10 +706,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         bool ok = c == CLS_STAY || j + 1u == L;
         if (!ok) {
             const bool side_b = c == CLS_EXIT_B;
-            const HopState h{side_b ? hb.kind : ha.kind, 0u, side_b ? hb.next_a : ha.next_a, side_b ? hb.next_b : ha.next_b,
-                             side_b ? hb.max : ha.max, side_b ? hb.cls : ha.cls};
-            const RunBytes lit{{side_b ? run_b.w[0] : run_a.w[0], side_b ? run_b.w[1] : run_a.w[1], side_b ? run_b.w[2] : run_a.w[2]}};
-            ok = walk_hop(T, h, sh.hop[side_b], lit, t, j + 1u, L);
+            ok = walk_hop(T, sh.task.hop[side_b], sh.hop[side_b], sh.run[side_b], t, j + 1u, L);
         }
         if (ok) set_bit(tok);
     };
@@ -814,6 +799,7 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
     const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
+    uint4 *row4 = reinterpret_cast<uint4 *>(row), *early4 = row4 + n4 + 1u;
     uint32_t ticket = 0, sid = 0, aux = 0;
     unsigned long long all = 0, mine_all = 0;         // workgroups | keys claimed << 20 | class tables claimed << 40
     uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
@@ -848,7 +834,6 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     }
     const RowTask in = kWhole ? sh.task : Cc.tasks[b];   // (requested with the reference; only used where that asks for it)
     const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kWhole ? sh.ref : Cc.row_ref[b]));
-    uint4 *row4 = reinterpret_cast<uint4 *>(row);
     uint32_t slot = kNoSlot;
     if (ref == kRefBuild) {
         // (the same for every lane: to scalar registers)
@@ -857,28 +842,34 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
         const HopState ha = hop(in.hop[0]), hb = hop(in.hop[1]);
         const RowTask me{one(in.sid), one(in.kind), one(in.lit), one(in.cls), one(in.run), one(in.r), one(in.class_state), one(in.eos_next), one(in.slot), {}};
         slot = me.slot;
-        uint32_t *early = row + 4u * n4 + 4u;
-        make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, early, b);
-        for (uint32_t w = tid; w < 4u * n4; w += kRowThreads) row[w] = w < n_words ? row[w] | early[w] : 0u;
-    } else {
-        const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
-        for (uint32_t q = tid; q < n4; q += kRowThreads) row4[q] = ref >= Cc.cap_rows ? uint4{0u, 0u, 0u, 0u} : kWhole && q == tid ? ahead : src[q];
+        if (!kWhole && tid == kRowThreads - 1u) { sh.task.hop[0] = ha; sh.task.hop[1] = hb; }
+        for (uint32_t q = tid; q < n4; q += kRowThreads) early4[q] = uint4{0u, 0u, 0u, 0u};
+        if (tid >> 6 == 1u && is_checkpoint(me.kind)) stage_class(T, sh, me.cls, tid & 63u);
+        __syncthreads();
+        make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b);
     }
-    __syncthreads();
-    if (slot != kNoSlot) {
-        uint4 *dst = reinterpret_cast<uint4 *>(Cc.arena + (size_t)slot * rs + w_lo);
-        for (uint32_t q = tid; q < n4; q += kRowThreads) dst[q] = row4[q];
-    }
-    {
-        uint32_t *dst = bitmask + (size_t)b * Vc.W + w_lo;
-        if (reinterpret_cast<uintptr_t>(dst) % 16u == 0u) {
-            const uint32_t whole = n_words / 4u;
-            for (uint32_t q = tid; q < whole; q += kRowThreads) reinterpret_cast<uint4 *>(dst)[q] = row4[q];
-            if (tid < n_words - 4u * whole) dst[4u * whole + tid] = row[4u * whole + tid];
-        } else {
-            for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
+    // out: to the cache, the caller's bitmask, and LDS for the masking
+    const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
+    uint4 *kept = reinterpret_cast<uint4 *>(Cc.arena + (size_t)slot * rs + w_lo);
+    uint32_t *dst = bitmask + (size_t)b * Vc.W + w_lo;
+    const bool aligned = reinterpret_cast<uintptr_t>(dst) % 16u == 0u;
+    for (uint32_t q = tid; q < n4; q += kRowThreads) {
+        uint4 x{0u, 0u, 0u, 0u};
+        if (ref == kRefBuild) x = row4[q] | early4[q];
+        else if (ref < Cc.cap_rows) x = kWhole && q == tid ? ahead : src[q];
+        if (slot != kNoSlot) kept[q] = x;
+        if (aligned) {
+            if (4u * q + 4u <= n_words) reinterpret_cast<uint4 *>(dst)[q] = x;
+            else {
+                dst[4u * q] = x.x;
+                if (4u * q + 1u < n_words) dst[4u * q + 1u] = x.y;
+                if (4u * q + 2u < n_words) dst[4u * q + 2u] = x.z;
+            }
         }
+        if (kMode || !aligned) row4[q] = x;
     }
+    if (kMode || !aligned) __syncthreads();
+    if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
     if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
     if (kWhole) {
         if (tid == 0) {
