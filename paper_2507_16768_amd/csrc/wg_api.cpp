@@ -134,12 +134,9 @@ int reserve_batch(wg_handle_s *h, uint32_t B) {
     WG_HIP(hipDeviceSynchronize());
     (void)hipFree(h->dc.row_ref);
     (void)hipFree(h->dc.tasks);
-    (void)hipFree(h->dc.tickets);
-    h->dc.row_ref = nullptr; h->dc.tasks = nullptr; h->dc.tickets = nullptr; h->max_batch = 0;
+    h->dc.row_ref = nullptr; h->dc.tasks = nullptr; h->max_batch = 0;
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.row_ref), B * sizeof(uint32_t)));
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tasks), B * sizeof(RowTask)));
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tickets), B * sizeof(uint32_t)));
-    WG_HIP(hipMemset(h->dc.tickets, 0, B * sizeof(uint32_t)));
     h->max_batch = B;
     return WG_OK;
 }
@@ -446,7 +443,7 @@ void wg_destroy(wg_handle_t h) {
     (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
     if (h->stage) (void)hipHostFree(h->stage);
-    (void)hipFree(h->dc.tickets); (void)hipFree(h->dc.ticket_all); (void)hipFree(h->d_free_rows);
+    (void)hipFree(h->dc.tickets); (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->lookup_events, &h->rows_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
@@ -500,11 +497,14 @@ static int compile(const char *const *templates, const wg_args_t *args, uint32_t
     const size_t spread_bytes = (size_t)kSpread * kSpreadStride * sizeof(unsigned long long);
     WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.spread), spread_bytes));
     WG_HIP(hipMemset(h->dc.spread, 0, spread_bytes));
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ticket_all), sizeof(unsigned long long)));
-    WG_HIP(hipMemset(h->dc.ticket_all, 0, sizeof(unsigned long long)));
     int cus = 0;
     WG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, vocab->device));
     if (cus > 0) h->n_cu = (uint32_t)cus;
+    // (a fill in one kernel has at most n_cu rows: plan_fill)
+    const size_t ticket_bytes = ((size_t)h->n_cu + 1) * kTicketStride * sizeof(uint32_t);
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tickets), ticket_bytes));
+    WG_HIP(hipMemset(h->dc.tickets, 0, ticket_bytes));
+    h->dc.rows_ticket = h->dc.tickets + (size_t)h->n_cu * kTicketStride;
     WG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->stage), kStageBytes, hipHostMallocDefault));
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
@@ -748,10 +748,21 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     for (uint32_t i = 0; i < kSpread; i++) {
         host_out->entries_walked += spread[i * kSpreadStride + kSpreadWalked];
         host_out->hits += spread[i * kSpreadStride + kSpreadHits];
+        host_out->builds += spread[i * kSpreadStride + kSpreadBuilds];
+        host_out->class_scans += spread[i * kSpreadStride + kSpreadClasses];
     }
     host_out->keys = h->dc.n_keys;
     host_out->cache_rows = h->dc.cap_rows;
-    const uint64_t taken = (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;
+    uint64_t taken = (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;
+    if (h->dc.direct) {                                // nothing counts the rows there: a key of this generation holds its own
+        unsigned long long tags[2048];
+        taken = 0;
+        for (size_t i = 0; i < h->dc.n_keys; i += 2048) {
+            const size_t n = h->dc.n_keys - i < 2048 ? h->dc.n_keys - i : 2048;
+            WG_HIP(hipMemcpy(tags, h->dc.tags + i, n * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+            for (size_t k = 0; k < n; k++) taken += (uint32_t)(tags[k] >> kTagEpochShift) == h->dc.epoch;
+        }
+    }
     host_out->rows_in_use = taken < h->dc.cap_rows ? taken : h->dc.cap_rows;
     const uint64_t row_bytes = (uint64_t)h->dc.row_stride * 4ull;
     host_out->arena_bytes = ((uint64_t)h->dc.cap_rows + h->cap_classes * 2ull) * row_bytes;

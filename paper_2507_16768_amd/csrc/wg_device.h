@@ -70,7 +70,8 @@ enum : uint32_t { CLASS_SELF = 0, CLASS_READY = 1, CLASS_OWN = 2 };
 struct Counters {
     uint32_t n_claims;           // keys claimed in the call in flight
     uint32_t n_class_claims;     // class tables claimed in the call in flight
-    unsigned long long slot_ctr; // generation << 32 | arena rows in use in that generation (<= cap_rows)
+    unsigned long long slot_ctr; // generation << 32 | arena rows in use in that generation (<= cap_rows); not kept up while
+                                 // the arena is addressed by key
     unsigned long long launch;   // number of the fill call in flight (its last kernel counts it up)
     unsigned long long lookups, builds, uncached_builds, class_scans, errors;
 };
@@ -91,7 +92,9 @@ constexpr uint32_t kRefBuild = 0xFFFFFFFEu;
 constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
-constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1;
+constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1,
+                   kSpreadBuilds = 2, kSpreadClasses = 3;       // of one-kernel fills
+constexpr uint32_t kTicketStride = 32;     // a 128-byte line for the tickets of a row
 
 struct DeviceCache {
     Counters *ctr;
@@ -109,8 +112,9 @@ struct DeviceCache {
     // per call
     uint32_t *row_ref;           // [B] arena row, kRefBuild or kNoKey
     RowTask *tasks;              // [B]
-    uint32_t *tickets;           // [B] workgroups of a row that have done their lookup (zero between calls),
-    unsigned long long *ticket_all;      // workgroups of the call, and what they claimed above
+    // one-kernel fill, zero between calls: workgroups of a row that have read its state (kTicketStride
+    // apart), rows all of whose workgroups have
+    uint32_t *tickets, *rows_ticket;
     uint32_t row_stride;         // words, multiple of 4
     uint32_t n_keys;
     uint32_t epoch;              // cache generation of this call

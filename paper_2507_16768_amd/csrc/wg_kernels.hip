@@ -235,6 +235,13 @@ struct Found {
     RowTask me;                  // when ref is kRefBuild
 };
 
+// In a fill of one kernel no workgroup waits to learn whether it owns the key or the class table that it makes: 8 to
+// 32 workgroups of every row that needs one would swap on one tag, 10 ns each (a cold call of 256 requests 42 us,
+// now 18).  All workgroups of a row make their shares and keep them; the row's first one then enters the tags,
+// behind what it has to do, and the first of a call to do so counts.  A workgroup that finds the tag entered by
+// another row of the call keeps nothing: that row's workgroups all find it old or their own, and keep theirs.
+struct Claim { unsigned long long key_tag, class_tag; uint32_t key, cls; };      // tags as the lookup found them
+
 // What a call writes into the tags it claims, but for the request; `launch` is ctr->launch.
 __device__ __forceinline__ unsigned long long tag_now(const DeviceCache &Cc, unsigned long long launch)
 {
@@ -252,9 +259,11 @@ __device__ __forceinline__ uint32_t key_of(const DeviceTable &T, uint32_t sid, u
     return sid < T.n_states ? d.key_base + variant : kNoKey;
 }
 
-// The lookup of request b in state (sid, aux), d its descriptor.
+// The lookup of request b in state (sid, aux), d its descriptor.  kShares: by every workgroup of its row, with the
+// arena addressed by key, and claimed by nobody: see Claim.
+template <bool kShares>
 __device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache &Cc, unsigned long long now, uint32_t b,
-                                         uint32_t sid, uint32_t aux, const StateDesc &d)
+                                         uint32_t sid, uint32_t aux, const StateDesc &d, Claim *claim)
 {
     Found f{};
     f.ref = kNoKey;
@@ -279,14 +288,20 @@ __device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache
     f.hit = made && !this_call && slot != kNoSlot;
     f.ref = f.hit ? slot : kRefBuild;
     if (f.hit) return f;
+    const bool class_this_call = (ct >> kTagRequestBits) == (now >> kTagRequestBits);
+    uint32_t class_state = (uint32_t)(ct >> kTagEpochShift) == Cc.epoch && !class_this_call ? CLASS_READY : CLASS_SELF;
+    if (kShares) {
+        f.keep = !this_call || t == mine;
+        if (ckpt && class_state != CLASS_READY && (!class_this_call || ct == mine)) class_state = CLASS_OWN;
+        claim->key = f.key; claim->key_tag = t;
+        claim->cls = class_state == CLASS_OWN ? cls : kNoKey; claim->class_tag = ct;
+    } else {
     unsigned long long is = t;
     if (!this_call) {
         is = atomicCAS(&Cc.tags[f.key], t, mine);
         f.claimed = is == t;
     }
     f.keep = f.claimed || is == mine;
-    const bool class_this_call = (ct >> kTagRequestBits) == (now >> kTagRequestBits);
-    uint32_t class_state = (uint32_t)(ct >> kTagEpochShift) == Cc.epoch && !class_this_call ? CLASS_READY : CLASS_SELF;
     if (f.keep && ckpt && class_state != CLASS_READY) {
         unsigned long long cis = ct;
         if (!class_this_call) {
@@ -294,6 +309,7 @@ __device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache
             f.class_claimed = cis == ct;
         }
         if (f.class_claimed || cis == mine) class_state = CLASS_OWN;
+    }
     }
     auto hop = [&](uint32_t nt, const StateDesc &n) {
         if (nt >= T.n_states) return HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
@@ -323,7 +339,7 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
             advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, true);
             states[b].sid = sid; states[b].aux = aux;
         }
-        f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, v.d);
+        f = look_up<false>(T, Cc, tag_now(Cc, launch), b, sid, aux, v.d, nullptr);
     }
     // the claimers of a wavefront take their arena rows together
     const unsigned long long cm = __ballot(f.claimed), km = __ballot(f.class_claimed);
@@ -481,6 +497,10 @@ struct RowShared {
     uint32_t n_ranges, total;
     RowTask task;                              // what the row's lookup left; two kernels: its successors only
     uint32_t ref;
+    wg_state_t state;                          // the request's, advanced
+    StateDesc desc;
+    Claim claim;
+    unsigned long long launch;
 };
 
 // Inclusive prefix sum over the wavefront, in registers (every lane calls it).
@@ -564,11 +584,24 @@ __device__ __forceinline__ void stage_class(const DeviceTable &T, RowShared &sh,
     if (lane < sizeof(ClassPlan) / 16u) reinterpret_cast<uint4 *>(&sh.plan)[lane] = p;
 }
 
+// Enters a row's claims (see Claim).
+__device__ __forceinline__ void claim_tags(const DeviceCache &Cc, const RowShared &sh, uint32_t b)
+{
+    const unsigned long long now = tag_now(Cc, sh.launch), mine = now | b;
+    const Claim c = sh.claim;
+    unsigned long long key_was = ~c.key_tag, class_was = ~c.class_tag;
+    if ((c.key_tag >> kTagRequestBits) != (now >> kTagRequestBits)) key_was = atomicCAS(&Cc.tags[c.key], c.key_tag, mine);
+    if (c.cls != kNoKey && (c.class_tag >> kTagRequestBits) != (now >> kTagRequestBits)) class_was = atomicCAS(&Cc.class_tags[c.cls], c.class_tag, mine);
+    unsigned long long *count = Cc.spread + (b % kSpread) * kSpreadStride;
+    if (key_was == c.key_tag) atomicAdd(&count[kSpreadBuilds], 1ull);
+    if (class_was == c.class_tag) atomicAdd(&count[kSpreadClasses], 1ull);
+}
+
 // The words [w_lo, w_hi) of a missing row are row[] | early[] (LDS, word 0 = w_lo): early holds what
 // the candidates add, row the rest, so that the two are made side by side.
 __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, RowShared &sh,
                                          const RowTask &me, const HopState &ha, const HopState &hb, uint32_t p0, uint32_t span,
-                                         uint32_t w_lo, uint32_t w_hi, uint32_t *row, uint32_t *early, uint32_t b)
+                                         uint32_t w_lo, uint32_t w_hi, uint32_t *row, uint32_t *early, uint32_t b, bool claims)
 {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t n_words = w_hi - w_lo, rs = Cc.row_stride;
@@ -639,8 +672,10 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         __builtin_amdgcn_wave_barrier();
     } else {
         // meanwhile the other wavefronts fill in what does not depend on a token's neighbours, four words
-        // of a thread at a time (rows are padded to whole 16 bytes with zeros)
-        const uint32_t n4 = (n_words + 3u) / 4u, n3 = kRowThreads - 64u, q0 = tid - 64u, w4 = w_lo / 4u;
+        // of a thread at a time (rows are padded to whole 16 bytes with zeros); the last one comes after what it
+        // has claimed, if it has
+        const uint32_t n4 = (n_words + 3u) / 4u, n3 = kRowThreads - (claims ? 128u : 64u), w4 = w_lo / 4u;
+        const uint32_t q0 = claims && wave == kRowWaves - 1u ? n4 : tid - 64u;
         const uint4 *rows = reinterpret_cast<const uint4 *>(Vc.rows) + w4;
         const uint32_t rs4 = rs / 4u;
         auto token_row = [&](uint32_t id) { return rows + (size_t)id * rs4; };
@@ -684,6 +719,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
                 }
             }
         }
+        if (claims && tid == kRowThreads - 64u) claim_tags(Cc, sh, b);
     }
     // The candidates: a few are the first wavefront's, right away; many are everybody's, once all
     // know the ranges.
@@ -784,12 +820,14 @@ __device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, ui
 
 // kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_span).
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
-// before it (tokens may be null), and takes two tickets right after it: the last workgroup of a row to
-// do so writes the row's state (all have read it), the last of all closes the call, each at its end, when
-// the tickets' answers have long been there.  One launch instead of two, and a row waits for its own
-// lookup only, not for the longest walk of the batch.
+// before it (tokens may be null).  One launch instead of two, and a row waits for its own lookup only, not for
+// the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket: the last
+// workgroup of a row to have read its state writes the new one, at its end, and the last such row of all opens
+// the next call.  (A ticket on one address for every workgroup of the call, taken by the wavefront that walks, cost
+// 10 ns a workgroup: this fill took 28 us for 2,048 workgroups, 18 as it is now.)  Within 64 vector registers, so
+// that 8 workgroups of a unit are resident: with 7 the last 256 of 2,048 began 7 to 11 us after the others.
 template <typename Elem, int kMode, bool kWhole>
-__global__ void __launch_bounds__(kRowThreads, kWhole ? 4 : 8)
+__global__ void __launch_bounds__(kRowThreads, 8)
 rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict__ bitmask, Elem *__restrict__ logits,
             int64_t logits_stride, wg_state_t *__restrict__ states, const int32_t *__restrict__ tokens)
 {
@@ -800,35 +838,48 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
     const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
     uint4 *row4 = reinterpret_cast<uint4 *>(row), *early4 = row4 + n4 + 1u;
-    uint32_t ticket = 0, sid = 0, aux = 0;
-    unsigned long long all = 0, mine_all = 0;         // workgroups | keys claimed << 20 | class tables claimed << 40
+    uint32_t ticket = 0, rows_done = 0;
     uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
     if (kWhole) {
-        StateDesc d{};
-        unsigned long long launch = 0;
+        wg_state_t st{};
+        int32_t t = 0;
         if (tid == 0) {
-            launch = Cc.ctr->launch;
-            sid = states[b].sid; aux = states[b].aux;
-            const int32_t t = tokens ? tokens[b] : 0;
-            Visit v = visit(T, sid);
-            if (tokens) advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, p0 == 0u);
-            d = v.d;
+            const unsigned long long launch = Cc.ctr->launch;
+            st = states[b];
+            if (tokens) t = tokens[b];
+            sh.launch = launch;
+            sh.state = st;
+        }
+        __syncthreads();
+        if (tid == kRowThreads - 64u) {
+            ticket = atomicAdd(&Cc.tickets[b * kTicketStride], 1u);
+            if (ticket == gridDim.x - 1u) rows_done = atomicAdd(Cc.rows_ticket, 1u);
+        }
+        if (tid == 0) {
+            Visit v = visit(T, st.sid);
+            if (tokens) {
+                advance_one(T, Vc, Cc, st.sid, st.aux, v, (int64_t)t, p0 == 0u);
+                sh.state = st;
+            }
             uint32_t variant;
-            sh.ref = key_of(T, sid, aux, d, variant);
+            sh.ref = key_of(T, st.sid, st.aux, v.d, variant);
+            sh.desc = v.d;
         }
         __syncthreads();
         // (key k has arena row k: the row is requested while its tag is looked at)
         const uint32_t key = sh.ref;
+        if (tid >= 128u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
         if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
         __syncthreads();
+        // (and what a missing row takes from the state's own class table)
+        if (tid >> 6 == 1u && is_checkpoint(sh.desc.kind_byte & 0xFFu)) stage_class(T, sh, (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.desc.cls), tid & 63u);
         if (tid == 0) {
-            const Found f = look_up(T, Cc, tag_now(Cc, launch), b, sid, aux, d);
+            const StateDesc d = sh.desc;
+            const Found f = look_up<true>(T, Cc, tag_now(Cc, sh.launch), b, sh.state.sid, sh.state.aux, d, &sh.claim);
             sh.ref = f.ref;
             if (f.ref == kRefBuild) sh.task = f.me;
-            mine_all = 1ull | (f.claimed ? 1ull << 20 : 0ull) | (f.class_claimed ? 1ull << 40 : 0ull);
-            all = atomicAdd(Cc.ticket_all, mine_all);
-            ticket = tokens ? atomicAdd(&Cc.tickets[b], 1u) : 0u;
-            if (f.hit && p0 == 0u) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadHits], 1ull);
+            unsigned long long *count = Cc.spread + (b % kSpread) * kSpreadStride;
+            if (f.hit && p0 == 0u) atomicAdd(&count[kSpreadHits], 1ull);
         }
         __syncthreads();
     }
@@ -842,11 +893,13 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
         const HopState ha = hop(in.hop[0]), hb = hop(in.hop[1]);
         const RowTask me{one(in.sid), one(in.kind), one(in.lit), one(in.cls), one(in.run), one(in.r), one(in.class_state), one(in.eos_next), one(in.slot), {}};
         slot = me.slot;
-        if (!kWhole && tid == kRowThreads - 1u) { sh.task.hop[0] = ha; sh.task.hop[1] = hb; }
-        for (uint32_t q = tid; q < n4; q += kRowThreads) early4[q] = uint4{0u, 0u, 0u, 0u};
-        if (tid >> 6 == 1u && is_checkpoint(me.kind)) stage_class(T, sh, me.cls, tid & 63u);
-        __syncthreads();
-        make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b);
+        if (!kWhole) {
+            if (tid == kRowThreads - 1u) { sh.task.hop[0] = ha; sh.task.hop[1] = hb; }
+            for (uint32_t q = tid; q < n4; q += kRowThreads) early4[q] = uint4{0u, 0u, 0u, 0u};
+            if (tid >> 6 == 1u && is_checkpoint(me.kind)) stage_class(T, sh, me.cls, tid & 63u);
+            __syncthreads();
+        }
+        make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b, kWhole && p0 == 0u);
     }
     // out: to the cache, the caller's bitmask, and LDS for the masking
     const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
@@ -872,15 +925,13 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
     if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
     if (kWhole) {
-        if (tid == 0) {
-            if (tokens && ticket == gridDim.x - 1u) {
-                Cc.tickets[b] = 0u;
-                states[b] = wg_state_t{sid, aux};
-            }
-            if ((uint32_t)(all & 0xFFFFFu) == gridDim.x * gridDim.y - 1u) {
-                *Cc.ticket_all = 0ull;
-                all += mine_all;
-                close_fill(Cc, gridDim.y, (uint32_t)(all >> 20) & 0xFFFFFu, (uint32_t)(all >> 40));
+        if (tid == kRowThreads - 64u && ticket == gridDim.x - 1u) {
+            Cc.tickets[b * kTicketStride] = 0u;
+            if (tokens) states[b] = sh.state;
+            if (rows_done == gridDim.y - 1u) {
+                *Cc.rows_ticket = 0u;
+                Cc.ctr->lookups += gridDim.y;
+                Cc.ctr->launch = sh.launch + 1ull;
             }
         }
     } else if (blockIdx.x == 0 && b == 0 && tid == 0) {
@@ -896,9 +947,16 @@ free_rows_kernel(DeviceCache Cc, uint32_t n_keys, uint32_t *__restrict__ free_ro
 {
     __shared__ uint32_t wave_n[16], base;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const unsigned long long sc = Cc.ctr->slot_ctr;
-    if (tid == 0) base = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;
-    for (uint32_t i = tid; i < n_keys; i += 1024u) Cc.slots[i] = i;
+    if (tid == 0) base = 0u;
+    __syncthreads();
+    uint32_t held = 0;
+    for (uint32_t i = tid; i < n_keys; i += 1024u) {
+        Cc.slots[i] = i;
+        held += (uint32_t)(Cc.tags[i] >> kTagEpochShift) == Cc.epoch;
+    }
+    atomicAdd(&base, held);
+    __syncthreads();
+    if (tid == 0) Cc.ctr->slot_ctr = (unsigned long long)Cc.epoch << 32 | base;
     for (uint32_t r0 = 0; r0 < Cc.cap_rows; r0 += 1024u) {
         const uint32_t r = r0 + tid;
         const bool is_free = r < Cc.cap_rows && !(r < n_keys && (uint32_t)(Cc.tags[r] >> kTagEpochShift) == Cc.epoch);
@@ -1044,39 +1102,38 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
     return dtype == WG_F32 ? n * 4u > kLineBytes32 : n * 2u > kLineBytes16;
 }
 
-// Workgroups per row: the row is cut at its token ranges, into `most` pieces where each gets kPartGroup
-// tokens, else into fewer.
-static uint32_t row_parts(uint32_t V, uint32_t most)
+// Workgroups per row (it is cut at its token ranges).  8, which with long rows of 256 requests is as many as are
+// resident together (kResident to a unit);
+// more where that leaves compute units idle, as long as a workgroup keeps enough tokens to be worth what it
+// starts with: 4,096 up to 6 workgroups on a unit, 6,144 up to 8.  us a step of wg_decode_step, mixed requests,
+// rows made and rows copied, with 8 / 16 / 32:
+//   V = 151936 B = 1 11.3 / 9.7 / 8.8 and 8.3 / 6.8 / 6.0, B = 16 14.2 / 12.6 / 11.7 and 9.1 / 7.5 / 7.2, B = 64 18.6 /
+//   17.7 / 17.0 and 11.7 / 11.0 / 10.9 (random trees 32.0 / 25.5 / 23.0 and 13.4 / 13.9 / 13.4), B = 128 21.5 / 21.1
+//   and 15.8 / 14.5, B = 160 24.1 / 27.2 and 17.3 / 17.4
+//   V = 98304 B = 16 13.9 / 11.4 / 11.6 and 7.8 / 6.8 / 6.8, B = 64 16.6 / 14.7 / 15.9 and 9.9 / 9.3 / 9.8
+//   V = 70000 B = 16 12.7 / 11.1 / 11.4 and 7.0 / 6.4 / 6.6, B = 64 14.6 / 14.1 / 15.2 and 8.7 / 8.5 / 9.2, B = 128
+//   (html) 15.2 / 15.9 and 9.7 / 10.3
+// Fewer where a short row would be cut into scraps: with 8 / 4, V = 20000 B = 256 18.1 / 16.3 and 11.7 / 10.7, B =
+// 1024 49.9 / 37.4 and 22.2 / 18.0, V = 24576 B = 33 10.8 / 11.4 and 6.7 / 6.9, V = 32000 B = 256 19.3 / 18.7 and 12.6
+// / 12.0, B = 1024 51.5 / 40.3 and 23.1 / 21.6 (random trees 57.8 / 48.1 and 26.8 / 32.0); with 4 / 2, V = 12000 B = 64
+// 11.1 / 11.5 and 6.9 / 7.1, B = 1024 36.4 / 29.6 and 16.1 / 15.3.
+constexpr uint32_t kLeastParts = 8, kResident = 8;
+static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
 {
-    uint32_t parts = most;
-    while (parts > 1u && (uint64_t)parts * kPartGroup > V) parts >>= 1;
+    uint32_t parts = kLeastParts;
+    while (parts < kParts) {
+        const uint64_t n = (uint64_t)B * parts * 2u;
+        if (n > (uint64_t)kResident * n_cu || parts * 2u * (n <= 6ull * n_cu ? 4096u : 6144u) > V) break;
+        parts *= 2u;
+    }
+    const uint32_t least = B > n_cu ? 3072u : (uint64_t)B * parts > n_cu ? 2560u : kPartGroup;
+    while (parts > 1u && parts * least > V) parts >>= 1;
     return parts;
 }
-// Most workgroups per row.  8, which is what fills the chip with long rows of 256 requests; more where
-// that leaves compute units idle or with little to do, as long as a workgroup keeps enough tokens to be
-// worth what it starts with:
-//   up to a workgroup on every second unit, 4096 tokens each (us a pass of 8 cached steps, 151936 tokens, 70000
-//   tokens): B = 1 69 with 8, 58 with 16, 51 with 32; B = 4 67, 57, 57; B = 8 72, 66 with 16, 70 with 32
-//   (70000 tokens: 60, 58, 68)
-//   above the one-kernel fill, up to 6 workgroups on a unit, 6144 tokens each.  With 8 / 16, us a step of mixed
-//   requests, rows copied and rows made: V = 151936 B = 48 13.5 / 12.3 and 22.5 / 21.3, B = 96 16.8 / 16.1 and
-//   26.7 / 26.0, B = 128 18.8 / 18.0 and 26.2 / 26.9, B = 160 21.2 / 20.2 and 29.9 / 30.7, B = 256 25.5 / 24.4 and
-//   37.5 / 43.0; V = 98304 B = 48 11.7 / 11.1 and 19.7 / 17.4, B = 96 14.1 / 13.4 and 23.1 / 21.5, B = 160 16.2 /
-//   15.6 and 25.3 / 27.4; html and JSON likewise (B = 128 -4 % and +2 to +5 %).  With fewer tokens the gain ends
-//   sooner: V = 70000 B = 48 10.6 / 10.1 and 18.7 / 17.0, B = 96 12.7 / 12.5 and 21.1 / 21.8 (random trees, fp32:
-//   34.6 / 37.0)
-constexpr uint32_t kLeastParts = 8;
-static uint32_t most_parts(uint32_t V, uint32_t B, uint32_t n_cu)
-{
-    uint32_t most = kLeastParts;
-    while (most < kParts && (uint64_t)B * most * 2u <= n_cu / 2u && (uint64_t)most * 2u * 4096u <= V) most *= 2u;
-    if ((uint64_t)B * most > n_cu && (uint64_t)B * 2u * kLeastParts <= n_cu * 6u && 2u * kLeastParts * 6144u <= V) most = 2u * kLeastParts;
-    return most;
-}
 
-uint32_t rows_lds_bytes(const DeviceVocab &Vc)
+static uint32_t rows_lds(const DeviceVocab &Vc, uint32_t parts)
 {
-    const uint32_t parts = row_parts(Vc.V, kLeastParts), span = kParts / parts;
+    const uint32_t span = kParts / parts;
     uint32_t most = 0;
     for (uint32_t p = 0; p < kParts; p += span) {
         const uint32_t n = ((range_token(Vc, p + span) + 31u) >> 5) - (range_token(Vc, p) >> 5);
@@ -1084,16 +1141,20 @@ uint32_t rows_lds_bytes(const DeviceVocab &Vc)
     }
     return 2u * (((most + 3u) & ~3u) + 4u) * 4u;
 }
+// (the most for any batch: a row in fewer parts than kLeastParts is short)
+uint32_t rows_lds_bytes(const DeviceVocab &Vc) { return rows_lds(Vc, row_parts(Vc.V, kMaxBatch, 1u)); }
 
 FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int dtype, uint32_t n_cu)
 {
     FillPlan p;
-    p.parts = row_parts(Vc.V, most_parts(Vc.V, B, n_cu));
-    // One kernel up to a workgroup per compute unit: there the launch it saves (10 to 13 us of 70 to 85 a
-    // pass of 8 cached steps, B <= 8, 151936 tokens) outweighs the lookup that every workgroup of a row
-    // repeats; with four per unit it is 199 us instead of 190 where the rows are made, and with eight 278
-    // instead of 232.
-    p.one_kernel = Cc.direct && (uint64_t)B * p.parts <= n_cu && !by_lines(dtype, B, Vc.V);
+    p.parts = row_parts(Vc.V, B, n_cu);
+    // One kernel while its workgroups are resident together: what every workgroup of a row repeats of the lookup
+    // is then paid once, and a launch with its lookup is saved.  us a step with two kernels / with one, rows made
+    // and rows copied: V = 151936, mixed, B = 16 16.4 / 12.6 and 10.3 / 7.5, B = 64 21.2 / 17.8 and 14.1 / 11.8, B =
+    // 256 33.8 / 31.6 and 26.0 / 23.0 (random trees 53.0 / 50.8 and 35.7 / 32.7); html, V = 70000, B = 256 21.9 /
+    // 20.3 and 14.3 / 13.4.  Above, workgroups that start late repeat it when the others are done: html, V =
+    // 151936, B = 288 29.5 / 34.7 and 21.2 / 20.4; V = 60000, B = 512 29.3 / 30.5 and 17.7 / 19.8.
+    p.one_kernel = Cc.direct && B <= n_cu && !by_lines(dtype, B, Vc.V);
     return p;
 }
 
@@ -1103,7 +1164,7 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
                        hipStream_t s, hipEvent_t *lookup_ev, hipEvent_t *rows_ev)
 {
     const dim3 g(plan.parts, B);
-    const uint32_t lds = rows_lds_bytes(Vc);
+    const uint32_t lds = rows_lds(Vc, plan.parts);
     const bool whole = plan.one_kernel;
     if (!whole) {
         const hipError_t e = launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, lookup_ev, T, Vc, Cc, states, tokens, B);

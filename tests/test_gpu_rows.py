@@ -123,7 +123,7 @@ def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, 
     assert torch.equal(buf.view(bits), want.view(bits))
 
 
-@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97),
+@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97), (65536, 97), (131072, 48), (131073, 64), (147456, 64), (20481, 40), (24577, 300), (98304, 128), (98304, 129), (40000, 256), (40000, 257),
                                  (40000, 32), (40000, 33), (8200, 7)])
 def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
     """Rows cut into 4 to 32 workgroups, looked up in the rows' kernel and before it."""
@@ -152,6 +152,55 @@ def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
         wg.select_tokens(mask, V, draws[k], tok)
     n = h.cache_stats()
     assert h.error_count() == 0 and n["lookups"] == 4 * B and n["hits"] + n["builds"] <= 4 * B
+
+
+@pytest.mark.parametrize("V,B", [(12001, 1), (20011, 31), (30000, 129), (98304, 96), (151936, 64), (20011, 255), (20011, 256), (20011, 257), (40000, 256)])
+def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
+    """Every workgroup of a row looks it up by itself up to a request per compute unit, and several make
+    the same row and class rows: masks, counters and rows in use are as if one had, the rows are there for
+    later calls in one kernel and in two, and they stay when the arena stops being addressed by key."""
+    torch = torch_cuda
+    base = ws.make_workload(3, V=V, B=1, steps=1)
+    args = list(base.args[:1]) + [{"x": bytes(np.random.default_rng(1).integers(1, 256, 5000, dtype=np.uint8))}]
+    texts = list(base.texts[:1]) + ["Sequence(Write($x))"]
+    w = dataclasses.replace(base, texts=texts, args=args, B=2, request_template=np.arange(2, dtype=np.int64))
+    o = H.make_oracle(w)
+    import paper_2507_16768_amd as wg
+    h = wg.Handle(texts[:1], args[:1], wg.Vocab(w.vocab.bytes, w.vocab.offsets, w.vocab.eos_id), flags=wg.EOS_RESTART)
+    own = h.num_states
+    mask = torch.empty((300, h.W), dtype=torch.int32, device="cuda")
+
+    def fill(sids):
+        st = np.stack([sids, np.zeros_like(sids)], 1).astype(np.uint32)
+        before = h.cache_stats()
+        mask.fill_(0x35353535)
+        h.fill_masks(H.dev_states(st), mask[:len(st)])
+        assert (H.host_mask(mask[:len(st)]) == o.fill_masks(st)).all()
+        after = h.cache_stats()
+        assert after["lookups"] - before["lookups"] == len(st)
+        return {k: after[k] - before[k] for k in ("builds", "hits", "class_scans")}, after["rows_in_use"]
+
+    sids = 1 + np.arange(B, dtype=np.uint32) % (own - 1)
+    n = len(np.unique(sids))
+    for _ in range(2):
+        d, used = fill(sids)
+        assert d["builds"] == n == used and d["hits"] == 0
+        d, used = fill(sids)
+        assert d["builds"] == 0 and d["class_scans"] == 0 and d["hits"] == B and used == n
+        h.cache_clear()
+    fill(sids)
+    rest = 1 + np.arange(300, dtype=np.uint32) % (own - 1)          # two kernels find them, and make the others
+    d, used = fill(rest)
+    assert d["builds"] == own - 1 - n and used == own - 1
+    h.add_instances(texts[1:], args[1:])                            # more keys than rows
+    s = h.cache_stats()
+    assert s["keys"] > s["cache_rows"] and s["rows_in_use"] == own - 1
+    d, used = fill(sids)
+    assert d["builds"] == 0 and d["hits"] == B
+    d, used = fill(np.arange(own, own + 40, dtype=np.uint32))
+    assert d["builds"] == 40 and used == own - 1 + 40
+    d, _ = fill(np.concatenate([sids[:200], np.arange(own, own + 40, dtype=np.uint32)]))
+    assert d["builds"] == 0
 
 
 def test_additions_of_every_size(torch_cuda):
