@@ -366,22 +366,65 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
 }
 
 // ---------------------------------------------------------------------------------------------
-// Masking a stretch of one row's logits: -inf over the tokens [lo, hi) whose bit is 0.  `row` is in
-// LDS, its bit 0 is token `base`; the whole workgroup calls it.
+// Masking: -inf over the tokens whose bit is 0.  Nothing is read from the logits where it can be helped.
 //
-// Nothing is read from the logits where it can be helped: a 16-byte piece with no allowed token is
-// overwritten, an untouched one is skipped, a mixed one gets one store per disallowed token
-// (found by count-trailing-zeros: a piece of a free-text row has one or two).  Such a store covers
-// part of a 64-byte block, which the last-level cache (256 MB) merges as long as the logits fit it;
-// beyond that the memory reads and writes the block.  kLine is for that case: every 128-byte line
-// with a disallowed token is read where it has to be and written whole, 8 lanes x 16 bytes.
-// Rows may start at any element: the pieces are cut where the addresses allow 16-byte stores, the
-// tokens before and behind them are stored one by one.
-template <typename Elem, bool kLine>
-__device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi, uint32_t base, const uint32_t *row)
+// A wavefront takes 64 tokens at a time, a lane each, and their mask bits are the lanes that store: one instruction
+// and two to four 64-byte requests per 64 tokens, whatever the pattern and wherever the row starts.  With a 16-byte
+// piece to a lane, and a store per disallowed token of a mixed piece, each of the stores was a request for every 64
+// bytes that the wavefront spans.  Before -> now, html outlines / JSON / mixed / random trees, us: wg_apply_mask, bf16,
+// V = 151936, B = 256 11.7 / 12.2 / 14.9 / 21.0 -> 11.4 / 11.3 / 13.4 / 15.7; V = 128256, B = 64 4.6 / 5.6 / 5.9 / 7.9 -> 4.4 / 4.5
+// / 4.8 / 5.1; fp32 6.5 / 7.8 / 7.1 / 9.5 -> 5.0 / 5.2 / 6.0 / 7.0; a cached wg_decode_step, V = 151936, B = 256, mixed 22.9 ->
+// 18.8, V = 128256, B = 64 8.8 / 9.3 / 9.8 / 11.9 -> 8.9 / 8.9 / 9.2 / 9.8.  (Wavefronts that take pieces where these are fewer
+// instructions were 5 to 15 % slower; so were stores without the compiler's branch around them, which skips words that
+// are allowed as a whole.)
+// What is left is the memory's: a store that covers part of a 64-byte block costs it 2.3 times a whole block.  The
+// last-level cache (256 MB) merges such stores as long as the logits fit it; beyond that the memory reads and writes
+// the block, and whole lines are written instead (mask_lines).
+//
+// Lanes first ... first + kChunk - 1 hold the mask bits of 64 tokens each in lo and hi, the first of them at p.
+constexpr uint32_t kChunk = 8u;
+template <typename Elem>
+__device__ __forceinline__ void mask_chunk(Elem *p, uint32_t lo, uint32_t hi, uint32_t first)
+{
+    constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
+    const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+    for (uint32_t u = 0; u < kChunk; u++) {
+        const unsigned long long m = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(first + u)) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(first + u));
+        if (__builtin_amdgcn_inverse_ballot_w64(~m)) p[u * 64u + lane] = kNinf;
+    }
+}
+// Word w of the `words` that hold a row's V tokens; what lies behind the last token counts as allowed.
+__device__ __forceinline__ uint32_t word_or_ones(const uint32_t *row, uint32_t w, uint32_t words, uint32_t V)
+{
+    uint32_t x = w < words ? row[w] : 0xFFFFFFFFu;
+    if (w + 1u == words && (V & 31u)) x |= ~0u << (V & 31u);
+    return x;
+}
+// The whole workgroup masks the tokens [lo, hi) of a row; `row` is in LDS, its bit 0 is token lo.  The wavefronts
+// take chunks in turn, so that all of them write close together (a quarter of the share each was 3 to 8 % slower).
+template <typename Elem>
+__device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t V = hi - lo, words = (V + 31u) >> 5, pairs = (words + 1u) >> 1, step = (blockDim.x >> 6) * kChunk;
+    for (uint32_t i0 = wave * kChunk; i0 < pairs; i0 += step * (64u / kChunk)) {
+        const uint32_t w = 2u * (i0 + lane / kChunk * step + lane % kChunk);      // a lane per pair of words, eight chunks at a time
+        const uint32_t a = word_or_ones(row, w, words, V), b = word_or_ones(row, w + 1u, words, V);
+        for (uint32_t c = 0; c < 64u / kChunk && i0 + c * step < pairs; c++)
+            mask_chunk<Elem>(logits + lo + (size_t)(i0 + c * step) * 64u, a, b, c * kChunk);
+    }
+}
+
+// The same by whole lines: every 128-byte line with a disallowed token is read where it has to be and written
+// whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
+// are stored one by one.
+template <typename Elem>
+__device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
     constexpr uint32_t kPer = 16u / sizeof(Elem);                  // tokens of a piece
-    constexpr uint32_t kAlign = kLine ? 128u : 16u;
+    constexpr uint32_t kAlign = 128u;
     constexpr uint32_t kBatch = 4u;                                // pieces of a thread in flight together
     constexpr uint32_t kAll = (1u << kPer) - 1u;
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
@@ -391,49 +434,39 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
     uint32_t head = at % sizeof(Elem) ? hi - lo : (uint32_t)((kAlign - at % kAlign) % kAlign / sizeof(Elem));
     if (head > hi - lo) head = hi - lo;
     const uint32_t t0 = lo + head, pieces = (hi - t0) / kPer, t1 = t0 + pieces * kPer;
-    auto disallowed = [&](uint32_t t) { return !((row[(t - base) >> 5] >> ((t - base) & 31u)) & 1u); };
+    auto disallowed = [&](uint32_t t) { return !((row[(t - lo) >> 5] >> ((t - lo) & 31u)) & 1u); };
     for (uint32_t i = tid; i < head; i += nt) if (disallowed(lo + i)) logits[lo + i] = kNinf;
     for (uint32_t t = t1 + tid; t < hi; t += nt) if (disallowed(t)) logits[t] = kNinf;
-    const uint32_t off = t0 - base;
     for (uint32_t p0 = 0; p0 < pieces; p0 += nt * kBatch) {
         uint32_t z[kBatch];                                        // disallowed tokens of the pieces
+        uint4 v[kBatch];
+        bool put[kBatch];
+        const unsigned long long line = 0xFFull << (tid & 56u);
 #pragma unroll
         for (uint32_t i = 0; i < kBatch; i++) {
-            const uint32_t p = p0 + i * nt + tid, bit = off + p * kPer;
+            const uint32_t p = p0 + i * nt + tid, bit = head + p * kPer;
             // (the word behind the row's last one is there to be read)
             z[i] = p < pieces ? ~__builtin_amdgcn_alignbit(row[(bit >> 5) + 1u], row[bit >> 5], bit & 31u) & kAll : 0u;
         }
-        if (kLine) {
-            uint4 v[kBatch];
-            bool put[kBatch];
-            const unsigned long long line = 0xFFull << (tid & 56u);
 #pragma unroll
-            for (uint32_t i = 0; i < kBatch; i++) {
-                const uint32_t p = p0 + i * nt + tid;
-                put[i] = p < pieces && (__ballot(z[i] != 0u) & line);
-                v[i] = uint4{0u, 0u, 0u, 0u};
-                if (put[i] && z[i] != kAll) v[i] = *reinterpret_cast<const uint4 *>(logits + t0 + (size_t)p * kPer);
+        for (uint32_t i = 0; i < kBatch; i++) {
+            const uint32_t p = p0 + i * nt + tid;
+            put[i] = p < pieces && (__ballot(z[i] != 0u) & line);
+            v[i] = uint4{0u, 0u, 0u, 0u};
+            if (put[i] && z[i] != kAll) v[i] = *reinterpret_cast<const uint4 *>(logits + t0 + (size_t)p * kPer);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kBatch; i++) {
+            if (!put[i]) continue;
+            uint32_t d[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; k++) {
+                uint32_t m;
+                if (sizeof(Elem) == 4) m = (uint32_t)__builtin_amdgcn_sbfe(z[i], k, 1);
+                else m = ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k, 1) & 0xFFFFu) | ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k + 1, 1) << 16);
+                d[k] = (d[k] & ~m) | (kFill & m);
             }
-#pragma unroll
-            for (uint32_t i = 0; i < kBatch; i++) {
-                if (!put[i]) continue;
-                uint32_t d[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-                for (uint32_t k = 0; k < 4u; k++) {
-                    uint32_t m;
-                    if (sizeof(Elem) == 4) m = (uint32_t)__builtin_amdgcn_sbfe(z[i], k, 1);
-                    else m = ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k, 1) & 0xFFFFu) | ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k + 1, 1) << 16);
-                    d[k] = (d[k] & ~m) | (kFill & m);
-                }
-                *reinterpret_cast<uint4 *>(logits + t0 + (size_t)(p0 + i * nt + tid) * kPer) = uint4{d[0], d[1], d[2], d[3]};
-            }
-        } else {
-#pragma unroll
-            for (uint32_t i = 0; i < kBatch; i++) {
-                Elem *p = logits + t0 + (size_t)(p0 + i * nt + tid) * kPer;
-                if (z[i] == kAll) *reinterpret_cast<uint4 *>(p) = uint4{kFill, kFill, kFill, kFill};
-                else while (z[i]) { p[__builtin_ctz(z[i])] = kNinf; z[i] &= z[i] - 1u; }
-            }
+            *reinterpret_cast<uint4 *>(logits + t0 + (size_t)(p0 + i * nt + tid) * kPer) = uint4{d[0], d[1], d[2], d[3]};
         }
     }
 }
@@ -818,7 +851,7 @@ __device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, ui
     Cc.ctr->launch++;
 }
 
-// kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_span).
+// kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_lines).
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
 // before it (tokens may be null).  One launch instead of two, and a row waits for its own lookup only, not for
 // the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket: the last
@@ -923,7 +956,8 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     }
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
-    if (kMode) mask_span<Elem, kMode == 2>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, tok_lo, row);
+    if (kMode == 1) mask_span<Elem>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 2) mask_lines<Elem>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
     if (kWhole) {
         if (tid == kRowThreads - 64u && ticket == gridDim.x - 1u) {
             Cc.tickets[b * kTicketStride] = 0u;
@@ -973,49 +1007,39 @@ free_rows_kernel(DeviceCache Cc, uint32_t n_keys, uint32_t *__restrict__ free_ro
     }
 }
 
-// apply: a workgroup takes kApplyTokens tokens of a row.
-constexpr uint32_t kApplyTokens = 8192;
-template <typename Elem, bool kLine>
+// apply: a wavefront takes kApplyPairs times 64 tokens of a row, its mask straight from memory (with 8, 16, 32 and
+// 64, V = 151936, B = 256, bf16, mixed 14.5, 13.6, 13.1 and 13.4 us; V = 32000, B = 256 5.0, 4.9, 4.6 and 5.6).
+constexpr uint32_t kApplyPairs = 32;
+template <typename Elem>
 __global__ void __launch_bounds__(256)
 apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
-    __shared__ uint32_t row[kApplyTokens / 32u + 1u];
-    const uint32_t b = blockIdx.y, lo = blockIdx.x * kApplyTokens, hi = lo + kApplyTokens < V ? lo + kApplyTokens : V;
-    static_assert(kApplyTokens == 32u * 256u, "a mask word per thread");
+    const uint32_t b = blockIdx.y, lane = threadIdx.x & 63u;
+    const uint32_t first = (blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * kApplyPairs;
+    const uint32_t *row = bitmask + (size_t)b * W;
+    const uint32_t w = 2u * (first + lane);
+    uint32_t lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu;
+    if (lane < kApplyPairs) {
+        lo = word_or_ones(row, w, W, V);
+        hi = word_or_ones(row, w + 1u, W, V);
+    }
+#pragma unroll
+    for (uint32_t c = 0; c < kApplyPairs; c += kChunk) mask_chunk<Elem>(logits + (int64_t)b * row_stride + (size_t)(first + c) * 64u, lo, hi, c);
+}
+
+// The same by whole lines: a workgroup takes kLineTokens tokens of a row.
+constexpr uint32_t kLineTokens = 8192;
+template <typename Elem>
+__global__ void __launch_bounds__(256)
+apply_lines_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
+{
+    __shared__ uint32_t row[kLineTokens / 32u + 1u];
+    const uint32_t b = blockIdx.y, lo = blockIdx.x * kLineTokens, hi = lo + kLineTokens < V ? lo + kLineTokens : V;
+    static_assert(kLineTokens == 32u * 256u, "a mask word per thread");
     const uint32_t w = (lo >> 5) + threadIdx.x;
     row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
     __syncthreads();
-    mask_span<Elem, kLine>(logits + (int64_t)b * row_stride, lo, hi, lo, row);
-}
-
-// The same for bf16 rows that begin at multiples of 16 bytes, where a mask byte is a 16-byte piece of logits:
-// kByteGroups bytes a thread straight from memory, no LDS and no barrier before the stores.  V = 151936, B =
-// 256, staged -> straight, us: html 13.4 -> 12.3, JSON 13.9 -> 13.0, mixed 16.0 -> 14.9, random trees 24.2 ->
-// 23.1, one token of 1,600 disallowed 7.5 -> 6.6 (two bytes a thread; with one 13.2, 13.7, 15.2, 22.5, 7.8, with
-// four 12.9, 13.4, 15.8, 24.0, 6.2).  fp32 is slower so: its pieces are half a byte (random trees, V = 128256, B =
-// 256 24.9 staged, 33.6 with two stores to a byte).
-constexpr uint32_t kByteGroups = 2;
-__global__ void __launch_bounds__(256)
-apply_bytes_kernel(uint16_t *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
-{
-    const uint32_t b = blockIdx.y, g0 = blockIdx.x * (256u * kByteGroups) + threadIdx.x;      // 8 tokens each
-    const uint8_t *row = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * W);
-    uint32_t m[kByteGroups];
-#pragma unroll
-    for (uint32_t i = 0; i < kByteGroups; i++) {
-        const uint32_t g = g0 + i * 256u;
-        m[i] = g * 8u < V ? row[g] : 0xFFu;
-    }
-#pragma unroll
-    for (uint32_t i = 0; i < kByteGroups; i++) {
-        if (m[i] == 0xFFu) continue;
-        const uint32_t t = (g0 + i * 256u) * 8u;
-        uint16_t *p = logits + (int64_t)b * row_stride + t;
-        uint32_t z = ~m[i] & 0xFFu;
-        if (V - t < 8u) z &= (1u << (V - t)) - 1u;             // (the row ends inside this byte)
-        if (z == 0xFFu) *reinterpret_cast<uint4 *>(p) = uint4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
-        else while (z) { p[__builtin_ctz(z)] = (uint16_t)0xFF80u; z &= z - 1u; }
-    }
+    mask_lines<Elem>(logits + (int64_t)b * row_stride, lo, hi, row);
 }
 
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
@@ -1081,16 +1105,16 @@ select_kernel(const uint32_t *__restrict__ bitmask, uint32_t W, const uint64_t *
 
 static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
-// Logits of more bytes than these are masked by whole lines (see mask_span): 128 bytes are read where a
+// Logits of more bytes than these are masked by whole lines (see mask_lines): 128 bytes are read where a
 // line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
 // depends on how many tokens of a line are disallowed, which the host does not know; the limits lie where
 // the geometric mean over four kinds of masks is the same for both.  By elements / by lines, us, a cached
 // step on the masks of html outlines, of JSON objects, of both mixed, and of random trees (16, 25, 45 and 63 %
 // of the tokens disallowed):
-//   bf16, V = 151936: 213 MB 55 / 79, 69 / 79, 97 / 84, 113 / 87; 225 MB 67 / 85, 77 / 84, 103 / 90, 110 / 89;
-//   252 MB 100 / 96, 98 / 95, 116 / 101, 129 / 102; 311 MB 127 / 118, 126 / 115, 144 / 121, 148 / 119
-//   fp32, V = 128256: 308 MB 60 / 90, 70 / 93, 113 / 104, 140 / 118; 328 MB 84 / 96, 90 / 98, 120 / 111, 146 / 125;
-//   359 MB 101 / 103, 97 / 102, 131 / 117, 152 / 126; 525 MB 153 / 145, 152 / 144, 189 / 164, 237 / 192
+//   bf16, V = 151936: 194 MB 50 / 72, 47 / 72, 83 / 78, 94 / 80; 213 MB 58 / 82, 63 / 79, 95 / 86, 101 / 89; 225 MB 78 / 88,
+//   76 / 87, 100 / 92, 103 / 90; 252 MB 97 / 100, 97 / 98, 114 / 103, 114 / 98; 311 MB 128 / 117, 125 / 117, 140 / 120, 147 / 124
+//   fp32, V = 128256: 308 MB 59 / 91, 66 / 93, 110 / 105, 126 / 110; 328 MB 79 / 98, 82 / 97, 119 / 110, 143 / 125; 359 MB
+//   81 / 102, 97 / 104, 131 / 118, 156 / 131; 513 MB 152 / 144, 148 / 142, 184 / 161, 224 / 184
 // (a block holds twice as many bf16 tokens, so fewer of them stay untouched.)  So html outlines lose up to a
 // quarter right above the limit and random trees a quarter right below it.  Deciding by the density of each
 // row or line was slower than the better of the two for all.
@@ -1103,27 +1127,23 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
 }
 
 // Workgroups per row (it is cut at its token ranges).  8, which with long rows of 256 requests is as many as are
-// resident together (kResident to a unit);
-// more where that leaves compute units idle, as long as a workgroup keeps enough tokens to be worth what it
-// starts with: 4,096 up to 6 workgroups on a unit, 6,144 up to 8.  us a step of wg_decode_step, mixed requests,
-// rows made and rows copied, with 8 / 16 / 32:
-//   V = 151936 B = 1 11.3 / 9.7 / 8.8 and 8.3 / 6.8 / 6.0, B = 16 14.2 / 12.6 / 11.7 and 9.1 / 7.5 / 7.2, B = 64 18.6 /
-//   17.7 / 17.0 and 11.7 / 11.0 / 10.9 (random trees 32.0 / 25.5 / 23.0 and 13.4 / 13.9 / 13.4), B = 128 21.5 / 21.1
-//   and 15.8 / 14.5, B = 160 24.1 / 27.2 and 17.3 / 17.4
-//   V = 98304 B = 16 13.9 / 11.4 / 11.6 and 7.8 / 6.8 / 6.8, B = 64 16.6 / 14.7 / 15.9 and 9.9 / 9.3 / 9.8
-//   V = 70000 B = 16 12.7 / 11.1 / 11.4 and 7.0 / 6.4 / 6.6, B = 64 14.6 / 14.1 / 15.2 and 8.7 / 8.5 / 9.2, B = 128
-//   (html) 15.2 / 15.9 and 9.7 / 10.3
+// resident together (8 to a unit); more where that leaves compute units idle, as long as a workgroup keeps enough
+// tokens to be worth what it starts with: 4,096 up to 4 workgroups on a unit, 6,144 up to 7.  Geometric means over the
+// masks of four kinds of templates, wg_decode_step, time with 16 / with 8, rows made and rows copied:
+//   V = 151936 B = 64 0.90 0.94, 96 0.95 0.98, 112 0.93 0.98, 128 0.96 1.01; 100003 B = 64 0.93 0.96, 96 0.94 1.00, 112 1.00
+//   1.00, 128 1.03 1.02; 65536 B = 24 0.93 0.96, 64 0.95 0.99, 96 1.01 1.01; with 32 / with 16, 151936 B = 16 0.96 0.97, 32 0.96
+//   0.99, 48 1.03 1.02; mixed, us with 8 / 16 / 32, 151936 B = 1 11.3 / 9.7 / 8.8 and 8.3 / 6.8 / 6.0
 // Fewer where a short row would be cut into scraps: with 8 / 4, V = 20000 B = 256 18.1 / 16.3 and 11.7 / 10.7, B =
 // 1024 49.9 / 37.4 and 22.2 / 18.0, V = 24576 B = 33 10.8 / 11.4 and 6.7 / 6.9, V = 32000 B = 256 19.3 / 18.7 and 12.6
 // / 12.0, B = 1024 51.5 / 40.3 and 23.1 / 21.6 (random trees 57.8 / 48.1 and 26.8 / 32.0); with 4 / 2, V = 12000 B = 64
 // 11.1 / 11.5 and 6.9 / 7.1, B = 1024 36.4 / 29.6 and 16.1 / 15.3.
-constexpr uint32_t kLeastParts = 8, kResident = 8;
+constexpr uint32_t kLeastParts = 8;
 static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
 {
     uint32_t parts = kLeastParts;
     while (parts < kParts) {
         const uint64_t n = (uint64_t)B * parts * 2u;
-        if (n > (uint64_t)kResident * n_cu || parts * 2u * (n <= 6ull * n_cu ? 4096u : 6144u) > V) break;
+        if (n > 7ull * n_cu || parts * 2u * (n <= 4ull * n_cu ? 4096u : 6144u) > V) break;
         parts *= 2u;
     }
     const uint32_t least = B > n_cu ? 3072u : (uint64_t)B * parts > n_cu ? 2560u : kPartGroup;
@@ -1212,15 +1232,11 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
                         const uint32_t *bitmask, hipStream_t s, hipEvent_t *ev)
 {
     const uint32_t W = (V + 31u) / 32u;
-    const dim3 g(cdiv(V, kApplyTokens), B);
-    if (dtype == WG_F32) {
-        uint32_t *x = static_cast<uint32_t *>(logits);
-        return launch(by_lines(dtype, B, V) ? apply_kernel<uint32_t, true> : apply_kernel<uint32_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
-    }
-    uint16_t *x = static_cast<uint16_t *>(logits);
-    if (!by_lines(dtype, B, V) && reinterpret_cast<uintptr_t>(logits) % 16u == 0u && row_stride % 8 == 0)
-        return launch(apply_bytes_kernel, dim3(cdiv(V, 8u * 256u * kByteGroups), B), dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
-    return launch(by_lines(dtype, B, V) ? apply_kernel<uint16_t, true> : apply_kernel<uint16_t, false>, g, dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
+    const bool lines = by_lines(dtype, B, V);
+    const dim3 g(cdiv(V, lines ? kLineTokens : 4u * 64u * kApplyPairs), B);
+    if (dtype == WG_F32)
+        return launch(lines ? apply_lines_kernel<uint32_t> : apply_kernel<uint32_t>, g, dim3(256), 0, s, ev, static_cast<uint32_t *>(logits), row_stride, V, W, bitmask);
+    return launch(lines ? apply_lines_kernel<uint16_t> : apply_kernel<uint16_t>, g, dim3(256), 0, s, ev, static_cast<uint16_t *>(logits), row_stride, V, W, bitmask);
 }
 
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,

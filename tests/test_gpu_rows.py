@@ -76,7 +76,7 @@ def _unpack(torch, mask, V):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("V", [33, 1000, 8191, 8193, 20001])
+@pytest.mark.parametrize("V", [1, 33, 65, 1000, 2047, 2049, 2113, 8191, 8193, 20001])
 def test_masking_at_every_alignment(torch_cuda, V, dtype):
     """apply_mask on rows that start 0 .. 17 elements into a buffer, odd and even strides."""
     torch = torch_cuda
@@ -123,7 +123,7 @@ def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, 
     assert torch.equal(buf.view(bits), want.view(bits))
 
 
-@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97), (65536, 97), (131072, 48), (131073, 64), (147456, 64), (20481, 40), (24577, 300), (98304, 128), (98304, 129), (40000, 256), (40000, 257),
+@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97), (65536, 97), (131072, 48), (131073, 64), (147456, 64), (20481, 40), (24577, 300), (98304, 64), (98304, 112), (98304, 113), (131072, 32), (131072, 33), (40000, 256), (40000, 257),
                                  (40000, 32), (40000, 33), (8200, 7)])
 def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
     """Rows cut into 4 to 32 workgroups, looked up in the rows' kernel and before it."""
