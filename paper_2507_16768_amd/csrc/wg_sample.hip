@@ -185,11 +185,17 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     const uint32_t lo = blockIdx.x * share < r.pieces ? blockIdx.x * share : r.pieces;
     const uint32_t hi = r.pieces - lo < share ? r.pieces : lo + share;
     float best = __builtin_nanf("");
-    uint32_t where = kNoPiece;                        // the thread's first piece with `best`
-    stream_row(r, mask, W, words, lo, hi, [&](uint32_t p, const uint4 &v, uint32_t m) {
+    // the thread's first piece with `best`, and its elements (looked up again at the end they were a trip to memory: V =
+    // 151936, bf16, B = 256 19.6 -> 18.8 us, B = 128 12.4 -> 11.9, B = 1 5.6 -> 5.5)
+    uint32_t where = kNoPiece;
+    union { uint4 v; Elem e[Row<Elem>::kPer]; } held;
+    held.v = uint4{0u, 0u, 0u, 0u};
+    uint32_t held_mask = 0;
+    auto see = [&](uint32_t p, const uint4 &v, uint32_t m) {
         const float x = piece_max(v, m, Elem(0));
-        if (x > best || (where == kNoPiece && x == x)) { best = x; where = p; }
-    });
+        if (x > best || (where == kNoPiece && x == x)) { best = x; where = p; held.v = v; held_mask = m; }
+    };
+    stream_row(r, mask, W, words, lo, hi, see);
     float top = best;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) top = __builtin_fmaxf(top, __shfl_xor(top, o));
@@ -201,16 +207,13 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     for (uint32_t w = 1; w < kWaves; w++) top = __builtin_fmaxf(top, part[w]);
     const bool number = top == top;
     if (number) {
-        // The lowest token whose logit equals the maximum (as numbers, so -0.0 and +0.0 tie), from
-        // the threads that hold it: their first such piece once more.
+        // The lowest token whose logit equals the maximum (as numbers, so -0.0 and +0.0 tie), from the
+        // threads that hold it, in the first such piece of each.
         if (where != kNoPiece && best == top) {
-            const uint32_t m = piece_mask(r, mask, W, where);
-            union { uint4 v; Elem e[Row<Elem>::kPer]; } u;
-            u.v = r.load(where, m);
             uint32_t eq = 0;
 #pragma unroll
-            for (uint32_t i = 0; i < Row<Elem>::kPer; i++) eq |= (uint32_t)(elem_float(u.e[i]) == top) << i;
-            atomicMin(&best_token, r.token(where, (uint32_t)__builtin_ctz(eq & m)));
+            for (uint32_t i = 0; i < Row<Elem>::kPer; i++) eq |= (uint32_t)(elem_float(held.e[i]) == top) << i;
+            atomicMin(&best_token, r.token(where, (uint32_t)__builtin_ctz(eq & held_mask)));
         }
     } else {
         // no number among the allowed tokens: the lowest of them (all NaN), if there is one
@@ -375,6 +378,24 @@ __device__ __forceinline__ uint32_t reaching(const uint4 &v, uint32_t m, uint32_
     return bound ? take & m : m;
 }
 
+// Element i of a piece, and the key of its token.
+__device__ __forceinline__ uint32_t element(const uint4 &v, uint32_t i, uint32_t)
+{
+    // (values: a choice between members is one between their addresses, which puts the piece into memory)
+    const uint32_t x = v.x, y = v.y, z = v.z, w = v.w, odd = 0u - (i & 1u), high = 0u - (i >> 1 & 1u);
+    const uint32_t lo = (x & ~odd) | (y & odd), hi = (z & ~odd) | (w & odd);
+    return (lo & ~high) | (hi & high);
+}
+__device__ __forceinline__ uint16_t element(const uint4 &v, uint32_t i, uint16_t)
+{
+    return (uint16_t)(element(v, i >> 1, 0u) >> (16u * (i & 1u)));
+}
+template <typename Elem>
+__device__ __forceinline__ unsigned long long key_of(const Row<Elem> &r, const uint4 &v, uint32_t p, uint32_t i)
+{
+    return (unsigned long long)rank_of(element(v, i, Elem(0))) << 32 | (0xFFFFFFFFu - r.token(p, i));
+}
+
 // The keys of n candidate tokens, from their logits read again (which register of which thread holds a
 // candidate's is not known at compile time; they are in the L2).
 template <uint32_t kT, typename Elem>
@@ -419,7 +440,6 @@ struct TopkShared {
         uint32_t bins[256];
     };
     uint32_t threads[kThreads];                      // threads that hold candidates
-    uint32_t id[kCand];                              // the candidates' tokens, before their keys are made
     uint32_t count[kWaves];
     uint32_t n, n_threads, digit, above;
 };
@@ -477,15 +497,14 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
                 const uint32_t i = (uint32_t)__builtin_ctz(take);
                 take &= take - 1u;
                 const uint32_t at = atomicAdd(&sh.n, 1u);
-                if (at < kCand) sh.id[at] = r.token(p[j], i);
+                if (at < kCand) sh.cand[at] = key_of(r, v[j], p[j], i);
             }
         }
     }
     __syncthreads();
     uint32_t n = sh.n;
-    if (n <= kCand) make_keys<kThreads>(sh.cand, sh.id, n, r);
-    __syncthreads();                                  // every thread has read the count
     if (n > kCand) {
+        __syncthreads();                              // every thread has read the count
         // Too many tie.  The rank of the k-th best exactly, a byte at a time from the counts of the
         // tokens that agree in the bytes before; then the tokens above it, and of those at it the
         // lowest ids.
