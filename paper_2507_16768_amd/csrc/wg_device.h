@@ -93,7 +93,7 @@ constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
 constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1,
-                   kSpreadBuilds = 2, kSpreadClasses = 3;       // of one-kernel fills
+                   kSpreadBuilds = 2, kSpreadClasses = 3;       // of fills with the arena addressed by key
 constexpr uint32_t kTicketStride = 32;     // a 128-byte line for the tickets of a row
 
 struct DeviceCache {

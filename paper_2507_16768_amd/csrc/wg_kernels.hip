@@ -343,14 +343,22 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
     }
     // the claimers of a wavefront take their arena rows together
     const unsigned long long cm = __ballot(f.claimed), km = __ballot(f.class_claimed);
-    if (cm) {
+    // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread, and the claims too
+    // where nothing is handed out by their number)
+    unsigned long long *count = &Cc.spread[(blockIdx.x % kSpread) * kSpreadStride];
+    if (cm && Cc.direct) {
+        if (lane == 0) {
+            atomicAdd(&count[kSpreadBuilds], (unsigned long long)__popcll(cm));
+            if (km) atomicAdd(&count[kSpreadClasses], (unsigned long long)__popcll(km));
+        }
+    } else if (cm) {
         uint32_t first = 0;
         if (lane == 0) {
             first = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
             if (km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
         }
         first = __shfl(first, 0);
-        if (f.claimed && !Cc.direct) {
+        if (f.claimed) {
             const uint32_t idx = rows0 + first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
             f.me.slot = idx < Cc.cap_rows ? (Cc.free_rows ? Cc.free_rows[idx] : idx) : kNoSlot;
             Cc.slots[f.key] = f.me.slot;
@@ -360,9 +368,8 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
         Cc.row_ref[b] = f.ref;
         if (f.ref == kRefBuild) Cc.tasks[b] = f.me;
     }
-    // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread)
     const unsigned long long hv = __ballot(f.hit);
-    if (lane == 0 && hv) atomicAdd(&Cc.spread[(blockIdx.x % kSpread) * kSpreadStride + kSpreadHits], (unsigned long long)__popcll(hv));
+    if (lane == 0 && hv) atomicAdd(&count[kSpreadHits], (unsigned long long)__popcll(hv));
 }
 
 // ---------------------------------------------------------------------------------------------
