@@ -210,7 +210,7 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
     if (n_states > h->up_states || n_classes > h->up_classes) {
         const uint32_t s0 = h->up_states, ns = n_states - s0, c0 = h->up_classes, nc = n_classes - c0;
         h->plans.resize(n_classes);
-        for (uint32_t c = c0; c < n_classes; c++) h->plans[c] = class_plan_of(t.classes.data() + (size_t)c * 256);
+        for (uint32_t c = c0; c < n_classes; c++) h->plans[c] = wide_plan_of(t.classes.data() + (size_t)c * 256);
         struct { void *dst; const void *src; size_t bytes; } part[4] = {
             {h->d_states + s0, t.states.data() + s0, ns * sizeof(StateDesc)},
             {h->d_lit + s0, t.lit.data() + s0, ns},
@@ -327,8 +327,17 @@ static int create_vocab(const uint8_t *host_bytes, const uint64_t *host_offsets,
     }
     // the token rows, likewise
     std::vector<uint32_t> rows;
-    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size() + ix.len_rows.size());
-    for (const auto *r : {&ix.byte_rows, &ix.block_rows, &ix.tail_rows, &ix.len_rows}) rows.insert(rows.end(), r->begin(), r->end());
+    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size() + ix.len_rows.size() + (size_t)kWideRows * ix.row_stride);
+    for (const auto *r : {&ix.byte_rows, &ix.block_rows, &ix.tail_rows}) rows.insert(rows.end(), r->begin(), r->end());
+    const size_t rs = ix.row_stride;
+    rows.resize((size_t)(kWideRow + kWideRows) * rs, 0u);
+    for (uint32_t values = 32; values <= 128; values *= 2)
+        for (uint32_t k = 0; k < 16; k++) {                // from the rows of 16 byte values
+            uint32_t *to = rows.data() + wide_row(16u * k, values) * rs;
+            const uint32_t *from = rows.data() + (kBigBlockRow + k) * rs;
+            for (size_t w = 0; w < rs; w++) to[w] |= from[w];
+        }
+    rows.insert(rows.end(), ix.len_rows.begin(), ix.len_rows.end());
     hipError_t e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());
     if (e == hipSuccess) e = upload(&v->d_chunks, ix.chunks.data(), ix.chunks.size());
     if (e == hipSuccess) e = upload(&v->d_rows, rows.data(), rows.size());

@@ -26,7 +26,7 @@ struct DeviceVocab {
     const uint64_t *chunks;      // chunks[k * V + t] = bytes 8k .. 8k+7 of token t, zero padded
     // token rows: row x (0 .. 255) the tokens that contain the byte x, row kBlockRow + k those that
     // contain a byte 4k .. 4k+3, row kBigBlockRow + k a byte 16k .. 16k+15; row kTailRow + x the tokens in
-    // which x occurs once, as the last byte; row kLenRow + r (r = 0 .. lmax+1) those with 1 <= length <= r
+    // which x occurs once, as the last byte; kWideRow: see wide_plan_of; row kLenRow + r (r = 0 .. lmax+1) those with 1 <= length <= r
     const uint32_t *rows;
     const ExitEntry *index;      // the four candidate indexes, entries {tok, off, cls, first, rem}; off + rem is the token's length
     // the entry numbers at which the ranges of the indexes begin, four directories:

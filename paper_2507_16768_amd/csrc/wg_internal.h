@@ -54,13 +54,21 @@ constexpr uint32_t kPartGroup = 2048;
 // | class << 8), ids[n_exits .. n_ids) the token rows that together hold every token with a
 // rejected byte (kBlockRow + k: byte values 4k .. 4k+3, kBigBlockRow + k: 16k .. 16k+15).
 constexpr uint32_t kFewLive = 8;
-constexpr uint32_t kBlockRow = 256, kBigBlockRow = 320, kTailRow = 336, kLenRow = 592;
+constexpr uint32_t kBlockRow = 256, kBigBlockRow = 320, kTailRow = 336, kWideRow = 592, kLenRow = 606;
 struct ClassPlan {
     uint16_t n_exits, n_ids, by_first, pad;
     uint16_t ids[260];
 };
 static_assert(sizeof(ClassPlan) % 16 == 0, "class plan layout");
 ClassPlan class_plan_of(const uint8_t *table);
+// The same for the device, with the rows of 16 byte values put together where 32, 64 or 128 are rejected as a
+// whole: kWideRow + k stands for the k-th of the blocks of 32 (k = 0 .. 7), of 64 (8 .. 11) and of 128 (12, 13).
+// Most tables reject all that is not ASCII: a row for it instead of eight (kWideRows rows of 19 KB for 152k tokens).
+constexpr uint32_t kWideRows = 14;
+ClassPlan wide_plan_of(const uint8_t *table);
+inline uint32_t wide_row(uint32_t first_value, uint32_t values) {
+    return kWideRow + (values == 32 ? 0u : values == 64 ? 8u : 12u) + first_value / values;
+}
 
 // A token that leaves a checkpoint state before its last byte: the part of a mask that
 // depends on what follows the state.  `off` bytes are consumed up to and including the

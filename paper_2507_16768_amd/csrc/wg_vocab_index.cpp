@@ -32,6 +32,27 @@ ClassPlan class_plan_of(const uint8_t *table) {
     return p;
 }
 
+ClassPlan wide_plan_of(const uint8_t *table) {
+    const ClassPlan p = class_plan_of(table);
+    ClassPlan out = p;
+    bool big[16] = {};
+    uint32_t n = p.n_exits;
+    for (uint32_t i = p.n_exits; i < p.n_ids; i++) {
+        if (p.ids[i] >= kBigBlockRow) big[p.ids[i] - kBigBlockRow] = true;
+        else out.ids[n++] = p.ids[i];
+    }
+    for (uint32_t k = 0; k < 16; k++) {
+        uint32_t size = 8;                                 // the largest aligned block of 16-value rows from k on
+        while (size && (!big[k] || k % size || !std::all_of(big + k, big + k + size, [](bool x) { return x; }))) size /= 2;
+        if (!size) continue;
+        out.ids[n++] = (uint16_t)(size == 1 ? kBigBlockRow + k : wide_row(16u * k, 16u * size));
+        k += size - 1;
+    }
+    out.n_ids = (uint16_t)n;
+    for (uint32_t i = n; i < p.n_ids; i++) out.ids[i] = 0;
+    return out;
+}
+
 namespace {
 
 int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, int32_t eos_id,

@@ -30,7 +30,10 @@ def _set(chars):
 # do not, exits that share a block with rejected values, no value that stays, all of them
 _TABLES = [((), b"a"), (b"b", b"a"), (b"bcdefgh", b"a"), (b"bcdefghi", b"a"), (bytes(range(0x60, 0x70)), b"pq"),
            (bytes(range(0x20, 0x30)) + b"abc", b"x/"), ((), bytes(range(0x30, 0x3A))), (bytes(range(256)), b"<"),
-           (bytes(c for c in range(0x20, 0x7F) if c % 3), b"!$'")]
+           (bytes(c for c in range(0x20, 0x7F) if c % 3), b"!$'"),
+           # values rejected in blocks of 128, 64 and 32, at their edges
+           (bytes(range(0x80, 0x100)), b"a"), (bytes(range(0x00, 0x80)), b"z"), (bytes(range(0x40, 0x80)), b" "),
+           (bytes(range(0x20, 0x40)) + bytes(range(0xA0, 0xE0)), b"ab"), (bytes(range(0x00, 0x20)) + bytes([0x3F, 0x40, 0x7F, 0xC0]), b"c")]
 
 
 def _texts():
