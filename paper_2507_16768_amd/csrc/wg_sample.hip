@@ -36,16 +36,6 @@ constexpr uint32_t kSegWords = 8192;                 // mask words staged at a t
 constexpr uint32_t kCand = 1024;                     // candidates ranked in LDS
 constexpr uint32_t kNoPiece = 0xFFFFFFFFu;
 
-// A piece that nobody reads again: not kept in the caches, where it would take the place of what the next fill reads
-// (a step of greedy decoding, V = 151936, B = 256, bf16, logits of four steps in turn: 34.8 -> 33.2 us; the k best look
-// at pieces again: 44.6 -> 45.9).
-typedef uint32_t piece_words __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 load_once(const uint4 *p)
-{
-    const piece_words x = __builtin_nontemporal_load(reinterpret_cast<const piece_words *>(p));
-    return uint4{x.x, x.y, x.z, x.w};
-}
-
 // One row of logits as aligned 16-byte pieces.
 template <typename Elem>
 struct Row {
@@ -66,10 +56,9 @@ struct Row {
     }
     // A piece with allowed tokens m.  An aligned 16-byte block that holds a token of the row lies in
     // the row's own memory page, also where it begins before the row or ends behind it.
-    template <bool kOnce = false>
     __device__ __forceinline__ uint4 load(uint32_t p, uint32_t m) const
     {
-        if (whole) return kOnce ? load_once(blocks + p) : blocks[p];
+        if (whole) return blocks[p];
         union { uint4 v; Elem e[kPer]; } u;
         u.v = uint4{0u, 0u, 0u, 0u};
         for (uint32_t i = 0; i < kPer; i++)
@@ -129,7 +118,7 @@ __device__ __forceinline__ float piece_max(const uint4 &v, uint32_t m, uint32_t)
 // Streams the pieces [lo, hi) of the row, lo a multiple of 32: what(p, piece, allowed tokens) for every
 // piece of the thread that has an allowed token, in ascending order.  `words` is kSegWords words of
 // LDS.  The whole workgroup calls it.
-template <bool kOnce, typename Elem, typename F>
+template <typename Elem, typename F>
 __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t *words,
                                            uint32_t lo, uint32_t hi, F what)
 {
@@ -153,7 +142,7 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
                 const uint32_t q = q0 + j * kThreads, bit = q * kPer;
                 mm[j] = q < n ? (words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : 0u;
                 vv[j] = uint4{0u, 0u, 0u, 0u};
-                if (mm[j]) vv[j] = r.template load<kOnce>(s0 + q, mm[j]);
+                if (mm[j]) vv[j] = r.load(s0 + q, mm[j]);
             }
         };
         auto look = [&](const uint32_t (&mm)[kHalf], const uint4 (&vv)[kHalf], uint32_t q0) {
@@ -206,7 +195,7 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
         const float x = piece_max(v, m, Elem(0));
         if (x > best || (where == kNoPiece && x == x)) { best = x; where = p; held.v = v; held_mask = m; }
     };
-    stream_row<true>(r, mask, W, words, lo, hi, see);
+    stream_row(r, mask, W, words, lo, hi, see);
     float top = best;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) top = __builtin_fmaxf(top, __shfl_xor(top, o));
@@ -284,7 +273,7 @@ argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uin
 #pragma unroll
     for (uint32_t j = 0; j < kChoicePieces; j++) {
         u[j].v = uint4{0u, 0u, 0u, 0u};
-        if (m[j]) u[j].v = load_once(r.blocks + base + j * kChoiceThreads);  // (elements lie at multiples of their size: launch_masked_argmax)
+        if (m[j]) u[j].v = r.blocks[base + j * kChoiceThreads];  // (elements lie at multiples of their size: launch_masked_argmax)
     }
     float best = __builtin_nanf("");
 #pragma unroll
@@ -470,7 +459,7 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
     Elem *value_out = values + (size_t)b * k;
     float best = __builtin_nanf("");
     uint32_t any = 0;                                 // the thread has an allowed token
-    stream_row<false>(r, mask, W, sh.words, 0u, r.pieces, [&](uint32_t, const uint4 &v, uint32_t m) {
+    stream_row(r, mask, W, sh.words, 0u, r.pieces, [&](uint32_t, const uint4 &v, uint32_t m) {
         best = __builtin_fmaxf(best, piece_max(v, m, Elem(0)));
         any = 1u;
     });
