@@ -426,13 +426,15 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 
 // The same by whole lines: every 128-byte line with a disallowed token is read where it has to be and written
 // whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
-// are stored one by one.
-template <typename Elem>
+// are stored one by one.  kBatch: pieces of a thread in flight together.  In the rows' kernel, where few of a unit's
+// workgroups mask at a time, 5 (fp32: 6); by itself 3.  us a cold step, V = 151936, B = 1024, random trees, with 3 / 4 / 5 / 6
+// 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as slow again); fp32, V = 128256, B =
+// 1000 198.4 / 195.6 / 196.5 / 194.1; a cached step through the separate calls 124.8 / 126.3 / 126.4 / 126.5.
+template <typename Elem, uint32_t kBatch>
 __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
     constexpr uint32_t kPer = 16u / sizeof(Elem);                  // tokens of a piece
     constexpr uint32_t kAlign = 128u;
-    constexpr uint32_t kBatch = 4u;                                // pieces of a thread in flight together
     constexpr uint32_t kAll = (1u << kPer) - 1u;
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
     constexpr uint32_t kFill = sizeof(Elem) == 4 ? 0xFF800000u : 0xFF80FF80u;
@@ -964,7 +966,7 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
     if (kMode == 1) mask_span<Elem>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
-    if (kMode == 2) mask_lines<Elem>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
     if (kWhole) {
         if (tid == kRowThreads - 64u && ticket == gridDim.x - 1u) {
             Cc.tickets[b * kTicketStride] = 0u;
@@ -1046,7 +1048,7 @@ apply_lines_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, ui
     const uint32_t w = (lo >> 5) + threadIdx.x;
     row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
     __syncthreads();
-    mask_lines<Elem>(logits + (int64_t)b * row_stride, lo, hi, row);
+    mask_lines<Elem, 3u>(logits + (int64_t)b * row_stride, lo, hi, row);
 }
 
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
