@@ -3,8 +3,8 @@
 //   rows         : the mask row of every request, a workgroup per (request, token range): copied from
 //                  the cache, or made in LDS from the vocabulary's static indexes; to the caller's
 //                  bitmask, to the cache, and (wg_decode_step) as -inf into the logits.  In front of
-//                  it, where the batch is small enough in the same kernel, the state is advanced by the
-//                  sampled token (wg_advance_fill_masks, wg_decode_step) and looked up
+//                  it, in the same kernel up to a request per compute unit (plan_fill), the state is advanced
+//                  by the sampled token (wg_advance_fill_masks, wg_decode_step) and looked up
 //   lookup       : the same by itself: request state -> cache key; claims a missing key and leaves the
 //                  task of making its row
 //   apply        : logits <- -inf where the mask bit is 0
@@ -395,12 +395,17 @@ __device__ __forceinline__ void mask_chunk(Elem *p, uint32_t lo, uint32_t hi, ui
 {
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
     const uint32_t lane = threadIdx.x & 63u;
+    // (all into scalar registers before the first store: one by one between the stores each was waited for; a cached
+    // step, html, V = 151936, B = 256, 16.9 -> 16.6 us)
+    lo = ~lo; hi = ~hi;
+    unsigned long long m[kChunk];
 #pragma unroll
-    for (uint32_t u = 0; u < kChunk; u++) {
-        const unsigned long long m = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(first + u)) << 32 |
-                                     (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(first + u));
-        if (__builtin_amdgcn_inverse_ballot_w64(~m)) p[u * 64u + lane] = kNinf;
-    }
+    for (uint32_t u = 0; u < kChunk; u++)
+        m[u] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(first + u)) << 32 |
+               (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(first + u));
+#pragma unroll
+    for (uint32_t u = 0; u < kChunk; u++)
+        if (__builtin_amdgcn_inverse_ballot_w64(m[u])) p[u * 64u + lane] = kNinf;
 }
 // Word w of the `words` that hold a row's V tokens; what lies behind the last token counts as allowed.
 __device__ __forceinline__ uint32_t word_or_ones(const uint32_t *row, uint32_t w, uint32_t words, uint32_t V)
@@ -419,6 +424,7 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
     for (uint32_t i0 = wave * kChunk; i0 < pairs; i0 += step * (64u / kChunk)) {
         const uint32_t w = 2u * (i0 + lane / kChunk * step + lane % kChunk);      // a lane per pair of words, eight chunks at a time
         const uint32_t a = word_or_ones(row, w, words, V), b = word_or_ones(row, w + 1u, words, V);
+        if (!__ballot((a & b) != 0xFFFFFFFFu)) continue;            // a step in text without an end: 12.4 -> 9.0 us
         for (uint32_t c = 0; c < 64u / kChunk && i0 + c * step < pairs; c++)
             mask_chunk<Elem>(logits + lo + (size_t)(i0 + c * step) * 64u, a, b, c * kChunk);
     }
@@ -428,8 +434,9 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 // whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
 // are stored one by one.  kBatch: pieces of a thread in flight together.  In the rows' kernel, where few of a unit's
 // workgroups mask at a time, 5 (fp32: 6); by itself 3.  us a cold step, V = 151936, B = 1024, random trees, with 3 / 4 / 5 / 6
-// 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as slow again); fp32, V = 128256, B =
-// 1000 198.4 / 195.6 / 196.5 / 194.1; a cached step through the separate calls 124.8 / 126.3 / 126.4 / 126.5.
+// 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as
+// slow again); fp32, V = 128256, B = 1000 198.4 / 195.6 / 196.5 / 194.1; a cached step through the separate calls
+// 124.8 / 126.3 / 126.3 / 126.4.
 template <typename Elem, uint32_t kBatch>
 __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
@@ -503,10 +510,11 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
 // what is left in LDS and decides them 64 at a time, so that the walks run on full wavefronts.
 //
-// What bounds it (V = 151936, B = 256, masks only): copied rows 5.9 us for 10 MB, the launch and two trips to
-// memory one after the other; made rows 17.8 us for 14 MB, the chain task -> plan -> directory -> entries ->
-// chunks -> walk, with 3.8 M instructions of wavefronts (6 us of the chip's vector units) in it.  With B = 1024
-// and 141 class tables a call, made rows are 80 us, half of them vector instructions (25 M).
+// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 9.2 us for 8 MB, the launch and the
+// chain state -> descriptor -> tag -> row of four trips to memory; made rows 17.2 us for 19 MB, the same chain and
+// then plan -> directory -> entries -> chunks -> walk, with 3.5 M instructions of wavefronts (6 us of the chip's
+// vector units) in it.  With a lookup kernel before it these were 7 + 5.9 and 7 + 17.8 us.  B = 1024 and 141 class
+// tables a call, two kernels: made rows 80 -> 64 us, 17 M vector instructions of wavefronts (28 us; were 25 M).
 constexpr uint32_t kRowThreads = 256;
 constexpr uint32_t kRowWaves = kRowThreads / 64u;
 constexpr uint32_t kRowBatch = 4;          // index entries of a lane in flight together
@@ -1032,6 +1040,8 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
         lo = word_or_ones(row, w, W, V);
         hi = word_or_ones(row, w + 1u, W, V);
     }
+    // nothing to do: V = 151936, B = 256 5.7 -> 2.8 us where all is allowed (a test per chunk: 0.1 us more elsewhere)
+    if (!__ballot((lo & hi) != 0xFFFFFFFFu)) return;
 #pragma unroll
     for (uint32_t c = 0; c < kApplyPairs; c += kChunk) mask_chunk<Elem>(logits + (int64_t)b * row_stride + (size_t)(first + c) * 64u, lo, hi, c);
 }

@@ -103,6 +103,40 @@ def test_masking_at_every_alignment(torch_cuda, V, dtype):
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [257, 2049, 16385, 40003, 131073])
+def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
+    """Wavefronts that have nothing to mask beside one that has a single token, at the edges of their shares."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
+    at = [None] + [t for t in (0, 1, 255, 256, 511, 512, 2047, 2048, 16383, 16384, 32768) if t < V] + [V - 1]
+    allowed = torch.ones((len(at), V), dtype=torch.bool, device="cuda")
+    for b, t in enumerate(at):
+        if t is not None:
+            allowed[b, t] = False
+    W = (V + 31) // 32
+    packed = np.packbits(np.pad(allowed.cpu().numpy(), ((0, 0), (0, 32 * W - V))), axis=1, bitorder="little").view(np.int32)
+    x = torch.randn((len(at), V), device="cuda").to(dt)
+    want = x.masked_fill(~allowed, float("-inf"))
+    wg.apply_mask(x, torch.from_numpy(packed.copy()).cuda())
+    assert torch.equal(x.view(bits), want.view(bits))
+    # the same from the rows' kernel: text without an end in which one byte, and so one token, is not allowed
+    vocab = ws.make_vocab(V, ("uniform", 1, 8), seed=V, utf8_tenths=0)
+    h = wg.Handle(["Sequence(Wait(denies={}, wait={<eos>}))", "Sequence(Wait(denies={\\x02}, wait={<eos>}))"], None,
+                  wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART)
+    st = H.dev_states(np.concatenate([h.start_states] * 3).view(np.uint32).reshape(-1, 2))
+    mask = torch.empty((6, h.W), dtype=torch.int32, device="cuda")
+    for cold in (True, False):
+        x = torch.randn((6, V), device="cuda").to(dt)
+        want = x.clone()
+        h.decode_step(st, None, mask, x)
+        ok = _unpack(torch, mask, V)
+        assert (V - ok.sum(1)).tolist() == [0, 1] * 3
+        want.masked_fill_(~ok, float("-inf"))
+        assert torch.equal(x.view(bits), want.view(bits)), cold
+
+
 @pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("bf16", 740, 151936, 0), ("bf16", 741, 151900, 3), ("f32", 400, 128256, 0), ("f32", 700, 128256, 0)])
 def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, pad):
     """Either side of 208 MiB of bf16 and 320 MiB of fp32 logits; above them lines are read where they are
