@@ -32,14 +32,15 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 
 # HBM bytes per launch in workloads 4 and 5, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
 # (profiles/bench_config4_hbm_traffic.txt, profiles/bench_config5_hbm_traffic.txt; fetch scaled x2.000,
-# write x1.000 by the counters of a 512 MiB device copy): the rows as made in a cold step, lookup as the mean
-# over cold and warm steps, with and without the advance.  They describe the kernels whose source hashes to
+# write x1.000 by the counters of a 512 MiB device copy): the rows as made in a cold step (workload 4: in one kernel
+# with the lookup, as the mean with and without the advance), lookup as the mean over cold and warm steps, with and
+# without the advance.  They describe the kernels whose source hashes to
 # TRAFFIC_SOURCE_SHA256; with any other kernel source, or any other workload, the field is reported as null.
 TRAFFIC_BYTES = {
-    4: {"lookup": 0.28e6, "rows": 13.84e6, "apply": 57.08e6, "advance": 0.25e6},
-    5: {"lookup": 0.55e6, "rows": 45.64e6, "apply": 535.02e6, "advance": 0.61e6},
+    4: {"rows": 18.60e6, "apply": 56.56e6, "advance": 0.25e6},
+    5: {"lookup": 0.56e6, "rows": 45.78e6, "apply": 535.02e6, "advance": 0.61e6},
 }
-TRAFFIC_SOURCE_SHA256 = "ae59342048bbe9cef48cb80deea5bcf6751713ec8a718396a3624f6d93df8b38"
+TRAFFIC_SOURCE_SHA256 = "42fbf9813574c9e4ab7ef3f40c02fea476e17f494a11c219d2dc9d68da3f3f17"
 WINDOW_START = 64              # first timed step of the trajectory (the warm-up steps come right before it)
 N_PASSES = 5                   # timed passes per figure; the median is reported
 RAMP_SECONDS = 0.08            # GPU work done before timing, for the clocks to settle
@@ -141,7 +142,7 @@ def apply_patterns(B=256, V=151936, K=200):
     halves = torch.zeros((B, W), dtype=torch.int32, device="cuda")
     halves[:, ::2] = -1
     cases = [("nothing disallowed (mask read only; the loop's launch rate)", words(-1)),
-             ("everything disallowed: 16-byte stores, every block written whole", words(0)),
+             ("everything disallowed: every block written whole", words(0)),
              ("every other row disallowed", rows),
              ("every other 64-byte block disallowed", halves),
              ("every other 16 bytes disallowed", words(0x00FF00FF)),
@@ -357,7 +358,7 @@ def main():
         return passes(lambda: single_rewind(cold), lambda k: single_step(cold, k))
 
     def decode_kernel_times(cold):
-        """Per-kernel durations of wg_decode_step: its first kernel counts as lookup, its second as build."""
+        """Per-kernel durations of wg_decode_step: its lookup kernel, where it has one, and the rows' kernel (build)."""
         ramp(lambda: single_rewind(cold), lambda k: single_step(cold, k))
         single_rewind(cold)
         torch.cuda.synchronize()
@@ -658,7 +659,7 @@ def main():
                  "dense_equivalent_GBs": dense_warm / sec_warm / 1e9,
                  "frac_of_hbm_peak_dense_equivalent": dense_warm / sec_warm / 1e9 / HBM_PEAK_GBS},
         "kernels_us_per_step": {"cold": kt_cold, "warm": kt_warm},
-        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, two launches)",
+        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, one launch up to a request per compute unit, else two)",
                              "cold_ms_per_step": sec_single_cold * 1e3, "warm_ms_per_step": sec_single_warm * 1e3,
                              "cold_request_steps_per_s": B / sec_single_cold,
                              "warm_request_steps_per_s": B / sec_single_warm,

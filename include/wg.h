@@ -211,8 +211,8 @@ uint32_t wg_num_instances(wg_handle_t h);
  * cache_rows), each key has its own.  With more keys than rows -- after wg_add_instances, or on a
  * smaller cache -- rows are handed out in order of first use (rows in use stay where they are); once
  * all are taken, further keys are still served correctly but rebuilt on every call that needs them
- * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  A fill of a small
- * batch is one kernel in the first case and two in the second, 0.4 to 2 us more a step at B <= 32;
+ * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  A fill of at most a
+ * request per compute unit is one kernel in the first case and two in the second, 2 to 4 us more a step;
  * an engine that expects additions keeps the first by making room for their keys here, at set-up.
  * Synchronises the device and clears the cache. */
 int wg_cache_resize(wg_handle_t h, uint32_t rows);
@@ -237,8 +237,8 @@ uint32_t wg_mask_words(wg_handle_t h);      /* W = ceil(V/32) */
  * wg_fill_masks: d_bitmask[b][0..W) <- mask of d_states[b] (mask creation with the global
  * cache of the section "Mask Generation and Global Caching"): cached rows are copied, missing
  * ones are made, and kept once per distinct key.  An ERROR or out-of-range state gets an all-zero
- * row.  One kernel for a small batch (up to a workgroup per compute unit, 8 to 32 of them a row),
- * two for a larger one. */
+ * row.  One kernel for up to a request per compute unit while the cache has a row for every key,
+ * else two (a workgroup for every 1/1 to 1/32 of a row). */
 int wg_fill_masks(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint32_t *d_bitmask,
                   void *stream);
 
@@ -358,8 +358,8 @@ const char *wg_last_error(void);
 typedef struct {
     uint64_t fill_calls, advance_calls;   /* (an advance inside a fill counts as part of the fill) */
     double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations: a fill has a lookup kernel and
-                                                                     one that makes or copies the rows (build_ms); a small
-                                                                     batch has the second alone, which then does the lookups,
+                                                                     one that makes or copies the rows (build_ms); one of up
+                                                                     to a request per compute unit has the second alone, which then does the lookups,
                                                                      and adds nothing to lookup_ms.  scan and gather stay 0 */
     uint64_t apply_calls;
     double apply_ms;

@@ -433,10 +433,10 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 // The same by whole lines: every 128-byte line with a disallowed token is read where it has to be and written
 // whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
 // are stored one by one.  kBatch: pieces of a thread in flight together.  In the rows' kernel, where few of a unit's
-// workgroups mask at a time, 5 (fp32: 6); by itself 3.  us a cold step, V = 151936, B = 1024, random trees, with 3 / 4 / 5 / 6
+// workgroups mask at a time, 5 (fp32: 6); by itself 4, a workgroup's share of bf16.  us a cold step, V = 151936, B = 1024, random trees, with 3 / 4 / 5 / 6
 // 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as
-// slow again); fp32, V = 128256, B = 1000 198.4 / 195.6 / 196.5 / 194.1; a cached step through the separate calls
-// 124.8 / 126.3 / 126.3 / 126.4.
+// slow again); fp32, V = 128256, B = 1000 198.4 / 195.6 / 196.5 / 194.1.  By itself 3 gains 1 %
+// on mixed masks and loses 5 % (bf16, B = 1000, 67.1 -> 70.6; 4 of fp32's 8 likewise) on rows masked nearly as a whole.
 template <typename Elem, uint32_t kBatch>
 __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
@@ -1058,7 +1058,7 @@ apply_lines_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, ui
     const uint32_t w = (lo >> 5) + threadIdx.x;
     row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
     __syncthreads();
-    mask_lines<Elem, 3u>(logits + (int64_t)b * row_stride, lo, hi, row);
+    mask_lines<Elem, 4u>(logits + (int64_t)b * row_stride, lo, hi, row);
 }
 
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that

@@ -10,9 +10,10 @@
 // made from such slices too (argmax_slice_kernel): a row of 600 KB per workgroup left compute units
 // idle whenever the rows did not come out even.
 //
-// Times for V = 151,936, bf16, the greedy choice and k = 50, before -> now (before: a workgroup per slice
-// and a second kernel always): B = 1 12.5 -> 5.9 and 14.6 -> 11.0 us, B = 64 12.2 -> 8.3 and 19.9 -> 18.2,
-// B = 256 19.5 -> 17.1 and 42 -> 28, B = 1,024 56 -> 52 and 117 -> 67.
+// Times for V = 151,936, bf16, every token allowed, the greedy choice and k = 50: B = 1 5.7 and 11.6 us, B = 64 9.1
+// and 18.3, B = 256 18.9 and 26.5, B = 1,024 62.9 (5.0 TB/s, a copy's rate) and 86.3.  Greedy choice with the best
+// piece kept instead of its number 19.7 -> 18.9 (B = 256), the k best by row with keys made from the loaded pieces
+// instead of reloaded ones 96.1 -> 86.3 (B = 1,024).
 //
 // The k best need no sorting of the row: in each of n wavefronts the ceil(k / n)-th largest of the 64
 // thread maxima is found by bisection on ballots, and the least of these is a lower bound for the k-th
