@@ -379,8 +379,8 @@ lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restr
 // and two to four 64-byte requests per 64 tokens, whatever the pattern and wherever the row starts.  With a 16-byte
 // piece to a lane, and a store per disallowed token of a mixed piece, each of the stores was a request for every 64
 // bytes that the wavefront spans.  Before -> now, html outlines / JSON / mixed / random trees, us: wg_apply_mask, bf16,
-// V = 151936, B = 256 11.7 / 12.2 / 14.9 / 21.0 -> 11.4 / 11.3 / 13.4 / 15.7; V = 128256, B = 64 4.6 / 5.6 / 5.9 / 7.9 -> 4.4 / 4.5
-// / 4.8 / 5.1; fp32 6.5 / 7.8 / 7.1 / 9.5 -> 5.0 / 5.2 / 6.0 / 7.0; a cached wg_decode_step, V = 151936, B = 256, mixed 22.9 ->
+// V = 151936, B = 256 11.7 / 11.9 / 14.7 / 20.4 -> 11.2 / 11.2 / 13.4 / 15.6; V = 128256, B = 64 4.5 / 5.5 / 5.8 / 7.8 -> 4.3 / 4.4
+// / 4.6 / 5.0; fp32 6.2 / 6.4 / 7.0 / 9.4 -> 4.7 / 5.2 / 5.9 / 6.9; a cached wg_decode_step, V = 151936, B = 256, mixed 22.9 ->
 // 18.8, V = 128256, B = 64 8.8 / 9.3 / 9.8 / 11.9 -> 8.9 / 8.9 / 9.2 / 9.8.  (Wavefronts that take pieces where these are fewer
 // instructions were 5 to 15 % slower; so were stores without the compiler's branch around them, which skips words that
 // are allowed as a whole.)
@@ -433,8 +433,8 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 // The same by whole lines: every 128-byte line with a disallowed token is read where it has to be and written
 // whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
 // are stored one by one.  kBatch: pieces of a thread in flight together.  In the rows' kernel, where few of a unit's
-// workgroups mask at a time, 5 (fp32: 6); by itself 4, a workgroup's share of bf16.  us a cold step, V = 151936, B = 1024, random trees, with 3 / 4 / 5 / 6
-// 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as
+// workgroups mask at a time, 5 (fp32: 6); by itself 4, a workgroup's share of bf16.  us a cold step, V = 151936,
+// B = 1024, random trees, with 3 / 4 / 5 / 6 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as
 // slow again); fp32, V = 128256, B = 1000 198.4 / 195.6 / 196.5 / 194.1.  By itself 3 gains 1 %
 // on mixed masks and loses 5 % (bf16, B = 1000, 67.1 -> 70.6; 4 of fp32's 8 likewise) on rows masked nearly as a whole.
 template <typename Elem, uint32_t kBatch>
@@ -1025,7 +1025,7 @@ free_rows_kernel(DeviceCache Cc, uint32_t n_keys, uint32_t *__restrict__ free_ro
 }
 
 // apply: a wavefront takes kApplyPairs times 64 tokens of a row, its mask straight from memory (with 8, 16, 32 and
-// 64, V = 151936, B = 256, bf16, mixed 14.5, 13.6, 13.1 and 13.4 us; V = 32000, B = 256 5.0, 4.9, 4.6 and 5.6).
+// 64, V = 151936, B = 256, bf16, mixed 14.8, 13.3, 13.4 and 13.1 us; V = 32000, B = 256 5.1, 4.9, 4.6 and 5.2).
 constexpr uint32_t kApplyPairs = 32;
 template <typename Elem>
 __global__ void __launch_bounds__(256)
@@ -1189,10 +1189,10 @@ FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int
     p.parts = row_parts(Vc.V, B, n_cu);
     // One kernel while its workgroups are resident together: what every workgroup of a row repeats of the lookup
     // is then paid once, and a launch with its lookup is saved.  us a step with two kernels / with one, rows made
-    // and rows copied: V = 151936, mixed, B = 16 16.4 / 12.6 and 10.3 / 7.5, B = 64 21.2 / 17.8 and 14.1 / 11.8, B =
-    // 256 33.8 / 31.6 and 26.0 / 23.0 (random trees 53.0 / 50.8 and 35.7 / 32.7); html, V = 70000, B = 256 21.9 /
-    // 20.3 and 14.3 / 13.4.  Above, workgroups that start late repeat it when the others are done: html, V =
-    // 151936, B = 288 29.5 / 34.7 and 21.2 / 20.4; V = 60000, B = 512 29.3 / 30.5 and 17.7 / 19.8.
+    // and rows copied: V = 151936, mixed, B = 16 14.6 / 11.4 and 10.2 / 7.2, B = 64 19.5 / 16.4 and 12.2 / 9.7, B =
+    // 256 29.8 / 25.6 and 21.8 / 18.6 (random trees 54.9 / 52.9 and 23.4 / 19.8); html, V = 70000, B = 256 21.3 /
+    // 20.5 and 14.1 / 13.1.  Above, workgroups that start late repeat it when the others are done: html, V =
+    // 151936, B = 288 28.2 / 28.9 and 19.5 / 19.0; V = 60000, B = 512 28.3 / 33.0 and 17.2 / 19.5.
     p.one_kernel = Cc.direct && B <= n_cu && !by_lines(dtype, B, Vc.V);
     return p;
 }
