@@ -207,8 +207,11 @@ __device__ __forceinline__ StateDesc descriptor(const DeviceTable &T, uint32_t s
 
 // One thread per request, 4 requests to a wavefront: the paths of the requests of a wavefront are
 // walked one after the other, each step a trip to memory (the lookup with an advance before it, B = 256:
-// 7.5 us with 64, 6.2 with 4; the advance alone 5.2 and 4.8).
-constexpr uint32_t kLookupThreads = 4;
+// 7.5 us with 64, 6.2 with 4).  With one to a wavefront the lookup of a cached step of 300 requests is 0.4 us faster,
+// that of a made one up to 1 us slower: more wavefronts claim on the same tags.  The advance alone claims nothing and
+// takes one as long as that fills no more than two wavefronts a unit: with 4 / with 1, B = 64 4.23 / 3.92 us, 256 4.45 /
+// 4.18, 512 4.26 / 4.16, 1024 4.60 / 4.78, 8192 5.6 / 7.7.
+constexpr uint32_t kLookupThreads = 4, kAdvanceAlone = 512;
 __global__ void __launch_bounds__(64)
 advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
                const int32_t *__restrict__ tokens, uint32_t B)
@@ -1262,7 +1265,8 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
                           wg_state_t *states, const int32_t *tokens, uint32_t B, hipStream_t s,
                           hipEvent_t *ev)
 {
-    return launch(advance_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, ev, T, Vc, Cc, states, tokens, B);
+    const uint32_t threads = B <= kAdvanceAlone ? 1u : kLookupThreads;
+    return launch(advance_kernel, dim3(cdiv(B, threads)), dim3(threads), 0, s, ev, T, Vc, Cc, states, tokens, B);
 }
 
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
