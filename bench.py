@@ -37,10 +37,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # without the advance.  They describe the kernels whose source hashes to
 # TRAFFIC_SOURCE_SHA256; with any other kernel source, or any other workload, the field is reported as null.
 TRAFFIC_BYTES = {
-    4: {"rows": 18.70e6, "apply": 56.56e6, "advance": 0.25e6},
-    5: {"lookup": 0.56e6, "rows": 45.81e6, "apply": 535.02e6, "advance": 0.61e6},
+    4: {"rows": 18.61e6, "apply": 56.56e6, "advance": 0.27e6},
+    5: {"lookup": 0.56e6, "rows": 45.83e6, "apply": 535.02e6, "advance": 0.61e6},
 }
-TRAFFIC_SOURCE_SHA256 = "8bc3d3023b770fa0c83a90ebd0188b4248e1a42d8328b0b79af9654caa3da35d"
+TRAFFIC_SOURCE_SHA256 = "22cf5fad3d1b390831ba280c9dc47facb00bae273755b019b99728c366749831"
 WINDOW_START = 64              # first timed step of the trajectory (the warm-up steps come right before it)
 N_PASSES = 5                   # timed passes per figure; the median is reported
 RAMP_SECONDS = 0.08            # GPU work done before timing, for the clocks to settle
