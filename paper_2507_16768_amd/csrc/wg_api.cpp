@@ -597,7 +597,7 @@ int fill(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t 
     if (B > h->max_batch)
         return fail(WG_ERR_INVALID, std::string(who) + ": B = " + std::to_string(B) + " is above the " +
                                         std::to_string(h->max_batch) + " requests the handle has room for (wg_reserve_batch)");
-    const FillPlan plan = plan_fill(h->vocab->dv, h->dc, B, dtype, h->n_cu);
+    const FillPlan plan = plan_fill(h->vocab->dv, h->dc, B, d_logits != nullptr, dtype, h->n_cu);
     Timing lookup(h, !plan.one_kernel, &h->lookup_events), rows(h, true, &h->rows_events);
     const hipError_t e = launch_fill(plan, h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, d_bitmask, d_logits, dtype, logits_stride,
                                      static_cast<hipStream_t>(stream), lookup.events(), rows.events());

@@ -120,10 +120,11 @@ struct DeviceCache {
     uint32_t epoch;              // cache generation of this call
 };
 
-// How a fill of B requests is launched: workgroups per row, and whether they do the lookups themselves
-// (one kernel) or find them done by a kernel before theirs.
-struct FillPlan { uint32_t parts; bool one_kernel; };
-FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int dtype, uint32_t n_cu);
+// How a fill of B requests is launched: workgroups per row, whether they do the lookups themselves
+// (one kernel) or find them done by a kernel before theirs, and whether they mask logits by whole lines.
+struct FillPlan { uint32_t parts; bool one_kernel, lines; };
+// dtype: of the logits, where the fill masks any.
+FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, bool masks_logits, int dtype, uint32_t n_cu);
 // lookup_ev, rows_ev: a begin / end pair of events for each kernel that the plan has, or null.
 // With tokens != nullptr the states are first advanced by them (in place, with the lookup); with
 // logits != nullptr the mask is also applied to them (in the rows kernel).

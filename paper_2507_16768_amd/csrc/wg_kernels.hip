@@ -1186,17 +1186,31 @@ static uint32_t rows_lds(const DeviceVocab &Vc, uint32_t parts)
 // (the most for any batch: a row in fewer parts than kLeastParts is short)
 uint32_t rows_lds_bytes(const DeviceVocab &Vc) { return rows_lds(Vc, row_parts(Vc.V, kMaxBatch, 1u)); }
 
-FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, int dtype, uint32_t n_cu)
+// Workgroups of the rows kernel that a unit holds: 8 by their registers, as many by its 160 KB of LDS.
+static uint32_t resident_rows(const DeviceVocab &Vc, uint32_t parts)
+{
+    const uint32_t fit = 160u * 1024u / (rows_lds(Vc, parts) + (uint32_t)sizeof(RowShared));
+    return fit < 8u ? fit : 8u;
+}
+
+FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, bool masks_logits, int dtype, uint32_t n_cu)
 {
     FillPlan p;
+    p.lines = masks_logits && by_lines(dtype, B, Vc.V);
     p.parts = row_parts(Vc.V, B, n_cu);
     // One kernel while its workgroups are resident together: what every workgroup of a row repeats of the lookup
     // is then paid once, and a launch with its lookup is saved.  us a step with two kernels / with one, rows made
     // and rows copied: V = 151936, mixed, B = 16 14.6 / 11.4 and 10.2 / 7.2, B = 64 19.5 / 16.4 and 12.2 / 9.7, B =
     // 256 29.8 / 25.6 and 21.8 / 18.6 (random trees 54.9 / 52.9 and 23.4 / 19.8); html, V = 70000, B = 256 21.3 /
     // 20.5 and 14.1 / 13.1.  Above, workgroups that start late repeat it when the others are done: html, V =
-    // 151936, B = 288 28.2 / 28.9 and 19.5 / 19.0; V = 60000, B = 512 28.3 / 33.0 and 17.2 / 19.5.
-    p.one_kernel = Cc.direct && B <= n_cu && !by_lines(dtype, B, Vc.V);
+    // 151936, B = 288 28.2 / 28.9 and 19.5 / 19.0; V = 60000, B = 512 28.3 / 33.0 and 17.2 / 19.5.  So it is with
+    // fewer rows whose shares take so much LDS that fewer workgroups are resident, from V = 350,000 on (masks only, html /
+    // mixed / random trees, one over two kernels, made and copied: V = 340001, B = 256, 8 to a unit, 1.12 0.92 0.98 and 1.06
+    // 1.04 0.92; 350000, B = 256, 7 to a unit, 1.20 1.07 0.96 and 1.13 1.14 1.02; 500000, B = 224, 6 to a unit, 1.08 1.02 0.99
+    // and 1.12 1.09 1.03, B = 192 0.92 0.94 1.01 and 0.97 1.00 0.85).  With logits to mask behind them the workgroups
+    // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.94 0.96
+    // 1.00 and 0.95 0.95 0.96); whole lines are masked behind a lookup of its own.
+    p.one_kernel = Cc.direct && B <= n_cu && (masks_logits ? !p.lines : B * p.parts <= resident_rows(Vc, p.parts) * n_cu);
     return p;
 }
 
@@ -1214,7 +1228,7 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
     }
     auto rows = [&](auto kernel, auto *x) { return launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
     if (!logits) return whole ? rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr) : rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);
-    const bool lines = by_lines(dtype, B, Vc.V);
+    const bool lines = plan.lines;
     if (dtype == WG_F32) {
         uint32_t *x = static_cast<uint32_t *>(logits);
         return whole ? rows(rows_kernel<uint32_t, 1, true>, x) : lines ? rows(rows_kernel<uint32_t, 2, false>, x) : rows(rows_kernel<uint32_t, 1, false>, x);

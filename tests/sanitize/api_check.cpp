@@ -85,7 +85,7 @@ static void look_at(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCac
     if (sum == 1u) std::printf(" ");                 // (the reads are not to be left out)
 }
 
-FillPlan plan_fill(const DeviceVocab &, const DeviceCache &, uint32_t, int, uint32_t) { return FillPlan{8u, false}; }
+FillPlan plan_fill(const DeviceVocab &, const DeviceCache &, uint32_t, bool, int, uint32_t) { return FillPlan{8u, false, false}; }
 hipError_t launch_fill(const FillPlan &, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, wg_state_t *, const int32_t *, uint32_t,
                        uint32_t *, void *, int, int64_t, hipStream_t, hipEvent_t *, hipEvent_t *) {
     look_at(T, Vc, Cc);

@@ -54,6 +54,33 @@ def test_kernel_timing_of_batches_of_one_and_of_two_kernels(torch_cuda, call):
     assert h.profile_read()["fill_calls"] == 0
 
 
+@pytest.mark.parametrize("V,one", [(340001, True), (350000, False)])
+def test_a_fill_without_logits_goes_by_its_own_workgroups(torch_cuda, V, one):
+    """Logits that are masked by whole lines (above 208 MiB of bf16, 320 MiB of fp32) are masked behind a lookup of
+    its own; a fill that masks no logits is one kernel while its workgroups are resident together."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    B = 256
+    rng = np.random.default_rng(1)
+    offsets = np.concatenate([[0], np.arange(257), 256 + np.cumsum(rng.integers(1, 5, V - 257))]).astype(np.uint64)
+    data = np.concatenate([np.arange(256, dtype=np.uint8), rng.integers(0x20, 0x7F, int(offsets[-1]) - 256, dtype=np.uint8)])
+    h = wg.Handle(['Sequence(Write("ab"), Wait(denies={}, wait={<}, max=256), Write("c"))'], None, wg.Vocab(data, offsets, 0), flags=wg.EOS_RESTART)
+    st = H.dev_states(np.stack([1 + np.arange(B, dtype=np.uint32) % (h.num_states - 1), np.zeros(B, dtype=np.uint32)], 1))
+    mask, want = (torch.empty((B, h.W), dtype=torch.int32, device="cuda") for _ in range(2))
+    tok = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    h.profile_enable()
+    for dt, kernels in ((torch.float32, 2), (torch.bfloat16, 1)):
+        h.cache_clear()
+        h.decode_step(st, None, want, torch.zeros((B, V), dtype=dt, device="cuda"))
+        assert (h.profile_read()["lookup_ms"] > 0.0) == (kernels == 2), dt
+        h.cache_clear()
+        h.fill_masks(st, mask)
+        assert torch.equal(mask, want)
+        h.advance_fill_masks(st.clone(), tok, mask)
+        p = h.profile_read()
+        assert p["fill_calls"] == 2 and (p["lookup_ms"] == 0.0) == one, p
+
+
 def test_errors_of_other_calls_are_not_reported_as_these(torch_cuda):
     """A call whose kernels were launched returns WG_OK, also when an earlier HIP call of the thread, made
     by somebody else, has failed: a caller who takes the step for failed would advance its states twice."""
