@@ -137,6 +137,34 @@ def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
         assert torch.equal(x.view(bits), want.view(bits)), cold
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [2048, 8191, 8193, 20001])
+def test_masking_of_few_scattered_tokens(torch_cuda, V, dtype):
+    """Either side of 64 disallowed tokens in a wavefront's 2,048, which it then lists and stores at once: at random
+    places, side by side, at the ends of the share; rows at any address, nothing outside them touched."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
+    rng = np.random.default_rng(V)
+    rows = []
+    for n in (1, 2, 63, 64, 65, 66, 200):
+        for places in (lambda m: rng.permutation(m)[:n], lambda m: np.arange(min(n, m)), lambda m: np.arange(max(0, m - n), m)):
+            ok = np.ones(V, dtype=bool)
+            for lo in range(0, V, 2048):
+                ok[lo + places(min(2048, V - lo))] = False
+            rows.append(ok)
+    allowed, W = np.stack(rows), (V + 31) // 32
+    packed = np.packbits(np.pad(allowed, ((0, 0), (0, 32 * W - V))), axis=1, bitorder="little").view(np.int32)
+    mask, B = torch.from_numpy(packed.copy()).cuda(), len(rows)
+    for off, pad in ((0, 0), (1, 3), (5, 64)):
+        buf = torch.randn(B * (V + pad) + 24, device="cuda").to(dt)
+        x = buf[off:off + B * (V + pad)].view(B, V + pad)[:, :V]
+        want = buf.clone()
+        want[off:off + B * (V + pad)].view(B, V + pad)[:, :V].masked_fill_(~torch.from_numpy(allowed).cuda(), float("-inf"))
+        wg.apply_mask(x, mask)
+        assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)
+
+
 @pytest.mark.parametrize("dtype,B,V,pad", [("bf16", 700, 151936, 0), ("bf16", 701, 151900, 3), ("bf16", 740, 151936, 0), ("bf16", 741, 151900, 3), ("f32", 400, 128256, 0), ("f32", 700, 128256, 0)])
 def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, pad):
     """Either side of 208 MiB of bf16 and 320 MiB of fp32 logits; above them lines are read where they are
