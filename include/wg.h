@@ -346,6 +346,8 @@ int wg_decode_step(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens,
 int wg_cache_clear(wg_handle_t h, void *stream);
 
 /* ---- introspection (these synchronise the device) ---------------------------------------- */
+/* (Counters are read in two small copies, whatever the number of keys; rows_in_use is counted by a launch while
+ * the cache has a row for every key.) */
 int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out);
 int wg_error_count(wg_handle_t h, uint64_t *host_out);
 const char *wg_last_error(void);

@@ -747,6 +747,10 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     if (!h || !host_out) return fail(WG_ERR_INVALID, "wg_cache_stats: null argument");
     Counters c;
     WG_HIP(hipDeviceSynchronize());
+    if (h->dc.direct) {                                // nothing counts the rows there: a key of this generation holds its own
+        WG_HIP(hipMemsetAsync(&h->dc.ctr->held, 0, sizeof c.held, nullptr));
+        WG_HIP(launch_count_rows(h->dc, nullptr));
+    }
     WG_HIP(hipMemcpy(&c, h->dc.ctr, sizeof c, hipMemcpyDeviceToHost));
     host_out->lookups = c.lookups; host_out->builds = c.builds;
     host_out->uncached_builds = c.uncached_builds;
@@ -762,16 +766,7 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     }
     host_out->keys = h->dc.n_keys;
     host_out->cache_rows = h->dc.cap_rows;
-    uint64_t taken = (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;
-    if (h->dc.direct) {                                // nothing counts the rows there: a key of this generation holds its own
-        unsigned long long tags[2048];
-        taken = 0;
-        for (size_t i = 0; i < h->dc.n_keys; i += 2048) {
-            const size_t n = h->dc.n_keys - i < 2048 ? h->dc.n_keys - i : 2048;
-            WG_HIP(hipMemcpy(tags, h->dc.tags + i, n * sizeof(unsigned long long), hipMemcpyDeviceToHost));
-            for (size_t k = 0; k < n; k++) taken += (uint32_t)(tags[k] >> kTagEpochShift) == h->dc.epoch;
-        }
-    }
+    const uint64_t taken = h->dc.direct ? c.held : (uint32_t)(c.slot_ctr >> 32) == h->dc.epoch ? (uint32_t)c.slot_ctr : 0u;
     host_out->rows_in_use = taken < h->dc.cap_rows ? taken : h->dc.cap_rows;
     const uint64_t row_bytes = (uint64_t)h->dc.row_stride * 4ull;
     host_out->arena_bytes = ((uint64_t)h->dc.cap_rows + h->cap_classes * 2ull) * row_bytes;

@@ -74,6 +74,7 @@ struct Counters {
                                  // the arena is addressed by key
     unsigned long long launch;   // number of the fill call in flight (its last kernel counts it up)
     unsigned long long lookups, builds, uncached_builds, class_scans, errors;
+    unsigned long long held;     // keys that hold a row, when last counted (launch_count_rows)
 };
 
 // The tag of a key or of a class table: the cache generation (30 bits) in which, the fill call (its
@@ -135,6 +136,8 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
 struct AppendSlice { uint8_t *dst; const uint8_t *src; uint32_t bytes; };
 struct AppendSlices { AppendSlice slice[4]; };
 hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s);
+// While the arena is addressed by key: adds the keys that hold a row in this generation to Cc.ctr->held.
+hipError_t launch_count_rows(const DeviceCache &Cc, hipStream_t s);
 hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t s);
 // Dynamic LDS of the rows kernel for this vocabulary; with its static part it stays within the 64 KB
 // a kernel gets without asking.

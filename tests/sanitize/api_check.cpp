@@ -17,6 +17,8 @@ static int failures = 0;
 
 #define EXPECT(cond, ...) do { if (!(cond)) { std::printf("FAILED "); std::printf(__VA_ARGS__); std::printf("\n"); failures++; } } while (0)
 
+static long copies = 0;                  // copies between host and device so far
+
 static bool fails() { return until_failure >= 0 && until_failure-- == 0; }
 
 static long until_bad_alloc = -1;        // the same for the host's own allocations
@@ -40,7 +42,7 @@ hipError_t hipMalloc(void **p, size_t n) {
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
 hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (fails()) return hipErrorUnknown; std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { copies++; if (fails()) return hipErrorUnknown; std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
 hipError_t hipMemset(void *d, int v, size_t n) { if (fails()) return hipErrorUnknown; std::memset(d, v, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
@@ -89,11 +91,17 @@ FillPlan plan_fill(const DeviceVocab &, const DeviceCache &, uint32_t, bool, int
 hipError_t launch_fill(const FillPlan &, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, wg_state_t *, const int32_t *, uint32_t,
                        uint32_t *, void *, int, int64_t, hipStream_t, hipEvent_t *, hipEvent_t *) {
     look_at(T, Vc, Cc);
+    for (uint32_t k = 0; k < 3u; k++) Cc.tags[k] = (unsigned long long)Cc.epoch << kTagEpochShift | 1ull;      // three keys have their rows
     return hipSuccess;
 }
 hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t) {
     if (fails()) return hipErrorUnknown;
     for (uint32_t i = 0; i < n; i++) std::memcpy(a.slice[i].dst, a.slice[i].src, a.slice[i].bytes);
+    return hipSuccess;
+}
+hipError_t launch_count_rows(const DeviceCache &Cc, hipStream_t) {
+    if (fails()) return hipErrorUnknown;
+    for (uint32_t k = 0; k < Cc.n_keys; k++) Cc.ctr->held += (uint32_t)(Cc.tags[k] >> kTagEpochShift) == Cc.epoch;
     return hipSuccess;
 }
 hipError_t launch_free_rows(const DeviceCache &Cc, uint32_t n_keys, uint32_t *free_rows, hipStream_t) {
@@ -174,6 +182,25 @@ int main() {
             calls++;
             if (!one(vocab, k, true, 0, a, false)) break;
         }
+    // what the statistics cost does not grow with the keys
+    for (const auto &text : {additions[0][0], many}) {
+        wg_handle_t h = nullptr;
+        const char *t = text.c_str();
+        std::vector<wg_state_t> start(1);
+        wg_state_t state{};
+        uint32_t mask[1];
+        wg_cache_stats_t s{};
+        EXPECT(wg_compile(&t, nullptr, 1, vocab, WG_EOS_RESTART, &h, start.data()) == WG_OK, "compile: %s", wg_last_error());
+        EXPECT(wg_cache_stats(h, &s) == WG_OK && s.rows_in_use == 0, "rows of a new handle: %llu", (unsigned long long)s.rows_in_use);
+        EXPECT(wg_fill_masks(h, &state, 1, mask, nullptr) == WG_OK, "fill: %s", wg_last_error());
+        for (int i = 0; i < 2; i++) {
+            const long before = copies;
+            EXPECT(wg_cache_stats(h, &s) == WG_OK && s.rows_in_use == 3, "rows in use: %llu", (unsigned long long)s.rows_in_use);
+            EXPECT(copies - before <= 2, "%ld copies for %llu keys", copies - before, (unsigned long long)s.keys);
+        }
+        EXPECT(wg_cache_clear(h, nullptr) == WG_OK && wg_cache_stats(h, &s) == WG_OK && s.rows_in_use == 0, "rows after a clear: %llu", (unsigned long long)s.rows_in_use);
+        wg_destroy(h);
+    }
     wg_vocab_destroy(vocab);
     for (int what = 0; what < 2; what++)
         for (long k = 0;; k++) {
