@@ -308,36 +308,10 @@ static int create_vocab(const uint8_t *host_bytes, const uint64_t *host_offsets,
         unsigned long long *unused = nullptr;
         (void)static_topk_scratch(&unused);
     }
-    // the candidate indexes, one behind the other, and their directories
     std::vector<ExitEntry> index;
     std::vector<uint32_t> dirs;
-    {
-        const std::vector<ExitEntry> *parts[4] = {&ix.sorted, &ix.lit_entries, &ix.bigram, &ix.places};
-        const std::vector<uint32_t> *dir[4] = {&ix.dir0, &ix.lit_start, &ix.dirN, &ix.place_start};
-        uint64_t n = 0;
-        for (const auto *p : parts) n += p->size();
-        if (n > 0xFFFFFFFFull) return fail(WG_ERR_INVALID, "wg_vocab_create: the candidate indexes have more than 2^32 entries");
-        index.reserve(n);
-        dirs.reserve(kDirWords);
-        for (int i = 0; i < 4; i++) {
-            const uint32_t at = (uint32_t)index.size();
-            for (uint32_t x : *dir[i]) dirs.push_back(at + x);
-            index.insert(index.end(), parts[i]->begin(), parts[i]->end());
-        }
-    }
-    // the token rows, likewise
-    std::vector<uint32_t> rows;
-    rows.reserve(ix.byte_rows.size() + ix.block_rows.size() + ix.tail_rows.size() + ix.len_rows.size() + (size_t)kWideRows * ix.row_stride);
-    for (const auto *r : {&ix.byte_rows, &ix.block_rows, &ix.tail_rows}) rows.insert(rows.end(), r->begin(), r->end());
-    const size_t rs = ix.row_stride;
-    rows.resize((size_t)(kWideRow + kWideRows) * rs, 0u);
-    for (uint32_t values = 32; values <= 128; values *= 2)
-        for (uint32_t k = 0; k < 16; k++) {                // from the rows of 16 byte values
-            uint32_t *to = rows.data() + wide_row(16u * k, values) * rs;
-            const uint32_t *from = rows.data() + (kBigBlockRow + k) * rs;
-            for (size_t w = 0; w < rs; w++) to[w] |= from[w];
-        }
-    rows.insert(rows.end(), ix.len_rows.begin(), ix.len_rows.end());
+    if (!candidates(ix, &index, &dirs)) return fail(WG_ERR_INVALID, "wg_vocab_create: the candidate indexes have more than 2^32 entries");
+    const std::vector<uint32_t> rows = token_rows(ix);
     hipError_t e = upload(&v->d_len8, ix.len8.data(), ix.len8.size());
     if (e == hipSuccess) e = upload(&v->d_chunks, ix.chunks.data(), ix.chunks.size());
     if (e == hipSuccess) e = upload(&v->d_rows, rows.data(), rows.size());

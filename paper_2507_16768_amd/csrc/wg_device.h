@@ -7,8 +7,6 @@
 namespace wg {
 
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
-constexpr uint32_t kDirSorted = 0, kDirFirst = kDirSorted + 256 * 257 + 1, kDirPairs = kDirFirst + 256 * kParts + 1,
-                   kDirPlaces = kDirPairs + 65536 + 1, kDirWords = kDirPlaces + 256 * kParts + 1;
 
 struct DeviceTable {
     const StateDesc *states;

@@ -101,6 +101,15 @@ struct VocabIndex {
     std::vector<uint32_t> place_start;     // 256 * kParts + 1
 };
 
+// What the device is given of an index.  token_rows: all rows one behind the other, in the order of their numbers (byte
+// values, blocks of 4 and 16, tails, wide blocks, lengths).  candidates: the four lists of entries one behind the other,
+// and their directories with the places among all of them, at kDirSorted (dir0), kDirFirst (lit_start), kDirPairs (dirN) and
+// kDirPlaces (place_start); false: more than 2^32 entries.
+constexpr uint32_t kDirSorted = 0, kDirFirst = kDirSorted + 256 * 257 + 1, kDirPairs = kDirFirst + 256 * kParts + 1,
+                   kDirPlaces = kDirPairs + 65536 + 1, kDirWords = kDirPlaces + 256 * kParts + 1;
+std::vector<uint32_t> token_rows(const VocabIndex &ix);
+bool candidates(const VocabIndex &ix, std::vector<ExitEntry> *index, std::vector<uint32_t> *dirs);
+
 // Checks the vocabulary arguments of wg_vocab_create and builds the indexes.  Returns WG_OK, or
 // an error code with the message in *err; `out` is then unspecified.
 int build_vocab_index(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, int32_t eos_id,

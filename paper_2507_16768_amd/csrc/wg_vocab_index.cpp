@@ -216,6 +216,38 @@ int build(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, i
 
 }  // namespace
 
+std::vector<uint32_t> token_rows(const VocabIndex &ix) {
+    const size_t rs = ix.row_stride;
+    std::vector<uint32_t> rows;
+    rows.reserve(kLenRow * rs + ix.len_rows.size());
+    for (const auto *r : {&ix.byte_rows, &ix.block_rows, &ix.tail_rows}) rows.insert(rows.end(), r->begin(), r->end());
+    rows.resize((size_t)(kWideRow + kWideRows) * rs, 0u);
+    for (uint32_t values = 32; values <= 128; values *= 2)
+        for (uint32_t k = 0; k < 16; k++) {                // from the rows of 16 byte values
+            uint32_t *to = rows.data() + wide_row(16u * k, values) * rs;
+            const uint32_t *from = rows.data() + (kBigBlockRow + k) * rs;
+            for (size_t w = 0; w < rs; w++) to[w] |= from[w];
+        }
+    rows.insert(rows.end(), ix.len_rows.begin(), ix.len_rows.end());
+    return rows;
+}
+
+bool candidates(const VocabIndex &ix, std::vector<ExitEntry> *index, std::vector<uint32_t> *dirs) {
+    const std::vector<ExitEntry> *parts[4] = {&ix.sorted, &ix.lit_entries, &ix.bigram, &ix.places};
+    const std::vector<uint32_t> *dir[4] = {&ix.dir0, &ix.lit_start, &ix.dirN, &ix.place_start};
+    uint64_t n = 0;
+    for (const auto *p : parts) n += p->size();
+    if (n > 0xFFFFFFFFull) return false;
+    index->reserve(n);
+    dirs->reserve(kDirWords);
+    for (int i = 0; i < 4; i++) {
+        const uint32_t at = (uint32_t)index->size();
+        for (uint32_t x : *dir[i]) dirs->push_back(at + x);
+        index->insert(index->end(), parts[i]->begin(), parts[i]->end());
+    }
+    return true;
+}
+
 int build_vocab_index(const uint8_t *host_bytes, const uint64_t *host_offsets, uint32_t V, int32_t eos_id,
                       VocabIndex *out, std::string *err) {
     try {

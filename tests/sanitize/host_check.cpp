@@ -188,43 +188,102 @@ static void check_index(const uint8_t *vb, const uint64_t *off, uint32_t V, int3
                     for (uint32_t row : {x, 256 + x / 4, 320 + x / 16, count[x] == 1 && byte_at(t, len(t) - 1) == x ? 336 + x : x})
                         want[row * rs + t / 32] |= 1u << (t % 32);
         }
-        static_assert(kBlockRow == 256 && kBigBlockRow == 320 && kTailRow == 336, "rows in the order they lie in on the device");
+        static_assert(kBlockRow == 256 && kBigBlockRow == 320 && kTailRow == 336 && kWideRow == 592 && kLenRow == 606, "rows in the order they lie in on the device");
         for (size_t i = 0; i < want.size(); i++) {
             const size_t r = i / rs;
             const uint32_t is = r < 256 ? ix.byte_rows[i] : r < 336 ? ix.block_rows[i - 256 * rs] : ix.tail_rows[i - 336 * rs];
             EXPECT(is == want[i], "token row %zu word %zu", r, i % rs);
         }
+        // all rows as the device is given them: the same, tokens that contain a byte of a block of 32, 64 or 128, and lengths
+        want.resize((kLenRow + lmax + 2) * rs, 0);
+        for (uint32_t t = 0; t < V; t++) {
+            for (uint32_t i = 0; i < len(t); i++) {
+                const uint32_t x = byte_at(t, i);
+                for (uint32_t row : {592 + x / 32, 600 + x / 64, 604 + x / 128}) want[row * rs + t / 32] |= 1u << (t % 32);
+            }
+            for (uint32_t r = std::max(1u, len(t)); r <= lmax + 1 && len(t); r++) want[(606 + r) * rs + t / 32] |= 1u << (t % 32);
+        }
+        const std::vector<uint32_t> rows = token_rows(ix);
+        EXPECT(rows.size() == want.size(), "device rows: %zu words for %zu", rows.size(), want.size());
+        for (size_t i = 0; i < want.size(); i++) EXPECT(rows[i] == want[i], "device row %zu word %zu", i / rs, i % rs);
+        for (uint32_t v = 32; v <= 128; v *= 2)
+            for (uint32_t x = 0; x < 256; x += v) EXPECT(wide_row(x, v) == (v == 32 ? 592 : v == 64 ? 600 : 604) + x / v, "number of the row of %u from %u", v, x);
+    }
+    // the candidate lists as the device is given them: each range of a directory holds its list's entries
+    {
+        std::vector<ExitEntry> index;
+        std::vector<uint32_t> dirs;
+        EXPECT(candidates(ix, &index, &dirs) && dirs.size() == kDirWords, "directories");
+        EXPECT(index.size() == ix.sorted.size() + ix.lit_entries.size() + ix.bigram.size() + ix.places.size(), "candidates");
+        const struct { uint32_t at; const std::vector<uint32_t> &dir; const std::vector<ExitEntry> &list; } part[4] = {
+            {kDirSorted, ix.dir0, ix.sorted}, {kDirFirst, ix.lit_start, ix.lit_entries}, {kDirPairs, ix.dirN, ix.bigram}, {kDirPlaces, ix.place_start, ix.places}};
+        for (const auto &p : part)
+            for (size_t y = 0; y + 1 < p.dir.size(); y++) {
+                EXPECT(dirs[p.at + y + 1] - dirs[p.at + y] == p.dir[y + 1] - p.dir[y] && dirs[p.at + y + 1] <= index.size(), "directory at %u, range %zu", p.at, y);
+                for (uint32_t i = 0; i < p.dir[y + 1] - p.dir[y]; i++)
+                    EXPECT(std::memcmp(&index[dirs[p.at + y] + i], &p.list[p.dir[y] + i], sizeof(ExitEntry)) == 0, "directory at %u, range %zu, entry %u", p.at, y, i);
+            }
     }
     std::printf("index ok %u %u %llu\n", V, with_bytes, (unsigned long long)pairs);
 }
 
-// The plans of the class tables from `first` on, each against its 256 bytes: which byte values it names, and
-// that the rows behind the exits stand for the rejected values, each once, and no others.
-static void check_class_plans(const wg::Table &t, size_t first) {
+// The byte values that a token row of a plan stands for, or none: no such row.
+static uint32_t row_values(uint32_t id, uint32_t *lo) {
     using namespace wg;
-    for (size_t c = first; c < t.classes.size() / 256; c++) {
-        const uint8_t *tab = t.classes.data() + c * 256;
-        const ClassPlan p = class_plan_of(tab);
-        uint32_t live = 0, named[256] = {};
-        for (uint32_t x = 0; x < 256; x++) { EXPECT(tab[x] < 4, "class byte"); live += tab[x] != CLS_REJECT; }
-        EXPECT(p.by_first == (live <= kFewLive) && p.n_exits <= p.n_ids && p.n_ids <= 256, "plan of %zu", c);
-        EXPECT(!p.by_first || p.n_ids == p.n_exits, "rows of %zu", c);
-        for (uint32_t i = 0; i < p.n_exits; i++) {
-            const uint32_t x = p.ids[i] & 0xFFu;
-            EXPECT(p.ids[i] >> 8 == tab[x] && tab[x] >= (p.by_first ? CLS_STAY : CLS_EXIT_A), "exit %u of %zu", i, c);
-            named[x]++;
-        }
-        for (uint32_t i = p.n_exits; i < p.n_ids; i++) {
-            const uint32_t id = p.ids[i], lo = id < kBlockRow ? id : id < kBigBlockRow ? 4 * (id - kBlockRow) : 16 * (id - kBigBlockRow);
-            const uint32_t n = id < kBlockRow ? 1 : id < kBigBlockRow ? 4 : 16;
-            EXPECT(id < kTailRow, "row id of %zu", c);
-            for (uint32_t x = lo; x < lo + n; x++) { EXPECT(tab[x] == CLS_REJECT, "row %u of %zu", id, c); named[x]++; }
-        }
-        for (uint32_t x = 0; x < 256; x++) {
-            const uint32_t want = p.by_first ? tab[x] != CLS_REJECT : tab[x] != CLS_STAY;
-            EXPECT(named[x] == want, "byte %u of %zu", x, c);
-        }
+    const struct { uint32_t from, rows, values; } kinds[] = {{0, 256, 1}, {kBlockRow, 64, 4}, {kBigBlockRow, 16, 16}, {kWideRow, 8, 32}, {kWideRow + 8, 4, 64}, {kWideRow + 12, 2, 128}};
+    for (const auto &k : kinds)
+        if (id >= k.from && id < k.from + k.rows) { *lo = (id - k.from) * k.values; return k.values; }
+    return 0;
+}
+
+// A plan against the 256 bytes of its class table: which byte values it names, and that the rows behind the exits stand
+// for the rejected values, each once, and no others.  wide: with blocks of more than 16.
+static void check_plan(const uint8_t *tab, size_t c, bool wide) {
+    using namespace wg;
+    const ClassPlan p = wide ? wide_plan_of(tab) : class_plan_of(tab);
+    uint32_t live = 0, named[256] = {};
+    for (uint32_t x = 0; x < 256; x++) { EXPECT(tab[x] < 4, "class byte"); live += tab[x] != CLS_REJECT; }
+    EXPECT(p.by_first == (live <= kFewLive) && p.n_exits <= p.n_ids && p.n_ids <= 256, "plan of %zu", c);
+    EXPECT(!p.by_first || p.n_ids == p.n_exits, "rows of %zu", c);
+    for (uint32_t i = 0; i < p.n_exits; i++) {
+        const uint32_t x = p.ids[i] & 0xFFu;
+        EXPECT(p.ids[i] >> 8 == tab[x] && tab[x] >= (p.by_first ? CLS_STAY : CLS_EXIT_A), "exit %u of %zu", i, c);
+        named[x]++;
     }
+    for (uint32_t i = p.n_exits; i < p.n_ids; i++) {
+        uint32_t lo = 0;
+        const uint32_t n = row_values(p.ids[i], &lo);
+        EXPECT(n && (wide || n <= 16), "row id of %zu", c);
+        for (uint32_t x = lo; x < lo + n; x++) { EXPECT(tab[x] == CLS_REJECT, "row %u of %zu", p.ids[i], c); named[x]++; }
+        // (the largest block that is rejected as a whole: 1, 4, 16, then 32, 64, 128)
+        const uint32_t up = n == 1 ? 4 : n == 4 ? 16 : 2 * n, at = lo / up * up;
+        bool whole = up <= (wide ? 128u : 16u);
+        for (uint32_t x = at; whole && x < at + up; x++) whole = tab[x] == CLS_REJECT;
+        EXPECT(!whole, "row %u of %zu lies in a larger one", p.ids[i], c);
+    }
+    for (uint32_t x = 0; x < 256; x++) {
+        const uint32_t want = p.by_first ? tab[x] != CLS_REJECT : tab[x] != CLS_STAY;
+        EXPECT(named[x] == want, "byte %u of %zu", x, c);
+    }
+}
+
+// The plans of the class tables from `first` on, as made and as the device is given them.
+static void check_class_plans(const wg::Table &t, size_t first) {
+    for (size_t c = first; c < t.classes.size() / 256; c++)
+        for (bool wide : {false, true}) check_plan(t.classes.data() + c * 256, c, wide);
+}
+
+// Tables that reject blocks of every size at every place, whole and with a hole in them.
+static void check_blocks() {
+    for (uint32_t size = 1; size <= 256; size *= 2)
+        for (uint32_t at = 0; at < 256; at += size)
+            for (uint32_t hole = 0; hole < 4; hole++) {
+                std::vector<uint8_t> tab(256, wg::CLS_STAY);
+                for (uint32_t x = at; x < at + size; x++) tab[x] = wg::CLS_REJECT;
+                if (hole) tab[hole == 1 ? at : hole == 2 ? at + size / 2 : at + size - 1] = hole == 3 ? wg::CLS_EXIT_B : wg::CLS_EXIT_A;
+                if (hole > 1) tab[255 - at] = wg::CLS_EXIT_A;
+                for (bool wide : {false, true}) check_plan(tab.data(), size << 16 | at << 8 | hole, wide);
+            }
 }
 
 static void compile_both(wg::Lowering &low, const Pending &p, uint32_t flags, const wgo_vocab *voc) {
@@ -272,6 +331,7 @@ static void compile_both(wg::Lowering &low, const Pending &p, uint32_t flags, co
 
 int main(int argc, char **argv) {
     if (argc != 2) return 2;
+    check_blocks();
     std::ifstream in(argv[1]);
     std::string line, vb;
     std::vector<uint64_t> voff;
