@@ -224,7 +224,8 @@ def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
 def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
     """Every workgroup of a row looks it up by itself up to a request per compute unit, and several make
     the same row and class rows: masks, counters and rows in use are as if one had, the rows are there for
-    later calls in one kernel and in two, and they stay when the arena stops being addressed by key."""
+    later calls in one kernel and in two, and they stay when the arena stops being addressed by key.  A class table
+    counts once, in the call that takes it up, whatever the keys that share it."""
     torch = torch_cuda
     base = ws.make_workload(3, V=V, B=1, steps=1)
     args = list(base.args[:1]) + [{"x": bytes(np.random.default_rng(1).integers(1, 256, 5000, dtype=np.uint8))}]
@@ -236,8 +237,14 @@ def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
     own = h.num_states
     mask = torch.empty((300, h.W), dtype=torch.int32, device="cuda")
 
-    def fill(sids):
-        st = np.stack([sids, np.zeros_like(sids)], 1).astype(np.uint32)
+    table = wg.Table(texts[:1], args[:1], flags=wg.EOS_RESTART, lmax=int(np.diff(w.vocab.offsets).max()))
+    sets = {s: tuple(table.symbol_class(s, x) for x in range(256)) for s in range(own) if table.state(s)["kind"] in (2, 3)}
+
+    def tables(sids):
+        return {sets[s] for s in sids.tolist() if s in sets}
+
+    def fill(sids, used_up=0):
+        st = np.stack([sids, np.full_like(sids, used_up)], 1).astype(np.uint32)
         before = h.cache_stats()
         mask.fill_(0x35353535)
         h.fill_masks(H.dev_states(st), mask[:len(st)])
@@ -250,21 +257,27 @@ def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
     n = len(np.unique(sids))
     for _ in range(2):
         d, used = fill(sids)
-        assert d["builds"] == n == used and d["hits"] == 0
+        assert d["builds"] == n == used and d["hits"] == 0 and d["class_scans"] == len(tables(sids))
         d, used = fill(sids)
         assert d["builds"] == 0 and d["class_scans"] == 0 and d["hits"] == B and used == n
         h.cache_clear()
     fill(sids)
     rest = 1 + np.arange(300, dtype=np.uint32) % (own - 1)          # two kernels find them, and make the others
     d, used = fill(rest)
-    assert d["builds"] == own - 1 - n and used == own - 1
+    assert d["builds"] == own - 1 - n and used == own - 1 and d["class_scans"] == len(tables(rest) - tables(sids))
+    # new keys whose class table is there: a bounded Wait with a byte left, in as many requests as before and in more
+    bounded = np.array([s for s in sets if table.state(s)["n_keys"] > 1], dtype=np.uint32)
+    for i, size in enumerate((B, 300)):
+        d, now = fill(np.resize(bounded, size), 255 - i)
+        used += min(size, len(bounded))
+        assert d["builds"] == min(size, len(bounded)) and d["class_scans"] == 0 and now == used, size
     h.add_instances(texts[1:], args[1:])                            # more keys than rows
     s = h.cache_stats()
-    assert s["keys"] > s["cache_rows"] and s["rows_in_use"] == own - 1
-    d, used = fill(sids)
+    assert s["keys"] > s["cache_rows"] and s["rows_in_use"] == used
+    d, _ = fill(sids)
     assert d["builds"] == 0 and d["hits"] == B
-    d, used = fill(np.arange(own, own + 40, dtype=np.uint32))
-    assert d["builds"] == 40 and used == own - 1 + 40
+    d, now = fill(np.arange(own, own + 40, dtype=np.uint32))
+    assert d["builds"] == 40 and now == used + 40
     d, _ = fill(np.concatenate([sids[:200], np.arange(own, own + 40, dtype=np.uint32)]))
     assert d["builds"] == 0
 
