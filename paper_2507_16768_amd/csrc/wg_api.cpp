@@ -698,7 +698,7 @@ int wg_advance(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uin
     if (!h || !d_states || !d_tokens) return fail(WG_ERR_INVALID, "wg_advance: null argument");
     if (B == 0) return fail(WG_ERR_INVALID, "wg_advance: B is 0");
     Timing advance(h, true, &h->advance_events);
-    WG_HIP(advance.launched(launch_advance(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, static_cast<hipStream_t>(stream), advance.events())));
+    WG_HIP(advance.launched(launch_advance(h->dt, h->vocab->dv, h->dc, d_states, d_tokens, B, h->n_cu, static_cast<hipStream_t>(stream), advance.events())));
     return WG_OK;
 }
 

@@ -157,7 +157,7 @@ hipError_t launch_masked_topk(const void *logits, int dtype, uint32_t B, uint32_
 constexpr uint64_t kTopkStaticKeys = 1ull << 19;
 hipError_t static_topk_scratch(unsigned long long **out);
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                          wg_state_t *states, const int32_t *tokens, uint32_t B, hipStream_t s,
+                          wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t n_cu, hipStream_t s,
                           hipEvent_t *ev);
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
                                uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, hipStream_t s);

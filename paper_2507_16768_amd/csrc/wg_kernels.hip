@@ -209,9 +209,9 @@ __device__ __forceinline__ StateDesc descriptor(const DeviceTable &T, uint32_t s
 // walked one after the other, each step a trip to memory (the lookup with an advance before it, B = 256:
 // 7.5 us with 64, 6.2 with 4).  With one to a wavefront the lookup of a cached step of 300 requests is 0.4 us faster,
 // that of a made one up to 1 us slower: more wavefronts claim on the same tags.  The advance alone claims nothing and
-// takes one as long as that fills no more than two wavefronts a unit: with 4 / with 1, B = 64 4.23 / 3.92 us, 256 4.45 /
+// takes one as long as that fills no more than two wavefronts a unit (launch_advance): with 4 / with 1, B = 64 4.23 / 3.92 us, 256 4.45 /
 // 4.18, 512 4.26 / 4.16, 1024 4.60 / 4.78, 8192 5.6 / 7.7.
-constexpr uint32_t kLookupThreads = 4, kAdvanceAlone = 512;
+constexpr uint32_t kLookupThreads = 4;
 __global__ void __launch_bounds__(64)
 advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
                const int32_t *__restrict__ tokens, uint32_t B)
@@ -1309,10 +1309,10 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
 }
 
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                          wg_state_t *states, const int32_t *tokens, uint32_t B, hipStream_t s,
+                          wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t n_cu, hipStream_t s,
                           hipEvent_t *ev)
 {
-    const uint32_t threads = B <= kAdvanceAlone ? 1u : kLookupThreads;
+    const uint32_t threads = B <= 2u * n_cu ? 1u : kLookupThreads;
     return launch(advance_kernel, dim3(cdiv(B, threads)), dim3(threads), 0, s, ev, T, Vc, Cc, states, tokens, B);
 }
 
