@@ -238,9 +238,9 @@ struct Found {
     RowTask me;                  // when ref is kRefBuild
 };
 
-// In a fill of one kernel no workgroup waits to learn whether it owns the key or the class table that it makes: 8 to
-// 32 workgroups of every row that needs one would swap on one tag, 10 ns each (a cold call of 256 requests 42 us,
-// now 18).  All workgroups of a row make their shares and keep them; the row's first one then enters the tags,
+// In a fill of one kernel no workgroup waits to learn whether it owns the key or the class table that it makes: all
+// workgroups of every row that needs one, up to 32 of each, would swap on one tag, 10 ns each (a cold call of 256
+// requests 42 us, now 18).  All workgroups of a row make their shares and keep them; the row's first one then enters the tags,
 // behind what it has to do, and the first of a call to do so counts.  A workgroup that finds the tag entered by
 // another row of the call keeps nothing: that row's workgroups all find it old or their own, and keep theirs.
 struct Claim { unsigned long long key_tag, class_tag; uint32_t key, cls; };      // tags as the lookup found them
@@ -506,8 +506,8 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 //     checkpoint follows, by the exit byte).
 // The first wavefront sees to the candidates (and to all that it needs for them itself: the successors' class
 // tables and literal bytes come with the directories), the others to the rest.  What the walks need of the
-// successors lies in LDS and not in scalar registers, of which this kernel has too few: with a pointer for each
-// of the vocabulary's arrays and both successors in them 136 values were kept in lanes of vector registers, now 78.
+// successors lies in LDS and not in scalar registers, of which this kernel has too few: what they do not hold is kept in
+// lanes of vector registers, 83 to 89 values with the lookup in a kernel before it and 104 to 112 with it in front.
 // Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
 // that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
@@ -1156,10 +1156,11 @@ static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b -
 
 // Logits of more bytes than these are masked by whole lines (see mask_lines): 128 bytes are read where a
 // line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
-// depends on how many tokens of a line are disallowed, which the host does not know; the limits lie where
-// the geometric mean over four kinds of masks is the same for both.  By elements / by lines, us, a cached
-// step on the masks of html outlines, of JSON objects, of both mixed, and of random trees (16, 25, 45 and 63 %
-// of the tokens disallowed):
+// depends on how many tokens of a line are disallowed, which the host does not know; the limits lie near where
+// the geometric mean over four kinds of masks is the same for both: 225 MB of bf16 and 360 MB of fp32 by the figures
+// below, a little above the limits, which were set before the masking by elements became faster and stay where
+// random trees gain.  By elements / by lines, us, a cached step on the masks of html outlines, of JSON objects, of
+// both mixed, and of random trees (16, 25, 45 and 63 % of the tokens disallowed):
 //   bf16, V = 151936: 194 MB 50 / 72, 47 / 72, 83 / 78, 94 / 80; 213 MB 58 / 82, 63 / 79, 95 / 86, 101 / 89; 225 MB 78 / 88,
 //   76 / 87, 100 / 92, 103 / 90; 252 MB 97 / 100, 97 / 98, 114 / 103, 114 / 98; 311 MB 128 / 117, 125 / 117, 140 / 120, 147 / 124
 //   fp32, V = 128256: 308 MB 59 / 91, 66 / 93, 110 / 105, 126 / 110; 328 MB 79 / 98, 82 / 97, 119 / 110, 143 / 125; 359 MB
