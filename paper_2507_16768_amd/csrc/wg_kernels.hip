@@ -1038,20 +1038,22 @@ __global__ void __launch_bounds__(256) count_rows_kernel(DeviceCache Cc)
 
 // apply: a wavefront takes kApplyPairs times 64 tokens of a row, its mask straight from memory (with 8, 16, 32 and
 // 64, V = 151936, B = 256, bf16, mixed 14.8, 13.3, 13.4 and 13.1 us; V = 32000, B = 256 5.1, 4.9, 4.6 and 5.2).
-// A wavefront with at most a token per lane to mask lists them in LDS and stores them all at once: reading lanes and
+// A wavefront with at most kApplyFew tokens to mask lists them in LDS and stores them all at once: reading lanes and
 // storing for every 64 tokens it was slower than a store per disallowed token of each piece had been (that / always 64 at
 // a time / now, V = 151936, bf16, tokens disallowed at random: 0.2 % B = 256 5.4 / 6.7 / 4.3, 600 11.6 / 12.7 / 7.9; 1.2 % B = 64
-// 3.6 / 4.1 / 3.5, 256 8.1 / 8.5 / 7.1, 600 15.4 / 15.0 / 13.6; fp32, 0.2 %, B = 256 8.2 / 6.7 / 4.3).  With at most 32 the gain ends at 1.5 %;
-// with 128 html and JSON, B = 256, take 11.9 and 11.9 instead of 11.7 and 11.8; the one loss seen with 64 is html, fp32, B = 64,
-// 5.0 -> 5.2.  Left: bf16 logits of 120 to 208 MB with 4 to 8 % disallowed at random, 3 to 6 % slower than by pieces (B = 600
-// 27.4 -> 28.3 and 34.4 -> 35.5).  16 times 64 tokens mend it (27.7, 34.7) but cost 13.1 for 7.9 at 0.2 % and 4 % of mixed masks, B = 256.
-constexpr uint32_t kApplyPairs = 32;
+// 3.7 / 4.0 / 3.5, 256 8.2 / 8.4 / 7.1, 600 15.4 / 15.0 / 13.6; 1.8 % B = 128 5.8 / 6.3 / 5.5, 256 9.2 / 9.3 / 8.8).  With 32 the gain ends at
+// 1.5 %; with 64 the free text of html and JSON (V = 128256, 3 %) is listed too, in 9.9 instead of 9.7 and 10.5 instead of
+// 10.2 us, B = 256.  Left: bf16 logits of 120 to 208 MB with 4 to 8 % disallowed at random, 3 to 6 % slower than by pieces
+// (B = 600 27.4 -> 28.3 and 34.4 -> 35.5).  16 times 64 tokens mend it (27.7, 34.7) but cost 13.1 for 7.9 at 0.2 % and 4 % of
+// mixed masks, B = 256.
+constexpr uint32_t kApplyPairs = 32, kApplyFew = 48;
 template <typename Elem>
 __global__ void __launch_bounds__(256)
 apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
-    __shared__ uint16_t few[4][64];
+    static_assert(kApplyFew <= 64u, "a lane each");
+    __shared__ uint16_t few[4][kApplyFew];
     const uint32_t b = blockIdx.y, lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t first = (blockIdx.x * 4u + wave) * kApplyPairs;
     const uint32_t *row = bitmask + (size_t)b * W;
@@ -1064,7 +1066,7 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
     Elem *p = logits + (int64_t)b * row_stride + (size_t)first * 64u;
     const uint32_t off = (uint32_t)(__popc(~lo) + __popc(~hi)), upto = wave_prefix_sum(off);
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    if (n <= 64u) {
+    if (n <= kApplyFew) {
         uint32_t at = upto - off;
         for (unsigned long long z = ~((unsigned long long)hi << 32 | lo); z; z &= z - 1ull)
             few[wave][at++] = (uint16_t)(lane * 64u + (uint32_t)__builtin_ctzll(z));

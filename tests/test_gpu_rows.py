@@ -140,14 +140,14 @@ def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V", [2048, 8191, 8193, 20001])
 def test_masking_of_few_scattered_tokens(torch_cuda, V, dtype):
-    """Either side of 64 disallowed tokens in a wavefront's 2,048, which it then lists and stores at once: at random
+    """Either side of 48 disallowed tokens in a wavefront's 2,048, which it then lists and stores at once: at random
     places, side by side, at the ends of the share; rows at any address, nothing outside them touched."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
     rng = np.random.default_rng(V)
     rows = []
-    for n in (1, 2, 63, 64, 65, 66, 200):
+    for n in (1, 2, 47, 48, 49, 64, 65, 200):
         for places in (lambda m: rng.permutation(m)[:n], lambda m: np.arange(min(n, m)), lambda m: np.arange(max(0, m - n), m)):
             ok = np.ones(V, dtype=bool)
             for lo in range(0, V, 2048):
