@@ -237,8 +237,8 @@ uint32_t wg_mask_words(wg_handle_t h);      /* W = ceil(V/32) */
  * wg_fill_masks: d_bitmask[b][0..W) <- mask of d_states[b] (mask creation with the global
  * cache of the section "Mask Generation and Global Caching"): cached rows are copied, missing
  * ones are made, and kept once per distinct key.  An ERROR or out-of-range state gets an all-zero
- * row.  One kernel for up to a request per compute unit while the cache has a row for every key,
- * else two (a workgroup for every 1/1 to 1/32 of a row). */
+ * row.  One kernel for up to a request per compute unit (fewer from about 350,000 tokens on) while the
+ * cache has a row for every key, else two (a workgroup for every 1/1 to 1/32 of a row). */
 int wg_fill_masks(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint32_t *d_bitmask,
                   void *stream);
 
