@@ -1036,37 +1036,42 @@ __global__ void __launch_bounds__(256) count_rows_kernel(DeviceCache Cc)
     if ((threadIdx.x & 63u) == 63u && held) atomicAdd(&Cc.ctr->held, (unsigned long long)held);
 }
 
-// apply: a wavefront takes kApplyPairs times 64 tokens of a row, its mask straight from memory (with 8, 16, 32 and
-// 64, V = 151936, B = 256, bf16, mixed 14.8, 13.3, 13.4 and 13.1 us; V = 32000, B = 256 5.1, 4.9, 4.6 and 5.2).
-// A wavefront with at most kApplyFew tokens to mask lists them in LDS and stores them all at once: reading lanes and
+// apply: a wavefront takes kPairs times 64 tokens of a row, its mask straight from memory: 32 (with 8, 16, 32 and 64, V =
+// 151936, B = 256, bf16, mixed 14.8, 13.3, 13.4 and 13.1 us; V = 32000, B = 256 5.1, 4.9, 4.6 and 5.2), and 24 of bf16 logits of
+// more than kApplyLarge bytes, where 32 were up to 5 % slower than a store per disallowed token of each piece on scattered
+// tokens (by pieces / 32 / 24, V = 151936, B = 600, 182 MB: 4 % at random 27.7 / 28.1 / 27.3, 8 % 34.4 / 35.3 / 33.1, html 24.7 / 25.3 /
+// 24.3, mixed 29.0 / 28.0 / 28.0; B = 400, 122 MB, 4 % 19.4 / 20.0 / 19.1).  Why is not shown; 3 KB of logits to a wavefront instead
+// of 4 may keep neighbours from storing to one channel at a time, but 40 (5 KB) are 3 % slower and 16 cost more launches.
+// Below: 78 MB html, JSON, mixed, random trees 0.98 0.98 1.01 1.01 of the time with 32, 33 MB 1.04 1.05 1.03 1.01; fp32, V =
+// 128256, B = 600, random trees 1.05.
+// A wavefront with at most 1.5 tokens of 64 to mask lists them in LDS and stores them all at once: reading lanes and
 // storing for every 64 tokens it was slower than a store per disallowed token of each piece had been (that / always 64 at
-// a time / now, V = 151936, bf16, tokens disallowed at random: 0.2 % B = 256 5.4 / 6.7 / 4.3, 600 11.6 / 12.7 / 7.9; 1.2 % B = 64
-// 3.7 / 4.0 / 3.5, 256 8.2 / 8.4 / 7.1, 600 15.4 / 15.0 / 13.6; 1.8 % B = 128 5.8 / 6.3 / 5.5, 256 9.2 / 9.3 / 8.8).  With 32 the gain ends at
-// 1.5 %; with 64 the free text of html and JSON (V = 128256, 3 %) is listed too, in 9.9 instead of 9.7 and 10.5 instead of
-// 10.2 us, B = 256.  Left: bf16 logits of 120 to 208 MB with 4 to 8 % disallowed at random, 3 to 6 % slower than by pieces
-// (B = 600 27.4 -> 28.3 and 34.4 -> 35.5).  16 times 64 tokens mend it (27.7, 34.7) but cost 13.1 for 7.9 at 0.2 % and 4 % of
-// mixed masks, B = 256.
-constexpr uint32_t kApplyPairs = 32, kApplyFew = 48;
-template <typename Elem>
+// a time / now, V = 151936, bf16, tokens disallowed at random: 0.2 % B = 256 5.4 / 6.7 / 4.3, 600 11.6 / 12.7 / 9.3; 1.2 % B = 64
+// 3.7 / 4.0 / 3.5, 256 8.2 / 8.4 / 7.1, 600 15.4 / 15.0 / 14.0; 1.8 % B = 128 5.8 / 6.3 / 5.5, 256 9.2 / 9.3 / 8.8).  With 1 of 64
+// the gain ends at 1.5 %; with 2 the free text of html and JSON (V = 128256, 3 %) is listed too, in 9.9 instead of 9.7 and 10.5
+// instead of 10.2 us, B = 256.
+constexpr uint64_t kApplyLarge = 96ull << 20;
+template <typename Elem, uint32_t kPairs>
 __global__ void __launch_bounds__(256)
 apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
-    static_assert(kApplyFew <= 64u, "a lane each");
-    __shared__ uint16_t few[4][kApplyFew];
+    constexpr uint32_t kFew = kPairs * 3u / 2u;
+    static_assert(kPairs % kChunk == 0u && kPairs <= 64u && kFew <= 64u, "a lane each");
+    __shared__ uint16_t few[4][kFew];
     const uint32_t b = blockIdx.y, lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t first = (blockIdx.x * 4u + wave) * kApplyPairs;
+    const uint32_t first = (blockIdx.x * 4u + wave) * kPairs;
     const uint32_t *row = bitmask + (size_t)b * W;
     const uint32_t w = 2u * (first + lane);
     uint32_t lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu;
-    if (lane < kApplyPairs) {
+    if (lane < kPairs) {
         lo = word_or_ones(row, w, W, V);
         hi = word_or_ones(row, w + 1u, W, V);
     }
     Elem *p = logits + (int64_t)b * row_stride + (size_t)first * 64u;
     const uint32_t off = (uint32_t)(__popc(~lo) + __popc(~hi)), upto = wave_prefix_sum(off);
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    if (n <= kApplyFew) {
+    if (n <= kFew) {
         uint32_t at = upto - off;
         for (unsigned long long z = ~((unsigned long long)hi << 32 | lo); z; z &= z - 1ull)
             few[wave][at++] = (uint16_t)(lane * 64u + (uint32_t)__builtin_ctzll(z));
@@ -1075,7 +1080,7 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
         return;
     }
 #pragma unroll
-    for (uint32_t c = 0; c < kApplyPairs; c += kChunk) mask_chunk<Elem>(p + (size_t)c * 64u, lo, hi, c);
+    for (uint32_t c = 0; c < kPairs; c += kChunk) mask_chunk<Elem>(p + (size_t)c * 64u, lo, hi, c);
 }
 
 // The same by whole lines: a workgroup takes kLineTokens tokens of a row.
@@ -1304,11 +1309,15 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
                         const uint32_t *bitmask, hipStream_t s, hipEvent_t *ev)
 {
     const uint32_t W = (V + 31u) / 32u;
+    auto apply = [&](auto kernel, auto *x, uint32_t tokens) { return launch(kernel, dim3(cdiv(V, tokens), B), dim3(256), 0, s, ev, x, row_stride, V, W, bitmask); };
     const bool lines = by_lines(dtype, B, V);
-    const dim3 g(cdiv(V, lines ? kLineTokens : 4u * 64u * kApplyPairs), B);
-    if (dtype == WG_F32)
-        return launch(lines ? apply_lines_kernel<uint32_t> : apply_kernel<uint32_t>, g, dim3(256), 0, s, ev, static_cast<uint32_t *>(logits), row_stride, V, W, bitmask);
-    return launch(lines ? apply_lines_kernel<uint16_t> : apply_kernel<uint16_t>, g, dim3(256), 0, s, ev, static_cast<uint16_t *>(logits), row_stride, V, W, bitmask);
+    if (dtype == WG_F32) {
+        uint32_t *x = static_cast<uint32_t *>(logits);
+        return lines ? apply(apply_lines_kernel<uint32_t>, x, kLineTokens) : apply(apply_kernel<uint32_t, 32u>, x, 4u * 64u * 32u);
+    }
+    uint16_t *x = static_cast<uint16_t *>(logits);
+    if (lines) return apply(apply_lines_kernel<uint16_t>, x, kLineTokens);
+    return (uint64_t)B * V * 2u > kApplyLarge ? apply(apply_kernel<uint16_t, 24u>, x, 4u * 64u * 24u) : apply(apply_kernel<uint16_t, 32u>, x, 4u * 64u * 32u);
 }
 
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,

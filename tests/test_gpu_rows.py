@@ -137,30 +137,32 @@ def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
         assert torch.equal(x.view(bits), want.view(bits)), cold
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("V", [2048, 8191, 8193, 20001])
-def test_masking_of_few_scattered_tokens(torch_cuda, V, dtype):
-    """Either side of 48 disallowed tokens in a wavefront's 2,048, which it then lists and stores at once: at random
-    places, side by side, at the ends of the share; rows at any address, nothing outside them touched."""
+@pytest.mark.parametrize("dtype,V,B", [(t, V, 24) for t in ("f32", "bf16") for V in (1536, 2048, 8191, 8193, 20001)] + [("bf16", 100003, 503), ("bf16", 100003, 504)])
+def test_masking_of_few_scattered_tokens(torch_cuda, V, B, dtype):
+    """Either side of 48 disallowed tokens in a wavefront's 2,048, or 36 in 1,536 (bf16 logits above 96 MiB), which it then
+    lists and stores at once: at random places, side by side, at the ends of the share; rows at any address, nothing
+    outside them touched."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
+    share, edge = (1536, 36) if B == 504 else (2048, 48)
     rng = np.random.default_rng(V)
     rows = []
-    for n in (1, 2, 47, 48, 49, 64, 65, 200):
+    for n in (1, 2, edge - 1, edge, edge + 1, 64, 65, 200):
         for places in (lambda m: rng.permutation(m)[:n], lambda m: np.arange(min(n, m)), lambda m: np.arange(max(0, m - n), m)):
             ok = np.ones(V, dtype=bool)
-            for lo in range(0, V, 2048):
-                ok[lo + places(min(2048, V - lo))] = False
+            for lo in range(0, V, share):
+                ok[lo + places(min(share, V - lo))] = False
             rows.append(ok)
     allowed, W = np.stack(rows), (V + 31) // 32
     packed = np.packbits(np.pad(allowed, ((0, 0), (0, 32 * W - V))), axis=1, bitorder="little").view(np.int32)
-    mask, B = torch.from_numpy(packed.copy()).cuda(), len(rows)
+    which = torch.arange(B, device="cuda") % len(rows)
+    mask, allowed = torch.from_numpy(packed.copy()).cuda()[which], torch.from_numpy(allowed).cuda()[which]
     for off, pad in ((0, 0), (1, 3), (5, 64)):
         buf = torch.randn(B * (V + pad) + 24, device="cuda").to(dt)
         x = buf[off:off + B * (V + pad)].view(B, V + pad)[:, :V]
         want = buf.clone()
-        want[off:off + B * (V + pad)].view(B, V + pad)[:, :V].masked_fill_(~torch.from_numpy(allowed).cuda(), float("-inf"))
+        want[off:off + B * (V + pad)].view(B, V + pad)[:, :V].masked_fill_(~allowed, float("-inf"))
         wg.apply_mask(x, mask)
         assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)
 
