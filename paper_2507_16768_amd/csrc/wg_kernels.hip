@@ -1194,6 +1194,11 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
 // 1024 49.9 / 37.4 and 22.2 / 18.0, V = 24576 B = 33 10.8 / 11.4 and 6.7 / 6.9, V = 32000 B = 256 19.3 / 18.7 and 12.6
 // / 12.0, B = 1024 51.5 / 40.3 and 23.1 / 21.6 (random trees 57.8 / 48.1 and 26.8 / 32.0); with 4 / 2, V = 12000 B = 64
 // 11.1 / 11.5 and 6.9 / 7.1, B = 1024 36.4 / 29.6 and 16.1 / 15.3.
+// Fewer too where the lookup that each repeats is most of a short share's work: up to a request per unit and more than
+// seven workgroups on one (above, rows are looked up once).  With 8 / 4, B = 256, kernel us of wg_decode_step on outlines, JSON,
+// mixed, random trees: copied V = 24576 9.3 9.5 9.7 9.5 / 9.0 9.0 9.3 9.3 (a lookup kernel and 8 shares: 9.3 10.0 9.8 12.1), 32768 10.8
+// 10.5 10.8 11.2 / 9.6 9.8 9.7 10.0 (9.8 10.1 10.2 15.1); made 24576 14.8 15.6 16.0 21.0 / 13.9 14.6 15.0 19.6, 32768 16.3 16.3 16.8 22.7 /
+// 14.7 15.2 15.5 23.4.  Longer rows of random trees take a tenth longer to make (V = 36800 23.9 / 26.3, 65536 27.9 / 33.7).
 constexpr uint32_t kLeastParts = 8;
 static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
 {
@@ -1203,6 +1208,7 @@ static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
         if (n > 7ull * n_cu || parts * 2u * (n <= 4ull * n_cu ? 4096u : 6144u) > V) break;
         parts *= 2u;
     }
+    if (parts == kLeastParts && B <= n_cu && B * parts > 7u * n_cu && V <= parts * 4096u) parts >>= 1;
     const uint32_t least = B > n_cu ? 3072u : (uint64_t)B * parts > n_cu ? 2560u : kPartGroup;
     while (parts > 1u && parts * least > V) parts >>= 1;
     return parts;

@@ -190,7 +190,7 @@ def test_masking_of_logits_beyond_the_last_level_cache(torch_cuda, dtype, B, V, 
     assert torch.equal(buf.view(bits), want.view(bits))
 
 
-@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97), (65536, 97), (131072, 48), (131073, 64), (147456, 64), (20481, 40), (24577, 300), (98304, 64), (98304, 112), (98304, 113), (131072, 32), (131072, 33), (40000, 256), (40000, 257),
+@pytest.mark.parametrize("V,B", [(65535, 8), (65536, 8), (131072, 4), (131073, 5), (151936, 1), (98304, 33), (98304, 96), (98305, 97), (65536, 97), (131072, 48), (131073, 64), (147456, 64), (20481, 40), (24577, 300), (98304, 64), (98304, 112), (98304, 113), (32768, 224), (32768, 225), (32768, 256), (32769, 256), (32768, 257), (131072, 32), (131072, 33), (40000, 256), (40000, 257),
                                  (40000, 32), (40000, 33), (8200, 7), (3000, 512), (3000, 513)])
 def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
     """Rows cut into 1 to 32 workgroups, looked up in the rows' kernel and before it; the advance by itself with
