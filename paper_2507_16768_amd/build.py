@@ -10,6 +10,8 @@ HEADERS = ["wg_internal.h", "wg_device.h", "wg_launch.h", "wg_order.h", os.path.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          # packed-fp32 instruction selection is switched off for every kernel in this library
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a kernel's first 14 dwords of arguments are in scalar registers when its wavefronts begin
+         "-Xarch_device", "-mllvm=-amdgpu-kernarg-preload-count=14",
          # found by its name next to the Python module, wherever the tree lies
          "-Wl,-soname,libwgrammar.so"]
 

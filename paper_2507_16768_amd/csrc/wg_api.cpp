@@ -423,10 +423,10 @@ void wg_destroy(wg_handle_t h) {
     if (!h) return;
     (void)hipDeviceSynchronize();
     (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
-    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.spread); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
+    (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
     if (h->stage) (void)hipHostFree(h->stage);
-    (void)hipFree(h->dc.tickets); (void)hipFree(h->d_free_rows);
+    (void)hipFree(h->d_free_rows);
     (void)hipFree(h->dc.class_tags); (void)hipFree(h->dc.class_rows);
     for (auto *v : {&h->lookup_events, &h->rows_events, &h->advance_events, &h->apply_events, &h->spare_events})
         for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
@@ -475,19 +475,11 @@ static int compile(const char *const *templates, const wg_args_t *args, uint32_t
     if (rows > fit) rows = fit ? fit : 1;
     if (rows > kMaxRows) rows = kMaxRows;
 
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ctr), sizeof(Counters)));
-    WG_HIP(hipMemset(h->dc.ctr, 0, sizeof(Counters)));
-    const size_t spread_bytes = (size_t)kSpread * kSpreadStride * sizeof(unsigned long long);
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.spread), spread_bytes));
-    WG_HIP(hipMemset(h->dc.spread, 0, spread_bytes));
+    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.ctr), sizeof(Control)));
+    WG_HIP(hipMemset(h->dc.ctr, 0, sizeof(Control)));
     int cus = 0;
     WG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, vocab->device));
     if (cus > 0) h->n_cu = (uint32_t)cus;
-    // (a fill in one kernel has at most n_cu rows: plan_fill)
-    const size_t ticket_bytes = ((size_t)h->n_cu + 1) * kTicketStride * sizeof(uint32_t);
-    WG_HIP(hipMalloc(reinterpret_cast<void **>(&h->dc.tickets), ticket_bytes));
-    WG_HIP(hipMemset(h->dc.tickets, 0, ticket_bytes));
-    h->dc.rows_ticket = h->dc.tickets + (size_t)h->n_cu * kTicketStride;
     WG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->stage), kStageBytes, hipHostMallocDefault));
     int rc = set_cache_rows(h.get(), (uint32_t)rows);
     if (rc == WG_OK) rc = sync_table(h.get(), nullptr);
@@ -730,7 +722,7 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
     host_out->uncached_builds = c.uncached_builds;
     host_out->class_scans = c.class_scans;
     unsigned long long spread[kSpread * kSpreadStride];
-    WG_HIP(hipMemcpy(spread, h->dc.spread, sizeof spread, hipMemcpyDeviceToHost));
+    WG_HIP(hipMemcpy(spread, h->dc.ctr->spread, sizeof spread, hipMemcpyDeviceToHost));
     host_out->entries_walked = host_out->hits = 0;
     for (uint32_t i = 0; i < kSpread; i++) {
         host_out->entries_walked += spread[i * kSpreadStride + kSpreadWalked];

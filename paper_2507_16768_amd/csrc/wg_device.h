@@ -93,11 +93,21 @@ constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
 constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1,
                    kSpreadBuilds = 2, kSpreadClasses = 3;       // of fills with the arena addressed by key
-constexpr uint32_t kTicketStride = 32;     // a 128-byte line for the tickets of a row
+constexpr uint32_t kTicketStride = 32, kTicketGroup = 16;       // a 128-byte line for the tickets of a row; rows of a group
+constexpr uint32_t kOneKernelRows = 512;                        // most rows of a fill in one kernel
+
+// All that calls count in, one piece of memory: a pointer costs the kernels two of their scalar registers.
+struct Control : Counters {
+    alignas(128) unsigned long long spread[kSpread * kSpreadStride];     // kSpread groups of counters, kSpreadStride apart
+    // one-kernel fill, zero between calls: groups all of whose rows have, rows of a group all of whose workgroups have,
+    // workgroups of a row that have read its state (the latter two kTicketStride apart)
+    alignas(128) uint32_t call_ticket;
+    alignas(128) uint32_t group_tickets[kOneKernelRows / kTicketGroup * kTicketStride];
+    alignas(128) uint32_t tickets[kOneKernelRows * kTicketStride];
+};
 
 struct DeviceCache {
-    Counters *ctr;
-    unsigned long long *spread;  // kSpread groups of counters, kSpreadStride apart
+    Control *ctr;
     // per state key
     unsigned long long *tags;
     uint32_t *slots;             // not direct: arena row of a claimed key, or kNoSlot: the arena was full (and stays so)
@@ -111,9 +121,6 @@ struct DeviceCache {
     // per call
     uint32_t *row_ref;           // [B] arena row, kRefBuild or kNoKey
     RowTask *tasks;              // [B]
-    // one-kernel fill, zero between calls: workgroups of a row that have read its state (kTicketStride
-    // apart), rows all of whose workgroups have
-    uint32_t *tickets, *rows_ticket;
     uint32_t row_stride;         // words, multiple of 4
     uint32_t n_keys;
     uint32_t epoch;              // cache generation of this call

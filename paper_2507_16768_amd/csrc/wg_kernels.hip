@@ -21,6 +21,62 @@
 namespace wg {
 
 // ---------------------------------------------------------------------------------------------
+// Arguments of the kernels that a step launches.  What their first loads need comes first, each by itself: it is in
+// scalar registers when a wavefront begins (kernarg preload, 14 dwords: build.py).  The rest lies behind it in the
+// kernel's argument memory and is read from there where it is needed, through references: structures passed by value were
+// loaded as a whole at the kernel's beginning, 60 registers in four to seven rounds of waiting, and put away in lanes of
+// vector registers.  A pass of 8 cached steps, us, by value / by reference: 1 request, V = 32000 49.5 / 38.8; 64, V = 128256 70.3 / 60.5;
+// 256, V = 151936 181 / 170; a cached fill of 1,024 rows behind a lookup 10.9 / 8.6.
+struct LateArgs {
+    DeviceTable T;
+    DeviceVocab Vc;
+    DeviceCache Cc;
+    uint32_t *bitmask;
+    void *logits;
+    int64_t logits_stride;
+    uint32_t span, shares, rows; // token ranges of a workgroup, workgroups of a row, rows of the call
+};
+#define WG_EARLY_ARGS wg_state_t *__restrict__ states, const int32_t *__restrict__ tokens, Control *ctr, const StateDesc *descs, \
+                      const uint64_t *chunks, const uint8_t *len8, uint32_t n_states, uint32_t V, LateArgs
+constexpr uint32_t kEarlyBytes = 6u * 8u + 2u * 4u;
+typedef const __attribute__((address_space(4))) LateArgs Late;
+template <typename M> using LateRef = const __attribute__((address_space(4))) M &;
+__device__ __forceinline__ Late &late_args()
+{
+    return *(Late *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kEarlyBytes);
+}
+struct TableView {
+    const StateDesc *states;
+    uint32_t n_states;
+    LateRef<const uint8_t *> classes, lit;
+    LateRef<const ClassPlan *> plans;
+    LateRef<uint32_t> lmax;
+};
+struct VocabView {
+    const uint8_t *len8;
+    const uint64_t *chunks;
+    uint32_t V;
+    LateRef<const uint32_t *> rows, dirs;
+    LateRef<const ExitEntry *> index;
+    LateRef<uint32_t> W, lmax, n_chunks;
+    LateRef<int32_t> eos_id;
+};
+struct CacheView {
+    Control *ctr;
+    LateRef<unsigned long long *> tags, class_tags;
+    LateRef<uint32_t *> slots, arena, class_rows, row_ref;
+    LateRef<const uint32_t *> free_rows;
+    LateRef<RowTask *> tasks;
+    LateRef<uint32_t> cap_rows, direct, row_stride, epoch;
+};
+#define WG_VIEWS \
+    Late &late = late_args(); \
+    const TableView T{descs, n_states, late.T.classes, late.T.lit, late.T.plans, late.T.lmax}; \
+    const VocabView Vc{len8, chunks, V, late.Vc.rows, late.Vc.dirs, late.Vc.index, late.Vc.W, late.Vc.lmax, late.Vc.n_chunks, late.Vc.eos_id}; \
+    const CacheView Cc{ctr, late.Cc.tags, late.Cc.class_tags, late.Cc.slots, late.Cc.arena, late.Cc.class_rows, late.Cc.row_ref, late.Cc.free_rows, \
+                   late.Cc.tasks, late.Cc.cap_rows, late.Cc.direct, late.Cc.row_stride, late.Cc.epoch}
+
+// ---------------------------------------------------------------------------------------------
 // Walking a token through the state table.
 
 // A token's bytes as 8-byte chunks of the vocabulary, two of them in registers at a time; the
@@ -32,7 +88,7 @@ struct TokenBytes {
     uint32_t q, n;               // n: chunks of the token
 };
 
-__device__ __forceinline__ TokenBytes token_bytes(const DeviceVocab &Vc, uint32_t tok, uint32_t L)
+__device__ __forceinline__ TokenBytes token_bytes(const VocabView &Vc, uint32_t tok, uint32_t L)
 {
     TokenBytes t;
     t.chunks = Vc.chunks + tok; t.stride = Vc.V;
@@ -105,11 +161,13 @@ __device__ __forceinline__ bool class_step(const StateDesc &d, uint32_t code, ui
     return left != CLS_REJECT;
 }
 
+__device__ __forceinline__ bool is_checkpoint(uint32_t kind) { return kind == WG_KIND_WAIT || kind == WG_KIND_COND; }
+
 // Walks bytes [i, L) of a token from (sid, aux), up to eight bytes per state visit: a run of
 // literal states is one masked 8-byte compare against the state table's literal bytes, a stay-run
 // inside a checkpoint is eight independent class look-ups.  Every state entered on the way starts
 // with aux = 0; only a bounded Wait counts.  False on the first rejected byte.
-__device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32_t &aux, TokenBytes &t, uint32_t i, uint32_t L)
+__device__ __forceinline__ bool walk(const TableView &T, uint32_t &sid, uint32_t &aux, TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
     while (i < L) {
@@ -129,100 +187,127 @@ __device__ __forceinline__ bool walk(const DeviceTable &T, uint32_t &sid, uint32
     return true;
 }
 
-// A state and the literal bytes around it, requested together (of state 0 where there is no such state).
-struct Visit { StateDesc d; uint64_t l0, l1; };
-__device__ __forceinline__ Visit visit(const DeviceTable &T, uint32_t sid)
-{
-    const uint64_t *lit64 = reinterpret_cast<const uint64_t *>(T.lit);
-    const uint32_t s = sid < T.n_states ? sid : 0u;
-    return Visit{T.states[s], lit64[s >> 3], lit64[(s >> 3) + 1u]};
-}
-// walk() for one token by itself, where every step is a trip to memory that nothing else hides (a pass of
-// 8 cached steps of one request 53 -> 49 us, of 4 mixed requests 58 -> 54): v is
-// the visit of sid, at the call and after it.  It is requested before it is known to be needed: with the
-// classes of a checkpoint's bytes both of its successors'.
-__device__ __forceinline__ bool walk_ahead(const DeviceTable &T, uint32_t &sid, uint32_t &aux, Visit &v, TokenBytes &t, uint32_t L)
-{
-    uint32_t i = 0;
-    while (i < L) {
-        if (sid >= T.n_states) return false;
-        const StateDesc d = v.d;
-        const uint32_t kind = d.kind_byte & 0xFFu;
-        const uint32_t n = L - i < 8u ? L - i : 8u;
-        const uint64_t tb = window(t, i);
-        if (kind == WG_KIND_LIT) {
-            if (!literal_step(d, v.l0, v.l1, tb, n, sid, aux, i)) return false;
-            v = visit(T, sid);
-        } else if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
-            // (behind the classes, so that a walk that stays does not wait for them)
-            const uint8_t *lut = T.classes + (size_t)d.cls * 256u;
-            uint32_t c[8], code = 0, left;
-#pragma unroll
-            for (int k = 0; k < 8; k++) c[k] = lut[(tb >> (8 * k)) & 0xFFu];
-            asm volatile("" ::: "memory");
-            const Visit va = visit(T, d.next_a), vb = visit(T, d.next_b);
-#pragma unroll
-            for (int k = 0; k < 8; k++) code |= c[k] << (2 * k);
-            if (!class_step(d, code, n, aux, i, left)) return false;
-            if (left == CLS_EXIT_A) { sid = d.next_a; v = va; }
-            else if (left == CLS_EXIT_B) { sid = d.next_b; v = vb; }
-        } else return false;
-    }
-    return true;
-}
-__device__ __forceinline__ bool walk_from(const DeviceTable &T, uint32_t sid, TokenBytes &t, uint32_t i, uint32_t L)
+__device__ __forceinline__ bool walk_from(const TableView &T, uint32_t sid, TokenBytes &t, uint32_t i, uint32_t L)
 {
     uint32_t aux = 0;
     return walk(T, sid, aux, t, i, L);
 }
 
 // ---------------------------------------------------------------------------------------------
-// advance: one thread per request (EOS is the one-symbol string [EOS]; any other byte-less token
-// is rejected).
-// v: the visit of sid, at the call and after it.
-__device__ __forceinline__ void advance_one(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
-                                            uint32_t &sid, uint32_t &aux, Visit &v, int64_t t, bool count_error)
+// advance: a wavefront per request, lane p the p-th byte of the token (EOS is the one-symbol string [EOS]; any other
+// byte-less token is rejected).  What the request is at is the same for all lanes, in scalar registers.
+__device__ __forceinline__ uint32_t of_first(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ uint32_t of_lane(uint32_t x, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane); }
+
+// The descriptors of two states in one load: lane k (modulo 16) has dword k % 8 of a's, from 8 on of b's (of state 0 where
+// there is no such state).
+__device__ __forceinline__ uint32_t two_states(const TableView &T, uint32_t a, uint32_t b)
 {
-    bool ok = t >= 0 && t < (int64_t)Vc.V && sid < T.n_states;
+    const uint32_t s = threadIdx.x & 8u ? b : a;
+    return reinterpret_cast<const uint32_t *>(T.states + (s < T.n_states ? s : 0u))[threadIdx.x & 7u];
+}
+__device__ __forceinline__ StateDesc state_of(uint32_t words, uint32_t at)      // at: 0 the first of the two, 8 the second
+{
+    return StateDesc{of_lane(words, at), of_lane(words, at + 1u), of_lane(words, at + 2u), of_lane(words, at + 3u),
+                     of_lane(words, at + 4u), of_lane(words, at + 5u), of_lane(words, at + 6u), of_lane(words, at + 7u)};
+}
+
+__device__ __forceinline__ uint32_t token_byte(const VocabView &Vc, uint32_t t, uint32_t p)
+{
+    if (p >= Vc.n_chunks * 8u) return 0u;
+    return reinterpret_cast<const uint8_t *>(Vc.chunks + (size_t)(p >> 3) * Vc.V + t)[p & 7u];
+}
+
+// walk() for one token by a wavefront, where every step is a trip to memory that nothing else hides: one per
+// state, however many bytes are consumed in it.  All bytes that a state might consume are compared or looked up
+// together, a byte per lane, and the descriptors of the states that may follow are requested with them.  (A thread
+// per request, eight bytes at a time, took two trips for every eight bytes of free text, and the longest walk of a
+// batch decides: of 256 mixed requests, V = 151936, the last had its state 8.9 us after the kernel's beginning, now 4.2;
+// wg_advance by itself, B = 64, 256, 1024 3.90, 4.28, 4.78 us -> 3.17, 3.20, 3.60, V = 16000, B = 8192 6.0 -> 5.2.)
+// d: the descriptor of sid, at the call and after it.  byte: the lane's.
+__device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, uint32_t &sid, uint32_t &aux, StateDesc &d,
+                                          uint32_t t, uint32_t byte, uint32_t L)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t i = 0, base = 0;                                // bytes consumed; the byte that lane 0 has
+    while (i < L) {
+        const uint32_t kind = d.kind_byte & 0xFFu;
+        const bool lit = kind == WG_KIND_LIT;
+        if (sid >= T.n_states || !(lit || is_checkpoint(kind))) return false;          // ERROR; FINAL and END accept no byte
+        if (i == base + 64u) { base = i; byte = token_byte(Vc, t, base + lane); }      // a token longer than the wavefront
+        uint32_t n = (L - base < 64u ? L - base : 64u) - (i - base);
+        if (lit && d.run < n) n = d.run;
+        const uint32_t k = base + lane - i;                  // the lane's byte is the k-th from here, if k < n
+        const uint8_t *src = lit ? T.lit + sid + k : T.classes + (size_t)d.cls * 256u + byte;
+        const uint32_t want = lit ? byte : (uint32_t)CLS_STAY;
+        uint32_t x = want;
+        if (k < n) x = *src;
+        asm volatile("" ::: "memory");                       // (the descriptors behind the bytes, so that a walk that stays does not wait for them)
+        const uint32_t sa = !lit ? d.next_a : n == d.run ? d.cls : sid + n;            // d.cls: state after the Write
+        const uint32_t next = two_states(T, sa, lit ? sa : d.next_b);
+        const unsigned long long off = __ballot(x != want);
+        if (lit) {
+            if (off) return false;
+            sid = sa; d = state_of(next, 0u); aux = 0; i += n;
+            continue;
+        }
+        const uint32_t stays = off ? (uint32_t)__builtin_ctzll(off) - (i - base) : n;
+        if (d.max != WG_UNBOUNDED && stays) {                // each stay needs budget left
+            if (aux >= d.max || stays > d.max - aux) return false;
+            aux += stays;
+        }
+        i += stays;
+        if (!off) continue;
+        const uint32_t left = of_lane(x, (uint32_t)__builtin_ctzll(off));
+        if (left == CLS_REJECT) return false;
+        const bool to_b = left != CLS_EXIT_A;
+        sid = to_b ? d.next_b : d.next_a;
+        d = state_of(next, to_b ? 8u : 0u);
+        aux = 0; i++;
+    }
+    return true;
+}
+// d: the descriptor of sid, at the call and after it.
+__device__ __forceinline__ void advance_one(const TableView &T, const VocabView &Vc, const CacheView &Cc,
+                                            uint32_t &sid, uint32_t &aux, StateDesc &d, int32_t t, bool count_error)
+{
+    // (the token's length and bytes are requested with the descriptor)
+    const bool is_token = t >= 0 && (uint32_t)t < Vc.V;
+    const uint32_t tok = is_token ? (uint32_t)t : 0u;
+    const uint32_t len = Vc.len8[tok], byte = token_byte(Vc, tok, threadIdx.x & 63u);
+    d = state_of(two_states(T, sid, sid), 0u);
+    bool ok = is_token && sid < T.n_states;
     if (ok) {
-        // (both chunks are requested with the length, not after it)
-        const uint32_t L = Vc.len8[t];
-        TokenBytes tk;
-        tk.chunks = Vc.chunks + t; tk.stride = Vc.V; tk.q = 0; tk.n = Vc.n_chunks;
-        tk.w0 = tk.chunks[0];
-        tk.w1 = tk.n > 1u ? tk.chunks[tk.stride] : 0ull;
-        if ((int64_t)Vc.eos_id == t) {
-            sid = v.d.eos_next; aux = 0;
+        if (Vc.eos_id == t) {
+            sid = d.eos_next; aux = 0;
             ok = sid != WG_SID_ERROR;
-            v = visit(T, sid);
-        } else ok = L != 0u && walk_ahead(T, sid, aux, v, tk, L);
+            d = state_of(two_states(T, sid, sid), 0u);
+        } else {
+            const uint32_t L = of_first(len);
+            ok = L != 0u && walk_wide(T, Vc, sid, aux, d, tok, byte, L);
+        }
     }
     if (!ok) {
         sid = WG_SID_ERROR; aux = 0;
-        if (count_error) atomicAdd(&Cc.ctr->errors, 1ull);
+        if (count_error && (threadIdx.x & 63u) == 0u) atomicAdd(&Cc.ctr->errors, 1ull);
     }
 }
 
-__device__ __forceinline__ StateDesc descriptor(const DeviceTable &T, uint32_t sid) { return T.states[sid < T.n_states ? sid : 0u]; }
-
-// One thread per request, 4 requests to a wavefront: the paths of the requests of a wavefront are
-// walked one after the other, each step a trip to memory (the lookup with an advance before it, B = 256:
-// 7.5 us with 64, 6.2 with 4).  With one to a wavefront the lookup of a cached step of 300 requests is 0.4 us faster,
-// that of a made one up to 1 us slower: more wavefronts claim on the same tags.  The advance alone claims nothing and
-// takes one as long as that fills no more than two wavefronts a unit (launch_advance): with 4 / with 1, B = 64 4.23 / 3.92 us, 256 4.45 /
-// 4.18, 512 4.26 / 4.16, 1024 4.60 / 4.78, 8192 5.6 / 7.7.
-constexpr uint32_t kLookupThreads = 4;
-__global__ void __launch_bounds__(64)
-advance_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
-               const int32_t *__restrict__ tokens, uint32_t B)
+// One request to a workgroup up to two on a compute unit, four above: with one / with four, mixed, us, B = 64 3.17 / 3.32, 256
+// 3.20 / 3.38, 512 3.40 / 3.48, 1024 3.49 / 3.62, 8192 5.58 / 5.22.
+constexpr uint32_t kAdvanceBlocks = 1u << 20;
+__global__ void __launch_bounds__(256)
+advance_kernel(WG_EARLY_ARGS)
 {
-    uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    uint32_t sid = states[b].sid, aux = states[b].aux;
-    const int32_t t = tokens[b];
-    Visit v = visit(T, sid);
-    advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, true);
-    states[b].sid = sid; states[b].aux = aux;
+    WG_VIEWS;
+    const uint32_t waves = late.shares, B = late.rows;       // (requests of a workgroup here)
+    // (wg_advance takes any number of requests: more than the grid holds come in turn)
+    for (uint64_t b = (uint64_t)blockIdx.x * waves + of_first(threadIdx.x >> 6); b < B; b += (uint64_t)gridDim.x * waves) {
+        uint32_t sid = of_first(states[b].sid), aux = of_first(states[b].aux);
+        StateDesc d;
+        advance_one(T, Vc, Cc, sid, aux, d, (int32_t)of_first((uint32_t)tokens[b]), true);
+        if ((threadIdx.x & 63u) == 0u) states[b] = wg_state_t{sid, aux};
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -246,13 +331,13 @@ struct Found {
 struct Claim { unsigned long long key_tag, class_tag; uint32_t key, cls; };      // tags as the lookup found them
 
 // What a call writes into the tags it claims, but for the request; `launch` is ctr->launch.
-__device__ __forceinline__ unsigned long long tag_now(const DeviceCache &Cc, unsigned long long launch)
+__device__ __forceinline__ unsigned long long tag_now(const CacheView &Cc, unsigned long long launch)
 {
     return (unsigned long long)Cc.epoch << kTagEpochShift | (launch & kTagLaunchMask) << kTagRequestBits;
 }
 
 // The key of the state (sid, aux), d its descriptor; kNoKey: no such state.
-__device__ __forceinline__ uint32_t key_of(const DeviceTable &T, uint32_t sid, uint32_t aux, const StateDesc &d, uint32_t &variant)
+__device__ __forceinline__ uint32_t key_of(const TableView &T, uint32_t sid, uint32_t aux, const StateDesc &d, uint32_t &variant)
 {
     variant = 0;
     if ((d.kind_byte & 0xFFu) == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
@@ -262,28 +347,42 @@ __device__ __forceinline__ uint32_t key_of(const DeviceTable &T, uint32_t sid, u
     return sid < T.n_states ? d.key_base + variant : kNoKey;
 }
 
-// The lookup of request b in state (sid, aux), d its descriptor.  kShares: by every workgroup of its row, with the
+// What a lookup reads of the state with the descriptor d: the key's tag and, although only a missing key needs them, the two
+// successors' descriptors and the tag of the class table, requested together so that nothing waits for them before the
+// tag has decided.
+struct Asked {
+    uint32_t key, variant, slot;
+    unsigned long long tag, class_tag;
+    uint32_t next;               // as two_states leaves them
+};
+__device__ __forceinline__ Asked ask(const TableView &T, const CacheView &Cc, uint32_t sid, uint32_t aux, const StateDesc &d)
+{
+    Asked q{};
+    q.key = key_of(T, sid, aux, d, q.variant);
+    if (q.key == kNoKey) return q;
+    q.tag = __hip_atomic_load(&Cc.tags[q.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.class_tag = __hip_atomic_load(&Cc.class_tags[is_checkpoint(d.kind_byte & 0xFFu) ? d.cls : 0u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.next = two_states(T, d.next_a, d.next_b);
+    q.slot = q.key;
+    if (!Cc.direct) q.slot = Cc.slots[q.key];
+    return q;
+}
+__device__ __forceinline__ unsigned long long of_first(unsigned long long x) { return (unsigned long long)of_first((uint32_t)(x >> 32)) << 32 | of_first((uint32_t)x); }
+
+// The lookup of request b in state sid, d its descriptor.  kShares: by every workgroup of its row, with the
 // arena addressed by key, and claimed by nobody: see Claim.
 template <bool kShares>
-__device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache &Cc, unsigned long long now, uint32_t b,
-                                         uint32_t sid, uint32_t aux, const StateDesc &d, Claim *claim)
+__device__ __forceinline__ Found look_up(const TableView &T, const CacheView &Cc, unsigned long long now, uint32_t b,
+                                         uint32_t sid, const StateDesc &d, const Asked &q, Claim *claim)
 {
     Found f{};
     f.ref = kNoKey;
-    uint32_t variant;
-    f.key = key_of(T, sid, aux, d, variant);
+    f.key = q.key;
     if (f.key == kNoKey) return f;
-    const unsigned long long mine = now | b;
-    const uint32_t kind = d.kind_byte & 0xFFu;
-    const bool ckpt = kind == WG_KIND_WAIT || kind == WG_KIND_COND;
-    const unsigned long long t = __hip_atomic_load(&Cc.tags[f.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t slot = Cc.direct ? f.key : Cc.slots[f.key];
-    // Requested right behind the key's tag, although only a missing key needs them: the two
-    // successors' descriptors and the tag of the class table.  Plain loads from clamped indexes, so
-    // that nothing waits for them before the tag has decided.
-    const StateDesc da = descriptor(T, d.next_a), db = descriptor(T, d.next_b);
-    const uint32_t cls = ckpt ? d.cls : 0u;
-    const unsigned long long ct = __hip_atomic_load(&Cc.class_tags[cls], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long mine = now | b, t = of_first(q.tag), ct = of_first(q.class_tag);
+    const uint32_t kind = d.kind_byte & 0xFFu, cls = is_checkpoint(kind) ? d.cls : 0u, slot = of_first(q.slot);
+    const bool leads = (threadIdx.x & 63u) == 0u;
+    const bool ckpt = is_checkpoint(kind);
     // (a slot is only read where the tag is of this generation and an earlier call: it does not
     // change after that call, so the two loads need no order)
     const bool made = (uint32_t)(t >> kTagEpochShift) == Cc.epoch;
@@ -299,80 +398,86 @@ __device__ __forceinline__ Found look_up(const DeviceTable &T, const DeviceCache
         claim->key = f.key; claim->key_tag = t;
         claim->cls = class_state == CLASS_OWN ? cls : kNoKey; claim->class_tag = ct;
     } else {
-    unsigned long long is = t;
-    if (!this_call) {
-        is = atomicCAS(&Cc.tags[f.key], t, mine);
-        f.claimed = is == t;
-    }
-    f.keep = f.claimed || is == mine;
-    if (f.keep && ckpt && class_state != CLASS_READY) {
-        unsigned long long cis = ct;
-        if (!class_this_call) {
-            cis = atomicCAS(&Cc.class_tags[cls], ct, mine);
-            f.class_claimed = cis == ct;
+        unsigned long long is = t;
+        if (!this_call) {
+            if (leads) is = atomicCAS(&Cc.tags[f.key], t, mine);
+            is = of_first(is);
+            f.claimed = is == t;
         }
-        if (f.class_claimed || cis == mine) class_state = CLASS_OWN;
-    }
+        f.keep = f.claimed || is == mine;
+        if (f.keep && ckpt && class_state != CLASS_READY) {
+            unsigned long long cis = ct;
+            if (!class_this_call) {
+                if (leads) cis = atomicCAS(&Cc.class_tags[cls], ct, mine);
+                cis = of_first(cis);
+                f.class_claimed = cis == ct;
+            }
+            if (f.class_claimed || cis == mine) class_state = CLASS_OWN;
+        }
     }
     auto hop = [&](uint32_t nt, const StateDesc &n) {
         if (nt >= T.n_states) return HopState{0xFFu, 0u, WG_SID_ERROR, WG_SID_ERROR, WG_UNBOUNDED, 0u};
         const bool lit = (n.kind_byte & 0xFFu) == WG_KIND_LIT;
         return HopState{n.kind_byte & 0xFFu, (n.kind_byte >> 8) & 0xFFu, lit ? nt : n.next_a, n.next_b, lit ? n.run : n.max, n.cls};
     };
-    f.me = RowTask{sid, kind, (d.kind_byte >> 8) & 0xFFu, d.cls, d.run, T.lmax - variant, class_state, d.eos_next,
-                   f.keep && Cc.direct ? f.key : kNoSlot, {hop(d.next_a, da), hop(d.next_b, db)}};
+    f.me = RowTask{sid, kind, (d.kind_byte >> 8) & 0xFFu, d.cls, d.run, T.lmax - q.variant, class_state, d.eos_next,
+                   f.keep && Cc.direct ? f.key : kNoSlot, {hop(d.next_a, state_of(q.next, 0u)), hop(d.next_b, state_of(q.next, 8u))}};
     return f;
 }
 
-// One thread per request.  With tokens the states are advanced first.
-__global__ void __launch_bounds__(64)
-lookup_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, wg_state_t *__restrict__ states,
-              const int32_t *__restrict__ tokens, uint32_t B)
+// A wavefront per request, four of them to a workgroup (with 1 / 4 / 16, mixed, us, found and claimed: B = 300 4.1 / 4.2 / 5.1 and 7.3 /
+// 7.4 / 9.1, B = 1024 5.2 / 5.2 / 5.8 and 13.8 / 13.2 / 15.4; with a thread per request and four to a wavefront 5.4 and 7.7,
+// 6.6 and 16.5).  With tokens the states are advanced first.
+constexpr uint32_t kLookupWaves = 4;
+__global__ void __launch_bounds__(64 * kLookupWaves)
+lookup_kernel(WG_EARLY_ARGS)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63u;
+    WG_VIEWS;
+    const uint32_t B = late.rows;
+    __shared__ uint32_t claims[kLookupWaves], first_claim;
+    const uint32_t wave = of_first(threadIdx.x >> 6), b = blockIdx.x * kLookupWaves + wave;
+    const bool leads = (threadIdx.x & 63u) == 0u;
     const unsigned long long sc = Cc.ctr->slot_ctr, launch = Cc.ctr->launch;
-    const uint32_t rows0 = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;      // rows in use before this call
     Found f{};
     f.ref = kNoKey;
     if (b < B) {
-        uint32_t sid = states[b].sid, aux = states[b].aux;
-        const int32_t t = tokens ? tokens[b] : 0;
-        Visit v = visit(T, sid);
+        uint32_t sid = of_first(states[b].sid), aux = of_first(states[b].aux);
+        StateDesc d;
         if (tokens) {
-            advance_one(T, Vc, Cc, sid, aux, v, (int64_t)t, true);
-            states[b].sid = sid; states[b].aux = aux;
-        }
-        f = look_up<false>(T, Cc, tag_now(Cc, launch), b, sid, aux, v.d, nullptr);
+            advance_one(T, Vc, Cc, sid, aux, d, (int32_t)of_first((uint32_t)tokens[b]), true);
+            if (leads) states[b] = wg_state_t{sid, aux};
+        } else d = state_of(two_states(T, sid, sid), 0u);
+        f = look_up<false>(T, Cc, tag_now(Cc, of_first(launch)), b, sid, d, ask(T, Cc, sid, aux, d), nullptr);
     }
-    // the claimers of a wavefront take their arena rows together
-    const unsigned long long cm = __ballot(f.claimed), km = __ballot(f.class_claimed);
     // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread, and the claims too
     // where nothing is handed out by their number)
-    unsigned long long *count = &Cc.spread[(blockIdx.x % kSpread) * kSpreadStride];
-    if (cm && Cc.direct) {
-        if (lane == 0) {
-            atomicAdd(&count[kSpreadBuilds], (unsigned long long)__popcll(cm));
-            if (km) atomicAdd(&count[kSpreadClasses], (unsigned long long)__popcll(km));
+    unsigned long long *count = &Cc.ctr->spread[(b % kSpread) * kSpreadStride];
+    if (leads && f.hit) atomicAdd(&count[kSpreadHits], 1ull);
+    if (Cc.direct) {
+        if (leads && f.claimed) atomicAdd(&count[kSpreadBuilds], 1ull);
+        if (leads && f.class_claimed) atomicAdd(&count[kSpreadClasses], 1ull);
+    } else {
+        // the claimers of a workgroup take their arena rows together
+        if (leads) claims[wave] = (uint32_t)f.claimed | (uint32_t)f.class_claimed << 16;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+        for (uint32_t w = 0; w < kLookupWaves; w++) { if (w < wave) before += claims[w]; all += claims[w]; }
+        if (threadIdx.x == 0) {
+            if (all & 0xFFFFu) first_claim = atomicAdd(&Cc.ctr->n_claims, all & 0xFFFFu);
+            if (all >> 16) atomicAdd(&Cc.ctr->n_class_claims, all >> 16);
         }
-    } else if (cm) {
-        uint32_t first = 0;
-        if (lane == 0) {
-            first = atomicAdd(&Cc.ctr->n_claims, (uint32_t)__popcll(cm));
-            if (km) atomicAdd(&Cc.ctr->n_class_claims, (uint32_t)__popcll(km));
-        }
-        first = __shfl(first, 0);
+        __syncthreads();
         if (f.claimed) {
-            const uint32_t idx = rows0 + first + (uint32_t)__popcll(cm & ((1ull << lane) - 1ull));
+            const uint32_t rows0 = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;      // rows in use before this call
+            const uint32_t idx = rows0 + first_claim + (before & 0xFFFFu);
             f.me.slot = idx < Cc.cap_rows ? (Cc.free_rows ? Cc.free_rows[idx] : idx) : kNoSlot;
-            Cc.slots[f.key] = f.me.slot;
+            if (leads) Cc.slots[f.key] = f.me.slot;
         }
     }
-    if (b < B) {
+    if (b < B && leads) {
         Cc.row_ref[b] = f.ref;
         if (f.ref == kRefBuild) Cc.tasks[b] = f.me;
     }
-    const unsigned long long hv = __ballot(f.hit);
-    if (lane == 0 && hv) atomicAdd(&count[kSpreadHits], (unsigned long long)__popcll(hv));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -551,7 +656,7 @@ struct RowShared {
     RowTask task;                              // what the row's lookup left; two kernels: its successors only
     uint32_t ref;
     wg_state_t state;                          // the request's, advanced
-    StateDesc desc;
+    StateDesc desc;                            // of its state
     Claim claim;
     unsigned long long launch;
 };
@@ -568,11 +673,9 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x)
     return x;
 }
 
-__device__ __forceinline__ bool is_checkpoint(uint32_t kind) { return kind == WG_KIND_WAIT || kind == WG_KIND_COND; }
-
 // Walks bytes [i, L), i < L, of a token from a literal state with `run` bytes to go, its first 24 in
 // `lit` (LDS), then the state table from the state `after` them.
-__device__ __forceinline__ bool walk_run(const DeviceTable &T, const uint64_t *lit, uint32_t sid, uint32_t run, uint32_t after,
+__device__ __forceinline__ bool walk_run(const TableView &T, const uint64_t *lit, uint32_t sid, uint32_t run, uint32_t after,
                                          TokenBytes &t, uint32_t i, uint32_t L)
 {
     const uint32_t n = L - i < run ? L - i : run;
@@ -590,7 +693,7 @@ __device__ __forceinline__ bool walk_run(const DeviceTable &T, const uint64_t *l
 
 // Walks bytes [i, L), i < L, of a token from the staged successor; goes on through the state table
 // when the token moves on to a third state.
-__device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h, const uint8_t *lut, const uint64_t *lit,
+__device__ __forceinline__ bool walk_hop(const TableView &T, const HopState &h, const uint8_t *lut, const uint64_t *lit,
                                          TokenBytes &t, uint32_t i, uint32_t L)
 {
     uint32_t sid = WG_SID_ERROR, aux = 0;
@@ -616,10 +719,10 @@ __device__ __forceinline__ bool walk_hop(const DeviceTable &T, const HopState &h
 
 // First token of range p (as the vocabulary's index is made; computed, because an array in a kernel
 // argument is not indexed in registers).
-__host__ __device__ __forceinline__ uint32_t range_token(const DeviceVocab &Vc, uint32_t p)
+__host__ __device__ __forceinline__ uint32_t range_token(uint32_t V, uint32_t p)
 {
-    const uint32_t groups = (Vc.V + kPartGroup - 1u) / kPartGroup, t = p * groups / kParts * kPartGroup;
-    return p >= kParts || t > Vc.V ? Vc.V : t;
+    const uint32_t groups = (V + kPartGroup - 1u) / kPartGroup, t = p * groups / kParts * kPartGroup;
+    return p >= kParts || t > V ? V : t;
 }
 
 __device__ __forceinline__ uint4 operator|(const uint4 &a, const uint4 &b) { return uint4{a.x | b.x, a.y | b.y, a.z | b.z, a.w | b.w}; }
@@ -627,7 +730,7 @@ __device__ __forceinline__ uint4 operator&(const uint4 &a, const uint4 &b) { ret
 __device__ __forceinline__ uint4 operator~(const uint4 &a) { return uint4{~a.x, ~a.y, ~a.z, ~a.w}; }
 
 // Brings a class table and its plan to LDS; one wavefront.
-__device__ __forceinline__ void stage_class(const DeviceTable &T, RowShared &sh, uint32_t cls, uint32_t lane)
+__device__ __forceinline__ void stage_class(const TableView &T, RowShared &sh, uint32_t cls, uint32_t lane)
 {
     static_assert(sizeof(ClassPlan) % 16 == 0 && sizeof(ClassPlan) / 16 <= 64, "a piece per lane");
     const uint32_t t = reinterpret_cast<const uint32_t *>(T.classes + (size_t)cls * 256u)[lane];
@@ -638,27 +741,43 @@ __device__ __forceinline__ void stage_class(const DeviceTable &T, RowShared &sh,
 }
 
 // Enters a row's claims (see Claim).
-__device__ __forceinline__ void claim_tags(const DeviceCache &Cc, const RowShared &sh, uint32_t b)
+__device__ __forceinline__ void claim_tags(const CacheView &Cc, const RowShared &sh, uint32_t b)
 {
     const unsigned long long now = tag_now(Cc, sh.launch), mine = now | b;
     const Claim c = sh.claim;
     unsigned long long key_was = ~c.key_tag, class_was = ~c.class_tag;
     if ((c.key_tag >> kTagRequestBits) != (now >> kTagRequestBits)) key_was = atomicCAS(&Cc.tags[c.key], c.key_tag, mine);
     if (c.cls != kNoKey && (c.class_tag >> kTagRequestBits) != (now >> kTagRequestBits)) class_was = atomicCAS(&Cc.class_tags[c.cls], c.class_tag, mine);
-    unsigned long long *count = Cc.spread + (b % kSpread) * kSpreadStride;
+    unsigned long long *count = Cc.ctr->spread + (b % kSpread) * kSpreadStride;
     if (key_was == c.key_tag) atomicAdd(&count[kSpreadBuilds], 1ull);
     if (class_was == c.class_tag) atomicAdd(&count[kSpreadClasses], 1ull);
 }
 
+// A row's workgroups that have read its state are counted, the last of a row counts in its group of rows, the last of a
+// group in the call: who closes a row or the call is known by the ticket it took.  (With 256 rows on one address the die
+// whose workgroups took them, one of the eight, had its loads up to 2.5 us later than the others: the last row of a
+// cached fill, V = 151936, was out 8.6 us after the kernel's beginning, of a made one 15.7, in groups 7.0 and 14.0.)
+struct Tickets {
+    uint32_t group, call;        // as taken (of rows and of groups before), or kNoTicket
+    bool row_last;
+};
+constexpr uint32_t kNoTicket = 0xFFFFFFFFu;
+__device__ __forceinline__ uint32_t *group_counter(const CacheView &Cc, uint32_t b) { return &Cc.ctr->group_tickets[b / kTicketGroup * kTicketStride]; }
+__device__ __forceinline__ bool group_last(const Tickets &t, uint32_t b, uint32_t rows)
+{
+    const uint32_t first = b / kTicketGroup * kTicketGroup;
+    return t.group + 1u == (rows - first < kTicketGroup ? rows - first : kTicketGroup);
+}
+
 // The words [w_lo, w_hi) of a missing row are row[] | early[] (LDS, word 0 = w_lo): early holds what
 // the candidates add, row the rest, so that the two are made side by side.
-__device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc, RowShared &sh,
+__device__ __forceinline__ void make_row(const TableView &T, const VocabView &Vc, const CacheView &Cc, RowShared &sh,
                                          const RowTask &me, const HopState &ha, const HopState &hb, uint32_t p0, uint32_t span,
                                          uint32_t w_lo, uint32_t w_hi, uint32_t *row, uint32_t *early, uint32_t b, bool claims)
 {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t n_words = w_hi - w_lo, rs = Cc.row_stride;
-    const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
+    const uint32_t tok_lo = range_token(Vc.V, p0), tok_hi = range_token(Vc.V, p0 + span);
     const bool literal = me.kind == WG_KIND_LIT, ckpt = is_checkpoint(me.kind);
     const bool ckpt_a = is_checkpoint(ha.kind), ckpt_b = is_checkpoint(hb.kind);
     // the literal byte behind an exit, or a value no byte has
@@ -716,7 +835,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
         if (lane < 48u) reinterpret_cast<uint8_t *>(sh.run[side])[at] = (uint8_t)byte;
         if (lane == 0) {
             sh.n_ranges = n; sh.total = total;
-            if (p0 == 0u && sure + total) atomicAdd(&Cc.spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)(sure + total));
+            if (p0 == 0u && sure + total) atomicAdd(&Cc.ctr->spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)(sure + total));
             if (Vc.eos_id >= 0 && me.eos_next != WG_SID_ERROR) {
                 const uint32_t ew = (uint32_t)Vc.eos_id >> 5;
                 if (ew >= w_lo && ew < w_hi) early[ew - w_lo] |= 1u << ((uint32_t)Vc.eos_id & 31u);
@@ -858,7 +977,7 @@ __device__ __forceinline__ void make_row(const DeviceTable &T, const DeviceVocab
 
 // The call is over for the cache once its lookups are: one thread then counts the claimed rows as used
 // and opens the next call.
-__device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, uint32_t n, uint32_t n_classes)
+__device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint32_t n, uint32_t n_classes)
 {
     const unsigned long long sc = Cc.ctr->slot_ctr;
     const uint32_t used = (uint32_t)(sc >> 32) == Cc.epoch ? (uint32_t)sc : 0u;
@@ -881,60 +1000,64 @@ __device__ __forceinline__ void close_fill(const DeviceCache &Cc, uint32_t B, ui
 // that 8 workgroups of a unit are resident: with 7 the last 256 of 2,048 began 7 to 11 us after the others.
 template <typename Elem, int kMode, bool kWhole>
 __global__ void __launch_bounds__(kRowThreads, 8)
-rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict__ bitmask, Elem *__restrict__ logits,
-            int64_t logits_stride, wg_state_t *__restrict__ states, const int32_t *__restrict__ tokens)
+rows_kernel(WG_EARLY_ARGS)
 {
+    WG_VIEWS;
     extern __shared__ __attribute__((aligned(16))) uint32_t row[];
     __shared__ __attribute__((aligned(16))) RowShared sh;
-    const uint32_t b = blockIdx.y, tid = threadIdx.x, span = kParts / gridDim.x, p0 = blockIdx.x * span;
-    const uint32_t tok_lo = range_token(Vc, p0), tok_hi = range_token(Vc, p0 + span);
+    const uint32_t b = blockIdx.y, tid = threadIdx.x, span = late.span, p0 = blockIdx.x * span;
+    const uint32_t tok_lo = range_token(Vc.V, p0), tok_hi = range_token(Vc.V, p0 + span);
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
     const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
     uint4 *row4 = reinterpret_cast<uint4 *>(row), *early4 = row4 + n4 + 1u;
-    uint32_t ticket = 0, rows_done = 0;
+    Tickets ticket{kNoTicket, kNoTicket, false};
     uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
     if (kWhole) {
-        wg_state_t st{};
-        int32_t t = 0;
-        if (tid == 0) {
+        const uint32_t wave = of_first(tid >> 6);
+        uint32_t sid = 0, aux = 0, t = 0;
+        StateDesc d{};
+        Asked asked{};
+        if (wave == 0u) {
             const unsigned long long launch = Cc.ctr->launch;
-            st = states[b];
-            if (tokens) t = tokens[b];
-            sh.launch = launch;
-            sh.state = st;
+            const wg_state_t st = states[b];
+            if (tokens) t = of_first((uint32_t)tokens[b]);
+            // (in one wait with them: the call's number, and a word of each line of the arguments, so that whoever reads
+            // them later does not wait for memory)
+            asm volatile("" :: "s"(launch), "s"(late.T.lit), "s"(late.Vc.rows), "s"(late.Cc.tags), "s"(late.Cc.tasks), "s"(late.rows));
+            sid = of_first(st.sid); aux = of_first(st.aux);
+            if (tid == 0) sh.launch = launch;
         }
         __syncthreads();
         if (tid == kRowThreads - 64u) {
-            ticket = atomicAdd(&Cc.tickets[b * kTicketStride], 1u);
-            if (ticket == gridDim.x - 1u) rows_done = atomicAdd(Cc.rows_ticket, 1u);
+            ticket.row_last = atomicAdd(&Cc.ctr->tickets[b * kTicketStride], 1u) == late.shares - 1u;
+            if (ticket.row_last) ticket.group = atomicAdd(group_counter(Cc, b), 1u);       // (waited for behind the walk)
         }
-        if (tid == 0) {
-            Visit v = visit(T, st.sid);
-            if (tokens) {
-                advance_one(T, Vc, Cc, st.sid, st.aux, v, (int64_t)t, p0 == 0u);
-                sh.state = st;
+        if (wave == 0u) {
+            if (tokens) advance_one(T, Vc, Cc, sid, aux, d, (int32_t)t, p0 == 0u);
+            else d = state_of(two_states(T, sid, sid), 0u);
+            asked = ask(T, Cc, sid, aux, d);
+            if (tid == 0) {
+                sh.state = wg_state_t{sid, aux};
+                sh.ref = asked.key;
+                sh.desc = d;
             }
-            uint32_t variant;
-            sh.ref = key_of(T, st.sid, st.aux, v.d, variant);
-            sh.desc = v.d;
-        }
+        } else if (wave >= 2u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
         __syncthreads();
-        // (key k has arena row k: the row is requested while its tag is looked at)
-        const uint32_t key = sh.ref;
-        if (tid >= 128u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
+        // (key k has arena row k: the row is requested while its tag is looked at, and what a missing row takes from the
+        // state's own class table)
+        const uint32_t key = of_first(sh.ref);
         if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
-        __syncthreads();
-        // (and what a missing row takes from the state's own class table)
-        if (tid >> 6 == 1u && is_checkpoint(sh.desc.kind_byte & 0xFFu)) stage_class(T, sh, (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.desc.cls), tid & 63u);
-        if (tid == 0) {
-            const StateDesc d = sh.desc;
-            const Found f = look_up<true>(T, Cc, tag_now(Cc, sh.launch), b, sh.state.sid, sh.state.aux, d, &sh.claim);
-            sh.ref = f.ref;
-            if (f.ref == kRefBuild) sh.task = f.me;
-            unsigned long long *count = Cc.spread + (b % kSpread) * kSpreadStride;
-            if (f.hit && p0 == 0u) atomicAdd(&count[kSpreadHits], 1ull);
+        if (wave == 1u && is_checkpoint(of_first(sh.desc.kind_byte) & 0xFFu)) stage_class(T, sh, of_first(sh.desc.cls), tid & 63u);
+        if (wave == 0u) {
+            const Found f = look_up<true>(T, Cc, tag_now(Cc, of_first(sh.launch)), b, sid, d, asked, &sh.claim);
+            if (tid == 0) {
+                sh.ref = f.ref;
+                if (f.ref == kRefBuild) sh.task = f.me;
+                if (f.hit && p0 == 0u) atomicAdd(&Cc.ctr->spread[(b % kSpread) * kSpreadStride + kSpreadHits], 1ull);
+            }
         }
         __syncthreads();
+        if (late.rows > kTicketGroup && group_last(ticket, b, late.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
     }
     const RowTask in = kWhole ? sh.task : Cc.tasks[b];   // (requested with the reference; only used where that asks for it)
     const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kWhole ? sh.ref : Cc.row_ref[b]));
@@ -957,7 +1080,7 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     // out: to the cache, the caller's bitmask, and LDS for the masking
     const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
     uint4 *kept = reinterpret_cast<uint4 *>(Cc.arena + (size_t)slot * rs + w_lo);
-    uint32_t *dst = bitmask + (size_t)b * Vc.W + w_lo;
+    uint32_t *dst = late.bitmask + (size_t)b * Vc.W + w_lo;
     const bool aligned = reinterpret_cast<uintptr_t>(dst) % 16u == 0u;
     for (uint32_t q = tid; q < n4; q += kRowThreads) {
         uint4 x{0u, 0u, 0u, 0u};
@@ -976,20 +1099,22 @@ rows_kernel(DeviceTable T, DeviceVocab Vc, DeviceCache Cc, uint32_t *__restrict_
     }
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
-    if (kMode == 1) mask_span<Elem>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
-    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(logits + (int64_t)b * logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 1) mask_span<Elem>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
     if (kWhole) {
-        if (tid == kRowThreads - 64u && ticket == gridDim.x - 1u) {
-            Cc.tickets[b * kTicketStride] = 0u;
+        if (ticket.row_last) {
+            Cc.ctr->tickets[b * kTicketStride] = 0u;
             if (tokens) states[b] = sh.state;
-            if (rows_done == gridDim.y - 1u) {
-                *Cc.rows_ticket = 0u;
-                Cc.ctr->lookups += gridDim.y;
+            const bool last = group_last(ticket, b, late.rows);
+            if (last) *group_counter(Cc, b) = 0u;
+            if (late.rows > kTicketGroup ? ticket.call + 1u == (late.rows + kTicketGroup - 1u) / kTicketGroup : last) {
+                Cc.ctr->call_ticket = 0u;
+                atomicAdd(&Cc.ctr->lookups, (unsigned long long)late.rows);       // (nobody waits for it)
                 Cc.ctr->launch = sh.launch + 1ull;
             }
         }
     } else if (blockIdx.x == 0 && b == 0 && tid == 0) {
-        close_fill(Cc, gridDim.y, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
+        close_fill(Cc, late.rows, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
         Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
     }
 }
@@ -1219,7 +1344,7 @@ static uint32_t rows_lds(const DeviceVocab &Vc, uint32_t parts)
     const uint32_t span = kParts / parts;
     uint32_t most = 0;
     for (uint32_t p = 0; p < kParts; p += span) {
-        const uint32_t n = ((range_token(Vc, p + span) + 31u) >> 5) - (range_token(Vc, p) >> 5);
+        const uint32_t n = ((range_token(Vc.V, p + span) + 31u) >> 5) - (range_token(Vc.V, p) >> 5);
         most = n > most ? n : most;
     }
     return 2u * (((most + 3u) & ~3u) + 4u) * 4u;
@@ -1251,9 +1376,11 @@ FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, boo
     // and 1.12 1.09 1.03, B = 192 0.92 0.94 1.01 and 0.97 1.00 0.85).  With logits to mask behind them the workgroups
     // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.94 0.96
     // 1.00 and 0.95 0.95 0.96); whole lines are masked behind a lookup of its own.
-    p.one_kernel = Cc.direct && B <= n_cu && (masks_logits ? !p.lines : B * p.parts <= resident_rows(Vc, p.parts) * n_cu);
+    p.one_kernel = Cc.direct && B <= n_cu && B <= kOneKernelRows && (masks_logits ? !p.lines : B * p.parts <= resident_rows(Vc, p.parts) * n_cu);
     return p;
 }
+
+#define WG_EARLY_VALUES states, tokens, Cc.ctr, T.states, Vc.chunks, Vc.len8, T.n_states, Vc.V
 
 hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,
                        wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t *bitmask,
@@ -1263,19 +1390,15 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
     const dim3 g(plan.parts, B);
     const uint32_t lds = rows_lds(Vc, plan.parts);
     const bool whole = plan.one_kernel;
+    const LateArgs late{T, Vc, Cc, bitmask, logits, logits_stride, kParts / plan.parts, plan.parts, B};
     if (!whole) {
-        const hipError_t e = launch(lookup_kernel, dim3(cdiv(B, kLookupThreads)), dim3(kLookupThreads), 0, s, lookup_ev, T, Vc, Cc, states, tokens, B);
+        const hipError_t e = launch(lookup_kernel, dim3(cdiv(B, kLookupWaves)), dim3(64 * kLookupWaves), 0, s, lookup_ev, WG_EARLY_VALUES, late);
         if (e != hipSuccess) return e;
     }
-    auto rows = [&](auto kernel, auto *x) { return launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, T, Vc, Cc, bitmask, x, logits_stride, states, tokens); };
-    if (!logits) return whole ? rows(rows_kernel<uint16_t, 0, true>, (uint16_t *)nullptr) : rows(rows_kernel<uint16_t, 0, false>, (uint16_t *)nullptr);
-    const bool lines = plan.lines;
-    if (dtype == WG_F32) {
-        uint32_t *x = static_cast<uint32_t *>(logits);
-        return whole ? rows(rows_kernel<uint32_t, 1, true>, x) : lines ? rows(rows_kernel<uint32_t, 2, false>, x) : rows(rows_kernel<uint32_t, 1, false>, x);
-    }
-    uint16_t *x = static_cast<uint16_t *>(logits);
-    return whole ? rows(rows_kernel<uint16_t, 1, true>, x) : lines ? rows(rows_kernel<uint16_t, 2, false>, x) : rows(rows_kernel<uint16_t, 1, false>, x);
+    auto rows = [&](auto kernel) { return launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, WG_EARLY_VALUES, late); };
+    if (!logits) return whole ? rows(rows_kernel<uint16_t, 0, true>) : rows(rows_kernel<uint16_t, 0, false>);
+    if (dtype == WG_F32) return whole ? rows(rows_kernel<uint32_t, 1, true>) : plan.lines ? rows(rows_kernel<uint32_t, 2, false>) : rows(rows_kernel<uint32_t, 1, false>);
+    return whole ? rows(rows_kernel<uint16_t, 1, true>) : plan.lines ? rows(rows_kernel<uint16_t, 2, false>) : rows(rows_kernel<uint16_t, 1, false>);
 }
 
 // New states and classes from pinned host memory to the ends of the device tables, all slices by one
@@ -1330,8 +1453,8 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
                           wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t n_cu, hipStream_t s,
                           hipEvent_t *ev)
 {
-    const uint32_t threads = B <= 2u * n_cu ? 1u : kLookupThreads;
-    return launch(advance_kernel, dim3(cdiv(B, threads)), dim3(threads), 0, s, ev, T, Vc, Cc, states, tokens, B);
+    const uint32_t waves = B <= 2u * n_cu ? 1u : 4u, blocks = cdiv(B, waves);
+    return launch(advance_kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, ev, WG_EARLY_VALUES, LateArgs{T, Vc, Cc, nullptr, nullptr, 0, 0u, waves, B});
 }
 
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,

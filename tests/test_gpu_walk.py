@@ -1,0 +1,119 @@
+"""GPU parity of the walk of a token by a wavefront, a byte per lane: tokens as long as the wavefront, a byte less, a byte
+more and of three of its windows, ended by every kind of state and budget; and of how a call of one kernel counts its
+rows (groups of 16)."""
+import numpy as np
+import pytest
+
+import wg_synth as ws
+from oracle import oracle as O
+from tests import helpers as H
+from wg_synth.vocab import from_tokens
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2507_16768_amd as wg
+    wg.load_library()
+    return torch
+
+
+_RUN = bytes(c for c in range(0x61, 0x7B)) * 6                      # 156 bytes
+_TEXTS = ['Sequence(Write("%s"), Wait(denies={}, wait={<}, max=130), Write("c>"))' % _RUN.decode(),
+          'Sequence(Wait(denies={}, wait={<}, max=64), Write("%s"))' % _RUN[:70].decode(),
+          'DoWhile(body=Sequence(Wait(denies={9}, wait={<}), Write("%s")), condition=Wait(allow={\\x20}, true_waits={\\x2C}, '
+          'false_waits={\\x5D}))' % _RUN[:63].decode()]
+
+
+def _tokens():
+    out = [b""] + [bytes([c]) for c in b"abcxyz<>9 ,]"]
+    for n in (1, 7, 8, 9, 24, 25, 62, 63, 64, 65, 66, 127, 128, 129, 130, 131, 193):
+        text, run = b"a" * n, (_RUN + b"x" * 60)[:n]
+        out += [text, run, text[:-1] + b"<", text[:-1] + b"9", run[:-1] + b"!", b"x" + run[:-1],
+                (b"xy<" + _RUN)[:n], (text + b"<" + _RUN)[:n + 5], (b"b" * 61 + b"<" + _RUN)[:n + 2], (b"<" + _RUN[:63] + b"  ,aa<")[:n + 6]]
+    return list(dict.fromkeys(out))
+
+
+@pytest.mark.parametrize("restart", [False, True])
+def test_tokens_as_long_as_a_wavefront_and_longer(torch_cuda, restart):
+    """Every state and budget with every token: through wg_advance (a request and four requests to a workgroup) and through
+    the fill that advances in its one kernel and behind a lookup kernel."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    toks = _tokens()
+    vocab = from_tokens(toks, eos_id=0)
+    o = O.Oracle(_TEXTS, None, O.OracleVocab(vocab.bytes, vocab.offsets, vocab.eos_id), restart=restart)
+    h = wg.Handle(_TEXTS, None, wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART if restart else wg.EOS_STOP)
+    h.reserve_batch(1024)
+    st = [[O.SID_ERROR, 0]]
+    for sid in range(o.num_states):
+        d = o.describe(sid)
+        st += [[sid, a] for a in (sorted({0, 1, d["max"] // 2, d["max"] - 1, d["max"], d["max"] + 1}) if d["kind"] == "WAIT" and d["max"] >= 0 else (0,))]
+    st = np.array(st, dtype=np.uint32)
+    rep, tk = np.repeat(st, vocab.V, axis=0), np.tile(np.arange(vocab.V, dtype=np.int32), len(st))
+    want = o.advance(rep, tk)
+    assert np.sum(want[:, 0] != O.SID_ERROR) >= 900
+    got = H.dev_states(rep)
+    h.advance(got, torch.from_numpy(tk).cuda())
+    assert (H.host_states(got) == want).all()
+    pick = np.random.default_rng(5).permutation(len(rep))
+    pick = np.concatenate([pick[want[pick, 0] != O.SID_ERROR][:900], pick[:150]])
+    for B in (256, 500, 300):
+        for k in range(0, len(pick) - B + 1, B):
+            p = pick[k:k + B]
+            a, b = H.dev_states(rep[p]), H.dev_states(rep[p])
+            mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+            t = torch.from_numpy(tk[p]).cuda()
+            h.advance(a, t)
+            h.advance_fill_masks(b, t, mask)
+            assert (H.host_states(a) == want[p]).all() and torch.equal(a, b), (B, k)
+            assert (H.host_mask(mask) == o.fill_masks(want[p])).all(), (B, k)
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33, 255, 256])
+def test_calls_of_one_kernel_count_their_rows(torch_cuda, B):
+    """Each call's states are written back, its lookups counted and its claims told from the next call's, whatever rows the
+    last group holds."""
+    torch = torch_cuda
+    w = ws.make_workload(4, V=5003, B=B, steps=6)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    cur = H.start_states(o, w)
+    st = H.dev_states(cur)
+    mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+    draws = w.token_draws()
+    lookups = 0
+    for k in range(6):
+        h.fill_masks(st, mask)                             # (made, from the second call of a step on found)
+        made = h.cache_stats()
+        want = o.fill_masks(cur)
+        assert (H.host_mask(mask) == want).all(), k
+        t = np.array([O.select_bit(r, int(draws[k][b]) % int(np.unpackbits(r.view(np.uint8)).sum())) for b, r in enumerate(want)], dtype=np.int32)
+        cur = o.advance(cur, t)
+        h.fill_masks(st, mask)
+        found = h.cache_stats()
+        assert found["builds"] == made["builds"] and found["hits"] == made["hits"] + B, k
+        h.advance_fill_masks(st, torch.from_numpy(t).cuda(), mask)
+        assert (H.host_states(st) == cur).all() and (H.host_mask(mask) == o.fill_masks(cur)).all(), k
+        lookups += 3 * B
+        assert h.cache_stats()["lookups"] == lookups, k
+        if k == 3:
+            h.cache_clear()
+    assert h.error_count() == 0
+
+
+def test_advance_of_more_requests_than_the_grid_holds(torch_cuda):
+    torch = torch_cuda
+    w = ws.make_workload(2, V=2003, B=8, steps=1)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    st = H.start_states(o, w)
+    few = np.arange(16, dtype=np.int32) + 60
+    want = o.advance(np.repeat(st[:1], 16, axis=0), few)
+    B = (4 << 20) + 21
+    big = torch.from_numpy(st[:1].view(np.int32).copy()).cuda().repeat(B, 1)
+    h.advance(big, (torch.arange(B, device="cuda", dtype=torch.int32) % 16 + 60))
+    assert torch.equal(big, torch.from_numpy(want.view(np.int32)).cuda().repeat(B // 16 + 1, 1)[:B])
