@@ -769,6 +769,27 @@ __device__ __forceinline__ bool group_last(const Tickets &t, uint32_t b, uint32_
     return t.group + 1u == (rows - first < kTicketGroup ? rows - first : kTicketGroup);
 }
 
+// What the last of a row and the last of the call do, once all of them have read the row's state and the call's number: on the
+// way, since the kernel's end would wait for these stores (a pass of 8 cached steps, 1 request 39.7 -> 37.8 us, 64
+// requests 61.0 -> 59.4).
+__device__ __forceinline__ void close_row(const CacheView &Cc, const Tickets &t, uint32_t b, wg_state_t *states, const int32_t *tokens, const RowShared &sh)
+{
+    if (!t.row_last) return;
+    Cc.ctr->tickets[b * kTicketStride] = 0u;
+    if (tokens) states[b] = sh.state;
+}
+__device__ __forceinline__ void close_call(const CacheView &Cc, const Tickets &t, uint32_t b, uint32_t rows, const RowShared &sh)
+{
+    if (!t.row_last) return;
+    const bool last = group_last(t, b, rows);
+    if (last) *group_counter(Cc, b) = 0u;
+    if (rows > kTicketGroup ? t.call + 1u == (rows + kTicketGroup - 1u) / kTicketGroup : last) {
+        Cc.ctr->call_ticket = 0u;
+        atomicAdd(&Cc.ctr->lookups, (unsigned long long)rows);       // (nobody waits for it)
+        Cc.ctr->launch = sh.launch + 1ull;
+    }
+}
+
 // The words [w_lo, w_hi) of a missing row are row[] | early[] (LDS, word 0 = w_lo): early holds what
 // the candidates add, row the rest, so that the two are made side by side.
 __device__ __forceinline__ void make_row(const TableView &T, const VocabView &Vc, const CacheView &Cc, RowShared &sh,
@@ -1047,6 +1068,7 @@ rows_kernel(WG_EARLY_ARGS)
         // state's own class table)
         const uint32_t key = of_first(sh.ref);
         if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
+        if (late.rows > kTicketGroup && group_last(ticket, b, late.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
         if (wave == 1u && is_checkpoint(of_first(sh.desc.kind_byte) & 0xFFu)) stage_class(T, sh, of_first(sh.desc.cls), tid & 63u);
         if (wave == 0u) {
             const Found f = look_up<true>(T, Cc, tag_now(Cc, of_first(sh.launch)), b, sid, d, asked, &sh.claim);
@@ -1057,7 +1079,7 @@ rows_kernel(WG_EARLY_ARGS)
             }
         }
         __syncthreads();
-        if (late.rows > kTicketGroup && group_last(ticket, b, late.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
+        close_row(Cc, ticket, b, states, tokens, sh);
     }
     const RowTask in = kWhole ? sh.task : Cc.tasks[b];   // (requested with the reference; only used where that asks for it)
     const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kWhole ? sh.ref : Cc.row_ref[b]));
@@ -1097,23 +1119,12 @@ rows_kernel(WG_EARLY_ARGS)
         }
         if (kMode || !aligned) row4[q] = x;
     }
+    if (kWhole) close_call(Cc, ticket, b, late.rows, sh);
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
     if (kMode == 1) mask_span<Elem>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
     if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
-    if (kWhole) {
-        if (ticket.row_last) {
-            Cc.ctr->tickets[b * kTicketStride] = 0u;
-            if (tokens) states[b] = sh.state;
-            const bool last = group_last(ticket, b, late.rows);
-            if (last) *group_counter(Cc, b) = 0u;
-            if (late.rows > kTicketGroup ? ticket.call + 1u == (late.rows + kTicketGroup - 1u) / kTicketGroup : last) {
-                Cc.ctr->call_ticket = 0u;
-                atomicAdd(&Cc.ctr->lookups, (unsigned long long)late.rows);       // (nobody waits for it)
-                Cc.ctr->launch = sh.launch + 1ull;
-            }
-        }
-    } else if (blockIdx.x == 0 && b == 0 && tid == 0) {
+    if (!kWhole && blockIdx.x == 0 && b == 0 && tid == 0) {
         close_fill(Cc, late.rows, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
         Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
     }
