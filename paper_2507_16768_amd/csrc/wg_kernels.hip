@@ -498,7 +498,8 @@ lookup_kernel(WG_EARLY_ARGS)
 //
 // Lanes first ... first + kChunk - 1 hold the mask bits of 64 tokens each in lo and hi, the first of them at p.
 constexpr uint32_t kChunk = 8u;
-template <typename Elem>
+// kThrough: the stores go through the die's L2 (masks_through).
+template <typename Elem, bool kThrough>
 __device__ __forceinline__ void mask_chunk(Elem *p, uint32_t lo, uint32_t hi, uint32_t first)
 {
     constexpr Elem kNinf = sizeof(Elem) == 4 ? (Elem)0xFF800000u : (Elem)0xFF80u;
@@ -513,7 +514,10 @@ __device__ __forceinline__ void mask_chunk(Elem *p, uint32_t lo, uint32_t hi, ui
                (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(first + u));
 #pragma unroll
     for (uint32_t u = 0; u < kChunk; u++)
-        if (__builtin_amdgcn_inverse_ballot_w64(m[u])) p[u * 64u + lane] = kNinf;
+        if (__builtin_amdgcn_inverse_ballot_w64(m[u])) {
+            if (kThrough) __hip_atomic_store(&p[u * 64u + lane], kNinf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else p[u * 64u + lane] = kNinf;
+        }
 }
 // Word w of the `words` that hold a row's V tokens; what lies behind the last token counts as allowed.
 __device__ __forceinline__ uint32_t word_or_ones(const uint32_t *row, uint32_t w, uint32_t words, uint32_t V)
@@ -522,19 +526,41 @@ __device__ __forceinline__ uint32_t word_or_ones(const uint32_t *row, uint32_t w
     if (w + 1u == words && (V & 31u)) x |= ~0u << (V & 31u);
     return x;
 }
+// Tokens that the first of a row lies behind a 128-byte line's beginning (0 where elements do not lie at multiples of their size).
+// Chunks are cut at the lines, so that a store covers one line and not parts of two, of which stores that go through the L2
+// (masks_through) would each cost a whole one: cut at the row's beginning / at lines, outlines, mixed, random trees, V = 100003,
+// bf16, B = 96, us, wg_apply_mask 4.4 4.8 6.3 / 4.0 4.3 5.1 (4.8 5.1 6.1 cut at the beginning and not through the L2).
+template <typename Elem>
+__device__ __forceinline__ uint32_t skew_of(const Elem *first)
+{
+    const uintptr_t at = reinterpret_cast<uintptr_t>(first);
+    return at % sizeof(Elem) ? 0u : (uint32_t)(at % 128u / sizeof(Elem));
+}
+// The mask bits of the 64 tokens from 64 * i - skew on; what lies in front of the first token counts as allowed too.
+__device__ __forceinline__ void bits_of_chunk(const uint32_t *row, uint32_t i, uint32_t words, uint32_t V, uint32_t skew, uint32_t &a, uint32_t &b)
+{
+    const uint32_t w = 2u * i - (skew >> 5), r = skew & 31u;         // (below 0: beyond the words)
+    a = word_or_ones(row, w, words, V);
+    b = word_or_ones(row, w + 1u, words, V);
+    if (r) {
+        b = __builtin_amdgcn_alignbit(b, a, 32u - r);
+        a = __builtin_amdgcn_alignbit(a, word_or_ones(row, w - 1u, words, V), 32u - r);
+    }
+}
 // The whole workgroup masks the tokens [lo, hi) of a row; `row` is in LDS, its bit 0 is token lo.  The wavefronts
 // take chunks in turn, so that all of them write close together (a quarter of the share each was 3 to 8 % slower).
-template <typename Elem>
+template <typename Elem, bool kThrough>
 __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t V = hi - lo, words = (V + 31u) >> 5, pairs = (words + 1u) >> 1, step = (blockDim.x >> 6) * kChunk;
+    const uint32_t V = hi - lo, words = (V + 31u) >> 5, skew = skew_of(logits + lo), pairs = (V + skew + 63u) >> 6, step = (blockDim.x >> 6) * kChunk;
+    Elem *p = logits + lo - skew;
     for (uint32_t i0 = wave * kChunk; i0 < pairs; i0 += step * (64u / kChunk)) {
-        const uint32_t w = 2u * (i0 + lane / kChunk * step + lane % kChunk);      // a lane per pair of words, eight chunks at a time
-        const uint32_t a = word_or_ones(row, w, words, V), b = word_or_ones(row, w + 1u, words, V);
+        uint32_t a, b;                                              // a lane per chunk of 64 tokens, eight stretches of kChunk at a time
+        bits_of_chunk(row, i0 + lane / kChunk * step + lane % kChunk, words, V, skew, a, b);
         if (!__ballot((a & b) != 0xFFFFFFFFu)) continue;            // a step in text without an end: 12.4 -> 9.0 us
         for (uint32_t c = 0; c < 64u / kChunk && i0 + c * step < pairs; c++)
-            mask_chunk<Elem>(logits + lo + (size_t)(i0 + c * step) * 64u, a, b, c * kChunk);
+            mask_chunk<Elem, kThrough>(p + (size_t)(i0 + c * step) * 64u, a, b, c * kChunk);
     }
 }
 
@@ -1011,7 +1037,8 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
     Cc.ctr->launch++;
 }
 
-// kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_lines).
+// kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_lines); 3: as 1, the stores
+// through the L2.
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
 // before it (tokens may be null).  One launch instead of two, and a row waits for its own lookup only, not for
 // the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket: the last
@@ -1122,7 +1149,7 @@ rows_kernel(WG_EARLY_ARGS)
     if (kWhole) close_call(Cc, ticket, b, late.rows, sh);
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
-    if (kMode == 1) mask_span<Elem>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 1 || kMode == 3) mask_span<Elem, kMode == 3>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
     if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
     if (!kWhole && blockIdx.x == 0 && b == 0 && tid == 0) {
         close_fill(Cc, late.rows, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
@@ -1187,7 +1214,7 @@ __global__ void __launch_bounds__(256) count_rows_kernel(DeviceCache Cc)
 // the gain ends at 1.5 %; with 2 the free text of html and JSON (V = 128256, 3 %) is listed too, in 9.9 instead of 9.7 and 10.5
 // instead of 10.2 us, B = 256.
 constexpr uint64_t kApplyLarge = 96ull << 20;
-template <typename Elem, uint32_t kPairs>
+template <typename Elem, uint32_t kPairs, bool kThrough>
 __global__ void __launch_bounds__(256)
 apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W, const uint32_t *__restrict__ bitmask)
 {
@@ -1198,13 +1225,11 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
     const uint32_t b = blockIdx.y, lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t first = (blockIdx.x * 4u + wave) * kPairs;
     const uint32_t *row = bitmask + (size_t)b * W;
-    const uint32_t w = 2u * (first + lane);
+    Elem *p = logits + (int64_t)b * row_stride;
+    const uint32_t skew = skew_of(p);
     uint32_t lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu;
-    if (lane < kPairs) {
-        lo = word_or_ones(row, w, W, V);
-        hi = word_or_ones(row, w + 1u, W, V);
-    }
-    Elem *p = logits + (int64_t)b * row_stride + (size_t)first * 64u;
+    if (lane < kPairs) bits_of_chunk(row, first + lane, W, V, skew, lo, hi);
+    p += (int64_t)first * 64 - skew;
     const uint32_t off = (uint32_t)(__popc(~lo) + __popc(~hi)), upto = wave_prefix_sum(off);
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
     if (n <= kFew) {
@@ -1216,7 +1241,7 @@ apply_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t
         return;
     }
 #pragma unroll
-    for (uint32_t c = 0; c < kPairs; c += kChunk) mask_chunk<Elem>(p + (size_t)c * 64u, lo, hi, c);
+    for (uint32_t c = 0; c < kPairs; c += kChunk) mask_chunk<Elem, kThrough>(p + (size_t)c * 64u, lo, hi, c);
 }
 
 // The same by whole lines: a workgroup takes kLineTokens tokens of a row.
@@ -1319,6 +1344,19 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
     return dtype == WG_F32 ? n * 4u > kLineBytes32 : n * 2u > kLineBytes16;
 }
 
+// Where the logits are not masked by whole lines, a store goes through the die's L2 (sc1) as long as the buffers that an engine
+// has in turn stay in the last-level cache: the end of the kernel then does not wait for the L2 to write back what it
+// holds.  40 MiB: six such buffers fit the 256 MB.  us, into the L2 / through it, outlines, mixed, random trees, bf16, V =
+// 151936: B = 64, two buffers in turn, wg_apply_mask 4.7 5.0 5.6 / 3.9 4.4 5.0, a cached wg_decode_step 7.4 7.8 8.1 / 6.8 7.0
+// 7.4; six in turn, the step with B = 128 (39 MB) 9.2 9.8 11.4 / 8.7 9.2 10.7, 160 (49 MB) 10.5 11.5 15.5 / 11.0 12.0 15.5, 256
+// (78 MB) 23.1 32.3 34.2 / 24.0 32.4 35.1.  (Two in turn gain up to 120 MB: 256 13.7 15.0 17.8 / 13.1 14.4 17.2.)
+constexpr uint64_t kThroughBytes = 40ull << 20;
+static bool masks_through(const void *logits, int dtype, uint32_t B, uint32_t V)
+{
+    const uint32_t e = dtype == WG_F32 ? 4u : 2u;
+    return logits && reinterpret_cast<uintptr_t>(logits) % e == 0u && (uint64_t)B * V * e <= kThroughBytes;
+}
+
 // Workgroups per row (it is cut at its token ranges).  8, which with long rows of 256 requests is as many as are
 // resident together (8 to a unit); more where that leaves compute units idle, as long as a workgroup keeps enough
 // tokens to be worth what it starts with: 4,096 up to 4 workgroups on a unit, 6,144 up to 7.  Geometric means over the
@@ -1407,9 +1445,14 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
         if (e != hipSuccess) return e;
     }
     auto rows = [&](auto kernel) { return launch(kernel, g, dim3(kRowThreads), lds, s, rows_ev, WG_EARLY_VALUES, late); };
+    auto of_type = [&](auto elem) {
+        using E = decltype(elem);
+        if (plan.lines) return rows(rows_kernel<E, 2, false>);
+        if (masks_through(logits, dtype, B, Vc.V)) return whole ? rows(rows_kernel<E, 3, true>) : rows(rows_kernel<E, 3, false>);
+        return whole ? rows(rows_kernel<E, 1, true>) : rows(rows_kernel<E, 1, false>);
+    };
     if (!logits) return whole ? rows(rows_kernel<uint16_t, 0, true>) : rows(rows_kernel<uint16_t, 0, false>);
-    if (dtype == WG_F32) return whole ? rows(rows_kernel<uint32_t, 1, true>) : plan.lines ? rows(rows_kernel<uint32_t, 2, false>) : rows(rows_kernel<uint32_t, 1, false>);
-    return whole ? rows(rows_kernel<uint16_t, 1, true>) : plan.lines ? rows(rows_kernel<uint16_t, 2, false>) : rows(rows_kernel<uint16_t, 1, false>);
+    return dtype == WG_F32 ? of_type(uint32_t{}) : of_type(uint16_t{});
 }
 
 // New states and classes from pinned host memory to the ends of the device tables, all slices by one
@@ -1449,15 +1492,26 @@ hipError_t launch_apply(void *logits, int dtype, uint32_t B, uint32_t V, int64_t
                         const uint32_t *bitmask, hipStream_t s, hipEvent_t *ev)
 {
     const uint32_t W = (V + 31u) / 32u;
-    auto apply = [&](auto kernel, auto *x, uint32_t tokens) { return launch(kernel, dim3(cdiv(V, tokens), B), dim3(256), 0, s, ev, x, row_stride, V, W, bitmask); };
-    const bool lines = by_lines(dtype, B, V);
+    if (by_lines(dtype, B, V)) {
+        const dim3 g(cdiv(V, kLineTokens), B);
+        if (dtype == WG_F32) return launch(apply_lines_kernel<uint32_t>, g, dim3(256), 0, s, ev, static_cast<uint32_t *>(logits), row_stride, V, W, bitmask);
+        return launch(apply_lines_kernel<uint16_t>, g, dim3(256), 0, s, ev, static_cast<uint16_t *>(logits), row_stride, V, W, bitmask);
+    }
+    // (a row that begins inside a line has up to 63 tokens more to its chunks)
+    const uint32_t e = dtype == WG_F32 ? 4u : 2u;
+    const bool at_lines = reinterpret_cast<uintptr_t>(logits) % 128u == 0u && (B == 1u || (uint64_t)row_stride * e % 128u == 0u);
+    auto apply = [&](auto kernel, auto *x, uint32_t tokens) {
+        return launch(kernel, dim3(cdiv((uint64_t)V + (at_lines ? 0u : 63u), tokens), B), dim3(256), 0, s, ev, x, row_stride, V, W, bitmask);
+    };
+    const bool through = masks_through(logits, dtype, B, V);
+    constexpr uint32_t kMany = 4u * 64u * 32u, kFewer = 4u * 64u * 24u;
     if (dtype == WG_F32) {
         uint32_t *x = static_cast<uint32_t *>(logits);
-        return lines ? apply(apply_lines_kernel<uint32_t>, x, kLineTokens) : apply(apply_kernel<uint32_t, 32u>, x, 4u * 64u * 32u);
+        return through ? apply(apply_kernel<uint32_t, 32u, true>, x, kMany) : apply(apply_kernel<uint32_t, 32u, false>, x, kMany);
     }
     uint16_t *x = static_cast<uint16_t *>(logits);
-    if (lines) return apply(apply_lines_kernel<uint16_t>, x, kLineTokens);
-    return (uint64_t)B * V * 2u > kApplyLarge ? apply(apply_kernel<uint16_t, 24u>, x, 4u * 64u * 24u) : apply(apply_kernel<uint16_t, 32u>, x, 4u * 64u * 32u);
+    if (through) return apply(apply_kernel<uint16_t, 32u, true>, x, kMany);
+    return (uint64_t)B * V * 2u > kApplyLarge ? apply(apply_kernel<uint16_t, 24u, false>, x, kFewer) : apply(apply_kernel<uint16_t, 32u, false>, x, kMany);
 }
 
 hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCache &Cc,

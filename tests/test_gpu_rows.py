@@ -103,6 +103,36 @@ def test_masking_at_every_alignment(torch_cuda, V, dtype):
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
 
 
+@pytest.mark.parametrize("dtype,V,B", [("bf16", 100003, 209), ("bf16", 100003, 210), ("bf16", 99904, 210), ("f32", 41003, 255), ("f32", 41003, 256), ("f32", 20011, 524), ("f32", 20011, 525)])
+def test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B):
+    """40 MiB of logits: rows at lines and inside them, by themselves and from the rows' kernel (one kernel and two)."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
+    w = ws.make_workload(4, V=V, B=B, steps=2)
+    o = H.make_oracle(w)
+    v, h = H.make_gpu(w)
+    cur = H.start_states(o, w)
+    st = H.dev_states(cur)
+    mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    noise = torch.randint(-2 ** 31, 2 ** 31, (B, h.W), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    if V % 32:
+        noise[:, -1] &= (1 << (V % 32)) - 1
+    for off, pad in ((0, 0), (5, 0), (64, 61)):
+        buf = torch.randn((B * (V + pad) + 128,), generator=g, device="cuda").to(dt)
+        for m in (None, noise):
+            x = buf[off:off + B * (V + pad)].view(B, V + pad)[:, :V]
+            want = buf.clone()
+            if m is None:
+                h.decode_step(st, None, mask, x)
+                assert (H.host_mask(mask[:3]) == o.fill_masks(cur[:3])).all()
+            else:
+                wg.apply_mask(x, m)
+            want[off:off + B * (V + pad)].view(B, V + pad)[:, :V].masked_fill_(~_unpack(torch, mask if m is None else m, V), float("-inf"))
+            assert torch.equal(buf.view(bits), want.view(bits)), (off, pad, m is None)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V", [257, 2049, 16385, 40003, 131073])
 def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
