@@ -1364,10 +1364,14 @@ static bool masks_through(const void *logits, int dtype, uint32_t B, uint32_t V)
 //   V = 151936 B = 64 0.90 0.94, 96 0.95 0.98, 112 0.93 0.98, 128 0.96 1.01; 100003 B = 64 0.93 0.96, 96 0.94 1.00, 112 1.00
 //   1.00, 128 1.03 1.02; 65536 B = 24 0.93 0.96, 64 0.95 0.99, 96 1.01 1.01; with 32 / with 16, 151936 B = 16 0.96 0.97, 32 0.96
 //   0.99, 48 1.03 1.02; mixed, us with 8 / 16 / 32, 151936 B = 1 11.3 / 9.7 / 8.8 and 8.3 / 6.8 / 6.0
-// Fewer where a short row would be cut into scraps: with 8 / 4, V = 20000 B = 256 18.1 / 16.3 and 11.7 / 10.7, B =
-// 1024 49.9 / 37.4 and 22.2 / 18.0, V = 24576 B = 33 10.8 / 11.4 and 6.7 / 6.9, V = 32000 B = 256 19.3 / 18.7 and 12.6
-// / 12.0, B = 1024 51.5 / 40.3 and 23.1 / 21.6 (random trees 57.8 / 48.1 and 26.8 / 32.0); with 4 / 2, V = 12000 B = 64
-// 11.1 / 11.5 and 6.9 / 7.1, B = 1024 36.4 / 29.6 and 16.1 / 15.3.
+// Up to a workgroup per unit as many as a row has groups (kPartGroup): with 16 or 32 / with 8, made rows, 8000 (4 / 2) B = 64 0.93, 20000
+// B = 8 0.97, 32000 B = 1 0.95, 50257 B = 6 0.94, 90000 B = 4 0.97; copied ones are a launch either way.
+// Fewer where a short row would be cut into scraps: with 4 / 2, V = 12000 B = 64 11.1 / 11.5 and 6.9 / 7.1.  Above a request per unit a share
+// pays for what it starts with only with 12,288 tokens, once there are more than eight workgroups to a unit.  wg_decode_step on outlines,
+// mixed, random trees, time to that of 3,072 tokens, rows made and rows copied: B = 400 V = 24576 0.79 0.91, 32000 0.85 0.95, 50257 0.90 0.98,
+// 65536 0.92 0.99, 90000 0.91 1.00; B = 800 16000 0.86 0.96, 32000 (44 us made, 18 copied) 0.73 0.87, 50257 0.83 0.93, 90000 0.91 0.99; B = 2048
+// 8000 0.84 0.96, 32000 0.64 0.83, 65536 0.97 1.03, 90000 0.96 0.99; with 4 / 8, 100003 B = 400 0.96 1.00, 1000 1.01 1.00 (random trees later),
+// 151936 B = 1000 1.06 1.02.
 // Fewer too where the lookup that each repeats is most of a short share's work: up to a request per unit and more than
 // seven workgroups on one (above, rows are looked up once).  With 8 / 4, B = 256, kernel us of wg_decode_step on outlines, JSON,
 // mixed, random trees: copied V = 24576 9.3 9.5 9.7 9.5 / 9.0 9.0 9.3 9.3 (a lookup kernel and 8 shares: 9.3 10.0 9.8 12.1), 32768 10.8
@@ -1379,12 +1383,14 @@ static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
     uint32_t parts = kLeastParts;
     while (parts < kParts) {
         const uint64_t n = (uint64_t)B * parts * 2u;
-        if (n > 7ull * n_cu || parts * 2u * (n <= 4ull * n_cu ? 4096u : 6144u) > V) break;
+        if (n > 7ull * n_cu || parts * 2u * (n <= n_cu ? kPartGroup / 2u : n <= 4ull * n_cu ? 4096u : 6144u) > V) break;
         parts *= 2u;
     }
     if (parts == kLeastParts && B <= n_cu && B * parts > 7u * n_cu && V <= parts * 4096u) parts >>= 1;
-    const uint32_t least = B > n_cu ? 3072u : (uint64_t)B * parts > n_cu ? 2560u : kPartGroup;
-    while (parts > 1u && parts * least > V) parts >>= 1;
+    for (; parts > 1u; parts >>= 1) {
+        const uint64_t n = (uint64_t)B * parts;
+        if (parts * (B > n_cu ? (n > 8ull * n_cu ? 12288u : 3072u) : n > n_cu ? 2560u : kPartGroup / 2u) <= V) break;
+    }
     return parts;
 }
 

@@ -252,6 +252,12 @@ def test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B):
     assert h.error_count() == 0 and n["lookups"] == 4 * B and n["hits"] + n["builds"] <= 4 * B
 
 
+@pytest.mark.parametrize("V,B", [(16384, 16), (16385, 16), (16385, 17), (32768, 8), (32769, 9), (8192, 64), (8192, 65), (4096, 128), (98303, 257), (98304, 257), (49151, 512), (49151, 513), (49152, 513), (24575, 1024)])
+def test_decode_step_at_the_edges_of_few_and_of_many_rows(torch_cuda, V, B):
+    """Up to a workgroup per compute unit, and above a request per unit either side of eight workgroups to one."""
+    test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B)
+
+
 @pytest.mark.parametrize("V,B", [(12001, 1), (20011, 31), (30000, 129), (98304, 96), (151936, 64), (20011, 255), (20011, 256), (20011, 257), (40000, 256)])
 def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
     """Every workgroup of a row looks it up by itself up to a request per compute unit, and several make
