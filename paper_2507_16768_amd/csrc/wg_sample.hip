@@ -3,17 +3,17 @@
 //
 // A workgroup of 1,024 threads takes a row.  The row's mask goes to LDS; every thread then keeps the
 // largest allowed logit of its 16-byte pieces and where it was.  From 256 rows on that is HBM bound,
-// and nothing has to be merged.  One compute unit streams only about 30 GB/s however much it has in
-// flight (a 304 KB row takes 10 us), so smaller batches cut their rows: the greedy choice into as
-// many workgroups as there are compute units, merged by the last of them to finish; the k best of
+// and nothing has to be merged.  Smaller batches cut their rows: the greedy choice into as
+// many workgroups as there are compute units, merged in pairs; the k best of
 // long rows into slices of 8,192 tokens, merged by a second kernel.  The greedy choice from long fp32 rows is
 // made from such slices too (argmax_slice_kernel): a row of 600 KB per workgroup left compute units
 // idle whenever the rows did not come out even.
 //
-// Times for V = 151,936, bf16, every token allowed, the greedy choice and k = 50: B = 1 5.7 and 11.6 us, B = 64 9.1
-// and 18.3, B = 256 18.9 and 26.5, B = 1,024 62.9 (5.0 TB/s, a copy's rate) and 86.3.  Greedy choice with the best
-// piece kept instead of its number 19.7 -> 18.9 (B = 256), the k best by row with keys made from the loaded pieces
-// instead of reloaded ones 96.1 -> 86.3 (B = 1,024).
+// The loads of logits and mask go through buffer descriptors: what is not wanted lies behind the buffer's end and costs no
+// branch, and the loads count by themselves.  (As flat loads behind a branch for rows at odd addresses each was waited for before
+// the next was issued, and the mask came in five trips, one after the other.)  Times of the greedy choice and of k = 50, us, so / now, bf16, every
+// token allowed: V = 128,256 B = 64 8.7 16.5 / 7.6 13.3; 151,936 B = 128 11.6 19.8 / 10.4 15.5, B = 256 18.5 26.1 / 15.9 (5.0 TB/s,
+// near a copy's rate) 19.8, B = 1,000 61.9 86.1 / 53.7 59.6; under the masks of 256 requests, half outlines and half JSON, 16.3 21.5 / 13.6 17.2.
 //
 // The k best need no sorting of the row: in each of n wavefronts the ceil(k / n)-th largest of the 64
 // thread maxima is found by bisection on ballots, and the least of these is a lower bound for the k-th
@@ -37,6 +37,19 @@ constexpr uint32_t kSegWords = 8192;                 // mask words staged at a t
 constexpr uint32_t kCand = 1024;                     // candidates ranked in LDS
 constexpr uint32_t kNoPiece = 0xFFFFFFFFu;
 
+// Memory that is read by 16 bytes or a word at an offset, 0 from `bytes` on: a load that is not wanted goes there, without a
+// branch around it, and costs nothing.
+typedef __amdgpu_buffer_rsrc_t Window;
+__device__ __forceinline__ Window window_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000); }
+constexpr uint32_t kNowhere = 0xFFFFFFF0u;           // an offset behind every window
+__device__ __forceinline__ uint4 block_at(Window w, uint32_t at)
+{
+    typedef uint32_t Four __attribute__((ext_vector_type(4)));
+    const Four x = __builtin_amdgcn_raw_buffer_load_b128(w, at, 0, 0);
+    return uint4{x.x, x.y, x.z, x.w};
+}
+__device__ __forceinline__ uint32_t word_at(Window w, uint32_t at) { return __builtin_amdgcn_raw_buffer_load_b32(w, at, 0, 0); }
+
 // One row of logits as aligned 16-byte pieces.
 template <typename Elem>
 struct Row {
@@ -52,14 +65,15 @@ struct Row {
         const uintptr_t at = reinterpret_cast<uintptr_t>(row);
         whole = at % sizeof(Elem) == 0u;
         skew = whole ? (uint32_t)(at % 16u / sizeof(Elem)) : 0u;
-        blocks = reinterpret_cast<const uint4 *>(at - (at % 16u));
+        blocks = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(row) - at % 16u);
         pieces = (V + skew + kPer - 1u) / kPer;
     }
-    // A piece with allowed tokens m.  An aligned 16-byte block that holds a token of the row lies in
+    // n pieces from p on, of a row that is whole.  An aligned 16-byte block that holds a token of the row lies in
     // the row's own memory page, also where it begins before the row or ends behind it.
-    __device__ __forceinline__ uint4 load(uint32_t p, uint32_t m) const
+    __device__ __forceinline__ Window window(uint32_t p, uint32_t n) const { return window_of(blocks + p, n * 16u); }
+    // A piece with allowed tokens m, of a row that is not.
+    __device__ __forceinline__ uint4 gather(uint32_t p, uint32_t m) const
     {
-        if (whole) return blocks[p];
         union { uint4 v; Elem e[kPer]; } u;
         u.v = uint4{0u, 0u, 0u, 0u};
         for (uint32_t i = 0; i < kPer; i++)
@@ -79,6 +93,32 @@ __device__ __forceinline__ uint32_t mask_word(const uint32_t *mask, uint32_t W, 
     };
     const uint32_t hi = word(i);
     return skew ? (hi << skew) | ((i ? word(i - 1u) : 0u) >> (32u - skew)) : hi;
+}
+
+// The words [w0, w0 + nw) of the same, nw up to kSegWords, to LDS, and a zero behind them; all of a thread's in flight together.
+// The whole workgroup calls it.
+__device__ __forceinline__ void stage_mask(const uint32_t *mask, uint32_t W, uint32_t V, uint32_t skew, uint32_t w0, uint32_t nw, uint32_t *words)
+{
+    constexpr uint32_t kMost = kSegWords / kThreads;
+    const Window win = window_of(mask + w0, (W > w0 ? W - w0 < nw ? W - w0 : nw : 0u) * 4u);
+    const uint32_t tid = threadIdx.x, last = W - 1u - w0, tail = V & 31u ? (1u << (V & 31u)) - 1u : 0xFFFFFFFFu;
+    uint32_t x[kMost], y[kMost];
+#pragma unroll
+    for (uint32_t j = 0; j < kMost; j++) {
+        x[j] = 0u; y[j] = 0u;
+        if (j * kThreads >= nw) continue;
+        x[j] = word_at(win, (tid + j * kThreads) * 4u);
+        if (skew) y[j] = tid + j * kThreads ? word_at(win, (tid + j * kThreads - 1u) * 4u) : w0 ? mask[w0 - 1u] : 0u;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kMost; j++) {
+        const uint32_t i = tid + j * kThreads;
+        if (j * kThreads >= nw) break;
+        if (i == last) x[j] &= tail;
+        if (skew) x[j] = x[j] << skew | (i == last + 1u ? y[j] & tail : y[j]) >> (32u - skew);
+        if (i < nw) words[i] = x[j];
+    }
+    if (tid == 0) words[nw] = 0u;
 }
 
 // The allowed tokens of piece p, from the mask as it lies in memory.
@@ -117,8 +157,8 @@ __device__ __forceinline__ float piece_max(const uint4 &v, uint32_t m, uint32_t)
 }
 
 // Streams the pieces [lo, hi) of the row, lo a multiple of 32: what(p, piece, allowed tokens) for every
-// piece of the thread that has an allowed token, in ascending order.  `words` is kSegWords words of
-// LDS.  The whole workgroup calls it.
+// piece of the thread that has an allowed token, in ascending order.  `words` is kSegWords + 1
+// words of LDS.  The whole workgroup calls it.
 template <typename Elem, typename F>
 __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t *words,
                                            uint32_t lo, uint32_t hi, F what)
@@ -129,22 +169,30 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
         const uint32_t n = hi - s0 < kSegPieces ? hi - s0 : kSegPieces;
         const uint32_t w0 = s0 / (32u / kPer), nw = (n * kPer + 31u) / 32u;
         if (s0 != lo) __syncthreads();                     // the segment before is done with the LDS
-        for (uint32_t i = tid; i < nw; i += kThreads) words[i] = mask_word(mask, W, r.V, r.skew, w0 + i);
+        stage_mask(mask, W, r.V, r.skew, w0, nw, words);
         __syncthreads();
-        // two batches of three pieces, one in flight while the other is looked at (B = 256, V = 151,936,
-        // bf16: 17.1 us; one batch of eight 17.9, two of four 18.9; within the 64 registers of two workgroups
-        // on a compute unit)
+        const uint32_t none = nw * (32u / kPer);           // a piece of the zero behind the words
+        auto allowed = [&](uint32_t q) {
+            if (q > none) q = none;
+            if (kPer == 8u) return (uint32_t)reinterpret_cast<const uint8_t *>(words)[q];
+            return words[q / (32u / kPer)] >> (q * kPer & 31u) & Row<Elem>::kAll;
+        };
+        if (!r.whole) {
+            for (uint32_t q = tid; q < n; q += kThreads) {
+                const uint32_t m = allowed(q);
+                if (m) what(s0 + q, r.gather(s0 + q, m), m);
+            }
+            continue;
+        }
         constexpr uint32_t kHalf = 3u;
+        const Window win = r.window(s0, n);
         uint32_t m[2][kHalf];
         uint4 v[2][kHalf];
         auto request = [&](uint32_t (&mm)[kHalf], uint4 (&vv)[kHalf], uint32_t q0) {
 #pragma unroll
-            for (uint32_t j = 0; j < kHalf; j++) {
-                const uint32_t q = q0 + j * kThreads, bit = q * kPer;
-                mm[j] = q < n ? (words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : 0u;
-                vv[j] = uint4{0u, 0u, 0u, 0u};
-                if (mm[j]) vv[j] = r.load(s0 + q, mm[j]);
-            }
+            for (uint32_t j = 0; j < kHalf; j++) mm[j] = allowed(q0 + j * kThreads);
+#pragma unroll
+            for (uint32_t j = 0; j < kHalf; j++) vv[j] = block_at(win, mm[j] ? (q0 + j * kThreads) * 16u : kNowhere);
         };
         auto look = [&](const uint32_t (&mm)[kHalf], const uint4 (&vv)[kHalf], uint32_t q0) {
 #pragma unroll
@@ -152,6 +200,7 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
                 if (mm[j]) what(s0 + q0 + j * kThreads, vv[j], mm[j]);
         };
         request(m[0], v[0], tid);
+#pragma nounroll
         for (uint32_t q0 = tid; q0 < n; q0 += kThreads * kHalf * 2u) {
             request(m[1], v[1], q0 + kThreads * kHalf);
             look(m[0], v[0], q0);
@@ -162,21 +211,20 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
 }
 
 // ---------------------------------------------------------------------------------------------
-// masked argmax.  A row cut into several workgroups is merged through the two arrays: each workgroup
-// raises the row's key (the order key of its logit << 32 | ~id; 0: nothing allowed) and then takes
-// a ticket; the one that takes the last ticket finds the row's key complete, and leaves both zero
-// for the next call.  (Rows in slices, below, have no tickets: a second kernel takes the keys.)  One copy
-// per GPU: calls that cut their rows must not overlap on one GPU.
-constexpr uint32_t kCutRows = 256;
+// masked argmax.  The workgroups of a row that is cut into 2^n are merged in pairs, by keys (the order key of a logit
+// << 32 | ~id): each swaps its key into its pair's node; the first to come finds zero there and is done, the
+// second finds the other's key, leaves zero for the next call and goes on with the larger one.  (Rows in slices,
+// below, raise one key per row, which a second kernel takes.)  One copy per GPU: calls that cut their rows must not overlap on one GPU.
+constexpr uint32_t kCutRows = 256;                   // most workgroups of a call that cuts its rows
 __device__ unsigned long long g_argmax_key[kMaxBatch];
-__device__ uint32_t g_argmax_ticket[kCutRows];
+__device__ unsigned long long g_argmax_node[kCutRows];
 
 template <typename Elem>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
                      const uint32_t *__restrict__ bitmask, int32_t *__restrict__ tokens)
 {
-    __shared__ uint32_t words[kSegWords];
+    __shared__ uint32_t words[kSegWords + 1u];
     __shared__ float part[kWaves];
     __shared__ uint32_t best_token;
     const uint32_t b = blockIdx.y, tid = threadIdx.x;
@@ -193,8 +241,8 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     held.v = uint4{0u, 0u, 0u, 0u};
     uint32_t held_mask = 0;
     auto see = [&](uint32_t p, const uint4 &v, uint32_t m) {
-        const float x = piece_max(v, m, Elem(0));
-        if (x > best || (where == kNoPiece && x == x)) { best = x; where = p; held.v = v; held_mask = m; }
+        const float x = __builtin_fmaxf(best, piece_max(v, m, Elem(0)));
+        if (!(x == best)) { best = x; where = p; held.v = v; held_mask = m; }      // (also while there is no number)
     };
     stream_row(r, mask, W, words, lo, hi, see);
     float top = best;
@@ -218,7 +266,7 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
         }
     } else {
         // no number among the allowed tokens: the lowest of them (all NaN), if there is one
-        for (uint32_t p = lo + tid; p < hi; p += kThreads) {
+        for (uint32_t p = lo + tid; where != kNoPiece && p < hi; p += kThreads) {
             const uint32_t m = piece_mask(r, mask, W, p);
             if (m) { atomicMin(&best_token, r.token(p, (uint32_t)__builtin_ctz(m))); break; }
         }
@@ -227,14 +275,17 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     if (tid) return;
     uint32_t token = best_token;                      // all ones is -1: nothing allowed
     if (gridDim.x > 1u) {
-        const unsigned long long key = token == 0xFFFFFFFFu ? 0ull :
+        unsigned long long key = token == 0xFFFFFFFFu ? 0ull :
             (unsigned long long)(number ? order_key(__float_as_uint(top)) : 0u) << 32 | (0xFFFFFFFFu - token);
-        const unsigned long long was = atomicMax(&g_argmax_key[b], key);
-        asm volatile("" : : "v"(was) : "memory");     // the key is raised before the ticket is taken
-        if (atomicAdd(&g_argmax_ticket[b], 1u) != gridDim.x - 1u) return;
-        const unsigned long long row = atomicExch(&g_argmax_key[b], 0ull);
-        g_argmax_ticket[b] = 0u;
-        token = row ? 0xFFFFFFFFu - (uint32_t)row : 0xFFFFFFFFu;
+        key += key == 0ull;                           // (0: nobody has been here)
+        unsigned long long *node = g_argmax_node + (size_t)b * (gridDim.x - 1u);
+        for (uint32_t n = gridDim.x >> 1, i = blockIdx.x >> 1; n; node += n, n >>= 1, i >>= 1) {
+            const unsigned long long other = atomicExch(&node[i], key);
+            if (!other) return;                       // the pair's other one goes on
+            __hip_atomic_store(&node[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            key = other > key ? other : key;
+        }
+        token = key == 1ull ? 0xFFFFFFFFu : 0xFFFFFFFFu - (uint32_t)key;
     }
     tokens[b] = (int32_t)token;
 }
@@ -243,11 +294,10 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
 // together, raises the row's key and is done; a second kernel turns the keys into tokens.  Bound by HBM.
 // Against a workgroup of 1,024 threads per row (two of which fit a compute unit, so that every count of
 // rows but a multiple of 512 leaves units without work) it costs a launch and evens out rows of any number
-// and of any number of allowed tokens.  V = 151,936, everything allowed / nothing in every other row, by row
-// -> in slices, us: B = 48 10.4 -> 10.0 / 10.0 -> 8.5, B = 129 29.8 -> 18.3 / 22.8 -> 12.6, B = 256 33.4 ->
-// 31.0 / 29.8 -> 19.7, B = 300 41.9 -> 35.0 / 36.9 -> 21.9, B = 1,024 111 -> 110 / 79.8 -> 59.9; a ticket
-// in place of the second kernel kept each workgroup for two more trips to memory (B = 1,024: 167).  bf16 rows
-// are not taken so (B = 256 20.1 -> 25.1, B = 1,024 63 -> 74).
+// and of any number of allowed tokens.  V = 151,936, everything allowed / a few tokens in every other row, by row
+// -> in slices, us: B = 40 8.7 -> 8.9 / 8.3 -> 6.7, B = 64 10.4 -> 11.0 / 10.0 -> 7.8, B = 128 15.9 -> 16.6 / 12.0 -> 10.7, B = 256
+// 29.9 -> 31.2 / 20.2 -> 17.0; a ticket in place of the second kernel kept each workgroup for two more trips to memory
+// (B = 1,024 110 -> 167).  bf16 rows are not taken so (B = 256 20.1 -> 25.1, B = 1,024 63 -> 74 when by row was slower than now).
 constexpr uint32_t kChoiceThreads = 256, kChoicePieces = 8;
 constexpr uint32_t kChoiceTokens = kChoiceThreads * kChoicePieces * Row<uint32_t>::kPer;
 __global__ void __launch_bounds__(kChoiceThreads)
@@ -264,6 +314,7 @@ argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uin
     words[tid] = mask_word(bitmask + (size_t)b * W, W, V, r.skew, blockIdx.x * kWords + tid);
     if (tid == 0) best_token = 0xFFFFFFFFu;
     __syncthreads();
+    const Window win = r.window(blockIdx.x * (kChoicePieces * kChoiceThreads), kChoicePieces * kChoiceThreads);
     uint32_t m[kChoicePieces];
     union { uint4 v; uint32_t e[kPer]; } u[kChoicePieces];
 #pragma unroll
@@ -272,10 +323,8 @@ argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uin
         m[j] = (words[bit >> 5] >> (bit & 31u)) & Row<uint32_t>::kAll;
     }
 #pragma unroll
-    for (uint32_t j = 0; j < kChoicePieces; j++) {
-        u[j].v = uint4{0u, 0u, 0u, 0u};
-        if (m[j]) u[j].v = r.blocks[base + j * kChoiceThreads];  // (elements lie at multiples of their size: launch_masked_argmax)
-    }
+    for (uint32_t j = 0; j < kChoicePieces; j++)               // (elements lie at multiples of their size: launch_masked_argmax)
+        u[j].v = block_at(win, m[j] ? (j * kChoiceThreads + tid) * 16u : kNowhere);
     float best = __builtin_nanf("");
 #pragma unroll
     for (uint32_t j = 0; j < kChoicePieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], 0u));
@@ -435,7 +484,7 @@ __device__ __forceinline__ Elem logit_of(unsigned long long key, const Elem *row
 }
 
 struct TopkShared {
-    uint32_t words[kSegWords];                       // the staged mask
+    uint32_t words[kSegWords + 1u];                  // the staged mask
     union {
         unsigned long long cand[kCand];              // the candidates: rank << 32 | ~id
         uint32_t bins[256];
@@ -458,23 +507,41 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
     const Row<Elem> r(logits + (int64_t)b * row_stride, V);
     int32_t *id_out = ids + (size_t)b * k;
     Elem *value_out = values + (size_t)b * k;
-    float best = __builtin_nanf("");
-    uint32_t any = 0;                                 // the thread has an allowed token
-    stream_row(r, mask, W, sh.words, 0u, r.pieces, [&](uint32_t, const uint4 &v, uint32_t m) {
-        best = __builtin_fmaxf(best, piece_max(v, m, Elem(0)));
+    // the thread's first piece with `best`, and the most of its other pieces
+    float best = __builtin_nanf(""), second = best;
+    uint32_t any = 0, where = 0, held_mask = 0;       // any: the thread has an allowed token
+    uint4 held{0u, 0u, 0u, 0u};
+    stream_row(r, mask, W, sh.words, 0u, r.pieces, [&](uint32_t p, const uint4 &v, uint32_t m) {
+        const float x = piece_max(v, m, Elem(0)), most = __builtin_fmaxf(best, x);
+        second = __builtin_fmaxf(second, most == best ? x : best);
+        if (!(most == best)) { best = most; where = p; held = v; held_mask = m; }
         any = 1u;
     });
     const uint32_t own = best == best ? order_key(__float_as_uint(best)) + 1u : any;
     if (tid == 0) { sh.n = 0u; sh.n_threads = 0u; }
     const uint32_t bound = bound_of<kWaves>(own, k, sh.count);
-    // Candidates: the allowed tokens at or above the bound, in the pieces of the threads whose maximum
-    // is.  Those pieces are looked at again, by all threads; they fit their list unless hundreds of
-    // tokens tie at the bound or are NaN.
-    if (any && own >= bound) sh.threads[atomicAdd(&sh.n_threads, 1u)] = tid;
+    const float value = bound_value(bound);
+    auto put = [&](const uint4 &v, uint32_t p, uint32_t m) {
+        uint32_t take = reaching(v, m, bound, value, Elem(0));
+        while (take) {
+            const uint32_t i = (uint32_t)__builtin_ctz(take);
+            take &= take - 1u;
+            const uint32_t at = atomicAdd(&sh.n, 1u);
+            if (at < kCand) sh.cand[at] = key_of(r, v, p, i);
+        }
+    };
+    // Candidates: the allowed tokens at or above the bound.  Those of most threads lie in the one piece that the
+    // thread holds; the pieces of the others are looked at again, by all threads (V = 151,936, bf16, k = 50, with those of all
+    // threads looked at again / now: B = 256 20.0 / 17.2 us, B = 1,000 62.3 / 48.9).  Of up to four pieces of a thread so are all: two ways one
+    // after the other are 4 % slower there (V = 20,011, B = 700 16.5 / 17.2).  The candidates fit their list unless hundreds
+    // of tokens tie at the bound or are NaN.
+    if (any && own >= bound) {
+        if (bound == 0u || r.pieces <= 4u * kThreads || second >= value) sh.threads[atomicAdd(&sh.n_threads, 1u)] = tid;
+        else put(held, where, held_mask);
+    }
     __syncthreads();
     const uint32_t per = (r.pieces + kThreads - 1u) / kThreads, items = sh.n_threads * per;
     const bool staged = r.pieces * kPer <= kSegWords * 32u;        // the row's mask is in LDS as a whole
-    const float value = bound_value(bound);
     constexpr uint32_t kItems = sizeof(Elem) == 4u ? 1u : 2u;      // in flight together, within 64 registers
     for (uint32_t i0 = tid; i0 < items; i0 += kThreads * kItems) {
         uint4 v[kItems];
@@ -488,19 +555,11 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
             if (i < items && p[j] < r.pieces) {
                 const uint32_t bit = p[j] * kPer;
                 m[j] = staged ? (sh.words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : piece_mask(r, mask, W, p[j]);
-                if (m[j]) v[j] = r.load(p[j], m[j]);
+                if (m[j]) v[j] = r.whole ? r.blocks[p[j]] : r.gather(p[j], m[j]);
             }
         }
 #pragma unroll
-        for (uint32_t j = 0; j < kItems; j++) {
-            uint32_t take = reaching(v[j], m[j], bound, value, Elem(0));
-            while (take) {
-                const uint32_t i = (uint32_t)__builtin_ctz(take);
-                take &= take - 1u;
-                const uint32_t at = atomicAdd(&sh.n, 1u);
-                if (at < kCand) sh.cand[at] = key_of(r, v[j], p[j], i);
-            }
-        }
+        for (uint32_t j = 0; j < kItems; j++) put(v[j], p[j], m[j]);
     }
     __syncthreads();
     uint32_t n = sh.n;
@@ -619,16 +678,17 @@ topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t 
     float best = __builtin_nanf("");
     uint32_t any = m_extra;
 #pragma unroll
-    for (uint32_t j = 0; j < kPieces; j++) { u[j].v = uint4{0u, 0u, 0u, 0u}; any |= m[j]; }
-    uint4 v_extra = uint4{0u, 0u, 0u, 0u};
+    for (uint32_t j = 0; j < kPieces; j++) any |= m[j];
+    uint4 v_extra;
     if (r.whole) {
+        const Window win = r.window(base, own_pieces);
 #pragma unroll
-        for (uint32_t j = 0; j < kPieces; j++) if (m[j]) u[j].v = r.blocks[base + j * kSliceThreads + tid];
-        if (m_extra) v_extra = r.blocks[extra];
+        for (uint32_t j = 0; j < kPieces; j++) u[j].v = block_at(win, m[j] ? (j * kSliceThreads + tid) * 16u : kNowhere);
+        v_extra = block_at(win, m_extra ? (kTopkSlice / kPer + tid) * 16u : kNowhere);
     } else {
 #pragma unroll
-        for (uint32_t j = 0; j < kPieces; j++) if (m[j]) u[j].v = r.load(base + j * kSliceThreads + tid, m[j]);
-        if (m_extra) v_extra = r.load(extra, m_extra);
+        for (uint32_t j = 0; j < kPieces; j++) u[j].v = r.gather(base + j * kSliceThreads + tid, m[j]);
+        v_extra = r.gather(extra, m_extra);
     }
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], Elem(0)));
@@ -756,7 +816,8 @@ hipError_t static_topk_scratch(unsigned long long **out)
 }
 
 // Workgroups of the greedy choice per row: as many as the compute units hold one of each, at least
-// 16,384 tokens in each.
+// 16,384 tokens in each.  (Two of each, bf16, V = 151,936, mixed masks, us: B = 64 7.5 -> 8.6, B = 128 9.2 -> 10.3, B = 256 13.7 -> 14.2; four:
+// B = 256 18.2.)
 static uint32_t argmax_parts(uint32_t B, uint32_t V)
 {
     uint32_t parts = 1u;
@@ -764,29 +825,33 @@ static uint32_t argmax_parts(uint32_t B, uint32_t V)
     return parts;
 }
 
-// fp32 rows are taken in slices (argmax_slice_kernel) from 33 rows of five slices on: with four (V = 32,000)
-// B = 256 with nothing allowed in every other row is 8.3 us by row, 9.3 in slices, with five (V = 40,000) 9.1
-// and 8.5; at B = 32, where argmax_parts still cuts rows in eight, V = 151,936 is 8.9 and 9.6, V = 128,256
-// 9.3 and 8.8.
+// fp32 rows are taken in slices (argmax_slice_kernel) from 33 rows of eight slices on.  In slices / by row, everything allowed, nothing and a
+// few tokens in every other row: V = 50,021 B = 40 1.09 1.10 1.16, 128 1.07 1.02 0.98, 256 1.11 0.95 0.96; 64,000 B = 40 0.99 1.05 0.94,
+// 128 1.00 0.89 0.94, 256 1.06 0.90 0.91; 100,003 B = 24 0.93 1.02 0.91, 32 1.01 0.91 0.90, 40 0.99 0.90 0.93, 256 1.04 0.88 0.88;
+// 151,936 B = 16 0.99 0.96 1.03, 32 1.11 0.92 0.94, 64 1.06 0.77 0.78, 256 1.04 0.85 0.84.
 static bool argmax_in_slices(int dtype, uint32_t B, uint32_t V, const void *logits)
 {
-    return dtype == WG_F32 && B > 32u && V > 4u * kChoiceTokens && reinterpret_cast<uintptr_t>(logits) % 4u == 0u;
+    return dtype == WG_F32 && B > 32u && V > 7u * kChoiceTokens && reinterpret_cast<uintptr_t>(logits) % 4u == 0u;
 }
 
 // The k best are taken by a workgroup per row where the row is short, or where there are rows enough to keep
-// the chip busy: a slice of fp32 is twice the bytes for what it costs besides, so fp32 rows are cut longer; and
-// what it costs grows with k.  Slices / by row, everything allowed, k = 20, 50, 64:
-//   fp32, V = 32000 1.04 to 1.34 for B = 1 to 256; 50021 B = 24 0.84 0.92 1.02, 64 0.88 1.00 1.07, 96 0.92 1.05 1.08;
-//   64000 B = 24 0.75 0.86 0.93, 64 0.84 0.95 1.03, 128 0.94 1.03 1.11; 84000 B = 96 0.81 0.90 1.00, 160 0.85 0.94
-//   1.00, 192 0.90 0.96 1.02; 100003 B = 24 0.62 0.67 0.77, 192 0.84 0.90 0.96, 256 0.91 0.96 1.02; 128256 B = 24 0.55
-//   0.61 0.69, 256 0.90 0.96 1.01 (nothing in every other row: 0.91 1.02 1.08); 151936 B = 24 0.47 0.55 0.63
-//   bf16, V = 64000 0.97 to 1.28; 100003 B = 24 0.85 0.95 1.08, 64 0.95 1.00 1.13; 128256 B = 24 0.76 0.89 0.96, 48 0.78
-//   0.92 1.00, 64 0.85 0.99 1.11; 151936 B = 24 0.69 0.81 0.92, 64 0.83 0.93 1.08, 96 1.03 1.17 1.25
+// the chip busy; what a slice costs besides its bytes grows with k.  Slices / by row, k = 20, 50, 64, everything allowed (nothing in
+// every other row up to 0.2 less from 64 rows on):
+//   bf16, V = 50021 B = 8 1.05 1.24 1.37; 64000 B = 8 0.94 1.12 1.24, 48 1.01 1.19 1.30; 84000 B = 48 0.93 1.12 1.27, 96 1.07 1.28
+//   1.41; 100003 B = 8 0.81 1.01 1.16, 64 0.99 1.21 1.34, 96 1.09 1.29 1.45; 128256 B = 24 0.79 1.00 1.10, 64 0.95 1.17 1.28, 96 1.16
+//   1.40 1.54; 151936 B = 8 0.69 0.85 1.01, 48 0.85 1.03 1.17, 64 0.92 1.06 1.24, 96 1.12 1.27 1.42
+//   fp32, V = 32000 1.09 to 1.43; 50021 B = 24 0.96 1.12 1.21, 64 1.05 1.21 1.33; 64000 B = 8 0.92 1.06 1.19, 64 1.04 1.24 1.35;
+//   84000 B = 33 0.86 1.01 1.12, 64 1.00 1.12 1.22, 96 1.07 1.21 1.30; 100003 B = 8 0.76 0.89 0.98, 64 0.96 1.10 1.18, 96 1.04 1.12 1.24,
+//   128 1.18 1.32 1.42; 128256 B = 48 0.84 1.00 1.08, 64 0.89 1.04 1.12, 96 1.09 1.27 1.36; 151936 B = 64 0.82 0.95 1.08, 96 1.03 1.17 1.31
 static bool topk_by_row(uint32_t B, uint32_t V, uint32_t k, uint32_t elem_bytes)
 {
-    if (V < (elem_bytes == 2u ? 14u : 6u) * kTopkSlice) return true;
-    const uint32_t rows = elem_bytes == 2u ? 64u : V < 10u * kTopkSlice ? 96u : V < 14u * kTopkSlice ? 192u : 256u;
-    return B >= (k > 50u ? rows / 2u : rows);
+    const uint32_t slices = V / kTopkSlice, kind = k <= 32u ? 0u : k <= 56u ? 1u : 2u;
+    if (elem_bytes == 2u) {
+        const uint32_t few[3] = {7u, 14u, 20u}, rows[3] = {slices < 10u ? 48u : 80u, 40u, 32u};
+        return slices < few[kind] || B >= rows[kind];
+    }
+    const uint32_t few[3] = {6u, 9u, 14u}, rows[3] = {slices < 9u ? 56u : 96u, slices < 16u ? 64u : 96u, 56u};
+    return slices < few[kind] || B >= rows[kind];
 }
 
 hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint32_t V, int64_t row_stride,

@@ -425,8 +425,45 @@ def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
         assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,V,off", [(5, 32768, 0), (5, 32777, 1), (39, 114688, 1), (40, 114688, 0), (5, 163840, 3), (48, 57344, 0), (56, 65537, 2),
+                                     (80, 81921, 0), (64, 131071, 1), (5, 262143, 3), (5, 262144, 1)])
+def test_the_k_best_where_threads_hold_one_piece_or_more(torch_cuda, B, V, off, dtype):
+    """Rows of a few pieces of a thread and of many, either side of the lines between slices and whole rows; the best
+    tokens all in one thread's pieces, all in neighbouring pieces, fewer numbers than k among NaNs, thousands of ties, one
+    value in every piece of a thread."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    rng = np.random.default_rng(V + B + off)
+    x = rng.standard_normal((B, V)).astype(np.float32)
+    per = 16384 // (4 if dtype == "f32" else 2)                     # tokens from a thread's piece to its next, 1,024 threads
+    x[0, 5::per] = 40.0 + np.arange(len(x[0, 5::per]))
+    x[1, 1000:1100] = 50.0 + rng.standard_normal(100)
+    x[2] = np.nan
+    x[2, rng.integers(0, V, 9)] = 1.0
+    x[3] = np.where(rng.random(V) < 0.9, 2.0, 1.0)
+    x[4, 8 * 77 % V::per] = 9.0
+    host = x if dtype == "f32" else ws.to_bf16_bits(x)
+    bits = rng.integers(0, 1 << 32, (B, (V + 31) // 32), dtype=np.uint32) | rng.integers(0, 1 << 32, (B, (V + 31) // 32), dtype=np.uint32)
+    if V % 32:
+        bits[:, -1] &= np.uint32((1 << (V % 32)) - 1)
+    d = H.dev_logits(host)
+    buf = torch.zeros((B * (V + off) + 64,), dtype=d.dtype, device="cuda")
+    view = buf[off:off + B * (V + off)].view(B, V + off)[:, :V]
+    view.copy_(d)
+    mask = torch.from_numpy(bits.view(np.int32)).cuda()
+    for k in (20, 33, 57):
+        ids = torch.empty((B, k), dtype=torch.int32, device="cuda")
+        vals = torch.empty((B, k), dtype=d.dtype, device="cuda")
+        work = torch.empty(wg.masked_topk_workspace(B, V, k), dtype=torch.uint8, device="cuda")
+        wg.masked_topk(view, mask, ids, vals, work)
+        want_ids, want_vals = O.masked_topk(host, bits, k)
+        assert (ids.cpu().numpy() == want_ids).all(), k
+        assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
+
+
 @pytest.mark.parametrize("B,V,off", [(32, 32769, 0), (33, 32768, 0), (33, 32769, 0), (33, 32769, 3), (40, 40957, 3), (40, 40958, 3), (40, 40961, 2),
-                                     (65, 50021, 1), (129, 131072, 0), (1030, 33000, 0)])
+                                     (65, 50021, 1), (129, 131072, 0), (1030, 33000, 0), (32, 57345, 0), (33, 57344, 0), (33, 57345, 3), (40, 65533, 3), (40, 65537, 2)])
 def test_greedy_choice_of_fp32_rows_in_slices(torch_cuda, B, V, off):
     """Rows of five and more slices of 8,192 tokens and the sizes just below, rows that begin inside a
     16-byte block (so that the last tokens make a slice of their own), maxima on either side of a slice's edge,
