@@ -15,6 +15,7 @@
 // No MFMA anywhere: the path is byte matching and memory traffic.
 #include <hip/hip_runtime.h>
 
+#include "wg_buffer.h"
 #include "wg_device.h"
 #include "wg_launch.h"
 
@@ -566,11 +567,14 @@ __device__ __forceinline__ void mask_span(Elem *logits, uint32_t lo, uint32_t hi
 
 // The same by whole lines: every 128-byte line with a disallowed token is read where it has to be and written
 // whole, 8 lanes x 16 bytes.  The pieces are cut where the addresses allow it, the tokens before and behind them
-// are stored one by one.  kBatch: pieces of a thread in flight together.  In the rows' kernel, where few of a unit's
-// workgroups mask at a time, 5 (fp32: 6); by itself 4, a workgroup's share of bf16.  us a cold step, V = 151936,
-// B = 1024, random trees, with 3 / 4 / 5 / 6 156.0 / 153.2 / 149.9 / 150.8, mixed 139.4 / 137.6 / 135.9 / 136.7 (with 8 registers go to memory: half as
-// slow again); fp32, V = 128256, B = 1000 198.4 / 195.6 / 196.5 / 194.1.  By itself 3 gains 1 %
-// on mixed masks and loses 5 % (bf16, B = 1000, 67.1 -> 70.6; 4 of fp32's 8 likewise) on rows masked nearly as a whole.
+// are stored one by one.  Without a branch around a piece's load or store, and as streams: behind branches each store was
+// waited for before the next one (loads and stores count together), and logits that the last-level cache does not hold
+// only take its place.  us, V = 151936, bf16, B = 1000, outlines, mixed, random trees, branches / none / none and streams:
+// wg_apply_mask 101 108 103 / 98 105 101 / 78 84 81 (streamed loads alone 96 101 96, stores alone 97 106 94), a cold step 124 139 139 / 121
+// 136 137 / 108 119 124; fp32, V = 128256, B = 700, the cold step 108 127 149 / 103 123 147 / 97 112 136.
+// kBatch: pieces of a thread in flight together.  In the rows' kernel 5 (fp32: 8); by itself 4, a workgroup's share of bf16 (fp32: 8).  us a cold
+// step, V = 151936, B = 1000, mixed, random trees, with 4 / 5 / 8 121.3 127.6 / 118.8 123.8 / 121.9 129.2; fp32, V = 128256, B = 700, with 4 / 6 / 8
+// 111.9 136.4 / 112.5 136.0 / 110.0 133.9; by itself fp32 with 4 / 8 88.1 107.2 / 85.5 103.7.
 template <typename Elem, uint32_t kBatch>
 __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t hi, const uint32_t *row)
 {
@@ -587,27 +591,26 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
     auto disallowed = [&](uint32_t t) { return !((row[(t - lo) >> 5] >> ((t - lo) & 31u)) & 1u); };
     for (uint32_t i = tid; i < head; i += nt) if (disallowed(lo + i)) logits[lo + i] = kNinf;
     for (uint32_t t = t1 + tid; t < hi; t += nt) if (disallowed(t)) logits[t] = kNinf;
+    const Window win = window_of(logits + t0, pieces * 16u);
     for (uint32_t p0 = 0; p0 < pieces; p0 += nt * kBatch) {
-        uint32_t z[kBatch];                                        // disallowed tokens of the pieces
+        uint32_t z[kBatch], at_piece[kBatch];                      // disallowed tokens of the pieces
         uint4 v[kBatch];
-        bool put[kBatch];
         const unsigned long long line = 0xFFull << (tid & 56u);
 #pragma unroll
         for (uint32_t i = 0; i < kBatch; i++) {
-            const uint32_t p = p0 + i * nt + tid, bit = head + p * kPer;
+            const uint32_t p = p0 + i * nt + tid, bit = head + (p < pieces ? p : pieces - 1u) * kPer;
             // (the word behind the row's last one is there to be read)
-            z[i] = p < pieces ? ~__builtin_amdgcn_alignbit(row[(bit >> 5) + 1u], row[bit >> 5], bit & 31u) & kAll : 0u;
+            z[i] = ~__builtin_amdgcn_alignbit(row[(bit >> 5) + 1u], row[bit >> 5], bit & 31u) & kAll;
+            if (p >= pieces) z[i] = 0u;
         }
 #pragma unroll
         for (uint32_t i = 0; i < kBatch; i++) {
             const uint32_t p = p0 + i * nt + tid;
-            put[i] = p < pieces && (__ballot(z[i] != 0u) & line);
-            v[i] = uint4{0u, 0u, 0u, 0u};
-            if (put[i] && z[i] != kAll) v[i] = *reinterpret_cast<const uint4 *>(logits + t0 + (size_t)p * kPer);
+            at_piece[i] = p < pieces && (__ballot(z[i] != 0u) & line) ? p * 16u : kNowhere;
+            v[i] = block_at<kStream>(win, z[i] != kAll ? at_piece[i] : kNowhere);
         }
 #pragma unroll
         for (uint32_t i = 0; i < kBatch; i++) {
-            if (!put[i]) continue;
             uint32_t d[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
             for (uint32_t k = 0; k < 4u; k++) {
@@ -616,7 +619,7 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
                 else m = ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k, 1) & 0xFFFFu) | ((uint32_t)__builtin_amdgcn_sbfe(z[i], 2 * k + 1, 1) << 16);
                 d[k] = (d[k] & ~m) | (kFill & m);
             }
-            *reinterpret_cast<uint4 *>(logits + t0 + (size_t)(p0 + i * nt + tid) * kPer) = uint4{d[0], d[1], d[2], d[3]};
+            put_block<kStream>(win, at_piece[i], uint4{d[0], d[1], d[2], d[3]});
         }
     }
 }
@@ -1150,7 +1153,7 @@ rows_kernel(WG_EARLY_ARGS)
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
     if (kMode == 1 || kMode == 3) mask_span<Elem, kMode == 3>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
-    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 6u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
+    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 8u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
     if (!kWhole && blockIdx.x == 0 && b == 0 && tid == 0) {
         close_fill(Cc, late.rows, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
         Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
@@ -1256,7 +1259,7 @@ apply_lines_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, ui
     const uint32_t w = (lo >> 5) + threadIdx.x;
     row[threadIdx.x] = w < W ? bitmask[(size_t)b * W + w] : 0u;
     __syncthreads();
-    mask_lines<Elem, 4u>(logits + (int64_t)b * row_stride, lo, hi, row);
+    mask_lines<Elem, sizeof(Elem) == 4 ? 8u : 4u>(logits + (int64_t)b * row_stride, lo, hi, row);
 }
 
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
@@ -1325,16 +1328,15 @@ static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b -
 // Logits of more bytes than these are masked by whole lines (see mask_lines): 128 bytes are read where a
 // line is mixed, but no store leaves the memory to read and write the block around it.  What it gains
 // depends on how many tokens of a line are disallowed, which the host does not know; the limits lie near where
-// the geometric mean over four kinds of masks is the same for both: 225 MB of bf16 and 360 MB of fp32 by the figures
-// below, a little above the limits, which were set before the masking by elements became faster and stay where
-// random trees gain.  By elements / by lines, us, a cached step on the masks of html outlines, of JSON objects, of
-// both mixed, and of random trees (16, 25, 45 and 63 % of the tokens disallowed):
-//   bf16, V = 151936: 194 MB 50 / 72, 47 / 72, 83 / 78, 94 / 80; 213 MB 58 / 82, 63 / 79, 95 / 86, 101 / 89; 225 MB 78 / 88,
-//   76 / 87, 100 / 92, 103 / 90; 252 MB 97 / 100, 97 / 98, 114 / 103, 114 / 98; 311 MB 128 / 117, 125 / 117, 140 / 120, 147 / 124
-//   fp32, V = 128256: 308 MB 59 / 91, 66 / 93, 110 / 105, 126 / 110; 328 MB 79 / 98, 82 / 97, 119 / 110, 143 / 125; 359 MB
-//   81 / 102, 97 / 104, 131 / 118, 156 / 131; 513 MB 152 / 144, 148 / 142, 184 / 161, 224 / 184
+// the geometric mean over four kinds of masks is the same for both: 215 MB of bf16 and 345 MB of fp32 by these
+// figures.  By elements / by lines, us, a cached step on the masks of html outlines, of JSON objects, of
+// both mixed, and of random trees (16, 25, 45 and 63 % of the tokens disallowed), two buffers in turn:
+//   bf16, V = 151936: 182 MB 29 / 60, 31 / 59, 54 / 64, 80 / 64; 213 MB 50 / 69, 61 / 68, 84 / 74, 89 / 72; 243 MB 81 / 78,
+//   87 / 76, 105 / 83, 107 / 83
+//   fp32, V = 128256: 257 MB 26 / 64, 31 / 67, 44 / 73, 113 / 87; 308 MB 42 / 75, 73 / 78, 85 / 86, 124 / 96; 359 MB 64 / 87, 95 / 89,
+//   111 / 99, 160 / 121
 // (a block holds twice as many bf16 tokens, so fewer of them stay untouched.)  So html outlines lose up to a
-// quarter right above the limit and random trees a quarter right below it.  Deciding by the density of each
+// third right above the limit and random trees a quarter right below it.  Deciding by the density of each
 // row or line was slower than the better of the two for all.
 constexpr uint64_t kLineBytes16 = 208ull << 20, kLineBytes32 = 320ull << 20;
 

@@ -25,6 +25,7 @@
 
 #include <mutex>
 
+#include "wg_buffer.h"
 #include "wg_device.h"
 #include "wg_launch.h"
 #include "wg_order.h"
@@ -36,19 +37,6 @@ constexpr uint32_t kWaves = kThreads / 64u;
 constexpr uint32_t kSegWords = 8192;                 // mask words staged at a time (32 KB: 262,144 tokens)
 constexpr uint32_t kCand = 1024;                     // candidates ranked in LDS
 constexpr uint32_t kNoPiece = 0xFFFFFFFFu;
-
-// Memory that is read by 16 bytes or a word at an offset, 0 from `bytes` on: a load that is not wanted goes there, without a
-// branch around it, and costs nothing.
-typedef __amdgpu_buffer_rsrc_t Window;
-__device__ __forceinline__ Window window_of(const void *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000); }
-constexpr uint32_t kNowhere = 0xFFFFFFF0u;           // an offset behind every window
-__device__ __forceinline__ uint4 block_at(Window w, uint32_t at)
-{
-    typedef uint32_t Four __attribute__((ext_vector_type(4)));
-    const Four x = __builtin_amdgcn_raw_buffer_load_b128(w, at, 0, 0);
-    return uint4{x.x, x.y, x.z, x.w};
-}
-__device__ __forceinline__ uint32_t word_at(Window w, uint32_t at) { return __builtin_amdgcn_raw_buffer_load_b32(w, at, 0, 0); }
 
 // One row of logits as aligned 16-byte pieces.
 template <typename Elem>
