@@ -1264,27 +1264,41 @@ apply_lines_kernel(Elem *__restrict__ logits, int64_t row_stride, uint32_t V, ui
 
 // The bytes a request is forced to produce next: from a state inside a Write, the rest of that
 // Write and of the Writes that follow it directly, up to the next state that is not a literal
-// byte.  One thread per request; a run of literal states is copied from the state table's
-// literal bytes.
-__global__ void __launch_bounds__(64)
-forced_bytes_kernel(DeviceTable T, const wg_state_t *__restrict__ states, uint32_t B, uint32_t cap,
-                    uint8_t *__restrict__ bytes, uint32_t *__restrict__ lens, wg_state_t *__restrict__ end_states)
+// byte.  A wavefront per request, a byte per lane: a Write costs one trip to memory, for its bytes and its descriptor
+// together, and the stores of one overlap the next one's trip.  (With a thread per request, a byte at a
+// time, a jump-forward step of 64 outlines took 17.9 us, now 17.3.)
+__global__ void __launch_bounds__(256)
+forced_bytes_kernel(const wg_state_t *__restrict__ states, const StateDesc *__restrict__ descs, const uint8_t *__restrict__ lit,
+                    uint8_t *__restrict__ bytes, uint32_t *__restrict__ lens, wg_state_t *__restrict__ end_states,
+                    uint32_t n_states, uint32_t cap, uint32_t B)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    uint32_t sid = states[b].sid, n = 0;
-    const uint32_t aux = states[b].aux;
-    uint8_t *out = bytes + (size_t)b * cap;
-    while (n < cap && sid < T.n_states) {
-        const StateDesc d = T.states[sid];
-        if ((d.kind_byte & 0xFFu) != WG_KIND_LIT) break;
-        const uint32_t m = d.run < cap - n ? d.run : cap - n;
-        for (uint32_t i = 0; i < m; i++) out[n + i] = T.lit[sid + i];
-        n += m;
-        sid = m == d.run ? d.cls : sid + m;                  // d.cls: state after the Write
+    const uint32_t lane = threadIdx.x & 63u, waves = blockDim.x >> 6;
+    // (any number of requests: more than the grid holds come in turn)
+    for (uint64_t b = (uint64_t)blockIdx.x * waves + of_first(threadIdx.x >> 6); b < B; b += (uint64_t)gridDim.x * waves) {
+        uint32_t sid = of_first(states[b].sid), n = 0;
+        const uint32_t aux = of_first(states[b].aux);
+        uint8_t *out = bytes + b * cap;
+        uint32_t words = 0, byte = 0;                        // dword lane % 8 of the state's descriptor; literal byte sid + lane
+        auto request = [&]() {
+            if (sid >= n_states) return;
+            words = reinterpret_cast<const uint32_t *>(descs + sid)[lane & 7u];
+            if (lane < n_states - sid) byte = lit[sid + lane];
+        };
+        request();
+        while (n < cap && sid < n_states) {
+            const StateDesc d = state_of(words, 0u);
+            if ((d.kind_byte & 0xFFu) != WG_KIND_LIT) break;
+            const uint32_t m = d.run < cap - n ? d.run : cap - n, from = sid, first = byte;
+            sid = m == d.run ? d.cls : sid + m;              // d.cls: state after the Write
+            request();
+            if (lane < m) out[n + lane] = (uint8_t)first;
+            for (uint32_t i = lane + 64u; i < m; i += 64u) out[n + i] = lit[from + i];
+            n += m;
+        }
+        if (lane) continue;
+        lens[b] = n;
+        if (end_states) end_states[b] = wg_state_t{sid, n ? 0u : aux};
     }
-    lens[b] = n;
-    if (end_states) end_states[b] = wg_state_t{sid, n ? 0u : aux};
 }
 
 // One block per row: d_tokens[b] = index of the (draw mod popcount)-th set bit.
@@ -1533,7 +1547,8 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
                                uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, hipStream_t s)
 {
-    return launch(forced_bytes_kernel, dim3(cdiv(B, 64)), dim3(64), 0, s, nullptr, T, states, B, cap, bytes, lens, end_states);
+    const uint32_t waves = B <= 512u ? 1u : 4u, blocks = cdiv(B, waves);
+    return launch(forced_bytes_kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, nullptr, states, T.states, T.lit, bytes, lens, end_states, T.n_states, cap, B);
 }
 
 hipError_t launch_select(const uint32_t *bitmask, uint32_t B, uint32_t V, const uint64_t *draws,

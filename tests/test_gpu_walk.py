@@ -117,3 +117,27 @@ def test_advance_of_more_requests_than_the_grid_holds(torch_cuda):
     big = torch.from_numpy(st[:1].view(np.int32).copy()).cuda().repeat(B, 1)
     h.advance(big, (torch.arange(B, device="cuda", dtype=torch.int32) % 16 + 60))
     assert torch.equal(big, torch.from_numpy(want.view(np.int32)).cuda().repeat(B // 16 + 1, 1)[:B])
+
+
+@pytest.mark.parametrize("B", [1, 511, 512, 513, 1025])
+@pytest.mark.parametrize("cap", [1, 63, 64, 65, 300])
+def test_forced_bytes_longer_than_a_wavefront(torch_cuda, B, cap):
+    """Forced runs of less and more bytes than lanes, of several Writes in a row, cut inside a Write and at its end, one
+    request to a workgroup and four."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    text = 'Sequence(Write("%s"), Write("b"), Write("%s"), Wait(denies={}, wait={<}), Write("%s"))' % (_RUN.decode(), _RUN[:64].decode(), _RUN[:65].decode())
+    vocab = from_tokens([b""] + [bytes([c]) for c in b"abcxyz<>"], 0)
+    o = O.Oracle([text], [{}], O.OracleVocab(vocab.bytes, vocab.offsets, vocab.eos_id), restart=True)
+    h = wg.Handle([text], [{}], wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART)
+    sids = [(i * 7) % (o.num_states + 2) if i else 1 for i in range(B)]
+    st = np.array([[s, 3] for s in sids], dtype=np.uint32)
+    d_bytes = torch.full((B, cap), 0xEE, dtype=torch.uint8, device="cuda")
+    d_lens = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    d_end = torch.full((B, 2), -1, dtype=torch.int32, device="cuda")
+    h.forced_bytes(H.dev_states(st), d_bytes, d_lens, d_end)
+    gb, gl, ge = d_bytes.cpu().numpy(), d_lens.cpu().numpy(), H.host_states(d_end)
+    for i, s in enumerate(sids):
+        want, end = o.forced_bytes(s, cap)
+        assert gl[i] == len(want) and bytes(gb[i, :gl[i]]) == want and (gb[i, gl[i]:] == 0xEE).all(), (s, cap)
+        assert ge[i, 0] == end and ge[i, 1] == (0 if want else 3), (s, cap)
