@@ -840,8 +840,9 @@ __device__ __forceinline__ void make_row(const TableView &T, const VocabView &Vc
     const bool by_first = ckpt && sh.plan.by_first;
     uint32_t total = 0;
     if (wave == 0u) {
-        // the index ranges with the key's candidates
-        uint32_t n = 0, sure = 0;
+        // the index ranges with the key's candidates; rest: what a lane's ranges hold for the row's other workgroups, counted
+        // by the first
+        uint32_t n = 0, sure = 0, rest = 0;
         // with them the class tables of the successors and the literal bytes, for this wavefront's own candidates
         uint32_t table[2] = {0u, 0u}, byte = 0;
         if (ckpt_a) table[0] = reinterpret_cast<const uint32_t *>(T.classes + (size_t)ha.cls * 256u)[lane];
@@ -871,9 +872,11 @@ __device__ __forceinline__ void make_row(const TableView &T, const VocabView &Vc
                 else if (from == FROM_PAIR) { a = kDirPairs + (x << 8 | lit); n_at = 1u; }
                 else if (from && from <= FROM_B) a += kDirFirst;
                 else a += kDirPlaces;
+                const bool by_range = from && from != FROM_PREFIX && from != FROM_PAIR;
                 if (!from) n_at = 0u;                          // nothing goes on behind this exit
                 lo = Vc.dirs[a];
                 len = Vc.dirs[a + n_at] - lo;
+                if (p0 == 0u && by_range) rest += Vc.dirs[a + kParts] - Vc.dirs[a + span];
                 sh.code[i] = (uint16_t)(x | from << 8);
             }
             const uint32_t inc = wave_prefix_sum(len);
@@ -883,9 +886,10 @@ __device__ __forceinline__ void make_row(const TableView &T, const VocabView &Vc
         if (ckpt_a) reinterpret_cast<uint32_t *>(sh.hop[0])[lane] = table[0];
         if (ckpt_b) reinterpret_cast<uint32_t *>(sh.hop[1])[lane] = table[1];
         if (lane < 48u) reinterpret_cast<uint8_t *>(sh.run[side])[at] = (uint8_t)byte;
+        if (p0 == 0u) sure += of_lane(wave_prefix_sum(rest), 63u) + total;
         if (lane == 0) {
             sh.n_ranges = n; sh.total = total;
-            if (p0 == 0u && sure + total) atomicAdd(&Cc.ctr->spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)(sure + total));
+            if (p0 == 0u && sure) atomicAdd(&Cc.ctr->spread[(b % kSpread) * kSpreadStride + kSpreadWalked], (unsigned long long)sure);
             if (Vc.eos_id >= 0 && me.eos_next != WG_SID_ERROR) {
                 const uint32_t ew = (uint32_t)Vc.eos_id >> 5;
                 if (ew >= w_lo && ew < w_hi) early[ew - w_lo] |= 1u << ((uint32_t)Vc.eos_id & 31u);

@@ -76,6 +76,32 @@ def test_every_literal_state_at_full_size(torch_cuda, idx, n_inst):
     assert len(direct) > 0
 
 
+@pytest.mark.parametrize("V", [5003, 8193, 20011, 70001])
+def test_the_candidates_counted_are_the_keys_own(torch_cuda, V):
+    """entries_walked per made row: what the indexes hold for the key, counted here from the tokens' bytes, however many
+    workgroups make the row (some of them without a token, where ranges are longer than shares)."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    vocab = ws.make_workload(4, V=V, B=1, steps=1).vocab
+    text = 'Sequence(Wait(denies={}, wait={<}), Wait(allow={a, b}, wait={>}), Write("xyz"), Wait(denies={}, wait={<}))'
+    toks = [bytes(vocab.bytes[int(a):int(b)]) for a, b in zip(vocab.offsets[:-1], vocab.offsets[1:])]
+    two = sum(t == b"x" or t[:2] == b"xy" for t in toks), sum(t == b"y" or t[:2] == b"yz" for t in toks)
+    want = {1: sum(t[:-1].count(b"<") for t in toks),                   # the exit leads to a checkpoint: every place of its byte but the last
+            2: sum(t[:1] in (b"a", b"b", b">") and t != b"" for t in toks),   # few byte values enter: every token that begins with one
+            3: two[0], 4: two[1],                                       # a literal in front of a literal: the byte itself, and the pair
+            5: sum(t[:1] == b"z" for t in toks)}                        # a literal in front of a checkpoint
+    h = wg.Handle([text], None, wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART)
+    for sid, n in want.items():
+        assert n > 0
+        for B in (1, 3, 16, 64, 100, 256, 257, 700):
+            st = H.dev_states(np.tile(np.array([[sid, 0]], dtype=np.uint32), (B, 1)))
+            mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+            h.cache_clear()
+            before = h.cache_stats()["entries_walked"]
+            h.fill_masks(st, mask)
+            assert h.cache_stats()["entries_walked"] - before == B * n, (sid, B)
+
+
 @pytest.mark.parametrize("idx,n_inst", [(2, 1), (3, 1), (4, 6), (5, 16)])
 def test_every_checkpoint_state_at_full_size(torch_cuda, idx, n_inst):
     """Every Wait / condition state (all byte budgets that bind, for a bounded Wait) at the full
