@@ -19,7 +19,7 @@
 // thread maxima is found by bisection on ballots, and the least of these is a lower bound for the k-th
 // best token.  Two to three times k tokens reach it; they are ranked by counting.
 //
-// Rows may start at any element: pieces are aligned 16-byte blocks, the first of them may begin
+// Rows may start at any byte.  Where elements lie at multiples of their size, pieces are aligned 16-byte blocks, the first of them may begin
 // before the row and the last may end behind it, and the staged mask has those tokens as disallowed.
 #include <hip/hip_runtime.h>
 
@@ -38,35 +38,45 @@ constexpr uint32_t kSegWords = 8192;                 // mask words staged at a t
 constexpr uint32_t kCand = 1024;                     // candidates ranked in LDS
 constexpr uint32_t kNoPiece = 0xFFFFFFFFu;
 
-// One row of logits as aligned 16-byte pieces.
-template <typename Elem>
+// One row of logits as 16-byte pieces.  kWhole: elements lie at multiples of their size, and pieces are aligned.  Else pieces are
+// cut at the row's beginning, each out of the five aligned words that it lies in.  (Element by element, behind branches, a piece was up
+// to eight trips to memory one after the other; a kernel for both spent 1 % of the whole rows' time on the choice.)  us at an odd byte,
+// mixed masks, so / now, the greedy choice and k = 50: bf16, V = 151,936, B = 40 15.2 41.0 / 7.4 15.3, 256 39.7 56.4 / 12.3 16.5; fp32, V =
+// 128,256, B = 64 12.6 34.9 / 8.1 18.4.
+template <typename Elem, bool kWhole>
 struct Row {
     static constexpr uint32_t kPer = 16u / sizeof(Elem);          // tokens of a piece: 8 bf16, 4 fp32
     static constexpr uint32_t kAll = (1u << kPer) - 1u;
     const Elem *tokens;
-    const uint4 *blocks;                             // piece p holds the tokens p * kPer - skew ...
-    uint32_t skew, pieces, V;
-    bool whole;                                      // elements lie at multiples of their size: pieces can be loaded as such
+    const char *first;                               // the aligned block, or word, that the row's first byte lies in
+    uint32_t skew, pieces, V;                        // piece p holds the tokens p * kPer - skew ...
+    uint32_t odd;                                    // not whole: bytes of the first word in front of the row
 
     __device__ __forceinline__ Row(const Elem *row, uint32_t V_) : tokens(row), V(V_)
     {
         const uintptr_t at = reinterpret_cast<uintptr_t>(row);
-        whole = at % sizeof(Elem) == 0u;
-        skew = whole ? (uint32_t)(at % 16u / sizeof(Elem)) : 0u;
-        blocks = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(row) - at % 16u);
+        odd = (uint32_t)(at % 4u);
+        skew = kWhole ? (uint32_t)(at % 16u / sizeof(Elem)) : 0u;
+        first = reinterpret_cast<const char *>(row) - (kWhole ? at % 16u : at % 4u);
         pieces = (V + skew + kPer - 1u) / kPer;
     }
-    // n pieces from p on, of a row that is whole.  An aligned 16-byte block that holds a token of the row lies in
-    // the row's own memory page, also where it begins before the row or ends behind it.
-    __device__ __forceinline__ Window window(uint32_t p, uint32_t n) const { return window_of(blocks + p, n * 16u); }
-    // A piece with allowed tokens m, of a row that is not.
-    __device__ __forceinline__ uint4 gather(uint32_t p, uint32_t m) const
+    // n pieces from p on.  An aligned block, or word, that holds a byte of the row lies in the row's own memory page, also
+    // where it begins before the row or ends behind it.
+    __device__ __forceinline__ Window window(uint32_t p, uint32_t n) const
     {
-        union { uint4 v; Elem e[kPer]; } u;
-        u.v = uint4{0u, 0u, 0u, 0u};
-        for (uint32_t i = 0; i < kPer; i++)
-            if ((m >> i) & 1u) u.e[i] = tokens[(size_t)p * kPer + i];
-        return u.v;
+        if (kWhole) return window_of(first + (size_t)p * 16u, n * 16u);
+        const uint64_t left = ((odd + (uint64_t)V * sizeof(Elem) + 3u) & ~3ull) - (uint64_t)p * 16u, most = n * 16u + 4u;
+        return window_of(first + (size_t)p * 16u, (uint32_t)(left < most ? left : most));
+    }
+    // The piece at an offset of a window (kNowhere: one without anything to look at).
+    __device__ __forceinline__ uint4 piece(const Window &win, uint32_t at) const
+    {
+        if (kWhole) return block_at(win, at);
+        uint32_t w[5];
+#pragma unroll
+        for (uint32_t k = 0; k < 5u; k++) w[k] = word_at(win, at + 4u * k);
+        return uint4{__builtin_amdgcn_alignbyte(w[1], w[0], odd), __builtin_amdgcn_alignbyte(w[2], w[1], odd),
+                     __builtin_amdgcn_alignbyte(w[3], w[2], odd), __builtin_amdgcn_alignbyte(w[4], w[3], odd)};
     }
     __device__ __forceinline__ uint32_t token(uint32_t p, uint32_t i) const { return p * kPer + i - skew; }
 };
@@ -110,11 +120,11 @@ __device__ __forceinline__ void stage_mask(const uint32_t *mask, uint32_t W, uin
 }
 
 // The allowed tokens of piece p, from the mask as it lies in memory.
-template <typename Elem>
-__device__ __forceinline__ uint32_t piece_mask(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t p)
+template <typename Elem, bool kWhole>
+__device__ __forceinline__ uint32_t piece_mask(const Row<Elem, kWhole> &r, const uint32_t *mask, uint32_t W, uint32_t p)
 {
-    const uint32_t bit = p * Row<Elem>::kPer;
-    return (mask_word(mask, W, r.V, r.skew, bit >> 5) >> (bit & 31u)) & Row<Elem>::kAll;
+    const uint32_t bit = p * r.kPer;
+    return (mask_word(mask, W, r.V, r.skew, bit >> 5) >> (bit & 31u)) & r.kAll;
 }
 
 // The largest allowed number of a piece (NaN when there is none): a disallowed token's bits are
@@ -147,11 +157,11 @@ __device__ __forceinline__ float piece_max(const uint4 &v, uint32_t m, uint32_t)
 // Streams the pieces [lo, hi) of the row, lo a multiple of 32: what(p, piece, allowed tokens) for every
 // piece of the thread that has an allowed token, in ascending order.  `words` is kSegWords + 1
 // words of LDS.  The whole workgroup calls it.
-template <typename Elem, typename F>
-__device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *mask, uint32_t W, uint32_t *words,
+template <typename Elem, bool kWhole, typename F>
+__device__ __forceinline__ void stream_row(const Row<Elem, kWhole> &r, const uint32_t *mask, uint32_t W, uint32_t *words,
                                            uint32_t lo, uint32_t hi, F what)
 {
-    constexpr uint32_t kPer = Row<Elem>::kPer, kSegPieces = kSegWords * 32u / kPer;
+    constexpr uint32_t kPer = Row<Elem, kWhole>::kPer, kSegPieces = kSegWords * 32u / kPer;
     const uint32_t tid = threadIdx.x;
     for (uint32_t s0 = lo; s0 < hi; s0 += kSegPieces) {
         const uint32_t n = hi - s0 < kSegPieces ? hi - s0 : kSegPieces;
@@ -163,16 +173,9 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
         auto allowed = [&](uint32_t q) {
             if (q > none) q = none;
             if (kPer == 8u) return (uint32_t)reinterpret_cast<const uint8_t *>(words)[q];
-            return words[q / (32u / kPer)] >> (q * kPer & 31u) & Row<Elem>::kAll;
+            return words[q / (32u / kPer)] >> (q * kPer & 31u) & r.kAll;
         };
-        if (!r.whole) {
-            for (uint32_t q = tid; q < n; q += kThreads) {
-                const uint32_t m = allowed(q);
-                if (m) what(s0 + q, r.gather(s0 + q, m), m);
-            }
-            continue;
-        }
-        constexpr uint32_t kHalf = 3u;
+        constexpr uint32_t kHalf = kWhole ? 3u : 2u;       // (of five words each, three are 3 % slower)
         const Window win = r.window(s0, n);
         uint32_t m[2][kHalf];
         uint4 v[2][kHalf];
@@ -180,7 +183,7 @@ __device__ __forceinline__ void stream_row(const Row<Elem> &r, const uint32_t *m
 #pragma unroll
             for (uint32_t j = 0; j < kHalf; j++) mm[j] = allowed(q0 + j * kThreads);
 #pragma unroll
-            for (uint32_t j = 0; j < kHalf; j++) vv[j] = block_at(win, mm[j] ? (q0 + j * kThreads) * 16u : kNowhere);
+            for (uint32_t j = 0; j < kHalf; j++) vv[j] = r.piece(win, mm[j] ? (q0 + j * kThreads) * 16u : kNowhere);
         };
         auto look = [&](const uint32_t (&mm)[kHalf], const uint4 (&vv)[kHalf], uint32_t q0) {
 #pragma unroll
@@ -207,7 +210,7 @@ constexpr uint32_t kCutRows = 256;                   // most workgroups of a cal
 __device__ unsigned long long g_argmax_key[kMaxBatch];
 __device__ unsigned long long g_argmax_node[kCutRows];
 
-template <typename Elem>
+template <typename Elem, bool kWhole>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
                      const uint32_t *__restrict__ bitmask, int32_t *__restrict__ tokens)
@@ -217,7 +220,7 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     __shared__ uint32_t best_token;
     const uint32_t b = blockIdx.y, tid = threadIdx.x;
     const uint32_t *mask = bitmask + (size_t)b * W;
-    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    const Row<Elem, kWhole> r(logits + (int64_t)b * row_stride, V);
     const uint32_t share = ((r.pieces + gridDim.x - 1u) / gridDim.x + 31u) & ~31u;
     const uint32_t lo = blockIdx.x * share < r.pieces ? blockIdx.x * share : r.pieces;
     const uint32_t hi = r.pieces - lo < share ? r.pieces : lo + share;
@@ -225,7 +228,7 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
     // the thread's first piece with `best`, and its elements (looked up again at the end they were a trip to memory: V =
     // 151936, bf16, B = 256 19.6 -> 18.8 us, B = 128 12.4 -> 11.9, B = 1 5.6 -> 5.5)
     uint32_t where = kNoPiece;
-    union { uint4 v; Elem e[Row<Elem>::kPer]; } held;
+    union { uint4 v; Elem e[16u / sizeof(Elem)]; } held;
     held.v = uint4{0u, 0u, 0u, 0u};
     uint32_t held_mask = 0;
     auto see = [&](uint32_t p, const uint4 &v, uint32_t m) {
@@ -249,7 +252,7 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
         if (where != kNoPiece && best == top) {
             uint32_t eq = 0;
 #pragma unroll
-            for (uint32_t i = 0; i < Row<Elem>::kPer; i++) eq |= (uint32_t)(elem_float(held.e[i]) == top) << i;
+            for (uint32_t i = 0; i < r.kPer; i++) eq |= (uint32_t)(elem_float(held.e[i]) == top) << i;
             atomicMin(&best_token, r.token(where, (uint32_t)__builtin_ctz(eq & held_mask)));
         }
     } else {
@@ -287,17 +290,17 @@ masked_argmax_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32
 // 29.9 -> 31.2 / 20.2 -> 17.0; a ticket in place of the second kernel kept each workgroup for two more trips to memory
 // (B = 1,024 110 -> 167).  bf16 rows are not taken so (B = 256 20.1 -> 25.1, B = 1,024 63 -> 74 when by row was slower than now).
 constexpr uint32_t kChoiceThreads = 256, kChoicePieces = 8;
-constexpr uint32_t kChoiceTokens = kChoiceThreads * kChoicePieces * Row<uint32_t>::kPer;
+constexpr uint32_t kChoiceTokens = kChoiceThreads * kChoicePieces * Row<uint32_t, true>::kPer;
 __global__ void __launch_bounds__(kChoiceThreads)
 argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
                     const uint32_t *__restrict__ bitmask)
 {
-    constexpr uint32_t kPer = Row<uint32_t>::kPer, kWords = kChoiceTokens / 32u;
+    constexpr uint32_t kPer = Row<uint32_t, true>::kPer, kWords = kChoiceTokens / 32u;
     __shared__ uint32_t words[kWords];
     __shared__ float part[kChoiceThreads / 64u];
     __shared__ uint32_t best_token;
     const uint32_t b = blockIdx.y, tid = threadIdx.x, base = blockIdx.x * (kChoicePieces * kChoiceThreads) + tid;
-    const Row<uint32_t> r(logits + (int64_t)b * row_stride, V);
+    const Row<uint32_t, true> r(logits + (int64_t)b * row_stride, V);
     static_assert(kWords == kChoiceThreads, "a mask word per thread");
     words[tid] = mask_word(bitmask + (size_t)b * W, W, V, r.skew, blockIdx.x * kWords + tid);
     if (tid == 0) best_token = 0xFFFFFFFFu;
@@ -308,7 +311,7 @@ argmax_slice_kernel(const uint32_t *__restrict__ logits, int64_t row_stride, uin
 #pragma unroll
     for (uint32_t j = 0; j < kChoicePieces; j++) {
         const uint32_t bit = (j * kChoiceThreads + tid) * kPer;
-        m[j] = (words[bit >> 5] >> (bit & 31u)) & Row<uint32_t>::kAll;
+        m[j] = (words[bit >> 5] >> (bit & 31u)) & Row<uint32_t, true>::kAll;
     }
 #pragma unroll
     for (uint32_t j = 0; j < kChoicePieces; j++)               // (elements lie at multiples of their size: launch_masked_argmax)
@@ -428,16 +431,16 @@ __device__ __forceinline__ uint16_t element(const uint4 &v, uint32_t i, uint16_t
 {
     return (uint16_t)(element(v, i >> 1, 0u) >> (16u * (i & 1u)));
 }
-template <typename Elem>
-__device__ __forceinline__ unsigned long long key_of(const Row<Elem> &r, const uint4 &v, uint32_t p, uint32_t i)
+template <typename Elem, bool kWhole>
+__device__ __forceinline__ unsigned long long key_of(const Row<Elem, kWhole> &r, const uint4 &v, uint32_t p, uint32_t i)
 {
     return (unsigned long long)rank_of(element(v, i, Elem(0))) << 32 | (0xFFFFFFFFu - r.token(p, i));
 }
 
 // The keys of n candidate tokens, from their logits read again (which register of which thread holds a
 // candidate's is not known at compile time; they are in the L2).
-template <uint32_t kT, typename Elem>
-__device__ __forceinline__ void make_keys(unsigned long long *cand, const uint32_t *ids, uint32_t n, const Row<Elem> &r)
+template <uint32_t kT, typename Elem, bool kWhole>
+__device__ __forceinline__ void make_keys(unsigned long long *cand, const uint32_t *ids, uint32_t n, const Row<Elem, kWhole> &r)
 {
     for (uint32_t i = threadIdx.x; i < n; i += kT) {
         const uint32_t id = ids[i];
@@ -482,17 +485,17 @@ struct TopkShared {
     uint32_t n, n_threads, digit, above;
 };
 
-template <typename Elem>
+template <typename Elem, bool kWhole>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
                    const uint32_t *__restrict__ bitmask, uint32_t k, int32_t *__restrict__ ids,
                    Elem *__restrict__ values, Elem ninf)
 {
-    constexpr uint32_t kPer = Row<Elem>::kPer;
+    constexpr uint32_t kPer = Row<Elem, kWhole>::kPer;
     __shared__ TopkShared sh;
     const uint32_t b = blockIdx.x, tid = threadIdx.x;
     const uint32_t *mask = bitmask + (size_t)b * W;
-    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    const Row<Elem, kWhole> r(logits + (int64_t)b * row_stride, V);
     int32_t *id_out = ids + (size_t)b * k;
     Elem *value_out = values + (size_t)b * k;
     // the thread's first piece with `best`, and the most of its other pieces
@@ -542,9 +545,10 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
             if (i < items) p[j] = sh.threads[of] + (i - of * per) * kThreads;
             if (i < items && p[j] < r.pieces) {
                 const uint32_t bit = p[j] * kPer;
-                m[j] = staged ? (sh.words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : piece_mask(r, mask, W, p[j]);
-                if (m[j]) v[j] = r.whole ? r.blocks[p[j]] : r.gather(p[j], m[j]);
+                m[j] = staged ? (sh.words[bit >> 5] >> (bit & 31u)) & r.kAll : piece_mask(r, mask, W, p[j]);
+                if (kWhole && m[j]) v[j] = reinterpret_cast<const uint4 *>(r.first)[p[j]];
             }
+            if (!kWhole) v[j] = r.piece(r.window(0u, r.pieces), m[j] ? p[j] * 16u : kNowhere);
         }
 #pragma unroll
         for (uint32_t j = 0; j < kItems; j++) put(v[j], p[j], m[j]);
@@ -627,16 +631,16 @@ struct SliceShared {
     uint32_t n;
 };
 
-template <typename Elem>
+template <typename Elem, bool kWhole>
 __global__ void __launch_bounds__(kSliceThreads) __attribute__((amdgpu_waves_per_eu(5)))
 topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t V, uint32_t W,
                   const uint32_t *__restrict__ bitmask, uint32_t k, unsigned long long *__restrict__ lists)
 {
-    constexpr uint32_t kPer = Row<Elem>::kPer, kPieces = kSlicePer / kPer;
+    constexpr uint32_t kPer = Row<Elem, kWhole>::kPer, kPieces = kSlicePer / kPer;
     __shared__ SliceShared sh;
     const uint32_t b = blockIdx.y, tid = threadIdx.x;
     const uint32_t *mask = bitmask + (size_t)b * W;
-    const Row<Elem> r(logits + (int64_t)b * row_stride, V);
+    const Row<Elem, kWhole> r(logits + (int64_t)b * row_stride, V);
     unsigned long long *out = lists + ((size_t)b * gridDim.x + blockIdx.x) * k;
     // Equal shares of whole mask words: a last slice of a few hundred tokens fills a wavefront or two, the
     // others then give no bound, and all of its tokens are ranked (V = 115,001: 10 us more).  Where the
@@ -659,25 +663,19 @@ topk_slice_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t 
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) {
         const uint32_t q = j * kSliceThreads + tid, bit = q * kPer;
-        m[j] = q < own_pieces ? (sh.words[bit >> 5] >> (bit & 31u)) & Row<Elem>::kAll : 0u;
+        m[j] = q < own_pieces ? (sh.words[bit >> 5] >> (bit & 31u)) & r.kAll : 0u;
     }
     const uint32_t extra = base + kTopkSlice / kPer + tid;        // at most one such piece
-    const uint32_t m_extra = kTopkSlice / kPer + tid < own_pieces ? sh.words[kWords] & Row<Elem>::kAll : 0u;
+    const uint32_t m_extra = kTopkSlice / kPer + tid < own_pieces ? sh.words[kWords] & r.kAll : 0u;
     float best = __builtin_nanf("");
     uint32_t any = m_extra;
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) any |= m[j];
     uint4 v_extra;
-    if (r.whole) {
-        const Window win = r.window(base, own_pieces);
+    const Window win = r.window(base, own_pieces);
 #pragma unroll
-        for (uint32_t j = 0; j < kPieces; j++) u[j].v = block_at(win, m[j] ? (j * kSliceThreads + tid) * 16u : kNowhere);
-        v_extra = block_at(win, m_extra ? (kTopkSlice / kPer + tid) * 16u : kNowhere);
-    } else {
-#pragma unroll
-        for (uint32_t j = 0; j < kPieces; j++) u[j].v = r.gather(base + j * kSliceThreads + tid, m[j]);
-        v_extra = r.gather(extra, m_extra);
-    }
+    for (uint32_t j = 0; j < kPieces; j++) u[j].v = r.piece(win, m[j] ? (j * kSliceThreads + tid) * 16u : kNowhere);
+    v_extra = r.piece(win, m_extra ? (kTopkSlice / kPer + tid) * 16u : kNowhere);
 #pragma unroll
     for (uint32_t j = 0; j < kPieces; j++) best = __builtin_fmaxf(best, piece_max(u[j].v, m[j], Elem(0)));
     if (m_extra) best = __builtin_fmaxf(best, piece_max(v_extra, m_extra, Elem(0)));
@@ -803,6 +801,9 @@ hipError_t static_topk_scratch(unsigned long long **out)
     return hipSuccess;
 }
 
+// All rows of a call are whole or none is: they lie a number of elements apart.
+template <typename Elem> static bool rows_are_whole(const Elem *logits) { return reinterpret_cast<uintptr_t>(logits) % sizeof(Elem) == 0u; }
+
 // Workgroups of the greedy choice per row: as many as the compute units hold one of each, at least
 // 16,384 tokens in each.  (Two of each, bf16, V = 151,936, mixed masks, us: B = 64 7.5 -> 8.6, B = 128 9.2 -> 10.3, B = 256 13.7 -> 14.2; four:
 // B = 256 18.2.)
@@ -819,7 +820,7 @@ static uint32_t argmax_parts(uint32_t B, uint32_t V)
 // 151,936 B = 16 0.99 0.96 1.03, 32 1.11 0.92 0.94, 64 1.06 0.77 0.78, 256 1.04 0.85 0.84.
 static bool argmax_in_slices(int dtype, uint32_t B, uint32_t V, const void *logits)
 {
-    return dtype == WG_F32 && B > 32u && V > 7u * kChoiceTokens && reinterpret_cast<uintptr_t>(logits) % 4u == 0u;
+    return dtype == WG_F32 && B > 32u && V > 7u * kChoiceTokens && rows_are_whole(static_cast<const uint32_t *>(logits));
 }
 
 // The k best are taken by a workgroup per row where the row is short, or where there are rows enough to keep
@@ -852,9 +853,13 @@ hipError_t launch_masked_argmax(const void *logits, int dtype, uint32_t B, uint3
         if (e != hipSuccess) return e;
         return launch(argmax_finish_kernel, dim3((B + 63u) / 64u), dim3(64), 0, s, nullptr, tokens, B);
     }
-    const dim3 g(argmax_parts(B, V), B);
-    if (dtype == WG_F32) return launch(masked_argmax_kernel<uint32_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint32_t *>(logits), row_stride, V, W, bitmask, tokens);
-    return launch(masked_argmax_kernel<uint16_t>, g, dim3(kThreads), 0, s, nullptr, static_cast<const uint16_t *>(logits), row_stride, V, W, bitmask, tokens);
+    auto choose = [&](auto kernel, auto *x) { return launch(kernel, dim3(argmax_parts(B, V), B), dim3(kThreads), 0, s, nullptr, x, row_stride, V, W, bitmask, tokens); };
+    if (dtype == WG_F32) {
+        const uint32_t *x = static_cast<const uint32_t *>(logits);
+        return rows_are_whole(x) ? choose(masked_argmax_kernel<uint32_t, true>, x) : choose(masked_argmax_kernel<uint32_t, false>, x);
+    }
+    const uint16_t *x = static_cast<const uint16_t *>(logits);
+    return rows_are_whole(x) ? choose(masked_argmax_kernel<uint16_t, true>, x) : choose(masked_argmax_kernel<uint16_t, false>, x);
 }
 
 template <typename Elem>
@@ -863,9 +868,9 @@ static hipError_t topk(const Elem *logits, uint32_t B, uint32_t V, int64_t row_s
 {
     const uint32_t W = (V + 31u) / 32u;
     if (topk_by_row(B, V, k, sizeof(Elem)))
-        return launch(masked_topk_kernel<Elem>, dim3(B), dim3(kThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, ids, values, ninf);
+        return launch(rows_are_whole(logits) ? masked_topk_kernel<Elem, true> : masked_topk_kernel<Elem, false>, dim3(B), dim3(kThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, ids, values, ninf);
     const uint32_t n_slices = (V + kTopkSlice - 1u) / kTopkSlice;
-    const hipError_t e = launch(topk_slice_kernel<Elem>, dim3(n_slices, B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, lists);
+    const hipError_t e = launch(rows_are_whole(logits) ? topk_slice_kernel<Elem, true> : topk_slice_kernel<Elem, false>, dim3(n_slices, B), dim3(kSliceThreads), 0, s, nullptr, logits, row_stride, V, W, bitmask, k, lists);
     if (e != hipSuccess) return e;
     constexpr uint32_t kMost = kTopkMergeKeys / kSliceThreads;
     const uint32_t held = (n_slices * k + kSliceThreads - 1u) / kSliceThreads;

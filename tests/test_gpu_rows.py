@@ -425,6 +425,46 @@ def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
         assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
 
 
+@pytest.mark.parametrize("dtype,byte", [("bf16", 1), ("bf16", 3), ("f32", 1), ("f32", 2), ("f32", 3)])
+@pytest.mark.parametrize("B,V,pad", [(3, 1, 0), (5, 3, 1), (5, 9, 0), (5, 4097, 2), (7, 8192, 1), (6, 8193, 0), (33, 20011, 1), (40, 57347, 3), (40, 114690, 1),
+                                     (9, 100003, 0), (2, 262143, 1), (2, 262149, 0)])
+def test_sampling_of_rows_at_odd_bytes(torch_cuda, B, V, pad, dtype, byte):
+    """masked_argmax and masked_topk where logits do not lie at multiples of their size: rows of one piece, of pieces and a part, of
+    several segments of the mask, whole and in slices, through the C ABI (no tensor has such an address)."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    L, code, e = wg.load_library(), wg.F32 if dtype == "f32" else wg.BF16, 4 if dtype == "f32" else 2
+    rng = np.random.default_rng(V + B + byte)
+    x = rng.standard_normal((B, V + pad)).astype(np.float32)
+    x[:, rng.integers(0, V, V // 20)] = np.nan
+    x[0] = np.round(x[0])                                           # ties, zeros of both signs
+    x[1, V - 1] = 60.0                                              # the last token, in the part of a piece
+    host = x if dtype == "f32" else ws.to_bf16_bits(x)
+    bits = rng.integers(0, 1 << 32, (B, (V + 31) // 32), dtype=np.uint32)
+    bits[1] = 0xFFFFFFFF
+    if V % 32:
+        bits[:, -1] &= np.uint32((1 << (V % 32)) - 1)
+    if B > 3:
+        bits[3] = 0
+    raw = np.concatenate([np.full(byte, 0x7F, np.uint8), np.ascontiguousarray(host).view(np.uint8).ravel(), np.full(64, 0x7F, np.uint8)])
+    buf = torch.from_numpy(raw).cuda()
+    assert buf.data_ptr() % 16 == 0
+    mask = torch.from_numpy(bits.view(np.int32)).cuda()
+    rows, stream = np.ascontiguousarray(host[:, :V]), torch.cuda.current_stream().cuda_stream
+    tok = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    assert L.wg_masked_argmax(buf.data_ptr() + byte, code, B, V, V + pad, mask.data_ptr(), tok.data_ptr(), stream) == 0
+    assert (tok.cpu().numpy() == O.masked_argmax(rows, bits)).all()
+    for k in (1, 20, 64):
+        ids = torch.empty((B, k), dtype=torch.int32, device="cuda")
+        vals = torch.empty((B, k), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        work = torch.empty(wg.masked_topk_workspace(B, V, k), dtype=torch.uint8, device="cuda")
+        assert L.wg_masked_topk(buf.data_ptr() + byte, code, B, V, V + pad, mask.data_ptr(), k, ids.data_ptr(), vals.data_ptr(),
+                                work.data_ptr(), work.numel(), stream) == 0
+        want_ids, want_vals = O.masked_topk(rows, bits, k)
+        assert (ids.cpu().numpy() == want_ids).all(), k
+        assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,V,off", [(5, 32768, 0), (5, 32777, 1), (39, 114688, 1), (40, 114688, 0), (5, 163840, 3), (48, 57344, 0), (56, 65537, 2),
                                      (80, 81921, 0), (64, 131071, 1), (5, 262143, 3), (5, 262144, 1)])
