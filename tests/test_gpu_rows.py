@@ -425,6 +425,41 @@ def test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype):
         assert (H.host_logit_bits(vals) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all(), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,V,off", [(5, 8192, 0), (5, 8193, 1), (5, 12288, 0), (5, 12289, 0), (5, 12285, 3), (5, 16384, 0), (5, 24576, 0), (5, 24577, 0), (5, 24569, 7),
+                                     (3, 98304, 0), (3, 98305, 0), (2, 196608, 0), (2, 196610, 1)])
+def test_sampling_either_side_of_one_round(torch_cuda, B, V, off, dtype):
+    """Rows, and shares of cut rows, of one, two and three pieces of a thread, of a piece more and where a row that begins
+    inside a block has one more."""
+    test_sampling_of_cut_and_whole_rows(torch_cuda, B, V, off, dtype)
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 262145), ("bf16", 286720), ("bf16", 286729), ("f32", 262149), ("f32", 274433)])
+def test_sampling_of_whole_rows_of_two_segments(torch_cuda, V, dtype):
+    """Rows whose mask comes to LDS in two turns, the second a single piece, one round and more than one."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    B, few = 130, 6
+    g = torch.Generator(device="cuda").manual_seed(V)
+    x = torch.randn((B, V), generator=g, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    x[1, V - 1], x[2, 262143], x[3, 262144] = 50.0, 50.0, 50.0
+    bits = torch.randint(-2 ** 31, 2 ** 31, (B, (V + 31) // 32), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    bits[1:4] = -1
+    bits[4] = 0
+    if V % 32:
+        bits[:, -1] &= (1 << (V % 32)) - 1
+    host, masks = H.host_logit_bits(x[:few]), H.host_mask(bits[:few])
+    host = host.view(np.float32) if dtype == "f32" else host
+    tok = torch.empty(B, dtype=torch.int32, device="cuda")
+    ids, vals = torch.empty((B, 9), dtype=torch.int32, device="cuda"), torch.empty((B, 9), dtype=x.dtype, device="cuda")
+    wg.masked_argmax(x, bits, tok)
+    wg.masked_topk(x, bits, ids, vals, torch.empty(wg.masked_topk_workspace(B, V, 9), dtype=torch.uint8, device="cuda"))
+    want_ids, want_vals = O.masked_topk(host, masks, 9)
+    assert (ids[:few].cpu().numpy() == want_ids).all() and (tok[:few].cpu().numpy() == want_ids[:, 0]).all()
+    assert (H.host_logit_bits(vals[:few]) == np.ascontiguousarray(want_vals).view(np.uint32 if dtype == "f32" else np.uint16)).all()
+    assert torch.equal(tok, ids[:, 0])
+
+
 @pytest.mark.parametrize("dtype,byte", [("bf16", 1), ("bf16", 3), ("f32", 1), ("f32", 2), ("f32", 3)])
 @pytest.mark.parametrize("B,V,pad", [(3, 1, 0), (5, 3, 1), (5, 9, 0), (5, 4097, 2), (7, 8192, 1), (6, 8193, 0), (33, 20011, 1), (40, 57347, 3), (40, 114690, 1),
                                      (9, 100003, 0), (2, 262143, 1), (2, 262149, 0)])
