@@ -1385,13 +1385,16 @@ static bool masks_through(const void *logits, int dtype, uint32_t B, uint32_t V)
 //   1.00, 128 1.03 1.02; 65536 B = 24 0.93 0.96, 64 0.95 0.99, 96 1.01 1.01; with 32 / with 16, 151936 B = 16 0.96 0.97, 32 0.96
 //   0.99, 48 1.03 1.02; mixed, us with 8 / 16 / 32, 151936 B = 1 11.3 / 9.7 / 8.8 and 8.3 / 6.8 / 6.0
 // Up to a workgroup per unit as many as a row has groups (kPartGroup): with 16 or 32 / with 8, made rows, 8000 (4 / 2) B = 64 0.93, 20000
-// B = 8 0.97, 32000 B = 1 0.95, 50257 B = 6 0.94, 90000 B = 4 0.97; copied ones are a launch either way.
+// B = 8 0.97, 32000 B = 1 0.95, 50257 B = 6 0.94, 90000 B = 4 0.97; copied ones are a launch either way
+// (but for the masks alone of up to 8 requests, 32 / 16 shares, V = 50257 to 128256: 4.25 / 4.12 us copied, 0.91 to 1.02 of it made).
 // Fewer where a short row would be cut into scraps: with 4 / 2, V = 12000 B = 64 11.1 / 11.5 and 6.9 / 7.1.  Above a request per unit a share
-// pays for what it starts with only with 12,288 tokens, once there are more than eight workgroups to a unit.  wg_decode_step on outlines,
-// mixed, random trees, time to that of 3,072 tokens, rows made and rows copied: B = 400 V = 24576 0.79 0.91, 32000 0.85 0.95, 50257 0.90 0.98,
-// 65536 0.92 0.99, 90000 0.91 1.00; B = 800 16000 0.86 0.96, 32000 (44 us made, 18 copied) 0.73 0.87, 50257 0.83 0.93, 90000 0.91 0.99; B = 2048
-// 8000 0.84 0.96, 32000 0.64 0.83, 65536 0.97 1.03, 90000 0.96 0.99; with 4 / 8, 100003 B = 400 0.96 1.00, 1000 1.01 1.00 (random trees later),
-// 151936 B = 1000 1.06 1.02.
+// pays for what it starts with the more, the more workgroups wait for a place; but what takes longest to make (states of random trees with
+// thousands of candidates) takes longer still in longer shares, while the units that are done wait for it.  So a share has 1.25 tokens per workgroup of
+// the call (of 256 units), 3,072 at least, 12,288 at most.  Cold wg_fill_masks on outlines, JSON, mixed, random trees, 4 shares / 8: B = 400 V =
+// 24576 (24 us with 8) 0.78 0.79 0.82 0.80; 512 32000 0.81 0.77 0.84 0.83, 40000 0.80 0.79 0.77 0.88; 1024 50257 0.78 0.80 0.77 0.97, 65536 0.77 0.75
+// 0.77 1.06; 2 / 8, 2048 32000 (68 us with 8) 0.51 0.57 0.58 0.60; copied rows 0.5 to 0.9.  Random trees, 4 / 8, mean and worst of six sets, on this
+// side of the line: B = 512 V = 40000 0.92 0.99, 700 50257 0.91 0.99, 1000 65536 0.91 0.99; beyond it: 257 50257 1.10 1.22, 65536 1.20 1.37, 90000 1.32
+// 1.43; 400 65536 1.12 1.29, 90000 1.18 1.36; 700 65536 1.04 1.15 (outlines there 0.75 to 1.0).
 // Fewer too where the lookup that each repeats is most of a short share's work: up to a request per unit and more than
 // seven workgroups on one (above, rows are looked up once).  With 8 / 4, B = 256, kernel us of wg_decode_step on outlines, JSON,
 // mixed, random trees: copied V = 24576 9.3 9.5 9.7 9.5 / 9.0 9.0 9.3 9.3 (a lookup kernel and 8 shares: 9.3 10.0 9.8 12.1), 32768 10.8
@@ -1408,8 +1411,8 @@ static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
     }
     if (parts == kLeastParts && B <= n_cu && B * parts > 7u * n_cu && V <= parts * 4096u) parts >>= 1;
     for (; parts > 1u; parts >>= 1) {
-        const uint64_t n = (uint64_t)B * parts;
-        if (parts * (B > n_cu ? (n > 8ull * n_cu ? 12288u : 3072u) : n > n_cu ? 2560u : kPartGroup / 2u) <= V) break;
+        const uint64_t n = (uint64_t)B * parts, busy = n * 320u / n_cu;
+        if (parts * (B > n_cu ? (busy < 3072u ? 3072u : busy > 12288u ? 12288u : (uint32_t)busy) : n > n_cu ? 2560u : kPartGroup / 2u) <= V) break;
     }
     return parts;
 }

@@ -258,6 +258,12 @@ def test_decode_step_at_the_edges_of_few_and_of_many_rows(torch_cuda, V, B):
     test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B)
 
 
+@pytest.mark.parametrize("V,B", [(40959, 512), (40960, 512), (65599, 820), (65600, 820), (20479, 1024), (20480, 1024), (28800, 360), (28799, 360)])
+def test_decode_step_where_shares_grow_with_the_batch(torch_cuda, V, B):
+    """Above a request per compute unit either side of where a row is cut into fewer shares for the workgroups of the call."""
+    test_decode_step_at_the_edges_of_the_split(torch_cuda, V, B)
+
+
 @pytest.mark.parametrize("V,B", [(12001, 1), (20011, 31), (30000, 129), (98304, 96), (151936, 64), (20011, 255), (20011, 256), (20011, 257), (40000, 256)])
 def test_keys_of_many_requests_of_one_call(torch_cuda, V, B):
     """Every workgroup of a row looks it up by itself up to a request per compute unit, and several make
