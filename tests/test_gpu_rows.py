@@ -133,6 +133,12 @@ def test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad, m is None)
 
 
+@pytest.mark.parametrize("dtype,V,B", [("bf16", 32768, 16), ("bf16", 32769, 16), ("f32", 16384, 16), ("f32", 16385, 16), ("f32", 1021, 256), ("f32", 1021, 257), ("f32", 1027, 257)])
+def test_masking_either_side_of_the_least_that_goes_through_the_l2(torch_cuda, dtype, V, B):
+    """1 MiB of logits, as above."""
+    test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V", [257, 2049, 16385, 40003, 131073])
 def test_masking_of_rows_with_one_token_disallowed(torch_cuda, V, dtype):
