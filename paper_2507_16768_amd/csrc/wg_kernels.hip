@@ -683,7 +683,7 @@ struct RowShared {
     uint32_t queue[kRowWaves][64u * (kRowBatch + 1u)];   // tokens to decide: id | length << 24
     uint32_t n_ranges, total;
     RowTask task;                              // what the row's lookup left; two kernels: its successors only
-    uint32_t ref;
+    uint32_t key, ref;                         // the row's key, and what its lookup found
     wg_state_t state;                          // the request's, advanced
     StateDesc desc;                            // of its state
     Claim claim;
@@ -1093,14 +1093,14 @@ rows_kernel(WG_EARLY_ARGS)
             asked = ask(T, Cc, sid, aux, d);
             if (tid == 0) {
                 sh.state = wg_state_t{sid, aux};
-                sh.ref = asked.key;
+                sh.key = asked.key;
                 sh.desc = d;
             }
         } else if (wave >= 2u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
         __syncthreads();
         // (key k has arena row k: the row is requested while its tag is looked at, and what a missing row takes from the
         // state's own class table)
-        const uint32_t key = of_first(sh.ref);
+        const uint32_t key = of_first(sh.key);
         if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
         if (late.rows > kTicketGroup && group_last(ticket, b, late.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
         if (wave == 1u && is_checkpoint(of_first(sh.desc.kind_byte) & 0xFFu)) stage_class(T, sh, of_first(sh.desc.cls), tid & 63u);
