@@ -1076,10 +1076,11 @@ rows_kernel(WG_EARLY_ARGS)
             const unsigned long long launch = Cc.ctr->launch;
             const wg_state_t st = states[b];
             if (tokens) t = of_first((uint32_t)tokens[b]);
-            // (in one wait with them: the call's number, and a word of each line of the arguments, so that whoever reads
-            // them later does not wait for memory)
-            asm volatile("" :: "s"(launch), "s"(late.T.lit), "s"(late.Vc.rows), "s"(late.Cc.tags), "s"(late.Cc.tasks), "s"(late.rows));
             sid = of_first(st.sid); aux = of_first(st.aux);
+            // The state and the call's number have to be here before the row's ticket counts this workgroup: the last one of the row
+            // replaces the state, the last one of the call the number (close_row, close_call).  In one wait with them a word of each line of the
+            // arguments, so that whoever reads them later does not wait for memory.
+            asm volatile("" :: "s"(launch), "s"(sid), "s"(aux), "s"(late.T.lit), "s"(late.Vc.rows), "s"(late.Cc.tags), "s"(late.Cc.tasks), "s"(late.rows));
             if (tid == 0) sh.launch = launch;
         }
         __syncthreads();

@@ -1,16 +1,45 @@
-"""What the kernels rely on without the hardware's or the compiler's word, checked on the source.  CPU only."""
+"""What the kernels rely on without the hardware's or the compiler's word, checked on the source and on the code that the compiler
+makes of it.  CPU only."""
 import os
 import re
+import subprocess
 
 from paper_2507_16768_amd import build
 
 KERNELS = os.path.join(build.CSRC, "wg_kernels.hip")
 
 
+def _compile(source, *more):
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC") and not f.startswith("-Wl,")]
+    return subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags + ["--cuda-device-only"] + list(more) + [source],
+                          capture_output=True, text=True, timeout=300)
+
+
 def _body(text, name):
     """The text of a function template, from its name to the closing brace in the first column."""
     at = text.index("\n%s(" % name)
     return text[at:text.index("\n}\n", at)]
+
+
+def test_a_row_is_not_written_back_before_it_is_read(tmp_path):
+    """The last workgroup of a row to take its ticket writes the row's state while others are still at work: what each reads of the state has to
+    have arrived before its ticket counts, which is behind the first barrier."""
+    head = _body(open(KERNELS).read(), "rows_kernel").split("__syncthreads();")[0]
+    waits = [line for line in head.splitlines() if "asm volatile" in line]
+    assert len(waits) == 1 and all('"s"(%s)' % x in waits[0] for x in ("launch", "sid", "aux")), waits
+    out = str(tmp_path / "kernels.s")
+    r = _compile(KERNELS, "-S", "-o", out)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = open(out).read()
+    names = re.findall(r"^(_ZN2wg11rows_kernelI.*Lb1EE\S*):", text, re.M)
+    assert len(names) == 5
+    for name in names:
+        at = text.index("\n%s:" % name)
+        code = [line.split(";")[0].strip() for line in text[at:text.index("s_barrier", at)].splitlines()]
+        code = [c for c in code if c]
+        for load, count in ((("s_load", "ds_"), "lgkmcnt(0)"), (("global_load", "flat_load", "buffer_load"), "vmcnt(0)")):
+            last = max([i for i, c in enumerate(code) if c.startswith(load)], default=-1)
+            assert last < 0 or any(c.startswith("s_waitcnt") and count in c for c in code[last:]), (name, count)
 
 
 def test_words_of_lds_are_not_rewritten_while_they_are_read():
