@@ -7,11 +7,12 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwgrammar.so")
 SOURCES = ["wg_api.cpp", "wg_lower.cpp", "wg_regex.cpp", "wg_vocab_index.cpp", "wg_kernels.hip", "wg_sample.hip"]
 HEADERS = ["wg_internal.h", "wg_buffer.h", "wg_device.h", "wg_launch.h", "wg_order.h", os.path.join("..", "..", "include", "wg.h")]
+# a kernel's first dwords of arguments are in scalar registers when its wavefronts begin
+PRELOADED_DWORDS = 14
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          # packed-fp32 instruction selection is switched off for every kernel in this library
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         # a kernel's first 14 dwords of arguments are in scalar registers when its wavefronts begin
-         "-Xarch_device", "-mllvm=-amdgpu-kernarg-preload-count=14",
+         "-Xarch_device", "-mllvm=-amdgpu-kernarg-preload-count=%d" % PRELOADED_DWORDS, "-DWG_PRELOADED_DWORDS=%d" % PRELOADED_DWORDS,
          # found by its name next to the Python module, wherever the tree lies
          "-Wl,-soname,libwgrammar.so"]
 

@@ -39,7 +39,17 @@ struct LateArgs {
 };
 #define WG_EARLY_ARGS wg_state_t *__restrict__ states, const int32_t *__restrict__ tokens, Control *ctr, const StateDesc *descs, \
                       const uint64_t *chunks, const uint8_t *len8, uint32_t n_states, uint32_t V, LateArgs
-constexpr uint32_t kEarlyBytes = 6u * 8u + 2u * 4u;
+// Where the last of a kernel's arguments lies in its argument memory.
+template <typename... P>
+constexpr uint32_t last_argument(void (*)(P...))
+{
+    size_t at = 0, last = 0;
+    ((last = (at + alignof(P) - 1) / alignof(P) * alignof(P), at = last + sizeof(P)), ...);
+    return (uint32_t)last;
+}
+typedef void StepKernel(WG_EARLY_ARGS);
+constexpr uint32_t kEarlyBytes = last_argument(static_cast<StepKernel *>(nullptr));
+static_assert(kEarlyBytes == 4u * WG_PRELOADED_DWORDS, "the early arguments are those that are preloaded (build.py), the late ones lie right behind them");
 typedef const __attribute__((address_space(4))) LateArgs Late;
 template <typename M> using LateRef = const __attribute__((address_space(4))) M &;
 __device__ __forceinline__ Late &late_args()

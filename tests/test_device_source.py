@@ -1,8 +1,11 @@
 """What the kernels rely on without the hardware's or the compiler's word, checked on the source and on the code that the compiler
-makes of it.  CPU only."""
+makes of it: where arguments lie, what is waited for before a barrier, which words of LDS are exchanged between barriers.  CPU only."""
 import os
 import re
+import shutil
 import subprocess
+
+import pytest
 
 from paper_2507_16768_amd import build
 
@@ -19,6 +22,22 @@ def _body(text, name):
     """The text of a function template, from its name to the closing brace in the first column."""
     at = text.index("\n%s(" % name)
     return text[at:text.index("\n}\n", at)]
+
+
+@pytest.mark.parametrize("old,new", [("uint32_t n_states, uint32_t V, LateArgs", "uint32_t n_states, uint32_t V, uint32_t more, LateArgs"),
+                                     ("const uint8_t *len8, uint32_t n_states", "uint32_t n_states"),
+                                     ("struct LateArgs {", "struct alignas(16) LateArgs {")])
+def test_arguments_that_would_lie_elsewhere_do_not_compile(tmp_path, old, new):
+    """The late arguments are read at an offset behind the early ones, and the early ones are in registers: one more, one less and a
+    wider alignment are refused."""
+    shutil.copytree(build.CSRC, tmp_path / "library" / "csrc")
+    shutil.copytree(os.path.join(build.HERE, "..", "include"), tmp_path / "include")
+    path = tmp_path / "library" / "csrc" / "wg_kernels.hip"
+    text = path.read_text()
+    assert text.count(old) == 1
+    path.write_text(text.replace(old, new))
+    r = _compile(str(path), "-fsyntax-only")
+    assert r.returncode != 0 and "early arguments" in r.stderr, r.stderr[-2000:]
 
 
 def test_a_row_is_not_written_back_before_it_is_read(tmp_path):
