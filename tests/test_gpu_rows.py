@@ -103,10 +103,8 @@ def test_masking_at_every_alignment(torch_cuda, V, dtype):
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad)     # nothing outside the rows either
 
 
-@pytest.mark.parametrize("dtype,V,B", [("bf16", 100003, 209), ("bf16", 100003, 210), ("bf16", 99904, 210), ("f32", 41003, 255), ("f32", 41003, 256), ("f32", 20011, 524), ("f32", 20011, 525)])
-def test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B):
-    """40 MiB of logits: rows at lines and inside them, by themselves and from the rows' kernel (one kernel and two)."""
-    torch = torch_cuda
+def _mask_by_itself_and_from_a_fill(torch, dtype, V, B):
+    """Rows at lines and inside them, by wg_apply_mask and from the rows' kernel."""
     import paper_2507_16768_amd as wg
     dt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
     w = ws.make_workload(4, V=V, B=B, steps=2)
@@ -133,10 +131,20 @@ def test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B
             assert torch.equal(buf.view(bits), want.view(bits)), (off, pad, m is None)
 
 
-@pytest.mark.parametrize("dtype,V,B", [("bf16", 32768, 16), ("bf16", 32769, 16), ("f32", 16384, 16), ("f32", 16385, 16), ("f32", 1021, 256), ("f32", 1021, 257), ("f32", 1027, 257)])
-def test_masking_either_side_of_the_least_that_goes_through_the_l2(torch_cuda, dtype, V, B):
+@pytest.mark.parametrize("dtype,V,B,through", [("bf16", 100003, 209, True), ("bf16", 100003, 210, False), ("bf16", 99904, 209, True), ("bf16", 99904, 210, False), ("f32", 41003, 255, True),
+                                               ("f32", 41003, 256, False), ("f32", 20011, 523, True), ("f32", 20011, 524, False), ("f32", 20011, 525, False)])
+def test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B, through):
+    """40 MiB of logits, in one kernel and, above a request per compute unit, in two."""
+    assert (B * V * (4 if dtype == "f32" else 2) <= 40 << 20) == through
+    _mask_by_itself_and_from_a_fill(torch_cuda, dtype, V, B)
+
+
+@pytest.mark.parametrize("dtype,V,B,through", [("bf16", 32768, 16, False), ("bf16", 32769, 16, True), ("f32", 16384, 16, False), ("f32", 16385, 16, True), ("f32", 1020, 257, False),
+                                               ("f32", 1021, 257, True), ("bf16", 2040, 257, False), ("bf16", 2041, 257, True)])
+def test_masking_either_side_of_the_least_that_goes_through_the_l2(torch_cuda, dtype, V, B, through):
     """1 MiB of logits, as above."""
-    test_masking_either_side_of_what_goes_through_the_l2(torch_cuda, dtype, V, B)
+    assert (B * V * (4 if dtype == "f32" else 2) > 1 << 20) == through
+    _mask_by_itself_and_from_a_fill(torch_cuda, dtype, V, B)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
