@@ -741,10 +741,12 @@ int wg_cache_stats(wg_handle_t h, wg_cache_stats_t *host_out) {
 
 int wg_error_count(wg_handle_t h, uint64_t *host_out) {
     if (!h || !host_out) return fail(WG_ERR_INVALID, "wg_error_count: null argument");
-    Counters c;
+    unsigned long long spread[kSpread * kSpreadStride];
     WG_HIP(hipDeviceSynchronize());
-    WG_HIP(hipMemcpy(&c, h->dc.ctr, sizeof c, hipMemcpyDeviceToHost));
-    *host_out = c.errors;
+    WG_HIP(hipMemcpy(spread, h->dc.ctr->spread, sizeof spread, hipMemcpyDeviceToHost));
+    uint64_t n = 0;
+    for (uint32_t i = 0; i < kSpread; i++) n += spread[i * kSpreadStride + kSpreadErrors];
+    *host_out = n;
     return WG_OK;
 }
 

@@ -71,7 +71,7 @@ struct Counters {
     unsigned long long slot_ctr; // generation << 32 | arena rows in use in that generation (<= cap_rows); not kept up while
                                  // the arena is addressed by key
     unsigned long long launch;   // number of the fill call in flight (its last kernel counts it up)
-    unsigned long long lookups, builds, uncached_builds, class_scans, errors;
+    unsigned long long lookups, builds, uncached_builds, class_scans;
     unsigned long long held;     // keys that hold a row, when last counted (launch_count_rows)
 };
 
@@ -92,7 +92,8 @@ constexpr uint32_t kMaxRows = 1u << 30, kMaxKeys = 0x7FFFFFFEu;
 constexpr uint32_t kMaxBatch = 65535u;     // requests of a call (grid.y)
 // Statistics that many workgroups add to are spread over 64 cache lines, a counter of each in every one.
 constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadHits = 1,
-                   kSpreadBuilds = 2, kSpreadClasses = 3;       // of fills with the arena addressed by key
+                   kSpreadBuilds = 2, kSpreadClasses = 3,       // of fills with the arena addressed by key
+                   kSpreadErrors = 4;                           // rejected tokens
 constexpr uint32_t kTicketStride = 32, kTicketGroup = 16;       // a 128-byte line for the tickets of a row; rows of a group
 constexpr uint32_t kOneKernelRows = 512;                        // most rows of a fill in one kernel
 

@@ -119,6 +119,28 @@ def test_advance_of_more_requests_than_the_grid_holds(torch_cuda):
     assert torch.equal(big, torch.from_numpy(want.view(np.int32)).cuda().repeat(B // 16 + 1, 1)[:B])
 
 
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 256, 257, 1000, 70000])
+def test_rejected_tokens_are_counted(torch_cuda, B):
+    """Each of them once, through wg_advance and through the fills that advance (in one kernel, whose workgroups all walk the token, and in
+    two); requests that are in ERROR already count again."""
+    torch = torch_cuda
+    w = ws.make_workload(4, V=20011, B=8, steps=1)
+    v, h = H.make_gpu(w)
+    start = H.dev_states(np.array([[h.start_states[0][0], 0]], dtype=np.uint32)).repeat(B, 1)
+    bad = (torch.arange(B, device="cuda") % 3 != 1).to(torch.int32)          # the template's first byte is no 0x00 token and no id above V
+    tokens = torch.where(bad == 1, torch.where(torch.arange(B, device="cuda") % 2 == 0, 0, 1 << 30), -7).to(torch.int32)
+    st = start.clone()
+    h.advance(st, tokens)
+    assert h.error_count() == B and bool((st[:, 0] == -1).all())
+    h.advance(st, tokens)
+    assert h.error_count() == 2 * B
+    if B <= h.max_batch():
+        mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+        st = start.clone()
+        h.advance_fill_masks(st, tokens, mask)
+        assert h.error_count() == 3 * B and bool((st[:, 0] == -1).all()) and not bool(mask.any())
+
+
 @pytest.mark.parametrize("B", [1, 511, 512, 513, 1025])
 @pytest.mark.parametrize("cap", [1, 63, 64, 65, 300])
 def test_forced_bytes_longer_than_a_wavefront(torch_cuda, B, cap):
