@@ -698,7 +698,7 @@ int wg_forced_bytes(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint3
                     uint32_t *d_lens, wg_state_t *d_end_states, void *stream) {
     if (!h || !d_states || !d_bytes || !d_lens) return fail(WG_ERR_INVALID, "wg_forced_bytes: null argument");
     if (B == 0 || cap == 0) return fail(WG_ERR_INVALID, "wg_forced_bytes: B or cap is 0");
-    WG_HIP(launch_forced_bytes(h->dt, d_states, B, cap, d_bytes, d_lens, d_end_states, static_cast<hipStream_t>(stream)));
+    WG_HIP(launch_forced_bytes(h->dt, d_states, B, cap, d_bytes, d_lens, d_end_states, h->n_cu, static_cast<hipStream_t>(stream)));
     return WG_OK;
 }
 

@@ -168,7 +168,7 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
                           wg_state_t *states, const int32_t *tokens, uint32_t B, uint32_t n_cu, hipStream_t s,
                           hipEvent_t *ev);
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
-                               uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, hipStream_t s);
+                               uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, uint32_t n_cu, hipStream_t s);
 hipError_t launch_select(const uint32_t *bitmask, uint32_t B, uint32_t V, const uint64_t *draws,
                          int32_t *tokens, hipStream_t s);
 

@@ -1318,6 +1318,28 @@ forced_bytes_kernel(const wg_state_t *__restrict__ states, const StateDesc *__re
     }
 }
 
+// The same by a thread per request, for batches whose wavefronts would have to take turns (launch_forced_bytes).
+__global__ void __launch_bounds__(64)
+forced_bytes_of_many_kernel(const wg_state_t *__restrict__ states, const StateDesc *__restrict__ descs, const uint8_t *__restrict__ lit,
+                            uint8_t *__restrict__ bytes, uint32_t *__restrict__ lens, wg_state_t *__restrict__ end_states,
+                            uint32_t n_states, uint32_t cap, uint32_t B)
+{
+    for (uint64_t b = (uint64_t)blockIdx.x * 64u + threadIdx.x; b < B; b += (uint64_t)gridDim.x * 64u) {
+        const wg_state_t st = states[b];
+        uint32_t sid = st.sid, n = 0;
+        while (n < cap && sid < n_states) {
+            const StateDesc d = descs[sid];
+            if ((d.kind_byte & 0xFFu) != WG_KIND_LIT) break;
+            const uint32_t m = d.run < cap - n ? d.run : cap - n;
+            for (uint32_t i = 0; i < m; i++) bytes[b * cap + n + i] = lit[sid + i];
+            n += m;
+            sid = m == d.run ? d.cls : sid + m;              // d.cls: state after the Write
+        }
+        lens[b] = n;
+        if (end_states) end_states[b] = wg_state_t{sid, n ? 0u : st.aux};
+    }
+}
+
 // One block per row: d_tokens[b] = index of the (draw mod popcount)-th set bit.
 __global__ void __launch_bounds__(256)
 select_kernel(const uint32_t *__restrict__ bitmask, uint32_t W, const uint64_t *__restrict__ draws,
@@ -1568,11 +1590,18 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
     return launch(advance_kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, ev, WG_EARLY_VALUES, LateArgs{T, Vc, Cc, nullptr, nullptr, 0, 0u, waves, B});
 }
 
+// A wavefront per request up to 32 requests to a unit, which are resident together.  A wavefront / a thread each, us, outlines, JSON, mixed,
+// random trees: B = 4,096 2.8 2.8 2.9 3.4 / 2.9 2.7 3.3 7.0; 8,192 3.3 3.3 3.4 4.1 / 2.9 2.7 3.3 7.1; 16,384 4.2 4.2 4.6 5.3 / 3.1 2.7 3.3 5.8; 60,000 9.4 9.3
+// 10.9 12.9 / 3.1 2.9 3.6 6.4.
 hipError_t launch_forced_bytes(const DeviceTable &T, const wg_state_t *states, uint32_t B, uint32_t cap,
-                               uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, hipStream_t s)
+                               uint8_t *bytes, uint32_t *lens, wg_state_t *end_states, uint32_t n_cu, hipStream_t s)
 {
-    const uint32_t waves = B <= 512u ? 1u : 4u, blocks = cdiv(B, waves);
-    return launch(forced_bytes_kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, nullptr, states, T.states, T.lit, bytes, lens, end_states, T.n_states, cap, B);
+    auto run = [&](auto kernel, uint32_t requests, uint32_t threads) {
+        const uint32_t blocks = cdiv(B, requests);
+        return launch(kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(threads), 0, s, nullptr, states, T.states, T.lit, bytes, lens, end_states, T.n_states, cap, B);
+    };
+    if (B > 32u * n_cu) return run(forced_bytes_of_many_kernel, 64u, 64u);
+    return B <= 2u * n_cu ? run(forced_bytes_kernel, 1u, 64u) : run(forced_bytes_kernel, 4u, 256u);
 }
 
 hipError_t launch_select(const uint32_t *bitmask, uint32_t B, uint32_t V, const uint64_t *draws,

@@ -118,7 +118,7 @@ hipError_t launch_masked_topk(const void *, int, uint32_t, uint32_t, int64_t, co
                               hipStream_t) { return hipSuccess; }
 hipError_t launch_advance(const DeviceTable &, const DeviceVocab &, const DeviceCache &, wg_state_t *, const int32_t *, uint32_t, uint32_t, hipStream_t,
                           hipEvent_t *) { return hipSuccess; }
-hipError_t launch_forced_bytes(const DeviceTable &, const wg_state_t *, uint32_t, uint32_t, uint8_t *, uint32_t *, wg_state_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_forced_bytes(const DeviceTable &, const wg_state_t *, uint32_t, uint32_t, uint8_t *, uint32_t *, wg_state_t *, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_select(const uint32_t *, uint32_t, uint32_t, const uint64_t *, int32_t *, hipStream_t) { return hipSuccess; }
 
 }  // namespace wg

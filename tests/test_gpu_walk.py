@@ -141,6 +141,13 @@ def test_rejected_tokens_are_counted(torch_cuda, B):
         assert h.error_count() == 3 * B and bool((st[:, 0] == -1).all()) and not bool(mask.any())
 
 
+@pytest.mark.parametrize("B", [8191, 8192, 8193, 70001])
+@pytest.mark.parametrize("cap", [1, 65, 300])
+def test_forced_bytes_of_many_requests(torch_cuda, B, cap):
+    """A wavefront per request and, above 32 requests to a unit, a thread."""
+    test_forced_bytes_longer_than_a_wavefront(torch_cuda, B, cap)
+
+
 @pytest.mark.parametrize("B", [1, 511, 512, 513, 1025])
 @pytest.mark.parametrize("cap", [1, 63, 64, 65, 300])
 def test_forced_bytes_longer_than_a_wavefront(torch_cuda, B, cap):
