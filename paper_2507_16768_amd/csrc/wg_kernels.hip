@@ -307,19 +307,31 @@ __device__ __forceinline__ void advance_one(const TableView &T, const VocabView 
 }
 
 // One request to a workgroup up to two on a compute unit, four above: with one / with four, mixed, us, B = 64 3.17 / 3.32, 256
-// 3.20 / 3.38, 512 3.40 / 3.48, 1024 3.49 / 3.62, 8192 5.58 / 5.22.
+// 3.20 / 3.38, 512 3.40 / 3.48, 1024 3.49 / 3.62, 8192 5.58 / 5.22.  The first request's state and token come in one wait with the arguments that follow the
+// early ones (one after the other, a copy of the states and wg_advance, B = 1 4.2, now 4.0, 64 4.4, 4.3).  Batches of 16,384 and 60,000 take 6.6 to
+// 7.5 and 19 to 20 us, a thread each with eight bytes at a time took 6.1 to 8.6 and 13 to 19.
 constexpr uint32_t kAdvanceBlocks = 1u << 20;
-__global__ void __launch_bounds__(256)
+template <uint32_t kWaves>
+__global__ void __launch_bounds__(64 * kWaves)
 advance_kernel(WG_EARLY_ARGS)
 {
     WG_VIEWS;
-    const uint32_t waves = late.shares, B = late.rows;       // (requests of a workgroup here)
-    // (wg_advance takes any number of requests: more than the grid holds come in turn)
-    for (uint64_t b = (uint64_t)blockIdx.x * waves + of_first(threadIdx.x >> 6); b < B; b += (uint64_t)gridDim.x * waves) {
-        uint32_t sid = of_first(states[b].sid), aux = of_first(states[b].aux);
+    uint64_t b = (uint64_t)blockIdx.x * kWaves + (kWaves > 1u ? of_first(threadIdx.x >> 6) : 0u);
+    if (kWaves > 1u && b >= late.rows) return;
+    wg_state_t st = states[b];
+    uint32_t t = of_first((uint32_t)tokens[b]);
+    // (in one wait with them a word of each line of the arguments)
+    asm volatile("" :: "s"(of_first(st.sid)), "s"(t), "s"(late.T.lit), "s"(late.Vc.n_chunks), "s"(late.Cc.tags), "s"(late.rows));
+    for (;;) {
+        uint32_t sid = of_first(st.sid), aux = of_first(st.aux);
         StateDesc d;
-        advance_one(T, Vc, Cc, sid, aux, d, (int32_t)of_first((uint32_t)tokens[b]), true, (uint32_t)b);
+        advance_one(T, Vc, Cc, sid, aux, d, (int32_t)t, true, (uint32_t)b);
         if ((threadIdx.x & 63u) == 0u) states[b] = wg_state_t{sid, aux};
+        // (wg_advance takes any number of requests: more than the grid holds come in turn)
+        b += (uint64_t)gridDim.x * kWaves;
+        if (b >= late.rows) return;
+        st = states[b];
+        t = of_first((uint32_t)tokens[b]);
     }
 }
 
@@ -1587,7 +1599,8 @@ hipError_t launch_advance(const DeviceTable &T, const DeviceVocab &Vc, const Dev
                           hipEvent_t *ev)
 {
     const uint32_t waves = B <= 2u * n_cu ? 1u : 4u, blocks = cdiv(B, waves);
-    return launch(advance_kernel, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, ev, WG_EARLY_VALUES, LateArgs{T, Vc, Cc, nullptr, nullptr, 0, 0u, waves, B});
+    return launch(waves == 1u ? advance_kernel<1> : advance_kernel<4>, dim3(blocks < kAdvanceBlocks ? blocks : kAdvanceBlocks), dim3(64u * waves), 0, s, ev, WG_EARLY_VALUES,
+                  LateArgs{T, Vc, Cc, nullptr, nullptr, 0, 0u, 1u, B});
 }
 
 // A wavefront per request up to 32 requests to a unit, which are resident together.  A wavefront / a thread each, us, outlines, JSON, mixed,
