@@ -665,17 +665,17 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 // The first wavefront sees to the candidates (and to all that it needs for them itself: the successors' class
 // tables and literal bytes come with the directories), the others to the rest.  What the walks need of the
 // successors lies in LDS and not in scalar registers, of which this kernel has too few: what they do not hold is kept in
-// lanes of vector registers, 83 to 89 values with the lookup in a kernel before it and 104 to 112 with it in front.
+// lanes of vector registers, 61 or 62 values with the lookup in a kernel before it and 73 (masks only: 78) with it in front.
 // Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
 // that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
 // what is left in LDS and decides them 64 at a time, so that the walks run on full wavefronts.
 //
-// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 9.2 us for 8 MB, the launch and the
-// chain state -> descriptor -> tag -> row of four trips to memory; made rows 17.2 us for 19 MB, the same chain and
-// then plan -> directory -> entries -> chunks -> walk, with 3.5 M instructions of wavefronts (6 us of the chip's
-// vector units) in it.  With a lookup kernel before it these were 7 + 5.9 and 7 + 17.8 us.  B = 1024 and 141 class
-// tables a call, two kernels: made rows 80 -> 64 us, 17 M vector instructions of wavefronts (28 us; were 25 M).
+// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 7.1 us, the launch and the
+// chain state -> descriptor -> tag -> row of four trips to memory; made rows 15.3 us for 19 MB, the same chain and
+// then plan -> directory -> entries -> chunks -> walk, with 2.8 M instructions of wavefronts (5 us of the chip's
+// vector units) in it.  B = 1024 and 141 class tables a call, two kernels: copied rows 5 + 10.0 us, made rows 5 + 57,
+// with 15 M vector instructions of wavefronts (25 us).
 constexpr uint32_t kRowThreads = 256;
 constexpr uint32_t kRowWaves = kRowThreads / 64u;
 constexpr uint32_t kRowBatch = 4;          // index entries of a lane in flight together
@@ -1072,9 +1072,9 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
 // through the L2.
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
 // before it (tokens may be null).  One launch instead of two, and a row waits for its own lookup only, not for
-// the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket: the last
-// workgroup of a row to have read its state writes the new one, at its end, and the last such row of all opens
-// the next call.  (A ticket on one address for every workgroup of the call, taken by the wavefront that walks, cost
+// the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket.  The last
+// workgroup of a row to have read its state writes the new one behind its lookup (close_row), before it makes or copies its
+// share; the last such row of all opens the next call (close_call).  (A ticket on one address for every workgroup of the call, taken by the wavefront that walks, cost
 // 10 ns a workgroup: this fill took 28 us for 2,048 workgroups, 18 as it is now.)  Within 64 vector registers, so
 // that 8 workgroups of a unit are resident: with 7 the last 256 of 2,048 began 7 to 11 us after the others.
 template <typename Elem, int kMode, bool kWhole>
@@ -1419,7 +1419,8 @@ static bool by_lines(int dtype, uint32_t B, uint32_t V)
 // (78 MB) 23.1 32.3 34.2 / 24.0 32.4 35.1.  (Two in turn gain up to 120 MB: 256 13.7 15.0 17.8 / 13.1 14.4 17.2.)
 // Up to 1 MiB the L2s have next to nothing to write back, and what goes through takes longer to be stored: geometric means over 24 to 54 batches each of bf16 and
 // fp32, into / through, wg_apply_mask up to 0.25 MiB 0.99, 0.5 0.99, 1 1.00, 2 1.01, a cached wg_decode_step 0.98, 0.98, 0.99, 1.00 (one
-// request, V = 32,000, fp32 4.41 / 4.47 us, 151,936, bf16 4.82 / 4.93).
+// request, V = 32,000, fp32 4.41 / 4.47 us, 151,936, bf16 4.82 / 4.93).  With the greedy choice over all logits behind the step, which reads what
+// was stored, four buffers in turn, through / into, 207 batches: up to 4 MiB 1.00, 8 0.98, 12 to 25 0.95 to 0.96, 40 0.98, 50 0.99, 60 1.01, 80 1.03.
 constexpr uint64_t kThroughLeast = 1ull << 20, kThroughBytes = 40ull << 20;
 static bool masks_through(const void *logits, int dtype, uint32_t B, uint32_t V)
 {
@@ -1447,10 +1448,10 @@ static bool masks_through(const void *logits, int dtype, uint32_t B, uint32_t V)
 // side of the line: B = 512 V = 40000 0.92 0.99, 700 50257 0.91 0.99, 1000 65536 0.91 0.99; beyond it: 257 50257 1.10 1.22, 65536 1.20 1.37, 90000 1.32
 // 1.43; 400 65536 1.12 1.29, 90000 1.18 1.36; 700 65536 1.04 1.15 (outlines there 0.75 to 1.0).
 // Fewer too where the lookup that each repeats is most of a short share's work: up to a request per unit and more than
-// seven workgroups on one (above, rows are looked up once).  With 8 / 4, B = 256, kernel us of wg_decode_step on outlines, JSON,
-// mixed, random trees: copied V = 24576 9.3 9.5 9.7 9.5 / 9.0 9.0 9.3 9.3 (a lookup kernel and 8 shares: 9.3 10.0 9.8 12.1), 32768 10.8
-// 10.5 10.8 11.2 / 9.6 9.8 9.7 10.0 (9.8 10.1 10.2 15.1); made 24576 14.8 15.6 16.0 21.0 / 13.9 14.6 15.0 19.6, 32768 16.3 16.3 16.8 22.7 /
-// 14.7 15.2 15.5 23.4.  Longer rows of random trees take a tenth longer to make (V = 36800 23.9 / 26.3, 65536 27.9 / 33.7).
+// seven workgroups on one (above, rows are looked up once).  With 8 / 4, B = 256, us of a wg_decode_step on outlines, JSON,
+// mixed, random trees: copied V = 24576 7.4 7.4 7.4 7.4 / 6.4 6.4 6.4 6.5, 32768 7.6 7.6 7.6 7.7 / 6.7 6.7 6.8 7.1; made 24576 12.9 13.7
+// 14.5 20.4 / 12.4 13.1 13.1 18.1, 32768 14.9 15.0 14.4 22.0 / 14.3 13.9 13.3 22.6.  Longer rows gain less and random trees
+// take up to a fifth longer to make (wg_fill_masks, 4 over 8, B = 225, V = 36800 1.01 1.01 0.93 1.14, 65536 0.89 1.00 1.00 1.21; copied 0.88).
 constexpr uint32_t kLeastParts = 8;
 static uint32_t row_parts(uint32_t V, uint32_t B, uint32_t n_cu)
 {
@@ -1494,17 +1495,19 @@ FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, boo
     p.lines = masks_logits && by_lines(dtype, B, Vc.V);
     p.parts = row_parts(Vc.V, B, n_cu);
     // One kernel while its workgroups are resident together: what every workgroup of a row repeats of the lookup
-    // is then paid once, and a launch with its lookup is saved.  us a step with two kernels / with one, rows made
-    // and rows copied: V = 151936, mixed, B = 16 14.6 / 11.4 and 10.2 / 7.2, B = 64 19.5 / 16.4 and 12.2 / 9.7, B =
-    // 256 29.8 / 25.6 and 21.8 / 18.6 (random trees 54.9 / 52.9 and 23.4 / 19.8); html, V = 70000, B = 256 21.3 /
-    // 20.5 and 14.1 / 13.1.  Above, workgroups that start late repeat it when the others are done: html, V =
-    // 151936, B = 288 28.2 / 28.9 and 19.5 / 19.0; V = 60000, B = 512 28.3 / 33.0 and 17.2 / 19.5.  So it is with
-    // fewer rows whose shares take so much LDS that fewer workgroups are resident, from V = 350,000 on (masks only, html /
-    // mixed / random trees, one over two kernels, made and copied: V = 340001, B = 256, 8 to a unit, 1.12 0.92 0.98 and 1.06
-    // 1.04 0.92; 350000, B = 256, 7 to a unit, 1.20 1.07 0.96 and 1.13 1.14 1.02; 500000, B = 224, 6 to a unit, 1.08 1.02 0.99
-    // and 1.12 1.09 1.03, B = 192 0.92 0.94 1.01 and 0.97 1.00 0.85).  With logits to mask behind them the workgroups
-    // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.94 0.96
-    // 1.00 and 0.95 0.95 0.96); whole lines are masked behind a lookup of its own.
+    // is then paid once, and a launch with its lookup is saved.  us a call with two kernels / with one, outlines, mixed, random
+    // trees, wg_fill_masks copied and made, then wg_decode_step: V = 151936, B = 16 5.1 4.8 4.8 / 4.6 4.6 4.6, 11.5 11.7 14.2 / 9.3 9.3
+    // 11.5, 6.2 6.1 6.1 / 5.5 5.6 5.6, 13.2 13.2 15.7 / 10.5 10.6 12.6; B = 256 6.4 6.4 6.4 / 6.2 6.2 6.1, 15.9 18.2 31.4 / 13.0 15.0 30.3, 16.4
+    // 17.9 20.8 / 14.3 15.7 18.7, 23.7 27.5 39.3 / 20.5 22.7 37.7; V = 65536, B = 256 9.8 10.3 11.7 / 8.5 9.1 10.3 and 18.0 20.2 28.5 /
+    // 15.4 15.8 25.8 a step.  Above, workgroups that start late repeat it when the others are done: copied rows, masks alone,
+    // V = 151936, B = 288 6.6 / 7.4, V = 65536, B = 512 7.0 / 8.7, while most made ones and steps
+    // gain, up to a fifth (outlines, V = 65536, B = 512 lose: made 22.4 / 23.6, a cached step 14.9 / 15.6).  So it is with
+    // fewer rows whose shares take so much LDS that fewer workgroups are resident, from V = 350,000 on (masks only, outlines /
+    // mixed / random trees, one over two kernels, made and copied: V = 340001, B = 256, 8 to a unit, 0.83 0.84 0.94 and 0.95
+    // 0.91 0.95; 350000, B = 256, 7 to a unit, 0.95 0.99 1.02 and 1.08 1.03 1.07; 500000, B = 224, 6 to a unit, 0.99 0.98 1.00
+    // and 1.11 1.03 1.10, B = 192 0.90 0.91 0.99 and 0.96 0.94 0.95).  With logits to mask behind them the workgroups
+    // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.91 0.96
+    // 0.95 and 0.95 0.97 0.97); whole lines are masked behind a lookup of its own.
     p.one_kernel = Cc.direct && B <= n_cu && B <= kOneKernelRows && (masks_logits ? !p.lines : B * p.parts <= resident_rows(Vc, p.parts) * n_cu);
     return p;
 }

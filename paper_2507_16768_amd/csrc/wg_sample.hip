@@ -630,8 +630,9 @@ masked_topk_kernel(const Elem *__restrict__ logits, int64_t row_stride, uint32_t
 
 // Small batches: a slice of kTopkSlice tokens of a row per workgroup of 256 threads, a thread's 32
 // tokens in registers.  The best k of the slice leave for the workspace, best first.  What it takes is the
-// trips to memory one after the other: mask, logits, the candidates' logits again (V = 128,256 fp32, B = 8: 7.3 us
-// with k = 20, 8.2 with k = 50; 7.4 and 8.0 before the row kernel, when candidates were sorted).
+// trips to memory one after the other: mask, logits, the candidates' logits again for their keys (a call, slices and merge, V = 128,256
+// fp32, B = 8, everything allowed: 9.5 us with k = 20, 12.2 with k = 50).  7 registers of a thread (fp32; bf16 13) have no room and
+// go to memory.
 constexpr uint32_t kSliceThreads = 256;
 constexpr uint32_t kSliceWaves = kSliceThreads / 64u;
 constexpr uint32_t kSlicePer = kTopkSlice / kSliceThreads;       // tokens of a thread
