@@ -44,7 +44,10 @@ struct wg_handle_s {
     StateDesc *d_states = nullptr;
     uint8_t *d_classes = nullptr, *d_lit = nullptr;
     ClassPlan *d_plans = nullptr;
+    ClassCodes *d_codes = nullptr;
     std::vector<ClassPlan> plans;                     // host copy, kept for the asynchronous uploads
+    std::vector<ClassCodes> codes;                    // by class table
+    std::vector<ClassCodes> new_codes;                // by new state, while it is uploaded without the staging memory
     uint32_t cap_states = 0, cap_classes = 0, cap_keys = 0;
     uint32_t up_states = 0, up_classes = 0;           // how much of the host table is on the device
     uint32_t max_batch = 0;
@@ -74,7 +77,7 @@ template <typename F> int no_throw(const char *who, F f) {
     }
 }
 
-constexpr size_t kStageBytes = 1u << 20;      // additions up to this size take the pinned memory that the handle keeps
+constexpr size_t kStageBytes = 3u << 20;      // additions up to this size take the pinned memory that the handle keeps
 constexpr uint32_t kDefaultBatch = 1024;   // requests per call a handle has room for after wg_compile
 
 #define WG_HIP(call)                                                                          \
@@ -175,6 +178,7 @@ int grow_table(wg_handle_s *h, uint32_t n_states, uint32_t n_classes) {
         int rc = regrow(&h->d_states, h->up_states, nc);
         // the literal bytes are read 8 at a time: keep 16 zero bytes behind the last state
         if (rc == WG_OK) rc = regrow(&h->d_lit, h->up_states, nc, 16);
+        if (rc == WG_OK) rc = regrow(&h->d_codes, h->up_states, nc);
         if (rc != WG_OK) return rc;
         h->cap_states = nc;
     }
@@ -205,13 +209,25 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
     const Table &t = h->low.table;
     const uint32_t n_states = (uint32_t)t.states.size(), n_classes = (uint32_t)(t.classes.size() / 256);
     const int rc = grow_table(h, n_states, n_classes);
-    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, h->dt.n_states, t.lmax};
+    h->dt = DeviceTable{h->d_states, h->d_classes, h->d_plans, h->d_lit, h->d_codes, h->dt.n_states, t.lmax};
     if (rc != WG_OK) return rc;
     if (n_states > h->up_states || n_classes > h->up_classes) {
         const uint32_t s0 = h->up_states, ns = n_states - s0, c0 = h->up_classes, nc = n_classes - c0;
         h->plans.resize(n_classes);
-        for (uint32_t c = c0; c < n_classes; c++) h->plans[c] = wide_plan_of(t.classes.data() + (size_t)c * 256);
-        struct { void *dst; const void *src; size_t bytes; } part[4] = {
+        h->codes.resize(n_classes);
+        for (uint32_t c = c0; c < n_classes; c++) {
+            h->plans[c] = wide_plan_of(t.classes.data() + (size_t)c * 256);
+            h->codes[c] = class_codes_of(t.classes.data() + (size_t)c * 256);
+        }
+        auto put_codes = [&](uint8_t *to) {            // of the new states
+            for (uint32_t s = s0; s < n_states; s++, to += sizeof(ClassCodes)) {
+                const uint32_t kind = t.states[s].kind_byte & 0xFFu;
+                if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) std::memcpy(to, &h->codes[t.states[s].cls], sizeof(ClassCodes));
+                else std::memset(to, 0, sizeof(ClassCodes));
+            }
+        };
+        struct { void *dst; const void *src; size_t bytes; } part[5] = {
+            {h->d_codes + s0, nullptr, ns * sizeof(ClassCodes)},
             {h->d_states + s0, t.states.data() + s0, ns * sizeof(StateDesc)},
             {h->d_lit + s0, t.lit.data() + s0, ns},
             {h->d_classes + (size_t)c0 * 256, t.classes.data() + (size_t)c0 * 256, (size_t)nc * 256},
@@ -226,17 +242,22 @@ int sync_table(wg_handle_s *h, hipStream_t s) {
                 if (!p.bytes) continue;
                 at = (at + 15u) & ~(size_t)15u;
                 uint8_t *src = h->stage + at + (reinterpret_cast<uintptr_t>(p.dst) & 15u);
-                std::memcpy(src, p.src, p.bytes);
+                if (p.src) std::memcpy(src, p.src, p.bytes);
+                else put_codes(src);
                 slices.slice[n++] = AppendSlice{static_cast<uint8_t *>(p.dst), src, (uint32_t)p.bytes};
                 at = (size_t)(src - h->stage) + p.bytes;
             }
             WG_HIP(launch_append(slices, n, s));
         } else {
+            h->new_codes.resize(ns);
+            put_codes(reinterpret_cast<uint8_t *>(h->new_codes.data()));
+            part[0].src = h->new_codes.data();
             for (const auto &p : part)
                 if (p.bytes) WG_HIP(hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyHostToDevice, s));
         }
         // (what is copied from may move or be filled again by a later append)
         WG_HIP(hipStreamSynchronize(s));
+        std::vector<ClassCodes>().swap(h->new_codes);
         h->up_states = n_states;
         h->up_classes = n_classes;
     }
@@ -422,7 +443,7 @@ void wg_table_destroy(wg_table_t t) { delete t; }
 void wg_destroy(wg_handle_t h) {
     if (!h) return;
     (void)hipDeviceSynchronize();
-    (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans);
+    (void)hipFree(h->d_states); (void)hipFree(h->d_classes); (void)hipFree(h->d_lit); (void)hipFree(h->d_plans); (void)hipFree(h->d_codes);
     (void)hipFree(h->dc.ctr); (void)hipFree(h->dc.tags); (void)hipFree(h->dc.slots);
     (void)hipFree(h->dc.arena); (void)hipFree(h->dc.row_ref); (void)hipFree(h->dc.tasks);
     if (h->stage) (void)hipHostFree(h->stage);

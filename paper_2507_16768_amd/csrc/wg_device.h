@@ -13,6 +13,7 @@ struct DeviceTable {
     const uint8_t *classes;      // 256-byte class tables
     const ClassPlan *plans;      // one per class table
     const uint8_t *lit;          // literal byte per state
+    const ClassCodes *codes;     // per state: a checkpoint's class table once more (see look_ahead); else zeros
     uint32_t n_states;
     uint32_t lmax;
 };
@@ -140,7 +141,7 @@ hipError_t launch_fill(const FillPlan &plan, const DeviceTable &T, const DeviceV
                        void *logits, int dtype, int64_t logits_stride,
                        hipStream_t s, hipEvent_t *lookup_ev, hipEvent_t *rows_ev);
 struct AppendSlice { uint8_t *dst; const uint8_t *src; uint32_t bytes; };
-struct AppendSlices { AppendSlice slice[4]; };
+struct AppendSlices { AppendSlice slice[5]; };
 hipError_t launch_append(const AppendSlices &a, uint32_t n, hipStream_t s);
 // While the arena is addressed by key: adds the keys that hold a row in this generation to Cc.ctr->held.
 hipError_t launch_count_rows(const DeviceCache &Cc, hipStream_t s);

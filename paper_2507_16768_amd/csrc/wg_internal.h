@@ -61,6 +61,9 @@ struct ClassPlan {
 };
 static_assert(sizeof(ClassPlan) % 16 == 0, "class plan layout");
 ClassPlan class_plan_of(const uint8_t *table);
+// A class table as the walk of a sampled token reads it: two bits a byte value, sixteen values to a word.
+struct ClassCodes { uint32_t word[16]; };
+ClassCodes class_codes_of(const uint8_t *table);
 // The same for the device, with the rows of 16 byte values put together where 32, 64 or 128 are rejected as a
 // whole: kWideRow + k stands for the k-th of the blocks of 32 (k = 0 .. 7), of 64 (8 .. 11) and of 128 (12, 13).
 // Most tables reject all that is not ASCII: a row for it instead of eight (kWideRows rows of 19 KB for 152k tokens).

@@ -60,6 +60,7 @@ struct TableView {
     const StateDesc *states;
     uint32_t n_states;
     LateRef<const uint8_t *> classes, lit;
+    LateRef<const ClassCodes *> codes;
     LateRef<const ClassPlan *> plans;
     LateRef<uint32_t> lmax;
 };
@@ -82,7 +83,7 @@ struct CacheView {
 };
 #define WG_VIEWS \
     Late &late = late_args(); \
-    const TableView T{descs, n_states, late.T.classes, late.T.lit, late.T.plans, late.T.lmax}; \
+    const TableView T{descs, n_states, late.T.classes, late.T.lit, late.T.codes, late.T.plans, late.T.lmax}; \
     const VocabView Vc{len8, chunks, V, late.Vc.rows, late.Vc.dirs, late.Vc.index, late.Vc.W, late.Vc.lmax, late.Vc.n_chunks, late.Vc.eos_id}; \
     const CacheView Cc{ctr, late.Cc.tags, late.Cc.class_tags, late.Cc.slots, late.Cc.arena, late.Cc.class_rows, late.Cc.row_ref, late.Cc.free_rows, \
                    late.Cc.tasks, late.Cc.cap_rows, late.Cc.direct, late.Cc.row_stride, late.Cc.epoch}
@@ -229,39 +230,66 @@ __device__ __forceinline__ uint32_t token_byte(const VocabView &Vc, uint32_t t, 
     return reinterpret_cast<const uint8_t *>(Vc.chunks + (size_t)(p >> 3) * Vc.V + t)[p & 7u];
 }
 
-// walk() for one token by a wavefront, where every step is a trip to memory that nothing else hides: one per
-// state, however many bytes are consumed in it.  All bytes that a state might consume are compared or looked up
-// together, a byte per lane, and the descriptors of the states that may follow are requested with them.  (A thread
+// What a walk takes from memory for a state, in one trip: the descriptors of eight states from it on (lane k: dword k % 8 of
+// the k / 8-th), 64 literal bytes from its own on (a lane each) and, of a checkpoint, the classes of all byte values
+// (lane k: word k % 16 of its codes).
+struct Ahead { uint32_t sid, words, lits, codes; };
+constexpr uint32_t kAheadStates = 8u;
+__device__ __forceinline__ Ahead look_ahead(const TableView &T, uint32_t sid)
+{
+    // (what is no state, ERROR among them, is state 0 here; who asks looks at the number first)
+    const uint32_t lane = threadIdx.x & 63u, s = sid + lane / 8u, c = sid + lane;
+    Ahead a;
+    a.sid = sid;
+    a.words = reinterpret_cast<const uint32_t *>(T.states + (s < T.n_states ? s : 0u))[lane & 7u];
+    a.codes = T.codes[sid < T.n_states ? sid : 0u].word[lane & 15u];
+    a.lits = T.lit[c < T.n_states ? c : 0u];
+    return a;
+}
+// (here: all of it has to have been requested; the compiler would move a load to where it is used)
+__device__ __forceinline__ void arrive(Ahead &a) { asm volatile("" : "+v"(a.words), "+v"(a.codes), "+v"(a.lits)); }
+
+// walk() for one token by a wavefront, where every trip to memory is one that nothing else hides: none for the state that the
+// request is in (its surroundings come with its descriptor), nor for the literal states and the last state within reach of them; one
+// for any other.  All bytes that a state might consume are compared or looked up together, a byte per lane.  (A thread
 // per request, eight bytes at a time, took two trips for every eight bytes of free text, and the longest walk of a
-// batch decides: of 256 mixed requests, V = 151936, the last had its state 8.9 us after the kernel's beginning, now 4.2;
-// wg_advance by itself, B = 64, 256, 1024 3.90, 4.28, 4.78 us -> 3.17, 3.20, 3.60, V = 16000, B = 8192 6.0 -> 5.2.)
-// d: the descriptor of sid, at the call and after it.  byte: the lane's.
-__device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, uint32_t &sid, uint32_t &aux, StateDesc &d,
+// batch decides: of 256 mixed requests, V = 151936, the last had its state 8.9 us after the kernel's beginning.  With a trip for
+// each state's bytes and the descriptors behind it 4.2.  Times with that / now, us: wg_advance, mixed, V = 151936, B = 256 4.88 / 3.84, outlines,
+// V = 128256, B = 64 3.84 / 2.68; eight cached steps of them 171.2 / 165.8 and 54.5 / 53.7.  The codes cost 64 bytes a state; asked for
+// by the number of the class table they would be a trip behind the descriptor.)
+// a: what lies ahead of sid, at the call; d: the descriptor of sid, at the call and after it.  byte: the lane's.
+__device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, uint32_t &sid, uint32_t &aux, Ahead a, StateDesc &d,
                                           uint32_t t, uint32_t byte, uint32_t L)
 {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t i = 0, base = 0;                                // bytes consumed; the byte that lane 0 has
+    auto renew = [&]() { a = look_ahead(T, sid); arrive(a); };
+    auto arrived = [&]() {                                   // in sid: its descriptor
+        if (sid - a.sid >= kAheadStates) renew();
+        d = state_of(a.words, (sid - a.sid) * 8u);
+    };
     while (i < L) {
         const uint32_t kind = d.kind_byte & 0xFFu;
         const bool lit = kind == WG_KIND_LIT;
         if (sid >= T.n_states || !(lit || is_checkpoint(kind))) return false;          // ERROR; FINAL and END accept no byte
         if (i == base + 64u) { base = i; byte = token_byte(Vc, t, base + lane); }      // a token longer than the wavefront
         uint32_t n = (L - base < 64u ? L - base : 64u) - (i - base);
-        if (lit && d.run < n) n = d.run;
         const uint32_t k = base + lane - i;                  // the lane's byte is the k-th from here, if k < n
-        const uint8_t *src = lit ? T.lit + sid + k : T.classes + (size_t)d.cls * 256u + byte;
-        const uint32_t want = lit ? byte : (uint32_t)CLS_STAY;
-        uint32_t x = want;
-        if (k < n) x = *src;
-        asm volatile("" ::: "memory");                       // (the descriptors behind the bytes, so that a walk that stays does not wait for them)
-        const uint32_t sa = !lit ? d.next_a : n == d.run ? d.cls : sid + n;            // d.cls: state after the Write
-        const uint32_t next = two_states(T, sa, lit ? sa : d.next_b);
-        const unsigned long long off = __ballot(x != want);
         if (lit) {
-            if (off) return false;
-            sid = sa; d = state_of(next, 0u); aux = 0; i += n;
+            if (d.run < n) n = d.run;
+            if (sid - a.sid + n > 64u) renew();
+            uint32_t x = a.lits;                             // literal byte a.sid + lane; wanted: sid + k
+            const uint32_t shift = sid - a.sid + base - i;
+            if (shift) x = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane + shift) * 4u), (int)x);
+            if (__ballot(k < n && x != byte)) return false;
+            sid = n == d.run ? d.cls : sid + n;              // d.cls: state after the Write
+            aux = 0; i += n;
+            arrived();
             continue;
         }
+        if (sid != a.sid) renew();
+        const uint32_t codes = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(byte >> 4 << 2), (int)a.codes), c = codes >> (byte & 15u) * 2u & 3u;
+        const unsigned long long off = __ballot(k < n && c != CLS_STAY);
         const uint32_t stays = off ? (uint32_t)__builtin_ctzll(off) - (i - base) : n;
         if (d.max != WG_UNBOUNDED && stays) {                // each stay needs budget left
             if (aux >= d.max || stays > d.max - aux) return false;
@@ -269,12 +297,11 @@ __device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &V
         }
         i += stays;
         if (!off) continue;
-        const uint32_t left = of_lane(x, (uint32_t)__builtin_ctzll(off));
+        const uint32_t left = of_lane(c, (uint32_t)__builtin_ctzll(off));
         if (left == CLS_REJECT) return false;
-        const bool to_b = left != CLS_EXIT_A;
-        sid = to_b ? d.next_b : d.next_a;
-        d = state_of(next, to_b ? 8u : 0u);
+        sid = left == CLS_EXIT_A ? d.next_a : d.next_b;
         aux = 0; i++;
+        arrived();
     }
     return true;
 }
@@ -282,11 +309,13 @@ __device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &V
 __device__ __forceinline__ void advance_one(const TableView &T, const VocabView &Vc, const CacheView &Cc,
                                             uint32_t &sid, uint32_t &aux, StateDesc &d, int32_t t, bool count_error, uint32_t b)
 {
-    // (the token's length and bytes are requested with the descriptor)
+    // (the token's length and bytes are requested with the state's surroundings)
     const bool is_token = t >= 0 && (uint32_t)t < Vc.V;
     const uint32_t tok = is_token ? (uint32_t)t : 0u;
-    const uint32_t len = Vc.len8[tok], byte = token_byte(Vc, tok, threadIdx.x & 63u);
-    d = state_of(two_states(T, sid, sid), 0u);
+    uint32_t len = Vc.len8[tok], byte = token_byte(Vc, tok, threadIdx.x & 63u);
+    Ahead a = look_ahead(T, sid);
+    asm volatile("" : "+v"(len), "+v"(byte), "+v"(a.words), "+v"(a.codes), "+v"(a.lits));
+    d = state_of(a.words, 0u);
     bool ok = is_token && sid < T.n_states;
     if (ok) {
         if (Vc.eos_id == t) {
@@ -295,7 +324,7 @@ __device__ __forceinline__ void advance_one(const TableView &T, const VocabView 
             d = state_of(two_states(T, sid, sid), 0u);
         } else {
             const uint32_t L = of_first(len);
-            ok = L != 0u && walk_wide(T, Vc, sid, aux, d, tok, byte, L);
+            ok = L != 0u && walk_wide(T, Vc, sid, aux, a, d, tok, byte, L);
         }
     }
     if (!ok) {

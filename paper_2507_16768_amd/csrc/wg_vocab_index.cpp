@@ -32,6 +32,12 @@ ClassPlan class_plan_of(const uint8_t *table) {
     return p;
 }
 
+ClassCodes class_codes_of(const uint8_t *table) {
+    ClassCodes c{};
+    for (uint32_t x = 0; x < 256u; x++) c.word[x >> 4] |= (uint32_t)table[x] << (2u * (x & 15u));
+    return c;
+}
+
 ClassPlan wide_plan_of(const uint8_t *table) {
     const ClassPlan p = class_plan_of(table);
     ClassPlan out = p;

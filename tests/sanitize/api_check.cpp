@@ -74,6 +74,8 @@ static void look_at(const DeviceTable &T, const DeviceVocab &Vc, const DeviceCac
         if (kind == WG_KIND_WAIT || kind == WG_KIND_COND) {
             sum += T.classes[(size_t)d.cls * 256u + 255u] + T.plans[d.cls].ids[259] + Cc.class_tags[d.cls];
             sum += Cc.class_rows[(size_t)(2u * d.cls + 2u) * Vc.row_stride - 1u];
+            for (uint32_t x = 0; x < 256u; x++)
+                EXPECT((T.codes[sid].word[x / 16u] >> 2u * (x % 16u) & 3u) == T.classes[(size_t)d.cls * 256u + x], "state %u: the code of byte value %u", sid, x);
         }
         sum += T.lit[sid];
     }

@@ -243,6 +243,8 @@ static void check_plan(const uint8_t *tab, size_t c, bool wide) {
     const ClassPlan p = wide ? wide_plan_of(tab) : class_plan_of(tab);
     uint32_t live = 0, named[256] = {};
     for (uint32_t x = 0; x < 256; x++) { EXPECT(tab[x] < 4, "class byte"); live += tab[x] != CLS_REJECT; }
+    const ClassCodes codes = class_codes_of(tab);
+    for (uint32_t x = 0; x < 256; x++) EXPECT((codes.word[x / 16u] >> 2u * (x % 16u) & 3u) == tab[x], "code of byte value %u of %zu", x, c);
     EXPECT(p.by_first == (live <= kFewLive) && p.n_exits <= p.n_ids && p.n_ids <= 256, "plan of %zu", c);
     EXPECT(!p.by_first || p.n_ids == p.n_exits, "rows of %zu", c);
     for (uint32_t i = 0; i < p.n_exits; i++) {

@@ -73,6 +73,47 @@ def test_tokens_as_long_as_a_wavefront_and_longer(torch_cuda, restart):
             assert (H.host_mask(mask) == o.fill_masks(want[p])).all(), (B, k)
 
 
+@pytest.mark.parametrize("n", [1, 6, 7, 8, 9, 56, 57, 63, 64, 65])
+def test_walks_past_what_lies_ahead_of_their_state(torch_cuda, n):
+    """A walk has eight states and 64 literal bytes from its state on at hand: runs that end on either side of both, in front of
+    checkpoints, of conditions that lead back, over a body and past one, and of another run; in instances compiled first, added to the
+    tables, and added with more than the tables had room for."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    run = _RUN[:n].decode()
+    text = ('DoWhile(body=Sequence(Write($r), Wait(denies={9}, wait={<}, max=40), IfElse(condition=Wait(allow={\\x20}, true_waits={\\x5B}, '
+            'false_waits={\\x22}), if_body=Write($r), else_body=Sequence(Wait(allow={x}, wait={y}), Write("b"), Write("<c"))), Write($r)), '
+            'condition=Wait(allow={\\x20}, true_waits={\\x2C}, false_waits={\\x5D}))')
+    path = [b"%s<[%s%s" % ((run.encode(),) * 3), b'%s<"xyb<c%s' % ((run.encode(),) * 2), b"%s,%s]" % ((run.encode(),) * 2), b"ab<  [" + run.encode(), b"9", b"<9"]
+    toks = [b""] + [bytes([c]) for c in b"abcxy<>9 ,[]\"!"] + [p[i:i + m] for p in path for i in (0, 1, n - 1, n, n + 1, n + 2, n + 5) for m in (2, 3, 7, 8, 9, 10, n, n + 1, n + 3, 2 * n + 4) if p[i:i + m]]
+    vocab = from_tokens(list(dict.fromkeys(toks)), eos_id=0)
+    args = [{"r": run.encode()}, {"r": run.encode()[::-1]}, {"r": b"<" * n}] + [{"r": (b"%d" % k).rjust(n, b"a")[-n:]} for k in range(40)]
+    texts = [text] * len(args)
+    o = O.Oracle(texts, args, O.OracleVocab(vocab.bytes, vocab.offsets, vocab.eos_id), restart=True)
+    h = wg.Handle(texts[:1], args[:1], wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART)
+    h.add_instances(texts[1:3], args[1:3])
+    h.add_instances(texts[3:], args[3:])
+    ends = o.num_states if len(args) * n < 200 else [k for k in range(o.num_states) if k < 3 * (o.num_states // len(args)) or k >= o.num_states - o.num_states // len(args)]
+    st = []
+    for sid in (range(ends) if isinstance(ends, int) else ends):
+        d = o.describe(sid)
+        st += [[sid, a] for a in ((0, 1, 39, 40) if d["kind"] == "WAIT" and d["max"] >= 0 else (0,))]
+    st = np.array(st, dtype=np.uint32)
+    rep, tk = np.repeat(st, vocab.V, axis=0), np.tile(np.arange(vocab.V, dtype=np.int32), len(st))
+    want = o.advance(rep, tk)
+    assert np.sum(want[:, 0] != O.SID_ERROR) >= 100
+    got = H.dev_states(rep)
+    h.advance(got, torch.from_numpy(tk).cuda())
+    assert (H.host_states(got) == want).all()
+    pick = np.random.default_rng(n).permutation(len(rep))
+    pick = np.concatenate([pick[want[pick, 0] != O.SID_ERROR][:200], pick[:100]])
+    for p in (pick[:200], pick):                                       # in one kernel, and behind a lookup kernel
+        b = H.dev_states(rep[p])
+        mask = torch.empty((len(p), h.W), dtype=torch.int32, device="cuda")
+        h.advance_fill_masks(b, torch.from_numpy(tk[p]).cuda(), mask)
+        assert (H.host_states(b) == want[p]).all() and (H.host_mask(mask) == o.fill_masks(want[p])).all()
+
+
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33, 255, 256])
 def test_calls_of_one_kernel_count_their_rows(torch_cuda, B):
     """Each call's states are written back, its lookups counted and its claims told from the next call's, whatever rows the
