@@ -224,9 +224,10 @@ __device__ __forceinline__ StateDesc state_of(uint32_t words, uint32_t at)      
                      of_lane(words, at + 4u), of_lane(words, at + 5u), of_lane(words, at + 6u), of_lane(words, at + 7u)};
 }
 
-__device__ __forceinline__ uint32_t token_byte(const VocabView &Vc, uint32_t t, uint32_t p)
+// (0 where the vocabulary has no chunk for it)
+__device__ __forceinline__ uint32_t token_byte(const VocabView &Vc, uint32_t n_chunks, uint32_t t, uint32_t p)
 {
-    if (p >= Vc.n_chunks * 8u) return 0u;
+    if (p >= n_chunks * 8u) return 0u;
     return reinterpret_cast<const uint8_t *>(Vc.chunks + (size_t)(p >> 3) * Vc.V + t)[p & 7u];
 }
 
@@ -235,20 +236,36 @@ __device__ __forceinline__ uint32_t token_byte(const VocabView &Vc, uint32_t t, 
 // (lane k: word k % 16 of its codes).
 struct Ahead { uint32_t sid, words, lits, codes; };
 constexpr uint32_t kAheadStates = 8u;
-__device__ __forceinline__ Ahead look_ahead(const TableView &T, uint32_t sid)
+// The late arguments that it needs, kept in registers: read from the arguments' memory where they were needed, each was a wait of
+// 100 cycles on the way of the one wavefront that everything waits for.
+struct WalkArgs {
+    const uint8_t *lit;
+    const ClassCodes *codes;
+    uint32_t n_chunks;
+    int32_t eos_id;
+    WalkArgs() = default;
+    __device__ __forceinline__ explicit WalkArgs(Late &late) : lit(late.T.lit), codes(late.T.codes), n_chunks(late.Vc.n_chunks), eos_id(late.Vc.eos_id) {}
+};
+// Values that the compiler must not read again from memory.
+template <typename X> __device__ __forceinline__ void hold_one(X &x) { asm volatile("" : "+s"(x)); }
+template <typename X> __device__ __forceinline__ void hold_one(X *&x)               // (they stay pointers to device memory for the compiler)
+{
+    auto g = (__attribute__((address_space(1))) X *)x;
+    asm volatile("" : "+s"(g));
+    x = (X *)g;
+}
+template <typename... X> __device__ __forceinline__ void hold(X &...x) { (hold_one(x), ...); }
+__device__ __forceinline__ Ahead look_ahead(const TableView &T, const WalkArgs &w, uint32_t sid)
 {
     // (what is no state, ERROR among them, is state 0 here; who asks looks at the number first)
     const uint32_t lane = threadIdx.x & 63u, s = sid + lane / 8u, c = sid + lane;
     Ahead a;
     a.sid = sid;
     a.words = reinterpret_cast<const uint32_t *>(T.states + (s < T.n_states ? s : 0u))[lane & 7u];
-    a.codes = T.codes[sid < T.n_states ? sid : 0u].word[lane & 15u];
-    a.lits = T.lit[c < T.n_states ? c : 0u];
+    a.codes = w.codes[sid < T.n_states ? sid : 0u].word[lane & 15u];
+    a.lits = w.lit[c < T.n_states ? c : 0u];
     return a;
 }
-// (here: all of it has to have been requested; the compiler would move a load to where it is used)
-__device__ __forceinline__ void arrive(Ahead &a) { asm volatile("" : "+v"(a.words), "+v"(a.codes), "+v"(a.lits)); }
-
 // walk() for one token by a wavefront, where every trip to memory is one that nothing else hides: none for the state that the
 // request is in (its surroundings come with its descriptor), nor for the literal states and the last state within reach of them; one
 // for any other.  All bytes that a state might consume are compared or looked up together, a byte per lane.  (A thread
@@ -258,12 +275,15 @@ __device__ __forceinline__ void arrive(Ahead &a) { asm volatile("" : "+v"(a.word
 // V = 128256, B = 64 3.84 / 2.68; eight cached steps of them 171.2 / 165.8 and 54.5 / 53.7.  The codes cost 64 bytes a state; asked for
 // by the number of the class table they would be a trip behind the descriptor.)
 // a: what lies ahead of sid, at the call; d: the descriptor of sid, at the call and after it.  byte: the lane's.
-__device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, uint32_t &sid, uint32_t &aux, Ahead a, StateDesc &d,
+__device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, const WalkArgs &w, uint32_t &sid, uint32_t &aux, Ahead a, StateDesc &d,
                                           uint32_t t, uint32_t byte, uint32_t L)
 {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t i = 0, base = 0;                                // bytes consumed; the byte that lane 0 has
-    auto renew = [&]() { a = look_ahead(T, sid); arrive(a); };
+    auto renew = [&]() {
+        a = look_ahead(T, w, sid);
+        asm volatile("" : "+v"(a.words), "+v"(a.codes), "+v"(a.lits));
+    };
     auto arrived = [&]() {                                   // in sid: its descriptor
         if (sid - a.sid >= kAheadStates) renew();
         d = state_of(a.words, (sid - a.sid) * 8u);
@@ -272,7 +292,7 @@ __device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &V
         const uint32_t kind = d.kind_byte & 0xFFu;
         const bool lit = kind == WG_KIND_LIT;
         if (sid >= T.n_states || !(lit || is_checkpoint(kind))) return false;          // ERROR; FINAL and END accept no byte
-        if (i == base + 64u) { base = i; byte = token_byte(Vc, t, base + lane); }      // a token longer than the wavefront
+        if (i == base + 64u) { base = i; byte = token_byte(Vc, w.n_chunks, t, base + lane); }      // a token longer than the wavefront
         uint32_t n = (L - base < 64u ? L - base : 64u) - (i - base);
         const uint32_t k = base + lane - i;                  // the lane's byte is the k-th from here, if k < n
         if (lit) {
@@ -305,26 +325,37 @@ __device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &V
     }
     return true;
 }
-// d: the descriptor of sid, at the call and after it.
-__device__ __forceinline__ void advance_one(const TableView &T, const VocabView &Vc, const CacheView &Cc,
+// What an advance takes from memory at first, in one trip: the state's surroundings, the token's length and bytes.
+struct Sampled {
+    uint32_t len, byte;
+    Ahead ahead;
+};
+__device__ __forceinline__ bool is_token(const VocabView &Vc, int32_t t) { return t >= 0 && (uint32_t)t < Vc.V; }
+__device__ __forceinline__ Sampled ask_sampled(const TableView &T, const VocabView &Vc, const WalkArgs &w, uint32_t sid, int32_t t)
+{
+    const uint32_t tok = is_token(Vc, t) ? (uint32_t)t : 0u;
+    Sampled s;
+    s.len = Vc.len8[tok];
+    s.byte = token_byte(Vc, w.n_chunks, tok, threadIdx.x & 63u);
+    s.ahead = look_ahead(T, w, sid);
+    return s;
+}
+// d: the descriptor of sid after it.
+__device__ __forceinline__ void advance_one(const TableView &T, const VocabView &Vc, const CacheView &Cc, const WalkArgs &w, Sampled s,
                                             uint32_t &sid, uint32_t &aux, StateDesc &d, int32_t t, bool count_error, uint32_t b)
 {
-    // (the token's length and bytes are requested with the state's surroundings)
-    const bool is_token = t >= 0 && (uint32_t)t < Vc.V;
-    const uint32_t tok = is_token ? (uint32_t)t : 0u;
-    uint32_t len = Vc.len8[tok], byte = token_byte(Vc, tok, threadIdx.x & 63u);
-    Ahead a = look_ahead(T, sid);
-    asm volatile("" : "+v"(len), "+v"(byte), "+v"(a.words), "+v"(a.codes), "+v"(a.lits));
-    d = state_of(a.words, 0u);
-    bool ok = is_token && sid < T.n_states;
+    // (here: all of it has to have been requested; the compiler would move a load to where it is used)
+    asm volatile("" : "+v"(s.len), "+v"(s.byte), "+v"(s.ahead.words), "+v"(s.ahead.codes), "+v"(s.ahead.lits));
+    d = state_of(s.ahead.words, 0u);
+    bool ok = is_token(Vc, t) && sid < T.n_states;
     if (ok) {
-        if (Vc.eos_id == t) {
+        if (w.eos_id == t) {
             sid = d.eos_next; aux = 0;
             ok = sid != WG_SID_ERROR;
             d = state_of(two_states(T, sid, sid), 0u);
         } else {
-            const uint32_t L = of_first(len);
-            ok = L != 0u && walk_wide(T, Vc, sid, aux, a, d, tok, byte, L);
+            const uint32_t L = of_first(s.len);
+            ok = L != 0u && walk_wide(T, Vc, w, sid, aux, s.ahead, d, (uint32_t)t, s.byte, L);
         }
     }
     if (!ok) {
@@ -350,15 +381,18 @@ advance_kernel(WG_EARLY_ARGS)
     wg_state_t st = states[b];
     uint32_t t = of_first((uint32_t)tokens[b]);
     // (in one wait with them a word of each line of the arguments)
-    asm volatile("" :: "s"(of_first(st.sid)), "s"(t), "s"(late.T.lit), "s"(late.Vc.n_chunks), "s"(late.Cc.tags), "s"(late.rows));
+    WalkArgs walk(late);
+    uint32_t rows = late.rows;
+    asm volatile("" :: "s"(of_first(st.sid)), "s"(t), "s"(walk.lit), "s"(walk.codes), "s"(walk.n_chunks), "s"(walk.eos_id), "s"(rows));
+    hold(walk.lit, walk.codes, walk.n_chunks, walk.eos_id, rows);
     for (;;) {
         uint32_t sid = of_first(st.sid), aux = of_first(st.aux);
         StateDesc d;
-        advance_one(T, Vc, Cc, sid, aux, d, (int32_t)t, true, (uint32_t)b);
+        advance_one(T, Vc, Cc, walk, ask_sampled(T, Vc, walk, sid, (int32_t)t), sid, aux, d, (int32_t)t, true, (uint32_t)b);
         if ((threadIdx.x & 63u) == 0u) states[b] = wg_state_t{sid, aux};
         // (wg_advance takes any number of requests: more than the grid holds come in turn)
         b += (uint64_t)gridDim.x * kWaves;
-        if (b >= late.rows) return;
+        if (b >= rows) return;
         st = states[b];
         t = of_first((uint32_t)tokens[b]);
     }
@@ -385,18 +419,18 @@ struct Found {
 struct Claim { unsigned long long key_tag, class_tag; uint32_t key, cls; };      // tags as the lookup found them
 
 // What a call writes into the tags it claims, but for the request; `launch` is ctr->launch.
-__device__ __forceinline__ unsigned long long tag_now(const CacheView &Cc, unsigned long long launch)
+__device__ __forceinline__ unsigned long long tag_now(uint32_t epoch, unsigned long long launch)
 {
-    return (unsigned long long)Cc.epoch << kTagEpochShift | (launch & kTagLaunchMask) << kTagRequestBits;
+    return (unsigned long long)epoch << kTagEpochShift | (launch & kTagLaunchMask) << kTagRequestBits;
 }
 
 // The key of the state (sid, aux), d its descriptor; kNoKey: no such state.
-__device__ __forceinline__ uint32_t key_of(const TableView &T, uint32_t sid, uint32_t aux, const StateDesc &d, uint32_t &variant)
+__device__ __forceinline__ uint32_t key_of(const TableView &T, uint32_t lmax, uint32_t sid, uint32_t aux, const StateDesc &d, uint32_t &variant)
 {
     variant = 0;
     if ((d.kind_byte & 0xFFu) == WG_KIND_WAIT && d.max != WG_UNBOUNDED) {
         const uint32_t left = d.max > aux ? d.max - aux : 0u;
-        variant = T.lmax - (left < T.lmax ? left : T.lmax);
+        variant = lmax - (left < lmax ? left : lmax);
     }
     return sid < T.n_states ? d.key_base + variant : kNoKey;
 }
@@ -409,19 +443,28 @@ struct Asked {
     unsigned long long tag, class_tag;
     uint32_t next;               // as two_states leaves them
 };
-__device__ __forceinline__ Asked ask(const TableView &T, const CacheView &Cc, uint32_t sid, uint32_t aux, const StateDesc &d)
+// slots: null where the arena is addressed by key.
+template <bool kDirect>
+__device__ __forceinline__ Asked ask(const TableView &T, uint32_t lmax, const unsigned long long *tags, const unsigned long long *class_tags, const uint32_t *slots,
+                                     uint32_t sid, uint32_t aux, const StateDesc &d)
 {
     Asked q{};
-    q.key = key_of(T, sid, aux, d, q.variant);
+    q.key = key_of(T, lmax, sid, aux, d, q.variant);
     if (q.key == kNoKey) return q;
-    q.tag = __hip_atomic_load(&Cc.tags[q.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    q.class_tag = __hip_atomic_load(&Cc.class_tags[is_checkpoint(d.kind_byte & 0xFFu) ? d.cls : 0u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.tag = __hip_atomic_load(&tags[q.key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.class_tag = __hip_atomic_load(&class_tags[is_checkpoint(d.kind_byte & 0xFFu) ? d.cls : 0u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     q.next = two_states(T, d.next_a, d.next_b);
     q.slot = q.key;
-    if (!Cc.direct) q.slot = Cc.slots[q.key];
+    if (!kDirect && slots) q.slot = slots[q.key];
     return q;
 }
 __device__ __forceinline__ unsigned long long of_first(unsigned long long x) { return (unsigned long long)of_first((uint32_t)(x >> 32)) << 32 | of_first((uint32_t)x); }
+
+// The tag t was entered in this generation, by an earlier call than the one that enters `now`.
+__device__ __forceinline__ bool made_before(unsigned long long t, unsigned long long now)
+{
+    return t >> kTagEpochShift == now >> kTagEpochShift && (t >> kTagRequestBits) != (now >> kTagRequestBits);
+}
 
 // The lookup of request b in state sid, d its descriptor.  kShares: by every workgroup of its row, with the
 // arena addressed by key, and claimed by nobody: see Claim.
@@ -439,13 +482,12 @@ __device__ __forceinline__ Found look_up(const TableView &T, const CacheView &Cc
     const bool ckpt = is_checkpoint(kind);
     // (a slot is only read where the tag is of this generation and an earlier call: it does not
     // change after that call, so the two loads need no order)
-    const bool made = (uint32_t)(t >> kTagEpochShift) == Cc.epoch;
     const bool this_call = (t >> kTagRequestBits) == (now >> kTagRequestBits);
-    f.hit = made && !this_call && slot != kNoSlot;
+    f.hit = made_before(t, now) && slot != kNoSlot;
     f.ref = f.hit ? slot : kRefBuild;
     if (f.hit) return f;
     const bool class_this_call = (ct >> kTagRequestBits) == (now >> kTagRequestBits);
-    uint32_t class_state = (uint32_t)(ct >> kTagEpochShift) == Cc.epoch && !class_this_call ? CLASS_READY : CLASS_SELF;
+    uint32_t class_state = made_before(ct, now) ? CLASS_READY : CLASS_SELF;
     if (kShares) {
         f.keep = !this_call || t == mine;
         if (ckpt && class_state != CLASS_READY && (!class_this_call || ct == mine)) class_state = CLASS_OWN;
@@ -498,10 +540,12 @@ lookup_kernel(WG_EARLY_ARGS)
         uint32_t sid = of_first(states[b].sid), aux = of_first(states[b].aux);
         StateDesc d;
         if (tokens) {
-            advance_one(T, Vc, Cc, sid, aux, d, (int32_t)of_first((uint32_t)tokens[b]), true, b);
+            const WalkArgs walk(late);
+            const int32_t t = (int32_t)of_first((uint32_t)tokens[b]);
+            advance_one(T, Vc, Cc, walk, ask_sampled(T, Vc, walk, sid, t), sid, aux, d, t, true, b);
             if (leads) states[b] = wg_state_t{sid, aux};
         } else d = state_of(two_states(T, sid, sid), 0u);
-        f = look_up<false>(T, Cc, tag_now(Cc, of_first(launch)), b, sid, d, ask(T, Cc, sid, aux, d), nullptr);
+        f = look_up<false>(T, Cc, tag_now(Cc.epoch, of_first(launch)), b, sid, d, ask<false>(T, T.lmax, Cc.tags, Cc.class_tags, Cc.direct ? nullptr : Cc.slots, sid, aux, d), nullptr);
     }
     // (an atomic on one address costs 10 ns per wavefront of the launch: statistics are spread, and the claims too
     // where nothing is handed out by their number)
@@ -811,21 +855,26 @@ __device__ __forceinline__ uint4 operator|(const uint4 &a, const uint4 &b) { ret
 __device__ __forceinline__ uint4 operator&(const uint4 &a, const uint4 &b) { return uint4{a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w}; }
 __device__ __forceinline__ uint4 operator~(const uint4 &a) { return uint4{~a.x, ~a.y, ~a.z, ~a.w}; }
 
-// Brings a class table and its plan to LDS; one wavefront.
-__device__ __forceinline__ void stage_class(const TableView &T, RowShared &sh, uint32_t cls, uint32_t lane)
+// A class table and its plan, asked for and brought to LDS; one wavefront, a piece per lane.
+struct StagedClass { uint32_t table; uint4 plan; };
+__device__ __forceinline__ StagedClass ask_class(const TableView &T, uint32_t cls, uint32_t lane)
 {
     static_assert(sizeof(ClassPlan) % 16 == 0 && sizeof(ClassPlan) / 16 <= 64, "a piece per lane");
-    const uint32_t t = reinterpret_cast<const uint32_t *>(T.classes + (size_t)cls * 256u)[lane];
-    uint4 p{0u, 0u, 0u, 0u};
-    if (lane < sizeof(ClassPlan) / 16u) p = reinterpret_cast<const uint4 *>(T.plans + cls)[lane];
-    reinterpret_cast<uint32_t *>(sh.own)[lane] = t;
-    if (lane < sizeof(ClassPlan) / 16u) reinterpret_cast<uint4 *>(&sh.plan)[lane] = p;
+    StagedClass s{};
+    s.table = reinterpret_cast<const uint32_t *>(T.classes + (size_t)cls * 256u)[lane];
+    if (lane < sizeof(ClassPlan) / 16u) s.plan = reinterpret_cast<const uint4 *>(T.plans + cls)[lane];
+    return s;
+}
+__device__ __forceinline__ void put_class(RowShared &sh, const StagedClass &s, uint32_t lane)
+{
+    reinterpret_cast<uint32_t *>(sh.own)[lane] = s.table;
+    if (lane < sizeof(ClassPlan) / 16u) reinterpret_cast<uint4 *>(&sh.plan)[lane] = s.plan;
 }
 
 // Enters a row's claims (see Claim).
 __device__ __forceinline__ void claim_tags(const CacheView &Cc, const RowShared &sh, uint32_t b)
 {
-    const unsigned long long now = tag_now(Cc, sh.launch), mine = now | b;
+    const unsigned long long now = tag_now(Cc.epoch, sh.launch), mine = now | b;
     const Claim c = sh.claim;
     unsigned long long key_was = ~c.key_tag, class_was = ~c.class_tag;
     if ((c.key_tag >> kTagRequestBits) != (now >> kTagRequestBits)) key_was = atomicCAS(&Cc.tags[c.key], c.key_tag, mine);
@@ -1097,6 +1146,22 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
     Cc.ctr->launch++;
 }
 
+// The late arguments that the way of a cached row needs, in registers before it needs them: behind the advance's first loads, or while
+// the other wavefronts wait for the first.  Read where they were needed they were eight waits of 100 cycles in turn.  A cached step, us, so / now,
+// V = 32000, B = 1 4.68 / 4.28; outlines, V = 128256, B = 64 6.88 / 6.64.  (Every wavefront deciding for itself by the tag, without the barrier
+// behind the lookup, and lanes that take the bits they mask from memory instead of LDS: 1 to 10 % slower with logits of 20 MB and more.)
+struct RowArgs {
+    unsigned long long *tags, *class_tags;
+    uint32_t *arena, *bitmask;
+    void *logits;
+    int64_t logits_stride;
+    uint32_t cap_rows, row_stride, epoch, lmax, W, rows;
+    RowArgs() = default;
+    __device__ __forceinline__ explicit RowArgs(Late &late)
+        : tags(late.Cc.tags), class_tags(late.Cc.class_tags), arena(late.Cc.arena), bitmask(late.bitmask), logits(late.logits), logits_stride(late.logits_stride),
+          cap_rows(late.Cc.cap_rows), row_stride(late.Cc.row_stride), epoch(late.Cc.epoch), lmax(late.T.lmax), W(late.Vc.W), rows(late.rows) {}
+};
+
 // kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_lines); 3: as 1, the stores
 // through the L2.
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
@@ -1116,24 +1181,30 @@ rows_kernel(WG_EARLY_ARGS)
     const uint32_t b = blockIdx.y, tid = threadIdx.x, span = late.span, p0 = blockIdx.x * span;
     const uint32_t tok_lo = range_token(Vc.V, p0), tok_hi = range_token(Vc.V, p0 + span);
     const uint32_t w_lo = tok_lo >> 5, w_hi = (tok_hi + 31u) >> 5, n_words = w_hi - w_lo;
-    const uint32_t rs = Cc.row_stride, n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
+    const uint32_t n4 = (n_words + 3u) / 4u;      // (rows are padded to whole 16 bytes)
     uint4 *row4 = reinterpret_cast<uint4 *>(row), *early4 = row4 + n4 + 1u;
     Tickets ticket{kNoTicket, kNoTicket, false};
     uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
+    constexpr bool kSpan = kMode == 1 || kMode == 3;
+    RowArgs args;
     if (kWhole) {
         const uint32_t wave = of_first(tid >> 6);
         uint32_t sid = 0, aux = 0, t = 0;
+        unsigned long long launch = 0;
         StateDesc d{};
         Asked asked{};
+        WalkArgs walk;
         if (wave == 0u) {
-            const unsigned long long launch = Cc.ctr->launch;
+            launch = Cc.ctr->launch;
             const wg_state_t st = states[b];
             if (tokens) t = of_first((uint32_t)tokens[b]);
             sid = of_first(st.sid); aux = of_first(st.aux);
             // The state and the call's number have to be here before the row's ticket counts this workgroup: the last one of the row
-            // replaces the state, the last one of the call the number (close_row, close_call).  In one wait with them a word of each line of the
-            // arguments, so that whoever reads them later does not wait for memory.
-            asm volatile("" :: "s"(launch), "s"(sid), "s"(aux), "s"(late.T.lit), "s"(late.Vc.rows), "s"(late.Cc.tags), "s"(late.Cc.tasks), "s"(late.rows));
+            // replaces the state, the last one of the call the number (close_row, close_call).  In one wait with them what the advance
+            // needs of the late arguments and a word of each of their lines, so that whoever reads them later does not wait for memory.
+            walk = WalkArgs(late);
+            asm volatile("" :: "s"(launch), "s"(sid), "s"(aux), "s"(walk.lit), "s"(walk.codes), "s"(walk.n_chunks), "s"(walk.eos_id), "s"(late.Vc.rows), "s"(late.Cc.tags), "s"(late.Cc.tasks), "s"(late.rows));
+            hold(walk.lit, walk.codes, walk.n_chunks, walk.eos_id);
             if (tid == 0) sh.launch = launch;
         }
         __syncthreads();
@@ -1141,25 +1212,48 @@ rows_kernel(WG_EARLY_ARGS)
             ticket.row_last = atomicAdd(&Cc.ctr->tickets[b * kTicketStride], 1u) == late.shares - 1u;
             if (ticket.row_last) ticket.group = atomicAdd(group_counter(Cc, b), 1u);       // (waited for behind the walk)
         }
+        // (behind the advance's first loads, or while the first wavefront is busy)
+        auto read_args = [&]() {
+            args = RowArgs(late);
+            hold(args.tags, args.class_tags, args.arena, args.cap_rows, args.row_stride, args.epoch, args.lmax, args.bitmask, args.W, args.rows);
+            if (kSpan) hold(args.logits, args.logits_stride);
+        };
         if (wave == 0u) {
-            if (tokens) advance_one(T, Vc, Cc, sid, aux, d, (int32_t)t, p0 == 0u, b);
-            else d = state_of(two_states(T, sid, sid), 0u);
-            asked = ask(T, Cc, sid, aux, d);
+            if (tokens) {
+                const Sampled s = ask_sampled(T, Vc, walk, sid, (int32_t)t);
+                read_args();
+                advance_one(T, Vc, Cc, walk, s, sid, aux, d, (int32_t)t, p0 == 0u, b);
+            } else {
+                const uint32_t words = two_states(T, sid, sid);
+                read_args();
+                d = state_of(words, 0u);
+            }
+            asked = ask<true>(T, args.lmax, args.tags, args.class_tags, nullptr, sid, aux, d);
             if (tid == 0) {
                 sh.state = wg_state_t{sid, aux};
                 sh.key = asked.key;
                 sh.desc = d;
             }
-        } else if (wave >= 2u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
+        } else {
+            read_args();
+            if (wave >= 2u) for (uint32_t q = tid - 128u; q < n4; q += kRowThreads - 128u) early4[q] = uint4{0u, 0u, 0u, 0u};
+        }
         __syncthreads();
         // (key k has arena row k: the row is requested while its tag is looked at, and what a missing row takes from the
         // state's own class table)
         const uint32_t key = of_first(sh.key);
-        if (key < Cc.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)key * rs + w_lo)[tid];
-        if (late.rows > kTicketGroup && group_last(ticket, b, late.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
-        if (wave == 1u && is_checkpoint(of_first(sh.desc.kind_byte) & 0xFFu)) stage_class(T, sh, of_first(sh.desc.cls), tid & 63u);
+        bool ckpt = false;
+        StagedClass staged{};
+        if (wave == 1u) {
+            ckpt = is_checkpoint(of_first(sh.desc.kind_byte) & 0xFFu);
+            if (ckpt) staged = ask_class(T, of_first(sh.desc.cls), tid & 63u);
+        }
+        if (key < args.cap_rows && tid < n4) ahead = reinterpret_cast<const uint4 *>(args.arena + (size_t)key * args.row_stride + w_lo)[tid];
+        if (args.rows > kTicketGroup && group_last(ticket, b, args.rows)) ticket.call = atomicAdd(&Cc.ctr->call_ticket, 1u);
+        close_row(Cc, ticket, b, states, tokens, sh);
+        if (ckpt) put_class(sh, staged, tid & 63u);
         if (wave == 0u) {
-            const Found f = look_up<true>(T, Cc, tag_now(Cc, of_first(sh.launch)), b, sid, d, asked, &sh.claim);
+            const Found f = look_up<true>(T, Cc, tag_now(args.epoch, launch), b, sid, d, asked, &sh.claim);
             if (tid == 0) {
                 sh.ref = f.ref;
                 if (f.ref == kRefBuild) sh.task = f.me;
@@ -1167,7 +1261,6 @@ rows_kernel(WG_EARLY_ARGS)
             }
         }
         __syncthreads();
-        close_row(Cc, ticket, b, states, tokens, sh);
     }
     const RowTask in = kWhole ? sh.task : Cc.tasks[b];   // (requested with the reference; only used where that asks for it)
     const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kWhole ? sh.ref : Cc.row_ref[b]));
@@ -1182,20 +1275,29 @@ rows_kernel(WG_EARLY_ARGS)
         if (!kWhole) {
             if (tid == kRowThreads - 1u) { sh.task.hop[0] = ha; sh.task.hop[1] = hb; }
             for (uint32_t q = tid; q < n4; q += kRowThreads) early4[q] = uint4{0u, 0u, 0u, 0u};
-            if (tid >> 6 == 1u && is_checkpoint(me.kind)) stage_class(T, sh, me.cls, tid & 63u);
+            if (tid >> 6 == 1u && is_checkpoint(me.kind)) put_class(sh, ask_class(T, me.cls, tid & 63u), tid & 63u);
             __syncthreads();
         }
         make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b, kWhole && p0 == 0u);
+        // (read again, which the compiler does not see: it would keep them in registers meanwhile)
+        Late *again = &late;
+        asm volatile("" : "+s"(again));
+        args = RowArgs(*again);
+        ahead = uint4{0u, 0u, 0u, 0u};
     }
+    if (!kWhole) args = RowArgs(late);
     // out: to the cache, the caller's bitmask, and LDS for the masking
-    const uint4 *src = reinterpret_cast<const uint4 *>(Cc.arena + (size_t)(ref < Cc.cap_rows ? ref : 0u) * rs + w_lo);
-    uint4 *kept = reinterpret_cast<uint4 *>(Cc.arena + (size_t)slot * rs + w_lo);
-    uint32_t *dst = late.bitmask + (size_t)b * Vc.W + w_lo;
+    const bool copied = ref < args.cap_rows;
+    const uint32_t *row_in = args.arena + (size_t)(copied ? ref : 0u) * args.row_stride + w_lo;
+    const uint4 *src = reinterpret_cast<const uint4 *>(row_in);
+    uint4 *kept = reinterpret_cast<uint4 *>(args.arena + (size_t)slot * args.row_stride + w_lo);
+    uint32_t *dst = args.bitmask + (size_t)b * args.W + w_lo;
+    Elem *logits = static_cast<Elem *>(args.logits) + (int64_t)b * args.logits_stride;
     const bool aligned = reinterpret_cast<uintptr_t>(dst) % 16u == 0u;
     for (uint32_t q = tid; q < n4; q += kRowThreads) {
         uint4 x{0u, 0u, 0u, 0u};
         if (ref == kRefBuild) x = row4[q] | early4[q];
-        else if (ref < Cc.cap_rows) x = kWhole && q == tid ? ahead : src[q];
+        else if (copied) x = kWhole && q == tid ? ahead : src[q];
         if (slot != kNoSlot) kept[q] = x;
         if (aligned) {
             if (4u * q + 4u <= n_words) reinterpret_cast<uint4 *>(dst)[q] = x;
@@ -1207,11 +1309,11 @@ rows_kernel(WG_EARLY_ARGS)
         }
         if (kMode || !aligned) row4[q] = x;
     }
-    if (kWhole) close_call(Cc, ticket, b, late.rows, sh);
+    if (kWhole) close_call(Cc, ticket, b, args.rows, sh);
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
-    if (kMode == 1 || kMode == 3) mask_span<Elem, kMode == 3>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
-    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 8u : 5u>(static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride, tok_lo, tok_hi, row);
+    if (kSpan) mask_span<Elem, kMode == 3>(logits, tok_lo, tok_hi, row);
+    if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 8u : 5u>(logits, tok_lo, tok_hi, row);
     if (!kWhole && blockIdx.x == 0 && b == 0 && tid == 0) {
         close_fill(Cc, late.rows, Cc.ctr->n_claims, Cc.ctr->n_class_claims);
         Cc.ctr->n_claims = 0; Cc.ctr->n_class_claims = 0;
