@@ -281,6 +281,7 @@ class Handle:
         self._h = C.c_void_p()
         _check(L.wg_compile(c_texts, c_args, n, vocab._v, flags, C.byref(self._h), starts.ctypes.data))
         self.start_states = starts[:n]
+        self._starts = None                      # (see _append_starts)
         self.num_states = L.wg_num_states(self._h)
         self.W = L.wg_mask_words(self._h)
         self.V = vocab.V
@@ -313,9 +314,19 @@ class Handle:
             _check(L.wg_add_instances(self._h, marshalled[0], marshalled[1], n, starts.ctypes.data, _stream_ptr(stream)))
         else:
             _native.add_instances(self._p, texts, args, starts.ctypes.data, n, stream)
-        self.start_states = np.concatenate([self.start_states, starts[:n]])
+        self.start_states = self._append_starts(starts[:n])
         self.num_states = L.wg_num_states(self._h)
         return starts[:n]
+
+    def _append_starts(self, new):
+        """All start states so far, in a buffer that doubles (copied as a whole they took longer than the addition from
+        some ten thousand instances on)."""
+        have, n = self.start_states, len(self.start_states) + len(new)
+        if self._starts is None or len(self._starts) < n or have.base is not self._starts:
+            self._starts = np.empty((max(2 * n, 64), 2), dtype=np.uint32)
+            self._starts[:len(have)] = have
+        self._starts[len(have):n] = new
+        return self._starts[:n]
 
     def num_instances(self):
         return load_library().wg_num_instances(self._h)

@@ -110,3 +110,14 @@ def test_errors_of_other_calls_are_not_reported_as_these(torch_cuda):
             hip.hipGetLastError()
     torch.cuda.synchronize()
     assert (H.host_mask(mask) == o.fill_masks(H.host_states(st))).all()
+
+
+def test_start_states_of_additions(torch_cuda):
+    """The start states of all instances, over additions of one and of many; what a caller took earlier stays as it was."""
+    w, o, h, st, mask = _batch(torch_cuda, 8)
+    want, taken = h.start_states.copy(), []
+    for n in (1, 3, 8, 1, 8, 8):
+        taken.append((h.start_states, want.copy()))
+        want = np.concatenate([want, h.add_instances(w.texts[:n], w.args[:n])])
+        assert (h.start_states == want).all() and len(h.start_states) == h.num_instances()
+    assert all((a == b).all() for a, b in taken)

@@ -113,6 +113,23 @@ def test_states_inside_one_instance_share_too():
     assert k < n
 
 
+def test_instances_that_differ_only_in_where_they_lead_keep_their_own_keys():
+    """Two templates with the same states in the same order, whose condition leads back in one and on in the other; and literal runs,
+    bounds and bytes that differ in one place.  Only an instance that is the same state for state takes another's keys."""
+    cond = 'Wait(allow={\\x20}, true_waits={\\x2C}, false_waits={\\x5D})'
+    texts = ['DoWhile(body=Sequence(Write("ab"), Wait(denies={}, wait={<}, max=9)), condition=%s)' % cond,
+             'Sequence(Write("ab"), Wait(denies={}, wait={<}, max=9), IfElse(condition=%s, if_body=None, else_body=None))' % cond,
+             'Sequence(Write("a"), Write("b"), Wait(denies={}, wait={<}, max=9), IfElse(condition=%s, if_body=None, else_body=None))' % cond,
+             'Sequence(Write("ab"), Wait(denies={}, wait={<}, max=8), IfElse(condition=%s, if_body=None, else_body=None))' % cond,
+             'Sequence(Write("ac"), Wait(denies={}, wait={<}, max=9), IfElse(condition=%s, if_body=None, else_body=None))' % cond]
+    for order in itertools.permutations(range(5)):
+        t = wg.Table([texts[i] for i in order] * 2, None, flags=wg.EOS_RESTART, lmax=4)
+        first = [t.start_state(i) for i in range(10)]
+        assert all(b - a == 5 for a, b in zip(first, first[1:]))
+        keys = [[t.state(s + k)["key"] for k in range(5)] for s in first]
+        assert keys[5:] == keys[:5] and len({tuple(k) for k in keys}) == 5, order
+
+
 def test_a_failed_add_leaves_the_keys_as_they_were():
     vocab = _vocab(b"ab<", 3)
     good = ['Sequence(Write("ab"), Wait(allow={a}, wait={<}, max=2), Write("b"))',
