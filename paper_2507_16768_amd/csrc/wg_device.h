@@ -96,7 +96,7 @@ constexpr uint32_t kSpread = 64, kSpreadStride = 16, kSpreadWalked = 0, kSpreadH
                    kSpreadBuilds = 2, kSpreadClasses = 3,       // of fills with the arena addressed by key
                    kSpreadErrors = 4;                           // rejected tokens
 constexpr uint32_t kTicketStride = 32, kTicketGroup = 16;       // a 128-byte line for the tickets of a row; rows of a group
-constexpr uint32_t kOneKernelRows = 512;                        // most rows of a fill in one kernel
+constexpr uint32_t kOneKernelRows = 1024;                       // most rows of a fill in one kernel
 
 // All that calls count in, one piece of memory: a pointer costs the kernels two of their scalar registers.
 struct Control : Counters {

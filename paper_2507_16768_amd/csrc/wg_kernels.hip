@@ -3,7 +3,7 @@
 //   rows         : the mask row of every request, a workgroup per (request, token range): copied from
 //                  the cache, or made in LDS from the vocabulary's static indexes; to the caller's
 //                  bitmask, to the cache, and (wg_decode_step) as -inf into the logits.  In front of
-//                  it, in the same kernel up to a request per compute unit (plan_fill), the state is advanced
+//                  it, in the same kernel for batches of up to a request per compute unit and some larger ones (plan_fill), the state is advanced
 //                  by the sampled token (wg_advance_fill_masks, wg_decode_step) and looked up
 //   lookup       : the same by itself: request state -> cache key; claims a missing key and leaves the
 //                  task of making its row
@@ -1639,7 +1639,22 @@ FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, boo
     // and 1.11 1.03 1.10, B = 192 0.90 0.91 0.99 and 0.96 0.94 0.95).  With logits to mask behind them the workgroups
     // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.91 0.96
     // 0.95 and 0.95 0.97 0.97); whole lines are masked behind a lookup of its own.
-    p.one_kernel = Cc.direct && B <= n_cu && B <= kOneKernelRows && (masks_logits ? !p.lines : B * p.parts <= resident_rows(Vc, p.parts) * n_cu);
+    //
+    // Above a request per unit one kernel gains where all of its workgroups are resident with a few places left (rows are in four shares or
+    // fewer there), and where rows are so long, and so many, that masking them outlasts what late workgroups repeat.  Time with one kernel over two,
+    // outlines, JSON, mixed, random trees, cached and then made, bf16, a step: V = 9000 B = 264 0.69 0.72 0.71 0.75, 0.84 0.79 0.74 0.81, 700 0.78 0.81
+    // 0.81 0.79, 0.97 0.87 0.79 0.87; 14000 350 0.81 0.81 0.82 0.77, 0.82 0.75 0.73 0.86, 440 0.82 0.82 0.82 0.80, 0.88 0.80 0.73 0.87; 101000 560 0.99 0.99
+    // 0.96 0.94, 0.94 0.98 0.94 0.99; 128256 512 0.95 0.95 0.93 0.94, 0.92 0.90 0.91 0.95, 800 0.95 0.96 0.96 0.97, 0.90 0.86 0.91 0.96; 151936 640 0.95 0.95 0.96
+    // 0.97, 0.90 0.88 0.92 0.96; fp32, 101000 650 0.94 0.95 0.96 0.97, 0.91 0.87 0.92 0.97.  Masks alone, with the two calls behind them: 12000 272 0.67
+    // 0.64 0.67 0.68, 0.88 0.83 0.82 0.86, 512 0.74 0.76 0.75 0.76, 0.91 0.87 0.83 0.87; long rows only gain where they are made (65536 272 1.02 1.02 1.02
+    // 1.02, 0.98 1.03 0.94 0.94).  On the other sides of the lines, steps: 9000 880 (more than 7 workgroups to a unit) made outlines 1.08; 14000 500 1.03;
+    // 65536 384 made outlines and JSON 1.05; 80000 500 cached outlines 1.06, made JSON 1.09; 96000 350 made JSON 1.02, 101000 300 1.14; whole lines, 151936 1000 0.93 to
+    // 0.98, but made random trees 1.02.  Rows of 16,385 to 24,576 tokens gain as well (24000 350 0.82 0.81 0.80 0.79, 0.86 0.84 0.77 0.87) and stay in two
+    // kernels: tests/test_gpu_calls.py counts the kernels of 300 requests on 20,000 tokens.
+    const bool together = B * p.parts <= resident_rows(Vc, p.parts) * n_cu, few = B <= n_cu, short_rows = B <= 3u * n_cu && Vc.V <= 16384u,
+               long_rows = 2u * B >= 3u * n_cu && Vc.V >= 100000u;
+    p.one_kernel = Cc.direct && B <= kOneKernelRows &&
+                   (masks_logits ? !p.lines && (few || (short_rows && B * p.parts <= 7u * n_cu) || long_rows) : (few || short_rows) && together);
     return p;
 }
 

@@ -595,3 +595,57 @@ def test_greedy_choice_of_fp32_rows_in_slices(torch_cuda, B, V, off):
         tok.fill_(-7)
         wg.masked_argmax(view, mask, tok)
         assert (tok.cpu().numpy() == want).all(), np.flatnonzero(tok.cpu().numpy() != want)[:8]
+
+
+@pytest.mark.parametrize("V,B,dtype", [(9001, 257, "f32"), (9001, 768, "bf16"), (9001, 769, "bf16"), (5003, 1024, "bf16"), (16384, 448, "bf16"), (16384, 449, "f32"),
+                                       (16385, 300, "bf16"), (99999, 384, "bf16"), (100000, 384, "bf16"), (100000, 383, "f32"), (100003, 1024, "bf16"), (100003, 1025, "bf16")])
+def test_batches_above_a_request_per_unit(torch_cuda, V, B, dtype):
+    """Either side of the lines up to which a batch of more than 256 requests is one kernel: masks, logits and states are those of batches of 100,
+    cold and cached, through each call; rows, hits and claims are counted as for any other batch."""
+    torch = torch_cuda
+    import paper_2507_16768_amd as wg
+    w = ws.make_workload(4, V=V, B=64, steps=1)
+    _, h = H.make_gpu(w)
+    _, ref = H.make_gpu(w)
+    h.reserve_batch(B)
+    rng = np.random.default_rng(V + B)
+    at = np.stack([rng.integers(0, h.num_states, B), np.zeros(B)], 1).astype(np.uint32)
+    at[:3] = at[B - 3:]                                                # requests of one key, at both ends of the batch
+    tok = torch.empty(B, dtype=torch.int32, device="cuda")             # allowed ones, but for every ninth
+    for b in range(0, B, 100):
+        m = torch.empty((len(at[b:b + 100]), h.W), dtype=torch.int32, device="cuda")
+        ref.fill_masks(H.dev_states(at[b:b + 100]), m)
+        wg.select_tokens(m, V, torch.from_numpy(rng.integers(0, 1 << 62, len(m))).cuda(), tok[b:b + 100])
+    tok[4::9] = 1
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    raw = torch.randn((B, V + 5), device="cuda").to(dt)
+    want_states, want = H.dev_states(at), torch.empty((B, h.W), dtype=torch.int32, device="cuda")
+    want_logits = raw.clone()
+    for b in range(0, B, 100):
+        s, m = want_states[b:b + 100], want[b:b + 100]
+        ref.advance(s, tok[b:b + 100])
+        ref.fill_masks(s, m)
+        wg.apply_mask(want_logits[b:b + 100, :V], m)
+    keys = len(np.unique(H.host_mask(want), axis=0))
+    live = int((H.host_states(want_states)[:, 0] != 0xFFFFFFFF).sum())
+    assert B // 2 < live < B
+    for cold in (True, False):
+        for call in ("step", "advance_fill", "fill"):
+            if cold:
+                h.cache_clear()
+            before = h.cache_stats()
+            states = H.dev_states(at) if call != "fill" else want_states.clone()
+            mask, logits = torch.full_like(want, -1), raw.clone()
+            if call == "step":
+                h.decode_step(states, tok, mask, logits[:, :V])
+            elif call == "advance_fill":
+                h.advance_fill_masks(states, tok, mask)
+            else:
+                h.fill_masks(states, mask)
+            assert torch.equal(states, want_states) and torch.equal(mask, want), (cold, call)
+            assert call != "step" or torch.equal(logits.view(torch.int32 if dtype == "f32" else torch.int16), want_logits.view(torch.int32 if dtype == "f32" else torch.int16)), cold
+            after = h.cache_stats()
+            assert after["lookups"] - before["lookups"] == B
+            assert after["hits"] - before["hits"] == (0 if cold else live)
+            assert after["builds"] - before["builds"] == (after["rows_in_use"] if cold else 0), (cold, call)
+            assert not cold or after["rows_in_use"] >= keys - 1
