@@ -659,7 +659,7 @@ def main():
                  "dense_equivalent_GBs": dense_warm / sec_warm / 1e9,
                  "frac_of_hbm_peak_dense_equivalent": dense_warm / sec_warm / 1e9 / HBM_PEAK_GBS},
         "kernels_us_per_step": {"cold": kt_cold, "warm": kt_warm},
-        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, one launch up to a request per compute unit, else two)",
+        "single_call_step": {"note": "the same steps through wg_decode_step (advance + fill + apply, one launch up to a request per compute unit and for some larger batches, else two)",
                              "cold_ms_per_step": sec_single_cold * 1e3, "warm_ms_per_step": sec_single_warm * 1e3,
                              "cold_request_steps_per_s": B / sec_single_cold,
                              "warm_request_steps_per_s": B / sec_single_warm,

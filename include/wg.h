@@ -212,7 +212,7 @@ uint32_t wg_num_instances(wg_handle_t h);
  * smaller cache -- rows are handed out in order of first use (rows in use stay where they are); once
  * all are taken, further keys are still served correctly but rebuilt on every call that needs them
  * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  A fill of at most a
- * request per compute unit is one kernel in the first case and two in the second, 2 to 4 us more a step;
+ * request per compute unit (and some larger ones) is one kernel in the first case and two in the second, 2 to 4 us more a step;
  * an engine that expects additions keeps the first by making room for their keys here, at set-up.
  * Synchronises the device and clears the cache. */
 int wg_cache_resize(wg_handle_t h, uint32_t rows);
@@ -237,8 +237,8 @@ uint32_t wg_mask_words(wg_handle_t h);      /* W = ceil(V/32) */
  * wg_fill_masks: d_bitmask[b][0..W) <- mask of d_states[b] (mask creation with the global
  * cache of the section "Mask Generation and Global Caching"): cached rows are copied, missing
  * ones are made, and kept once per distinct key.  An ERROR or out-of-range state gets an all-zero
- * row.  One kernel for up to a request per compute unit (fewer from about 350,000 tokens on) while the
- * cache has a row for every key, else two (a workgroup for every 1/1 to 1/32 of a row). */
+ * row.  One kernel for up to a request per compute unit (fewer from about 350,000 tokens on, up to three per unit
+ * on rows of at most 16,384 tokens) while the cache has a row for every key, else two (a workgroup for every 1/1 to 1/32 of a row). */
 int wg_fill_masks(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint32_t *d_bitmask,
                   void *stream);
 
@@ -361,7 +361,7 @@ typedef struct {
     uint64_t fill_calls, advance_calls;   /* (an advance inside a fill counts as part of the fill) */
     double lookup_ms, scan_ms, build_ms, gather_ms, advance_ms;   /* summed kernel durations: a fill has a lookup kernel and
                                                                      one that makes or copies the rows (build_ms); one of up
-                                                                     to a request per compute unit has the second alone, which then does the lookups,
+                                                                     to a request per compute unit, and some larger ones, have the second alone, which then does the lookups,
                                                                      and adds nothing to lookup_ms.  scan and gather stay 0 */
     uint64_t apply_calls;
     double apply_ms;
