@@ -60,7 +60,6 @@ struct TableView {
     const StateDesc *states;
     uint32_t n_states;
     LateRef<const uint8_t *> classes, lit;
-    LateRef<const ClassCodes *> codes;
     LateRef<const ClassPlan *> plans;
     LateRef<uint32_t> lmax;
 };
@@ -83,7 +82,7 @@ struct CacheView {
 };
 #define WG_VIEWS \
     Late &late = late_args(); \
-    const TableView T{descs, n_states, late.T.classes, late.T.lit, late.T.codes, late.T.plans, late.T.lmax}; \
+    const TableView T{descs, n_states, late.T.classes, late.T.lit, late.T.plans, late.T.lmax}; \
     const VocabView Vc{len8, chunks, V, late.Vc.rows, late.Vc.dirs, late.Vc.index, late.Vc.W, late.Vc.lmax, late.Vc.n_chunks, late.Vc.eos_id}; \
     const CacheView Cc{ctr, late.Cc.tags, late.Cc.class_tags, late.Cc.slots, late.Cc.arena, late.Cc.class_rows, late.Cc.row_ref, late.Cc.free_rows, \
                    late.Cc.tasks, late.Cc.cap_rows, late.Cc.direct, late.Cc.row_stride, late.Cc.epoch}
@@ -368,8 +367,9 @@ __device__ __forceinline__ void advance_one(const TableView &T, const VocabView 
 
 // One request to a workgroup up to two on a compute unit, four above: with one / with four, mixed, us, B = 64 3.17 / 3.32, 256
 // 3.20 / 3.38, 512 3.40 / 3.48, 1024 3.49 / 3.62, 8192 5.58 / 5.22.  The first request's state and token come in one wait with the arguments that follow the
-// early ones (one after the other, a copy of the states and wg_advance, B = 1 4.2, now 4.0, 64 4.4, 4.3).  Batches of 16,384 and 60,000 take 6.6 to
-// 7.5 and 19 to 20 us, a thread each with eight bytes at a time took 6.1 to 8.6 and 13 to 19.
+// early ones (one after the other, a copy of the states and wg_advance, B = 1 4.2, now 4.0, 64 4.4, 4.3).  Batches of 16,384 and 60,000 took 6.6 to
+// 7.5 and 19 to 20 us, a thread each with eight bytes at a time 6.1 to 8.6 and 13 to 19.  These are times before look_ahead; with it, and a
+// copy of the states, 16,384 9.2 to 9.5 -> 8.6 to 8.7, 60,000 22.6 to 22.8 -> 19.9 to 20.5.
 constexpr uint32_t kAdvanceBlocks = 1u << 20;
 template <uint32_t kWaves>
 __global__ void __launch_bounds__(64 * kWaves)
@@ -738,14 +738,14 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 // The first wavefront sees to the candidates (and to all that it needs for them itself: the successors' class
 // tables and literal bytes come with the directories), the others to the rest.  What the walks need of the
 // successors lies in LDS and not in scalar registers, of which this kernel has too few: what they do not hold is kept in
-// lanes of vector registers, 61 or 62 values with the lookup in a kernel before it and 73 (masks only: 78) with it in front.
+// lanes of vector registers, 61 to 63 values with the lookup in a kernel before it and 80 (masks only: 77) with it in front.
 // Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
 // that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
 // what is left in LDS and decides them 64 at a time, so that the walks run on full wavefronts.
 //
-// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 7.1 us, the launch and the
-// chain state -> descriptor -> tag -> row of four trips to memory; made rows 15.3 us for 19 MB, the same chain and
+// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 7.2 us, the launch and the
+// chain state -> descriptor -> tag -> row of four trips to memory; made rows 15.1 us for 19 MB, the same chain and
 // then plan -> directory -> entries -> chunks -> walk, with 2.8 M instructions of wavefronts (5 us of the chip's
 // vector units) in it.  B = 1024 and 141 class tables a call, two kernels: copied rows 5 + 10.0 us, made rows 5 + 57,
 // with 15 M vector instructions of wavefronts (25 us).
@@ -1167,8 +1167,7 @@ struct RowArgs {
 // kWhole: the lookups have not been done: each workgroup of a row does its row's, with the advance
 // before it (tokens may be null).  One launch instead of two, and a row waits for its own lookup only, not for
 // the longest walk of the batch.  While the first wavefront walks, the last one takes the row's ticket.  The last
-// workgroup of a row to have read its state writes the new one behind its lookup (close_row), before it makes or copies its
-// share; the last such row of all opens the next call (close_call).  (A ticket on one address for every workgroup of the call, taken by the wavefront that walks, cost
+// workgroup of a row to have read its state writes the new one as soon as it has it (close_row), before it looks it up; the last such row of all opens the next call (close_call).  (A ticket on one address for every workgroup of the call, taken by the wavefront that walks, cost
 // 10 ns a workgroup: this fill took 28 us for 2,048 workgroups, 18 as it is now.)  Within 64 vector registers, so
 // that 8 workgroups of a unit are resident: with 7 the last 256 of 2,048 began 7 to 11 us after the others.
 template <typename Elem, int kMode, bool kWhole>
