@@ -281,7 +281,6 @@ class Handle:
         self._h = C.c_void_p()
         _check(L.wg_compile(c_texts, c_args, n, vocab._v, flags, C.byref(self._h), starts.ctypes.data))
         self.start_states = starts[:n]
-        self._starts = None                      # (see _append_starts)
         self.num_states = L.wg_num_states(self._h)
         self.W = L.wg_mask_words(self._h)
         self.V = vocab.V
@@ -314,19 +313,34 @@ class Handle:
             _check(L.wg_add_instances(self._h, marshalled[0], marshalled[1], n, starts.ctypes.data, _stream_ptr(stream)))
         else:
             _native.add_instances(self._p, texts, args, starts.ctypes.data, n, stream)
-        self.start_states = self._append_starts(starts[:n])
+        self._append_starts(starts[:n])
         self.num_states = L.wg_num_states(self._h)
         return starts[:n]
 
+    @property
+    def start_states(self):
+        """Start states [n, 2] of all instances so far.  The array is the caller's: an addition makes another one."""
+        self._starts_out = True
+        return self._starts
+
+    @start_states.setter
+    def start_states(self, states):
+        self._starts, self._starts_room, self._starts_out = states, None, True
+
     def _append_starts(self, new):
-        """All start states so far, in a buffer that doubles (copied as a whole they took longer than the addition from
-        some ten thousand instances on)."""
-        have, n = self.start_states, len(self.start_states) + len(new)
-        if self._starts is None or len(self._starts) < n or have.base is not self._starts:
-            self._starts = np.empty((max(2 * n, 64), 2), dtype=np.uint32)
-            self._starts[:len(have)] = have
-        self._starts[len(have):n] = new
-        return self._starts[:n]
+        """While nobody has asked for the array, it grows in a buffer that doubles (copied as a whole, the start states took
+        longer than the addition from some ten thousand instances on)."""
+        out, self._starts_out = self._starts_out, False
+        have, room = self._starts, self._starts_room
+        n = len(have) + len(new)
+        if out:
+            self._starts, self._starts_room = np.concatenate([have, new]), None
+            return
+        if room is None or len(room) < n:
+            room = np.empty((max(2 * n, 64), 2), dtype=np.uint32)
+            room[:len(have)] = have
+        room[len(have):n] = new
+        self._starts, self._starts_room = room[:n], room
 
     def num_instances(self):
         return load_library().wg_num_instances(self._h)

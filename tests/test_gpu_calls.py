@@ -121,3 +121,28 @@ def test_start_states_of_additions(torch_cuda):
         want = np.concatenate([want, h.add_instances(w.texts[:n], w.args[:n])])
         assert (h.start_states == want).all() and len(h.start_states) == h.num_instances()
     assert all((a == b).all() for a, b in taken)
+
+
+def test_start_states_given_out_are_the_callers(torch_cuda):
+    """What a caller writes into an array that it was given before an addition is not in the handle's behind it; what it writes into
+    the handle's present one is, and so is an array that it puts in its place.  Additions leave all of them as they are."""
+    w, o, h, st, mask = _batch(torch_cuda, 8)
+    add = lambda n: h.add_instances(w.texts[:n], w.args[:n])
+    taken = []
+    for n in (1, 8, 2, 40):                                            # also with additions in between that nobody looks behind
+        mine, want = h.start_states, h.start_states.copy()
+        for m in (n, 1, 3)[:1 + n % 3]:
+            want = np.concatenate([want, add(m % 8 + 1)])
+        mine[:] = 0xDEAD
+        assert (h.start_states == want).all()
+        taken.append((mine, np.full_like(mine, 0xDEAD)))
+    h.start_states[0] = (7, 9)
+    want = np.concatenate([h.start_states, add(2)])
+    assert (h.start_states == want).all() and tuple(want[0]) == (7, 9)
+    whole = h.start_states
+    h.start_states = whole[:5]
+    taken.append((whole, whole.copy()))
+    want = np.concatenate([whole[:5], add(3)])
+    want = np.concatenate([want, add(3)])
+    assert (h.start_states == want).all()
+    assert all((a == b).all() for a, b in taken)
