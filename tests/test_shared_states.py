@@ -4,6 +4,7 @@ library gives one key must have, budget for budget, the same mask in the oracle,
 whose longest token is as long as the lowering was told.  The oracle does not know about keys:
 its masks come from walking every token from every state."""
 import itertools
+import time
 
 import numpy as np
 import pytest
@@ -128,6 +129,25 @@ def test_instances_that_differ_only_in_where_they_lead_keep_their_own_keys():
         assert all(b - a == 5 for a, b in zip(first, first[1:]))
         keys = [[t.state(s + k)["key"] for k in range(5)] for s in first]
         assert keys[5:] == keys[:5] and len({tuple(k) for k in keys}) == 5, order
+
+
+def test_many_templates_that_differ_only_in_where_they_lead_lower_as_fast_as_others():
+    """2^13 templates with the same states in the same order, the literals of each in the one or the other branch, or in a branch and
+    behind it: finding out that none has an earlier one's shape takes no more than for as many that differ in a byte."""
+    cond = 'condition=Wait(allow={\\x20}, true_waits={\\x2C}, false_waits={\\x5D})'
+    ab = 'IfElse(%s, if_body=Write("ab"), else_body=None)' % cond
+    kinds = {"byte": (ab, 'IfElse(%s, if_body=Write("ac"), else_body=None)' % cond), "branch": (ab, 'IfElse(%s, if_body=None, else_body=Write("ab"))' % cond),
+             "behind": ('IfElse(%s, if_body=Write("a"), else_body=Write("c"))' % cond, 'Sequence(IfElse(%s, if_body=Write("a"), else_body=None), Write("c"))' % cond)}
+    took = {}
+    for kind, two in kinds.items():
+        texts = ["Sequence(%s)" % ", ".join(two[k >> i & 1] for i in range(13)) for k in range(1 << 13)]
+        for _ in range(3):
+            start = time.process_time()
+            t = wg.Table(texts, None, flags=wg.EOS_RESTART, lmax=4)
+            took[kind] = min(took.get(kind, 1e9), time.process_time() - start)
+        first = [t.start_state(i) for i in (0, 1, 5000)]
+        assert len({t.state(s)["key"] for s in first}) == 3
+    assert max(took.values()) < 2.5 * took["byte"], took
 
 
 def test_a_failed_add_leaves_the_keys_as_they_were():
