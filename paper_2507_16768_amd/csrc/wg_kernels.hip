@@ -738,7 +738,7 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 // The first wavefront sees to the candidates (and to all that it needs for them itself: the successors' class
 // tables and literal bytes come with the directories), the others to the rest.  What the walks need of the
 // successors lies in LDS and not in scalar registers, of which this kernel has too few: what they do not hold is kept in
-// lanes of vector registers, 61 to 63 values with the lookup in a kernel before it and 80 (masks only: 77) with it in front.
+// lanes of vector registers, 61 or 62 values with the lookup in a kernel before it and 77 to 80 with it in front.
 // Every candidate is then decided by its bytes, so an index may offer any superset of the tokens
 // that count.  The candidates of all ranges are one sequence, handed out to the wavefronts in
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
@@ -1146,9 +1146,14 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
     Cc.ctr->launch++;
 }
 
-// The late arguments that the way of a cached row needs, in registers before it needs them: behind the advance's first loads, or while
-// the other wavefronts wait for the first.  Read where they were needed they were eight waits of 100 cycles in turn.  A cached step, us, so / now,
-// V = 32000, B = 1 4.68 / 4.28; outlines, V = 128256, B = 64 6.88 / 6.64.  (Every wavefront deciding for itself by the tag, without the barrier
+// The late arguments that the way of a cached row needs, asked for before it needs them: behind the advance's first loads, or while
+// the other wavefronts wait for the first.  Read where they were needed they were eight waits of 100 cycles in turn.  Held in registers from there to the
+// end (kHeld) where the logits are masked through the L2: eight cached steps, outlines, V = 128256, B = 64, us, so / not, 51.4 / 51.5, cold ones of 96 mixed
+// requests on V = 100003 111.7 / 112.3.  Not where more logits are masked, which are asked for again behind the lookup: the kernel has too few
+// scalar registers to hold what its end needs through the lookup.  Held / asked for again, V = 151936, B = 256, mixed, cached 169.7 / 167.5, cold 216.9 / 216.4,
+// random trees 184 / 182.8, outlines 135.3 / 134.9, cold 175 / 173.1.  (Neither held nor asked for again, by which the compiler puts them into lanes of vector registers,
+// cached ones take 166.0, 179 and 135.8, cold ones 218.2, 390 and 175.2, and those of 600 requests, V = 128256, 440.5, not 437.8.)  Nor in a fill that masks nothing: a
+// greedy step of the 256 21.55 / 21.43.  (Every wavefront deciding for itself by the tag, without the barrier
 // behind the lookup, and lanes that take the bits they mask from memory instead of LDS: 1 to 10 % slower with logits of 20 MB and more.)
 struct RowArgs {
     unsigned long long *tags, *class_tags;
@@ -1185,7 +1190,14 @@ rows_kernel(WG_EARLY_ARGS)
     Tickets ticket{kNoTicket, kNoTicket, false};
     uint4 ahead{0u, 0u, 0u, 0u};                      // the cached row's piece of this thread, should there be one
     constexpr bool kSpan = kMode == 1 || kMode == 3;
+    constexpr bool kHeld = kMode == 3;
     RowArgs args;
+    // (read again, which the compiler does not see: it would keep them in registers meanwhile)
+    auto again = [&]() {
+        Late *l = &late;
+        asm volatile("" : "+s"(l));
+        return RowArgs(*l);
+    };
     if (kWhole) {
         const uint32_t wave = of_first(tid >> 6);
         uint32_t sid = 0, aux = 0, t = 0;
@@ -1214,8 +1226,7 @@ rows_kernel(WG_EARLY_ARGS)
         // (behind the advance's first loads, or while the first wavefront is busy)
         auto read_args = [&]() {
             args = RowArgs(late);
-            hold(args.tags, args.class_tags, args.arena, args.cap_rows, args.row_stride, args.epoch, args.lmax, args.bitmask, args.W, args.rows);
-            if (kSpan) hold(args.logits, args.logits_stride);
+            if (kHeld) hold(args.tags, args.class_tags, args.arena, args.cap_rows, args.row_stride, args.epoch, args.lmax, args.bitmask, args.W, args.rows, args.logits, args.logits_stride);
         };
         if (wave == 0u) {
             if (tokens) {
@@ -1278,13 +1289,11 @@ rows_kernel(WG_EARLY_ARGS)
             __syncthreads();
         }
         make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b, kWhole && p0 == 0u);
-        // (read again, which the compiler does not see: it would keep them in registers meanwhile)
-        Late *again = &late;
-        asm volatile("" : "+s"(again));
-        args = RowArgs(*again);
+        args = again();
         ahead = uint4{0u, 0u, 0u, 0u};
     }
     if (!kWhole) args = RowArgs(late);
+    else if (kMode == 1) args = again();
     // out: to the cache, the caller's bitmask, and LDS for the masking
     const bool copied = ref < args.cap_rows;
     const uint32_t *row_in = args.arena + (size_t)(copied ? ref : 0u) * args.row_stride + w_lo;
