@@ -25,6 +25,16 @@ def make_gpu(w, restart=True, share=False):
     return v, h
 
 
+def fill_kernels(h, call):
+    """How many kernels the one fill in `call` was: two, where a lookup is timed by itself."""
+    h.profile_enable()
+    call()
+    p = h.profile_read()
+    h.profile_enable(False)
+    assert p["fill_calls"] == 1 and p["build_ms"] > 0.0
+    return 2 if p["lookup_ms"] > 0.0 else 1
+
+
 def dev_states(st):
     import torch
     return torch.from_numpy(np.ascontiguousarray(st, dtype=np.uint32).view(np.int32).copy()).cuda()
