@@ -1289,18 +1289,21 @@ rows_kernel(WG_EARLY_ARGS)
             __syncthreads();
         }
         make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b, kWhole && p0 == 0u);
-        args = again();
+        if (kWhole) args = again();
         ahead = uint4{0u, 0u, 0u, 0u};
     }
-    if (!kWhole) args = RowArgs(late);
-    else if (kMode == 1) args = again();
+    if (!kWhole) {
+        // (each where it is needed: asked for together, the cached rows of 257 to 1,024 requests took 0.3 % longer)
+        args.arena = Cc.arena; args.cap_rows = Cc.cap_rows; args.row_stride = Cc.row_stride;
+        args.bitmask = late.bitmask; args.W = Vc.W;
+    } else if (kMode == 1) args = again();
     // out: to the cache, the caller's bitmask, and LDS for the masking
     const bool copied = ref < args.cap_rows;
     const uint32_t *row_in = args.arena + (size_t)(copied ? ref : 0u) * args.row_stride + w_lo;
     const uint4 *src = reinterpret_cast<const uint4 *>(row_in);
     uint4 *kept = reinterpret_cast<uint4 *>(args.arena + (size_t)slot * args.row_stride + w_lo);
     uint32_t *dst = args.bitmask + (size_t)b * args.W + w_lo;
-    Elem *logits = static_cast<Elem *>(args.logits) + (int64_t)b * args.logits_stride;
+    Elem *logits = kWhole ? static_cast<Elem *>(args.logits) + (int64_t)b * args.logits_stride : nullptr;
     const bool aligned = reinterpret_cast<uintptr_t>(dst) % 16u == 0u;
     for (uint32_t q = tid; q < n4; q += kRowThreads) {
         uint4 x{0u, 0u, 0u, 0u};
@@ -1320,6 +1323,7 @@ rows_kernel(WG_EARLY_ARGS)
     if (kWhole) close_call(Cc, ticket, b, args.rows, sh);
     if (kMode || !aligned) __syncthreads();
     if (!aligned) for (uint32_t w = tid; w < n_words; w += kRowThreads) dst[w] = row[w];
+    if (!kWhole) logits = static_cast<Elem *>(late.logits) + (int64_t)b * late.logits_stride;
     if (kSpan) mask_span<Elem, kMode == 3>(logits, tok_lo, tok_hi, row);
     if (kMode == 2) mask_lines<Elem, sizeof(Elem) == 4 ? 8u : 5u>(logits, tok_lo, tok_hi, row);
     if (!kWhole && blockIdx.x == 0 && b == 0 && tid == 0) {
