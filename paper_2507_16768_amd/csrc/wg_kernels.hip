@@ -1149,11 +1149,12 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
 // The late arguments that the way of a cached row needs, asked for before it needs them: behind the advance's first loads, or while
 // the other wavefronts wait for the first.  Read where they were needed they were eight waits of 100 cycles in turn.  Held in registers from there to the
 // end (kHeld) where the logits are masked through the L2: eight cached steps, outlines, V = 128256, B = 64, us, so / not, 51.4 / 51.5, cold ones of 96 mixed
-// requests on V = 100003 111.7 / 112.3.  Not where more logits are masked, which are asked for again behind the lookup: the kernel has too few
-// scalar registers to hold what its end needs through the lookup.  Held / asked for again, V = 151936, B = 256, mixed, cached 169.7 / 167.5, cold 216.9 / 216.4,
-// random trees 184 / 182.8, outlines 135.3 / 134.9, cold 175 / 173.1.  (Neither held nor asked for again, by which the compiler puts them into lanes of vector registers,
-// cached ones take 166.0, 179 and 135.8, cold ones 218.2, 390 and 175.2, and those of 600 requests, V = 128256, 440.5, not 437.8.)  Nor in a fill that masks nothing: a
-// greedy step of the 256 21.55 / 21.43.  (Every wavefront deciding for itself by the tag, without the barrier
+// requests on V = 100003 111.7 / 112.3.  Else asked for again behind the lookup, when their lines are near: the kernel has too few scalar registers to hold
+// what its end needs through the lookup, and puts other values into lanes of vector registers on the way of every wavefront.  Held / asked for again,
+// V = 151936, B = 256, eight steps, mixed, cached 169.7 / 167.5, cold 216.9 / 216.4, random trees 183.6 / 182.4, outlines 135.2 / 134.7, cold 174.5 / 173.1; masks
+// alone behind a sampled token, outlines and mixed, copied 7.21 / 7.13, 7.28 / 7.10, made 15.7 / 14.5, 16.9 / 15.8; up to 16 requests, masks alone 0.99 to 1.01 of it, logits of
+// up to 1 MiB 1.00 to 1.01.  (Neither held nor asked for again, by which the compiler has them in lanes, eight cached steps took 166.0, 179 and 135.8, but
+// cold ones 218.2, and 175.2, and those of 600 requests, V = 128256, 440.5, not 437.8.)  (Every wavefront deciding for itself by the tag, without the barrier
 // behind the lookup, and lanes that take the bits they mask from memory instead of LDS: 1 to 10 % slower with logits of 20 MB and more.)
 struct RowArgs {
     unsigned long long *tags, *class_tags;
@@ -1166,6 +1167,13 @@ struct RowArgs {
         : tags(late.Cc.tags), class_tags(late.Cc.class_tags), arena(late.Cc.arena), bitmask(late.bitmask), logits(late.logits), logits_stride(late.logits_stride),
           cap_rows(late.Cc.cap_rows), row_stride(late.Cc.row_stride), epoch(late.Cc.epoch), lmax(late.T.lmax), W(late.Vc.W), rows(late.rows) {}
 };
+// (which the compiler does not see to be the same: it would keep them in registers meanwhile)
+__device__ __forceinline__ RowArgs read_again(Late &late)
+{
+    Late *l = &late;
+    asm volatile("" : "+s"(l));
+    return RowArgs(*l);
+}
 
 // kMode 0: masks only; 1: -inf into the logits as well; 2: the same, whole lines (see mask_lines); 3: as 1, the stores
 // through the L2.
@@ -1192,12 +1200,6 @@ rows_kernel(WG_EARLY_ARGS)
     constexpr bool kSpan = kMode == 1 || kMode == 3;
     constexpr bool kHeld = kMode == 3;
     RowArgs args;
-    // (read again, which the compiler does not see: it would keep them in registers meanwhile)
-    auto again = [&]() {
-        Late *l = &late;
-        asm volatile("" : "+s"(l));
-        return RowArgs(*l);
-    };
     if (kWhole) {
         const uint32_t wave = of_first(tid >> 6);
         uint32_t sid = 0, aux = 0, t = 0;
@@ -1227,6 +1229,7 @@ rows_kernel(WG_EARLY_ARGS)
         auto read_args = [&]() {
             args = RowArgs(late);
             if (kHeld) hold(args.tags, args.class_tags, args.arena, args.cap_rows, args.row_stride, args.epoch, args.lmax, args.bitmask, args.W, args.rows, args.logits, args.logits_stride);
+            else asm volatile("" :: "s"(args.tags), "s"(args.arena), "s"(args.bitmask), "s"(args.lmax));
         };
         if (wave == 0u) {
             if (tokens) {
@@ -1289,14 +1292,14 @@ rows_kernel(WG_EARLY_ARGS)
             __syncthreads();
         }
         make_row(T, Vc, Cc, sh, me, ha, hb, p0, span, w_lo, w_hi, row, reinterpret_cast<uint32_t *>(early4), b, kWhole && p0 == 0u);
-        if (kWhole) args = again();
+        if (kWhole) args = read_again(late);
         ahead = uint4{0u, 0u, 0u, 0u};
     }
     if (!kWhole) {
         // (each where it is needed: asked for together, the cached rows of 257 to 1,024 requests took 0.3 % longer)
         args.arena = Cc.arena; args.cap_rows = Cc.cap_rows; args.row_stride = Cc.row_stride;
         args.bitmask = late.bitmask; args.W = Vc.W;
-    } else if (kMode == 1) args = again();
+    } else if (!kHeld) args = read_again(late);
     // out: to the cache, the caller's bitmask, and LDS for the masking
     const bool copied = ref < args.cap_rows;
     const uint32_t *row_in = args.arena + (size_t)(copied ? ref : 0u) * args.row_stride + w_lo;
