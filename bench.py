@@ -37,10 +37,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # without the advance.  They describe the kernels whose source hashes to
 # TRAFFIC_SOURCE_SHA256; with any other kernel source, or any other workload, the field is reported as null.
 TRAFFIC_BYTES = {
-    4: {"rows": 18.68e6, "apply": 56.56e6, "advance": 0.29e6},
-    5: {"lookup": 0.64e6, "rows": 45.75e6, "apply": 535.00e6, "advance": 0.72e6},
+    4: {"rows": 18.72e6, "apply": 56.56e6, "advance": 0.41e6},
+    5: {"lookup": 0.66e6, "rows": 45.70e6, "apply": 535.01e6, "advance": 0.78e6},
 }
-TRAFFIC_SOURCE_SHA256 = "e98395aeddc3a65fb09630b783fd30d17469edb1b8b0cdb3934dc2ddc940a7f7"
+TRAFFIC_SOURCE_SHA256 = "9d5fc81f7c5b1ba0d3d7df4ec7c02a11f42945fdabf08d2001150f9c7b61057b"
 WINDOW_START = 64              # first timed step of the trajectory (the warm-up steps come right before it)
 N_PASSES = 5                   # timed passes per figure; the median is reported
 RAMP_SECONDS = 0.08            # GPU work done before timing, for the clocks to settle

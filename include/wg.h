@@ -212,7 +212,7 @@ uint32_t wg_num_instances(wg_handle_t h);
  * smaller cache -- rows are handed out in order of first use (rows in use stay where they are); once
  * all are taken, further keys are still served correctly but rebuilt on every call that needs them
  * (wg_cache_stats.uncached_builds counts them) until wg_cache_clear or a resize.  A fill of at most a
- * request per compute unit (and some larger ones) is one kernel in the first case and two in the second, 2 to 4 us more a step;
+ * request per compute unit (and some larger ones: wg_fill_masks, wg_decode_step) is one kernel in the first case and two in the second, 2 to 4 us more a step;
  * an engine that expects additions keeps the first by making room for their keys here, at set-up.
  * Synchronises the device and clears the cache. */
 int wg_cache_resize(wg_handle_t h, uint32_t rows);
@@ -237,8 +237,9 @@ uint32_t wg_mask_words(wg_handle_t h);      /* W = ceil(V/32) */
  * wg_fill_masks: d_bitmask[b][0..W) <- mask of d_states[b] (mask creation with the global
  * cache of the section "Mask Generation and Global Caching"): cached rows are copied, missing
  * ones are made, and kept once per distinct key.  An ERROR or out-of-range state gets an all-zero
- * row.  One kernel for up to a request per compute unit (fewer from about 350,000 tokens on, up to three per unit
- * on rows of at most 16,384 tokens) while the cache has a row for every key, else two (a workgroup for every 1/1 to 1/32 of a row). */
+ * row.  One kernel for up to a request per compute unit, and up to three per unit on rows of at most 16,384 tokens, as long as
+ * all of its workgroups (one for every 1/1 to 1/32 of a row) are resident together -- which they are not from about 350,000
+ * tokens on, nor, for instance, above two requests per unit on 16,384 -- and the cache has a row for every key; else two. */
 int wg_fill_masks(wg_handle_t h, const wg_state_t *d_states, uint32_t B, uint32_t *d_bitmask,
                   void *stream);
 
@@ -332,7 +333,10 @@ int wg_advance_fill_masks(wg_handle_t h, wg_state_t *d_states, const int32_t *d_
  * d_logits ([B][V] with V of the handle's vocabulary, layout as in wg_apply_mask) as by
  * wg_apply_mask.  Same results as wg_advance + wg_fill_masks + wg_apply_mask in one or two kernel
  * launches instead of three or four: the advance rides in the kernel that does the lookup and the
- * masking in the kernel that makes the rows. */
+ * masking in the kernel that makes the rows.  One launch, while the cache has a row for every key and the
+ * logits are not masked by whole lines (up to 208 MiB of bf16, 320 MiB of fp32), for up to a request per compute
+ * unit, for up to three per unit on rows of at most 16,384 tokens as long as they make at most seven workgroups
+ * per unit, and for 1.5 to 4 per unit (1,024 requests at most) on rows of 100,000 tokens and more. */
 int wg_decode_step(wg_handle_t h, wg_state_t *d_states, const int32_t *d_tokens, uint32_t B,
                    uint32_t *d_bitmask, void *d_logits, wg_dtype_t dtype, int64_t row_stride_elems,
                    void *stream);

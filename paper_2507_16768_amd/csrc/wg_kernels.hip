@@ -270,8 +270,8 @@ __device__ __forceinline__ Ahead look_ahead(const TableView &T, const WalkArgs &
 // for any other.  All bytes that a state might consume are compared or looked up together, a byte per lane.  (A thread
 // per request, eight bytes at a time, took two trips for every eight bytes of free text, and the longest walk of a
 // batch decides: of 256 mixed requests, V = 151936, the last had its state 8.9 us after the kernel's beginning.  With a trip for
-// each state's bytes and the descriptors behind it 4.2.  Times with that / now, us: wg_advance, mixed, V = 151936, B = 256 4.88 / 3.84, outlines,
-// V = 128256, B = 64 3.84 / 2.68; eight cached steps of them 171.2 / 165.8 and 54.5 / 53.7.  The codes cost 64 bytes a state; asked for
+// each state's bytes and the descriptors behind it 4.2.  Times with that / now, us: wg_advance in a decode loop, mixed, V = 151936, B = 256 4.88 / 3.84, outlines,
+// V = 128256, B = 64 3.84 / 2.68 (20 calls in a row, which hide most of it, 3.06 / 2.98 and 2.93 / 2.85); eight cached steps of them 171.2 / 165.8 and 54.5 / 53.7.  The codes cost 64 bytes a state; asked for
 // by the number of the class table they would be a trip behind the descriptor.)
 // a: what lies ahead of sid, at the call; d: the descriptor of sid, at the call and after it.  byte: the lane's.
 __device__ __forceinline__ bool walk_wide(const TableView &T, const VocabView &Vc, const WalkArgs &w, uint32_t &sid, uint32_t &aux, Ahead a, StateDesc &d,
@@ -365,11 +365,12 @@ __device__ __forceinline__ void advance_one(const TableView &T, const VocabView 
     }
 }
 
-// One request to a workgroup up to two on a compute unit, four above: with one / with four, mixed, us, B = 64 3.17 / 3.32, 256
-// 3.20 / 3.38, 512 3.40 / 3.48, 1024 3.49 / 3.62, 8192 5.58 / 5.22.  The first request's state and token come in one wait with the arguments that follow the
-// early ones (one after the other, a copy of the states and wg_advance, B = 1 4.2, now 4.0, 64 4.4, 4.3).  Batches of 16,384 and 60,000 took 6.6 to
-// 7.5 and 19 to 20 us, a thread each with eight bytes at a time 6.1 to 8.6 and 13 to 19.  These are times before look_ahead; with it, and a
-// copy of the states, 16,384 9.2 to 9.5 -> 8.6 to 8.7, 60,000 22.6 to 22.8 -> 19.9 to 20.5.
+// One request to a workgroup up to two on a compute unit, four above: with one / with four, V = 151936, us of 20 calls in a row, B = 64 mixed 2.89 / 2.98,
+// random trees 2.86 / 3.00, 256 2.98 / 3.18, 2.97 / 3.08, 512 3.06 / 3.15, 3.02 / 3.08, 1024 3.21 / 3.33, 3.10 / 3.17, 2048 3.53 / 3.47, 3.47 / 3.32, 4096 4.30 / 3.89, 4.25 / 3.69,
+// 8192 5.84 / 4.90, 5.87 / 4.85, 60,000 18.2 / 18.4, 18.0 / 19.4: the sides change between 1,024 and 2,048 and differ by 2 to 4 % from 513 on to there.  The first request's
+// state and token come in one wait with the arguments that follow the early ones (one after the other, B = 1 4.2 us with a copy of the states, in one 4.0, 64 4.4, 4.3).
+// Before look_ahead 256 took 3.06, 8192 5.28, 16,384 7.8 (now 7.2), 60,000 21.0; a thread each with eight bytes at a time took 6.1 to 8.6 us at 16,384 and 13 to 19 at
+// 60,000.
 constexpr uint32_t kAdvanceBlocks = 1u << 20;
 template <uint32_t kWaves>
 __global__ void __launch_bounds__(64 * kWaves)
@@ -744,10 +745,13 @@ __device__ __forceinline__ void mask_lines(Elem *logits, uint32_t lo, uint32_t h
 // stretches of kRowBatch * 64; a wavefront filters its entries by their neighbouring byte, queues
 // what is left in LDS and decides them 64 at a time, so that the walks run on full wavefronts.
 //
-// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 7.2 us, the launch and the
-// chain state -> descriptor -> tag -> row of four trips to memory; made rows 15.1 us for 19 MB, the same chain and
-// then plan -> directory -> entries -> chunks -> walk, with 2.8 M instructions of wavefronts (5 us of the chip's
-// vector units) in it.  B = 1024 and 141 class tables a call, two kernels: copied rows 5 + 10.0 us, made rows 5 + 57,
+// What bounds it (V = 151936, masks only).  B = 256, one kernel: copied rows 6.9 us, the launch and the
+// chain state -> descriptor -> tag -> row of four trips to memory; made rows 14.8 us for 19 MB, the same chain and
+// then plan -> directory -> entries -> chunks -> walk, with 2.9 M instructions of wavefronts (5 us of the chip's
+// vector units) in it.  The first wavefront is what the others wait for: stamps of a cold fill, cycles from a workgroup's beginning, median: the state and
+// its key 3,700, looked up 6,800, directories 10,800, entries 13,100, filtered 15,200, walked and at the barrier 19,300, row out 21,100; the other three are at the barrier
+// at 11,200 (128 JSON requests on 128,256 tokens 18,200 and 8,400 to 9,900, 96 mixed ones on 100,003 18,200 and 9,300 to 10,600; the first share of a row, whose last wavefront
+// claims, 21,100 and 11,200 to 13,300).  B = 1024 and 141 class tables a call, two kernels: copied rows 5 + 9.8 us, made rows 5 + 57,
 // with 15 M vector instructions of wavefronts (25 us).
 constexpr uint32_t kRowThreads = 256;
 constexpr uint32_t kRowWaves = kRowThreads / 64u;
@@ -1154,7 +1158,7 @@ __device__ __forceinline__ void close_fill(const CacheView &Cc, uint32_t B, uint
 // V = 151936, B = 256, eight steps, mixed, cached 169.7 / 167.5, cold 216.9 / 216.4, random trees 183.6 / 182.4, outlines 135.2 / 134.7, cold 174.5 / 173.1; masks
 // alone behind a sampled token, outlines and mixed, copied 7.21 / 7.13, 7.28 / 7.10, made 15.7 / 14.5, 16.9 / 15.8; up to 16 requests, masks alone 0.99 to 1.01 of it, logits of
 // up to 1 MiB 1.00 to 1.01.  (Neither held nor asked for again, by which the compiler has them in lanes, eight cached steps took 166.0, 179 and 135.8, but
-// cold ones 218.2, and 175.2, and those of 600 requests, V = 128256, 440.5, not 437.8.)  (Every wavefront deciding for itself by the tag, without the barrier
+// cold ones 218.2 and 175.2, and those of 600 requests, V = 128256, 440.5, not 437.8.)  (Every wavefront deciding for itself by the tag, without the barrier
 // behind the lookup, and lanes that take the bits they mask from memory instead of LDS: 1 to 10 % slower with logits of 20 MB and more.)
 struct RowArgs {
     unsigned long long *tags, *class_tags;
@@ -1642,30 +1646,32 @@ FillPlan plan_fill(const DeviceVocab &Vc, const DeviceCache &Cc, uint32_t B, boo
     p.parts = row_parts(Vc.V, B, n_cu);
     // One kernel while its workgroups are resident together: what every workgroup of a row repeats of the lookup
     // is then paid once, and a launch with its lookup is saved.  us a call with two kernels / with one, outlines, mixed, random
-    // trees, wg_fill_masks copied and made, then wg_decode_step: V = 151936, B = 16 5.1 4.8 4.8 / 4.6 4.6 4.6, 11.5 11.7 14.2 / 9.3 9.3
-    // 11.5, 6.2 6.1 6.1 / 5.5 5.6 5.6, 13.2 13.2 15.7 / 10.5 10.6 12.6; B = 256 6.4 6.4 6.4 / 6.2 6.2 6.1, 15.9 18.2 31.4 / 13.0 15.0 30.3, 16.4
-    // 17.9 20.8 / 14.3 15.7 18.7, 23.7 27.5 39.3 / 20.5 22.7 37.7; V = 65536, B = 256 9.8 10.3 11.7 / 8.5 9.1 10.3 and 18.0 20.2 28.5 /
-    // 15.4 15.8 25.8 a step.  Above, workgroups that start late repeat it when the others are done: copied rows, masks alone,
-    // V = 151936, B = 288 6.6 / 7.4, V = 65536, B = 512 7.0 / 8.7, while most made ones and steps
-    // gain, up to a fifth (outlines, V = 65536, B = 512 lose: made 22.4 / 23.6, a cached step 14.9 / 15.6).  So it is with
+    // trees, wg_fill_masks copied and made, then wg_decode_step: V = 151936, B = 16 4.7 4.9 4.9 / 4.3 4.3 4.3, 9.9 10.8 13.6 / 7.9 8.5
+    // 10.7, 6.0 6.1 6.1 / 5.2 5.1 5.1, 11.4 12.4 15.0 / 9.2 10.1 12.3; B = 256 6.9 6.9 6.8 / 6.6 6.7 6.7, 17.9 17.8 37.9 / 13.8 14.1 35.0, 17.1
+    // 18.3 20.7 / 14.7 16.1 18.1, 27.2 27.6 45.5 / 21.8 22.0 41.7; V = 65536, B = 256 9.7 10.4 11.9 / 8.5 8.8 10.6 and 18.3 19.6 32.3 /
+    // 14.3 15.4 29.3 a step.  Above, workgroups that start late repeat it when the others are done: copied rows, masks alone,
+    // V = 151936, B = 288 7.1 / 7.8, V = 65536, B = 512 7.5 / 9.2, while made ones and steps
+    // gain, up to a fifth.  So it is with
     // fewer rows whose shares take so much LDS that fewer workgroups are resident, from V = 350,000 on (masks only, outlines /
-    // mixed / random trees, one over two kernels, made and copied: V = 340001, B = 256, 8 to a unit, 0.83 0.84 0.94 and 0.95
-    // 0.91 0.95; 350000, B = 256, 7 to a unit, 0.95 0.99 1.02 and 1.08 1.03 1.07; 500000, B = 224, 6 to a unit, 0.99 0.98 1.00
-    // and 1.11 1.03 1.10, B = 192 0.90 0.91 0.99 and 0.96 0.94 0.95).  With logits to mask behind them the workgroups
-    // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 0.91 0.96
-    // 0.95 and 0.95 0.97 0.97); whole lines are masked behind a lookup of its own.
+    // mixed / random trees, one over two kernels, made and copied: V = 340001, B = 256, 8 to a unit, 0.80 0.85 0.95 and 0.93
+    // 0.94 0.97; 350000, B = 256, 7 to a unit, 0.88 1.00 1.00 and 1.04 1.06 1.10; 500000, B = 224, 6 to a unit, 0.94 0.99 0.98
+    // and 1.03 1.01 1.09).  With logits to mask behind them the workgroups
+    // that are late find memory less busy, and one kernel gains up to where lines begin (V = 400000, B = 256 copied 0.94 0.97
+    // 0.97, made 0.89 0.93 0.96); whole lines are masked behind a lookup of its own.
     //
     // Above a request per unit one kernel gains where all of its workgroups are resident with a few places left (rows are in four shares or
     // fewer there), and where rows are so long, and so many, that masking them outlasts what late workgroups repeat.  Time with one kernel over two,
-    // outlines, JSON, mixed, random trees, cached and then made, bf16, a step: V = 9000 B = 264 0.69 0.72 0.71 0.75, 0.84 0.79 0.74 0.81, 700 0.78 0.81
+    // outlines, JSON, mixed, random trees, cached and then made, bf16, a step of a decode loop (profiles/dispatch_rules.txt: single steps without a sampled token): V = 9000 B = 264 0.69 0.72 0.71 0.75, 0.84 0.79 0.74 0.81, 700 0.78 0.81
     // 0.81 0.79, 0.97 0.87 0.79 0.87; 14000 350 0.81 0.81 0.82 0.77, 0.82 0.75 0.73 0.86, 440 0.82 0.82 0.82 0.80, 0.88 0.80 0.73 0.87; 101000 560 0.99 0.99
     // 0.96 0.94, 0.94 0.98 0.94 0.99; 128256 512 0.95 0.95 0.93 0.94, 0.92 0.90 0.91 0.95, 800 0.95 0.96 0.96 0.97, 0.90 0.86 0.91 0.96; 151936 640 0.95 0.95 0.96
     // 0.97, 0.90 0.88 0.92 0.96; fp32, 101000 650 0.94 0.95 0.96 0.97, 0.91 0.87 0.92 0.97.  Masks alone, with the two calls behind them: 12000 272 0.67
     // 0.64 0.67 0.68, 0.88 0.83 0.82 0.86, 512 0.74 0.76 0.75 0.76, 0.91 0.87 0.83 0.87; long rows only gain where they are made (65536 272 1.02 1.02 1.02
     // 1.02, 0.98 1.03 0.94 0.94).  On the other sides of the lines, steps: 9000 880 (more than 7 workgroups to a unit) made outlines 1.08; 14000 500 1.03;
     // 65536 384 made outlines and JSON 1.05; 80000 500 cached outlines 1.06, made JSON 1.09; 96000 350 made JSON 1.02, 101000 300 1.14; whole lines, 151936 1000 0.93 to
-    // 0.98, but made random trees 1.02.  Rows of 16,385 to 24,576 tokens gain as well (24000 350 0.82 0.81 0.80 0.79, 0.86 0.84 0.77 0.87) and stay in two
-    // kernels: tests/test_gpu_calls.py counts the kernels of 300 requests on 20,000 tokens.
+    // 0.98, but made random trees 1.02.  Masks alone that are not resident together: 14000 600 copied 1.12 to 1.14, 16384 768 1.19 to 1.20.
+    // The lower line of V is not where the gain ends: rows of 16,385 to 24,575 tokens are resident together up to the same batches and gain as much (steps, 20011 350 0.89 0.89
+    // 0.87 0.82, 0.74 0.74 0.77 0.86, 24000 448 0.87 0.87 0.85 0.86, 0.77 0.79 0.80 0.94; masks alone 0.93 to 0.96, 0.71 to 0.91).  They have been two kernels, each
+    // timed by itself (wg_profile_read), and still are.
     const bool together = B * p.parts <= resident_rows(Vc, p.parts) * n_cu, few = B <= n_cu, short_rows = B <= 3u * n_cu && Vc.V <= 16384u,
                long_rows = 2u * B >= 3u * n_cu && Vc.V >= 100000u;
     p.one_kernel = Cc.direct && B <= kOneKernelRows &&
