@@ -40,7 +40,7 @@ def _tokens():
 @pytest.mark.parametrize("restart", [False, True])
 def test_tokens_as_long_as_a_wavefront_and_longer(torch_cuda, restart):
     """Every state and budget with every token: through wg_advance (a request and four requests to a workgroup) and through
-    the fill that advances in its one kernel, above a request per compute unit too, and in a lookup kernel, with a row for every key and without."""
+    the fill that advances in its one kernel and behind a lookup kernel."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     toks = _tokens()
@@ -61,16 +61,14 @@ def test_tokens_as_long_as_a_wavefront_and_longer(torch_cuda, restart):
     assert (H.host_states(got) == want).all()
     pick = np.random.default_rng(5).permutation(len(rep))
     pick = np.concatenate([pick[want[pick, 0] != O.SID_ERROR][:900], pick[:150]])
-    keys = h.cache_stats()["keys"]
-    for B, rows, kernels in ((256, keys, 1), (500, keys, 1), (300, keys, 1), (1000, keys, 2), (256, keys // 2, 2), (300, keys // 2, 2)):
-        h.cache_resize(rows)
+    for B in (256, 500, 300):
         for k in range(0, len(pick) - B + 1, B):
             p = pick[k:k + B]
             a, b = H.dev_states(rep[p]), H.dev_states(rep[p])
             mask = torch.empty((B, h.W), dtype=torch.int32, device="cuda")
             t = torch.from_numpy(tk[p]).cuda()
             h.advance(a, t)
-            assert H.fill_kernels(h, lambda: h.advance_fill_masks(b, t, mask)) == kernels, (B, rows)
+            h.advance_fill_masks(b, t, mask)
             assert (H.host_states(a) == want[p]).all() and torch.equal(a, b), (B, k)
             assert (H.host_mask(mask) == o.fill_masks(want[p])).all(), (B, k)
 
@@ -79,8 +77,7 @@ def test_tokens_as_long_as_a_wavefront_and_longer(torch_cuda, restart):
 def test_walks_past_what_lies_ahead_of_their_state(torch_cuda, n):
     """A walk has eight states and 64 literal bytes from its state on at hand: runs that end on either side of both, in front of
     checkpoints, of conditions that lead back, over a body and past one, and of another run; in instances compiled first, added to the
-    tables, and added with more than the tables had room for; through wg_advance and through the fill that advances, in its one kernel and in a
-    lookup kernel."""
+    tables, and added with more than the tables had room for."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     run = _RUN[:n].decode()
@@ -110,14 +107,11 @@ def test_walks_past_what_lies_ahead_of_their_state(torch_cuda, n):
     assert (H.host_states(got) == want).all()
     pick = np.random.default_rng(n).permutation(len(rep))
     pick = np.concatenate([pick[want[pick, 0] != O.SID_ERROR][:200], pick[:100]])
-    keys = h.cache_stats()["keys"]
-    for rows, kernels in ((keys, 1), (keys - 1, 2)):                   # in one kernel, and in a lookup kernel
-        h.cache_resize(rows)
-        for p in (pick[:200], pick):
-            b, t = H.dev_states(rep[p]), torch.from_numpy(tk[p]).cuda()
-            mask = torch.empty((len(p), h.W), dtype=torch.int32, device="cuda")
-            assert H.fill_kernels(h, lambda: h.advance_fill_masks(b, t, mask)) == kernels
-            assert (H.host_states(b) == want[p]).all() and (H.host_mask(mask) == o.fill_masks(want[p])).all()
+    for p in (pick[:200], pick):                                       # in one kernel, and behind a lookup kernel
+        b = H.dev_states(rep[p])
+        mask = torch.empty((len(p), h.W), dtype=torch.int32, device="cuda")
+        h.advance_fill_masks(b, torch.from_numpy(tk[p]).cuda(), mask)
+        assert (H.host_states(b) == want[p]).all() and (H.host_mask(mask) == o.fill_masks(want[p])).all()
 
 
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33, 255, 256])
