@@ -148,10 +148,10 @@ def test_start_states_given_out_are_the_callers(torch_cuda):
     assert all((a == b).all() for a, b in taken)
 
 
-@pytest.mark.parametrize("states", [1, 32000, 32409, 32500, 49153, 98304, 120007])
+@pytest.mark.parametrize("states", [1, 10790, 10820, 16385, 32768, 50007, 180007])
 def test_additions_either_side_of_what_one_launch_uploads(torch_cuda, states):
-    """3 MiB of tables, 97 bytes a state, go to the device in one launch, more in halves of that: every state behind an addition of either
-    kind takes tokens as the oracle's does, and so do those before it and those of an addition behind it."""
+    """1 MiB of tables, 97 bytes a state, goes to the device in one launch, more in halves of that: every state behind an addition of either kind takes tokens as the oracle's does, and so do those before it and those of an addition
+    behind it, and all of them compiled at once."""
     torch = torch_cuda
     import paper_2507_16768_amd as wg
     from oracle import oracle as O
@@ -165,20 +165,25 @@ def test_additions_either_side_of_what_one_launch_uploads(torch_cuda, states):
     base, last = ["Sequence(%s, %s)" % (block(0), write(3))], ["Sequence(%s, %s)" % (block(1), write(5))]
     vocab = from_tokens([b"", b"a", b"b", b"<", b"aa", b"ab", b"ba", b"bb", b"a<", b"b<a", b"abab", b"c"], eos_id=0)
     o = O.Oracle(base + texts + last, None, O.OracleVocab(vocab.bytes, vocab.offsets, vocab.eos_id), restart=True)
-    h = wg.Handle(base, None, wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id), flags=wg.EOS_RESTART)
+    v = wg.Vocab(vocab.bytes, vocab.offsets, vocab.eos_id)
+    h = wg.Handle(base, None, v, flags=wg.EOS_RESTART)
     own = h.num_states
     h.add_instances(texts, None)
     assert h.num_states - own == states
     h.add_instances(last, None)
-    assert h.num_states == o.num_states
+    at_once = wg.Handle(base + texts + last, None, v, flags=wg.EOS_RESTART)
+    assert h.num_states == at_once.num_states == o.num_states
     st = np.zeros((h.num_states, 2), dtype=np.uint32)
     st[:, 0] = np.arange(h.num_states)
     for _ in range(4):
         tok = rng.integers(0, vocab.V, len(st)).astype(np.int32)
-        got = H.dev_states(st)
-        h.advance(got, torch.from_numpy(tok).cuda())
-        assert (H.host_states(got) == o.advance(st, tok)).all()
+        want = o.advance(st, tok)
+        for x in (h, at_once):
+            got = H.dev_states(st)
+            x.advance(got, torch.from_numpy(tok).cuda())
+            assert (H.host_states(got) == want).all()
     some = rng.permutation(len(st))[:200]
     mask = torch.empty((len(some), h.W), dtype=torch.int32, device="cuda")
-    h.fill_masks(H.dev_states(st[some]), mask)
-    assert (H.host_mask(mask) == o.fill_masks(st[some])).all()
+    for x in (h, at_once):
+        x.fill_masks(H.dev_states(st[some]), mask)
+        assert (H.host_mask(mask) == o.fill_masks(st[some])).all()
